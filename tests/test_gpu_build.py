@@ -206,3 +206,29 @@ def test_ivf_encode_guards_ids_and_cells(Q, O):
     want[5] = 0
     want[9] = 0
     assert np.array_equal(codes, want)
+
+
+# ------------------------------------------------------------------ k-means
+
+@pytest.mark.parametrize("n,d,m,ksub", [(1, 4, 4, 16), (700, 6, 2, 16), (8191, 8, 4, 16), (8192, 8, 4, 16), (8193, 130, 1, 16),
+                                        (20_001, 24, 8, 64), (17_000, 96, 8, 256), (9_000, 130, 2, 16)])
+def test_pq_train_means_are_row_order_float64_sums(Q, O, n, d, m, ksub):
+    """One update from known labels, bit for bit: sums in row order in float64, one division, one rounding; a
+    centroid that owns nothing keeps its value.  Sizes around a round of labels (8192), a stage of rows and a
+    workgroup's 64 components; one centroid owns most of the rows."""
+    rng = np.random.default_rng(n + d)
+    x = rng.uniform(0, 255, size=(n, d)).astype(np.float32)
+    x[n // 3:] = (x[n // 3:n // 3 + 1] + rng.normal(scale=3, size=(n - n // 3, d))).astype(np.float32)
+    rows = np.minimum(rng.permutation(max(n, ksub))[:ksub], n - 1).astype(np.int64)   # n < ksub: repeated rows, centroids that own nothing
+    dsub = d // m
+    start = np.stack([x[rows, j * dsub:(j + 1) * dsub] for j in range(m)])
+    want = start.copy()
+    labels = O.pq_encode(x, start)
+    for j in range(m):
+        for i in range(ksub):
+            own = np.flatnonzero(labels[:, j] == i)
+            if len(own):
+                sums = np.cumsum(x[own, j * dsub:(j + 1) * dsub].astype(np.float64), axis=0)[-1]   # cumsum: strictly in order
+                want[j, i] = (sums / len(own)).astype(np.float32)
+    got = Q.qadc_pq_train(to_gpu(x), m, ksub, to_gpu(rows), 1).cpu().numpy()
+    assert np.array_equal(got, want)
