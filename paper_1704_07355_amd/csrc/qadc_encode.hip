@@ -3,7 +3,7 @@
 // standard code layout; for an inverted index (Section 2.2) the vector encoded at storage
 // position p is the residual x[ids[p]] - coarse[cells[ids[p]]].  Not on the query path.
 
-#include "qadc_common.h"
+#include "qadc_nearest.h"
 
 namespace qadc {
 
@@ -25,152 +25,93 @@ __device__ inline const float *centroid_part(const CellCentroids &cc, int c, int
     return off < dh ? cc.halves + (size_t)i * dh + off : cc.halves + ((size_t)cc.Kh + j) * dh + (off - dh);
 }
 
-// One thread per output byte.  ksub == 16: the byte holds components 2jb (low
-// nibble) and 2jb+1 (high nibble); ksub == 256: the byte is component jb.
-// Distances in float64 from the float32 differences' exact values, summed in increasing t with
-// separate multiply and add; ties go to the lowest index.  With `coarse`, row r of the output
-// encodes the float32 residual of vector ids[r].
-template <int KSUB>
+// A wavefront takes 64 consecutive output rows, a lane each, and ENC_GROUP bytes of their codes (8 components
+// of 4 bits, 4 of 8 bits, 4 of 6 bits): its lanes read neighbouring sub-vectors of their rows, the centroids
+// are uniform over the wavefront (qadc_nearest.h), nothing goes through LDS, and the wavefronts of a row block
+// are neighbours, so the row's lines are shared in the caches.  Before, a thread per output byte computed the
+// float64 distances from a codebook in LDS, where the lanes of a wavefront met on the same banks: 2 M vectors
+// of 128 dimensions, m = 16: 1029 us; residuals of 1 M vectors, m = 32: 865 us; now 270 and 211 us
+// (reading the vectors at 5 TB/s takes 200 and 200 us).
+// With `coarse`, row r of the output encodes the float32 residual of vector ids[r].
+template <int KSUB, int DS>
 __global__ __launch_bounds__(256) void pq_encode_kernel(
     const float *__restrict__ codebooks, int d, int m, const float *__restrict__ x, int64_t n,
     uint8_t *__restrict__ codes, CellCentroids cc, const int32_t *__restrict__ cells,
     const uint32_t *__restrict__ ids, int64_t n_x)
 {
-#pragma clang fp contract(off)
-    const int dsub = d / m;
-    const int row = (KSUB == 16) ? m / 2 : m;
-    const int64_t gid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (gid >= n * row) return;
-    const int64_t r = gid / row;
-    const int jb = (int)(gid - r * row);
-    const int64_t src = ids ? (int64_t)ids[r] : r;
+    constexpr int COMPS = KSUB == 16 ? 8 : 4;     // components per wavefront
+    constexpr int GROUP = KSUB == 64 ? 3 : 4;     // bytes they fill
+    const int dsub = DS ? DS : d / m;
+    const int row = KSUB == 16 ? m / 2 : KSUB == 64 ? 3 * (m / 4) : m;
+    const int groups = (m + COMPS - 1) / COMPS;
+    const int64_t unit = (int64_t)blockIdx.x * (256 / WAVE) + __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE);
+    const int64_t block = unit / groups;
+    const int gr = (int)(unit - block * groups);
+    const int64_t r = block * WAVE + (threadIdx.x & (WAVE - 1));
+    if (block * WAVE >= n) return;                // uniform
+    bool ok = r < n;
     const bool resid = cc.coarse || cc.halves;
+    int64_t src = ids ? (ok ? (int64_t)ids[r] : 0) : (ok ? r : 0);
     int c = 0;
-    if (resid) {  // an id or a cell out of range: a zero byte, no access
-        if (src >= n_x) { codes[gid] = 0; return; }
-        c = cells[src];
-        if (c < 0 || c >= cc.K) { codes[gid] = 0; return; }
+    if (resid) {  // an id or a cell out of range: zero bytes, no access
+        if (src >= n_x) ok = false;
+        if (ok) c = cells[src];
+        if (c < 0 || c >= cc.K) ok = false;
     }
-    const int ncomp = (KSUB == 16) ? 2 : 1;
+    // (lanes without a row read row 0 of x and cell 0; with an empty x there is nothing to read)
+    if (!ok) { src = 0; c = 0; }
+    const bool readable = n_x > 0;                // uniform
+    // Components fetched together: a lane's loads then use up a cache line at once.  (One component at a time the
+    // lines of 32 wavefronts left the L1 and the L2 between two uses: 386 us for the first of those.)
+    constexpr int BATCH = DS == 0 || KSUB != 16 ? 1 : DS > 8 ? 2 : DS >= 6 ? 4 : COMPS;
     unsigned out = 0;
-    for (int h = 0; h < ncomp; ++h) {
-        const int j = (KSUB == 16) ? 2 * jb + h : jb;
-        const float *xs = x + src * d + (int64_t)j * dsub;
-        const float *bs = resid ? centroid_part(cc, c, j * dsub, d) : nullptr;
-        const float *cb = codebooks + (size_t)j * KSUB * dsub;
-        double best = __builtin_inf();
-        unsigned arg = 0;
-        for (int i = 0; i < KSUB; ++i) {
-            double acc = 0.0;
-            for (int t = 0; t < dsub; ++t) {
-                const float xv = bs ? xs[t] - bs[t] : xs[t];
-                const double df = (double)xv - (double)cb[i * dsub + t];
-                acc += df * df;
+#pragma unroll
+    for (int h0 = 0; h0 < COMPS; h0 += BATCH) {
+        float xv[BATCH][DS ? DS : 1];
+        const int j0 = gr * COMPS + h0;
+        if (j0 >= m || !readable) break;          // uniform
+        const float *xs = x + src * d + (int64_t)j0 * dsub;
+        if constexpr (DS != 0) {
+#pragma unroll
+            for (int h = 0; h < BATCH; ++h) {
+                if (j0 + h < m) {                 // uniform
+#pragma unroll
+                    for (int t = 0; t < DS; ++t) xv[h][t] = xs[h * DS + t];
+                }
             }
-            if (acc < best) { best = acc; arg = (unsigned)i; }
-        }
-        out |= arg << (4 * h);
-    }
-    codes[gid] = (uint8_t)out;
-}
-
-// ksub == 64 (6-bit components): one thread per group of four components = three output bytes;
-// component j is bits 6j .. 6j+5 of the code read as a little-endian number.  Arithmetic as above.
-__global__ __launch_bounds__(256) void pq_encode6_kernel(
-    const float *__restrict__ codebooks, int d, int m, const float *__restrict__ x, int64_t n,
-    uint8_t *__restrict__ codes)
-{
-#pragma clang fp contract(off)
-    const int dsub = d / m;
-    const int groups = m / 4;
-    const int64_t gid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (gid >= n * groups) return;
-    const int64_t r = gid / groups;
-    const int gq = (int)(gid - r * groups);
-    unsigned out = 0;
-    for (int h = 0; h < 4; ++h) {
-        const int j = 4 * gq + h;
-        const float *xs = x + r * d + (int64_t)j * dsub;
-        const float *cb = codebooks + (size_t)j * 64 * dsub;
-        double best = __builtin_inf();
-        unsigned arg = 0;
-        for (int i = 0; i < 64; ++i) {
-            double acc = 0.0;
-            for (int t = 0; t < dsub; ++t) {
-                const double df = (double)xs[t] - (double)cb[i * dsub + t];
-                acc += df * df;
-            }
-            if (acc < best) { best = acc; arg = (unsigned)i; }
-        }
-        out |= arg << (6 * h);
-    }
-    uint8_t *o = codes + r * (int64_t)(3 * groups) + 3 * gq;
-    o[0] = (uint8_t)out;
-    o[1] = (uint8_t)(out >> 8);
-    o[2] = (uint8_t)(out >> 16);
-}
-
-// ksub == 16 with the codebooks in LDS as [j][t][16] floats: one thread per output byte; for each
-// component it reads x^j[t] once and advances the 16 distances together, each still summed in
-// increasing t.  Same arithmetic and result as pq_encode_kernel<16>.
-__global__ __launch_bounds__(256) void pq_encode16_lds_kernel(
-    const float *__restrict__ codebooks, int d, int m, const float *__restrict__ x, int64_t n,
-    uint8_t *__restrict__ codes, CellCentroids cc, const int32_t *__restrict__ cells,
-    const uint32_t *__restrict__ ids, int64_t n_x)
-{
-#pragma clang fp contract(off)
-    extern __shared__ __attribute__((aligned(16))) float cbt[];   // [m][dsub][16]
-    const int dsub = d / m;
-    for (int e = threadIdx.x; e < d * 16; e += 256) {
-        const int j = e / (16 * dsub), rem = e - j * 16 * dsub;   // codebooks[j][i][t]
-        const int i = rem / dsub, t = rem - i * dsub;
-        cbt[(j * dsub + t) * 16 + i] = codebooks[e];
-    }
-    __syncthreads();
-    const int row = m / 2;
-    const int64_t gid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (gid >= n * row) return;
-    const int64_t r = gid / row;
-    const int jb = (int)(gid - r * row);
-    const int64_t src = ids ? (int64_t)ids[r] : r;
-    const bool resid = cc.coarse || cc.halves;
-    int c = 0;
-    if (resid) {
-        if (src >= n_x) { codes[gid] = 0; return; }
-        c = cells[src];
-        if (c < 0 || c >= cc.K) { codes[gid] = 0; return; }
-    }
-    unsigned out = 0;
+            if (resid) {
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
-        const int j = 2 * jb + h;
-        const float *xs = x + src * d + (int64_t)j * dsub;
-        const float *bs = resid ? centroid_part(cc, c, j * dsub, d) : nullptr;
-        double acc[16];
+                for (int h = 0; h < BATCH; ++h) {
+                    if (j0 + h < m) {
+                        const float *bs = centroid_part(cc, c, (j0 + h) * DS, d);
 #pragma unroll
-        for (int i = 0; i < 16; ++i) acc[i] = 0.0;
-        for (int t = 0; t < dsub; ++t) {
-            const float xv = bs ? xs[t] - bs[t] : xs[t];
-            const float4 *c4 = reinterpret_cast<const float4 *>(cbt + (j * dsub + t) * 16);
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const float4 c = c4[q];
-                const float cv[4] = {c.x, c.y, c.z, c.w};
-#pragma unroll
-                for (int k = 0; k < 4; ++k) {
-                    const double df = (double)xv - (double)cv[k];
-                    acc[4 * q + k] += df * df;
+                        for (int t = 0; t < DS; ++t) xv[h][t] = xv[h][t] - bs[t];
+                    }
                 }
             }
         }
-        double best = __builtin_inf();
-        unsigned arg = 0;
 #pragma unroll
-        for (int i = 0; i < 16; ++i)
-            if (acc[i] < best) { best = acc[i]; arg = (unsigned)i; }
-        out |= arg << (4 * h);
+        for (int h = 0; h < BATCH; ++h) {
+            const int j = j0 + h;
+            if (j < m) {                          // uniform
+                const float *bs = resid ? centroid_part(cc, c, j * dsub, d) : nullptr;
+                const unsigned a = nearest_centroid<KSUB, DS>(xv[h], xs + h * dsub, bs, codebooks + (size_t)j * KSUB * dsub,
+                                                              dsub, ok);
+                out |= a << (KSUB == 16 ? 4 * (h0 + h) : KSUB == 64 ? 6 * (h0 + h) : 8 * (h0 + h));
+            }
+        }
     }
-    codes[gid] = (uint8_t)out;
+    if (r >= n) return;
+    if (!ok) out = 0;
+    const int64_t at = r * row + (int64_t)gr * GROUP;
+    const int bytes = min(GROUP, row - gr * GROUP);
+    if (GROUP == 4 && bytes == 4 && ((uintptr_t)(codes + at) & 3) == 0) {
+        *reinterpret_cast<unsigned *>(codes + at) = out;
+    } else {
+#pragma unroll
+        for (int k = 0; k < GROUP; ++k)
+            if (k < bytes) codes[at + k] = (uint8_t)(out >> (8 * k));
+    }
 }
 
 static int encode_launch(const char *name, const float *codebooks, int d, int m, int ksub, const float *x,
@@ -182,25 +123,30 @@ static int encode_launch(const char *name, const float *codebooks, int d, int m,
         return fail(QADC_EINVAL, "%s: unsupported d=%d m=%d ksub=%d", name, d, m, ksub);
     if (n == 0) return QADC_OK;
     if (!codebooks || !x || !codes) return fail(QADC_EINVAL, "%s: null pointer", name);
-    if (ksub == 64) {
-        const int64_t blocks6 = ceil_div(n * (m / 4), 256);
-        if (blocks6 > 0x7fffffffll) return fail(QADC_EINVAL, "%s: n too large for one call", name);
-        hipLaunchKernelGGL(pq_encode6_kernel, dim3((unsigned)blocks6), dim3(256), 0, st, codebooks, d, m, x, n, codes);
-        QADC_HIP_TRY(hipGetLastError());
-        return QADC_OK;
+    const int groups = (int)ceil_div(m, ksub == 16 ? 8 : 4);
+    const int64_t blocks = ceil_div(ceil_div(n, WAVE) * groups, 256 / WAVE);
+    if (ceil_div(n * (ksub == 16 ? m / 2 : ksub == 64 ? m / 4 : m), 256) > 0x7fffffffll || blocks > 0x7fffffffll)
+        return fail(QADC_EINVAL, "%s: n too large for one call", name);
+    // sub-vectors of the usual dimensions stay in registers
+#define QADC_ENC(K_, D_)                                                                                    \
+    hipLaunchKernelGGL((pq_encode_kernel<K_, D_>), dim3((unsigned)blocks), dim3(256), 0, st, codebooks, d, m, x, \
+                       n, codes, cc, cells, ids, n_x)
+#define QADC_ENC_DS(K_)                          \
+    switch (d / m) {                             \
+    case 2: QADC_ENC(K_, 2); break;              \
+    case 3: QADC_ENC(K_, 3); break;              \
+    case 4: QADC_ENC(K_, 4); break;              \
+    case 6: QADC_ENC(K_, 6); break;              \
+    case 8: QADC_ENC(K_, 8); break;              \
+    case 12: QADC_ENC(K_, 12); break;            \
+    case 16: QADC_ENC(K_, 16); break;            \
+    default: QADC_ENC(K_, 0); break;             \
     }
-    const int64_t total = n * (ksub == 16 ? m / 2 : m);
-    const int64_t blocks = ceil_div(total, 256);
-    if (blocks > 0x7fffffffll) return fail(QADC_EINVAL, "%s: n too large for one call", name);
-    if (ksub == 16 && (size_t)d * 64 <= 65536)
-        hipLaunchKernelGGL(pq_encode16_lds_kernel, dim3((unsigned)blocks), dim3(256), (size_t)d * 64, st,
-                           codebooks, d, m, x, n, codes, cc, cells, ids, n_x);
-    else if (ksub == 16)
-        hipLaunchKernelGGL(pq_encode_kernel<16>, dim3((unsigned)blocks), dim3(256), 0, st, codebooks, d,
-                           m, x, n, codes, cc, cells, ids, n_x);
-    else
-        hipLaunchKernelGGL(pq_encode_kernel<256>, dim3((unsigned)blocks), dim3(256), 0, st, codebooks,
-                           d, m, x, n, codes, cc, cells, ids, n_x);
+    if (ksub == 16) { QADC_ENC_DS(16) }
+    else if (ksub == 64) { QADC_ENC_DS(64) }
+    else { QADC_ENC_DS(256) }
+#undef QADC_ENC_DS
+#undef QADC_ENC
     QADC_HIP_TRY(hipGetLastError());
     return QADC_OK;
 }

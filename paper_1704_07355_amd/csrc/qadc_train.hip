@@ -7,7 +7,7 @@
 // centroid by the mean of its sub-vectors (float64 sum in row order, stored as float32);
 // a centroid that owns nothing keeps its value.  No atomics: the result is deterministic.
 
-#include "qadc_common.h"
+#include "qadc_nearest.h"
 
 namespace qadc {
 
@@ -23,27 +23,44 @@ __global__ void train_init_kernel(const float *__restrict__ train, int64_t n, in
     cb[e] = train[row * d + j * dsub + t];
 }
 
-__global__ void train_assign_kernel(const float *__restrict__ train, int64_t n, int d, int m, int ksub,
-                                    const float *__restrict__ cb, uint8_t *__restrict__ labels)
+// labels[j][r] = closest centroid of sub-vector j of row r.  A wavefront takes 64 rows and one sub-quantizer
+// (qadc_nearest.h); the labels are stored a column per sub-quantizer, as the update reads them.  20,000 rows of
+// 128 dimensions, m = 16, 16 centroids: 145 -> 15 us.
+template <int KSUB, int DS>
+__global__ __launch_bounds__(256) void train_assign_kernel(const float *__restrict__ train, int64_t n, int d, int m,
+                                                           const float *__restrict__ cb, uint8_t *__restrict__ labels)
 {
-    const int dsub = d / m;
-    const int64_t gid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;  // (r, j)
-    if (gid >= n * m) return;
-    const int64_t r = gid / m;
-    const int j = (int)(gid - r * m);
-    const float *xs = train + r * d + j * dsub;
-    const float *c = cb + (size_t)j * ksub * dsub;
-    double best = __builtin_inf();
-    int arg = 0;
-    for (int i = 0; i < ksub; ++i) {
-        double acc = 0.0;
-        for (int t = 0; t < dsub; ++t) {
-            const double df = (double)xs[t] - (double)c[i * dsub + t];
-            acc += df * df;
-        }
-        if (acc < best) { best = acc; arg = i; }
+    const int dsub = DS ? DS : d / m;
+    const int64_t unit = (int64_t)blockIdx.x * (256 / WAVE) + __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE);
+    const int64_t block = unit / m;
+    const int j = (int)(unit - block * m);
+    if (block * WAVE >= n) return;  // uniform
+    const int64_t r = block * WAVE + (threadIdx.x & (WAVE - 1));
+    const float *xs = train + min(r, n - 1) * d + (int64_t)j * dsub;
+    float xv[DS ? DS : 1];
+    if constexpr (DS != 0) {
+#pragma unroll
+        for (int t = 0; t < DS; ++t) xv[t] = xs[t];
     }
-    labels[(size_t)j * n + r] = (uint8_t)arg;  // a column per sub-quantizer, as the update reads them
+    const unsigned a = nearest_centroid<KSUB, DS>(xv, xs, nullptr, cb + (size_t)j * KSUB * dsub, dsub, r < n);
+    if (r < n) labels[(size_t)j * n + r] = (uint8_t)a;
+}
+
+template <int KSUB>
+static void launch_train_assign(const float *train, int64_t n, int d, int m, const float *cb, uint8_t *labels,
+                                hipStream_t st)
+{
+    const dim3 grid((unsigned)ceil_div(ceil_div(n, WAVE) * m, 256 / WAVE));
+#define QADC_ASG(D_)                                                                                          \
+    case D_:                                                                                                  \
+        hipLaunchKernelGGL((train_assign_kernel<KSUB, D_>), grid, dim3(256), 0, st, train, n, d, m, cb, labels); \
+        return;
+    switch (d / m) {
+    QADC_ASG(2) QADC_ASG(3) QADC_ASG(4) QADC_ASG(6) QADC_ASG(8) QADC_ASG(12) QADC_ASG(16)
+    default:
+        hipLaunchKernelGGL((train_assign_kernel<KSUB, 0>), grid, dim3(256), 0, st, train, n, d, m, cb, labels);
+    }
+#undef QADC_ASG
 }
 
 // Means of the sub-vectors of one centroid: workgroup (i, j, block of TRAIN_TD dimensions).  The
@@ -54,20 +71,20 @@ __global__ void train_assign_kernel(const float *__restrict__ train, int64_t n, 
 // flight together, and while the next stage is fetched the first wavefront adds the stage before it, a
 // lane per component, from LDS.  Bound by the chain of float64 additions over the centroid's rows.
 // 20,000 rows, m = 16, 16 centroids, 8 dimensions: 4000 us (one thread per component walking all rows:
-// 32 wavefronts, a dependent label load per row) -> 49 us.
+// 32 wavefronts, a dependent label load per row) -> 41 us.
 constexpr int TRAIN_NT = 512;
 constexpr int TRAIN_WAVES = TRAIN_NT / WAVE;
 constexpr int TRAIN_PER = 16;                            // labels per lane and round
 constexpr int TRAIN_SEG = TRAIN_NT * TRAIN_PER;          // labels per round
 constexpr int TRAIN_TD = 64;                             // components per workgroup, at most: a lane each
-constexpr int TRAIN_STAGE = 8192;                        // floats per stage
+constexpr int TRAIN_STAGE = 4096;                        // values per stage, already float64: the adding lane has nothing to convert
 
 __global__ __launch_bounds__(TRAIN_NT) void train_update_kernel(
     const float *__restrict__ train, int64_t n, int d, int m, int ksub, const uint8_t *__restrict__ labels,
     float *__restrict__ cb)
 {
     __shared__ uint16_t rows[TRAIN_SEG];                 // the centroid's rows of the round, in row order
-    __shared__ float stage[2][TRAIN_STAGE];
+    __shared__ double stage[2][TRAIN_STAGE];
     __shared__ unsigned wcount[TRAIN_WAVES];
     const int tid = threadIdx.x, lane = tid & (WAVE - 1), wave = tid / WAVE;
     const int dsub = d / m;
@@ -113,24 +130,42 @@ __global__ __launch_bounds__(TRAIN_NT) void train_update_kernel(
             if (s < stages) {
                 const int r0 = s * per_stage;
                 const int elems = min(per_stage, (int)found - r0) * td;
-                float *to = stage[s & 1];
-                for (int e = tid; e < elems; e += TRAIN_NT) {
-                    const int r = e / td, t = e - r * td;
-                    to[e] = src[(base + rows[r0 + r]) * d + t];
+                double *to = stage[s & 1];
+                constexpr int FL = 8;                    // loads in flight per thread
+                for (int e0 = tid; e0 < elems; e0 += FL * TRAIN_NT) {
+                    float v[FL];
+#pragma unroll
+                    for (int u = 0; u < FL; ++u) {
+                        const int e = min(e0 + u * TRAIN_NT, elems - 1);
+                        const int r = e / td, t = e - r * td;
+                        v[u] = src[(base + rows[r0 + r]) * d + t];
+                    }
+#pragma unroll
+                    for (int u = 0; u < FL; ++u)
+                        if (e0 + u * TRAIN_NT < elems) to[e0 + u * TRAIN_NT] = (double)v[u];
                 }
             }
             if (s > 0 && tid < td) {
-                const float *from = stage[(s - 1) & 1] + tid;
+                const double *from = stage[(s - 1) & 1] + tid;
                 const int have = min(per_stage, (int)found - (s - 1) * per_stage);
                 int r = 0;
-                for (; r + 8 <= have; r += 8) {
-                    float v[8];
+                if (have >= 16) {  // the next sixteen rows are read from LDS while sixteen are added
+                    double v[16];
 #pragma unroll
-                    for (int u = 0; u < 8; ++u) v[u] = from[(r + u) * td];
+                    for (int u = 0; u < 16; ++u) v[u] = from[u * td];
+                    for (r = 16; r + 16 <= have; r += 16) {
+                        double nx[16];
 #pragma unroll
-                    for (int u = 0; u < 8; ++u) sum += (double)v[u];
+                        for (int u = 0; u < 16; ++u) nx[u] = from[(r + u) * td];
+#pragma unroll
+                        for (int u = 0; u < 16; ++u) sum += v[u];
+#pragma unroll
+                        for (int u = 0; u < 16; ++u) v[u] = nx[u];
+                    }
+#pragma unroll
+                    for (int u = 0; u < 16; ++u) sum += v[u];
                 }
-                for (; r < have; ++r) sum += (double)from[r * td];
+                for (; r < have; ++r) sum += from[r * td];
             }
             __syncthreads();
         }
@@ -152,8 +187,9 @@ int pq_train(const float *train, int64_t n, int d, int m, int ksub, const int64_
     hipLaunchKernelGGL(train_init_kernel, dim3((unsigned)ceil_div(entries, 256)), dim3(256), 0, st, train,
                        n, d, m, ksub, init_rows, codebooks);
     for (int it = 0; it < iters; ++it) {
-        hipLaunchKernelGGL(train_assign_kernel, dim3((unsigned)ceil_div(n * m, 256)), dim3(256), 0, st,
-                           train, n, d, m, ksub, codebooks, labels);
+        if (ksub == 16) launch_train_assign<16>(train, n, d, m, codebooks, labels, st);
+        else if (ksub == 64) launch_train_assign<64>(train, n, d, m, codebooks, labels, st);
+        else launch_train_assign<256>(train, n, d, m, codebooks, labels, st);
         hipLaunchKernelGGL(train_update_kernel,
                            dim3((unsigned)(ksub * m * ceil_div(d / m, TRAIN_TD))), dim3(TRAIN_NT), 0, st, train, n, d,
                            m, ksub, labels, codebooks);

@@ -232,3 +232,64 @@ def test_pq_train_means_are_row_order_float64_sums(Q, O, n, d, m, ksub):
                 want[j, i] = (sums / len(own)).astype(np.float32)
     got = Q.qadc_pq_train(to_gpu(x), m, ksub, to_gpu(rows), 1).cpu().numpy()
     assert np.array_equal(got, want)
+
+
+def _codes_by_definition(x, cb):
+    """enc(x) from float64 distances summed in increasing component order, ties to the lowest index; u8 [n][m]."""
+    m, k, dsub = cb.shape
+    out = np.empty((len(x), m), dtype=np.uint8)
+    with np.errstate(all="ignore"):
+        for j in range(m):
+            acc = np.zeros((len(x), k))
+            for t in range(dsub):
+                df = x[:, j * dsub + t, None].astype(np.float64) - cb[j, None, :, t].astype(np.float64)
+                acc = acc + df * df
+            acc[np.isnan(acc)] = np.inf
+            out[:, j] = np.argmin(acc, axis=1)
+    return out
+
+
+def _pack(comps, k):
+    n, m = comps.shape
+    if k == 256:
+        return comps
+    bits = 4 if k == 16 else 6
+    v = np.zeros((n, bits * m), dtype=np.uint8)
+    for b in range(bits):
+        v[:, b::bits] = (comps >> b) & 1
+    return np.packbits(v.reshape(n, -1, 8), axis=2, bitorder="little")[:, :, 0]
+
+
+@pytest.mark.parametrize("n,m,dsub,k", [(1, 2, 8, 16), (63, 6, 1, 16), (65, 10, 4, 16), (257, 16, 5, 16), (700, 18, 16, 16),
+                                        (130, 8, 30, 16), (190, 8, 3, 64), (61, 12, 12, 64), (129, 4, 17, 64),
+                                        (100, 1, 2, 256), (66, 7, 12, 256), (321, 8, 6, 256), (64, 5, 40, 256)])
+def test_pq_encode_where_float32_cannot_tell(Q, n, m, dsub, k):
+    """Near ties around the float32 margin, exact ties, and values at both ends of the float32 range, infinities and
+    NaN included: the codes are those of the float64 definition; rows and bytes around a wavefront's share; an output
+    that starts at an odd address."""
+    import torch
+    rng = np.random.default_rng(n * m + k)
+    cb = rng.uniform(0, 255, size=(m, k, dsub)).astype(np.float32)
+    cb[:, k // 2] = cb[:, k // 3]                                                   # the lower index wins
+    cb[:, k // 4] = np.nextafter(cb[:, k // 5], np.float32(1e9))                   # one unit in the last place apart
+    x = rng.uniform(0, 255, size=(n, m * dsub)).astype(np.float32)
+    own = rng.integers(0, k, size=(n, m))
+    near = np.concatenate([cb[j][own[:, j]] for j in range(m)], axis=1)
+    mid = np.concatenate([(cb[j][own[:, j]] + cb[j][(own[:, j] + 1) % k]) / 2 for j in range(m)], axis=1).astype(np.float32)
+    kind = rng.integers(0, 8, size=n)
+    x[kind == 1] = near[kind == 1]
+    x[kind == 2] = mid[kind == 2]                                                   # as far from two centroids
+    x[kind == 3] = near[kind == 3] + np.float32(1e-3)
+    x[kind == 4] *= np.float32(1e17)                                                # squares leave the float32 range
+    x[kind == 5, 0] = np.inf
+    x[kind == 6, -1] = np.nan
+    if n > 300:
+        cb[m - 1] *= np.float32(1e-22)                                              # squares below the normal range
+        x[kind == 7, -dsub:] *= np.float32(1e-22)
+        cb[0, k - 1, 0] = np.inf
+        cb[0, 0, -1] = np.nan
+    want = _pack(_codes_by_definition(x, cb), k)
+    flat = torch.zeros((n * want.shape[1] + 1,), dtype=torch.uint8, device="cuda:0")
+    for out in (flat[1:].view(n, -1), flat[:-1].view(n, -1)):
+        got = Q.qadc_pq_encode(to_gpu(cb), to_gpu(x), out=out)
+        assert np.array_equal(got.cpu().numpy(), want)
