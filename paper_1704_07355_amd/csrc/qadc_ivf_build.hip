@@ -1,19 +1,10 @@
-// Database side of the inverted index on gfx950 (Section 2.2 of the paper): which cell a vector
-// falls in, and the list order of a database.
+// Database side of the inverted index on gfx950 (Section 2.2 of the paper): the list order of a
+// database.  (The cell of a vector: qadc_assign.hip.)
 //
-//   assign   cell(x) = index of the closest coarse centroid (float64 distances from the
-//            differences, ties to the lowest cell) -- the vector quantizer q_i of Section 2.2.
 //   group    a stable grouping by cell: list_off[c] = number of vectors in cells < c, and
 //            ids[list_off[c] + r] = the r-th vector (in input order) of cell c.
 //
 // The codes of the residuals are then written in list order by the encoder (qadc_encode.hip).
-//
-// assign: a workgroup of 256 threads takes 128 vectors and walks over all cells 128 at a time;
-// 16 components of both go through LDS as float64 per step, every thread accumulates 8 x 8
-// distances (one subtraction and one fused multiply-add per component) and keeps, per vector,
-// the best of the cells it has seen; the 16 threads of a vector compare their candidates at the
-// end under the order (distance, cell).  Vector-ALU bound: 2 float64 operations per (vector,
-// cell, component).
 //
 // group: the database is cut into P contiguous parts, one wavefront per part.  Pass 1 counts
 // cnt[part][cell]; a column pass turns each column into running sums over the parts and yields
@@ -27,141 +18,6 @@
 #include <algorithm>
 
 namespace qadc {
-
-constexpr int ASG_TM = 128;  // vectors per workgroup
-constexpr int ASG_TN = 128;  // cells per step
-constexpr int ASG_TK = 16;   // components per step
-constexpr int ASG_LD = ASG_TM + 2;  // row stride in doubles: keeps 16-byte alignment, shifts the banks
-
-// Thread (tx, ty), tx = tid & 15, ty = tid >> 4, owns the vectors 8*ty .. 8*ty+7 of the tile and
-// the cells 32*k + 2*tx + e (k < 4, e < 2): a wavefront's 16-byte reads of the cells are
-// contiguous across its lanes, its reads of the vectors are the same for 16 lanes.
-__global__ __launch_bounds__(256) void ivf_assign_kernel(const float *__restrict__ coarse, int K, int d,
-                                                         const float *__restrict__ x, int64_t ldx, int64_t n,
-                                                         int32_t *__restrict__ cells, int scale, int accumulate)
-{
-    __shared__ __attribute__((aligned(16))) double xs[ASG_TK][ASG_LD];
-    __shared__ __attribute__((aligned(16))) double cs[ASG_TK][ASG_LD];
-    __shared__ double cand_d[ASG_TM][16];
-    __shared__ int cand_c[ASG_TM][16];
-    const int tid = threadIdx.x;
-    const int tx = tid & 15, ty = tid >> 4;
-    const int64_t i0 = (int64_t)blockIdx.x * ASG_TM;
-    double best_d[8];
-    int best_c[8];
-#pragma unroll
-    for (int a = 0; a < 8; ++a) { best_d[a] = __builtin_inf(); best_c[a] = 0x7fffffff; }
-
-    for (int c0 = 0; c0 < K; c0 += ASG_TN) {
-        double acc[8][8];
-#pragma unroll
-        for (int a = 0; a < 8; ++a)
-#pragma unroll
-            for (int b = 0; b < 8; ++b) acc[a][b] = 0.0;
-        for (int t0 = 0; t0 < d; t0 += ASG_TK) {
-            // 128 x 16 elements of x and of the centroids, eight of each per thread, zero beyond the edges
-#pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                const int idx = tid + e * 256;
-                const int row = idx >> 4, col = idx & 15;
-                const int t = t0 + col;
-                const int64_t i = i0 + row;
-                const int c = c0 + row;
-                xs[col][row] = (i < n && t < d) ? (double)x[i * ldx + t] : 0.0;
-                cs[col][row] = (c < K && t < d) ? (double)coarse[(size_t)c * d + t] : 0.0;
-            }
-            __syncthreads();
-#pragma unroll 4
-            for (int kk = 0; kk < ASG_TK; ++kk) {
-                double xv[8], cv[8];
-#pragma unroll
-                for (int a = 0; a < 8; a += 2) {
-                    const double2 v = *reinterpret_cast<const double2 *>(&xs[kk][8 * ty + a]);
-                    xv[a] = v.x; xv[a + 1] = v.y;
-                }
-#pragma unroll
-                for (int k = 0; k < 4; ++k) {
-                    const double2 v = *reinterpret_cast<const double2 *>(&cs[kk][32 * k + 2 * tx]);
-                    cv[2 * k] = v.x; cv[2 * k + 1] = v.y;
-                }
-#pragma unroll
-                for (int a = 0; a < 8; ++a)
-#pragma unroll
-                    for (int b = 0; b < 8; ++b) {
-                        const double df = xv[a] - cv[b];
-                        acc[a][b] = fma(df, df, acc[a][b]);
-                    }
-            }
-            __syncthreads();
-        }
-        // the smaller distance wins, the lower cell among equal distances
-#pragma unroll
-        for (int a = 0; a < 8; ++a)
-#pragma unroll
-            for (int b = 0; b < 8; ++b) {
-                const int c = c0 + 32 * (b >> 1) + 2 * tx + (b & 1);
-                if (c < K && (acc[a][b] < best_d[a] || (acc[a][b] == best_d[a] && c < best_c[a]))) {
-                    best_d[a] = acc[a][b];
-                    best_c[a] = c;
-                }
-            }
-    }
-#pragma unroll
-    for (int a = 0; a < 8; ++a) {
-        cand_d[8 * ty + a][tx] = best_d[a];
-        cand_c[8 * ty + a][tx] = best_c[a];
-    }
-    __syncthreads();
-    if (tid < ASG_TM) {
-        const int64_t i = i0 + tid;
-        if (i < n) {
-            double bd = cand_d[tid][0];
-            int bc = cand_c[tid][0];
-            for (int k = 1; k < 16; ++k) {
-                const double dd = cand_d[tid][k];
-                const int cc = cand_c[tid][k];
-                if (dd < bd || (dd == bd && cc < bc)) { bd = dd; bc = cc; }
-            }
-            cells[i] = (accumulate ? cells[i] : 0) + bc * scale;
-        }
-    }
-}
-
-int ivf_assign(const float *coarse, int K, int d, const float *x, int64_t n, int32_t *cells, hipStream_t st)
-{
-    if (K < 1 || d < 1 || n < 0)
-        return fail(QADC_EINVAL, "qadc_ivf_assign: K=%d d=%d n=%lld", K, d, (long long)n);
-    if (n == 0) return QADC_OK;
-    if (!coarse || !x || !cells) return fail(QADC_EINVAL, "qadc_ivf_assign: null pointer");
-    const int64_t grid = ceil_div(n, ASG_TM);
-    if (grid > 0x7fffffffll) return fail(QADC_EINVAL, "qadc_ivf_assign: n too large for one call");
-    hipLaunchKernelGGL(ivf_assign_kernel, dim3((unsigned)grid), dim3(256), 0, st, coarse, K, d, x, (int64_t)d, n,
-                       cells, 1, 0);
-    QADC_HIP_TRY(hipGetLastError());
-    return QADC_OK;
-}
-
-// Cells of an inverted multi-index: the coarse quantizer is the product of two quantizers of K
-// centroids over the two halves of the vector, cell = K * (closest of halves[0] to the first half)
-// + (closest of halves[1] to the second half).  Two passes of the assignment kernel over the
-// halves of the rows of x.
-int multi_index_assign(const float *halves, int K, int d, const float *x, int64_t n, int32_t *cells,
-                       hipStream_t st)
-{
-    if (K < 1 || K > 16384 || d < 2 || (d & 1) || n < 0)
-        return fail(QADC_EINVAL, "qadc_multi_index_assign: K=%d d=%d n=%lld", K, d, (long long)n);
-    if (n == 0) return QADC_OK;
-    if (!halves || !x || !cells) return fail(QADC_EINVAL, "qadc_multi_index_assign: null pointer");
-    const int64_t grid = ceil_div(n, ASG_TM);
-    if (grid > 0x7fffffffll) return fail(QADC_EINVAL, "qadc_multi_index_assign: n too large for one call");
-    const int dh = d / 2;
-    hipLaunchKernelGGL(ivf_assign_kernel, dim3((unsigned)grid), dim3(256), 0, st, halves, K, dh, x, (int64_t)d, n,
-                       cells, K, 0);
-    hipLaunchKernelGGL(ivf_assign_kernel, dim3((unsigned)grid), dim3(256), 0, st, halves + (size_t)K * dh, K, dh,
-                       x + dh, (int64_t)d, n, cells, 1, 1);
-    QADC_HIP_TRY(hipGetLastError());
-    return QADC_OK;
-}
 
 // ------------------------------------------------------------------ group
 

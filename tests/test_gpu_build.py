@@ -125,6 +125,67 @@ def test_ivf_assign_matches_oracle(Q, O, K, d, n):
         assert got[7] == 2 and got[-1] == 5
 
 
+def _closest(x, coarse):
+    """Closest cell by float64 differences, lowest cell among equals; x in pieces that fit the memory."""
+    x, c = np.asarray(x, np.float64), np.asarray(coarse, np.float64)
+    step = max(1, 4_000_000 // c.size)
+    return np.concatenate([((x[i:i + step, None] - c[None]) ** 2).sum(2).argmin(1) for i in range(0, len(x), step)])
+
+
+# every width of the matrix filter (and one beyond it), tails of tiles of cells and of vectors, both vector tiles
+@pytest.mark.parametrize("d,K,n", [(7, 5, 1), (32, 33, 127), (33, 64, 129), (64, 65, 300), (65, 31, 257), (96, 97, 128),
+                                   (100, 200, 385), (128, 1000, 640), (129, 40, 130), (252, 300, 129), (256, 32, 200),
+                                   (257, 20, 129), (16, 3, 131_073), (64, 70, 131_200), (90, 33, 131_072),
+                                   (128, 65, 131_111)])
+@pytest.mark.parametrize("kind", ["uniform", "offset", "ties"])
+def test_ivf_assign_exact_on_close_calls(Q, d, K, n, kind):
+    """The matrix filter may not decide a close call: far from the origin its margin spans many cells, and with
+    small whole components many cells are exactly equally close (their squared differences are exact in float64, so
+    the order of the reference's sums does not matter)."""
+    rng = np.random.default_rng(d * K + n)
+    if kind == "ties":
+        coarse = rng.integers(0, 3, size=(K, d)).astype(np.float32)
+        x = rng.integers(0, 3, size=(n, d)).astype(np.float32)
+    else:
+        base = 3000.0 if kind == "offset" else 0.0
+        coarse = (base + rng.uniform(0, 1, size=(K, d))).astype(np.float32)
+        x = (base + rng.uniform(0, 1, size=(n, d))).astype(np.float32)
+        x[:min(n, K)] = coarse[:min(n, K)]
+    got = Q.qadc_ivf_assign(to_gpu(coarse), to_gpu(x)).cpu().numpy()
+    assert np.array_equal(got, _closest(x, coarse))
+
+
+def test_ivf_assign_values_at_the_ends_of_float32(Q):
+    """Squares beyond float32, below it, infinities and NaN: the float64 distances decide, an infinite distance
+    loses to a finite one, the lowest cell wins among infinite ones, and a vector with a NaN keeps its marker."""
+    rng = np.random.default_rng(3)
+    for scale in (1e25, 1e-18, 1e-30):
+        coarse = (scale * rng.uniform(0, 1, size=(70, 24))).astype(np.float32)
+        x = (scale * rng.uniform(0, 1, size=(150, 24))).astype(np.float32)
+        assert np.array_equal(Q.qadc_ivf_assign(to_gpu(coarse), to_gpu(x)).cpu().numpy(), _closest(x, coarse)), scale
+    coarse = rng.uniform(0, 1, size=(70, 24)).astype(np.float32)
+    x = rng.uniform(0, 1, size=(150, 24)).astype(np.float32)
+    want = _closest(x, coarse)
+    x[3, 5], x[149, 0] = np.inf, np.nan
+    want[3], want[149] = 0, 0x7fffffff
+    assert np.array_equal(Q.qadc_ivf_assign(to_gpu(coarse), to_gpu(x)).cpu().numpy(), want)
+    coarse[want[10], 2] = np.inf       # the cell vector 10 was in
+    keep = np.isfinite(coarse).all(1)
+    fine = np.delete(np.arange(150), [3, 149])
+    want[fine] = np.flatnonzero(keep)[_closest(x[fine], coarse[keep])]
+    want[3] = 0 if np.isfinite(coarse[0, 5]) else want[3]
+    assert np.array_equal(Q.qadc_ivf_assign(to_gpu(coarse), to_gpu(x)).cpu().numpy(), want)
+
+
+def test_ivf_assign_unaligned_rows(Q):
+    """Rows and centroids that start 4 bytes off a 16-byte boundary."""
+    rng = np.random.default_rng(9)
+    coarse, x = rng.uniform(0, 1, size=(50, 64)).astype(np.float32), rng.uniform(0, 1, size=(333, 64)).astype(np.float32)
+    gc = to_gpu(np.concatenate([[0.0], coarse.ravel()]).astype(np.float32))[1:].view(50, 64)
+    gx = to_gpu(np.concatenate([[0.0], x.ravel()]).astype(np.float32))[1:].view(333, 64)
+    assert np.array_equal(Q.qadc_ivf_assign(gc, gx).cpu().numpy(), _closest(x, coarse))
+
+
 @pytest.mark.parametrize("K,n", [(1000, 100_003), (1, 5000), (65536, 300_000), (48, 63), (7, 0), (300, 4096 * 3 + 1)])
 def test_ivf_group_is_the_stable_grouping(Q, O, K, n):
     import torch
