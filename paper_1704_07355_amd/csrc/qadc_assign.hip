@@ -12,9 +12,10 @@
 // them than a lane remembers (equal centroids, values beyond the float32 range, infinities, NaN) is measured
 // against all cells.  The result is the definition's, whatever the route.
 //
-// Bound: 3 x 2 n K d operations on the matrix units; the float32 centroids are split again by every workgroup,
-// which takes about a third as long, so a workgroup of four wavefronts takes 256 vectors (operands in
-// registers for the whole walk) and two workgroups per CU fill each other's gaps.
+// Bound: 3 x 2 n K d operations on the matrix units.  Measured for 1 M vectors, d = 128, K = 4096: 2.9 ms =
+// 1.1 PFLOP/s of bfloat16 products (the float64 kernel: 37.8 ms); 2.0 ms of it are products and group minima,
+// 0.4 splitting the centroids, which every workgroup does again -- so eight wavefronts share the tiles and keep
+// the operands of 64 vectors each in registers for the whole walk -- and 0.5 the last step.
 //
 // assign_f64_kernel (d > 256: the vectors no longer fit the registers): a workgroup of 256 threads takes 128
 // vectors and walks over all cells 128 at a time; 16 components of both go through LDS as float64 per step,
@@ -133,7 +134,6 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x8 __attribute__((ext_vector_type(8)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 
-constexpr int AF_NT = 256;
 constexpr int AF_MAX_D = 256;
 
 // hi + lo = v to 2^-17 relative
@@ -148,10 +148,9 @@ template <bool VEC>
 __device__ __forceinline__ f32x8 load8(const float *row, int t, int d)
 {
     f32x8 v;
-    if constexpr (VEC) {  // d % 4 == 0 and 16-byte aligned rows
-        const float4 z = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-        const float4 a = t < d ? *reinterpret_cast<const float4 *>(row + t) : z;
-        const float4 b = t + 4 < d ? *reinterpret_cast<const float4 *>(row + t + 4) : z;
+    if constexpr (VEC) {  // 16-byte aligned rows of whole steps
+        const float4 a = *reinterpret_cast<const float4 *>(row + t);
+        const float4 b = *reinterpret_cast<const float4 *>(row + t + 4);
         v[0] = a.x; v[1] = a.y; v[2] = a.z; v[3] = a.w;
         v[4] = b.x; v[5] = b.y; v[6] = b.z; v[7] = b.w;
     } else {
@@ -161,36 +160,38 @@ __device__ __forceinline__ f32x8 load8(const float *row, int t, int d)
     return v;
 }
 
-// KS: steps of 16 components (16 KS >= d).  NB: blocks of 32 vectors per wavefront.
-template <int KS, int NB, bool VEC>
-__global__ __launch_bounds__(AF_NT, 2) void assign_filter_kernel(const float *__restrict__ coarse, int K, int d,
+// NT: threads.  KS: steps of 16 components (16 KS >= d).  NB: blocks of 32 vectors per wavefront.  VEC: 16 KS = d, and
+// the rows of x and of the centroids start on 16-byte boundaries.
+template <int NT, int KS, int NB, bool VEC>
+__global__ __launch_bounds__(NT, 2) void assign_filter_kernel(const float *__restrict__ coarse, int K, int d,
                                                                  const float *__restrict__ x, int64_t ldx,
                                                                  int64_t n, int32_t *__restrict__ cells, int scale,
                                                                  int accumulate)
 {
     constexpr int PS = KS <= 4 ? 4 : 8;     // threads that split one centroid at a time
     constexpr int IT = (KS + PS - 1) / PS;  // steps of 16 components per thread
-    constexpr int TC = AF_NT / PS;          // cells per tile
+    constexpr int NW = NT / WAVE;
+    constexpr int TC = NT / PS;             // cells per tile
     constexpr int CT = TC / 32;
-    constexpr int TM = 4 * NB * 32;         // vectors per workgroup
+    constexpr int TM = NW * NB * 32;        // vectors per workgroup
     static_assert(TC % 32 == 0 && KS <= PS * IT, "");
     // A tile of centroids as the matrix instructions read them: step s, part (hi, lo), lane, 16 bytes
     __shared__ __attribute__((aligned(16))) bf16x8 tile[2][CT][KS][2][WAVE];
     __shared__ __attribute__((aligned(16))) float nrm[2][TC];
     __shared__ __attribute__((aligned(16))) float ref[16 * KS];
-    __shared__ float cmax_s[4];
+    __shared__ float cmax_s[NW];
     __shared__ int cand[TM][4];     // groups to measure, -1: none
     __shared__ int redo[TM];        // vectors to measure against all cells
     __shared__ int nredo;
-    __shared__ double red_d[4][4];  // [vector of four][wavefront]
-    __shared__ int red_c[4][4];
+    __shared__ double red_d[4][NW];  // [vector of four][wavefront]
+    __shared__ int red_c[4][NW];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int col = lane & 31, half = lane >> 5;
     const int64_t i0 = (int64_t)blockIdx.x * TM;
 
     // the reference: the mean of eight centroids of the range (any vector would do; one amid the
     // centroids keeps the norms, and with them the margin, small)
-    for (int t = tid; t < 16 * KS; t += AF_NT) {
+    for (int t = tid; t < 16 * KS; t += NT) {
         float s = 0.0f;
         if (t < d)
             for (int k = 0; k < 8; ++k) s += coarse[(size_t)((int64_t)k * K >> 3) * d + t];
@@ -232,7 +233,8 @@ __global__ __launch_bounds__(AF_NT, 2) void assign_filter_kernel(const float *__
 #pragma unroll
         for (int it = 0; it < IT; ++it)
 #pragma unroll
-            for (int h = 0; h < 2; ++h) raw[it][h] = load8<VEC>(row, 16 * (part + PS * it) + 8 * h, d);
+            for (int h = 0; h < 2; ++h)
+                if (part + PS * it < KS) raw[it][h] = load8<VEC>(row, 16 * (part + PS * it) + 8 * h, d);
     };
     float cmax = 0.0f;
     auto stash = [&](int c0, int buf) {
@@ -289,9 +291,21 @@ __global__ __launch_bounds__(AF_NT, 2) void assign_filter_kernel(const float *__
             f32x16 acc[NB];
 #pragma unroll
             for (int nb = 0; nb < NB; ++nb) acc[nb] = init;
+            // (the operands of a step are requested two steps ahead)
+            bf16x8 a[3][2];
+#pragma unroll
+            for (int s = 0; s < 2; ++s) {
+                a[s][0] = tile[buf][ct][s][0][lane];
+                a[s][1] = tile[buf][ct][s][1][lane];
+            }
 #pragma unroll
             for (int s = 0; s < KS; ++s) {
-                const bf16x8 ah = tile[buf][ct][s][0][lane], al = tile[buf][ct][s][1][lane];
+                if (s + 2 < KS) {
+                    a[(s + 2) % 3][0] = tile[buf][ct][s + 2][0][lane];
+                    a[(s + 2) % 3][1] = tile[buf][ct][s + 2][1][lane];
+                }
+                const bf16x8 ah = a[s % 3][0], al = a[s % 3][1];
+                __builtin_amdgcn_sched_barrier(0);  // (left to itself the compiler requests them where they are used)
 #pragma unroll
                 for (int nb = 0; nb < NB; ++nb)
                     acc[nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah, bh[nb][s], acc[nb], 0, 0, 0);
@@ -312,7 +326,8 @@ __global__ __launch_bounds__(AF_NT, 2) void assign_filter_kernel(const float *__
                 b3[nb] = fminf(b3[nb], fmaxf(b2[nb], v));
                 b2[nb] = fminf(b2[nb], fmaxf(b1[nb], v));
                 b1[nb] = fminf(b1[nb], v);
-                a2[nb] = l1 ? a1[nb] : (l2 ? g : a2[nb]);
+                const int second = l2 ? g : a2[nb];
+                a2[nb] = l1 ? a1[nb] : second;
                 a1[nb] = l1 ? g : a1[nb];
             }
         }
@@ -329,7 +344,7 @@ __global__ __launch_bounds__(AF_NT, 2) void assign_filter_kernel(const float *__
     if (lane == 0) cmax_s[wave] = cmax;
     __syncthreads();
     cmax = cmax_s[0];
-    for (int k = 1; k < 4; ++k) cmax = cmax_s[k] > cmax || cmax_s[k] != cmax_s[k] ? cmax_s[k] : cmax;
+    for (int k = 1; k < NW; ++k) cmax = cmax_s[k] > cmax || cmax_s[k] != cmax_s[k] ? cmax_s[k] : cmax;
 
     // Bound of |score - (exact distance - |x'|^2)|, with S = |x'|^2 + max |c'|^2 >= 2 |x'| |c'| and D = 16 KS:
     // rounding of the differences 4 S 2^-24; what the splits and the missing lo.lo leave out 3.1 S 2^-18; 3 D + 1
@@ -343,60 +358,109 @@ __global__ __launch_bounds__(AF_NT, 2) void assign_filter_kernel(const float *__
         const float thr = fminf(b1[nb], __shfl_xor(b1[nb], 32)) + margin;
         // (comparisons that a NaN fails)
         const bool sure = S < 1e37f && thr < 1e37f && b3[nb] > thr;
-        const int other = __shfl_xor((int)sure, 32);
-        cand[v][2 * half] = b1[nb] <= thr ? 2 * a1[nb] + half : -1;
-        cand[v][2 * half + 1] = b2[nb] <= thr ? 2 * a2[nb] + half : -1;
-        if (half == 0 && !(sure && other)) {
-            cand[v][0] = -2;
-            if (i0 + v < n) redo[atomicAdd(&nredo, 1)] = v;
+        // this lane's groups in question, then those of the other half; the first entry is never empty
+        // unless the vector has to be measured against all cells
+        const int g1 = b1[nb] <= thr ? 2 * a1[nb] + half : -1, g2 = b2[nb] <= thr ? 2 * a2[nb] + half : -1;
+        const int o1 = __shfl_xor(g1, 32), o2 = __shfl_xor(g2, 32);
+        const bool all = !(sure && __shfl_xor((int)sure, 32));
+        if (half == 0) {
+            cand[v][0] = all ? -2 : g1 >= 0 ? g1 : o1;
+            cand[v][1] = g1 >= 0 ? g2 : o2;
+            cand[v][2] = g1 >= 0 ? o1 : -1;
+            cand[v][3] = g1 >= 0 ? o2 : -1;
+            if (all && i0 + v < n) redo[atomicAdd(&nredo, 1)] = v;
         }
     }
     __syncthreads();
 
-    // the groups in question, by the definition: 16 lanes per vector, a cell each
-    auto dist = [&](const float *xr, const float *cr) {
-        double acc = 0.0;
-        if constexpr (VEC) {
-#pragma unroll 4
-            for (int t = 0; t < d; t += 4) {
-                const float4 a = *reinterpret_cast<const float4 *>(xr + t);
-                const float4 b = *reinterpret_cast<const float4 *>(cr + t);
-                double df = (double)a.x - (double)b.x;
-                acc = fma(df, df, acc);
-                df = (double)a.y - (double)b.y;
-                acc = fma(df, df, acc);
-                df = (double)a.z - (double)b.z;
-                acc = fma(df, df, acc);
-                df = (double)a.w - (double)b.w;
-                acc = fma(df, df, acc);
-            }
-        } else {
-            for (int t = 0; t < d; ++t) {
-                const double df = (double)xr[t] - (double)cr[t];
-                acc = fma(df, df, acc);
-            }
-        }
-        return acc;
-    };
+    // The groups in question, 16 lanes per vector.  One group: its 16 distances in float32, the lanes side by
+    // side along the components (a lane per cell would read 64 different lines per load), and unless a second
+    // one lies within the rounding of the closest that is the cell.  Otherwise by the definition, a lane per cell.
     const int r = tid & 15;
-    for (int v = tid >> 4; v < TM; v += AF_NT / 16) {
+    auto cell_of = [&](int g, int k) { return (g >> 1) * 32 + 8 * (k >> 2) + 4 * (g & 1) + (k & 3); };
+    for (int v = tid >> 4; v < TM; v += NT / 16) {
         const int64_t i = i0 + v;
-        if (i >= n || cand[v][0] == -2) continue;  // uniform over the 16 lanes
-        double bd = __builtin_inf();
-        int bc = 0x7fffffff;
-        for (int k = 0; k < 4; ++k) {
-            const int g = cand[v][k];
-            if (g < 0) continue;
-            const int c = (g >> 1) * 32 + 8 * (r >> 2) + 4 * (g & 1) + (r & 3);
-            if (c >= K) continue;
-            const double dd = dist(x + i * ldx, coarse + (size_t)c * d);
-            if (dd < bd || (dd == bd && c < bc)) { bd = dd; bc = c; }
-        }
+        const int g0 = cand[v][0];
+        if (i >= n || g0 < 0) continue;  // uniform over the 16 lanes
+        const float *xr = x + i * ldx;
+        float xv[KS];
+        constexpr int W = VEC && KS % 4 == 0 ? 4 : 1;  // components per load
 #pragma unroll
-        for (int m = 8; m >= 1; m >>= 1) {
-            const double od = __shfl_xor(bd, m);
-            const int oc = __shfl_xor(bc, m);
-            if (od < bd || (od == bd && oc < bc)) { bd = od; bc = oc; }
+        for (int e = 0; e < KS / W; ++e)
+#pragma unroll
+            for (int u = 0; u < W; ++u) {
+                const int t = W * (r + 16 * e) + u;
+                xv[W * e + u] = VEC || t < d ? xr[t] : 0.0f;
+            }
+        float part[16];
+#pragma unroll
+        for (int k = 0; k < 16; ++k) {
+            const float *cr = coarse + (size_t)min(cell_of(g0, k), K - 1) * d;
+            float acc = 0.0f;
+#pragma unroll
+            for (int e = 0; e < KS / W; ++e) {
+                float cv[W];
+                if constexpr (W == 4) {
+                    const float4 f = *reinterpret_cast<const float4 *>(cr + 4 * (r + 16 * e));
+                    cv[0] = f.x; cv[1] = f.y; cv[2] = f.z; cv[3] = f.w;
+                } else {
+                    const int t = r + 16 * e;
+                    cv[0] = VEC || t < d ? cr[t] : 0.0f;
+                }
+#pragma unroll
+                for (int u = 0; u < W; ++u) {
+                    const float df = xv[W * e + u] - cv[u];
+                    acc = __builtin_fmaf(df, df, acc);
+                }
+            }
+            part[k] = acc;
+        }
+        // sums over the 16 lanes, halving the cells a lane is responsible for: lane r ends with cell r
+#pragma unroll
+        for (int w = 8; w >= 1; w >>= 1)
+#pragma unroll
+            for (int k = 0; k < w; ++k) {
+                const bool up = r & w;
+                const float keep = up ? part[k + w] : part[k], give = up ? part[k] : part[k + w];
+                part[k] = keep + __shfl_xor(give, w);
+            }
+        int bc = cell_of(g0, r);
+        const bool in = bc < K;
+        const float d0 = in ? part[0] : __builtin_inff();
+        float d1 = d0, d2 = __builtin_inff();  // the two smallest of the 16 lanes (NaN: ignored here, caught below)
+        int at = r;
+#pragma unroll
+        for (int w = 8; w >= 1; w >>= 1) {
+            const float o1 = __shfl_xor(d1, w), o2 = __shfl_xor(d2, w);
+            const int oa = __shfl_xor(at, w);
+            d2 = fminf(fmaxf(d1, o1), fminf(d2, o2));
+            at = o1 < d1 ? oa : at;
+            d1 = fminf(d1, o1);
+        }
+        // rounding of two sums of d squares (d / 16 + 4 additions, the differences, the squares), doubled
+        const float close = __builtin_fmaf(d1, 2e-6f + 1e-7f * KS, 1e-33f);
+        if (cand[v][1] < 0 && cand[v][2] < 0 && cand[v][3] < 0 && d1 < 1e37f && d2 > d1 + close) {
+            bc = cell_of(g0, at);
+        } else {
+            double bd = __builtin_inf();
+            bc = 0x7fffffff;
+            for (int e = 0; e < 4; ++e) {
+                const int g = cand[v][e];
+                if (g < 0 || cell_of(g, r) >= K) continue;
+                const float *cr = coarse + (size_t)cell_of(g, r) * d;
+                double dd = 0.0;
+                for (int t = 0; t < d; ++t) {
+                    const double df = (double)xr[t] - (double)cr[t];
+                    dd = fma(df, df, dd);
+                }
+                if (dd < bd || (dd == bd && cell_of(g, r) < bc)) { bd = dd; bc = cell_of(g, r); }
+            }
+#pragma unroll
+            for (int w = 8; w >= 1; w >>= 1) {
+                const double od = __shfl_xor(bd, w);
+                const int oc = __shfl_xor(bc, w);
+                if (od < bd || (od == bd && oc < bc)) { bd = od; bc = oc; }
+            }
         }
         if (r == 0) cells[i] = (accumulate ? cells[i] : 0) + bc * scale;
     }
@@ -413,7 +477,7 @@ __global__ __launch_bounds__(AF_NT, 2) void assign_filter_kernel(const float *__
             bd[k] = __builtin_inf();
             bc[k] = 0x7fffffff;
         }
-        for (int c = tid; c < K; c += AF_NT) {
+        for (int c = tid; c < K; c += NT) {
             const float *cr = coarse + (size_t)c * d;
             double acc[4] = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll 4
@@ -443,7 +507,7 @@ __global__ __launch_bounds__(AF_NT, 2) void assign_filter_kernel(const float *__
         if (tid < 4 && k0 + tid < todo) {
             double d0 = red_d[tid][0];
             int c0 = red_c[tid][0];
-            for (int w = 1; w < 4; ++w)
+            for (int w = 1; w < NW; ++w)
                 if (red_d[tid][w] < d0 || (red_d[tid][w] == d0 && red_c[tid][w] < c0)) {
                     d0 = red_d[tid][w];
                     c0 = red_c[tid][w];
@@ -457,17 +521,23 @@ __global__ __launch_bounds__(AF_NT, 2) void assign_filter_kernel(const float *__
 
 // ------------------------------------------------------------------ host
 
-template <int KS, int NB>
+template <int KS>
 static void launch_filter(const float *coarse, int K, int d, const float *x, int64_t ldx, int64_t n, int32_t *cells,
                           int scale, int accumulate, hipStream_t st)
 {
-    const bool vec = d % 4 == 0 && ldx % 4 == 0 && ((uintptr_t)coarse & 15) == 0 && ((uintptr_t)x & 15) == 0;
-    const dim3 grid((unsigned)ceil_div(n, 4 * NB * 32));
+    const bool vec = d == 16 * KS && ldx % 4 == 0 && ((uintptr_t)coarse & 15) == 0 && ((uintptr_t)x & 15) == 0;
+    if constexpr (KS <= 8)
+        if (vec && n >= 512 * 256) {  // 512 vectors per workgroup once that fills the chip; else 128
+            hipLaunchKernelGGL((assign_filter_kernel<512, KS, 2, true>), dim3((unsigned)ceil_div(n, 512)), dim3(512), 0,
+                               st, coarse, K, d, x, ldx, n, cells, scale, accumulate);
+            return;
+        }
+    const dim3 grid((unsigned)ceil_div(n, 128));
     if (vec)
-        hipLaunchKernelGGL((assign_filter_kernel<KS, NB, true>), grid, dim3(AF_NT), 0, st, coarse, K, d, x, ldx, n,
+        hipLaunchKernelGGL((assign_filter_kernel<256, KS, 1, true>), grid, dim3(256), 0, st, coarse, K, d, x, ldx, n,
                            cells, scale, accumulate);
     else
-        hipLaunchKernelGGL((assign_filter_kernel<KS, NB, false>), grid, dim3(AF_NT), 0, st, coarse, K, d, x, ldx, n,
+        hipLaunchKernelGGL((assign_filter_kernel<256, KS, 1, false>), grid, dim3(256), 0, st, coarse, K, d, x, ldx, n,
                            cells, scale, accumulate);
 }
 
@@ -475,23 +545,16 @@ static void launch_filter(const float *coarse, int K, int d, const float *x, int
 static int assign_pass(const float *coarse, int K, int d, const float *x, int64_t ldx, int64_t n, int32_t *cells,
                        int scale, int accumulate, hipStream_t st)
 {
-    // 256 vectors per workgroup once that fills the chip twice over; half as many below, and above 128
-    // components, where the operands of 64 vectors would not leave registers for a second workgroup
-    const bool big = n >= 2 * 256 * 256;
     if (d <= 32)
-        big ? launch_filter<2, 2>(coarse, K, d, x, ldx, n, cells, scale, accumulate, st)
-            : launch_filter<2, 1>(coarse, K, d, x, ldx, n, cells, scale, accumulate, st);
+        launch_filter<2>(coarse, K, d, x, ldx, n, cells, scale, accumulate, st);
     else if (d <= 64)
-        big ? launch_filter<4, 2>(coarse, K, d, x, ldx, n, cells, scale, accumulate, st)
-            : launch_filter<4, 1>(coarse, K, d, x, ldx, n, cells, scale, accumulate, st);
+        launch_filter<4>(coarse, K, d, x, ldx, n, cells, scale, accumulate, st);
     else if (d <= 96)
-        big ? launch_filter<6, 2>(coarse, K, d, x, ldx, n, cells, scale, accumulate, st)
-            : launch_filter<6, 1>(coarse, K, d, x, ldx, n, cells, scale, accumulate, st);
+        launch_filter<6>(coarse, K, d, x, ldx, n, cells, scale, accumulate, st);
     else if (d <= 128)
-        big ? launch_filter<8, 2>(coarse, K, d, x, ldx, n, cells, scale, accumulate, st)
-            : launch_filter<8, 1>(coarse, K, d, x, ldx, n, cells, scale, accumulate, st);
+        launch_filter<8>(coarse, K, d, x, ldx, n, cells, scale, accumulate, st);
     else if (d <= AF_MAX_D)
-        launch_filter<16, 1>(coarse, K, d, x, ldx, n, cells, scale, accumulate, st);
+        launch_filter<16>(coarse, K, d, x, ldx, n, cells, scale, accumulate, st);
     else
         hipLaunchKernelGGL(assign_f64_kernel, dim3((unsigned)ceil_div(n, ASG_TM)), dim3(256), 0, st, coarse, K, d, x,
                            ldx, n, cells, scale, accumulate);
