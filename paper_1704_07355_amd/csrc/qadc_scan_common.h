@@ -253,9 +253,11 @@ __device__ __forceinline__ float ord2f(unsigned o)
 
 constexpr int MERGE_NT = 1024;
 constexpr int MERGE_CAP = 6144;   // keys staged in LDS
-constexpr int MERGE_WG_PER_THREAD = 8;
-constexpr int MERGE_FLAT_G = 256;        // regions and ...
-constexpr int MERGE_FLAT_SLOTS = 32768;  // ... key slots up to which every slot is visited
+constexpr int MERGE_PER = MERGE_CAP / MERGE_NT;
+constexpr int MERGE_GU = 4;       // regions per thread whose counts are requested together
+constexpr int MERGE_FLAT_G = 512; // regions whose counts are kept in LDS, and ...
+constexpr int MERGE_REP = 16;    // replicas of the histogram of a flat gather (in the memory of lkeys)
+constexpr int MERGE_SLOTS = 24;   // key slots per thread up to which every slot is visited at once
 
 // R best of the keys reported by the G workgroups of each query (64-bit keys
 // dist << 32 | index, at most R per workgroup), ordered; then everything the call wrote
@@ -266,6 +268,13 @@ constexpr int MERGE_FLAT_SLOTS = 32768;  // ... key slots up to which every slot
 // histogram pass over the eight most significant bits in which they differ at all finds the
 // bin of the R-th key; the keys up to that bin are ranked against each other by counting,
 // which selects and orders in one step.  Massive ties fall back to the full radix select.
+//
+// Bound by latency: one workgroup, a chain of round trips to memory written by other XCDs.  So the counts of
+// all regions travel at once, and then all keys at once.  Few regions (inverted-index scans, short databases;
+// often well filled): a slot of a region per thread and register.  Many regions, mostly of a key or two: the
+// places of the keys are laid out in LDS first, from running sums of the counts.  A thread walking its region,
+// or a slot per thread and round trip, took 20.7 us for one inverted-index query (192 regions of up to 100 keys),
+// 14.8 us for 16 queries over 98 regions each, 8.6 us for one query over 2048 regions.
 // Two report regions may exist per query: region B (G workgroups, up to R keys each) written
 // by the single-query kernels, and region A (GA workgroups, up to pitchA keys each) written
 // by the query-tiled kernel.  flags[q]: 0 = region A holds the result of query q; 1 = region A is
@@ -281,11 +290,12 @@ __global__ __launch_bounds__(MERGE_NT) void merge_topk_kernel(
 {
     // need = min(R, number of codes scanned): at least that many keys were reported.
     // ids: the keys' low words are storage positions and out_idx gets ids[position] (inverted index).
-    __shared__ uint64_t lkeys[MERGE_CAP];
+    __shared__ uint64_t lkeys[MERGE_CAP];  // first the places of the keys, then the keys
     __shared__ uint64_t cand[MERGE_NT];
     __shared__ SelectScratch sc;
     __shared__ unsigned lcnt, ccnt;
     __shared__ unsigned long long all_or, all_and;
+    __shared__ unsigned rank_s[MERGE_NT / 2];
     __shared__ unsigned fcnt[MERGE_FLAT_G];
 
     const int tid = threadIdx.x;
@@ -305,28 +315,23 @@ __global__ __launch_bounds__(MERGE_NT) void merge_topk_kernel(
         G = GA;
         pitch = pitchA;
     }
-    // Few, well-filled regions (inverted-index scans, short databases): every slot of every
-    // region is visited, a slot per thread at a time, so that the loads are spread over the whole
-    // workgroup instead of one thread walking each region.
-    const bool flat = G <= MERGE_FLAT_G && (size_t)G * pitch <= (size_t)MERGE_FLAT_SLOTS;  // uniform
-    // every reported key, spread over the threads by workgroup (after the gather below)
+    const unsigned slotsB = (unsigned)G * (unsigned)pitch, slotsA = both ? (unsigned)GA * (unsigned)pitchA : 0u;
+    const bool flat = G <= MERGE_FLAT_G && slotsB + slotsA <= (unsigned)(MERGE_SLOTS * MERGE_NT);  // uniform
+    // every reported key, spread over the threads by region (only where neither the registers nor the LDS hold
+    // the keys, or too many of them tie)
     auto each_key = [&](auto f) {
-        if (flat) {
-            for (unsigned sidx = tid; sidx < (unsigned)G * pitch; sidx += MERGE_NT) {
-                const unsigned g = sidx / (unsigned)pitch, i = sidx - g * (unsigned)pitch;
-                if (i < fcnt[g]) f(lists[sidx]);
-            }
-        }
-        for (int g = tid; g < G && !flat; g += MERGE_NT) {
+        const int step = flat ? MERGE_NT / WAVE : MERGE_NT;  // few regions: a wavefront per region
+        const unsigned i0 = flat ? tid % WAVE : 0, di = flat ? WAVE : 1;
+        for (int g = flat ? tid / WAVE : tid; g < G; g += step) {
             const unsigned c = min(counts[g], (unsigned)pitch);
             const uint64_t *l = lists + (size_t)g * pitch;
-            for (unsigned i = 0; i < c; i += 8) {  // eight loads in flight before the first use
-                uint64_t k[8];
+            for (unsigned i = i0; i < c; i += 4 * di) {  // four loads in flight before the first use
+                uint64_t k[4];
 #pragma unroll
-                for (int u = 0; u < 8; ++u) k[u] = (i + u < c) ? l[i + u] : 0;
+                for (int u = 0; u < 4; ++u) k[u] = (i + u * di < c) ? l[i + u * di] : 0;
 #pragma unroll
-                for (int u = 0; u < 8; ++u)
-                    if (i + u < c) f(k[u]);
+                for (int u = 0; u < 4; ++u)
+                    if (i + u * di < c) f(k[u]);
             }
         }
         if (both) {
@@ -342,80 +347,141 @@ __global__ __launch_bounds__(MERGE_NT) void merge_topk_kernel(
         return ((int64_t)pos < n_ids) ? ids[pos] : 0xffffffffu;
     };
 
-    // Gather, region by region.
     if (tid == 0) { lcnt = 0; ccnt = 0; all_or = 0ull; all_and = ~0ull; }
     for (int i = tid; i < 256; i += MERGE_NT) sc.hist[i] = 0;
+    for (int i = tid; i < MERGE_NT / 2; i += MERGE_NT) rank_s[i] = 0;
     __syncthreads();
-    // Histogram bits.  Integer distances: the distance byte itself, counted while gathering.
-    // Float distances: the eight most significant bits in which the keys differ at all (the
-    // bits above them agree), found from the OR and the AND of all keys, counted afterwards.
+    // Histogram bits.  Integer distances: the distance byte itself.  Float distances: the eight most
+    // significant bits in which the keys differ at all (the bits above them agree), found from the OR and the
+    // AND of all keys.
     constexpr bool ADAPT = sizeof(DistT) != 1;
-    unsigned long long my_or = 0ull, my_and = ~0ull;
-    auto take = [&](uint64_t k) {
-        const unsigned slot = atomicAdd(&lcnt, 1u);
-        if (slot < (unsigned)MERGE_CAP) lkeys[slot] = k;
-        if constexpr (ADAPT) {
-            my_or |= k;
-            my_and &= k;
-        } else {
-            atomicAdd(&sc.hist[(unsigned)(k >> 32) & 255u], 1u);
+    const int lane = lane_id();
+    uint64_t key[MERGE_SLOTS];    // flat: the keys of this thread's slots, ~0 for none
+    unsigned place[MERGE_PER];    // else: where the keys of this thread lie
+    unsigned total;
+    bool in_lds = false;          // the keys (or, of too many, those that matter) are in lkeys
+    // Thousands of keys that differ in a few bins would queue at the same LDS words: 16 replicas, a word apart.
+    unsigned *rep = reinterpret_cast<unsigned *>(lkeys);
+    static_assert(MERGE_REP * 257 * sizeof(unsigned) <= sizeof(lkeys), "replicas of the histogram");
+    auto count = [&](unsigned bin) { atomicAdd(flat ? &rep[(lane % MERGE_REP) * 257 + bin] : &sc.hist[bin], 1u); };
+    auto join_counts = [&]() {  // the whole workgroup, after a barrier
+        if (flat && tid < 256) {
+            unsigned h = 0;
+#pragma unroll
+            for (int r = 0; r < MERGE_REP; ++r) h += rep[r * 257 + tid];
+            sc.hist[tid] = h;
         }
     };
-    unsigned mycnt[MERGE_WG_PER_THREAD];
     if (flat) {
-        for (int g = tid; g < G; g += MERGE_NT) fcnt[g] = min(counts[g], (unsigned)pitch);
-        __syncthreads();
-        for (unsigned sidx = tid; sidx < (unsigned)G * pitch; sidx += MERGE_NT) {
-            const unsigned g = sidx / (unsigned)pitch, i = sidx - g * (unsigned)pitch;
-            if (i < fcnt[g]) take(lists[sidx]);
+        for (int i = tid; i < MERGE_REP * 257; i += MERGE_NT) rep[i] = 0;
+        if (tid < MERGE_FLAT_G) {
+            const unsigned c = tid < G ? min(counts[tid], (unsigned)pitch) : 0u;
+            fcnt[tid] = c;
+            unsigned sum = c;
+            if (both && tid < GA) sum += min(countsA[tid], (unsigned)pitchA);
+#pragma unroll
+            for (int w = 32; w >= 1; w >>= 1) sum += __shfl_xor(sum, w);
+            if (lane == 0 && sum) atomicAdd(&lcnt, sum);
         }
-    } else {
+        __syncthreads();
+        total = lcnt;
 #pragma unroll
-        for (int t = 0; t < MERGE_WG_PER_THREAD; ++t) {
-            const int g = tid + t * MERGE_NT;
-            mycnt[t] = 0;
-            if (g < G) {
-                // count and first key fetched together: most regions hold zero or one key
-                const unsigned c = min(counts[g], (unsigned)pitch);
-                const uint64_t *l = lists + (size_t)g * pitch;
-                const uint64_t k0 = l[0];
-                mycnt[t] = c;
-                if (c) take(k0);
-                for (unsigned i = 1; i < c; i += 4) {  // four loads in flight
-                    uint64_t k[4];
-#pragma unroll
-                    for (int u = 0; u < 4; ++u) k[u] = (i + u < c) ? l[i + u] : 0;
-#pragma unroll
-                    for (int u = 0; u < 4; ++u)
-                        if (i + u < c) take(k[u]);
-                }
+        for (int t = 0; t < MERGE_SLOTS; ++t) {
+            key[t] = ~0ull;
+            if ((unsigned)(t * MERGE_NT) >= slotsB + slotsA) continue;  // uniform
+            const unsigned s = tid + t * MERGE_NT;
+            if (s < slotsB) {
+                const unsigned g = s / (unsigned)pitch;
+                if (s - g * (unsigned)pitch < fcnt[g]) key[t] = lists[s];
+            } else if (s - slotsB < slotsA) {
+                const unsigned sa = s - slotsB, g = sa / (unsigned)pitchA;
+                if (sa - g * (unsigned)pitchA < min(countsA[g], (unsigned)pitchA)) key[t] = listsA[sa];
             }
         }
-        for (int g = tid + MERGE_WG_PER_THREAD * MERGE_NT; g < G; g += MERGE_NT) {  // very wide grids
-            const unsigned c = min(counts[g], (unsigned)pitch);
-            for (unsigned i = 0; i < c; ++i) take(lists[(size_t)g * pitch + i]);
+    } else {
+        // running sums over the wavefront, one atomic per wavefront (the order of the keys does not matter)
+        for (int g0 = 0; g0 < G; g0 += MERGE_GU * MERGE_NT) {  // uniform
+            unsigned c[MERGE_GU], sum = 0;
+#pragma unroll
+            for (int u = 0; u < MERGE_GU; ++u) {
+                const int g = g0 + u * MERGE_NT + tid;
+                c[u] = g < G ? counts[g] : 0u;
+            }
+#pragma unroll
+            for (int u = 0; u < MERGE_GU; ++u) {
+                c[u] = min(c[u], (unsigned)pitch);
+                sum += c[u];
+            }
+            unsigned inc = sum;
+#pragma unroll
+            for (int dd = 1; dd < WAVE; dd <<= 1) {
+                const unsigned up = __shfl_up(inc, dd);
+                if (lane >= dd) inc += up;
+            }
+            unsigned base = 0;
+            if (lane == WAVE - 1 && inc > 0) base = atomicAdd(&lcnt, inc);
+            unsigned at = __shfl(base, WAVE - 1) + inc - sum;
+#pragma unroll
+            for (int u = 0; u < MERGE_GU; ++u) {
+                const unsigned first = (unsigned)(g0 + u * MERGE_NT + tid) * (unsigned)pitch;
+                for (unsigned i = 0; i < c[u] && at + i < (unsigned)MERGE_CAP; ++i) lkeys[at + i] = first + i;
+                at += c[u];
+            }
+        }
+        __syncthreads();
+        total = lcnt;
+        if (both)
+            for (int g = 0; g < GA; ++g) total += min(countsA[g], (unsigned)pitchA);
+        if (total <= (unsigned)MERGE_CAP && !both) {  // uniform
+            in_lds = true;
+#pragma unroll
+            for (int t = 0; t < MERGE_PER; ++t) {
+                const unsigned i = tid + t * MERGE_NT;
+                place[t] = i < total ? (unsigned)lkeys[i] : NO_KEY;
+            }
+#pragma unroll
+            for (int t = 0; t < MERGE_PER; ++t) key[t] = place[t] != NO_KEY ? lists[place[t]] : ~0ull;
+#pragma unroll
+            for (int t = 0; t < MERGE_PER; ++t)
+                if (place[t] != NO_KEY) lkeys[tid + t * MERGE_NT] = key[t];
         }
     }
-    if (both) {  // region A on top of region B (few regions, spread over the whole workgroup)
-        for (int g = 0; g < GA; ++g) {
-            const unsigned c = min(countsA[g], (unsigned)pitchA);
-            for (unsigned i = tid; i < c; i += MERGE_NT) take(listsA[(size_t)g * pitchA + i]);
+    const bool placed = in_lds;                        // place[] is set
+    const int nkey = flat ? MERGE_SLOTS : placed ? MERGE_PER : 0;  // keys of this thread in registers
+    auto own_keys = [&](auto f) {
+#pragma unroll
+        for (int t = 0; t < MERGE_SLOTS; ++t) {
+            if (t >= nkey || (unsigned)(t * MERGE_NT) >= (flat ? slotsB + slotsA : total)) break;  // uniform
+            if (key[t] != ~0ull) f(key[t]);
         }
-    }
+    };
     if constexpr (ADAPT) {
-        if (my_or != 0ull || my_and != ~0ull) {
+        unsigned long long my_or = 0ull, my_and = ~0ull;
+        own_keys([&](uint64_t k) { my_or |= k; my_and &= k; });
+#pragma unroll
+        for (int w = 32; w >= 1; w >>= 1) {
+            my_or |= __shfl_xor(my_or, w);
+            my_and &= __shfl_xor(my_and, w);
+        }
+        if (lane == 0 && (my_or != 0ull || my_and != ~0ull)) {
             atomicOr(&all_or, my_or);
             atomicAnd(&all_and, my_and);
         }
+    } else {
+        auto count_key = [&](uint64_t k) { count((unsigned)(k >> 32) & 255u); };
+        if (nkey) own_keys(count_key);
+        else each_key(count_key);
+        if (flat) {  // uniform
+            __syncthreads();
+            join_counts();
+        }
     }
     __syncthreads();
-    unsigned total = lcnt;
     need = min(need, total);
-    bool in_lds = total <= (unsigned)MERGE_CAP;
     if constexpr (!ADAPT) {
-        // More keys than LDS holds (loose bounds, many regions): the histogram counted all of them, so
-        // the bin of the need-th key is known, and only the keys up to that bin are gathered again.
-        if (!in_lds && need > 0) {  // uniform
+        // More keys than registers and LDS hold (loose bounds, many regions): the histogram counted all of
+        // them, so the bin of the need-th key is known, and only the keys up to that bin are gathered.
+        if (!nkey && need > 0) {  // uniform
             select_bin(&sc, need);
             __syncthreads();
             const unsigned bin = sc.bin;
@@ -438,32 +504,47 @@ __global__ __launch_bounds__(MERGE_NT) void merge_topk_kernel(
         const unsigned long long diff = all_or ^ all_and;
         const int top = diff ? 63 - __clzll((long long)diff) : 7;
         TOP = top > 7 ? top - 7 : 0;
-        if (in_lds)
-            for (unsigned i = tid; i < total; i += MERGE_NT)
-                atomicAdd(&sc.hist[(unsigned)(lkeys[i] >> TOP) & 255u], 1u);
+        own_keys([&](uint64_t k) { count((unsigned)(k >> TOP) & 255u); });
+        __syncthreads();
+        join_counts();
         __syncthreads();
     }
 
     bool done = false;
-    if (need > 0 && in_lds) {
+    if (need > 0 && (nkey || in_lds)) {  // uniform
         // bin of the need-th key by its most significant byte, and the keys up to that bin
         select_bin(&sc, need);
         __syncthreads();
         const unsigned bin = sc.bin;
-        for (unsigned i = tid; i < total; i += MERGE_NT) {
-            const uint64_t k = lkeys[i];
+        auto keep = [&](uint64_t k) {
             if (((unsigned)(k >> TOP) & 255u) <= bin) {
                 const unsigned slot = atomicAdd(&ccnt, 1u);
                 if (slot < (unsigned)MERGE_NT) cand[slot] = k;
             }
+        };
+        if (nkey) {
+            own_keys(keep);
+        } else {
+            for (unsigned i = tid; i < total; i += MERGE_NT) keep(lkeys[i]);
         }
         __syncthreads();
         const unsigned nc = ccnt;
         if (nc <= (unsigned)MERGE_NT) {  // uniform: rank the candidates against each other
+            // each candidate's comparisons are split over as many threads as there are to go round
+            const unsigned span = nc <= 128u ? 128u : nc <= 256u ? 256u : nc <= 512u ? 512u : 1024u;
+            const unsigned parts = MERGE_NT / span, e = tid & (span - 1u), p = tid / span;
+            uint64_t k = ~0ull;
+            unsigned rank = 0;
+            if (e < nc) {
+                k = cand[e];
+                const unsigned hi = nc * (p + 1u) / parts;
+#pragma unroll 4
+                for (unsigned j = nc * p / parts; j < hi; ++j) rank += (cand[j] < k) ? 1u : 0u;
+                if (parts > 1u) atomicAdd(&rank_s[e], rank);  // uniform
+            }
+            __syncthreads();
             if ((unsigned)tid < nc) {
-                const uint64_t k = cand[tid];
-                unsigned rank = 0;
-                for (unsigned j = 0; j < nc; ++j) rank += (cand[j] < k) ? 1u : 0u;
+                if (parts > 1u) rank = rank_s[tid];
                 if (rank < need) {
                     DistT d;
                     if constexpr (sizeof(DistT) == 1) d = (DistT)((k >> 32) & 0xff);
@@ -526,27 +607,21 @@ __global__ __launch_bounds__(MERGE_NT) void merge_topk_kernel(
     // Leave every word this call wrote in the workspace zero again, so that the next call
     // finds clean control blocks wherever its own layout puts them.
     if (flat) {
-        for (unsigned sidx = tid; sidx < (unsigned)G * pitch; sidx += MERGE_NT) {
-            const unsigned g = sidx / (unsigned)pitch, i = sidx - g * (unsigned)pitch;
-            if (i < fcnt[g]) lists[sidx] = 0;
-        }
-        for (int g = tid; g < G; g += MERGE_NT)
-            if (fcnt[g]) counts[g] = 0;
-    } else {
 #pragma unroll
-        for (int t = 0; t < MERGE_WG_PER_THREAD; ++t) {
-            const int g = tid + t * MERGE_NT;
-            if (g < G && mycnt[t]) {
-                for (unsigned i = 0; i < mycnt[t]; ++i) lists[(size_t)g * pitch + i] = 0;
-                counts[g] = 0;
-            }
-        }
-        for (int g = tid + MERGE_WG_PER_THREAD * MERGE_NT; g < G; g += MERGE_NT) {
+        for (int t = 0; t < MERGE_SLOTS; ++t)
+            if (key[t] != ~0ull && tid + t * MERGE_NT < (int)slotsB) lists[tid + t * MERGE_NT] = 0;
+    } else if (placed) {
+#pragma unroll
+        for (int t = 0; t < MERGE_PER; ++t)
+            if (place[t] != NO_KEY) lists[place[t]] = 0;
+    } else {
+        for (int g = tid; g < G; g += MERGE_NT) {
             const unsigned c = min(counts[g], (unsigned)pitch);
             for (unsigned i = 0; i < c; ++i) lists[(size_t)g * pitch + i] = 0;
-            if (c) counts[g] = 0;
         }
+        __syncthreads();
     }
+    for (int g = tid; g < G; g += MERGE_NT) counts[g] = 0;
     if (redone || both) {  // the abandoned report of the tiled kernel, or the second half of the result
         __syncthreads();  // (both: every thread is done reading region A)
         for (int g = 0; g < GA; ++g) {
