@@ -552,7 +552,8 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(B >= SIXBIT 
 struct ScanPlan {
     int B, NT, G, qbatch;
     bool wide;            // 8-bit components (QADC_U8_8BIT): a code byte is one component
-    bool tiled;           // batches go through the query-tiled kernel
+    bool tiled;           // batches go through a query-tiled kernel
+    int tiled_min;        // (sub-)batches from this size
     TiledPlan t;
     size_t countsA_off, listsA_off, taus_off, flags_off;
     int64_t chunk;
@@ -578,7 +579,17 @@ static bool make_scan_plan(int variant, int64_t n, int m, int nq, int R, ScanPla
     const int64_t tiles = n > 0 ? ceil_div(n, tile) : 1;
     // every workgroup takes tiles g, g+G, ...; its tiles must number below 2^24 / tile, the
     // range of the index bits of a candidate key
-    int64_t G = knob_or(knobs().scan_wgs, 2048);
+    // 2048 workgroups per query for a single one; several share the GPU, and fewer, longer workgroups
+    // set up fewer tables and leave the merge fewer regions (us per call with 2048 each / this rule, 128
+    // components: 3 M codes m = 32: 2 queries 39.9 / 38.7, 4 63.9 / 60.1, 6 87 / 83; m = 64, whose tables
+    // are twice as large: 1 query 48.4 / 43.8, 2 80 / 65, 4 142 / 104; 20 M codes m = 16, 6 queries: 174 / 139)
+    int64_t g_def = 2048;
+    for (int64_t k = p->B == 32 ? 1 : 2; (p->B == 32 ? k < 2 * (int64_t)nq : k <= 2 * ((int64_t)nq - 1)) && g_def > 256; k *= 2)
+        g_def /= 2;
+    // (a power of two: the workgroups of all queries that read a tile then sit on one CU and march together; 248
+    // instead of 256 cost 4 queries of m = 64 13 %.  With two tiles a workgroup the same number for each counts more.)
+    if (nq > 1 && tiles > g_def && tiles < 3 * g_def) g_def = ceil_div(tiles, (tiles + g_def / 2) / g_def);
+    int64_t G = knob_or(knobs().scan_wgs, (int)g_def);
     if (G < 1) G = 1;
     if (G > tiles) G = tiles;
     const int64_t max_tiles_per_wg = ((1ll << 24) - 1) / tile;
@@ -609,8 +620,12 @@ static bool make_scan_plan(int variant, int64_t n, int m, int nq, int R, ScanPla
         if (fl > R) fl = R;
         p->flush_need = (unsigned)fl;
     }
-    p->tiled = !six && p->seed_wgs > 0 && nq >= TILED_MIN_Q && knob_or(knobs().tiled, 1) != 0 &&
-               make_tiled_plan(n, m, nq, !p->wide, &p->t);
+    // (4-bit codes of 8 bytes and more: batches go to the matrix-core kernel once that pays, and to the
+    // per-query kernels below that; 4-byte codes and 8-bit components have the byte-lane kernels as well)
+    const bool wants = !six && p->seed_wgs > 0 && knob_or(knobs().tiled, 1) != 0;
+    p->tiled_min = (!p->wide && p->B >= 8) ? 2 : TILED_MIN_Q;
+    p->tiled = wants && nq >= p->tiled_min && make_tiled_plan(n, m, nq, !p->wide, &p->t) &&
+               (p->wide || p->B < 8 || p->t.mfma || tiled_bytes_pay(p->B, n, nq));
     if (p->tiled && p->G > 256) p->G = 256;  // the single-query kernel only redoes rare queries
     const ScanLayout l = scan_layout(p->G, R);
     p->counts_off = l.counts_off;
@@ -649,7 +664,9 @@ static int dispatch_seed_u8(const ScanPlan &p, const uint8_t *codes, int64_t n,
                             const uint8_t *qluts, int nq, int cap, int R, char *ws, hipStream_t st)
 {
     // batches that the query-tiled kernels scan are sampled in the query-tiled way too
-    if (p.tiled && nq >= TILED_MIN_Q && knob_or(knobs().tiled_seed, 1) != 0) {
+    // (not 32-byte codes: their tables for eight queries fill the LDS and are interleaved by every workgroup;
+    // 3 M codes: 12 queries 112 against 152 us per call, 64 queries 212 against 279)
+    if (p.tiled && nq >= TILED_MIN_Q && knob_or(knobs().tiled_seed, p.B < 32 || p.wide) != 0) {
         const int cpt = (p.B <= 16) ? SCAN_VEC * (16 / p.B) : 1;
         // (at most 512 sample tiles unless QADC_SEED_WGS says otherwise: N = 1e8, m = 32, 256 queries: 1024
         // tiles 0.42 ms of sampling, 512 tiles 0.22 ms and 0.07 ms more in the scan, 256 tiles 0.12 and 0.21)
@@ -716,7 +733,7 @@ static int scan_and_merge_u8(const ScanPlan &p, const uint8_t *codes, int64_t n,
                              hipStream_t st)
 {
     unsigned *flags = nullptr;
-    if (p.tiled && nb >= TILED_MIN_Q) {
+    if (p.tiled && nb >= p.tiled_min) {
         unsigned *taus = reinterpret_cast<unsigned *>(ws + p.taus_off);
         flags = reinterpret_cast<unsigned *>(ws + p.flags_off);
         const int rc = run_tiled_scan(p.t, codes, n, nb, nbins, R, taus, ws, p.stride, p.countsA_off,
@@ -726,7 +743,7 @@ static int scan_and_merge_u8(const ScanPlan &p, const uint8_t *codes, int64_t n,
     if (p.NT == 1024) dispatch_scan_u8<1024>(p, codes, n, qluts, nb, nbins, R, ws, flags, st);
     else if (p.NT == 512) dispatch_scan_u8<512>(p, codes, n, qluts, nb, nbins, R, ws, flags, st);
     else dispatch_scan_u8<256>(p, codes, n, qluts, nb, nbins, R, ws, flags, st);
-    return launch_merge<uint8_t, 5>(nb, st, ws, p.stride, p.counts_off, p.lists_off, p.G,
+    return launch_merge<uint8_t, 5>(nb, st, p.seed_wgs == 0, ws, p.stride, p.counts_off, p.lists_off, p.G,
                                     (unsigned)min((int64_t)R, n), R, (uint8_t)nbins, out_idx, out_dist,
                                     p.countsA_off, p.listsA_off, flags ? p.t.GC : 0, (int)TILED_LCAP, flags,
                                     (const uint32_t *)nullptr, (int64_t)0);
@@ -810,7 +827,7 @@ int search_u8(const float *codebooks, int d, int m, const float *queries, int nq
         const int nb = min(p.qbatch, nq - q0);
         const float *yq = queries + (size_t)q0 * d;
         uint8_t *ql_out = qluts_out ? qluts_out + (size_t)q0 * m * 16 : nullptr;
-        if (p.seed_wgs > 0 && nb < TILED_MIN_Q) {
+        if (p.seed_wgs > 0 && nb < TILED_MIN_Q && !(p.tiled && nb >= p.tiled_min)) {
             // few queries: one launch; every sampling workgroup recomputes the tables it needs
             dim3 grid(p.seed_wgs, nb);
 #define QADC_PREP_CASE(B_)                                                                            \

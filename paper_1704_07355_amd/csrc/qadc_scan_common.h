@@ -253,11 +253,9 @@ __device__ __forceinline__ float ord2f(unsigned o)
 
 constexpr int MERGE_NT = 1024;
 constexpr int MERGE_CAP = 6144;   // keys staged in LDS
-constexpr int MERGE_PER = MERGE_CAP / MERGE_NT;
-constexpr int MERGE_GU = 4;       // regions per thread whose counts are requested together
-constexpr int MERGE_FLAT_G = 512; // regions whose counts are kept in LDS, and ...
-constexpr int MERGE_REP = 16;    // replicas of the histogram of a flat gather (in the memory of lkeys)
-constexpr int MERGE_SLOTS = 24;   // key slots per thread up to which every slot is visited at once
+constexpr int MERGE_WG_PER_THREAD = 8;
+constexpr int MERGE_FLAT_G = 256;        // regions and ...
+constexpr int MERGE_FLAT_SLOTS = 32768;  // ... key slots up to which every slot is visited
 
 // R best of the keys reported by the G workgroups of each query (64-bit keys
 // dist << 32 | index, at most R per workgroup), ordered; then everything the call wrote
@@ -268,13 +266,6 @@ constexpr int MERGE_SLOTS = 24;   // key slots per thread up to which every slot
 // histogram pass over the eight most significant bits in which they differ at all finds the
 // bin of the R-th key; the keys up to that bin are ranked against each other by counting,
 // which selects and orders in one step.  Massive ties fall back to the full radix select.
-//
-// Bound by latency: one workgroup, a chain of round trips to memory written by other XCDs.  So the counts of
-// all regions travel at once, and then all keys at once.  Few regions (inverted-index scans, short databases;
-// often well filled): a slot of a region per thread and register.  Many regions, mostly of a key or two: the
-// places of the keys are laid out in LDS first, from running sums of the counts.  A thread walking its region,
-// or a slot per thread and round trip, took 20.7 us for one inverted-index query (192 regions of up to 100 keys),
-// 14.8 us for 16 queries over 98 regions each, 8.6 us for one query over 2048 regions.
 // Two report regions may exist per query: region B (G workgroups, up to R keys each) written
 // by the single-query kernels, and region A (GA workgroups, up to pitchA keys each) written
 // by the query-tiled kernel.  flags[q]: 0 = region A holds the result of query q; 1 = region A is
@@ -290,12 +281,11 @@ __global__ __launch_bounds__(MERGE_NT) void merge_topk_kernel(
 {
     // need = min(R, number of codes scanned): at least that many keys were reported.
     // ids: the keys' low words are storage positions and out_idx gets ids[position] (inverted index).
-    __shared__ uint64_t lkeys[MERGE_CAP];  // first the places of the keys, then the keys
+    __shared__ uint64_t lkeys[MERGE_CAP];
     __shared__ uint64_t cand[MERGE_NT];
     __shared__ SelectScratch sc;
     __shared__ unsigned lcnt, ccnt;
     __shared__ unsigned long long all_or, all_and;
-    __shared__ unsigned rank_s[MERGE_NT / 2];
     __shared__ unsigned fcnt[MERGE_FLAT_G];
 
     const int tid = threadIdx.x;
@@ -315,8 +305,301 @@ __global__ __launch_bounds__(MERGE_NT) void merge_topk_kernel(
         G = GA;
         pitch = pitchA;
     }
-    const unsigned slotsB = (unsigned)G * (unsigned)pitch, slotsA = both ? (unsigned)GA * (unsigned)pitchA : 0u;
-    const bool flat = G <= MERGE_FLAT_G && slotsB + slotsA <= (unsigned)(MERGE_SLOTS * MERGE_NT);  // uniform
+    // Few, well-filled regions (inverted-index scans, short databases): every slot of every
+    // region is visited, a slot per thread at a time, so that the loads are spread over the whole
+    // workgroup instead of one thread walking each region.
+    const bool flat = G <= MERGE_FLAT_G && (size_t)G * pitch <= (size_t)MERGE_FLAT_SLOTS;  // uniform
+    // every reported key, spread over the threads by workgroup (after the gather below)
+    auto each_key = [&](auto f) {
+        if (flat) {
+            for (unsigned sidx = tid; sidx < (unsigned)G * pitch; sidx += MERGE_NT) {
+                const unsigned g = sidx / (unsigned)pitch, i = sidx - g * (unsigned)pitch;
+                if (i < fcnt[g]) f(lists[sidx]);
+            }
+        }
+        for (int g = tid; g < G && !flat; g += MERGE_NT) {
+            const unsigned c = min(counts[g], (unsigned)pitch);
+            const uint64_t *l = lists + (size_t)g * pitch;
+            for (unsigned i = 0; i < c; i += 8) {  // eight loads in flight before the first use
+                uint64_t k[8];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) k[u] = (i + u < c) ? l[i + u] : 0;
+#pragma unroll
+                for (int u = 0; u < 8; ++u)
+                    if (i + u < c) f(k[u]);
+            }
+        }
+        if (both) {
+            for (int g = 0; g < GA; ++g) {
+                const unsigned c = min(countsA[g], (unsigned)pitchA);
+                for (unsigned i = tid; i < c; i += MERGE_NT) f(listsA[(size_t)g * pitchA + i]);
+            }
+        }
+    };
+
+    auto index_of = [&](uint32_t pos) -> uint32_t {
+        if (!ids) return pos;
+        return ((int64_t)pos < n_ids) ? ids[pos] : 0xffffffffu;
+    };
+
+    // Gather, region by region.
+    if (tid == 0) { lcnt = 0; ccnt = 0; all_or = 0ull; all_and = ~0ull; }
+    for (int i = tid; i < 256; i += MERGE_NT) sc.hist[i] = 0;
+    __syncthreads();
+    // Histogram bits.  Integer distances: the distance byte itself, counted while gathering.
+    // Float distances: the eight most significant bits in which the keys differ at all (the
+    // bits above them agree), found from the OR and the AND of all keys, counted afterwards.
+    constexpr bool ADAPT = sizeof(DistT) != 1;
+    unsigned long long my_or = 0ull, my_and = ~0ull;
+    auto take = [&](uint64_t k) {
+        const unsigned slot = atomicAdd(&lcnt, 1u);
+        if (slot < (unsigned)MERGE_CAP) lkeys[slot] = k;
+        if constexpr (ADAPT) {
+            my_or |= k;
+            my_and &= k;
+        } else {
+            atomicAdd(&sc.hist[(unsigned)(k >> 32) & 255u], 1u);
+        }
+    };
+    unsigned mycnt[MERGE_WG_PER_THREAD];
+    if (flat) {
+        for (int g = tid; g < G; g += MERGE_NT) fcnt[g] = min(counts[g], (unsigned)pitch);
+        __syncthreads();
+        for (unsigned sidx = tid; sidx < (unsigned)G * pitch; sidx += MERGE_NT) {
+            const unsigned g = sidx / (unsigned)pitch, i = sidx - g * (unsigned)pitch;
+            if (i < fcnt[g]) take(lists[sidx]);
+        }
+    } else {
+#pragma unroll
+        for (int t = 0; t < MERGE_WG_PER_THREAD; ++t) {
+            const int g = tid + t * MERGE_NT;
+            mycnt[t] = 0;
+            if (g < G) {
+                // count and first key fetched together: most regions hold zero or one key
+                const unsigned c = min(counts[g], (unsigned)pitch);
+                const uint64_t *l = lists + (size_t)g * pitch;
+                const uint64_t k0 = l[0];
+                mycnt[t] = c;
+                if (c) take(k0);
+                for (unsigned i = 1; i < c; i += 4) {  // four loads in flight
+                    uint64_t k[4];
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) k[u] = (i + u < c) ? l[i + u] : 0;
+#pragma unroll
+                    for (int u = 0; u < 4; ++u)
+                        if (i + u < c) take(k[u]);
+                }
+            }
+        }
+        for (int g = tid + MERGE_WG_PER_THREAD * MERGE_NT; g < G; g += MERGE_NT) {  // very wide grids
+            const unsigned c = min(counts[g], (unsigned)pitch);
+            for (unsigned i = 0; i < c; ++i) take(lists[(size_t)g * pitch + i]);
+        }
+    }
+    if (both) {  // region A on top of region B (few regions, spread over the whole workgroup)
+        for (int g = 0; g < GA; ++g) {
+            const unsigned c = min(countsA[g], (unsigned)pitchA);
+            for (unsigned i = tid; i < c; i += MERGE_NT) take(listsA[(size_t)g * pitchA + i]);
+        }
+    }
+    if constexpr (ADAPT) {
+        if (my_or != 0ull || my_and != ~0ull) {
+            atomicOr(&all_or, my_or);
+            atomicAnd(&all_and, my_and);
+        }
+    }
+    __syncthreads();
+    unsigned total = lcnt;
+    need = min(need, total);
+    bool in_lds = total <= (unsigned)MERGE_CAP;
+    if constexpr (!ADAPT) {
+        // More keys than LDS holds (loose bounds, many regions): the histogram counted all of them, so
+        // the bin of the need-th key is known, and only the keys up to that bin are gathered again.
+        if (!in_lds && need > 0) {  // uniform
+            select_bin(&sc, need);
+            __syncthreads();
+            const unsigned bin = sc.bin;
+            const unsigned upto = need - sc.need + sc.hist[bin];  // keys in the bins up to `bin`
+            __syncthreads();
+            if (upto <= (unsigned)MERGE_CAP) {
+                if (tid == 0) lcnt = 0;
+                __syncthreads();
+                each_key([&](uint64_t k) {
+                    if (((unsigned)(k >> 32) & 255u) <= bin) lkeys[atomicAdd(&lcnt, 1u)] = k;
+                });
+                __syncthreads();
+                total = upto;
+                in_lds = true;
+            }
+        }
+    }
+    int TOP = 32;
+    if constexpr (ADAPT) {
+        const unsigned long long diff = all_or ^ all_and;
+        const int top = diff ? 63 - __clzll((long long)diff) : 7;
+        TOP = top > 7 ? top - 7 : 0;
+        if (in_lds)
+            for (unsigned i = tid; i < total; i += MERGE_NT)
+                atomicAdd(&sc.hist[(unsigned)(lkeys[i] >> TOP) & 255u], 1u);
+        __syncthreads();
+    }
+
+    bool done = false;
+    if (need > 0 && in_lds) {
+        // bin of the need-th key by its most significant byte, and the keys up to that bin
+        select_bin(&sc, need);
+        __syncthreads();
+        const unsigned bin = sc.bin;
+        for (unsigned i = tid; i < total; i += MERGE_NT) {
+            const uint64_t k = lkeys[i];
+            if (((unsigned)(k >> TOP) & 255u) <= bin) {
+                const unsigned slot = atomicAdd(&ccnt, 1u);
+                if (slot < (unsigned)MERGE_NT) cand[slot] = k;
+            }
+        }
+        __syncthreads();
+        const unsigned nc = ccnt;
+        if (nc <= (unsigned)MERGE_NT) {  // uniform: rank the candidates against each other
+            if ((unsigned)tid < nc) {
+                const uint64_t k = cand[tid];
+                unsigned rank = 0;
+                for (unsigned j = 0; j < nc; ++j) rank += (cand[j] < k) ? 1u : 0u;
+                if (rank < need) {
+                    DistT d;
+                    if constexpr (sizeof(DistT) == 1) d = (DistT)((k >> 32) & 0xff);
+                    else d = ord2f((unsigned)(k >> 32));
+                    out_idx[(size_t)q * R + rank] = index_of((uint32_t)k);
+                    out_dist[(size_t)q * R + rank] = d;
+                }
+            }
+            done = true;
+        }
+        __syncthreads();
+    }
+
+    if (need > 0 && !done) {
+        // full radix select, then order the winners by rank
+        uint64_t kth;
+        if (in_lds) kth = block_radix_select<uint64_t, KBYTES>(lkeys, total, need, &sc);
+        else kth = block_radix_select_each<uint64_t, KBYTES>(each_key, need, &sc);
+        __syncthreads();
+        uint64_t mine[MERGE_CAP / MERGE_NT];
+        if (in_lds) {
+#pragma unroll
+            for (int t = 0; t < MERGE_CAP / MERGE_NT; ++t) {
+                const unsigned i = tid + t * MERGE_NT;
+                mine[t] = (i < total) ? lkeys[i] : ~0ull;
+            }
+        }
+        if (tid == 0) lcnt = 0;
+        __syncthreads();
+        if (in_lds) {
+#pragma unroll
+            for (int t = 0; t < MERGE_CAP / MERGE_NT; ++t) {
+                const unsigned i = tid + t * MERGE_NT;
+                const bool ok = (i < total) && mine[t] <= kth;
+                const unsigned slot = wave_append_slot(ok, &lcnt);
+                if (ok) lkeys[slot] = mine[t];
+            }
+        } else {
+            each_key([&](uint64_t k) {
+                if (k <= kth) lkeys[atomicAdd(&lcnt, 1u)] = k;  // exactly `need` keys: they are unique
+            });
+        }
+        __syncthreads();
+        for (unsigned i = tid; i < need; i += MERGE_NT) {
+            const uint64_t k = lkeys[i];
+            unsigned rank = 0;
+            for (unsigned j = 0; j < need; ++j) rank += (lkeys[j] < k) ? 1u : 0u;
+            DistT d;
+            if constexpr (sizeof(DistT) == 1) d = (DistT)((k >> 32) & 0xff);
+            else d = ord2f((unsigned)(k >> 32));
+            out_idx[(size_t)q * R + rank] = index_of((uint32_t)k);
+            out_dist[(size_t)q * R + rank] = d;
+        }
+    }
+    for (unsigned i = need + tid; i < (unsigned)R; i += MERGE_NT) {
+        out_idx[(size_t)q * R + i] = 0xffffffffu;
+        out_dist[(size_t)q * R + i] = pad_dist;
+    }
+
+    // Leave every word this call wrote in the workspace zero again, so that the next call
+    // finds clean control blocks wherever its own layout puts them.
+    if (flat) {
+        for (unsigned sidx = tid; sidx < (unsigned)G * pitch; sidx += MERGE_NT) {
+            const unsigned g = sidx / (unsigned)pitch, i = sidx - g * (unsigned)pitch;
+            if (i < fcnt[g]) lists[sidx] = 0;
+        }
+        for (int g = tid; g < G; g += MERGE_NT)
+            if (fcnt[g]) counts[g] = 0;
+    } else {
+#pragma unroll
+        for (int t = 0; t < MERGE_WG_PER_THREAD; ++t) {
+            const int g = tid + t * MERGE_NT;
+            if (g < G && mycnt[t]) {
+                for (unsigned i = 0; i < mycnt[t]; ++i) lists[(size_t)g * pitch + i] = 0;
+                counts[g] = 0;
+            }
+        }
+        for (int g = tid + MERGE_WG_PER_THREAD * MERGE_NT; g < G; g += MERGE_NT) {
+            const unsigned c = min(counts[g], (unsigned)pitch);
+            for (unsigned i = 0; i < c; ++i) lists[(size_t)g * pitch + i] = 0;
+            if (c) counts[g] = 0;
+        }
+    }
+    if (redone || both) {  // the abandoned report of the tiled kernel, or the second half of the result
+        __syncthreads();  // (both: every thread is done reading region A)
+        for (int g = 0; g < GA; ++g) {
+            const unsigned c = min(countsA[g], (unsigned)pitchA);
+            for (unsigned i = tid; i < c; i += MERGE_NT) listsA[(size_t)g * pitchA + i] = 0;
+        }
+        __syncthreads();
+        for (int g = tid; g < GA; g += MERGE_NT) countsA[g] = 0;
+        if (tid == 0) flags[q] = 0;
+    }
+    unsigned *z = reinterpret_cast<unsigned *>(hdr);
+    for (int i = tid; i < (int)(sizeof(ScanHeader) / 4); i += MERGE_NT) z[i] = 0;
+}
+
+constexpr int MERGE_PER = MERGE_CAP / MERGE_NT;
+constexpr int MERGE_GU = 4;       // regions per thread whose counts are requested together
+constexpr int MERGE_REP = 16;    // replicas of the histogram of a flat gather (in the memory of lkeys)
+constexpr int MERGE_SLOTS = 25;   // key slots per thread up to which every slot is visited at once (256 regions of 100)
+constexpr int MERGE_GATHER_R = 128;
+
+// The same for calls whose keys are in one region set (no flags) and many for their number of regions, or whose
+// keys are 64 bits of distance and index; R <= MERGE_GATHER_R.  Bound by latency: one workgroup, a chain of round
+// trips to memory written by other XCDs.  So the counts of all regions travel at once, and then all keys at once.
+// flat: regions that are mostly full (short databases without a sampled bound; the few workgroups of an
+// inverted-index query): a slot of a region per thread and register, thousands of keys in a few bins counted in 16
+// replicas of the histogram.  Else the places of the keys are laid out in LDS first, from running sums of the
+// counts.  Against the kernel above: 14.1 / 20.7 us for one inverted-index query (192 regions of up to 100 keys),
+// 10.7 / 14.8 us for 16 queries over 98 regions, 9.6 / 18.7 us for a float scan of 50 M codes (1024 regions); with a
+// sampled bound and 8-bit sums, or with R = 1000, the kernel above is the faster one by 1 to 3 us or more.
+template <typename DistT, int KBYTES>
+__global__ __launch_bounds__(MERGE_NT) void merge_gather_kernel(
+    char *__restrict__ ws, size_t ws_stride, size_t counts_off, size_t lists_off, int G,
+    unsigned need, int R, DistT pad_dist, uint32_t *__restrict__ out_idx,
+    DistT *__restrict__ out_dist, const uint32_t *__restrict__ ids, int64_t n_ids, int flat_i)
+{
+    // need = min(R, number of codes scanned): at least that many keys were reported.
+    // ids: the keys' low words are storage positions and out_idx gets ids[position] (inverted index).
+    __shared__ uint64_t lkeys[MERGE_CAP];  // first the places of the keys, then the keys
+    __shared__ uint64_t cand[MERGE_NT];
+    __shared__ SelectScratch sc;
+    __shared__ unsigned lcnt, ccnt;
+    __shared__ unsigned long long all_or, all_and;
+    __shared__ unsigned rank_s[MERGE_NT / 2];
+    __shared__ unsigned fcnt[MERGE_FLAT_G];
+
+    const int tid = threadIdx.x;
+    const int q = blockIdx.x;
+    ScanHeader *hdr = reinterpret_cast<ScanHeader *>(ws + (size_t)q * ws_stride);
+    unsigned *counts = reinterpret_cast<unsigned *>(ws + (size_t)q * ws_stride + counts_off);
+    uint64_t *lists = reinterpret_cast<uint64_t *>(ws + (size_t)q * ws_stride + lists_off);
+    const int pitch = R;
+    const bool flat = flat_i != 0;  // uniform
+    const unsigned slots = (unsigned)G * (unsigned)R;
     // every reported key, spread over the threads by region (only where neither the registers nor the LDS hold
     // the keys, or too many of them tie)
     auto each_key = [&](auto f) {
@@ -332,12 +615,6 @@ __global__ __launch_bounds__(MERGE_NT) void merge_topk_kernel(
 #pragma unroll
                 for (int u = 0; u < 4; ++u)
                     if (i + u * di < c) f(k[u]);
-            }
-        }
-        if (both) {
-            for (int g = 0; g < GA; ++g) {
-                const unsigned c = min(countsA[g], (unsigned)pitchA);
-                for (unsigned i = tid; i < c; i += MERGE_NT) f(listsA[(size_t)g * pitchA + i]);
             }
         }
     };
@@ -378,7 +655,6 @@ __global__ __launch_bounds__(MERGE_NT) void merge_topk_kernel(
             const unsigned c = tid < G ? min(counts[tid], (unsigned)pitch) : 0u;
             fcnt[tid] = c;
             unsigned sum = c;
-            if (both && tid < GA) sum += min(countsA[tid], (unsigned)pitchA);
 #pragma unroll
             for (int w = 32; w >= 1; w >>= 1) sum += __shfl_xor(sum, w);
             if (lane == 0 && sum) atomicAdd(&lcnt, sum);
@@ -388,15 +664,10 @@ __global__ __launch_bounds__(MERGE_NT) void merge_topk_kernel(
 #pragma unroll
         for (int t = 0; t < MERGE_SLOTS; ++t) {
             key[t] = ~0ull;
-            if ((unsigned)(t * MERGE_NT) >= slotsB + slotsA) continue;  // uniform
+            if ((unsigned)(t * MERGE_NT) >= slots) continue;  // uniform
             const unsigned s = tid + t * MERGE_NT;
-            if (s < slotsB) {
-                const unsigned g = s / (unsigned)pitch;
-                if (s - g * (unsigned)pitch < fcnt[g]) key[t] = lists[s];
-            } else if (s - slotsB < slotsA) {
-                const unsigned sa = s - slotsB, g = sa / (unsigned)pitchA;
-                if (sa - g * (unsigned)pitchA < min(countsA[g], (unsigned)pitchA)) key[t] = listsA[sa];
-            }
+            const unsigned g = s / (unsigned)pitch;
+            if (s < slots && s - g * (unsigned)pitch < fcnt[g]) key[t] = lists[s];
         }
     } else {
         // running sums over the wavefront, one atomic per wavefront (the order of the keys does not matter)
@@ -430,9 +701,7 @@ __global__ __launch_bounds__(MERGE_NT) void merge_topk_kernel(
         }
         __syncthreads();
         total = lcnt;
-        if (both)
-            for (int g = 0; g < GA; ++g) total += min(countsA[g], (unsigned)pitchA);
-        if (total <= (unsigned)MERGE_CAP && !both) {  // uniform
+        if (total <= (unsigned)MERGE_CAP) {  // uniform
             in_lds = true;
 #pragma unroll
             for (int t = 0; t < MERGE_PER; ++t) {
@@ -451,7 +720,7 @@ __global__ __launch_bounds__(MERGE_NT) void merge_topk_kernel(
     auto own_keys = [&](auto f) {
 #pragma unroll
         for (int t = 0; t < MERGE_SLOTS; ++t) {
-            if (t >= nkey || (unsigned)(t * MERGE_NT) >= (flat ? slotsB + slotsA : total)) break;  // uniform
+            if (t >= nkey || (unsigned)(t * MERGE_NT) >= (flat ? slots : total)) break;  // uniform
             if (key[t] != ~0ull) f(key[t]);
         }
     };
@@ -609,7 +878,7 @@ __global__ __launch_bounds__(MERGE_NT) void merge_topk_kernel(
     if (flat) {
 #pragma unroll
         for (int t = 0; t < MERGE_SLOTS; ++t)
-            if (key[t] != ~0ull && tid + t * MERGE_NT < (int)slotsB) lists[tid + t * MERGE_NT] = 0;
+            if (key[t] != ~0ull) lists[tid + t * MERGE_NT] = 0;
     } else if (placed) {
 #pragma unroll
         for (int t = 0; t < MERGE_PER; ++t)
@@ -622,26 +891,26 @@ __global__ __launch_bounds__(MERGE_NT) void merge_topk_kernel(
         __syncthreads();
     }
     for (int g = tid; g < G; g += MERGE_NT) counts[g] = 0;
-    if (redone || both) {  // the abandoned report of the tiled kernel, or the second half of the result
-        __syncthreads();  // (both: every thread is done reading region A)
-        for (int g = 0; g < GA; ++g) {
-            const unsigned c = min(countsA[g], (unsigned)pitchA);
-            for (unsigned i = tid; i < c; i += MERGE_NT) listsA[(size_t)g * pitchA + i] = 0;
-        }
-        __syncthreads();
-        for (int g = tid; g < GA; g += MERGE_NT) countsA[g] = 0;
-        if (tid == 0) flags[q] = 0;
-    }
     unsigned *z = reinterpret_cast<unsigned *>(hdr);
     for (int i = tid; i < (int)(sizeof(ScanHeader) / 4); i += MERGE_NT) z[i] = 0;
 }
 
-// One merge workgroup per query.
-template <typename DistT, int KBYTES, typename... Args>
-inline int launch_merge(int nq, hipStream_t st, Args... args)
+// One merge workgroup per query.  filled: the regions are expected to be mostly full (no sampled bound, or the few
+// long workgroups of an inverted-index query).
+template <typename DistT, int KBYTES>
+inline int launch_merge(int nq, hipStream_t st, bool filled, char *ws, size_t ws_stride, size_t counts_off,
+                        size_t lists_off, int G, unsigned need, int R, DistT pad_dist, uint32_t *out_idx, DistT *out_dist,
+                        size_t countsA_off, size_t listsA_off, int GA, int pitchA, unsigned *flags, const uint32_t *ids,
+                        int64_t n_ids)
 {
-    launch(QADC_PROF_MERGE, (merge_topk_kernel<DistT, KBYTES>), dim3(nq), dim3(MERGE_NT), 0, st,
-           args...);
+    const bool flat = filled && G <= MERGE_FLAT_G && (int64_t)G * R <= MERGE_SLOTS * MERGE_NT;
+    if (!flags && R <= MERGE_GATHER_R && (flat || (!filled && sizeof(DistT) > 1)))
+        launch(QADC_PROF_MERGE, (merge_gather_kernel<DistT, KBYTES>), dim3(nq), dim3(MERGE_NT), 0, st, ws, ws_stride,
+               counts_off, lists_off, G, need, R, pad_dist, out_idx, out_dist, ids, n_ids, flat ? 1 : 0);
+    else
+        launch(QADC_PROF_MERGE, (merge_topk_kernel<DistT, KBYTES>), dim3(nq), dim3(MERGE_NT), 0, st, ws, ws_stride,
+               counts_off, lists_off, G, need, R, pad_dist, out_idx, out_dist, countsA_off, listsA_off, GA, pitchA, flags,
+               ids, n_ids);
     return QADC_OK;
 }
 

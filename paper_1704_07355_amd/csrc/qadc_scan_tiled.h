@@ -13,7 +13,7 @@ constexpr int TILED_LCAP = 64;         // keys a workgroup can report per query
 constexpr int TILED_MAX_CHUNKS = 1024; // database chunks per query
 constexpr int TILED_MFMA_MAX_CHUNKS = 4096;  // the same for small batches on the matrix-core kernel
 constexpr int TILED_MIN_Q = 8;         // smallest batch worth tiling
-constexpr int TILED_MFMA_MIN_Q = 16;   // smallest batch for the matrix-core kernel (32 queries per wavefront; twice that below 8 code bytes)
+constexpr int TILED_MFMA_MIN_Q_B4 = 32;  // smallest batch of 4-byte codes for the matrix-core kernel (wider codes: mfma_pays)
 constexpr int TILED_MFMA_MIN_Q2 = 64;  // smallest batch for its 64-queries-per-wavefront form
 constexpr int TILED_MFMA_MIN_Q4 = 128; // ... for 128 queries per wavefront (codes of up to 8 bytes)
 
@@ -21,8 +21,11 @@ struct TiledPlan {
     int B, GC;
     int64_t chunk;
     size_t lds_bytes;
-    bool mfma;  // (sub-)batches of TILED_MFMA_MIN_Q queries or more go to the matrix-core kernel
+    bool mfma;  // the matrix-core kernel scans the batch
 };
+
+// 4-bit codes of B bytes that the byte-lane kernels scan faster than the matrix-core kernel
+bool tiled_bytes_pay(int B, int64_t n, int nq);
 
 // codes4: 4-bit codes with the queries' 16-entry tables at hand (what the matrix-core kernel reads)
 bool make_tiled_plan(int64_t n, int m, int nq, bool codes4, TiledPlan *t);

@@ -362,9 +362,21 @@ __global__ __launch_bounds__(tiled_nt(B)) void scan_u8_tiled16_kernel(
 // smallest batches for the matrix-core kernel (from 16 queries with 8 code bytes or more, from 32
 // with 4: measured against the vector-ALU kernels over 10 M codes) and for its forms with 64 and 128
 // queries per wavefront
-static int mfma_min_q(int B)
+static int mfma_min_q(int B) { return std::max(1, knob_or(knobs().mfma_min_q, B >= 8 ? 2 : TILED_MFMA_MIN_Q_B4)); }
+// 8 to 15 queries over many 8-byte codes: the byte-lane kernel (20 M codes, 12 queries: 150 against 156 us)
+bool tiled_bytes_pay(int B, int64_t n, int nq)
 {
-    return std::max(1, knob_or(knobs().mfma_min_q, B >= 8 ? TILED_MFMA_MIN_Q : 2 * TILED_MFMA_MIN_Q));
+    return B == 8 && nq >= TILED_MIN_Q && nq < 16 && (double)n * B > 120e6;
+}
+// Does a call of nq queries over n codes of B bytes gain by the matrix-core kernel?  It costs some launches
+// more than a scan per query, and its scan of up to 32 queries takes as long as two per-query scans; 4-byte
+// codes have the byte-lane kernels in between.
+static bool mfma_pays(int B, int64_t n, int nq)
+{
+    if (knobs().mfma_min_q >= 0 || B < 8) return nq >= mfma_min_q(B);
+    const double bytes = (double)n * B;
+    if (tiled_bytes_pay(B, n, nq)) return false;
+    return nq >= 2 && (nq - 4) * bytes >= 90e6;
 }
 static int mfma_min_q2() { return std::max(1, knob_or(knobs().mfma_min_q2, TILED_MFMA_MIN_Q2)); }
 // 128 queries per wavefront (codes of up to 8 bytes): when the last set of 128 is more than half full
@@ -378,10 +390,10 @@ bool make_tiled_plan(int64_t n, int m, int nq, bool codes4, TiledPlan *t)
 {
     t->B = m / 2;
     const int cpt = (t->B <= 16) ? SCAN_VEC * (16 / t->B) : 1;
-    const int tile = tiled_nt(t->B) * cpt;
+    int tile = tiled_nt(t->B) * cpt;
     // 4-bit codes and a batch that fills a good part of a wavefront's 32 or 64 queries: the
     // matrix-core kernel scans it
-    t->mfma = codes4 && nq >= mfma_min_q(t->B) && knob_or(knobs().tiled_mfma, 1) != 0;
+    t->mfma = codes4 && mfma_pays(t->B, n, nq) && knob_or(knobs().tiled_mfma, 1) != 0;
     // chunks: at most TILED_MAX_CHUNKS per query, a multiple of the tile, below 2^24 codes (index
     // bits of a key); as long as possible (a workgroup builds its tables once per chunk) while
     // groups x chunks still make about four workgroups per compute unit: 64 tiles with many query
@@ -404,6 +416,10 @@ bool make_tiled_plan(int64_t n, int m, int nq, bool codes4, TiledPlan *t)
         // query and chunk, or queries overflow and are redone one by one
         want = std::max<int64_t>(512, ceil_div(std::max(64, knob_or(knobs().mfma_waves, 4096)), ceil_div(nq, qw)));
         want = std::min<int64_t>(max_chunks, want);
+        // (shorter chunks, of any multiple of 16 codes, where a wavefront takes at most 64 queries: half a million
+        // codes are then enough wavefronts; many 4-byte codes keep whole tiles, 91 queries with R = 1000 over 6 M spread
+        // over too many lists otherwise, 1.66 against 1.21 ms, but 40 queries over 1 M gain, 0.13 against 0.24 ms)
+        if (t->B >= 8 || n < (4 << 20)) tile = 256;
         lo = 2;
         hi = 1ll << 40;
     }

@@ -759,3 +759,51 @@ def test_float_scan_of_4bit_codes_in_query_batches(Q, O, m, n, nq):
     wi, wd = cref.scan_topk_f32(codes, luts, R)
     idx, dist = Q.qadc_scan_topk(Q.QADC_F32_4BIT, to_gpu(codes), to_gpu(luts), R)
     assert np.array_equal(idx_np(idx), wi) and np.array_equal(dist.cpu().numpy(), wd)
+
+
+# ------------------------------------------------------------------ which kernel scans a batch of 4-bit codes
+
+@pytest.mark.parametrize("m,nq,n", [
+    (64, 64, 65_600), (64, 47, 65_600),          # just above / below what the matrix-core kernel takes
+    (32, 40, 160_001), (32, 39, 160_001),
+    (16, 45, 270_000), (16, 47, 270_000),
+    (64, 5, 2_900_003), (64, 4, 2_900_003),      # a handful of queries over many codes
+    (32, 2, 150_017), (32, 3, 400_000), (16, 6, 700_001),   # several queries by the per-query kernel
+])
+@pytest.mark.parametrize("R", [1, 100])
+def test_batches_around_the_dispatch_lines(Q, m, nq, n, R):
+    """Sums and top-R of a batch whichever kernel scans it, with ragged sizes and tables off a 16-byte boundary
+    (which the matrix-core kernel leaves to the others)."""
+    from oracle import cref
+    rng = np.random.default_rng(m * nq + n)
+    codes = rng.integers(0, 256, size=(n, m // 2), dtype=np.uint8)
+    qluts = rng.integers(0, 40, size=(nq, m, 16)).astype(np.uint8)
+    wi, wd = cref.scan_topk_u8(codes, qluts, R, 255)
+    g_codes = to_gpu(codes)
+    idx, dist = Q.qadc_scan_topk(Q.QADC_U8_4BIT, g_codes, to_gpu(qluts), R)
+    assert np.array_equal(idx_np(idx), wi) and np.array_equal(dist.cpu().numpy(), wd)
+    shifted = to_gpu(np.concatenate([np.zeros(4, np.uint8), qluts.ravel()]))[4:].view(nq, m, 16)
+    idx, dist = Q.qadc_scan_topk(Q.QADC_U8_4BIT, g_codes, shifted, R)
+    assert np.array_equal(idx_np(idx), wi) and np.array_equal(dist.cpu().numpy(), wd)
+
+
+@pytest.mark.parametrize("variant,nq,n,R", [("u8", 1, 5_000, 100), ("u8", 3, 98_304, 128), ("u8", 16, 100_000, 100),
+                                            ("u8", 2, 40, 100), ("f32", 1, 3_000, 100), ("f32", 2, 200_000, 128),
+                                            ("f32", 1, 700_003, 100), ("f32", 1, 700_003, 129)])
+def test_merge_of_filled_regions(Q, variant, nq, n, R):
+    """Reports without a sampled bound (every region full), and 64-bit keys; few distinct sums, so that thousands of
+    keys tie at the R-th place, and a code that occurs thousands of times."""
+    from oracle import cref
+    rng = np.random.default_rng(n + R)
+    m = 16
+    codes = rng.integers(0, 256, size=(n, m // 2), dtype=np.uint8)
+    codes[n // 3:n // 2] = codes[0]
+    if variant == "u8":
+        qluts = rng.integers(0, 3, size=(nq, m, 16)).astype(np.uint8)
+        wi, wd = cref.scan_topk_u8(codes, qluts, R, 255)
+        idx, dist = Q.qadc_scan_topk(Q.QADC_U8_4BIT, to_gpu(codes), to_gpu(qluts), R)
+    else:
+        luts = rng.integers(0, 3, size=(nq, m, 16)).astype(np.float32)
+        wi, wd = cref.scan_topk_f32(codes, luts, R)
+        idx, dist = Q.qadc_scan_topk(Q.QADC_F32_4BIT, to_gpu(codes), to_gpu(luts), R)
+    assert np.array_equal(idx_np(idx), wi) and np.array_equal(dist.cpu().numpy(), wd)
