@@ -80,16 +80,24 @@ struct IvfClear {
 // A workgroup computes 16*AQ queries x 128 cells, 16 components of both at a time through LDS,
 // AQ x 8 distances per thread.  Thread (tx, ty) owns queries AQ*ty.. and the cells
 // 32*k + 2*tx + e, so that a wavefront's 8-byte LDS reads of the cells are contiguous.  AQ = 8
-// (128 queries per workgroup) for batches, AQ = 1 (16 queries) for a few queries, whose cost is
-// then one pass over the centroids.
+// (128 queries per workgroup).
 constexpr int IVF_CT = 128;  // cells per workgroup
 constexpr int IVF_CK = 16;   // components per step
 
+// Row strides of the queries and of the distances, and what one step of blockIdx.z adds to the three arrays (the
+// two halves of a multi-index; else one step).
+struct IvfDistRows {
+    size_t query_ld, dist_ld, coarse_z, query_z, dist_z;
+};
+
 template <int AQ>
 __global__ __launch_bounds__(256) void ivf_coarse_dist_kernel(
-    const float *__restrict__ coarse, int K, int d, const float *__restrict__ queries, int nq,
+    const float *__restrict__ coarse, int K, int d, const float *__restrict__ queries, int nq, IvfDistRows rows,
     float *__restrict__ dist, unsigned *__restrict__ blockmin, int nblk)
 {
+    coarse += blockIdx.z * rows.coarse_z;
+    queries += blockIdx.z * rows.query_z;
+    dist += blockIdx.z * rows.dist_z;
     constexpr int QT = 16 * AQ;
     __shared__ __attribute__((aligned(16))) float ys[IVF_CK][QT + 4];
     __shared__ __attribute__((aligned(16))) float cs[IVF_CK][IVF_CT + 4];
@@ -115,7 +123,7 @@ __global__ __launch_bounds__(256) void ivf_coarse_dist_kernel(
             yn[e] = 0.0f;
             if (row < QT) {
                 const int q = q0 + row;
-                if (q < nq && t < d) yn[e] = queries[(size_t)q * d + t];
+                if (q < nq && t < d) yn[e] = queries[(size_t)q * rows.query_ld + t];
             }
         }
     };
@@ -168,11 +176,11 @@ __global__ __launch_bounds__(256) void ivf_coarse_dist_kernel(
             if (c < K) mn = min(mn, f2ord(acc[a][2 * k]));
             if (c + 1 < K) mn = min(mn, f2ord(acc[a][2 * k + 1]));
             if (q >= nq) continue;
-            if (c + 1 < K && (K & 1) == 0) {  // K even: the pair is 8-byte aligned
-                *reinterpret_cast<float2 *>(&dist[(size_t)q * K + c]) = make_float2(acc[a][2 * k], acc[a][2 * k + 1]);
+            if (c + 1 < K && (rows.dist_ld & 1) == 0 && (rows.dist_z & 1) == 0) {  // the pair is 8-byte aligned
+                *reinterpret_cast<float2 *>(&dist[(size_t)q * rows.dist_ld + c]) = make_float2(acc[a][2 * k], acc[a][2 * k + 1]);
             } else {
-                if (c < K) dist[(size_t)q * K + c] = acc[a][2 * k];
-                if (c + 1 < K) dist[(size_t)q * K + c + 1] = acc[a][2 * k + 1];
+                if (c < K) dist[(size_t)q * rows.dist_ld + c] = acc[a][2 * k];
+                if (c + 1 < K) dist[(size_t)q * rows.dist_ld + c + 1] = acc[a][2 * k + 1];
             }
         }
         if (blockmin) {  // uniform: the 16 lanes tx of a query are neighbours in the wavefront
@@ -223,9 +231,12 @@ __device__ __forceinline__ void few_walk(const float *c_row, const float *ys, in
 }
 
 __global__ __launch_bounds__(256) void ivf_coarse_dist_few_kernel(
-    const float *__restrict__ coarse, int K, int d, const float *__restrict__ queries, int nq,
+    const float *__restrict__ coarse, int K, int d, const float *__restrict__ queries, int nq, IvfDistRows rows,
     float *__restrict__ dist, unsigned *__restrict__ blockmin, int nblk, int vec4)
 {
+    coarse += blockIdx.z * rows.coarse_z;
+    queries += blockIdx.z * rows.query_z;
+    dist += blockIdx.z * rows.dist_z;
     constexpr int LD = IVF_FEW_DK + 4;  // rows 16-byte aligned, eight neighbouring cells on all the banks
     constexpr int QH = IVF_FEW_Q / 2;   // queries per thread
     __shared__ __attribute__((aligned(16))) float cs[IVF_CT][LD];
@@ -259,7 +270,7 @@ __global__ __launch_bounds__(256) void ivf_coarse_dist_few_kernel(
                 const int row = idx / dk4, col4 = idx - row * dk4;
                 float4 y = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
                 const int q = blockIdx.y * IVF_FEW_Q + row;
-                if (q < nq) y = *reinterpret_cast<const float4 *>(queries + (size_t)q * d + t0 + 4 * col4);
+                if (q < nq) y = *reinterpret_cast<const float4 *>(queries + (size_t)q * rows.query_ld + t0 + 4 * col4);
                 *reinterpret_cast<float4 *>(&ys[row][4 * col4]) = y;
             }
 #pragma unroll
@@ -272,7 +283,7 @@ __global__ __launch_bounds__(256) void ivf_coarse_dist_few_kernel(
             for (int idx = tid; idx < IVF_FEW_Q * 4 * dk4; idx += 256) {
                 const int row = idx / (4 * dk4), col = idx - row * (4 * dk4);
                 const int q = blockIdx.y * IVF_FEW_Q + row;
-                ys[row][col] = (q < nq && col < dk) ? queries[(size_t)q * d + t0 + col] : 0.0f;
+                ys[row][col] = (q < nq && col < dk) ? queries[(size_t)q * rows.query_ld + t0 + col] : 0.0f;
             }
             for (int idx = tid; idx < IVF_CT * 4 * dk4; idx += 256) {
                 const int row = idx / (4 * dk4), col = idx - row * (4 * dk4);
@@ -299,7 +310,7 @@ __global__ __launch_bounds__(256) void ivf_coarse_dist_few_kernel(
     for (int a = 0; a < QH; ++a) {
         mn[a] = 0xffffffffu;
         if (a < nmine && c < K) {
-            dist[(size_t)(q0 + a) * K + c] = acc[a];
+            dist[(size_t)(q0 + a) * rows.dist_ld + c] = acc[a];
             mn[a] = f2ord(acc[a]);
         }
     }
@@ -319,6 +330,34 @@ __global__ __launch_bounds__(256) void ivf_coarse_dist_few_kernel(
         const int q = blockIdx.y * IVF_FEW_Q + tid;
         if (q < nq) blockmin[(size_t)q * nblk + blockIdx.x] = min(wmin[2 * h][a], wmin[2 * h + 1][a]);
     }
+}
+
+// The distances of nq queries to K centroids (`parts` times, see IvfDistRows).  The tiled kernel reads a centroid
+// once for 128 queries; where its workgroups would leave most of the GPU idle (a few hundred cells), or for up
+// to 32 queries, the kernel for 16 queries is the faster one: 150 queries x 256 cells 10 against 44 us.
+void ivf_distances(const float *coarse, int K, int d, const float *queries, int nq, IvfDistRows rows, int parts,
+                   float *dist, unsigned *bmin, hipStream_t st)
+{
+    const int nblk = (int)ceil_div(K, IVF_CT);
+    const int64_t tiles = (int64_t)nblk * ceil_div(nq, 128) * parts;
+    if (nq > 32 && tiles >= 256) {
+        dim3 grid((unsigned)nblk, (unsigned)ceil_div(nq, 128), (unsigned)parts);
+        launch(QADC_PROF_IVF_INDEX, ivf_coarse_dist_kernel<8>, grid, dim3(256), 0, st, coarse, K, d, queries, nq, rows,
+               dist, bmin, nblk);
+    } else {
+        const int vec4 = (d % 4 == 0 && rows.query_ld % 4 == 0 && rows.query_z % 4 == 0 && rows.coarse_z % 4 == 0 &&
+                          ((uintptr_t)coarse & 15) == 0 && ((uintptr_t)queries & 15) == 0) ? 1 : 0;
+        dim3 grid((unsigned)nblk, (unsigned)ceil_div(nq, IVF_FEW_Q), (unsigned)parts);
+        launch(QADC_PROF_IVF_INDEX, ivf_coarse_dist_few_kernel, grid, dim3(256), 0, st, coarse, K, d, queries, nq, rows,
+               dist, bmin, nblk, vec4);
+    }
+}
+
+// The 2 K half distances of nq queries: hd[(q * 2 + h)][i] to half-centroid i of half h.
+void multi_half_distances(const float *halves, int K, int dh, const float *queries, int nq, float *hd, hipStream_t st)
+{
+    const IvfDistRows rows = {(size_t)(2 * dh), (size_t)(2 * K), (size_t)K * dh, (size_t)dh, (size_t)K};
+    ivf_distances(halves, K, dh, queries, nq, rows, 2, hd, nullptr, st);
 }
 
 // probes[q][0..nprobe) = the nprobe closest cells, closest first, ties to the lowest cell id.
@@ -1494,7 +1533,7 @@ struct IvfPlan {
 };
 
 constexpr int IVF_SHARED_PITCH = MERGE_CAP;   // keys of a query's region: what the merge kernel holds in LDS
-constexpr int IVF_SHARED_MIN_Q = 384;         // smallest batch whose popular lists are scanned once for all (even at 360 on 65536 Zipf lists)
+constexpr int IVF_SHARED_MIN_Q = 384;         // smallest batch whose popular lists are scanned once for all (see shared_lists_pay)
 constexpr int IVF_SHARED_MAX_R = 128;         // the region must hold a few dozen times R keys
 constexpr int IVF_SHARED_MAX_K = 1 << 18;     // one workgroup sums the per-cell counts
 
@@ -1503,6 +1542,20 @@ constexpr int IVF_SHARED_MIN_PAIRS = 4;       // pairs of a cell from which its 
 int ivf_shared_scan(int, const int64_t *, const uint8_t *, int64_t, int, const int32_t *, int, int, const uint8_t *,
                     int, char *, size_t, size_t, size_t, int, unsigned *, unsigned *, unsigned *, unsigned *,
                     unsigned *, unsigned *, unsigned *, int32_t *, unsigned *, long long, int, int, hipStream_t);
+
+// Is a batch large enough that its popular lists are scanned once for all their queries?  That costs ten launches
+// more; it gains where lists are met by many queries or where there is much to read.  With lists and probes taken as
+// even, from 14 pairs per list, or from 5e7 (code, query)s of 384 queries and more.  us per call per-query / shared:
+//   pairs per list  1e6 codes in 256, 150 queries x 24 (14) 179 / 163, 70 (6.6) 174 / 181; 2e6 in 256, 150 x 64 (37)
+//                   328 / 230; 4e6 in 1000, 200 x 64 (12.8) 309 / 324;
+//   met             1e8 in 16384, 500 x 64 (2e8) 971 / 835, 250 (1e8) 595 / 637; 5e7 in 65536, 400 x 64 (2e7) 544 / 679,
+//                   800 (4e7) 994 / 1020, 4096 (2e8) 4932 / 3807; 3e7 in 16384, 4000 x 8 (6e7) 2218 / 1309;
+//                   multi-index of 1e8 codes, 512 queries (4e7) 404 / 462.
+static bool shared_lists_pay(const qadc_ivf_index *ix, int nq, int nprobe)
+{
+    const double pairs = (double)nq * nprobe / (double)ix->K;
+    return nq >= 64 && (pairs >= 14.0 || (nq >= IVF_SHARED_MIN_Q && pairs * (double)ix->n >= 5e7));
+}
 
 static bool make_ivf_plan(const qadc_ivf_index *ix, int nq, int nprobe, int R, IvfPlan *p)
 {
@@ -1521,8 +1574,11 @@ static bool make_ivf_plan(const qadc_ivf_index *ix, int nq, int nprobe, int R, I
     p->W = knob_or(knobs().ivf_wgs, w_def);
     if (p->W < 1) p->W = 1;
     if (p->W > 4096) p->W = 4096;
-    // about 1/16 of an average list, between 64 and 1024 codes
-    int64_t spl = ix->n / ix->K / 16;
+    // Half of an average list, between 64 and 1024 codes.  With 1/16 the R-th smallest sum of the sample was so loose
+    // a bound over short lists that the report lists overflowed and were cut back again and again: 1e8 codes in 16384
+    // lists, 1000 queries 2.02 ms per call against 1.17, 4 queries 149 against 96 us; 4e6 in 1000, 200 queries
+    // 453 against 304; 1e9 codes in 65536 lists (1024 codes against 953) the same.
+    int64_t spl = ix->n / ix->K / 2;
     if (spl < 64) spl = 64;
     if (spl > 1024) spl = 1024;
     p->seed_per_list = knob_or(knobs().ivf_seed, 1) ? (int)spl : 0;
@@ -1531,7 +1587,7 @@ static bool make_ivf_plan(const qadc_ivf_index *ix, int nq, int nprobe, int R, I
     // that probe it (QADC_IVF_SHARED=1 / 0 forces / forbids it)
     const int shared_knob = knobs().ivf_shared;
     p->shared = R <= IVF_SHARED_MAX_R && ix->K <= IVF_SHARED_MAX_K && p->seed_per_list > 0 && ix->m <= 64 &&
-                (shared_knob >= 0 ? shared_knob != 0 : nq >= IVF_SHARED_MIN_Q);
+                (shared_knob >= 0 ? shared_knob != 0 : shared_lists_pay(ix, nq, nprobe));
     p->shared_wgs = std::max(1, std::min(65535, knob_or(knobs().ivf_shared_wgs, 32768)));
     p->shared_min_pairs = std::max(1, knob_or(knobs().ivf_shared_min_pairs, IVF_SHARED_MIN_PAIRS));
     p->stride = p->l.stride;
@@ -1670,16 +1726,8 @@ int ivf_search(const qadc_ivf_index *ix, const float *queries, int nq, int nprob
                 unsigned *bmin = nullptr;
                 const int nblk = (int)ceil_div(K, IVF_CT);
                 if (nblk >= 2 * nprobe && nblk <= IVF_SEL_MAXBLK) bmin = (unsigned *)(ws + p.off_bmin);
-                if (nb > 32) {
-                    dim3 grid((unsigned)nblk, (unsigned)ceil_div(ni, 128));
-                    launch(QADC_PROF_IVF_INDEX, ivf_coarse_dist_kernel<8>, grid, dim3(256), 0, st, ix->coarse, K, d,
-                           yi, ni, dist, bmin, nblk);
-                } else {
-                    const int vec4 = (d % 4 == 0 && ((uintptr_t)ix->coarse & 15) == 0 && ((uintptr_t)yi & 15) == 0) ? 1 : 0;
-                    dim3 grid((unsigned)nblk, (unsigned)ceil_div(ni, IVF_FEW_Q));
-                    launch(QADC_PROF_IVF_INDEX, ivf_coarse_dist_few_kernel, grid, dim3(256), 0, st, ix->coarse, K, d,
-                           yi, ni, dist, bmin, nblk, vec4);
-                }
+                const IvfDistRows rows = {(size_t)d, (size_t)K, 0, 0, 0};
+                ivf_distances(ix->coarse, K, d, yi, ni, rows, 1, dist, bmin, st);
                 launch(QADC_PROF_IVF_INDEX, ivf_select_probes_kernel, dim3(ni), dim3(IVF_SEL_NT), 0, st, dist, K,
                        nprobe, probes + (size_t)i0 * nprobe, (const unsigned *)bmin, (int)ceil_div(K, IVF_CT), clr);
             }

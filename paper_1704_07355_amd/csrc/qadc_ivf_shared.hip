@@ -30,8 +30,20 @@
 namespace qadc {
 
 constexpr unsigned IVFS_NONE = 0xffffffffu;
-constexpr int IVFS_CHUNK = 4096;   // codes of a list per work item, at most (relative positions fit 24 bits)
+constexpr int IVFS_CHUNK_MIN = 128, IVFS_CHUNK_MAX = 2048;  // codes of a list per work item (relative positions fit 24 bits)
 constexpr int IVFS_LC = 64;        // keys a wavefront holds per pair before it writes them out
+
+// Codes per work item for a batch that meets about `met` (code, pair)s.  An item is one wavefront's serial walk and a
+// set-up of 32 pairs' tables: long items for much work, short ones so that little work fills the GPU.  Measured ms
+// per call at 4096 / 2048 / 1024 / 512 / 256 / 128 codes: 1e9 codes, 4096 queries (4e9 met) 9.66 / 9.56 / 9.75 / 10.2;
+// 1e8 codes in 4096 lists, 800 queries (5e8) 0.99 / - / 0.81 / 0.85 / 0.94 / 1.13; multi-index of 1e8 codes, 512 queries
+// (4e7) 0.79 / - / - / 0.56 / 0.53 / 0.53; 1e6 codes, 150 queries (1.4e7) 0.66 / - / 0.28 / 0.20 / 0.17 / 0.16.
+static int ivfs_chunk(double met)
+{
+    int chunk = IVFS_CHUNK_MIN;
+    while (chunk < IVFS_CHUNK_MAX && (32.0 * chunk) * (32.0 * chunk) < met) chunk *= 2;
+    return chunk;
+}
 
 // codes of the leading part of a list of n codes: 1/16, whole 32-code steps, at least one
 __host__ __device__ inline long long ivfs_lead(long long n)
@@ -67,7 +79,7 @@ __global__ __launch_bounds__(256) void ivfs_count_kernel(const int32_t *__restri
 
 // Exclusive running sums over the cells of (pairs, work items of the leading parts, work items of the
 // rest).  A cell with P >= min_pairs pairs and n codes is ceil(P / qw) sets of pairs times
-// ceil(len / IVFS_CHUNK) chunks of either part; a cell with fewer pairs is no work here.  Two launches:
+// ceil(len / chunk) chunks of either part; a cell with fewer pairs is no work here.  Two launches:
 // every workgroup sums its 1024 cells and leaves its totals in blk[3][nblk]; then every workgroup adds
 // the totals of the workgroups before it (one workgroup walking all the cells took 64 rounds of
 // barriers and LDS chains for 65536 cells).
@@ -75,7 +87,7 @@ constexpr int IVFS_OFF_NT = 1024;
 
 __global__ __launch_bounds__(IVFS_OFF_NT) void ivfs_offsets_kernel(const unsigned *__restrict__ pair_cnt,
                                                                    const int64_t *__restrict__ list_off, int K,
-                                                                   int64_t n_total, int qw, int min_pairs,
+                                                                   int64_t n_total, int qw, int min_pairs, int chunk,
                                                                    unsigned *__restrict__ pair_off,
                                                                    unsigned *__restrict__ item_off0,
                                                                    unsigned *__restrict__ item_off1,
@@ -93,8 +105,8 @@ __global__ __launch_bounds__(IVFS_OFF_NT) void ivfs_offsets_kernel(const unsigne
         const long long n = h - l, s = ivfs_lead(n);
         const unsigned sets = P >= (unsigned)min_pairs ? (P + (unsigned)qw - 1u) / (unsigned)qw : 0u;
         v[0] = P;
-        v[1] = sets * (unsigned)((s + IVFS_CHUNK - 1) / IVFS_CHUNK);
-        v[2] = sets * (unsigned)((n - s + IVFS_CHUNK - 1) / IVFS_CHUNK);
+        v[1] = sets * (unsigned)((s + chunk - 1) / chunk);
+        v[2] = sets * (unsigned)((n - s + chunk - 1) / chunk);
     }
     unsigned inc[3] = {v[0], v[1], v[2]};
 #pragma unroll
@@ -181,7 +193,7 @@ __global__ __launch_bounds__(256) void ivfs_place_kernel(const int32_t *__restri
 // scan_u8_mfma_kernel with one group of 32 "queries" = pairs.
 template <int B>
 __global__ __launch_bounds__(64) void ivfs_scan_kernel(
-    int part, const int64_t *__restrict__ list_off, const uint8_t *__restrict__ codes, int64_t n_total, int K,
+    int part, int chunk, const int64_t *__restrict__ list_off, const uint8_t *__restrict__ codes, int64_t n_total, int K,
     const unsigned *__restrict__ pair_off, const unsigned *__restrict__ item_off,
     const unsigned *__restrict__ pairs, int nprobe, const uint8_t *__restrict__ qluts,
     const unsigned *__restrict__ taus, char *__restrict__ ws, size_t ws_stride, size_t countsA_off,
@@ -221,8 +233,8 @@ __global__ __launch_bounds__(64) void ivfs_scan_kernel(
         const unsigned set = local % sets, ch = local / sets;
         const long long lead = ivfs_lead(lh - ll);
         const long long r0 = part == 0 ? ll : ll + lead, r1 = part == 0 ? ll + lead : lh;
-        const int64_t c0 = r0 + (long long)ch * IVFS_CHUNK;
-        const int64_t c1 = min((long long)r1, (long long)c0 + IVFS_CHUNK);
+        const int64_t c0 = r0 + (long long)ch * chunk;
+        const int64_t c1 = min((long long)r1, (long long)c0 + chunk);
         if (c0 >= c1) continue;
 
         // this lane's pair: its tables (code byte jb: the 16 entries of table 2jb + half) and bound
@@ -445,6 +457,7 @@ int ivf_shared_scan(int B, const int64_t *list_off, const uint8_t *codes, int64_
                     int wgs, hipStream_t st)
 {
     const int64_t npairs = (int64_t)nb * nprobe;
+    const int chunk = ivfs_chunk((double)npairs * (double)n_total / (double)K);
     const unsigned pgrid = (unsigned)ceil_div(npairs, 256);
     launch(QADC_PROF_SEED, ivfs_zero_kernel, dim3((unsigned)ceil_div(K, 256)), dim3(256), 0, st, pair_cnt, (int64_t)K);
     launch(QADC_PROF_SEED, ivfs_count_kernel, dim3(pgrid), dim3(256), 0, st, probes, nprobe, npairs, K,
@@ -452,20 +465,20 @@ int ivf_shared_scan(int B, const int64_t *list_off, const uint8_t *codes, int64_
     const unsigned ogrid = (unsigned)ceil_div(K, IVFS_OFF_NT);
     unsigned *blk = pair_cnt + (size_t)K + 1;  // (the region of pair_cnt has room for 3 x 256 totals behind it)
     launch(QADC_PROF_SEED, ivfs_offsets_kernel, dim3(ogrid), dim3(IVFS_OFF_NT), 0, st, (const unsigned *)pair_cnt,
-           list_off, K, n_total, 32, min_pairs, pair_off, item_off0, item_off1, blk);
+           list_off, K, n_total, 32, min_pairs, chunk, pair_off, item_off0, item_off1, blk);
     launch(QADC_PROF_SEED, ivfs_offsets_add_kernel, dim3(ogrid), dim3(IVFS_OFF_NT), 0, st, K, (const unsigned *)blk,
            pair_off, item_off0, item_off1);
     launch(QADC_PROF_SEED, ivfs_place_kernel, dim3(pgrid), dim3(256), 0, st, probes, npairs, K,
            (const unsigned *)pair_off, pair_cnt, pairs);
 #define QADC_IVFS_CASE(B_)                                                                                      \
     case B_:                                                                                                   \
-        launch(QADC_PROF_IVF_SHARED, ivfs_scan_kernel<B_>, dim3((unsigned)wgs), dim3(64), 0, st, 0, list_off, codes,  \
+        launch(QADC_PROF_IVF_SHARED, ivfs_scan_kernel<B_>, dim3((unsigned)wgs), dim3(64), 0, st, 0, chunk, list_off, codes,  \
                n_total, K, (const unsigned *)pair_off, (const unsigned *)item_off0, (const unsigned *)pairs,   \
                nprobe, qluts, (const unsigned *)taus, scan_ws, ws_stride, countsA_off, listsA_off, pitchA,     \
                flags);                                                                                         \
         launch(QADC_PROF_SEED, ivfs_refine_kernel, dim3((unsigned)nb), dim3(IVFS_REFINE_NT), 0, st, scan_ws,    \
                ws_stride, countsA_off, listsA_off, pitchA, R, taus, (const unsigned *)flags);                  \
-        launch(QADC_PROF_IVF_SHARED, ivfs_scan_kernel<B_>, dim3((unsigned)wgs), dim3(64), 0, st, 1, list_off, codes,  \
+        launch(QADC_PROF_IVF_SHARED, ivfs_scan_kernel<B_>, dim3((unsigned)wgs), dim3(64), 0, st, 1, chunk, list_off, codes,  \
                n_total, K, (const unsigned *)pair_off, (const unsigned *)item_off1, (const unsigned *)pairs,   \
                nprobe, qluts, (const unsigned *)taus, scan_ws, ws_stride, countsA_off, listsA_off, pitchA,     \
                flags);                                                                                         \
