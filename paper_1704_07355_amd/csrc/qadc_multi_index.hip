@@ -11,7 +11,7 @@
 //   slots    the list number of a cell in an index that keeps lists for its occupied cells only.
 //
 // probes: 2K half distances per query (float32, summed in increasing component with one fused
-// multiply-add each, by the kernels of the Index step of the inverted index), the T = min(nprobe, K) smallest
+// multiply-add each, as the Index step of the inverted index), the T = min(nprobe, K) smallest
 // of each half in order, then the pairs of ranks (a, b) with (a+1)(b+1) <= nprobe -- a cell
 // outside that corner has at least nprobe cells in front of it, every pair of lower ranks -- whose
 // sums are ranked exactly under (sum, cell id).  That corner holds about nprobe * ln(nprobe)
@@ -42,6 +42,32 @@ __global__ __launch_bounds__(256) void mi_cells_kernel(const float *__restrict__
     const int i = (int)(cell / K), j = (int)(cell % K);
     coarse[e] = t < dh ? halves[((size_t)i) * dh + t] : halves[((size_t)K + j) * dh + (t - dh)];
 }
+
+// hd[(q*2 + h)][i] = sum_t (y[q][h*dh + t] - halves[h][i][t])^2, float32, increasing t, one fused
+// multiply-add per component.  Grid (ceil(K / 256), 2, nq); the query's half sits in LDS.
+__global__ __launch_bounds__(256) void mi_half_dist_kernel(const float *__restrict__ halves, int K, int dh,
+                                                           const float *__restrict__ queries, int nq,
+                                                           float *__restrict__ hd)
+{
+    extern __shared__ float yh[];  // [dh]
+    const int h = blockIdx.y, q = blockIdx.z;
+    const float *y = queries + (size_t)q * (2 * dh) + (size_t)h * dh;
+    for (int t = threadIdx.x; t < dh; t += 256) yh[t] = y[t];
+    __syncthreads();
+    const int i = blockIdx.x * 256 + threadIdx.x;
+    if (i >= K) return;
+    const float *c = halves + ((size_t)h * K + i) * dh;
+    float acc = 0.0f;
+    for (int t = 0; t < dh; ++t) {
+        const float df = yh[t] - c[t];
+        acc = __builtin_fmaf(df, df, acc);
+    }
+    hd[((size_t)q * 2 + h) * K + i] = acc;
+}
+// For up to MI_FEW of nq * K * dh: more short workgroups than the kernels of ivf_distances, which stage rows in LDS
+// first.  us of the whole Index step here / there: K = 512, dh = 128, 8 queries 23.8 / 28.7; K = 4096, dh = 64, 16 queries
+// 25.5 / 27.6, 32 queries 29.4 / 28.0; K = 4096, dh = 128, 64 queries 51.3 / 32.2.
+constexpr int64_t MI_FEW = 8 << 20;
 
 // One workgroup per query.  top[(q*2 + h)][r] = the half-centroid of rank r of half h.  The
 // candidate pairs are laid out by rank a of the first half: row a holds b = 0 .. nb(a)-1,
@@ -153,7 +179,11 @@ int multi_index_probes(const float *halves, int K, int d, const float *queries, 
     float *hd = reinterpret_cast<float *>(ws + p.hd_off);
     int32_t *top = reinterpret_cast<int32_t *>(ws + p.top_off);
     const int dh = d / 2;
-    multi_half_distances(halves, K, dh, queries, nq, hd, st);
+    if ((int64_t)nq * K * dh <= MI_FEW)
+        launch(QADC_PROF_IVF_INDEX, mi_half_dist_kernel, dim3((unsigned)ceil_div(K, 256), 2, (unsigned)nq), dim3(256),
+               (size_t)dh * sizeof(float), st, halves, K, dh, queries, nq, hd);
+    else
+        multi_half_distances(halves, K, dh, queries, nq, hd, st);
     ivf_select_smallest(hd, 2 * nq, K, p.T, top, st);
     launch(QADC_PROF_IVF_INDEX, mi_combine_kernel, dim3((unsigned)nq), dim3(256), 0, st, (const float *)hd,
            (const int32_t *)top, K, p.T, nprobe, probes);

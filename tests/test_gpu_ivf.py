@@ -463,3 +463,25 @@ def test_ivf_random_shapes(Q, O, seed):
             own = O.ivf_quick_adc_search(index, coarse, cb, queries[iq], nprobe, init, R, qmin_mode=mode,
                                          probes=probes[iq])
             assert np.abs(own["qluts"].astype(int) - qluts[iq].astype(int)).max() <= 1, (case, iq)
+
+
+@pytest.mark.parametrize("K,d,nq", [(256, 32, 33), (257, 30, 150), (1000, 64, 40), (9000, 32, 500), (40_000, 16, 70)])
+def test_cells_do_not_depend_on_the_batch(Q, O, K, d, nq):
+    """The Index step takes one of two distance kernels by the number of its workgroups: the same bits, so a query
+    gets the cells it gets on its own."""
+    import torch
+    rng = np.random.default_rng(K + nq)
+    n, m = 4 * K, 8
+    coarse = rng.normal(size=(K, d)).astype(np.float32)
+    cb = rng.normal(size=(m, 16, -(-d // m))).astype(np.float32)
+    d = m * cb.shape[2]
+    coarse = np.ascontiguousarray(np.resize(coarse, (K, d)))
+    off = torch.arange(0, n + 1, 4, dtype=torch.int64).cuda()
+    codes = to_gpu(rng.integers(0, 256, size=(n, m // 2), dtype=np.uint8))
+    gix = Q.IvfIndex(to_gpu(coarse), off, codes, torch.arange(n, dtype=torch.int32).cuda(), to_gpu(cb))
+    queries = to_gpu(rng.normal(size=(nq, d)).astype(np.float32))
+    nprobe = 20
+    _, _, probes, _ = Q.qadc_ivf_search(gix, queries, nprobe, 5, 50, debug=True)
+    for iq in list(range(0, nq, max(1, nq // 7))) + [nq - 1]:
+        _, _, one, _ = Q.qadc_ivf_search(gix, queries[iq:iq + 1].contiguous(), nprobe, 5, 50, debug=True)
+        assert torch.equal(probes[iq], one[0]), iq

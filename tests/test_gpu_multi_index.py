@@ -299,3 +299,16 @@ def test_index_without_centroids_needs_probes(Q, O):
                      to_gpu(cb), halves=to_gpu(halves), cell_ids=to_gpu(index["cell_ids"].view(np.int32)))
     with pytest.raises(Q.QadcError):
         Q.qadc_ivf_search(gix, to_gpu(x[:3]), 4, 10, 100)
+
+
+@pytest.mark.parametrize("K,dh,nq", [(4096, 64, 32), (4096, 64, 33), (1000, 20, 450), (517, 128, 127), (517, 128, 300),
+                                     (4096, 66, 700)])
+def test_probes_do_not_depend_on_the_batch(Q, K, dh, nq):
+    """The half distances come from three kernels by the size of the call; the same bits, so the same cells in the
+    same order, as for a query on its own."""
+    import torch
+    rng = np.random.default_rng(K + nq)
+    halves, queries = to_gpu(rng.normal(size=(2, K, dh)).astype(np.float32)), to_gpu(rng.normal(size=(nq, 2 * dh)).astype(np.float32))
+    got = Q.qadc_multi_index_probes(halves, queries, 48)
+    for iq in list(range(0, nq, max(1, nq // 9))) + [nq - 1]:
+        assert torch.equal(got[iq:iq + 1], Q.qadc_multi_index_probes(halves, queries[iq:iq + 1].contiguous(), 48)), iq
