@@ -1519,6 +1519,7 @@ int quantize_luts(int, const float *, int, int, int, const uint8_t *, int64_t, c
 
 struct IvfPlan {
     int qb, W;
+    int wgs;  // workgroups a query gets of the per-query scan, at most (W: report regions laid out)
     int qd;  // queries per pass of the Index step (its distances take K floats per query)
     int seed_per_list;  // codes sampled per probed list for the bound of the scan (0: no seed kernel)
     ScanLayout l;
@@ -1582,12 +1583,15 @@ static bool make_ivf_plan(const qadc_ivf_index *ix, int nq, int nprobe, int R, I
     if (spl < 64) spl = 64;
     if (spl > 1024) spl = 1024;
     p->seed_per_list = knob_or(knobs().ivf_seed, 1) ? (int)spl : 0;
-    p->l = scan_layout(p->W, R);
     // large batches over a moderate number of cells: every list is scanned once for all the queries
     // that probe it (QADC_IVF_SHARED=1 / 0 forces / forbids it)
     const int shared_knob = knobs().ivf_shared;
     p->shared = R <= IVF_SHARED_MAX_R && ix->K <= IVF_SHARED_MAX_K && p->seed_per_list > 0 && ix->m <= 64 &&
                 (shared_knob >= 0 ? shared_knob != 0 : shared_lists_pay(ix, nq, nprobe));
+    // (the per-query kernel then only takes the rarely probed lists and queries that are redone: 150 queries over 1e6
+    // codes spent 25 us on 109 workgroup slots per query, nearly all empty)
+    p->wgs = p->shared && knobs().ivf_wgs < 0 ? std::min(p->W, 24) : p->W;
+    p->l = scan_layout(p->W, R);
     p->shared_wgs = std::max(1, std::min(65535, knob_or(knobs().ivf_shared_wgs, 32768)));
     p->shared_min_pairs = std::max(1, knob_or(knobs().ivf_shared_min_pairs, IVF_SHARED_MIN_PAIRS));
     p->stride = p->l.stride;
@@ -1778,9 +1782,9 @@ int ivf_search(const qadc_ivf_index *ix, const float *queries, int nq, int nprob
                                nullptr, nullptr, st);
         }
         if (rc != QADC_OK) return rc;
-        // Scan: up to p.W workgroups per query, one per `upw` units of its lists (batches that fill
+        // Scan: up to p.wgs workgroups per query, one per `upw` units of its lists (batches that fill
         // the GPU by their number alone), one per unit otherwise
-        dim3 grid((unsigned)p.W * (unsigned)nb);
+        dim3 grid((unsigned)p.wgs * (unsigned)nb);
         const int upw = nb >= 64 ? max(1, knob_or(knobs().ivf_units, 16)) : 1;
         // a few queries: their lists are sampled by several workgroups each
         const int seed_parts_env = knob_or(knobs().ivf_seed_parts, 0);
@@ -1820,25 +1824,25 @@ int ivf_search(const qadc_ivf_index *ix, const float *queries, int nq, int nprob
                                  qunits_light, unit, p.shared_min_pairs, p.shared_wgs, st);
             if (rc != QADC_OK) return rc;
         }
-        // (a few queries need no map: every query gets its p.W workgroup slots in turn)
+        // (a few queries need no map: every query gets its p.wgs workgroup slots in turn)
         const bool mapped = nb >= 64 || p.shared;
         // a few queries: workgroups of 1024 threads (measured at N = 1e9: 1 query 0.121 against 0.136 ms,
         // 4 queries 0.163 against 0.181, 8 queries 0.208 against 0.220, 12 the same, 16 slower)
         const bool wide_wgs = !mapped && nb <= knob_or(knobs().ivf_wide_q, IVF_WIDE_MAX_Q);
         if (mapped)
-            launch(QADC_PROF_SEED, ivf_wgmap_kernel, dim3(1), dim3(IVF_MAP_NT), 0, st, qunits, nb, upw, p.W, wgmap,
+            launch(QADC_PROF_SEED, ivf_wgmap_kernel, dim3(1), dim3(IVF_MAP_NT), 0, st, qunits, nb, upw, p.wgs, wgmap,
                    (const unsigned *)qunits_light, (const unsigned *)flags);
         const int hist_bound = (p.seed_per_list > 0 && seed_parts > 1) ? 1 : 0;
 #define QADC_IVF_CASE(B_)                                                                              \
     case B_:                                                                                          \
         if (wide_wgs)                                                                                  \
             launch(QADC_PROF_SCAN, ivf_scan_kernel<B_, 1024>, grid, dim3(1024), 0, st, ix->list_off, ix->codes, \
-                   ix->n, probes, nprobe, qluts, nbins, R, upw, p.W, mapped ? wgmap : (unsigned *)nullptr, scan_ws, \
+                   ix->n, probes, nprobe, qluts, nbins, R, upw, p.wgs, mapped ? wgmap : (unsigned *)nullptr, scan_ws, \
                    p.stride, p.l.counts_off, p.l.lists_off, (const int32_t *)probes_light,              \
                    (const unsigned *)flags, fq, hist_bound);                                           \
         else                                                                                           \
             launch(QADC_PROF_SCAN, ivf_scan_kernel<B_, IVF_NT>, grid, dim3(IVF_NT), 0, st, ix->list_off, ix->codes, \
-                   ix->n, probes, nprobe, qluts, nbins, R, upw, p.W, mapped ? wgmap : (unsigned *)nullptr, scan_ws, \
+                   ix->n, probes, nprobe, qluts, nbins, R, upw, p.wgs, mapped ? wgmap : (unsigned *)nullptr, scan_ws, \
                    p.stride, p.l.counts_off, p.l.lists_off, (const int32_t *)probes_light,              \
                    (const unsigned *)flags, fq, hist_bound);                                           \
         break;
@@ -1850,7 +1854,7 @@ int ivf_search(const qadc_ivf_index *ix, const float *queries, int nq, int nprob
         }
 #undef QADC_IVF_CASE
         uint32_t *oi = out_ids + (size_t)q0 * R;
-        rc = launch_merge<uint8_t, 5>(nb, st, front, scan_ws, p.stride, p.l.counts_off, p.l.lists_off, p.W,
+        rc = launch_merge<uint8_t, 5>(nb, st, front, scan_ws, p.stride, p.l.counts_off, p.l.lists_off, p.wgs,
                                       (unsigned)R, R, (uint8_t)nbins, oi, out_dist + (size_t)q0 * R, p.countsA_off,
                                       p.listsA_off, p.shared ? 1 : 0, p.shared ? IVF_SHARED_PITCH : 0, flags,
                                       (const uint32_t *)ix->ids, (int64_t)ix->n);  // positions -> vector ids
