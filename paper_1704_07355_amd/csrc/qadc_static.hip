@@ -79,16 +79,23 @@ int search_static(const float *codebooks, int d, int m, const float *queries, in
     }
     if (ds.n != n || ds.m != m || ds.nb != nb || ds.R != R) ds.clean = false;
     ds.n = n; ds.m = m; ds.nb = nb; ds.R = R;
-    if (!ds.clean) {
-        // first call on this GPU, a call of a new shape, or a call failed part-way: a fill kernel, not
-        // a memset node, so that a caller may capture the call into a graph
+    // A last, shorter sequence lays its scratch out differently: it starts from cleared scratch, and so does every
+    // call that ends in one (a captured call as well, whose replays follow each other).
+    const bool mixed = nq > nb && nq % nb != 0;
+    auto clear = [&]() {
         hipLaunchKernelGGL(static_scratch_clear_kernel, dim3(2048), dim3(256), 0, st, (uint4 *)ds.ptr,
                            STATIC_SCRATCH_BYTES / 16);
-        QADC_HIP_TRY(hipGetLastError());
-        ds.clean = true;
+        return hipGetLastError();
+    };
+    if (!ds.clean || mixed) {
+        // first call on this GPU, a call of a new shape, or a call failed part-way: a fill kernel, not
+        // a memset node, so that a caller may capture the call into a graph
+        QADC_HIP_TRY(clear());
+        ds.clean = !mixed;
     }
     for (int q0 = 0; q0 < nq; q0 += nb) {
         const int cnt = min(nb, nq - q0);
+        if (q0 > 0 && cnt != nb) QADC_HIP_TRY(clear());
         const int rc = search_u8(codebooks, d, m, queries + (size_t)q0 * d, cnt, codes, n, R, init, nbins,
                                  qmin_mode, out_idx + (size_t)q0 * R, out_dist + (size_t)q0 * R,
                                  qluts_out ? qluts_out + (size_t)q0 * m * 16 : nullptr, ds.ptr,

@@ -79,3 +79,18 @@ def test_static_scratch_rejects_sizes_beyond_the_array(monkeypatch):
     rc = L.qadc_search_static(None, 128, m, None, 1, None, n, R, 200, 255, 0, None, None, None, None)
     assert rc == Q.QADC_ENOMEM
     assert b"static" in L.qadc_last_error()
+
+
+@pytest.mark.parametrize("n,m,nq,R", [(200_003, 16, 37, 1000), (700_001, 32, 35, 1000), (1_500_000, 64, 11, 1024)])
+def test_static_scratch_calls_cut_into_unequal_sequences(n, m, nq, R):
+    """A call of more queries than the array takes ends in a shorter launch sequence, which lays the scratch out its
+    own way: it, and the call that follows, may not find anything of the one before."""
+    import torch
+    import paper_1704_07355_amd as Q
+    L = Q.lib()
+    rng = np.random.default_rng(n)
+    cb = to_gpu(rng.uniform(0, 255, size=(m, 16, 2)).astype(np.float32))
+    codes = to_gpu(rng.integers(0, 256, size=(n, m // 2), dtype=np.uint8))
+    queries = to_gpu(rng.uniform(0, 255, size=(nq, 2 * m)).astype(np.float32))
+    for _ in range(2):
+        _call_both(Q, L, torch, cb, queries, codes, R, 200)
