@@ -1545,17 +1545,17 @@ int ivf_shared_scan(int, const int64_t *, const uint8_t *, int64_t, int, const i
                     unsigned *, unsigned *, unsigned *, int32_t *, unsigned *, long long, int, int, hipStream_t);
 
 // Is a batch large enough that its popular lists are scanned once for all their queries?  That costs ten launches
-// more; it gains where lists are met by many queries or where there is much to read.  With lists and probes taken as
-// even, from 14 pairs per list, or from 5e7 (code, query)s of 384 queries and more.  us per call per-query / shared:
-//   pairs per list  1e6 codes in 256, 150 queries x 24 (14) 179 / 163, 70 (6.6) 174 / 181; 2e6 in 256, 150 x 64 (37)
-//                   328 / 230; 4e6 in 1000, 200 x 64 (12.8) 309 / 324;
-//   met             1e8 in 16384, 500 x 64 (2e8) 971 / 835, 250 (1e8) 595 / 637; 5e7 in 65536, 400 x 64 (2e7) 544 / 679,
-//                   800 (4e7) 994 / 1020, 4096 (2e8) 4932 / 3807; 3e7 in 16384, 4000 x 8 (6e7) 2218 / 1309;
-//                   multi-index of 1e8 codes, 512 queries (4e7) 404 / 462.
+// more; it gains where lists are met by many queries.  From 384 queries always: what the queries meet follows from the
+// lengths of the lists, which only the GPU knows, and where a few lists hold most of the codes a query-by-query scan
+// reads them once per query (5e7 codes in 65536 lists of Zipf(2) lengths, 8 probes: 384 queries 12.2 against 1.7 ms,
+// 4096 queries 127 against 13; Zipf(1.2), 2e7 codes, 4096 queries 9.6 against 2.5) -- while over even lists that few
+// queries share it costs at most a fifth (multi-index of 1e8 codes, 512 queries 404 against 462 us; 5e7 in 65536,
+// 400 queries x 64 544 against 679).  From 64 queries when an average list has 14 pairs, so that sharing gains whatever
+// the lengths are; us per call per-query / shared: 1e6 codes in 256 lists, 150 queries x 24 (14 pairs) 179 / 163, 70 x 24
+// (6.6) 174 / 181; 2e6 in 256, 150 x 64 (37) 328 / 230; 4e6 in 1000, 200 x 64 (12.8) 309 / 324.
 static bool shared_lists_pay(const qadc_ivf_index *ix, int nq, int nprobe)
 {
-    const double pairs = (double)nq * nprobe / (double)ix->K;
-    return nq >= 64 && (pairs >= 14.0 || (nq >= IVF_SHARED_MIN_Q && pairs * (double)ix->n >= 5e7));
+    return nq >= IVF_SHARED_MIN_Q || (nq >= 64 && (double)nq * nprobe >= 14.0 * (double)ix->K);
 }
 
 static bool make_ivf_plan(const qadc_ivf_index *ix, int nq, int nprobe, int R, IvfPlan *p)

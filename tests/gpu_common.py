@@ -27,3 +27,20 @@ def to_gpu(a):
 
 def idx_np(t):
     return t.cpu().numpy().view(np.uint32)
+
+
+def gpu_us(f, reps=20, rounds=3):
+    """Microseconds of one call of f among others, the fastest of a few rounds."""
+    import torch
+    f()
+    best = float("inf")
+    for _ in range(rounds):
+        a, b = torch.cuda.Event(True), torch.cuda.Event(True)
+        torch.cuda.synchronize()
+        a.record()
+        for _ in range(reps):
+            f()
+        b.record()
+        torch.cuda.synchronize()
+        best = min(best, a.elapsed_time(b) * 1e3 / reps)
+    return best

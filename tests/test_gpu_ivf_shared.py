@@ -4,7 +4,7 @@ once for all the queries that probe it) against the CPU oracle and against the p
 import numpy as np
 import pytest
 
-from gpu_common import to_gpu, idx_np
+from gpu_common import to_gpu, idx_np, gpu_us
 from test_gpu_ivf import build_ivf, gpu_index
 
 pytestmark = pytest.mark.gpu
@@ -231,3 +231,35 @@ def test_calls_beyond_one_launch_sequence_and_tiny_indexes(Q, O):
                                          probes=probes[iq].cpu().numpy(), qluts=qluts[iq].cpu().numpy())
             assert np.array_equal(idx_np(ids)[iq], rep["ids"]), (K, iq)
             assert np.array_equal(dist[iq].cpu().numpy(), rep["dist"]), (K, iq)
+
+
+def skewed_index(Q, n, K, m, big, seed):
+    """One list of `big` codes in the middle, the others of even lengths; random codes."""
+    import torch
+    g = torch.Generator(device="cuda:0")
+    g.manual_seed(seed)
+    rnd = lambda *s: torch.randn(s, generator=g, device="cuda:0")
+    sizes = np.full(K, (n - big) // (K - 1), dtype=np.int64)
+    sizes[K // 2] = n - int(sizes.sum()) + int(sizes[K // 2])
+    off = to_gpu(np.concatenate([[0], np.cumsum(sizes)]))
+    coarse = 30 * rnd(K, 64)
+    codes = torch.randint(0, 256, (n, m // 2), generator=g, device="cuda:0", dtype=torch.uint8)
+    ids = torch.arange(n, dtype=torch.int32, device="cuda:0")
+    return Q.IvfIndex(coarse, off, codes, ids, 18 * rnd(m, 16, 64 // m)), coarse, rnd
+
+
+def test_route_of_a_skewed_index(Q, monkeypatch):
+    """Half of the codes in one list that every query probes: the route taken is no slower than the better of the two
+    by more than half (a query-by-query scan reads that list once per query)."""
+    gix, coarse, rnd = skewed_index(Q, 8_000_000, 16384, 16, 4_000_000, 5)
+    gq = (coarse[8192] + 18 * rnd(400, 64)).contiguous()
+    import torch
+    ws = Q.qadc_workspace_init(torch.empty((Q.qadc_ivf_workspace_bytes(gix, 400, 8, 100),), dtype=torch.uint8, device="cuda"))
+    own = gpu_us(lambda: Q.qadc_ivf_search(gix, gq, 8, 100, 300, workspace=ws))
+    forced = []
+    for route in "01":
+        monkeypatch.setenv("QADC_IVF_SHARED", route)
+        ws = Q.qadc_workspace_init(torch.empty((Q.qadc_ivf_workspace_bytes(gix, 400, 8, 100),), dtype=torch.uint8, device="cuda"))
+        forced.append(gpu_us(lambda: Q.qadc_ivf_search(gix, gq, 8, 100, 300, workspace=ws)))
+    monkeypatch.delenv("QADC_IVF_SHARED")
+    assert own < 1.5 * min(forced), (own, forced)
