@@ -30,7 +30,9 @@
 namespace qadc {
 
 constexpr unsigned IVFS_NONE = 0xffffffffu;
-constexpr int IVFS_CHUNK_MIN = 128, IVFS_CHUNK_MAX = 2048;  // codes of a list per work item (relative positions fit 24 bits)
+constexpr int IVFS_CHUNK_MIN = 128, IVFS_CHUNK_MAX = 2048;  // codes of a list per work item
+constexpr int IVFS_CHUNK_LONG = 4096;                       // ... of one list that alone fills the GPU (below 2^24)
+constexpr long long IVFS_LIST_ITEMS = 8192;
 constexpr int IVFS_LC = 64;        // keys a wavefront holds per pair before it writes them out
 
 // Codes per work item for a batch that meets about `met` (code, pair)s.  An item is one wavefront's serial walk and a
@@ -42,6 +44,16 @@ static int ivfs_chunk(double met)
 {
     int chunk = IVFS_CHUNK_MIN;
     while (chunk < IVFS_CHUNK_MAX && (32.0 * chunk) * (32.0 * chunk) < met) chunk *= 2;
+    return chunk;
+}
+
+// The same for a list of n codes wanted by `sets` sets of 32 pairs: where the batch as a whole looks small but this list
+// alone is many thousand items, longer ones.  (A few lists that hold most of the codes, 5e7 codes in 65536 lists of
+// Zipf(2) lengths, 8 probes: 384 queries 1.64 ms against 2.98, 4096 queries 13.7 against 17.3.)
+__device__ __forceinline__ int ivfs_list_chunk(int chunk, unsigned sets, long long n)
+{
+    const long long steps = (long long)sets * n;
+    while (chunk < IVFS_CHUNK_LONG && steps > IVFS_LIST_ITEMS * chunk) chunk *= 2;
     return chunk;
 }
 
@@ -79,7 +91,7 @@ __global__ __launch_bounds__(256) void ivfs_count_kernel(const int32_t *__restri
 
 // Exclusive running sums over the cells of (pairs, work items of the leading parts, work items of the
 // rest).  A cell with P >= min_pairs pairs and n codes is ceil(P / qw) sets of pairs times
-// ceil(len / chunk) chunks of either part; a cell with fewer pairs is no work here.  Two launches:
+// ceil(len / ivfs_list_chunk) chunks of either part; a cell with fewer pairs is no work here.  Two launches:
 // every workgroup sums its 1024 cells and leaves its totals in blk[3][nblk]; then every workgroup adds
 // the totals of the workgroups before it (one workgroup walking all the cells took 64 rounds of
 // barriers and LDS chains for 65536 cells).
@@ -104,9 +116,10 @@ __global__ __launch_bounds__(IVFS_OFF_NT) void ivfs_offsets_kernel(const unsigne
         if (l < 0 || h > n_total || h < l) l = h = 0;  // offsets that are not a list: no work
         const long long n = h - l, s = ivfs_lead(n);
         const unsigned sets = P >= (unsigned)min_pairs ? (P + (unsigned)qw - 1u) / (unsigned)qw : 0u;
+        const int len = ivfs_list_chunk(chunk, sets, n);
         v[0] = P;
-        v[1] = sets * (unsigned)((s + chunk - 1) / chunk);
-        v[2] = sets * (unsigned)((n - s + chunk - 1) / chunk);
+        v[1] = sets * (unsigned)((s + len - 1) / len);
+        v[2] = sets * (unsigned)((n - s + len - 1) / len);
     }
     unsigned inc[3] = {v[0], v[1], v[2]};
 #pragma unroll
@@ -233,8 +246,9 @@ __global__ __launch_bounds__(64) void ivfs_scan_kernel(
         const unsigned set = local % sets, ch = local / sets;
         const long long lead = ivfs_lead(lh - ll);
         const long long r0 = part == 0 ? ll : ll + lead, r1 = part == 0 ? ll + lead : lh;
-        const int64_t c0 = r0 + (long long)ch * chunk;
-        const int64_t c1 = min((long long)r1, (long long)c0 + chunk);
+        const int len = ivfs_list_chunk(chunk, sets, lh - ll);
+        const int64_t c0 = r0 + (long long)ch * len;
+        const int64_t c1 = min((long long)r1, (long long)c0 + len);
         if (c0 >= c1) continue;
 
         // this lane's pair: its tables (code byte jb: the 16 entries of table 2jb + half) and bound

@@ -248,6 +248,17 @@ def skewed_index(Q, n, K, m, big, seed):
     return Q.IvfIndex(coarse, off, codes, ids, 18 * rnd(m, 16, 64 // m)), coarse, rnd
 
 
+# a list of 13 sets of 32 pairs is cut into items of 128 codes up to 80,659 codes, of 256 and more beyond
+@pytest.mark.parametrize("m,big", [(16, 80_640), (16, 80_700), (32, 330_001), (8, 1_500_000)])
+def test_items_of_one_long_list(Q, monkeypatch, m, big):
+    """The length of a list's work items follows the list's own length; every length gives the same result."""
+    gix, coarse, rnd = skewed_index(Q, big + 20_000, 64, m, big, big)
+    gq = (coarse[32] + 18 * rnd(400, 64)).contiguous()
+    (ids, dist, _, _), (ids2, dist2, _, _) = both_routes(Q, monkeypatch, gix, gq, 3, 100, 300)
+    assert np.array_equal(idx_np(ids), idx_np(ids2))
+    assert np.array_equal(dist.cpu().numpy(), dist2.cpu().numpy())
+
+
 def test_route_of_a_skewed_index(Q, monkeypatch):
     """Half of the codes in one list that every query probes: the route taken is no slower than the better of the two
     by more than half (a query-by-query scan reads that list once per query)."""
