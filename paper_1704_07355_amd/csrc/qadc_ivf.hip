@@ -1854,7 +1854,7 @@ int ivf_search(const qadc_ivf_index *ix, const float *queries, int nq, int nprob
         }
 #undef QADC_IVF_CASE
         uint32_t *oi = out_ids + (size_t)q0 * R;
-        rc = launch_merge<uint8_t, 5>(nb, st, front, scan_ws, p.stride, p.l.counts_off, p.l.lists_off, p.wgs,
+        rc = launch_merge<uint8_t, 5>(nb, st, front ? MERGE_FILLED : MERGE_MIXED, scan_ws, p.stride, p.l.counts_off, p.l.lists_off, p.wgs,
                                       (unsigned)R, R, (uint8_t)nbins, oi, out_dist + (size_t)q0 * R, p.countsA_off,
                                       p.listsA_off, p.shared ? 1 : 0, p.shared ? IVF_SHARED_PITCH : 0, flags,
                                       (const uint32_t *)ix->ids, (int64_t)ix->n);  // positions -> vector ids

@@ -272,7 +272,8 @@ constexpr int MERGE_FLAT_SLOTS = 32768;  // ... key slots up to which every slot
 // incomplete and region B holds the result; 2 = the result is spread over both regions (the lists
 // of an inverted index scanned partly by one kernel, partly by the other).  Without flags only
 // region B exists.
-template <typename DistT, int KBYTES>
+// VISIT: regions that are few and well filled are gathered slot by slot (not for sparse ones).
+template <typename DistT, int KBYTES, bool VISIT>
 __global__ __launch_bounds__(MERGE_NT) void merge_topk_kernel(
     char *__restrict__ ws, size_t ws_stride, size_t counts_off, size_t lists_off, int G,
     unsigned need, int R, DistT pad_dist, uint32_t *__restrict__ out_idx,
@@ -308,7 +309,7 @@ __global__ __launch_bounds__(MERGE_NT) void merge_topk_kernel(
     // Few, well-filled regions (inverted-index scans, short databases): every slot of every
     // region is visited, a slot per thread at a time, so that the loads are spread over the whole
     // workgroup instead of one thread walking each region.
-    const bool flat = G <= MERGE_FLAT_G && (size_t)G * pitch <= (size_t)MERGE_FLAT_SLOTS;  // uniform
+    const bool flat = VISIT && G <= MERGE_FLAT_G && (size_t)G * pitch <= (size_t)MERGE_FLAT_SLOTS;  // uniform
     // every reported key, spread over the threads by workgroup (after the gather below)
     auto each_key = [&](auto f) {
         if (flat) {
@@ -565,7 +566,7 @@ constexpr int MERGE_PER = MERGE_CAP / MERGE_NT;
 constexpr int MERGE_GU = 4;       // regions per thread whose counts are requested together
 constexpr int MERGE_REP = 16;    // replicas of the histogram of a flat gather (in the memory of lkeys)
 constexpr int MERGE_SLOTS = 25;   // key slots per thread up to which every slot is visited at once (256 regions of 100)
-constexpr int MERGE_GATHER_R = 128;
+constexpr int MERGE_GATHER_R = 128, MERGE_GATHER_MIN_R = 32;
 
 // The same for calls whose keys are in one region set (no flags) and many for their number of regions, or whose
 // keys are 64 bits of distance and index; R <= MERGE_GATHER_R.  Bound by latency: one workgroup, a chain of round
@@ -574,17 +575,17 @@ constexpr int MERGE_GATHER_R = 128;
 // inverted-index query): a slot of a region per thread and register, thousands of keys in a few bins counted in 16
 // replicas of the histogram.  Else the places of the keys are laid out in LDS first, from running sums of the
 // counts.  Against the kernel above: 14.1 / 20.7 us for one inverted-index query (192 regions of up to 100 keys),
-// 10.7 / 14.8 us for 16 queries over 98 regions, 9.6 / 18.7 us for a float scan of 50 M codes (1024 regions); with a
-// sampled bound and 8-bit sums, or with R = 1000, the kernel above is the faster one by 1 to 3 us or more.
-template <typename DistT, int KBYTES>
+// 10.7 / 14.8 us for 16 queries over 98 regions, 9.6 / 18.7 us for a float scan of 50 M codes (1024 regions).  (Code
+// size counts: a second unrolled walk over the 25 slots in the rarely taken part cost every call 3 to 5 us.)
+template <typename DistT, int KBYTES, bool FLAT>
 __global__ __launch_bounds__(MERGE_NT) void merge_gather_kernel(
     char *__restrict__ ws, size_t ws_stride, size_t counts_off, size_t lists_off, int G,
     unsigned need, int R, DistT pad_dist, uint32_t *__restrict__ out_idx,
-    DistT *__restrict__ out_dist, const uint32_t *__restrict__ ids, int64_t n_ids, int flat_i)
+    DistT *__restrict__ out_dist, const uint32_t *__restrict__ ids, int64_t n_ids)
 {
     // need = min(R, number of codes scanned): at least that many keys were reported.
     // ids: the keys' low words are storage positions and out_idx gets ids[position] (inverted index).
-    __shared__ uint64_t lkeys[MERGE_CAP];  // first the places of the keys, then the keys
+    __shared__ uint64_t lkeys[MERGE_CAP];  // the places of the keys, or the histogram's replicas; then the winners
     __shared__ uint64_t cand[MERGE_NT];
     __shared__ SelectScratch sc;
     __shared__ unsigned lcnt, ccnt;
@@ -598,23 +599,19 @@ __global__ __launch_bounds__(MERGE_NT) void merge_gather_kernel(
     unsigned *counts = reinterpret_cast<unsigned *>(ws + (size_t)q * ws_stride + counts_off);
     uint64_t *lists = reinterpret_cast<uint64_t *>(ws + (size_t)q * ws_stride + lists_off);
     const int pitch = R;
-    const bool flat = flat_i != 0;  // uniform
     const unsigned slots = (unsigned)G * (unsigned)R;
-    // every reported key, spread over the threads by region (only where neither the registers nor the LDS hold
-    // the keys, or too many of them tie)
+    // every reported key, a thread per region (only where neither the registers nor the LDS hold the keys)
     auto each_key = [&](auto f) {
-        const int step = flat ? MERGE_NT / WAVE : MERGE_NT;  // few regions: a wavefront per region
-        const unsigned i0 = flat ? tid % WAVE : 0, di = flat ? WAVE : 1;
-        for (int g = flat ? tid / WAVE : tid; g < G; g += step) {
+        for (int g = tid; g < G; g += MERGE_NT) {
             const unsigned c = min(counts[g], (unsigned)pitch);
             const uint64_t *l = lists + (size_t)g * pitch;
-            for (unsigned i = i0; i < c; i += 4 * di) {  // four loads in flight before the first use
+            for (unsigned i = 0; i < c; i += 4) {  // four loads in flight before the first use
                 uint64_t k[4];
 #pragma unroll
-                for (int u = 0; u < 4; ++u) k[u] = (i + u * di < c) ? l[i + u * di] : 0;
+                for (int u = 0; u < 4; ++u) k[u] = (i + u < c) ? l[i + u] : 0;
 #pragma unroll
                 for (int u = 0; u < 4; ++u)
-                    if (i + u * di < c) f(k[u]);
+                    if (i + u < c) f(k[u]);
             }
         }
     };
@@ -632,24 +629,26 @@ __global__ __launch_bounds__(MERGE_NT) void merge_gather_kernel(
     // significant bits in which the keys differ at all (the bits above them agree), found from the OR and the
     // AND of all keys.
     constexpr bool ADAPT = sizeof(DistT) != 1;
+    static_assert(FLAT || ADAPT, "byte sums are gathered from filled regions only");
+    constexpr int PER = FLAT ? MERGE_SLOTS : MERGE_PER;
     const int lane = lane_id();
-    uint64_t key[MERGE_SLOTS];    // flat: the keys of this thread's slots, ~0 for none
-    unsigned place[MERGE_PER];    // else: where the keys of this thread lie
+    uint64_t key[PER];            // flat: the keys of this thread's slots, ~0 for none
+    unsigned place[PER];          // else: where the keys of this thread lie
     unsigned total;
-    bool in_lds = false;          // the keys (or, of too many, those that matter) are in lkeys
+    bool placed = false;          // place[] is set
     // Thousands of keys that differ in a few bins would queue at the same LDS words: 16 replicas, a word apart.
     unsigned *rep = reinterpret_cast<unsigned *>(lkeys);
     static_assert(MERGE_REP * 257 * sizeof(unsigned) <= sizeof(lkeys), "replicas of the histogram");
-    auto count = [&](unsigned bin) { atomicAdd(flat ? &rep[(lane % MERGE_REP) * 257 + bin] : &sc.hist[bin], 1u); };
+    auto count = [&](unsigned bin) { atomicAdd(FLAT ? &rep[(lane % MERGE_REP) * 257 + bin] : &sc.hist[bin], 1u); };
     auto join_counts = [&]() {  // the whole workgroup, after a barrier
-        if (flat && tid < 256) {
+        if (FLAT && tid < 256) {
             unsigned h = 0;
 #pragma unroll
             for (int r = 0; r < MERGE_REP; ++r) h += rep[r * 257 + tid];
             sc.hist[tid] = h;
         }
     };
-    if (flat) {
+    if constexpr (FLAT) {
         for (int i = tid; i < MERGE_REP * 257; i += MERGE_NT) rep[i] = 0;
         if (tid < MERGE_FLAT_G) {
             const unsigned c = tid < G ? min(counts[tid], (unsigned)pitch) : 0u;
@@ -702,7 +701,7 @@ __global__ __launch_bounds__(MERGE_NT) void merge_gather_kernel(
         __syncthreads();
         total = lcnt;
         if (total <= (unsigned)MERGE_CAP) {  // uniform
-            in_lds = true;
+            placed = true;
 #pragma unroll
             for (int t = 0; t < MERGE_PER; ++t) {
                 const unsigned i = tid + t * MERGE_NT;
@@ -710,17 +709,14 @@ __global__ __launch_bounds__(MERGE_NT) void merge_gather_kernel(
             }
 #pragma unroll
             for (int t = 0; t < MERGE_PER; ++t) key[t] = place[t] != NO_KEY ? lists[place[t]] : ~0ull;
-#pragma unroll
-            for (int t = 0; t < MERGE_PER; ++t)
-                if (place[t] != NO_KEY) lkeys[tid + t * MERGE_NT] = key[t];
         }
     }
-    const bool placed = in_lds;                        // place[] is set
-    const int nkey = flat ? MERGE_SLOTS : placed ? MERGE_PER : 0;  // keys of this thread in registers
+    const bool in_regs = FLAT || placed;               // key[] is set
     auto own_keys = [&](auto f) {
+        if (!in_regs) return;  // uniform
 #pragma unroll
-        for (int t = 0; t < MERGE_SLOTS; ++t) {
-            if (t >= nkey || (unsigned)(t * MERGE_NT) >= (flat ? slots : total)) break;  // uniform
+        for (int t = 0; t < PER; ++t) {
+            if ((unsigned)(t * MERGE_NT) >= (FLAT ? slots : total)) break;  // uniform
             if (key[t] != ~0ull) f(key[t]);
         }
     };
@@ -737,37 +733,12 @@ __global__ __launch_bounds__(MERGE_NT) void merge_gather_kernel(
             atomicAnd(&all_and, my_and);
         }
     } else {
-        auto count_key = [&](uint64_t k) { count((unsigned)(k >> 32) & 255u); };
-        if (nkey) own_keys(count_key);
-        else each_key(count_key);
-        if (flat) {  // uniform
-            __syncthreads();
-            join_counts();
-        }
+        own_keys([&](uint64_t k) { count((unsigned)(k >> 32) & 255u); });
+        __syncthreads();
+        join_counts();
     }
     __syncthreads();
     need = min(need, total);
-    if constexpr (!ADAPT) {
-        // More keys than registers and LDS hold (loose bounds, many regions): the histogram counted all of
-        // them, so the bin of the need-th key is known, and only the keys up to that bin are gathered.
-        if (!nkey && need > 0) {  // uniform
-            select_bin(&sc, need);
-            __syncthreads();
-            const unsigned bin = sc.bin;
-            const unsigned upto = need - sc.need + sc.hist[bin];  // keys in the bins up to `bin`
-            __syncthreads();
-            if (upto <= (unsigned)MERGE_CAP) {
-                if (tid == 0) lcnt = 0;
-                __syncthreads();
-                each_key([&](uint64_t k) {
-                    if (((unsigned)(k >> 32) & 255u) <= bin) lkeys[atomicAdd(&lcnt, 1u)] = k;
-                });
-                __syncthreads();
-                total = upto;
-                in_lds = true;
-            }
-        }
-    }
     int TOP = 32;
     if constexpr (ADAPT) {
         const unsigned long long diff = all_or ^ all_and;
@@ -780,7 +751,7 @@ __global__ __launch_bounds__(MERGE_NT) void merge_gather_kernel(
     }
 
     bool done = false;
-    if (need > 0 && (nkey || in_lds)) {  // uniform
+    if (need > 0 && in_regs) {  // uniform
         // bin of the need-th key by its most significant byte, and the keys up to that bin
         select_bin(&sc, need);
         __syncthreads();
@@ -791,11 +762,7 @@ __global__ __launch_bounds__(MERGE_NT) void merge_gather_kernel(
                 if (slot < (unsigned)MERGE_NT) cand[slot] = k;
             }
         };
-        if (nkey) {
-            own_keys(keep);
-        } else {
-            for (unsigned i = tid; i < total; i += MERGE_NT) keep(lkeys[i]);
-        }
+        own_keys(keep);
         __syncthreads();
         const unsigned nc = ccnt;
         if (nc <= (unsigned)MERGE_NT) {  // uniform: rank the candidates against each other
@@ -829,32 +796,32 @@ __global__ __launch_bounds__(MERGE_NT) void merge_gather_kernel(
 
     if (need > 0 && !done) {
         // full radix select, then order the winners by rank
-        uint64_t kth;
-        if (in_lds) kth = block_radix_select<uint64_t, KBYTES>(lkeys, total, need, &sc);
-        else kth = block_radix_select_each<uint64_t, KBYTES>(each_key, need, &sc);
-        __syncthreads();
-        uint64_t mine[MERGE_CAP / MERGE_NT];
-        if (in_lds) {
-#pragma unroll
-            for (int t = 0; t < MERGE_CAP / MERGE_NT; ++t) {
-                const unsigned i = tid + t * MERGE_NT;
-                mine[t] = (i < total) ? lkeys[i] : ~0ull;
-            }
-        }
-        if (tid == 0) lcnt = 0;
-        __syncthreads();
-        if (in_lds) {
-#pragma unroll
-            for (int t = 0; t < MERGE_CAP / MERGE_NT; ++t) {
-                const unsigned i = tid + t * MERGE_NT;
-                const bool ok = (i < total) && mine[t] <= kth;
-                const unsigned slot = wave_append_slot(ok, &lcnt);
-                if (ok) lkeys[slot] = mine[t];
-            }
-        } else {
-            each_key([&](uint64_t k) {
+        auto winners = [&](auto each, uint64_t kth) {
+            each([&](uint64_t k) {
                 if (k <= kth) lkeys[atomicAdd(&lcnt, 1u)] = k;  // exactly `need` keys: they are unique
             });
+        };
+        const unsigned held = FLAT ? slots : total;  // key[t] of thread tid is number tid + t MERGE_NT of these
+        if (held <= (unsigned)MERGE_CAP) {  // uniform: eight passes over LDS are shorter than over the registers
+#pragma unroll
+            for (int t = 0; t < (PER < MERGE_PER ? PER : MERGE_PER); ++t)
+                if (tid + t * MERGE_NT < held) lkeys[tid + t * MERGE_NT] = key[t];  // (an empty slot's ~0 comes last)
+            __syncthreads();
+            const uint64_t kth = block_radix_select<uint64_t, KBYTES>(lkeys, held, need, &sc);
+            __syncthreads();
+            if (tid == 0) lcnt = 0;
+            __syncthreads();
+            winners(own_keys, kth);
+        } else {
+            auto all_keys = [&](auto f) {
+                if constexpr (FLAT) own_keys(f);
+                else each_key(f);
+            };
+            const uint64_t kth = block_radix_select_each<uint64_t, KBYTES>(all_keys, need, &sc);
+            __syncthreads();
+            if (tid == 0) lcnt = 0;
+            __syncthreads();
+            winners(all_keys, kth);
         }
         __syncthreads();
         for (unsigned i = tid; i < need; i += MERGE_NT) {
@@ -875,7 +842,7 @@ __global__ __launch_bounds__(MERGE_NT) void merge_gather_kernel(
 
     // Leave every word this call wrote in the workspace zero again, so that the next call
     // finds clean control blocks wherever its own layout puts them.
-    if (flat) {
+    if constexpr (FLAT) {
 #pragma unroll
         for (int t = 0; t < MERGE_SLOTS; ++t)
             if (key[t] != ~0ull) lists[tid + t * MERGE_NT] = 0;
@@ -895,22 +862,53 @@ __global__ __launch_bounds__(MERGE_NT) void merge_gather_kernel(
     for (int i = tid; i < (int)(sizeof(ScanHeader) / 4); i += MERGE_NT) z[i] = 0;
 }
 
-// One merge workgroup per query.  filled: the regions are expected to be mostly full (no sampled bound, or the few
-// long workgroups of an inverted-index query).
+// What the single-query kernels leave in a region of region B.
+enum MergeFill {
+    MERGE_SPARSE,  // a key or two: a sampled bound stood before the scan
+    MERGE_MIXED,   // anything (batches over an inverted index)
+    MERGE_FILLED   // mostly R keys: no sampled bound, or the few long workgroups of an inverted-index query
+};
+
+// One merge workgroup per query.  The gathering kernel takes filled regions whose slots fit its registers, and float
+// keys behind a sampled bound; not where hardly a key is there to gather.  us per call, the kernel above / gathering:
+//   byte sums, 16 queries x 100 k codes, m = 16 (98 regions): R = 1 13.0 / 13.9, R = 20 15.4 / 15.6, R = 100 24.9 / 20.3;
+//   floats, one query, 4-bit components, m = 16: 20 k codes (20 regions) R = 1 13.3 / 14.4, R = 10 17.2 / 14.9, 100 k R = 1
+//   16.0 / 14.6; behind a bound, 2 M codes: R = 1 21.5 / 23.1, R = 20 26.7 / 26.9, R = 50 27.6 / 26.6, R = 100 30.1 / 27.3.
+// Visiting every slot of sparse regions (256 regions, R = 100) took calls of 5 to 7 queries 8 us of 28.
 template <typename DistT, int KBYTES>
-inline int launch_merge(int nq, hipStream_t st, bool filled, char *ws, size_t ws_stride, size_t counts_off,
+inline int launch_merge(int nq, hipStream_t st, MergeFill fill, char *ws, size_t ws_stride, size_t counts_off,
                         size_t lists_off, int G, unsigned need, int R, DistT pad_dist, uint32_t *out_idx, DistT *out_dist,
                         size_t countsA_off, size_t listsA_off, int GA, int pitchA, unsigned *flags, const uint32_t *ids,
                         int64_t n_ids)
 {
-    const bool flat = filled && G <= MERGE_FLAT_G && (int64_t)G * R <= MERGE_SLOTS * MERGE_NT;
-    if (!flags && R <= MERGE_GATHER_R && (flat || (!filled && sizeof(DistT) > 1)))
-        launch(QADC_PROF_MERGE, (merge_gather_kernel<DistT, KBYTES>), dim3(nq), dim3(MERGE_NT), 0, st, ws, ws_stride,
-               counts_off, lists_off, G, need, R, pad_dist, out_idx, out_dist, ids, n_ids, flat ? 1 : 0);
-    else
-        launch(QADC_PROF_MERGE, (merge_topk_kernel<DistT, KBYTES>), dim3(nq), dim3(MERGE_NT), 0, st, ws, ws_stride,
-               counts_off, lists_off, G, need, R, pad_dist, out_idx, out_dist, countsA_off, listsA_off, GA, pitchA, flags,
-               ids, n_ids);
+    constexpr bool BYTES = sizeof(DistT) == 1;
+    const int64_t slots = (int64_t)G * R;
+    if (!flags && R <= MERGE_GATHER_R) {
+        if (fill == MERGE_FILLED && G <= MERGE_FLAT_G && slots <= MERGE_SLOTS * MERGE_NT && (BYTES ? slots >= 2048 : R >= 64 || (G >= 8 && slots >= 96))) {
+            launch(QADC_PROF_MERGE, (merge_gather_kernel<DistT, KBYTES, true>), dim3(nq), dim3(MERGE_NT), 0, st, ws,
+                   ws_stride, counts_off, lists_off, G, need, R, pad_dist, out_idx, out_dist, ids, n_ids);
+            return QADC_OK;
+        }
+        if constexpr (!BYTES) {
+            if (fill == MERGE_SPARSE && R >= MERGE_GATHER_MIN_R) {
+                launch(QADC_PROF_MERGE, (merge_gather_kernel<DistT, KBYTES, false>), dim3(nq), dim3(MERGE_NT), 0, st, ws,
+                       ws_stride, counts_off, lists_off, G, need, R, pad_dist, out_idx, out_dist, ids, n_ids);
+                return QADC_OK;
+            }
+        }
+    }
+#define QADC_MERGE(VISIT_)                                                                                             \
+    launch(QADC_PROF_MERGE, (merge_topk_kernel<DistT, KBYTES, VISIT_>), dim3(nq), dim3(MERGE_NT), 0, st, ws, ws_stride, \
+           counts_off, lists_off, G, need, R, pad_dist, out_idx, out_dist, countsA_off, listsA_off, GA, pitchA, flags,  \
+           ids, n_ids)
+    if constexpr (BYTES) {
+        if (fill == MERGE_SPARSE && !flags) {
+            QADC_MERGE(false);
+            return QADC_OK;
+        }
+    }
+    QADC_MERGE(true);
+#undef QADC_MERGE
     return QADC_OK;
 }
 

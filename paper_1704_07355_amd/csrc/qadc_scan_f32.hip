@@ -671,7 +671,7 @@ int scan_topk_f32(int variant, const uint8_t *codes, int64_t n, int m, const flo
         int rc = (p.KSUB == 16) ? dispatch_f32<16>(p, codes, n, lq, nb, R, ws, flags, st)
                                 : dispatch_f32<256>(p, codes, n, lq, nb, R, ws, flags, st);
         if (rc != QADC_OK) return rc;
-        rc = launch_merge<float, 8>(nb, st, p.seed_wgs == 0, ws, p.stride, p.l.counts_off, p.l.lists_off, p.G,
+        rc = launch_merge<float, 8>(nb, st, p.seed_wgs == 0 ? MERGE_FILLED : MERGE_SPARSE, ws, p.stride, p.l.counts_off, p.l.lists_off, p.G,
                                     (unsigned)min((int64_t)R, n), R, __builtin_inff(),
                                     out_idx + (size_t)q0 * R, out_dist + (size_t)q0 * R, p.countsA_off,
                                     p.listsA_off, flags ? p.GC : 0, (int)F32T_LCAP, flags, (const uint32_t *)nullptr,

@@ -5,7 +5,7 @@ import os
 import numpy as np
 import pytest
 
-from gpu_common import config1, to_gpu, idx_np
+from gpu_common import gpu_us, config1, to_gpu, idx_np
 
 pytestmark = pytest.mark.gpu
 
@@ -807,3 +807,31 @@ def test_merge_of_filled_regions(Q, variant, nq, n, R):
         wi, wd = cref.scan_topk_f32(codes, luts, R)
         idx, dist = Q.qadc_scan_topk(Q.QADC_F32_4BIT, to_gpu(codes), to_gpu(luts), R)
     assert np.array_equal(idx_np(idx), wi) and np.array_equal(dist.cpu().numpy(), wd)
+
+
+# around the lines of the choice of a merge kernel: regions of 1024 codes; 2048 key slots of byte sums, 8 regions and 96
+# slots or R = 64 of floats, R = 32 behind a bound, 6144 keys held in LDS where thousands tie
+@pytest.mark.parametrize("variant,n,R", [("u8", 20_480, 100), ("u8", 20_481, 100), ("u8", 62_464, 100), ("u8", 62_465, 100),
+                                         ("f32", 7_168, 13), ("f32", 7_169, 13), ("f32", 1_500, 63), ("f32", 1_500, 64),
+                                         ("f32", 62_464, 100), ("f32", 62_465, 100), ("f32", 700_003, 31),
+                                         ("f32", 700_003, 32)])
+def test_merge_kernels_around_their_lines(Q, variant, n, R):
+    test_merge_of_filled_regions(Q, variant, 2, n, R)
+
+
+def test_a_few_queries_do_not_pay_for_empty_regions(Q):
+    """Five queries over a million codes: 256 regions that hold a key or two each.  The merge may not visit every key
+    slot they could have, which it did for R = 100 and not, of more slots, for R = 200."""
+    import torch
+    rng = np.random.default_rng(5)
+    codes = to_gpu(rng.integers(0, 256, size=(1_000_000, 4), dtype=np.uint8))
+    qluts = to_gpu(rng.integers(0, 60, size=(5, 8, 16)).astype(np.uint8))
+    us = []
+    for R in (100, 200):
+        ws = Q.qadc_workspace_init(torch.empty((Q.qadc_workspace_bytes(Q.QADC_WS_SCAN_TOPK, 1_000_000, 8, 5, R),),
+                                               dtype=torch.uint8, device="cuda:0"))
+        oi = torch.empty((5, R), dtype=torch.int32, device="cuda:0")
+        od = torch.empty((5, R), dtype=torch.uint8, device="cuda:0")
+        us.append(gpu_us(lambda: Q.qadc_scan_topk(Q.QADC_U8_4BIT, codes, qluts, R, workspace=ws, out_idx=oi, out_dist=od),
+                         reps=200))
+    assert us[0] < 1.15 * us[1], us
