@@ -579,16 +579,25 @@ static bool make_scan_plan(int variant, int64_t n, int m, int nq, int R, ScanPla
     const int64_t tiles = n > 0 ? ceil_div(n, tile) : 1;
     // every workgroup takes tiles g, g+G, ...; its tiles must number below 2^24 / tile, the
     // range of the index bits of a candidate key
-    // 2048 workgroups per query for a single one; several share the GPU, and fewer, longer workgroups
-    // set up fewer tables and leave the merge fewer regions (us per call with 2048 each / this rule, 128
-    // components: 3 M codes m = 32: 2 queries 39.9 / 38.7, 4 63.9 / 60.1, 6 87 / 83; m = 64, whose tables
-    // are twice as large: 1 query 48.4 / 43.8, 2 80 / 65, 4 142 / 104; 20 M codes m = 16, 6 queries: 174 / 139)
+    // 2048 workgroups per query for a single one; several share the GPU, and fewer, longer workgroups set up fewer tables
+    // and leave the merge fewer regions: a power of two (the workgroups of all queries that read a tile then sit on one
+    // CU and march together; 248 instead of 256 cost 4 queries of m = 64 13 %), halved as the queries double, an octave
+    // earlier for 32-byte codes, whose tables are twice as large.  us per call with 2048 each / this rule, R = 100:
+    //   4-bit, 4 M codes m = 32: 2 queries 37.0 / 35.9, 4 57.4 / 56.6, 5 68.6 / 69.3; 16 M m = 16: 4 queries 89.8 / 90.6;
+    //   m = 64, 4 M: 1 query 50.7 / 46.8, 2 81.9 / 65.1, 4 142.7 / 103.9; 1 M m = 32: 5 queries 37.3 / 32.0;
+    //   8-bit, 4 M m = 16: 4 queries 54.6 / 55.8, 7 queries 83.9 / 88.2 with 256 and 82.2 with 1024; 16 M m = 16: 3 133.6 /
+    //   125.4; 4 M m = 32: 4 142.0 / 102.9;  6-bit codes gain below 4 M codes, m = 32, and lose above it (16 M m = 8, 5 queries
+    //   114.9 / 130.9; m = 32, 2 queries 153.5 / 167.5) and keep 2048.
     int64_t g_def = 2048;
-    for (int64_t k = p->B == 32 ? 1 : 2; (p->B == 32 ? k < 2 * (int64_t)nq : k <= 2 * ((int64_t)nq - 1)) && g_def > 256; k *= 2)
-        g_def /= 2;
-    // (a power of two: the workgroups of all queries that read a tile then sit on one CU and march together; 248
-    // instead of 256 cost 4 queries of m = 64 13 %.  With two tiles a workgroup the same number for each counts more.)
-    if (nq > 1 && tiles > g_def && tiles < 3 * g_def) g_def = ceil_div(tiles, (tiles + g_def / 2) / g_def);
+    if (!six) {
+        for (int64_t k = p->B == 32 ? 1 : 2; (p->B == 32 ? k < 2 * (int64_t)nq : k <= 2 * ((int64_t)nq - 1)) && g_def > 256; k *= 2)
+            g_def /= 2;
+        if (p->wide && p->B < 32 && nq > 4) g_def = 1024;
+        // (long reports: 7 queries, R = 1000, 600 k codes m = 16: 50.8 us with 512, 53.6 with 256)
+        if (p->B < 32 && R > 256) g_def = std::max<int64_t>(g_def, 512);
+        // (a tile each where a second round would be half empty: 300 k codes m = 16, 293 tiles, 5 queries 18.1 against 18.8)
+        if (nq > 1 && 2 * tiles < 3 * g_def) g_def = std::max(tiles, g_def);
+    }
     int64_t G = knob_or(knobs().scan_wgs, (int)g_def);
     if (G < 1) G = 1;
     if (G > tiles) G = tiles;

@@ -835,3 +835,29 @@ def test_a_few_queries_do_not_pay_for_empty_regions(Q):
         us.append(gpu_us(lambda: Q.qadc_scan_topk(Q.QADC_U8_4BIT, codes, qluts, R, workspace=ws, out_idx=oi, out_dist=od),
                          reps=200))
     assert us[0] < 1.15 * us[1], us
+
+
+@pytest.mark.parametrize("variant,m,n,nq", [("U8_6BIT", 8, 16_000_000, 5), ("U8_6BIT", 32, 16_000_000, 2),
+                                            ("U8_8BIT", 16, 4_000_000, 7), ("U8_4BIT", 64, 4_000_000, 4)])
+def test_workgroups_per_query_follow_the_codes(Q, monkeypatch, variant, m, n, nq):
+    """The number of workgroups of a query is no worse than 256 and than 2048, for each kind of codes."""
+    import torch
+    k, row = {"U8_4BIT": (16, m // 2), "U8_6BIT": (64, 3 * m // 4), "U8_8BIT": (256, m)}[variant]
+    call = {"U8_4BIT": Q.QADC_WS_SCAN_TOPK, "U8_6BIT": Q.QADC_WS_SCAN_U8_6BIT, "U8_8BIT": Q.QADC_WS_SCAN_U8_8BIT}[variant]
+    g = torch.Generator(device="cuda:0")
+    g.manual_seed(m)
+    codes = torch.randint(0, 256, (n, row), generator=g, device="cuda:0", dtype=torch.uint8)
+    qluts = torch.randint(0, 512 // m, (nq, m, k), generator=g, device="cuda:0", dtype=torch.uint8)
+    us, ref = {}, None
+    for wgs in (None, "256", "2048"):
+        if wgs:
+            monkeypatch.setenv("QADC_SCAN_WGS", wgs)
+        ws = Q.qadc_workspace_init(torch.empty((Q.qadc_workspace_bytes(call, n, m, nq, 100),), dtype=torch.uint8,
+                                               device="cuda:0"))
+        f = lambda: Q.qadc_scan_topk(getattr(Q, "QADC_" + variant), codes, qluts, 100, workspace=ws)
+        out = f()
+        ref = ref or out
+        assert torch.equal(out[0], ref[0]) and torch.equal(out[1], ref[1])
+        us[wgs] = gpu_us(f, reps=50)
+    monkeypatch.delenv("QADC_SCAN_WGS")
+    assert us[None] < 1.1 * min(us.values()), us
