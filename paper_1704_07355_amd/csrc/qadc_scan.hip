@@ -585,14 +585,16 @@ static bool make_scan_plan(int variant, int64_t n, int m, int nq, int R, ScanPla
     // earlier for 32-byte codes, whose tables are twice as large.  us per call with 2048 each / this rule, R = 100:
     //   4-bit, 4 M codes m = 32: 2 queries 37.0 / 35.9, 4 57.4 / 56.6, 5 68.6 / 69.3; 16 M m = 16: 4 queries 89.8 / 90.6;
     //   m = 64, 4 M: 1 query 50.7 / 46.8, 2 81.9 / 65.1, 4 142.7 / 103.9; 1 M m = 32: 5 queries 37.3 / 32.0;
-    //   8-bit, 4 M m = 16: 4 queries 54.6 / 55.8, 7 queries 83.9 / 88.2 with 256 and 82.2 with 1024; 16 M m = 16: 3 133.6 /
+    //   8-bit, 4 M m = 16: 4 queries 54.6 / 55.8, 7 queries 83.9 / 82.2 (88.2 with 256); 16 M m = 16: 3 133.6 /
     //   125.4; 4 M m = 32: 4 142.0 / 102.9;  6-bit codes gain below 4 M codes, m = 32, and lose above it (16 M m = 8, 5 queries
     //   114.9 / 130.9; m = 32, 2 queries 153.5 / 167.5) and keep 2048.
     int64_t g_def = 2048;
     if (!six) {
         for (int64_t k = p->B == 32 ? 1 : 2; (p->B == 32 ? k < 2 * (int64_t)nq : k <= 2 * ((int64_t)nq - 1)) && g_def > 256; k *= 2)
             g_def /= 2;
-        if (p->wide && p->B < 32 && nq > 4) g_def = 1024;
+        // (5 to 7 queries over codes of 8 and 16 bytes, once there are two tiles each: 5 queries m = 16, 6 M 68.7 us with 256,
+        // 65.5 with 1024; 10 M 89.2 / 85.3; 1 M 22.4 / 24.8; m = 8, 20 M 97.6 / 100.5)
+        if (p->B >= 8 && p->B < 32 && nq > 4 && tiles >= 2048) g_def = 1024;
         // (long reports: 7 queries, R = 1000, 600 k codes m = 16: 50.8 us with 512, 53.6 with 256)
         if (p->B < 32 && R > 256) g_def = std::max<int64_t>(g_def, 512);
         // (a tile each where a second round would be half empty: 300 k codes m = 16, 293 tiles, 5 queries 18.1 against 18.8)

@@ -363,10 +363,11 @@ __global__ __launch_bounds__(tiled_nt(B)) void scan_u8_tiled16_kernel(
 // with 4: measured against the vector-ALU kernels over 10 M codes) and for its forms with 64 and 128
 // queries per wavefront
 static int mfma_min_q(int B) { return std::max(1, knob_or(knobs().mfma_min_q, B >= 8 ? 2 : TILED_MFMA_MIN_Q_B4)); }
-// 8 to 15 queries over many 8-byte codes: the byte-lane kernel (20 M codes, 12 queries: 150 against 156 us)
+// 8 to 15 queries over many 8-byte codes: the byte-lane kernel (20 M codes, 12 queries: 150 against 156 us), and the 8
+// queries of one of its workgroups over many 16-byte codes (20 M 174 against 212 us, 10 M 117 / 127, 5 M 91 / 87)
 bool tiled_bytes_pay(int B, int64_t n, int nq)
 {
-    return B == 8 && nq >= TILED_MIN_Q && nq < 16 && (double)n * B > 120e6;
+    return (double)n * B > 120e6 && ((B == 8 && nq >= TILED_MIN_Q && nq < 16) || (B == 16 && nq == TILED_Q));
 }
 // Does a call of nq queries over n codes of B bytes gain by the matrix-core kernel?  It costs some launches
 // more than a scan per query, and its scan of up to 32 queries takes as long as two per-query scans; 4-byte

@@ -838,7 +838,8 @@ def test_a_few_queries_do_not_pay_for_empty_regions(Q):
 
 
 @pytest.mark.parametrize("variant,m,n,nq", [("U8_6BIT", 8, 16_000_000, 5), ("U8_6BIT", 32, 16_000_000, 2),
-                                            ("U8_8BIT", 16, 4_000_000, 7), ("U8_4BIT", 64, 4_000_000, 4)])
+                                            ("U8_8BIT", 16, 4_000_000, 7), ("U8_4BIT", 64, 4_000_000, 4),
+                                            ("U8_4BIT", 32, 5_000_000, 5)])
 def test_workgroups_per_query_follow_the_codes(Q, monkeypatch, variant, m, n, nq):
     """The number of workgroups of a query is no worse than 256 and than 2048, for each kind of codes."""
     import torch
@@ -861,3 +862,26 @@ def test_workgroups_per_query_follow_the_codes(Q, monkeypatch, variant, m, n, nq
         us[wgs] = gpu_us(f, reps=50)
     monkeypatch.delenv("QADC_SCAN_WGS")
     assert us[None] < 1.1 * min(us.values()), us
+
+
+@pytest.mark.parametrize("m,n,nq", [(32, 20_000_000, 8), (32, 8_000_000, 8), (16, 15_100_000, 12), (16, 14_900_000, 12)])
+def test_batches_that_fill_the_byte_lane_kernels(Q, monkeypatch, m, n, nq):
+    """Full groups of 8 queries over many codes, on both sides of 120 MB: the same result as without the matrix-core
+    kernel, and not slower by more than a tenth."""
+    import torch
+    g = torch.Generator(device="cuda:0")
+    g.manual_seed(m)
+    codes = torch.randint(0, 256, (n, m // 2), generator=g, device="cuda:0", dtype=torch.uint8)
+    qluts = torch.randint(0, 512 // m, (nq, m, 16), generator=g, device="cuda:0", dtype=torch.uint8)
+    us, ref = [], None
+    for mfma in ("1", "0"):
+        monkeypatch.setenv("QADC_TILED_MFMA", mfma)
+        ws = Q.qadc_workspace_init(torch.empty((Q.qadc_workspace_bytes(Q.QADC_WS_SCAN_TOPK, n, m, nq, 100),),
+                                               dtype=torch.uint8, device="cuda:0"))
+        f = lambda: Q.qadc_scan_topk(Q.QADC_U8_4BIT, codes, qluts, 100, workspace=ws)
+        out = f()
+        ref = ref or out
+        assert torch.equal(out[0], ref[0]) and torch.equal(out[1], ref[1])
+        us.append(gpu_us(f, reps=30))
+    monkeypatch.delenv("QADC_TILED_MFMA")
+    assert us[0] < 1.1 * us[1], us
