@@ -24,6 +24,9 @@
  *    differently, and table data of the earlier call may lie where the new one
  *    keeps its control words.  Calls of one shape need no clearing in between.
  *    (qadc_ivf_search clears its own control words at every call.)
+ *    The sizes asked for hold the fastest plan of the call and a smaller one; the call itself only
+ *    refuses (QADC_ENOMEM) a workspace that does not hold the smaller one, and is slower in between.
+ *    So a workspace sized for a batch of up to 7 queries serves every smaller batch too.
  *    Calls that share a workspace must be ordered on one stream.
  *  - Return value: QADC_OK, or a negative error.  On QADC_EINVAL / QADC_ENOMEM
  *    nothing was enqueued and the outputs are untouched.  qadc_last_error()
@@ -209,8 +212,8 @@ int qadc_search(const float *codebooks, int d, int m, const float *queries, int 
  * of QADC_STATIC_SCRATCH_BYTES inside the library (each GPU the entry point is used on holds its
  * own copy until the process ends).  The call allocates nothing and frees nothing.
  *   - Limit: the scratch of ONE query (qadc_workspace_bytes(QADC_WS_SEARCH, n, m, 1, R)) must fit
- *     the array, else QADC_ENOMEM and nothing is enqueued; batches larger than the array holds are
- *     cut into several launch sequences on `stream` (same results).
+ *     the array, else QADC_ENOMEM and nothing is enqueued; batches whose smaller plan (see above) the
+ *     array does not hold are cut into several launch sequences on `stream` (same results).
  *   - All calls on one GPU share that GPU's array: calls that overlap in time on one GPU -- from two
  *     streams or two threads -- race; order them on one stream.  The array is cleared by a kernel
  *     on `stream` at the first call on a GPU, at a call whose sizes (n, m, nq, R) differ from the

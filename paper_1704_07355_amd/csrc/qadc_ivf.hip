@@ -1558,7 +1558,9 @@ static bool shared_lists_pay(const qadc_ivf_index *ix, int nq, int nprobe)
     return nq >= IVF_SHARED_MIN_Q || (nq >= 64 && (double)nq * nprobe >= 14.0 * (double)ix->K);
 }
 
-static bool make_ivf_plan(const qadc_ivf_index *ix, int nq, int nprobe, int R, IvfPlan *p)
+// small: the plan for a workspace that the best one does not fit (batches of 64 to 383 queries scan query by query).
+// qadc_ivf_workspace_bytes counts both, and what this one takes is enough: see make_scan_plan.
+static bool make_ivf_plan(const qadc_ivf_index *ix, int nq, int nprobe, int R, bool small, IvfPlan *p)
 {
     if (!ix || nq < 1 || nprobe < 1 || nprobe > IVF_MAX_NPROBE || R < 1 || R > QADC_MAX_R) return false;
     if (!(ix->m == 8 || ix->m == 16 || ix->m == 32 || ix->m == 64)) return false;
@@ -1587,7 +1589,7 @@ static bool make_ivf_plan(const qadc_ivf_index *ix, int nq, int nprobe, int R, I
     // that probe it (QADC_IVF_SHARED=1 / 0 forces / forbids it)
     const int shared_knob = knobs().ivf_shared;
     p->shared = R <= IVF_SHARED_MAX_R && ix->K <= IVF_SHARED_MAX_K && p->seed_per_list > 0 && ix->m <= 64 &&
-                (shared_knob >= 0 ? shared_knob != 0 : shared_lists_pay(ix, nq, nprobe));
+                (shared_knob >= 0 ? shared_knob != 0 : small ? nq >= IVF_SHARED_MIN_Q : shared_lists_pay(ix, nq, nprobe));
     // (the per-query kernel then only takes the rarely probed lists and queries that are redone: 150 queries over 1e6
     // codes spent 25 us on 109 workgroup slots per query, nearly all empty)
     p->wgs = p->shared && knobs().ivf_wgs < 0 ? std::min(p->W, 24) : p->W;
@@ -1653,9 +1655,9 @@ static bool make_ivf_plan(const qadc_ivf_index *ix, int nq, int nprobe, int R, I
 
 size_t ivf_workspace_bytes(const qadc_ivf_index *ix, int nq, int nprobe, int R)
 {
-    IvfPlan p;
-    if (!make_ivf_plan(ix, nq, nprobe, R, &p)) return 0;
-    return p.bytes;
+    IvfPlan p, small;
+    if (!make_ivf_plan(ix, nq, nprobe, R, false, &p) || !make_ivf_plan(ix, nq, nprobe, R, true, &small)) return 0;
+    return std::max(p.bytes, small.bytes);
 }
 
 int ivf_search(const qadc_ivf_index *ix, const float *queries, int nq, int nprobe, int R, int init,
@@ -1663,11 +1665,11 @@ int ivf_search(const qadc_ivf_index *ix, const float *queries, int nq, int nprob
                uint8_t *out_dist, int32_t *dbg_probes, uint8_t *dbg_qluts, void *workspace,
                size_t workspace_bytes, hipStream_t st)
 {
-    IvfPlan p;
+    IvfPlan p, small;
     if (nq == 0) return QADC_OK;  // nothing asked for, whatever the pointers
     if (!ix || !queries || !out_ids || !out_dist)
         return fail(QADC_EINVAL, "qadc_ivf_search: null pointer");
-    if (!make_ivf_plan(ix, nq, nprobe, R, &p))
+    if (!make_ivf_plan(ix, nq, nprobe, R, false, &p) || !make_ivf_plan(ix, nq, nprobe, R, true, &small))
         return fail(QADC_EINVAL, "qadc_ivf_search: unsupported nq=%d nprobe=%d R=%d d=%d m=%d K=%d", nq,
                     nprobe, R, ix->d, ix->m, ix->K);
     if (!ix->list_off || !ix->codes || !ix->ids || !ix->codebooks)
@@ -1684,8 +1686,9 @@ int ivf_search(const qadc_ivf_index *ix, const float *queries, int nq, int nprob
         return fail(QADC_EINVAL, "qadc_ivf_search: init=%d nbins=%d", init, nbins);
     if (((uintptr_t)ix->codes & 15) != 0)
         return fail(QADC_EINVAL, "qadc_ivf_search: codes must be 16-byte aligned");
-    if (!workspace || workspace_bytes < p.bytes)
-        return fail(QADC_ENOMEM, "qadc_ivf_search: workspace %zu < %zu bytes", workspace_bytes, p.bytes);
+    if (!workspace || workspace_bytes < small.bytes)
+        return fail(QADC_ENOMEM, "qadc_ivf_search: workspace %zu < %zu bytes", workspace_bytes, small.bytes);
+    if (workspace_bytes < p.bytes) p = small;
     if (((uintptr_t)workspace & 255) != 0)
         return fail(QADC_EINVAL, "qadc_ivf_search: workspace must be 256-byte aligned");
     const int d = ix->d, m = ix->m, K = ix->K;

@@ -23,7 +23,7 @@ namespace qadc {
 
 constexpr int GRP_MAX_PARTS = 1024;
 // vectors per part, at least: a wavefront's serial walk (1 M vectors: count and place 62 + 116 us at 4096); the shorter
-// one as long as the counters of all parts are no more than four per vector
+// one as long as the counters of all parts are no more than four per vector, and the workspace holds them
 constexpr int64_t GRP_MIN_PART = 1024, GRP_MIN_PART_WIDE = 4096;
 constexpr int64_t GRP_MAX_COUNTERS = 1ll << 26;  // parts * K, at most (256 MiB of counters)
 constexpr int GRP_MAX_K = 1 << 24;
@@ -34,10 +34,13 @@ struct GroupPlan {
     size_t cnt_off, size_off, total;
 };
 
-static bool make_group_plan(int64_t n, int K, GroupPlan *g)
+// small: parts of GRP_MIN_PART_WIDE vectors, for a workspace that holds no more counters.  The workspace queries give the
+// size of the best plan; the small one's is enough for any call.
+static bool make_group_plan(int64_t n, int K, bool small, GroupPlan *g)
 {
     if (n < 0 || n > 0xffffffffll || K < 1 || K > GRP_MAX_K) return false;
-    int64_t P = std::min<int64_t>(n / GRP_MIN_PART, std::max<int64_t>(n / GRP_MIN_PART_WIDE, 4 * n / K));
+    int64_t P = n / GRP_MIN_PART_WIDE;
+    if (!small) P = std::min<int64_t>(n / GRP_MIN_PART, std::max<int64_t>(P, 4 * n / K));
     P = std::max<int64_t>(1, std::min<int64_t>(GRP_MAX_PARTS, P));
     P = std::max<int64_t>(1, std::min<int64_t>(P, GRP_MAX_COUNTERS / K));
     g->P = (int)P;
@@ -51,7 +54,7 @@ static bool make_group_plan(int64_t n, int K, GroupPlan *g)
 size_t ivf_group_workspace(int64_t n, int K)
 {
     GroupPlan g;
-    return make_group_plan(n, K, &g) ? g.total : 0;
+    return make_group_plan(n, K, false, &g) ? g.total : 0;
 }
 
 __global__ void grp_zero_kernel(uint4 *p, size_t n16)
@@ -220,14 +223,15 @@ static void group_pass(const GroupKeys &g, int64_t n, int K, const GroupPlan &pl
 int ivf_group(const int32_t *cells, int64_t n, int K, int64_t *list_off, uint32_t *ids, void *workspace,
               size_t workspace_bytes, hipStream_t st)
 {
-    GroupPlan g;
-    if (!make_group_plan(n, K, &g))
+    GroupPlan g, small;
+    if (!make_group_plan(n, K, false, &g) || !make_group_plan(n, K, true, &small))
         return fail(QADC_EINVAL, "qadc_ivf_group: n=%lld (at most 2^32) K=%d (at most 2^24)", (long long)n, K);
     if (!list_off || !workspace || (n > 0 && (!cells || !ids)))
         return fail(QADC_EINVAL, "qadc_ivf_group: null pointer");
-    if (workspace_bytes < g.total || ((uintptr_t)workspace & 15))
+    if (workspace_bytes < small.total || ((uintptr_t)workspace & 15))
         return fail(QADC_ENOMEM, "qadc_ivf_group: workspace of %zu bytes, %zu needed (16-byte aligned)",
-                    workspace_bytes, g.total);
+                    workspace_bytes, small.total);
+    if (workspace_bytes < g.total) g = small;
     group_pass(GroupKeys{cells, nullptr, nullptr, 0, 1, K}, n, K, g, (char *)workspace, list_off, ids, st);
     QADC_HIP_TRY(hipGetLastError());
     return QADC_OK;
@@ -250,9 +254,9 @@ struct MiGroupPlan {
     size_t perm_off, offa_off, offb_off, bcnt_off, boff_off, total;
 };
 
-static bool make_mi_group_plan(int64_t n, int Kh, MiGroupPlan *p)
+static bool make_mi_group_plan(int64_t n, int Kh, bool small, MiGroupPlan *p)
 {
-    if (Kh < 1 || Kh > 16384 || !make_group_plan(n, Kh, &p->g)) return false;
+    if (Kh < 1 || Kh > 16384 || !make_group_plan(n, Kh, small, &p->g)) return false;
     p->nblocks = std::max<int64_t>(1, ceil_div(n, MIG_BLOCK));
     size_t o = align_up(p->g.total, 256);
     p->perm_off = o; o += align_up((size_t)std::max<int64_t>(n, 1) * sizeof(uint32_t), 256);
@@ -267,7 +271,7 @@ static bool make_mi_group_plan(int64_t n, int Kh, MiGroupPlan *p)
 size_t multi_index_group_workspace(int64_t n, int Kh)
 {
     MiGroupPlan p;
-    return make_mi_group_plan(n, Kh, &p) ? p.total : 0;
+    return make_mi_group_plan(n, Kh, false, &p) ? p.total : 0;
 }
 
 // is place p the first of its cell?  (places at and beyond n_valid are no boundaries)
@@ -350,17 +354,18 @@ int multi_index_group(const int32_t *cells, int64_t n, int Kh, int64_t max_lists
                       int64_t *list_off, uint32_t *ids, int64_t *n_lists, void *workspace, size_t workspace_bytes,
                       hipStream_t st)
 {
-    MiGroupPlan p;
-    if (!make_mi_group_plan(n, Kh, &p))
+    MiGroupPlan p, small;
+    if (!make_mi_group_plan(n, Kh, false, &p) || !make_mi_group_plan(n, Kh, true, &small))
         return fail(QADC_EINVAL, "qadc_multi_index_group: n=%lld (at most 2^32) K=%d (at most 16384)", (long long)n, Kh);
     if (max_lists < std::min<int64_t>(n, (int64_t)Kh * Kh))
         return fail(QADC_EINVAL, "qadc_multi_index_group: max_lists=%lld, min(n, K*K)=%lld needed", (long long)max_lists,
                     (long long)std::min<int64_t>(n, (int64_t)Kh * Kh));
     if (!list_off || !n_lists || !workspace || (n > 0 && (!cells || !ids || !cell_ids)))
         return fail(QADC_EINVAL, "qadc_multi_index_group: null pointer");
-    if (workspace_bytes < p.total || ((uintptr_t)workspace & 15))
+    if (workspace_bytes < small.total || ((uintptr_t)workspace & 15))
         return fail(QADC_ENOMEM, "qadc_multi_index_group: workspace of %zu bytes, %zu needed (16-byte aligned)",
-                    workspace_bytes, p.total);
+                    workspace_bytes, small.total);
+    if (workspace_bytes < p.total) p = small;
     char *ws = (char *)workspace;
     uint32_t *perm = (uint32_t *)(ws + p.perm_off);
     int64_t *offa = (int64_t *)(ws + p.offa_off);

@@ -563,7 +563,12 @@ struct ScanPlan {
     size_t counts_off, lists_off, stride, ws_bytes;
 };
 
-static bool make_scan_plan(int variant, int64_t n, int m, int nq, int R, ScanPlan *p)
+// small: the plan for a workspace that the best one does not fit.  Both are counted in qadc_workspace_bytes, and what the
+// small one takes is enough for any call: so a workspace of a given size serves the calls it always served (one sized
+// for a batch also serves the single queries of it, up to 7 queries), whatever the best plan has come to use, and the
+// static scratch array takes as many queries at a time.  It has 2048 report regions per query, or 256 and the lists
+// of longer chunks from 8 queries.
+static bool make_scan_plan(int variant, int64_t n, int m, int nq, int R, bool small, ScanPlan *p)
 {
     if (variant != QADC_U8_4BIT && variant != QADC_U8_8BIT && variant != QADC_U8_6BIT) return false;
     p->wide = variant == QADC_U8_8BIT;
@@ -589,7 +594,7 @@ static bool make_scan_plan(int variant, int64_t n, int m, int nq, int R, ScanPla
     //   125.4; 4 M m = 32: 4 142.0 / 102.9;  6-bit codes gain below 4 M codes, m = 32, and lose above it (16 M m = 8, 5 queries
     //   114.9 / 130.9; m = 32, 2 queries 153.5 / 167.5) and keep 2048.
     int64_t g_def = 2048;
-    if (!six) {
+    if (!six && !small) {
         for (int64_t k = p->B == 32 ? 1 : 2; (p->B == 32 ? k < 2 * (int64_t)nq : k <= 2 * ((int64_t)nq - 1)) && g_def > 256; k *= 2)
             g_def /= 2;
         // (5 to 7 queries over codes of 8 and 16 bytes, once there are two tiles each: 5 queries m = 16, 6 M 68.7 us with 256,
@@ -634,9 +639,10 @@ static bool make_scan_plan(int variant, int64_t n, int m, int nq, int R, ScanPla
     // (4-bit codes of 8 bytes and more: batches go to the matrix-core kernel once that pays, and to the
     // per-query kernels below that; 4-byte codes and 8-bit components have the byte-lane kernels as well)
     const bool wants = !six && p->seed_wgs > 0 && knob_or(knobs().tiled, 1) != 0;
-    p->tiled_min = (!p->wide && p->B >= 8) ? 2 : TILED_MIN_Q;
-    p->tiled = wants && nq >= p->tiled_min && make_tiled_plan(n, m, nq, !p->wide, &p->t) &&
-               (p->wide || p->B < 8 || p->t.mfma || tiled_bytes_pay(p->B, n, nq));
+    const bool per_query = !small && !p->wide && p->B >= 8;
+    p->tiled_min = per_query ? 2 : TILED_MIN_Q;
+    p->tiled = wants && nq >= p->tiled_min && make_tiled_plan(n, m, nq, !p->wide, small, &p->t) &&
+               (!per_query || p->t.mfma || tiled_bytes_pay(p->B, n, nq));
     if (p->tiled && p->G > 256) p->G = 256;  // the single-query kernel only redoes rare queries
     const ScanLayout l = scan_layout(p->G, R);
     p->counts_off = l.counts_off;
@@ -764,15 +770,17 @@ int scan_topk_u8(int variant, const uint8_t *codes, int64_t n, int m, const uint
                  int nbins, uint32_t *out_idx, uint8_t *out_dist, void *workspace,
                  size_t workspace_bytes, hipStream_t st)
 {
-    ScanPlan p;
-    if (!make_scan_plan(variant, n, m, nq, R, &p))
+    ScanPlan p, small;
+    if (!make_scan_plan(variant, n, m, nq, R, false, &p) ||
+        !make_scan_plan(variant, n, m, nq, R, true, &small))
         return fail(QADC_EINVAL, "qadc_scan_topk: unsupported n=%lld m=%d nq=%d R=%d",
                     (long long)n, m, nq, R);
     if (nbins < 1 || nbins > 255) return fail(QADC_EINVAL, "qadc_scan_topk: nbins=%d not in 1..255", nbins);
     if (((uintptr_t)codes & 15) != 0) return fail(QADC_EINVAL, "qadc_scan_topk: codes must be 16-byte aligned");
     if (((uintptr_t)qluts & 3) != 0) return fail(QADC_EINVAL, "qadc_scan_topk: luts must be 4-byte aligned");
-    if (workspace_bytes < p.ws_bytes || !workspace)
-        return fail(QADC_ENOMEM, "qadc_scan_topk: workspace %zu < %zu bytes", workspace_bytes, p.ws_bytes);
+    if (workspace_bytes < small.ws_bytes || !workspace)
+        return fail(QADC_ENOMEM, "qadc_scan_topk: workspace %zu < %zu bytes", workspace_bytes, small.ws_bytes);
+    if (workspace_bytes < p.ws_bytes) p = small;
     if (((uintptr_t)workspace & 255) != 0)
         return fail(QADC_EINVAL, "qadc_scan_topk: workspace must be 256-byte aligned");
     char *ws = (char *)workspace;
@@ -801,11 +809,20 @@ static size_t search_extra_bytes(int m, int qbatch)
     return align_up((size_t)qbatch * m * 16 * sizeof(float), 256) + align_up((size_t)qbatch * m * 16, 256);
 }
 
+static size_t search_bytes(const ScanPlan &p, int m) { return p.ws_bytes + search_extra_bytes(m, p.qbatch); }
+
+// What a call takes at least (0: unsupported sizes), and what qadc_workspace_bytes asks for.
+size_t search_workspace_small(int64_t n, int m, int nq, int R)
+{
+    ScanPlan p;
+    return make_scan_plan(QADC_U8_4BIT, n, m, nq, R, true, &p) ? search_bytes(p, m) : 0;
+}
+
 size_t search_workspace(int64_t n, int m, int nq, int R)
 {
     ScanPlan p;
-    if (!make_scan_plan(QADC_U8_4BIT, n, m, nq, R, &p)) return 0;
-    return p.ws_bytes + search_extra_bytes(m, p.qbatch);
+    if (!make_scan_plan(QADC_U8_4BIT, n, m, nq, R, false, &p)) return 0;
+    return std::max(search_bytes(p, m), search_workspace_small(n, m, nq, R));
 }
 
 int search_u8(const float *codebooks, int d, int m, const float *queries, int nq, const uint8_t *codes,
@@ -813,11 +830,12 @@ int search_u8(const float *codebooks, int d, int m, const float *queries, int nq
               uint8_t *out_dist, uint8_t *qluts_out, void *workspace, size_t workspace_bytes,
               hipStream_t st)
 {
-    ScanPlan p;
+    ScanPlan p, small;
     if (!codebooks || !queries || !out_idx || !out_dist || (!codes && n > 0))
         return fail(QADC_EINVAL, "qadc_search: null pointer");
     if (nq == 0) return QADC_OK;
-    if (!make_scan_plan(QADC_U8_4BIT, n, m, nq, R, &p) || d < m || d % m != 0 || d > PREP_MAX_D)
+    if (!make_scan_plan(QADC_U8_4BIT, n, m, nq, R, false, &p) ||
+        !make_scan_plan(QADC_U8_4BIT, n, m, nq, R, true, &small) || d < m || d % m != 0 || d > PREP_MAX_D)
         return fail(QADC_EINVAL, "qadc_search: unsupported n=%lld d=%d m=%d nq=%d R=%d", (long long)n, d, m,
                     nq, R);
     if (nbins < 1 || nbins > 255 || init < 1 || init > QADC_MAX_INIT || n < 1)
@@ -825,9 +843,9 @@ int search_u8(const float *codebooks, int d, int m, const float *queries, int nq
     if (qmin_mode != QADC_QMIN_PER_TABLE && qmin_mode != QADC_QMIN_GLOBAL)
         return fail(QADC_EINVAL, "qadc_search: qmin_mode=%d", qmin_mode);
     if (((uintptr_t)codes & 15) != 0) return fail(QADC_EINVAL, "qadc_search: codes must be 16-byte aligned");
-    const size_t need = p.ws_bytes + search_extra_bytes(m, p.qbatch);
-    if (!workspace || workspace_bytes < need)
-        return fail(QADC_ENOMEM, "qadc_search: workspace %zu < %zu bytes", workspace_bytes, need);
+    if (!workspace || workspace_bytes < search_bytes(small, m))
+        return fail(QADC_ENOMEM, "qadc_search: workspace %zu < %zu bytes", workspace_bytes, search_bytes(small, m));
+    if (workspace_bytes < search_bytes(p, m)) p = small;
     if (((uintptr_t)workspace & 255) != 0)
         return fail(QADC_EINVAL, "qadc_search: workspace must be 256-byte aligned");
     char *ws = (char *)workspace;
@@ -879,9 +897,10 @@ int search_u8(const float *codebooks, int d, int m, const float *queries, int nq
 
 size_t scan_topk_u8_workspace(int variant, int64_t n, int m, int nq, int R)
 {
-    ScanPlan p;
-    if (!make_scan_plan(variant, n, m, nq, R, &p)) return 0;
-    return p.ws_bytes;
+    ScanPlan p, small;
+    if (!make_scan_plan(variant, n, m, nq, R, false, &p) || !make_scan_plan(variant, n, m, nq, R, true, &small))
+        return 0;
+    return std::max(p.ws_bytes, small.ws_bytes);
 }
 
 int workspace_init(void *workspace, size_t bytes, hipStream_t st)

@@ -13,7 +13,8 @@ constexpr int TILED_LCAP = 64;         // keys a workgroup can report per query
 constexpr int TILED_MAX_CHUNKS = 1024; // database chunks per query
 constexpr int TILED_MFMA_MAX_CHUNKS = 4096;  // the same for small batches on the matrix-core kernel
 constexpr int TILED_MIN_Q = 8;         // smallest batch worth tiling
-constexpr int TILED_MFMA_MIN_Q_B4 = 32;  // smallest batch of 4-byte codes for the matrix-core kernel (wider codes: mfma_pays)
+constexpr int TILED_MFMA_MIN_Q = 16;   // smallest batch for the matrix-core kernel in a small workspace (else: mfma_pays)
+constexpr int TILED_MFMA_MIN_Q_B4 = 32;  // ... of 4-byte codes, in any workspace
 constexpr int TILED_MFMA_MIN_Q2 = 64;  // smallest batch for its 64-queries-per-wavefront form
 constexpr int TILED_MFMA_MIN_Q4 = 128; // ... for 128 queries per wavefront (codes of up to 8 bytes)
 
@@ -28,7 +29,8 @@ struct TiledPlan {
 bool tiled_bytes_pay(int B, int64_t n, int nq);
 
 // codes4: 4-bit codes with the queries' 16-entry tables at hand (what the matrix-core kernel reads)
-bool make_tiled_plan(int64_t n, int m, int nq, bool codes4, TiledPlan *t);
+// small: the plan of the scan driver's smaller workspace
+bool make_tiled_plan(int64_t n, int m, int nq, bool codes4, bool small, TiledPlan *t);
 
 // tau kernel + tiled scan kernel for `nq` queries whose control blocks (histogram, pair
 // tables) were filled by the seed/prepare kernel.  qluts16: the queries' 16-entry quantized

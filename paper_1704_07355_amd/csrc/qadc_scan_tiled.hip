@@ -359,9 +359,8 @@ __global__ __launch_bounds__(tiled_nt(B)) void scan_u8_tiled16_kernel(
     }
 }
 
-// smallest batches for the matrix-core kernel (from 16 queries with 8 code bytes or more, from 32
-// with 4: measured against the vector-ALU kernels over 10 M codes) and for its forms with 64 and 128
-// queries per wavefront
+// smallest (sub-)batches that the matrix-core kernel takes, and its forms with 64 and 128 queries per wavefront.  Which
+// calls are worth it: mfma_pays; 4-byte codes from 32 queries (measured against the byte-lane kernels over 10 M codes).
 static int mfma_min_q(int B) { return std::max(1, knob_or(knobs().mfma_min_q, B >= 8 ? 2 : TILED_MFMA_MIN_Q_B4)); }
 // 8 to 15 queries over many 8-byte codes: the byte-lane kernel (20 M codes, 12 queries: 150 against 156 us), and the 8
 // queries of one of its workgroups over many 16-byte codes (20 M 174 against 212 us, 10 M 117 / 127, 5 M 91 / 87)
@@ -387,14 +386,16 @@ static bool mfma_four(int B, int nq)
     return B <= 8 && nq >= min_q4 && ((nq & 127) == 0 || (nq & 127) > 64);
 }
 
-bool make_tiled_plan(int64_t n, int m, int nq, bool codes4, TiledPlan *t)
+bool make_tiled_plan(int64_t n, int m, int nq, bool codes4, bool small, TiledPlan *t)
 {
     t->B = m / 2;
     const int cpt = (t->B <= 16) ? SCAN_VEC * (16 / t->B) : 1;
     int tile = tiled_nt(t->B) * cpt;
     // 4-bit codes and a batch that fills a good part of a wavefront's 32 or 64 queries: the
     // matrix-core kernel scans it
-    t->mfma = codes4 && mfma_pays(t->B, n, nq) && knob_or(knobs().tiled_mfma, 1) != 0;
+    t->mfma = codes4 && (small ? nq >= knob_or(knobs().mfma_min_q, t->B >= 8 ? TILED_MFMA_MIN_Q : TILED_MFMA_MIN_Q_B4)
+                               : mfma_pays(t->B, n, nq)) &&
+              knob_or(knobs().tiled_mfma, 1) != 0;
     // chunks: at most TILED_MAX_CHUNKS per query, a multiple of the tile, below 2^24 codes (index
     // bits of a key); as long as possible (a workgroup builds its tables once per chunk) while
     // groups x chunks still make about four workgroups per compute unit: 64 tiles with many query
@@ -417,10 +418,10 @@ bool make_tiled_plan(int64_t n, int m, int nq, bool codes4, TiledPlan *t)
         // query and chunk, or queries overflow and are redone one by one
         want = std::max<int64_t>(512, ceil_div(std::max(64, knob_or(knobs().mfma_waves, 4096)), ceil_div(nq, qw)));
         want = std::min<int64_t>(max_chunks, want);
-        // (shorter chunks, of any multiple of 16 codes, where a wavefront takes at most 64 queries: half a million
-        // codes are then enough wavefronts; many 4-byte codes keep whole tiles, 91 queries with R = 1000 over 6 M spread
-        // over too many lists otherwise, 1.66 against 1.21 ms, but 40 queries over 1 M gain, 0.13 against 0.24 ms)
-        if (t->B >= 8 || n < (4 << 20)) tile = 256;
+        // (shorter chunks, of any multiple of 256 codes: half a million codes are then enough wavefronts; many 4-byte codes
+        // keep whole tiles, 91 queries with R = 1000 over 6 M spread over too many lists otherwise, 1.66 against 1.21 ms,
+        // but 40 queries over 1 M gain, 0.13 against 0.24 ms)
+        if (!small && (t->B >= 8 || n < (4 << 20))) tile = 256;
         lo = 2;
         hi = 1ll << 40;
     }

@@ -11,7 +11,7 @@ namespace qadc {
 
 int search_u8(const float *, int, int, const float *, int, const uint8_t *, int64_t, int, int, int, int,
               uint32_t *, uint8_t *, uint8_t *, void *, size_t, hipStream_t);
-size_t search_workspace(int64_t, int, int, int);
+size_t search_workspace_small(int64_t, int, int, int);
 
 constexpr size_t STATIC_SCRATCH_BYTES = 32ull << 20;
 static_assert(STATIC_SCRATCH_BYTES == QADC_STATIC_SCRATCH_BYTES, "header and library disagree");
@@ -48,14 +48,15 @@ int search_static(const float *codebooks, int d, int m, const float *queries, in
     knobs_refresh();
     if (nq < 0) return fail(QADC_EINVAL, "qadc_search_static: nq=%d", nq);
     if (nq == 0) return QADC_OK;
-    // the largest number of queries per launch sequence whose scratch fits the array
+    // the largest number of queries per launch sequence whose scratch fits the array (the small plan of a search; the
+    // search takes its best plan where the array holds that too)
     int nb = nq;
-    size_t need = search_workspace(n, m, nb, R);
+    size_t need = search_workspace_small(n, m, nb, R);
     if (need == 0)
         return fail(QADC_EINVAL, "qadc_search_static: unsupported n=%lld m=%d nq=%d R=%d", (long long)n, m, nq, R);
     while (need > STATIC_SCRATCH_BYTES && nb > 1) {
         nb = (nb + 1) / 2;
-        need = search_workspace(n, m, nb, R);
+        need = search_workspace_small(n, m, nb, R);
         if (need == 0)
             return fail(QADC_EINVAL, "qadc_search_static: unsupported n=%lld m=%d nq=%d R=%d", (long long)n, m, nb, R);
     }

@@ -44,3 +44,22 @@ def gpu_us(f, reps=20, rounds=3):
         torch.cuda.synchronize()
         best = min(best, a.elapsed_time(b) * 1e3 / reps)
     return best
+
+
+def smallest_workspace(Q, call):
+    """call(workspace) with the least bytes it takes, one byte less having been refused; that number and its result."""
+    import re
+    import torch
+    buf = lambda nbytes: Q.qadc_workspace_init(torch.empty((nbytes,), dtype=torch.uint8, device="cuda:0"))
+    try:
+        call(buf(256))
+        raise AssertionError("256 bytes were enough")
+    except Q.QadcError as e:
+        assert e.code == Q.QADC_ENOMEM
+        least = max(int(v) for v in re.findall(r"\b\d+\b", Q.qadc_last_error()))
+    try:
+        call(buf(least)[:least - 1])
+        raise AssertionError("a byte less was enough")
+    except Q.QadcError as e:
+        assert e.code == Q.QADC_ENOMEM
+    return least, call(buf(least))

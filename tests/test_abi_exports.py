@@ -103,3 +103,21 @@ def test_occupied_cell_entry_points_check_arguments_on_the_host():
     assert L.qadc_multi_index_slots(None, 4, None, 3, None, None) == Q.QADC_EINVAL
     assert L.qadc_multi_index_encode(None, 0, None, 8, 4, None, 0, None, None, 0, None, None) == Q.QADC_EINVAL  # K < 1
     assert L.qadc_multi_index_encode(None, 4, None, 7, 4, None, 0, None, None, 0, None, None) == Q.QADC_EINVAL  # odd d
+
+
+def test_workspaces_sized_for_a_batch_serve_its_smaller_batches():
+    """What a call asks for may follow its fastest plan, but a size given for 2 to 7 queries covers fewer queries, and
+    shorter databases, of the same kind; the sizes of the calls measured here are those callers have budgeted for."""
+    import paper_1704_07355_amd as Q
+    for call, ms in ((Q.QADC_WS_SCAN_TOPK, (8, 16, 32, 64)), (Q.QADC_WS_SEARCH, (8, 16, 32, 64)),
+                     (Q.QADC_WS_SCAN_U8_8BIT, (4, 8, 16, 32)), (Q.QADC_WS_SCAN_U8_6BIT, (8, 16, 32))):
+        for m in ms:
+            for R in (1, 100, 1000):
+                for n in (50_000, 390_000, 1_000_000, 10_000_000, 100_000_000):
+                    sizes = [Q.qadc_workspace_bytes(call, n, m, nq, R) for nq in range(1, 8)]
+                    assert sizes == sorted(sizes) and sizes[0] > 0, (call, m, R, n, sizes)
+                    for nq in (1, 3, 5, 7):
+                        less = Q.qadc_workspace_bytes(call, n // 3, m, nq, R)
+                        assert less <= Q.qadc_workspace_bytes(call, n, m, nq, R), (call, m, R, n, nq)
+    # at least what 2048 report regions per query take
+    assert Q.qadc_workspace_bytes(Q.QADC_WS_SCAN_TOPK, 10_000_000, 16, 5, 100) >= 5 * 2048 * 100 * 8

@@ -354,3 +354,24 @@ def test_pq_encode_where_float32_cannot_tell(Q, n, m, dsub, k):
     for out in (flat[1:].view(n, -1), flat[:-1].view(n, -1)):
         got = Q.qadc_pq_encode(to_gpu(cb), to_gpu(x), out=out)
         assert np.array_equal(got.cpu().numpy(), want)
+
+
+@pytest.mark.parametrize("n,K", [(100_003, 256), (300_000, 4096), (1_000_000, 5_998)])
+def test_group_with_the_smallest_workspace(Q, n, K):
+    """Fewer, longer parts where the workspace holds no more counters: the same grouping.  A workspace for K cells also
+    serves fewer cells."""
+    import torch
+    from gpu_common import smallest_workspace
+    cells = to_gpu(np.random.default_rng(n).integers(0, K, size=n).astype(np.int32))
+    want = Q.qadc_ivf_group(cells, K)
+    least, got = smallest_workspace(Q, lambda ws: Q.qadc_ivf_group(cells, K, workspace=ws))
+    assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1])
+    assert least <= Q.qadc_ivf_group_workspace_bytes(n, K)
+    fewer = cells % (K - 28)
+    ws = torch.empty((Q.qadc_ivf_group_workspace_bytes(n, K),), dtype=torch.uint8, device="cuda:0")
+    got, want = Q.qadc_ivf_group(fewer, K - 28, workspace=ws), Q.qadc_ivf_group(fewer, K - 28)
+    assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1])
+    if K < 5000:
+        want = Q.qadc_multi_index_group(cells, K)
+        _, got = smallest_workspace(Q, lambda ws: Q.qadc_multi_index_group(cells, K, workspace=ws))
+        assert all(torch.equal(a, b) for a, b in zip(got, want))

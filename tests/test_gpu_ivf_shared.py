@@ -4,7 +4,7 @@ once for all the queries that probe it) against the CPU oracle and against the p
 import numpy as np
 import pytest
 
-from gpu_common import to_gpu, idx_np, gpu_us
+from gpu_common import to_gpu, idx_np, gpu_us, smallest_workspace
 from test_gpu_ivf import build_ivf, gpu_index
 
 pytestmark = pytest.mark.gpu
@@ -274,3 +274,15 @@ def test_route_of_a_skewed_index(Q, monkeypatch):
         forced.append(gpu_us(lambda: Q.qadc_ivf_search(gix, gq, 8, 100, 300, workspace=ws)))
     monkeypatch.delenv("QADC_IVF_SHARED")
     assert own < 1.5 * min(forced), (own, forced)
+
+
+@pytest.mark.parametrize("nq,nprobe,R", [(150, 24, 100), (400, 8, 100), (70, 64, 10), (30, 8, 100)])
+def test_search_with_the_smallest_workspace(Q, nq, nprobe, R):
+    """A workspace that does not hold the shared-list plan of a middle-sized batch: the same result, query by query."""
+    import torch
+    gix, coarse, rnd = skewed_index(Q, 400_000, 100, 16, 50_000, 9)
+    gq = (coarse[torch.arange(nq, device="cuda") % 100] + 18 * rnd(nq, 64)).contiguous()
+    want = Q.qadc_ivf_search(gix, gq, nprobe, R, 300)
+    least, got = smallest_workspace(Q, lambda ws: Q.qadc_ivf_search(gix, gq, nprobe, R, 300, workspace=ws))
+    assert least <= Q.qadc_ivf_workspace_bytes(gix, nq, nprobe, R)
+    assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1])

@@ -5,7 +5,7 @@ import os
 import numpy as np
 import pytest
 
-from gpu_common import gpu_us, config1, to_gpu, idx_np
+from gpu_common import gpu_us, smallest_workspace, config1, to_gpu, idx_np
 
 pytestmark = pytest.mark.gpu
 
@@ -885,3 +885,31 @@ def test_batches_that_fill_the_byte_lane_kernels(Q, monkeypatch, m, n, nq):
         us.append(gpu_us(f, reps=30))
     monkeypatch.delenv("QADC_TILED_MFMA")
     assert us[0] < 1.1 * us[1], us
+
+
+@pytest.mark.parametrize("m,n,nq,R", [(16, 2_000_003, 1, 100), (16, 2_000_003, 5, 100), (64, 700_001, 3, 37), (32, 900_017, 12, 100),
+                                      (8, 1_500_000, 7, 1000), (16, 3_000_000, 20, 100), (64, 1_000_003, 12, 100), (16, 5_000, 3, 10)])
+def test_smallest_workspace_gives_the_same_result(Q, m, n, nq, R):
+    """A call takes less than the size asked for, down to what its smaller plan needs, and a workspace of a batch takes
+    the batch's single queries."""
+    import torch
+    rng = np.random.default_rng(n + m)
+    cb = to_gpu(rng.uniform(0, 255, size=(m, 16, 2)).astype(np.float32))
+    codes = to_gpu(rng.integers(0, 256, size=(n, m // 2), dtype=np.uint8))
+    queries = to_gpu(rng.uniform(0, 255, size=(nq, 2 * m)).astype(np.float32))
+    want = Q.qadc_search(cb, queries, codes, R, 200)
+    least, got = smallest_workspace(Q, lambda ws: Q.qadc_search(cb, queries, codes, R, 200, workspace=ws))
+    assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1])
+    asked = Q.qadc_workspace_bytes(Q.QADC_WS_SEARCH, n, m, nq, R)
+    assert least <= asked
+    qluts = to_gpu(rng.integers(0, 510 // m + 2, size=(nq, m, 16)).astype(np.uint8))
+    want = Q.qadc_scan_topk(Q.QADC_U8_4BIT, codes, qluts, R)
+    _, got = smallest_workspace(Q, lambda ws: Q.qadc_scan_topk(Q.QADC_U8_4BIT, codes, qluts, R, workspace=ws))
+    assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1])
+    if nq <= 7:
+        ws = torch.empty((asked,), dtype=torch.uint8, device="cuda:0")
+        for k in range(1, nq + 1):
+            Q.qadc_workspace_init(ws)
+            q = queries[:k].contiguous()
+            got, want = Q.qadc_search(cb, q, codes, R, 200, workspace=ws), Q.qadc_search(cb, q, codes, R, 200)
+            assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1])

@@ -5,7 +5,7 @@ import ctypes
 import numpy as np
 import pytest
 
-from gpu_common import config1, to_gpu
+from gpu_common import config1, to_gpu, gpu_us
 
 pytestmark = pytest.mark.gpu
 
@@ -94,3 +94,32 @@ def test_static_scratch_calls_cut_into_unequal_sequences(n, m, nq, R):
     queries = to_gpu(rng.uniform(0, 255, size=(nq, 2 * m)).astype(np.float32))
     for _ in range(2):
         _call_both(Q, L, torch, cb, queries, codes, R, 200)
+
+
+@pytest.mark.parametrize("m,n,nq", [(16, 10_000_000, 16), (32, 3_000_000, 64)])
+def test_static_scratch_batches_are_not_cut_finer_than_they_were(m, n, nq):
+    """The static array holds a batch of 16 queries over 10 M codes (and 16 of 64 at a time over 3 M, m = 32), whatever
+    larger workspace a search would like better."""
+    import torch
+    import paper_1704_07355_amd as Q
+    L = Q.lib()
+    g = torch.Generator(device="cuda:0")
+    g.manual_seed(m)
+    cb = 30 * torch.randn((m, 16, 8), generator=g, device="cuda:0")
+    codes = torch.randint(0, 256, (n, m // 2), generator=g, device="cuda:0", dtype=torch.uint8)
+    queries = 30 * torch.randn((nq, 8 * m), generator=g, device="cuda:0")
+    _call_both(Q, L, torch, cb, queries, codes, 100, 200)
+    out = (torch.empty((nq, 100), dtype=torch.int32, device="cuda:0"), torch.empty((nq, 100), dtype=torch.uint8, device="cuda:0"))
+    vp = ctypes.c_void_p
+
+    def static():
+        assert L.qadc_search_static(vp(cb.data_ptr()), 8 * m, m, vp(queries.data_ptr()), nq, vp(codes.data_ptr()), n, 100, 200, 255,
+                                    0, vp(out[0].data_ptr()), vp(out[1].data_ptr()), None,
+                                    vp(torch.cuda.current_stream().cuda_stream)) == 0
+
+    ws = Q.qadc_workspace_init(torch.empty((Q.qadc_workspace_bytes(Q.QADC_WS_SEARCH, n, m, 16, 100),), dtype=torch.uint8,
+                                           device="cuda:0"))
+    q16 = queries[:16].contiguous()
+    one = gpu_us(lambda: Q.qadc_search(cb, q16, codes, 100, 200, workspace=ws), reps=30)
+    us = gpu_us(static, reps=30)
+    assert us < 1.3 * one * (nq // 16), (us, one)
