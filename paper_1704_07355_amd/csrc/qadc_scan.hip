@@ -567,8 +567,8 @@ struct ScanPlan {
 // small one takes is enough for any call: so a workspace of a given size serves the calls it always served (one sized
 // for a batch also serves the single queries of it, up to 7 queries), whatever the best plan has come to use, and the
 // static scratch array takes as many queries at a time.  It has 2048 report regions per query, or 256 and the lists
-// of longer chunks from 8 queries.
-static bool make_scan_plan(int variant, int64_t n, int m, int nq, int R, bool small, ScanPlan *p)
+// of longer chunks from 8 queries.  tables16: the tables are where the matrix-core kernel can read them.
+static bool make_scan_plan(int variant, int64_t n, int m, int nq, int R, bool small, bool tables16, ScanPlan *p)
 {
     if (variant != QADC_U8_4BIT && variant != QADC_U8_8BIT && variant != QADC_U8_6BIT) return false;
     p->wide = variant == QADC_U8_8BIT;
@@ -637,11 +637,13 @@ static bool make_scan_plan(int variant, int64_t n, int m, int nq, int R, bool sm
         p->flush_need = (unsigned)fl;
     }
     // (4-bit codes of 8 bytes and more: batches go to the matrix-core kernel once that pays, and to the
-    // per-query kernels below that; 4-byte codes and 8-bit components have the byte-lane kernels as well)
+    // per-query kernels below that; 4-byte codes, 8-bit components and tables that the matrix-core kernel cannot read
+    // have the byte-lane kernels)
     const bool wants = !six && p->seed_wgs > 0 && knob_or(knobs().tiled, 1) != 0;
-    const bool per_query = !small && !p->wide && p->B >= 8;
+    const bool mfma = !p->wide && (small || tables16) && mfma_allowed(p->B, nq);
+    const bool per_query = !small && mfma && p->B >= 8;
     p->tiled_min = per_query ? 2 : TILED_MIN_Q;
-    p->tiled = wants && nq >= p->tiled_min && make_tiled_plan(n, m, nq, !p->wide, small, &p->t) &&
+    p->tiled = wants && nq >= p->tiled_min && make_tiled_plan(n, m, nq, mfma, small, &p->t) &&
                (!per_query || p->t.mfma || tiled_bytes_pay(p->B, n, nq));
     if (p->tiled && p->G > 256) p->G = 256;  // the single-query kernel only redoes rare queries
     const ScanLayout l = scan_layout(p->G, R);
@@ -771,8 +773,8 @@ int scan_topk_u8(int variant, const uint8_t *codes, int64_t n, int m, const uint
                  size_t workspace_bytes, hipStream_t st)
 {
     ScanPlan p, small;
-    if (!make_scan_plan(variant, n, m, nq, R, false, &p) ||
-        !make_scan_plan(variant, n, m, nq, R, true, &small))
+    if (!make_scan_plan(variant, n, m, nq, R, false, ((uintptr_t)qluts & 15) == 0, &p) ||
+        !make_scan_plan(variant, n, m, nq, R, true, true, &small))
         return fail(QADC_EINVAL, "qadc_scan_topk: unsupported n=%lld m=%d nq=%d R=%d",
                     (long long)n, m, nq, R);
     if (nbins < 1 || nbins > 255) return fail(QADC_EINVAL, "qadc_scan_topk: nbins=%d not in 1..255", nbins);
@@ -780,7 +782,9 @@ int scan_topk_u8(int variant, const uint8_t *codes, int64_t n, int m, const uint
     if (((uintptr_t)qluts & 3) != 0) return fail(QADC_EINVAL, "qadc_scan_topk: luts must be 4-byte aligned");
     if (workspace_bytes < small.ws_bytes || !workspace)
         return fail(QADC_ENOMEM, "qadc_scan_topk: workspace %zu < %zu bytes", workspace_bytes, small.ws_bytes);
-    if (workspace_bytes < p.ws_bytes) p = small;
+    // (tables that the matrix-core kernel cannot read: the byte-lane kernels over the small plan's chunks, 70 queries over
+    // 300 k codes m = 16 57 us, over chunks of their own 66, over the best plan's 107)
+    if (workspace_bytes < p.ws_bytes || (((uintptr_t)qluts & 15) != 0 && nq >= TILED_MIN_Q)) p = small;
     if (((uintptr_t)workspace & 255) != 0)
         return fail(QADC_EINVAL, "qadc_scan_topk: workspace must be 256-byte aligned");
     char *ws = (char *)workspace;
@@ -815,13 +819,13 @@ static size_t search_bytes(const ScanPlan &p, int m) { return p.ws_bytes + searc
 size_t search_workspace_small(int64_t n, int m, int nq, int R)
 {
     ScanPlan p;
-    return make_scan_plan(QADC_U8_4BIT, n, m, nq, R, true, &p) ? search_bytes(p, m) : 0;
+    return make_scan_plan(QADC_U8_4BIT, n, m, nq, R, true, true, &p) ? search_bytes(p, m) : 0;
 }
 
 size_t search_workspace(int64_t n, int m, int nq, int R)
 {
     ScanPlan p;
-    if (!make_scan_plan(QADC_U8_4BIT, n, m, nq, R, false, &p)) return 0;
+    if (!make_scan_plan(QADC_U8_4BIT, n, m, nq, R, false, true, &p)) return 0;
     return std::max(search_bytes(p, m), search_workspace_small(n, m, nq, R));
 }
 
@@ -834,8 +838,8 @@ int search_u8(const float *codebooks, int d, int m, const float *queries, int nq
     if (!codebooks || !queries || !out_idx || !out_dist || (!codes && n > 0))
         return fail(QADC_EINVAL, "qadc_search: null pointer");
     if (nq == 0) return QADC_OK;
-    if (!make_scan_plan(QADC_U8_4BIT, n, m, nq, R, false, &p) ||
-        !make_scan_plan(QADC_U8_4BIT, n, m, nq, R, true, &small) || d < m || d % m != 0 || d > PREP_MAX_D)
+    if (!make_scan_plan(QADC_U8_4BIT, n, m, nq, R, false, true, &p) ||
+        !make_scan_plan(QADC_U8_4BIT, n, m, nq, R, true, true, &small) || d < m || d % m != 0 || d > PREP_MAX_D)
         return fail(QADC_EINVAL, "qadc_search: unsupported n=%lld d=%d m=%d nq=%d R=%d", (long long)n, d, m,
                     nq, R);
     if (nbins < 1 || nbins > 255 || init < 1 || init > QADC_MAX_INIT || n < 1)
@@ -898,7 +902,7 @@ int search_u8(const float *codebooks, int d, int m, const float *queries, int nq
 size_t scan_topk_u8_workspace(int variant, int64_t n, int m, int nq, int R)
 {
     ScanPlan p, small;
-    if (!make_scan_plan(variant, n, m, nq, R, false, &p) || !make_scan_plan(variant, n, m, nq, R, true, &small))
+    if (!make_scan_plan(variant, n, m, nq, R, false, true, &p) || !make_scan_plan(variant, n, m, nq, R, true, true, &small))
         return 0;
     return std::max(p.ws_bytes, small.ws_bytes);
 }

@@ -28,7 +28,10 @@ struct TiledPlan {
 // 4-bit codes of B bytes that the byte-lane kernels scan faster than the matrix-core kernel
 bool tiled_bytes_pay(int B, int64_t n, int nq);
 
-// codes4: 4-bit codes with the queries' 16-entry tables at hand (what the matrix-core kernel reads)
+// May a batch of 4-bit codes of B bytes go to the matrix-core kernel?  Not where a tuning variable says otherwise.
+bool mfma_allowed(int B, int nq);
+
+// codes4: 4-bit codes with the queries' 16-entry tables at hand (what the matrix-core kernel reads), and mfma_allowed
 // small: the plan of the scan driver's smaller workspace
 bool make_tiled_plan(int64_t n, int m, int nq, bool codes4, bool small, TiledPlan *t);
 

@@ -378,6 +378,10 @@ static bool mfma_pays(int B, int64_t n, int nq)
     if (tiled_bytes_pay(B, n, nq)) return false;
     return nq >= 2 && (nq - 4) * bytes >= 90e6;
 }
+bool mfma_allowed(int B, int nq)
+{
+    return knob_or(knobs().tiled_mfma, 1) != 0 && (knobs().mfma_min_q < 0 || nq >= mfma_min_q(B));
+}
 static int mfma_min_q2() { return std::max(1, knob_or(knobs().mfma_min_q2, TILED_MFMA_MIN_Q2)); }
 // 128 queries per wavefront (codes of up to 8 bytes): when the last set of 128 is more than half full
 static bool mfma_four(int B, int nq)
@@ -394,8 +398,7 @@ bool make_tiled_plan(int64_t n, int m, int nq, bool codes4, bool small, TiledPla
     // 4-bit codes and a batch that fills a good part of a wavefront's 32 or 64 queries: the
     // matrix-core kernel scans it
     t->mfma = codes4 && (small ? nq >= knob_or(knobs().mfma_min_q, t->B >= 8 ? TILED_MFMA_MIN_Q : TILED_MFMA_MIN_Q_B4)
-                               : mfma_pays(t->B, n, nq)) &&
-              knob_or(knobs().tiled_mfma, 1) != 0;
+                               : mfma_pays(t->B, n, nq));
     // chunks: at most TILED_MAX_CHUNKS per query, a multiple of the tile, below 2^24 codes (index
     // bits of a key); as long as possible (a workgroup builds its tables once per chunk) while
     // groups x chunks still make about four workgroups per compute unit: 64 tiles with many query

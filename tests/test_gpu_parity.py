@@ -913,3 +913,45 @@ def test_smallest_workspace_gives_the_same_result(Q, m, n, nq, R):
             q = queries[:k].contiguous()
             got, want = Q.qadc_search(cb, q, codes, R, 200, workspace=ws), Q.qadc_search(cb, q, codes, R, 200)
             assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1])
+
+
+@pytest.mark.parametrize("m,n,nq,shift,knobs", [
+    (16, 1_000_003, 130, 0, {"QADC_TILED_MFMA": "0"}), (64, 400_003, 40, 0, {"QADC_TILED_MFMA": "0"}),
+    (32, 700_003, 12, 0, {"QADC_MFMA_MIN_Q": "16"}), (32, 700_003, 12, 4, {}), (16, 1_000_003, 70, 8, {})])
+def test_byte_lane_kernels_take_what_the_matrix_cores_may_not(Q, monkeypatch, m, n, nq, shift, knobs):
+    """Batches from 8 queries that a tuning variable or the tables' alignment keeps from the matrix-core kernel run on the
+    query-tiled byte-lane kernels (three launches: both widths of their sums and the queries redone), as they did."""
+    from oracle import cref
+    rng = np.random.default_rng(n + nq)
+    codes = rng.integers(0, 256, size=(n, m // 2), dtype=np.uint8)
+    qluts = rng.integers(0, 510 // m + 2, size=(nq, m, 16)).astype(np.uint8)
+    wi, wd = cref.scan_topk_u8(codes, qluts, 100, 255)
+    g = to_gpu(np.concatenate([np.zeros(shift, np.uint8), qluts.ravel()]))[shift:].view(nq, m, 16)
+    assert g.data_ptr() % 16 == shift
+    for k, v in knobs.items():
+        monkeypatch.setenv(k, v)
+    Q.qadc_profile_enable(True)
+    idx, dist = Q.qadc_scan_topk(Q.QADC_U8_4BIT, to_gpu(codes), g, 100)
+    _, launches = Q.qadc_profile_read(Q.QADC_PROF_SCAN)
+    Q.qadc_profile_enable(False)
+    assert launches >= 3, launches
+    assert np.array_equal(idx_np(idx), wi) and np.array_equal(dist.cpu().numpy(), wd)
+
+
+@pytest.mark.parametrize("m,n,nq", [(16, 300_000, 70), (32, 2_900_000, 12), (64, 2_900_000, 5)])
+def test_misaligned_tables_are_not_scanned_in_short_chunks(Q, monkeypatch, m, n, nq):
+    """The chunks of a batch whose tables the matrix-core kernel cannot read: not slower by a third than the same batch,
+    aligned, on the kernels it is left to."""
+    import torch
+    g = torch.Generator(device="cuda:0")
+    g.manual_seed(m)
+    codes = torch.randint(0, 256, (n, m // 2), generator=g, device="cuda:0", dtype=torch.uint8)
+    buf = torch.randint(0, 512 // m, (nq * m * 16 + 4,), generator=g, device="cuda:0", dtype=torch.uint8)
+    us = []
+    for tables, mfma in ((buf[4:].view(nq, m, 16), "1"), (buf[4:].clone().view(nq, m, 16), "0")):
+        monkeypatch.setenv("QADC_TILED_MFMA", mfma)
+        ws = Q.qadc_workspace_init(torch.empty((Q.qadc_workspace_bytes(Q.QADC_WS_SCAN_TOPK, n, m, nq, 100),),
+                                               dtype=torch.uint8, device="cuda:0"))
+        us.append(gpu_us(lambda: Q.qadc_scan_topk(Q.QADC_U8_4BIT, codes, tables, 100, workspace=ws), reps=50))
+    monkeypatch.delenv("QADC_TILED_MFMA")
+    assert us[0] < 1.3 * us[1], us
