@@ -30,7 +30,7 @@ __device__ inline const float *centroid_part(const CellCentroids &cc, int c, int
 // are uniform over the wavefront (qadc_nearest.h), nothing goes through LDS, and the wavefronts of a row block
 // are neighbours, so the row's lines are shared in the caches.  Before, a thread per output byte computed the
 // float64 distances from a codebook in LDS, where the lanes of a wavefront met on the same banks: 2 M vectors
-// of 128 dimensions, m = 16: 1029 us; residuals of 1 M vectors, m = 32: 865 us; now 270 and 211 us
+// of 128 dimensions, m = 16: 1029 us; residuals of 1 M vectors, m = 32: 865 us; now 277 and 208 us
 // (reading the vectors at 5 TB/s takes 200 and 200 us).
 // With `coarse`, row r of the output encodes the float32 residual of vector ids[r].
 template <int KSUB, int DS>
@@ -127,24 +127,29 @@ static int encode_launch(const char *name, const float *codebooks, int d, int m,
     const int64_t blocks = ceil_div(ceil_div(n, WAVE) * groups, 256 / WAVE);
     if (ceil_div(n * (ksub == 16 ? m / 2 : ksub == 64 ? m / 4 : m), 256) > 0x7fffffffll || blocks > 0x7fffffffll)
         return fail(QADC_EINVAL, "%s: n too large for one call", name);
-    // sub-vectors of the usual dimensions stay in registers
+    // Sub-vectors of the usual dimensions stay in registers; with 16 centroids, whose walk is short, all up to 20 do (500 k
+    // vectors of 16 x 5 components 46 us; the general form, which waits for its scalar loads, took 221).
 #define QADC_ENC(K_, D_)                                                                                    \
-    hipLaunchKernelGGL((pq_encode_kernel<K_, D_>), dim3((unsigned)blocks), dim3(256), 0, st, codebooks, d, m, x, \
-                       n, codes, cc, cells, ids, n_x)
-#define QADC_ENC_DS(K_)                          \
-    switch (d / m) {                             \
-    case 2: QADC_ENC(K_, 2); break;              \
-    case 3: QADC_ENC(K_, 3); break;              \
-    case 4: QADC_ENC(K_, 4); break;              \
-    case 6: QADC_ENC(K_, 6); break;              \
-    case 8: QADC_ENC(K_, 8); break;              \
-    case 12: QADC_ENC(K_, 12); break;            \
-    case 16: QADC_ENC(K_, 16); break;            \
-    default: QADC_ENC(K_, 0); break;             \
+    case D_:                                                                                                \
+        hipLaunchKernelGGL((pq_encode_kernel<K_, D_>), dim3((unsigned)blocks), dim3(256), 0, st, codebooks, d, m, x, \
+                           n, codes, cc, cells, ids, n_x);                                                  \
+        break;
+#define QADC_ENC_DS(K_, ...)                                                                                \
+    switch (d / m) {                                                                                        \
+    QADC_ENC(K_, 1) QADC_ENC(K_, 2) QADC_ENC(K_, 3) QADC_ENC(K_, 4) QADC_ENC(K_, 6) QADC_ENC(K_, 8) QADC_ENC(K_, 12) QADC_ENC(K_, 16) \
+    __VA_ARGS__                                                                                             \
+    default:                                                                                                \
+        hipLaunchKernelGGL((pq_encode_kernel<K_, 0>), dim3((unsigned)blocks), dim3(256), 0, st, codebooks, d, m, x, \
+                           n, codes, cc, cells, ids, n_x);                                                  \
     }
-    if (ksub == 16) { QADC_ENC_DS(16) }
-    else if (ksub == 64) { QADC_ENC_DS(64) }
-    else { QADC_ENC_DS(256) }
+    if (ksub == 16) {
+        QADC_ENC_DS(16, QADC_ENC(16, 5) QADC_ENC(16, 7) QADC_ENC(16, 9) QADC_ENC(16, 10) QADC_ENC(16, 11) QADC_ENC(16, 13)
+                    QADC_ENC(16, 14) QADC_ENC(16, 15) QADC_ENC(16, 17) QADC_ENC(16, 18) QADC_ENC(16, 19) QADC_ENC(16, 20))
+    } else if (ksub == 64) {
+        QADC_ENC_DS(64)
+    } else {
+        QADC_ENC_DS(256)
+    }
 #undef QADC_ENC_DS
 #undef QADC_ENC
     QADC_HIP_TRY(hipGetLastError());

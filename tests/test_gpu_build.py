@@ -375,3 +375,46 @@ def test_group_with_the_smallest_workspace(Q, n, K):
         want = Q.qadc_multi_index_group(cells, K)
         _, got = smallest_workspace(Q, lambda ws: Q.qadc_multi_index_group(cells, K, workspace=ws))
         assert all(torch.equal(a, b) for a, b in zip(got, want))
+
+
+# every compiled length of a sub-vector, and the general form's blocks of 8, 4, 2 and 1 components with and without rests
+@pytest.mark.parametrize("dsub", list(range(1, 22)) + [22, 23, 24, 27, 28, 31, 32, 33])
+@pytest.mark.parametrize("k", [16, 64, 256])
+def test_pq_encode_lengths_of_sub_vectors(Q, dsub, k):
+    test_pq_encode_where_float32_cannot_tell(Q, 330, 4, dsub, k)
+
+
+@pytest.mark.parametrize("dsub,m", [(8, 8), (11, 6), (21, 4), (23, 2)])
+def test_residual_codes_of_ties(Q, dsub, m):
+    """Residuals that are zero, or as far from two centroids, in whole wavefronts: the float64 walk on differences."""
+    rng = np.random.default_rng(dsub)
+    d, n, K = dsub * m, 1000, 7
+    coarse = rng.integers(0, 9, size=(K, d)).astype(np.float32)
+    cb = rng.integers(-2, 3, size=(m, 16, dsub)).astype(np.float32)
+    cb[0, 3] = cb[0, 9]
+    cells = rng.integers(0, K, size=n).astype(np.int32)
+    x = coarse[cells] + rng.integers(-2, 3, size=(n, d)).astype(np.float32)
+    x[:200] = coarse[cells[:200]]
+    ids = rng.permutation(n).astype(np.int32)
+    got = Q.qadc_ivf_encode(to_gpu(coarse), to_gpu(cb), to_gpu(x), to_gpu(cells), to_gpu(ids))
+    want = _pack(_codes_by_definition((x - coarse[cells])[ids], cb), 16)
+    assert np.array_equal(got.cpu().numpy(), want)
+
+
+@pytest.mark.parametrize("k,m,dsub", [(16, 16, 5), (16, 16, 8), (16, 8, 24), (64, 8, 8), (256, 8, 8), (256, 8, 10)])
+def test_pq_encode_of_ties_is_not_much_slower(Q, k, m, dsub):
+    """Components that are zero everywhere (padded vectors), repeated centroids: every sub-vector needs float64.  That costs
+    a second walk over the centroids, not fifty."""
+    import torch
+    from gpu_common import gpu_us
+    g = torch.Generator(device="cuda:0")
+    g.manual_seed(k)
+    x = torch.randn((200_000, m * dsub), generator=g, device="cuda:0")
+    cb = torch.randn((m, k, dsub), generator=g, device="cuda:0")
+    usual = gpu_us(lambda: Q.qadc_pq_encode(cb, x), reps=5)
+    twice = cb.clone()
+    twice[:, k // 2:] = cb[:, :k // 2]
+    assert gpu_us(lambda: Q.qadc_pq_encode(twice, x), reps=5) < 8 * usual
+    x[:] = 0
+    cb[:] = 0
+    assert gpu_us(lambda: Q.qadc_pq_encode(cb, x), reps=5) < 8 * usual
