@@ -136,7 +136,7 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 
 constexpr int AF_MAX_D = 256;
 
-// hi + lo = v to 2^-17 relative
+// hi + lo = v to 2^-18 relative
 __device__ __forceinline__ void split_bf16(const f32x8 v, bf16x8 *hi, bf16x8 *lo)
 {
     *hi = __builtin_convertvector(v, bf16x8);
@@ -362,7 +362,8 @@ __global__ __launch_bounds__(NT, 2) void assign_filter_kernel(const float *__res
         // unless the vector has to be measured against all cells
         const int g1 = b1[nb] <= thr ? 2 * a1[nb] + half : -1, g2 = b2[nb] <= thr ? 2 * a2[nb] + half : -1;
         const int o1 = __shfl_xor(g1, 32), o2 = __shfl_xor(g2, 32);
-        const bool all = !(sure && __shfl_xor((int)sure, 32));
+        const int other = __shfl_xor((int)sure, 32);  // (asked by all lanes: a lane that does not ask gives nothing)
+        const bool all = !(sure && other);
         if (half == 0) {
             cand[v][0] = all ? -2 : g1 >= 0 ? g1 : o1;
             cand[v][1] = g1 >= 0 ? g2 : o2;

@@ -418,3 +418,57 @@ def test_pq_encode_of_ties_is_not_much_slower(Q, k, m, dsub):
     x[:] = 0
     cb[:] = 0
     assert gpu_us(lambda: Q.qadc_pq_encode(cb, x), reps=5) < 8 * usual
+
+
+# (131,072 vectors and more in aligned rows of 32, 64, 96 or 128 components take the kernel of 512 threads)
+@pytest.mark.parametrize("d,K,n", [(32, 300, 131_500), (64, 70, 131_200), (96, 500, 131_072), (128, 333, 131_111),
+                                   (4, 900, 5_000), (16, 200, 3_000), (20, 128, 9_999), (100, 64, 1_300), (200, 97, 2_000),
+                                   (256, 60, 700), (128, 40, 1)])
+@pytest.mark.parametrize("kind", ["lattice", "near", "repeats", "stray", "nan"])
+def test_ivf_assign_of_crowded_cells(Q, d, K, n, kind):
+    """More close cells than a lane of the filter remembers, in one half of its lanes or both; a few centroids far away
+    or not finite, which may not loosen or spoil the choice among the others."""
+    import torch
+    rng = np.random.default_rng(d + K + n)
+    coarse = rng.integers(0, 3, size=(K, d)).astype(np.float32)
+    x = rng.integers(0, 3, size=(n, d)).astype(np.float32)
+    if kind == "near":
+        coarse += rng.normal(size=(K, d)).astype(np.float32) * np.float32(1e-4)
+    if kind == "repeats":
+        coarse = coarse[rng.integers(0, max(1, K // 5), size=K)]
+        x[::3] = coarse[rng.integers(0, K, size=len(x[::3]))]
+    if kind in ("stray", "nan"):
+        coarse[::9] *= np.float32(1e6)
+        coarse[K // 2] = np.float32(3e19)
+        coarse[K // 3] = np.inf
+    if kind == "nan":
+        coarse[1::3, 0] = np.nan
+        coarse[1::3, -1] = np.nan
+        x[n // 2] = np.float32(1e20)
+    g, got = to_gpu(coarse).double(), Q.qadc_ivf_assign(to_gpu(coarse), to_gpu(x))
+    want = torch.empty_like(got)
+    for s in range(0, n, 2048):
+        xx = to_gpu(x[s:s + 2048]).double()
+        dist = torch.zeros((len(xx), K), dtype=torch.float64, device="cuda:0")
+        for t in range(d):  # in increasing component order; a fused step rounds once, as close calls may need
+            dist = torch.addcmul(dist, xx[:, t, None] - g[None, :, t], xx[:, t, None] - g[None, :, t])
+        dist = torch.where(dist.isnan(), torch.inf, dist)
+        want[s:s + 2048] = (dist == dist.min(1, keepdim=True).values).int().argmax(1).int()
+    assert torch.equal(got, want)
+
+
+@pytest.mark.parametrize("K,dh,n", [(2, 4, 1_000), (64, 16, 4_000), (333, 32, 131_500)])
+def test_multi_index_assign_of_crowded_cells(Q, K, dh, n):
+    """Both halves leave vectors to the second kernel, which finds them among the cells of the first half."""
+    import torch
+    rng = np.random.default_rng(K)
+    halves = rng.integers(0, 2, size=(2, K, dh)).astype(np.float32)
+    halves[:, K // 2:] = halves[:, :K - K // 2]
+    x = rng.integers(0, 2, size=(n, 2 * dh)).astype(np.float32)
+    got = Q.qadc_multi_index_assign(to_gpu(halves), to_gpu(x)).cpu().numpy()
+    want = np.zeros(n, np.int64)
+    for h in range(2):
+        xx = x[:, h * dh:(h + 1) * dh]
+        dist = (xx ** 2).sum(1)[:, None] - 2 * xx @ halves[h].T + (halves[h] ** 2).sum(1)[None]  # whole numbers: exact
+        want = want * K + dist.argmin(1)
+    assert np.array_equal(got, want)
