@@ -7,15 +7,22 @@
 // on the cell is a matrix product: both factors are split into two bfloat16 numbers (16 significant bits)
 // and hi.hi + hi.lo + lo.hi is summed in float32 by the matrix units.  A lane keeps, per vector, the three
 // smallest of its group minima (a group: the 16 cells of a result tile that lie in one lane).  Whatever the
-// rounding, the closest cell lies in a group whose minimum is within `margin` (bound below) of the smallest;
-// those groups -- mostly one -- are measured in float64 by the definition, and a vector that may have more of
-// them than a lane remembers (equal centroids, values beyond the float32 range, infinities, NaN) is measured
+// rounding, the closest cell lies in a group whose minimum is within a margin (bound below) of the smallest;
+// those groups -- mostly one -- are measured in float32 and, cells that come within its rounding of each other, in
+// float64 by the definition.  A vector that may have more of them than a lane remembers (more than two equal
+// centroids, values beyond the float32 range, infinities, NaN) is marked, and assign_rest_kernel measures it
 // against all cells.  The result is the definition's, whatever the route.
 //
-// Bound: 3 x 2 n K d operations on the matrix units.  Measured for 1 M vectors, d = 128, K = 4096: 2.9 ms =
-// 1.1 PFLOP/s of bfloat16 products (the float64 kernel: 37.8 ms); 2.0 ms of it are products and group minima,
-// 0.4 splitting the centroids, which every workgroup does again -- so eight wavefronts share the tiles and keep
-// the operands of 64 vectors each in registers for the whole walk -- and 0.5 the last step.
+// Bound: 3 x 2 n K d operations on the matrix units.  Measured for 1 M vectors, d = 128, K = 4096: 2.8 ms =
+// 1.1 PFLOP/s of bfloat16 products (the float64 kernel: 37.5 ms); 2.0 ms of it are products and group minima,
+// 0.4 splitting the centroids, which every workgroup does again -- so eight wavefronts share the tiles and hold
+// the operands of 64 vectors each for the whole walk, all but a few of them in registers (256 per lane; 10
+// spilled for d = 128; the form for d = 129 to 255 and other rows spills 46 and takes 2.5 ms for 262 k vectors, d = 200,
+// K = 4096: 17.2 in float64) -- and 0.5 the last step.
+// A margin is a matter of the vector and of the closest cells: a far or NaN centroid costs the other cells
+// nothing (2.8 ms; with one margin for all, from the farthest centroid, 122).  Every centroid twice: 1.0 ms for 262 k
+// vectors (4.5 when every cell of a group was measured in float64, a lane per row).  Every centroid four times, all
+// vectors marked: 45 ms per 1 M (69 when the filter's own workgroups walked over the cells, a lane per row).
 //
 // assign_f64_kernel (d > 256: the vectors no longer fit the registers): a workgroup of 256 threads takes 128
 // vectors and walks over all cells 128 at a time; 16 components of both go through LDS as float64 per step,
@@ -34,24 +41,29 @@ constexpr int ASG_TN = 128;  // cells per step
 constexpr int ASG_TK = 16;   // components per step
 constexpr int ASG_LD = ASG_TM + 2;  // row stride in doubles: keeps 16-byte alignment, shifts the banks
 
+struct AssignTile {
+    __attribute__((aligned(16))) double xs[ASG_TK][ASG_LD];
+    __attribute__((aligned(16))) double cs[ASG_TK][ASG_LD];
+    double cand_d[ASG_TM][16];
+    int cand_c[ASG_TM][16];
+};
+
+// The cells of up to ASG_TM vectors, by a workgroup of 256 threads; row(k): the row of x that is vector k of the tile, -1
+// for none.
 // Thread (tx, ty), tx = tid & 15, ty = tid >> 4, owns the vectors 8*ty .. 8*ty+7 of the tile and
 // the cells 32*k + 2*tx + e (k < 4, e < 2): a wavefront's 16-byte reads of the cells are
 // contiguous across its lanes, its reads of the vectors are the same for 16 lanes.
-__global__ __launch_bounds__(256) void assign_f64_kernel(const float *__restrict__ coarse, int K, int d,
-                                                         const float *__restrict__ x, int64_t ldx, int64_t n,
-                                                         int32_t *__restrict__ cells, int scale, int accumulate)
+template <typename Row, typename Store>
+__device__ __forceinline__ void assign_tile(AssignTile &s, const float *__restrict__ coarse, int K, int d,
+                                            const float *__restrict__ x, int64_t ldx, Row row, Store store)
 {
-    __shared__ __attribute__((aligned(16))) double xs[ASG_TK][ASG_LD];
-    __shared__ __attribute__((aligned(16))) double cs[ASG_TK][ASG_LD];
-    __shared__ double cand_d[ASG_TM][16];
-    __shared__ int cand_c[ASG_TM][16];
     const int tid = threadIdx.x;
     const int tx = tid & 15, ty = tid >> 4;
-    const int64_t i0 = (int64_t)blockIdx.x * ASG_TM;
     double best_d[8];
     int best_c[8];
+    int from[8];  // the rows this thread fetches from
 #pragma unroll
-    for (int a = 0; a < 8; ++a) { best_d[a] = __builtin_inf(); best_c[a] = 0x7fffffff; }
+    for (int a = 0; a < 8; ++a) { best_d[a] = __builtin_inf(); best_c[a] = 0x7fffffff; from[a] = row(ty + 16 * a); }
 
     for (int c0 = 0; c0 < K; c0 += ASG_TN) {
         double acc[8][8];
@@ -64,12 +76,11 @@ __global__ __launch_bounds__(256) void assign_f64_kernel(const float *__restrict
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
                 const int idx = tid + e * 256;
-                const int row = idx >> 4, col = idx & 15;
+                const int r = idx >> 4, col = idx & 15;
                 const int t = t0 + col;
-                const int64_t i = i0 + row;
-                const int c = c0 + row;
-                xs[col][row] = (i < n && t < d) ? (double)x[i * ldx + t] : 0.0;
-                cs[col][row] = (c < K && t < d) ? (double)coarse[(size_t)c * d + t] : 0.0;
+                const int c = c0 + r;
+                s.xs[col][r] = (from[e] >= 0 && t < d) ? (double)x[from[e] * ldx + t] : 0.0;
+                s.cs[col][r] = (c < K && t < d) ? (double)coarse[(size_t)c * d + t] : 0.0;
             }
             __syncthreads();
 #pragma unroll 4
@@ -77,12 +88,12 @@ __global__ __launch_bounds__(256) void assign_f64_kernel(const float *__restrict
                 double xv[8], cv[8];
 #pragma unroll
                 for (int a = 0; a < 8; a += 2) {
-                    const double2 v = *reinterpret_cast<const double2 *>(&xs[kk][8 * ty + a]);
+                    const double2 v = *reinterpret_cast<const double2 *>(&s.xs[kk][8 * ty + a]);
                     xv[a] = v.x; xv[a + 1] = v.y;
                 }
 #pragma unroll
                 for (int k = 0; k < 4; ++k) {
-                    const double2 v = *reinterpret_cast<const double2 *>(&cs[kk][32 * k + 2 * tx]);
+                    const double2 v = *reinterpret_cast<const double2 *>(&s.cs[kk][32 * k + 2 * tx]);
                     cv[2 * k] = v.x; cv[2 * k + 1] = v.y;
                 }
 #pragma unroll
@@ -109,22 +120,126 @@ __global__ __launch_bounds__(256) void assign_f64_kernel(const float *__restrict
     }
 #pragma unroll
     for (int a = 0; a < 8; ++a) {
-        cand_d[8 * ty + a][tx] = best_d[a];
-        cand_c[8 * ty + a][tx] = best_c[a];
+        s.cand_d[8 * ty + a][tx] = best_d[a];
+        s.cand_c[8 * ty + a][tx] = best_c[a];
     }
     __syncthreads();
-    if (tid < ASG_TM) {
-        const int64_t i = i0 + tid;
-        if (i < n) {
-            double bd = cand_d[tid][0];
-            int bc = cand_c[tid][0];
-            for (int k = 1; k < 16; ++k) {
-                const double dd = cand_d[tid][k];
-                const int cc = cand_c[tid][k];
-                if (dd < bd || (dd == bd && cc < bc)) { bd = dd; bc = cc; }
-            }
-            cells[i] = (accumulate ? cells[i] : 0) + bc * scale;
+    if (tid < ASG_TM && row(tid) >= 0) {
+        double bd = s.cand_d[tid][0];
+        int bc = s.cand_c[tid][0];
+        for (int k = 1; k < 16; ++k) {
+            const double dd = s.cand_d[tid][k];
+            const int cc = s.cand_c[tid][k];
+            if (dd < bd || (dd == bd && cc < bc)) { bd = dd; bc = cc; }
         }
+        store(row(tid), bc);
+    }
+}
+
+__global__ __launch_bounds__(256) void assign_f64_kernel(const float *__restrict__ coarse, int K, int d,
+                                                         const float *__restrict__ x, int64_t ldx, int64_t n,
+                                                         int32_t *__restrict__ cells, int scale, int accumulate)
+{
+    __shared__ AssignTile s;
+    const int64_t i0 = (int64_t)blockIdx.x * ASG_TM;
+    assign_tile(s, coarse, K, d, x + i0 * ldx, ldx, [&](int k) { return i0 + k < n ? k : -1; },
+                [&](int k, int bc) { cells[i0 + k] = (accumulate ? cells[i0 + k] : 0) + bc * scale; });
+}
+
+// ------------------------------------------------------------------ what the filter leaves
+
+// A vector that the filter cannot decide is marked in `cells`: what the pass found there (0 without `accumulate`) with
+// bit 30 turned over.  No cell looks like that: cells are below 2^28 where they accumulate and below 2^30 otherwise (the
+// filter takes no more centroids), or, for a vector with a NaN, 0x7fffffff times the scale plus a cell.
+constexpr int ASG_MARK = 0x40000000;
+constexpr int ASG_MARK_MAX_K = 1 << 30;
+
+__device__ __forceinline__ bool assign_marked(int cell, int K, int accumulate)
+{
+    const int was = cell ^ ASG_MARK;
+    return accumulate ? (unsigned)was < (1u << 28) || was == (int)(0x7fffffffu * (unsigned)K) : was == 0;
+}
+
+// Every workgroup looks for the marks of `range` vectors (a multiple of ASG_TM, up to ASG_RANGE) and measures those
+// vectors against all cells, by the definition: 128 at a time in tiles, or, of a few, four at a time and a lane per
+// cell (a tile takes as long as five such rounds whatever it holds).  The filter's own last steps were slower at it, and
+// cost the filter its registers.  Ranges rather than single tiles, so that few marks fill few tiles; 512 workgroups.
+constexpr int ASG_RANGE = 4096, ASG_FEW = 20;
+
+__global__ __launch_bounds__(256) void assign_rest_kernel(const float *__restrict__ coarse, int K, int d,
+                                                          const float *__restrict__ x, int64_t ldx, int64_t n, int range,
+                                                          int32_t *__restrict__ cells, int scale, int accumulate)
+{
+    __shared__ AssignTile s;
+    __shared__ uint16_t todo[ASG_RANGE];
+    __shared__ int ntodo;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int64_t i0 = (int64_t)blockIdx.x * range;
+    if (tid == 0) ntodo = 0;
+    __syncthreads();
+    for (int k = tid; k < range; k += 256) {
+        const bool found = i0 + k < n && assign_marked(cells[i0 + k], K, accumulate);
+        if (found) todo[atomicAdd(&ntodo, 1)] = (uint16_t)k;
+    }
+    __syncthreads();
+    const int count = ntodo;
+    auto store = [&](int k, int bc) { cells[i0 + k] = (cells[i0 + k] ^ ASG_MARK) + bc * scale; };
+    const int few = d <= 4 ? ASG_RANGE : ASG_FEW;  // (a tile computes 16 components at least)
+    int k0 = 0;
+    for (; count - k0 > few; k0 += ASG_TM) {  // uniform
+        assign_tile(s, coarse, K, d, x + i0 * ldx, ldx, [&](int k) { return k0 + k < count ? (int)todo[k0 + k] : -1; }, store);
+        __syncthreads();
+    }
+    double(&red_d)[16][4] = *reinterpret_cast<double(*)[16][4]>(s.cand_d);
+    int(&red_c)[16][4] = *reinterpret_cast<int(*)[16][4]>(s.cand_c);
+    for (; k0 < count; k0 += 4) {  // uniform
+        const float *xr[4];
+        double bd[4];
+        int bc[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            xr[k] = x + (i0 + todo[min(k0 + k, count - 1)]) * ldx;
+            bd[k] = __builtin_inf();
+            bc[k] = 0x7fffffff;
+        }
+        for (int c = tid; c < K; c += 256) {
+            const float *cr = coarse + (size_t)c * d;
+            double acc[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll 4
+            for (int t = 0; t < d; ++t) {
+                const double cv = (double)cr[t];
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    const double df = (double)xr[k][t] - cv;
+                    acc[k] = fma(df, df, acc[k]);
+                }
+            }
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+                if (acc[k] < bd[k] || (acc[k] == bd[k] && c < bc[k])) { bd[k] = acc[k]; bc[k] = c; }
+        }
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+#pragma unroll
+            for (int m = 32; m >= 1; m >>= 1) {
+                const double od = __shfl_xor(bd[k], m);
+                const int oc = __shfl_xor(bc[k], m);
+                if (od < bd[k] || (od == bd[k] && oc < bc[k])) { bd[k] = od; bc[k] = oc; }
+            }
+            if (lane == 0) { red_d[wave][k] = bd[k]; red_c[wave][k] = bc[k]; }
+        }
+        __syncthreads();
+        if (tid < 4 && k0 + tid < count) {
+            double d0 = red_d[0][tid];
+            int c0 = red_c[0][tid];
+            for (int w = 1; w < 4; ++w)
+                if (red_d[w][tid] < d0 || (red_d[w][tid] == d0 && red_c[w][tid] < c0)) {
+                    d0 = red_d[w][tid];
+                    c0 = red_c[w][tid];
+                }
+            store(todo[k0 + tid], c0);
+        }
+        __syncthreads();
     }
 }
 
@@ -181,23 +296,26 @@ __global__ __launch_bounds__(NT, 2) void assign_filter_kernel(const float *__res
     __shared__ __attribute__((aligned(16))) float ref[16 * KS];
     __shared__ float cmax_s[NW];
     __shared__ int cand[TM][4];     // groups to measure, -1: none
-    __shared__ int redo[TM];        // vectors to measure against all cells
-    __shared__ int nredo;
-    __shared__ double red_d[4][NW];  // [vector of four][wavefront]
-    __shared__ int red_c[4][NW];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int col = lane & 31, half = lane >> 5;
     const int64_t i0 = (int64_t)blockIdx.x * TM;
 
-    // the reference: the mean of eight centroids of the range (any vector would do; one amid the
-    // centroids keeps the norms, and with them the margin, small)
+    // The reference: per component, the middle of eight centroids of the range.  (Any vector would do; one amid the
+    // centroids keeps the norms, and with them the margins, small, and a few stray or non-finite ones do not move this.)
     for (int t = tid; t < 16 * KS; t += NT) {
-        float s = 0.0f;
-        if (t < d)
-            for (int k = 0; k < 8; ++k) s += coarse[(size_t)((int64_t)k * K >> 3) * d + t];
-        ref[t] = s * 0.125f;
+        float v[8];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) v[k] = t < d ? coarse[(size_t)((int64_t)k * K >> 3) * d + t] : 0.0f;
+#pragma unroll
+        for (int a = 0; a < 8; ++a)  // odd-even transposition sort (a NaN goes out at the first comparison)
+#pragma unroll
+            for (int b = a & 1; b + 1 < 8; b += 2) {
+                const float lo = fminf(v[b], v[b + 1]), hi = fmaxf(v[b], v[b + 1]);
+                v[b] = lo;
+                v[b + 1] = hi;
+            }
+        ref[t] = 0.5f * v[3] + 0.5f * v[4];
     }
-    if (tid == 0) nredo = 0;
     __syncthreads();
 
     // this wavefront's vectors: operand -2 x', split; lane (col, half) holds components 16 s + 8 half ..
@@ -222,6 +340,13 @@ __global__ __launch_bounds__(NT, 2) void assign_filter_kernel(const float *__res
         }
         xn[nb] = s2 + __shfl_xor(s2, 32);
     }
+
+    // Rounding of a score, whatever the unit: |score - (distance^2 - |x'|^2)| <= eps (|x'|^2 + |c'|^2), with D = 16 KS:
+    // the differences 4 2^-24; what the splits and the missing lo.lo leave out 3.1 2^-18; 3 D + 1 additions of values
+    // up to 2 (|x'|^2 + |c'|^2) (3 D + 1) 2^-22 (2^-23 each: no assumption on how the matrix units round); the norms
+    // (D + 8) 2^-24; 1.28e-5 + 7.8e-7 D in all.  The part of the centroid comes off its score from the start, so that a
+    // far centroid loosens its own score and no other's.
+    constexpr float eps = 1.5e-5f + 9e-7f * (16 * KS);
 
     // thread -> centroid and steps it splits: eight neighbouring lanes hold eight centroids (their
     // 16-byte LDS writes are contiguous), a centroid's threads lie in one wavefront
@@ -262,8 +387,8 @@ __global__ __launch_bounds__(NT, 2) void assign_filter_kernel(const float *__res
 #pragma unroll
         for (int m = 8; m < 8 * PS; m <<= 1) s2 += __shfl_xor(s2, m);
         const bool in = c0 + crow < K;
-        if (in) cmax = s2 > cmax || s2 != s2 ? s2 : cmax;  // (a NaN stays: it makes every margin NaN)
-        if (part == 0) nrm[buf][crow] = in ? s2 : __builtin_inff();
+        if (in) cmax = fmaxf(cmax, s2);  // (NaN: left out)
+        if (part == 0) nrm[buf][crow] = in ? s2 * (1.0f - eps) : __builtin_inff();
     };
 
     float b1[NB], b2[NB], b3[NB];  // the three smallest group minima, ascending; the groups of the first two
@@ -337,29 +462,26 @@ __global__ __launch_bounds__(NT, 2) void assign_filter_kernel(const float *__res
 
     // largest |c'|^2
 #pragma unroll
-    for (int m = 32; m >= 1; m >>= 1) {
-        const float o = __shfl_xor(cmax, m);
-        cmax = o > cmax || o != o ? o : cmax;
-    }
+    for (int m = 32; m >= 1; m >>= 1) cmax = fmaxf(cmax, __shfl_xor(cmax, m));
     if (lane == 0) cmax_s[wave] = cmax;
     __syncthreads();
     cmax = cmax_s[0];
-    for (int k = 1; k < NW; ++k) cmax = cmax_s[k] > cmax || cmax_s[k] != cmax_s[k] ? cmax_s[k] : cmax;
+    for (int k = 1; k < NW; ++k) cmax = fmaxf(cmax, cmax_s[k]);
 
-    // Bound of |score - (exact distance - |x'|^2)|, with S = |x'|^2 + max |c'|^2 >= 2 |x'| |c'| and D = 16 KS:
-    // rounding of the differences 4 S 2^-24; what the splits and the missing lo.lo leave out 3.1 S 2^-18; 3 D + 1
-    // additions of the product 2 S (3 D + 1) 2^-23 (2^-23: no assumption on how the matrix units round); the
-    // norms S (D + 8) 2^-24.  The margin is twice that for two candidates, rounded up.
+    // With b1 the smallest score, reached by a cell c*: the closest cell's score is at most b1 + 2 eps (|x'|^2 + |c*'|^2).
+    // |c*'|^2 is at most the largest of all cells, and |c*'| <= |x'| + |x' - c*'| with |x' - c*'|^2 <= b1 + |x'|^2 + what
+    // rounding adds, under a thousandth of |x'|^2.  A centroid whose score overflows or is NaN (it loses every
+    // comparison) is not the closest to a vector that has one within 1e18.
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb) {
         const int v = (wave * NB + nb) * 32 + col;
-        const float S = xn[nb] + cmax;
-        const float margin = __builtin_fmaf(S, 3e-5f + 1.8e-6f * (16 * KS), 1e-30f);
-        const float thr = fminf(b1[nb], __shfl_xor(b1[nb], 32)) + margin;
+        const float low = fminf(b1[nb], __shfl_xor(b1[nb], 32));
+        const float far = __builtin_sqrtf(xn[nb]) + __builtin_sqrtf(fmaxf(low + xn[nb], 0.0f) + 1e-3f * xn[nb]);
+        const float thr = low + __builtin_fmaf(2.0f * eps, xn[nb] + 1.01f * fminf(far * far, cmax), 1e-30f);
         // (comparisons that a NaN fails)
-        const bool sure = S < 1e37f && thr < 1e37f && b3[nb] > thr;
+        const bool sure = xn[nb] < 1e36f && thr < 1e36f && b3[nb] > thr;
         // this lane's groups in question, then those of the other half; the first entry is never empty
-        // unless the vector has to be measured against all cells
+        // unless the vector is left to the kernel after this one
         const int g1 = b1[nb] <= thr ? 2 * a1[nb] + half : -1, g2 = b2[nb] <= thr ? 2 * a2[nb] + half : -1;
         const int o1 = __shfl_xor(g1, 32), o2 = __shfl_xor(g2, 32);
         const int other = __shfl_xor((int)sure, 32);  // (asked by all lanes: a lane that does not ask gives nothing)
@@ -369,20 +491,19 @@ __global__ __launch_bounds__(NT, 2) void assign_filter_kernel(const float *__res
             cand[v][1] = g1 >= 0 ? g2 : o2;
             cand[v][2] = g1 >= 0 ? o1 : -1;
             cand[v][3] = g1 >= 0 ? o2 : -1;
-            if (all && i0 + v < n) redo[atomicAdd(&nredo, 1)] = v;
+            if (all && i0 + v < n) cells[i0 + v] = (accumulate ? cells[i0 + v] : 0) ^ ASG_MARK;
         }
     }
     __syncthreads();
 
-    // The groups in question, 16 lanes per vector.  One group: its 16 distances in float32, the lanes side by
-    // side along the components (a lane per cell would read 64 different lines per load), and unless a second
-    // one lies within the rounding of the closest that is the cell.  Otherwise by the definition, a lane per cell.
-    const int r = tid & 15;
+    // The groups in question, 16 lanes per vector: the 16 distances of a group in float32, the lanes side by side along
+    // the components (a lane per cell would read 64 different lines per load).  A cell that no other comes within the
+    // rounding of is the closest; else the cells that do are measured by the definition, a lane each.
+    const int r = tid & 15, team = (lane >> 4) * 16;
     auto cell_of = [&](int g, int k) { return (g >> 1) * 32 + 8 * (k >> 2) + 4 * (g & 1) + (k & 3); };
     for (int v = tid >> 4; v < TM; v += NT / 16) {
         const int64_t i = i0 + v;
-        const int g0 = cand[v][0];
-        if (i >= n || g0 < 0) continue;  // uniform over the 16 lanes
+        if (i >= n || cand[v][0] < 0) continue;  // uniform over the 16 lanes
         const float *xr = x + i * ldx;
         float xv[KS];
         constexpr int W = VEC && KS % 4 == 0 ? 4 : 1;  // components per load
@@ -393,68 +514,102 @@ __global__ __launch_bounds__(NT, 2) void assign_filter_kernel(const float *__res
                 const int t = W * (r + 16 * e) + u;
                 xv[W * e + u] = VEC || t < d ? xr[t] : 0.0f;
             }
-        float part[16];
+        // distance to cell r of group g
+        auto measure = [&](int g) {
+            float part[16];
 #pragma unroll
-        for (int k = 0; k < 16; ++k) {
-            const float *cr = coarse + (size_t)min(cell_of(g0, k), K - 1) * d;
-            float acc = 0.0f;
+            for (int k = 0; k < 16; ++k) {
+                const float *cr = coarse + (size_t)min(cell_of(g, k), K - 1) * d;
+                float acc = 0.0f;
 #pragma unroll
-            for (int e = 0; e < KS / W; ++e) {
-                float cv[W];
-                if constexpr (W == 4) {
-                    const float4 f = *reinterpret_cast<const float4 *>(cr + 4 * (r + 16 * e));
-                    cv[0] = f.x; cv[1] = f.y; cv[2] = f.z; cv[3] = f.w;
-                } else {
-                    const int t = r + 16 * e;
-                    cv[0] = VEC || t < d ? cr[t] : 0.0f;
+                for (int e = 0; e < KS / W; ++e) {
+                    float cv[W];
+                    if constexpr (W == 4) {
+                        const float4 f = *reinterpret_cast<const float4 *>(cr + 4 * (r + 16 * e));
+                        cv[0] = f.x; cv[1] = f.y; cv[2] = f.z; cv[3] = f.w;
+                    } else {
+                        const int t = r + 16 * e;
+                        cv[0] = VEC || t < d ? cr[t] : 0.0f;
+                    }
+#pragma unroll
+                    for (int u = 0; u < W; ++u) {
+                        const float df = xv[W * e + u] - cv[u];
+                        acc = __builtin_fmaf(df, df, acc);
+                    }
                 }
+                part[k] = acc;
+            }
+            // sums over the 16 lanes, halving the cells a lane is responsible for: lane r ends with cell r
 #pragma unroll
-                for (int u = 0; u < W; ++u) {
-                    const float df = xv[W * e + u] - cv[u];
-                    acc = __builtin_fmaf(df, df, acc);
+            for (int w = 8; w >= 1; w >>= 1)
+#pragma unroll
+                for (int k = 0; k < w; ++k) {
+                    const bool up = r & w;
+                    const float keep = up ? part[k + w] : part[k], give = up ? part[k] : part[k + w];
+                    part[k] = keep + __shfl_xor(give, w);
                 }
+            return cell_of(g, r) < K && part[0] == part[0] ? part[0] : __builtin_inff();  // (a NaN is never the closest)
+        };
+        auto lowest = [&](float f) {
+#pragma unroll
+            for (int w = 8; w >= 1; w >>= 1) f = fminf(f, __shfl_xor(f, w));
+            return f;
+        };
+        // rounding of two sums of d squares (d / 16 + 4 additions, the differences, the squares): (d / 8 + 14) 2^-24,
+        // here at least 1.3 times that
+        auto slack = [&](float f) { return f + __builtin_fmaf(f, 2e-6f + 1e-7f * KS, 1e-33f); };
+        auto among = [&](bool near) { return __popcll((__ballot(near) >> team) & 0xffffull); };
+        const int g0 = cand[v][0];
+        const bool more = cand[v][1] >= 0 || cand[v][2] >= 0 || cand[v][3] >= 0;  // uniform over the 16 lanes
+        float dist[4] = {measure(g0), __builtin_inff(), __builtin_inff(), __builtin_inff()};
+        float close = slack(lowest(dist[0]));
+        int rivals = among(dist[0] <= close);
+        int bc = dist[0] <= close ? cell_of(g0, r) : 0x7fffffff;
+        if (more) {
+#pragma unroll 1
+            for (int q = 1; q < 4; ++q) {
+                const int g = cand[v][q];
+                if (g < 0) continue;  // uniform over the 16 lanes
+                const float to = measure(g);
+#pragma unroll
+                for (int p = 1; p < 4; ++p) dist[p] = p == q ? to : dist[p];
             }
-            part[k] = acc;
-        }
-        // sums over the 16 lanes, halving the cells a lane is responsible for: lane r ends with cell r
+            close = slack(lowest(fminf(fminf(dist[0], dist[1]), fminf(dist[2], dist[3]))));
+            bc = 0x7fffffff;
+            rivals = 0;
 #pragma unroll
-        for (int w = 8; w >= 1; w >>= 1)
-#pragma unroll
-            for (int k = 0; k < w; ++k) {
-                const bool up = r & w;
-                const float keep = up ? part[k + w] : part[k], give = up ? part[k] : part[k + w];
-                part[k] = keep + __shfl_xor(give, w);
+            for (int q = 0; q < 4; ++q) {
+                const bool near = dist[q] <= close && cand[v][q] >= 0;
+                rivals += among(near);
+                if (near) bc = cell_of(cand[v][q], r);
             }
-        int bc = cell_of(g0, r);
-        const bool in = bc < K;
-        const float d0 = in ? part[0] : __builtin_inff();
-        float d1 = d0, d2 = __builtin_inff();  // the two smallest of the 16 lanes (NaN: ignored here, caught below)
-        int at = r;
-#pragma unroll
-        for (int w = 8; w >= 1; w >>= 1) {
-            const float o1 = __shfl_xor(d1, w), o2 = __shfl_xor(d2, w);
-            const int oa = __shfl_xor(at, w);
-            d2 = fminf(fmaxf(d1, o1), fminf(d2, o2));
-            at = o1 < d1 ? oa : at;
-            d1 = fminf(d1, o1);
         }
-        // rounding of two sums of d squares (d / 16 + 4 additions, the differences, the squares), doubled
-        const float close = __builtin_fmaf(d1, 2e-6f + 1e-7f * KS, 1e-33f);
-        if (cand[v][1] < 0 && cand[v][2] < 0 && cand[v][3] < 0 && d1 < 1e37f && d2 > d1 + close) {
-            bc = cell_of(g0, at);
-        } else {
+        if (rivals > 1) {  // uniform over the 16 lanes
             double bd = __builtin_inf();
             bc = 0x7fffffff;
-            for (int e = 0; e < 4; ++e) {
-                const int g = cand[v][e];
-                if (g < 0 || cell_of(g, r) >= K) continue;
-                const float *cr = coarse + (size_t)cell_of(g, r) * d;
+#pragma unroll 1
+            for (int q = 0; q < 4; ++q) {
+                const int g = cand[v][q];
+                const float dq = q == 0 ? dist[0] : q == 1 ? dist[1] : q == 2 ? dist[2] : dist[3];
+                const int c = cell_of(g, r);
+                if (g < 0 || !(dq <= close) || c >= K) continue;
+                const float *cr = coarse + (size_t)c * d;
                 double dd = 0.0;
-                for (int t = 0; t < d; ++t) {
-                    const double df = (double)xr[t] - (double)cr[t];
+                auto add = [&](float a, float b) {
+                    const double df = (double)a - (double)b;
                     dd = fma(df, df, dd);
+                };
+                if constexpr (VEC) {
+#pragma unroll 4
+                    for (int t = 0; t < d; t += 4) {
+                        const float4 a = *reinterpret_cast<const float4 *>(xr + t), b = *reinterpret_cast<const float4 *>(cr + t);
+                        add(a.x, b.x); add(a.y, b.y); add(a.z, b.z); add(a.w, b.w);
+                    }
+                } else {
+#pragma unroll 8
+                    for (int t = 0; t < d; ++t) add(xr[t], cr[t]);
                 }
-                if (dd < bd || (dd == bd && cell_of(g, r) < bc)) { bd = dd; bc = cell_of(g, r); }
+                if (dd < bd || (dd == bd && c < bc)) { bd = dd; bc = c; }
             }
 #pragma unroll
             for (int w = 8; w >= 1; w >>= 1) {
@@ -462,61 +617,11 @@ __global__ __launch_bounds__(NT, 2) void assign_filter_kernel(const float *__res
                 const int oc = __shfl_xor(bc, w);
                 if (od < bd || (od == bd && oc < bc)) { bd = od; bc = oc; }
             }
+        } else {
+#pragma unroll
+            for (int w = 8; w >= 1; w >>= 1) bc = min(bc, __shfl_xor(bc, w));
         }
         if (r == 0) cells[i] = (accumulate ? cells[i] : 0) + bc * scale;
-    }
-
-    // vectors to measure against all cells, four at a time
-    const int todo = nredo;
-    for (int k0 = 0; k0 < todo; k0 += 4) {  // uniform
-        const float *xr[4];
-        double bd[4];
-        int bc[4];
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            xr[k] = x + (i0 + redo[min(k0 + k, todo - 1)]) * ldx;
-            bd[k] = __builtin_inf();
-            bc[k] = 0x7fffffff;
-        }
-        for (int c = tid; c < K; c += NT) {
-            const float *cr = coarse + (size_t)c * d;
-            double acc[4] = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll 4
-            for (int t = 0; t < d; ++t) {
-                const double cv = (double)cr[t];
-#pragma unroll
-                for (int k = 0; k < 4; ++k) {
-                    const double df = (double)xr[k][t] - cv;
-                    acc[k] = fma(df, df, acc[k]);
-                }
-            }
-#pragma unroll
-            for (int k = 0; k < 4; ++k)
-                if (acc[k] < bd[k] || (acc[k] == bd[k] && c < bc[k])) { bd[k] = acc[k]; bc[k] = c; }
-        }
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-#pragma unroll
-            for (int m = 32; m >= 1; m >>= 1) {
-                const double od = __shfl_xor(bd[k], m);
-                const int oc = __shfl_xor(bc[k], m);
-                if (od < bd[k] || (od == bd[k] && oc < bc[k])) { bd[k] = od; bc[k] = oc; }
-            }
-            if (lane == 0) { red_d[k][wave] = bd[k]; red_c[k][wave] = bc[k]; }
-        }
-        __syncthreads();
-        if (tid < 4 && k0 + tid < todo) {
-            double d0 = red_d[tid][0];
-            int c0 = red_c[tid][0];
-            for (int w = 1; w < NW; ++w)
-                if (red_d[tid][w] < d0 || (red_d[tid][w] == d0 && red_c[tid][w] < c0)) {
-                    d0 = red_d[tid][w];
-                    c0 = red_c[tid][w];
-                }
-            const int64_t i = i0 + redo[k0 + tid];
-            cells[i] = (accumulate ? cells[i] : 0) + c0 * scale;
-        }
-        __syncthreads();
     }
 }
 
@@ -546,7 +651,11 @@ static void launch_filter(const float *coarse, int K, int d, const float *x, int
 static int assign_pass(const float *coarse, int K, int d, const float *x, int64_t ldx, int64_t n, int32_t *cells,
                        int scale, int accumulate, hipStream_t st)
 {
-    if (d <= 32)
+    const bool filter = d <= AF_MAX_D && K <= ASG_MARK_MAX_K;
+    if (!filter)
+        hipLaunchKernelGGL(assign_f64_kernel, dim3((unsigned)ceil_div(n, ASG_TM)), dim3(256), 0, st, coarse, K, d, x,
+                           ldx, n, cells, scale, accumulate);
+    else if (d <= 32)
         launch_filter<2>(coarse, K, d, x, ldx, n, cells, scale, accumulate, st);
     else if (d <= 64)
         launch_filter<4>(coarse, K, d, x, ldx, n, cells, scale, accumulate, st);
@@ -554,11 +663,13 @@ static int assign_pass(const float *coarse, int K, int d, const float *x, int64_
         launch_filter<6>(coarse, K, d, x, ldx, n, cells, scale, accumulate, st);
     else if (d <= 128)
         launch_filter<8>(coarse, K, d, x, ldx, n, cells, scale, accumulate, st);
-    else if (d <= AF_MAX_D)
-        launch_filter<16>(coarse, K, d, x, ldx, n, cells, scale, accumulate, st);
     else
-        hipLaunchKernelGGL(assign_f64_kernel, dim3((unsigned)ceil_div(n, ASG_TM)), dim3(256), 0, st, coarse, K, d, x,
-                           ldx, n, cells, scale, accumulate);
+        launch_filter<16>(coarse, K, d, x, ldx, n, cells, scale, accumulate, st);
+    if (filter) {
+        const int64_t range = std::min<int64_t>(ASG_RANGE, std::max<int64_t>(512, ceil_div(ceil_div(n, 512), ASG_TM) * ASG_TM));
+        hipLaunchKernelGGL(assign_rest_kernel, dim3((unsigned)ceil_div(n, range)), dim3(256), 0, st, coarse, K, d, x, ldx, n,
+                           (int)range, cells, scale, accumulate);
+    }
     QADC_HIP_TRY(hipGetLastError());
     return QADC_OK;
 }

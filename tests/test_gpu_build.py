@@ -472,3 +472,22 @@ def test_multi_index_assign_of_crowded_cells(Q, K, dh, n):
         dist = (xx ** 2).sum(1)[:, None] - 2 * xx @ halves[h].T + (halves[h] ** 2).sum(1)[None]  # whole numbers: exact
         want = want * K + dist.argmin(1)
     assert np.array_equal(got, want)
+
+
+@pytest.mark.parametrize("d,K", [(128, 256), (64, 1024), (200, 300)])
+def test_ivf_assign_is_not_slowed_by_a_few_centroids(Q, d, K):
+    """One stray centroid, one that is not finite, all of them twice: not much slower than without."""
+    import torch
+    from gpu_common import gpu_us
+    g = torch.Generator(device="cuda:0")
+    g.manual_seed(d)
+    coarse = 30 * torch.randn((K, d), generator=g, device="cuda:0")
+    x = coarse[torch.randint(0, K, (200_000,), generator=g, device="cuda:0")] + 18 * torch.randn((200_000, d), generator=g,
+                                                                                                device="cuda:0")
+    usual = gpu_us(lambda: Q.qadc_ivf_assign(coarse, x), reps=5)
+    for change, limit in ((lambda c: c[K // 3].mul_(100), 2), (lambda c: c[K // 5].fill_(float("nan")), 2),
+                          (lambda c: c[K // 2:].copy_(c[:K // 2]), 4.5), (lambda c: c.copy_(c[:1].expand(K, d).clone()), 14)):
+        c = coarse.clone()
+        change(c)
+        us = gpu_us(lambda: Q.qadc_ivf_assign(c, x), reps=5)
+        assert us < limit * usual, (us, usual)
