@@ -600,18 +600,20 @@ __global__ __launch_bounds__(MERGE_NT) void merge_gather_kernel(
     uint64_t *lists = reinterpret_cast<uint64_t *>(ws + (size_t)q * ws_stride + lists_off);
     const int pitch = R;
     const unsigned slots = (unsigned)G * (unsigned)R;
-    // every reported key, a thread per region (only where neither the registers nor the LDS hold the keys)
+    // every reported key, spread over the threads by region (only where too many of them tie for LDS to hold them)
     auto each_key = [&](auto f) {
-        for (int g = tid; g < G; g += MERGE_NT) {
+        constexpr int step = FLAT ? MERGE_NT / WAVE : MERGE_NT;  // few regions: a wavefront per region
+        const unsigned i0 = FLAT ? tid % WAVE : 0, di = FLAT ? WAVE : 1;
+        for (int g = FLAT ? tid / WAVE : tid; g < G; g += step) {
             const unsigned c = min(counts[g], (unsigned)pitch);
             const uint64_t *l = lists + (size_t)g * pitch;
-            for (unsigned i = 0; i < c; i += 4) {  // four loads in flight before the first use
+            for (unsigned i = i0; i < c; i += 4 * di) {  // four loads in flight before the first use
                 uint64_t k[4];
 #pragma unroll
-                for (int u = 0; u < 4; ++u) k[u] = (i + u < c) ? l[i + u] : 0;
+                for (int u = 0; u < 4; ++u) k[u] = (i + u * di < c) ? l[i + u * di] : 0;
 #pragma unroll
                 for (int u = 0; u < 4; ++u)
-                    if (i + u < c) f(k[u]);
+                    if (i + u * di < c) f(k[u]);
             }
         }
     };
@@ -796,32 +798,28 @@ __global__ __launch_bounds__(MERGE_NT) void merge_gather_kernel(
 
     if (need > 0 && !done) {
         // full radix select, then order the winners by rank
-        auto winners = [&](auto each, uint64_t kth) {
-            each([&](uint64_t k) {
-                if (k <= kth) lkeys[atomicAdd(&lcnt, 1u)] = k;  // exactly `need` keys: they are unique
-            });
-        };
         const unsigned held = FLAT ? slots : total;  // key[t] of thread tid is number tid + t MERGE_NT of these
-        if (held <= (unsigned)MERGE_CAP) {  // uniform: eight passes over LDS are shorter than over the registers
+        if (held <= (unsigned)MERGE_CAP) {           // uniform
+            constexpr int HELD = PER < MERGE_PER ? PER : MERGE_PER;
 #pragma unroll
-            for (int t = 0; t < (PER < MERGE_PER ? PER : MERGE_PER); ++t)
+            for (int t = 0; t < HELD; ++t)
                 if (tid + t * MERGE_NT < held) lkeys[tid + t * MERGE_NT] = key[t];  // (an empty slot's ~0 comes last)
             __syncthreads();
             const uint64_t kth = block_radix_select<uint64_t, KBYTES>(lkeys, held, need, &sc);
             __syncthreads();
             if (tid == 0) lcnt = 0;
             __syncthreads();
-            winners(own_keys, kth);
+#pragma unroll
+            for (int t = 0; t < HELD; ++t)
+                if (tid + t * MERGE_NT < held && key[t] <= kth) lkeys[atomicAdd(&lcnt, 1u)] = key[t];  // exactly `need`
         } else {
-            auto all_keys = [&](auto f) {
-                if constexpr (FLAT) own_keys(f);
-                else each_key(f);
-            };
-            const uint64_t kth = block_radix_select_each<uint64_t, KBYTES>(all_keys, need, &sc);
+            const uint64_t kth = block_radix_select_each<uint64_t, KBYTES>(each_key, need, &sc);
             __syncthreads();
             if (tid == 0) lcnt = 0;
             __syncthreads();
-            winners(all_keys, kth);
+            each_key([&](uint64_t k) {
+                if (k <= kth) lkeys[atomicAdd(&lcnt, 1u)] = k;  // exactly `need` keys: they are unique
+            });
         }
         __syncthreads();
         for (unsigned i = tid; i < need; i += MERGE_NT) {
