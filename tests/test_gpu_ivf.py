@@ -199,9 +199,9 @@ def test_ivf_probe_selection_many_cells_with_exact_ties(Q, O):
 
 @pytest.mark.parametrize("K,d", [(331, 64), (48, 40)])
 def test_ivf_index_step_of_large_batches_equals_small_batches(Q, O, K, d):
-    """Batches of 64 queries and more take the tiled distance kernel: same cells, same order, as the
-    same queries sent a few at a time (both sum the float32 differences in increasing component
-    order), and the oracle's cells up to float32 ties.  K odd, d not a multiple of 16, a ragged batch."""
+    """A batch takes the same cells, in the same order, as the same queries sent a few at a time (here both by the
+    few-queries distance kernel; the tiled one, which sums in the same order, below), and the oracle's cells up to
+    float32 ties.  K odd, d not a multiple of 16, a ragged batch."""
     import torch
     m = 8
     coarse, cb, x, index = build_ivf(O, n=20_000, K=K, d=d, m=m, seed=K)
@@ -485,3 +485,9 @@ def test_cells_do_not_depend_on_the_batch(Q, O, K, d, nq):
     for iq in list(range(0, nq, max(1, nq // 7))) + [nq - 1]:
         _, _, one, _ = Q.qadc_ivf_search(gix, queries[iq:iq + 1].contiguous(), nprobe, 5, 50, debug=True)
         assert torch.equal(probes[iq], one[0]), iq
+
+
+@pytest.mark.parametrize("K,d,nq", [(9001, 32, 500), (32_767, 24, 129)])
+def test_cells_of_an_odd_number_do_not_depend_on_the_batch(Q, O, K, d, nq):
+    """The tiled distance kernel over an odd number of cells: rows of distances that start off an 8-byte boundary."""
+    test_cells_do_not_depend_on_the_batch(Q, O, K, d, nq)

@@ -312,3 +312,9 @@ def test_probes_do_not_depend_on_the_batch(Q, K, dh, nq):
     got = Q.qadc_multi_index_probes(halves, queries, 48)
     for iq in list(range(0, nq, max(1, nq // 9))) + [nq - 1]:
         assert torch.equal(got[iq:iq + 1], Q.qadc_multi_index_probes(halves, queries[iq:iq + 1].contiguous(), 48)), iq
+
+
+@pytest.mark.parametrize("K,dh,nq", [(4097, 64, 700), (16_383, 16, 300)])
+def test_probes_of_an_odd_number_of_centroids_do_not_depend_on_the_batch(Q, K, dh, nq):
+    """The tiled distance kernel over both halves: the second half's distances start off an 8-byte boundary."""
+    test_probes_do_not_depend_on_the_batch(Q, K, dh, nq)

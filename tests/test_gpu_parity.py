@@ -516,8 +516,9 @@ def test_search_large_init_and_other_code_sizes(Q, O):
 
 @pytest.mark.parametrize("m", [8, 16, 32, 64])
 def test_scan_topk_query_batches_share_code_reads(Q, O, m):
-    """Batches of >= 8 queries on a long database go through the query-tiled kernel (8 queries per
-    workgroup); queries whose bound is useless (all sums tie) fall back to the single-query kernel."""
+    """Batches on a long database: m = 8 by the query-tiled byte-lane kernel (8 queries per workgroup), m = 32 and 64 by
+    the matrix-core kernel, m = 16 query by query (a longer database below); queries whose bound is useless (all sums tie)
+    fall back to the single-query kernel."""
     rng = np.random.default_rng(m)
     n, R, nq = 500_009, 100, 21
     codes = rng.integers(0, 256, size=(n, m // 2), dtype=np.uint8)
@@ -566,8 +567,8 @@ def test_scan_topk_query_groups_by_bound(Q, O, m):
 @pytest.mark.parametrize("m", [8, 16, 32, 64])
 @pytest.mark.parametrize("nq,R,nbins", [(130, 100, 255), (97, 1000, 127), (256, 10, 255), (40, 100, 255)])
 def test_scan_topk_large_batches_on_the_matrix_cores(Q, O, m, nq, R, nbins):
-    """Batches of 4-bit codes from 16 queries up (32 for the shortest codes) are scanned as one-hot matrix
-    products, 32 or 64 queries per wavefront: full and partial sets of queries, a ragged database
+    """Batches of 4-bit codes are scanned as one-hot matrix products once (queries - 4) x bytes of the database reach
+    90 MB (from 32 queries for the shortest codes), 32, 64 or 128 queries per wavefront: full and partial sets of queries, a ragged database
     tail, tables that tie heavily, saturate, exceed nbins or are all zero (those queries overflow
     their lists and are redone one by one).  Indices and sums equal the plain-C scan bit for bit."""
     from oracle import cref
@@ -664,8 +665,8 @@ def test_scan_topk_batch_with_tables_at_a_4_byte_offset(Q, O):
 
 
 def test_search_batch_config1_shaped(Q, O):
-    """qadc_search on a batch of 16 mixture queries over a long database (fused prepare kernel +
-    query-tiled scan) against the oracle's replay of the integer part and its own tables."""
+    """qadc_search on a batch of 16 mixture queries over a long database (tables and quantizer kernels, sample, scan
+    query by query) against the oracle's replay of the integer part and its own tables."""
     import torch
     c = config1()
     n = 800_000
@@ -764,7 +765,7 @@ def test_float_scan_of_4bit_codes_in_query_batches(Q, O, m, n, nq):
 # ------------------------------------------------------------------ which kernel scans a batch of 4-bit codes
 
 @pytest.mark.parametrize("m,nq,n", [
-    (64, 64, 65_600), (64, 47, 65_600),          # just above / below what the matrix-core kernel takes
+    (64, 64, 65_600), (64, 47, 65_600),          # above and just above what the matrix-core kernel takes
     (32, 40, 160_001), (32, 39, 160_001),
     (16, 45, 270_000), (16, 47, 270_000),
     (64, 5, 2_900_003), (64, 4, 2_900_003),      # a handful of queries over many codes
@@ -955,3 +956,59 @@ def test_misaligned_tables_are_not_scanned_in_short_chunks(Q, monkeypatch, m, n,
         us.append(gpu_us(lambda: Q.qadc_scan_topk(Q.QADC_U8_4BIT, codes, tables, 100, workspace=ws), reps=50))
     monkeypatch.delenv("QADC_TILED_MFMA")
     assert us[0] < 1.3 * us[1], us
+
+
+# the lines themselves: (queries - 4) x bytes of 90 MB on either side; 120 MB of 8- and 16-byte codes for the batches that
+# the byte-lane kernels keep
+@pytest.mark.parametrize("m,nq,n,mfma", [(64, 46, 65_600, False), (64, 47, 65_600, True), (16, 46, 270_000, True),
+                                         (16, 45, 270_000, False), (16, 12, 15_000_100, False), (32, 8, 7_500_100, False),
+                                         (32, 8, 7_499_900, True), (32, 9, 7_500_100, True)])
+def test_batches_at_the_dispatch_lines(Q, m, nq, n, mfma):
+    """Which kernels run, by their number of launches (matrix cores and redo: 2; byte lanes of two widths and redo: 3; query
+    by query: 1), and what they return."""
+    from oracle import cref
+    rng = np.random.default_rng(m * nq)
+    codes = rng.integers(0, 256, size=(n, m // 2), dtype=np.uint8)
+    qluts = rng.integers(0, 510 // m + 2, size=(nq, m, 16)).astype(np.uint8)
+    Q.qadc_profile_enable(True)
+    idx, dist = Q.qadc_scan_topk(Q.QADC_U8_4BIT, to_gpu(codes), to_gpu(qluts), 50)
+    _, launches = Q.qadc_profile_read(Q.QADC_PROF_SCAN)
+    Q.qadc_profile_enable(False)
+    assert launches == (2 if mfma else 1 if n * m // 2 < 100e6 else 3), launches
+    some = [0, nq // 2, nq - 1]
+    wi, wd = cref.scan_topk_u8(codes, qluts[some], 50, 255)
+    assert np.array_equal(idx_np(idx)[some], wi) and np.array_equal(dist.cpu().numpy()[some], wd)
+
+
+@pytest.mark.parametrize("nq,n", [(21, 700_009), (8, 3_000_017)])
+def test_queries_of_64_bit_codes_that_overflow_their_lists(Q, nq, n):
+    """m = 16 on the matrix-core kernel: useless bounds, heavy ties and saturation, redone query by query."""
+    rng = np.random.default_rng(nq)
+    m, R = 16, 100
+    codes = rng.integers(0, 256, size=(n, m // 2), dtype=np.uint8)
+    codes[::5] = codes[3]
+    qluts = rng.integers(0, 1 + 255 // m, size=(nq, m, 16)).astype(np.uint8)
+    qluts[4] = 0
+    qluts[5] = rng.integers(0, 2, size=(m, 16))
+    qluts[6] = 255
+    qluts[7, :, :8] = 0
+    gi, gd = gpu_topk(Q, to_gpu(codes), qluts, R)
+    for iq in range(nq):
+        wi, wd = oracle_topk(codes, qluts[iq], R)
+        assert np.array_equal(gi[iq], wi) and np.array_equal(gd[iq], wd), iq
+
+
+def test_search_of_a_batch_on_the_query_tiled_path(Q, O):
+    """qadc_search of 16 queries over a database long enough for the matrix-core kernel, against the library's own tables."""
+    import torch
+    c = config1()
+    n = 1_000_003
+    rng = np.random.default_rng(4)
+    codes = np.tile(c["codes"], (-(-n // len(c["codes"])), 1))[:n].copy()
+    codes[100_000:] ^= rng.integers(0, 256, size=codes[100_000:].shape, dtype=np.uint8) & 0x33
+    ql_out = torch.empty((16, 16, 16), dtype=torch.uint8, device="cuda:0")
+    si, sd = Q.qadc_search(to_gpu(c["codebooks"]), to_gpu(c["queries"]), to_gpu(codes), 100, 200, qluts_out=ql_out)
+    h_ql = ql_out.cpu().numpy()
+    for iq in range(16):
+        wi, wd = oracle_topk(codes, h_ql[iq], 100)
+        assert np.array_equal(idx_np(si)[iq], wi) and np.array_equal(sd[iq].cpu().numpy(), wd)
