@@ -199,6 +199,19 @@ MFMA_I8_PEAK_TOPS = 5000.0      # dense int8 MFMA peak of the chip
 ALU_PEAK_TLOOKUPS = 157.3  # 256 CUs x 64 lanes x 2.4 GHz x 4 byte lanes per 32-bit lane-op
 
 
+def batch_scan_kernel(n, m, nb):
+    """The kernel that scans a batch of nb queries over n 4-bit codes (tables on a 16-byte boundary)."""
+    size = n * (m // 2)
+    min_q = os.environ.get("QADC_MFMA_MIN_Q")
+    allowed = os.environ.get("QADC_TILED_MFMA", "1") != "0" and (min_q is None or nb >= int(min_q))
+    if m == 8 or not allowed or min_q is not None:
+        matrix = allowed and (min_q is not None or nb >= 32)
+        return "scan_u8_mfma_kernel" if matrix else "scan_u8_tiled16_kernel" if nb >= 8 else "scan_u8_kernel"
+    if size > 120e6 and ((m == 16 and 8 <= nb < 16) or (m == 32 and nb == 8)):
+        return "scan_u8_tiled16_kernel"
+    return "scan_u8_mfma_kernel" if nb >= 2 and (nb - 4) * size >= 90e6 else "scan_u8_kernel"
+
+
 def run_batched(args):
     """Config 3: batches of queries over 128-bit codes; a step = one batch through qadc_search."""
     import numpy as np
@@ -251,8 +264,8 @@ def run_batched(args):
         ms_merge, _ = Q.qadc_profile_read(Q.QADC_PROF_MERGE)
         Q.qadc_profile_enable(False)
         ach = n * nb * m / (ms_scan * 1e-3) / 1e12
-        on_matrix_cores = nb >= (16 if m >= 16 else 32) and os.environ.get("QADC_TILED_MFMA", "1") != "0"
-        if on_matrix_cores:
+        kernel = batch_scan_kernel(n, m, nb)
+        if kernel == "scan_u8_mfma_kernel":
             # The method's work is m lookup-adds per (code, query) pair (Alg. 2); the ceiling quoted for
             # it is the vector ALU's byte-lane rate, whatever unit executes it.  This kernel forms the
             # sums as one-hot int8 products on the sparse matrix instruction: every lookup-add is a
@@ -271,7 +284,8 @@ def run_batched(args):
                         "traffic_source": "profiles/hbm_traffic_configs_3_4_5.md (rocprofv3 --pmc FETCH_SIZE, bytes read per launch)",
                         "scan_ms": round(ms_scan, 3), "launches_timed": launches}
         else:
-            roofline = {"bound": "alu", "kernel": "scan_u8_tiled16_kernel (+ 16-bit-lane and redo launches)", "achieved": round(ach, 2),
+            roofline = {"bound": "alu", "achieved": round(ach, 2),
+                        "kernel": kernel + (" (+ 16-bit-lane and redo launches)" if "tiled" in kernel else ""),
                         "peak": ALU_PEAK_TLOOKUPS, "unit": "T lookup-adds/s", "frac": round(ach / ALU_PEAK_TLOOKUPS, 4),
                         "traffic": TILED_TRAFFIC if (n, m, nb) == (100_000_000, 32, 256) else None,
                         "traffic_source": "profiles/hbm_traffic_configs_3_4_5.md (rocprofv3 --pmc FETCH_SIZE, bytes read per launch)",
