@@ -1549,13 +1549,18 @@ int ivf_shared_scan(int, const int64_t *, const uint8_t *, int64_t, int, const i
 // lengths of the lists, which only the GPU knows, and where a few lists hold most of the codes a query-by-query scan
 // reads them once per query (5e7 codes in 65536 lists of Zipf(2) lengths, 8 probes: 384 queries 12.2 against 1.7 ms,
 // 4096 queries 127 against 13; Zipf(1.2), 2e7 codes, 4096 queries 9.6 against 2.5) -- while over even lists that few
-// queries share it costs at most a fifth (multi-index of 1e8 codes, 512 queries 404 against 462 us; 5e7 in 65536,
-// 400 queries x 64 544 against 679).  From 64 queries when an average list has 14 pairs, so that sharing gains whatever
-// the lengths are; us per call per-query / shared: 1e6 codes in 256 lists, 150 queries x 24 (14 pairs) 179 / 163, 70 x 24
-// (6.6) 174 / 181; 2e6 in 256, 150 x 64 (37) 328 / 230; 4e6 in 1000, 200 x 64 (12.8) 309 / 324.
+// queries share it costs at most a quarter (multi-index of 1e8 codes, 512 queries 404 against 462 us; 5e7 in 65536,
+// 400 queries x 64 544 against 679).  From 64 queries where an average list has 18 pairs and the queries meet 5e7 codes,
+// or 1e7 in lists enough to spread: of 744 batches of 64 to 383 queries over 16 to 2000 lists (20 k to 8 M codes, even and
+// Zipf(0.8) lengths, 7 to 48 pairs per list) none that the rule takes was slower than query by query, the best took 0.37
+// of the time.  With 1e7 codes in few lists too 8 were, by up to 34 % (1e6 codes in 16 lists, 64 queries x 5 229 against
+// 172 us, though 40 pairs gain 27 %), from 14 pairs 28 by up to 39 % (8e6 in 256, 120 x 30 288 against 210), from 14
+// pairs without a line for the codes 154 by up to 61 % (2e4 in 64, 220 x 6 116 against 72: the launches alone take 35).
 static bool shared_lists_pay(const qadc_ivf_index *ix, int nq, int nprobe)
 {
-    return nq >= IVF_SHARED_MIN_Q || (nq >= 64 && (double)nq * nprobe >= 14.0 * (double)ix->K);
+    if (nq >= IVF_SHARED_MIN_Q) return true;
+    const double pairs = (double)nq * nprobe / (double)ix->K, met = pairs * (double)ix->n;
+    return nq >= 64 && pairs >= 18.0 && met >= (ix->K >= 128 ? 1e7 : 5e7);
 }
 
 // small: the plan for a workspace that the best one does not fit (batches of 64 to 383 queries scan query by query).

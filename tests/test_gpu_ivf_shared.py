@@ -280,9 +280,31 @@ def test_route_of_a_skewed_index(Q, monkeypatch):
 def test_search_with_the_smallest_workspace(Q, nq, nprobe, R):
     """A workspace that does not hold the shared-list plan of a middle-sized batch: the same result, query by query."""
     import torch
-    gix, coarse, rnd = skewed_index(Q, 400_000, 100, 16, 50_000, 9)
-    gq = (coarse[torch.arange(nq, device="cuda") % 100] + 18 * rnd(nq, 64)).contiguous()
+    gix, coarse, rnd = skewed_index(Q, 400_000, 128, 16, 50_000, 9)
+    gq = (coarse[torch.arange(nq, device="cuda") % 128] + 18 * rnd(nq, 64)).contiguous()
     want = Q.qadc_ivf_search(gix, gq, nprobe, R, 300)
     least, got = smallest_workspace(Q, lambda ws: Q.qadc_ivf_search(gix, gq, nprobe, R, 300, workspace=ws))
     assert least <= Q.qadc_ivf_workspace_bytes(gix, nq, nprobe, R)
     assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1])
+
+
+@pytest.mark.parametrize("n,K,nq,nprobe", [(20_000, 64, 220, 6), (20_000, 16, 64, 4), (200_000, 64, 120, 11), (1_000_000, 256, 220, 47),
+                                           (8_000_000, 256, 120, 24), (8_000_000, 256, 383, 27), (8_000_000, 1000, 220, 182)])
+def test_route_of_middle_sized_batches(Q, monkeypatch, n, K, nq, nprobe):
+    """64 to 383 queries: the route taken is not slower by more than a fifth than query by query."""
+    import torch
+    gix, coarse, rnd = skewed_index(Q, n, K, 16, 3 * n // K, n + K)
+    home = torch.randint(0, K, (nq,), device="cuda")
+    gq = (coarse[home] + 18 * rnd(nq, 64)).contiguous()
+    us, ref = [], None
+    for route in (None, "0", "1"):
+        if route:
+            monkeypatch.setenv("QADC_IVF_SHARED", route)
+        ws = Q.qadc_workspace_init(torch.empty((Q.qadc_ivf_workspace_bytes(gix, nq, nprobe, 100),), dtype=torch.uint8, device="cuda"))
+        f = lambda: Q.qadc_ivf_search(gix, gq, nprobe, 100, 200, workspace=ws)
+        out = f()
+        ref = ref or out
+        assert torch.equal(out[0], ref[0]) and torch.equal(out[1], ref[1])
+        us.append(gpu_us(f, reps=30))
+    monkeypatch.delenv("QADC_IVF_SHARED")
+    assert us[0] < 1.2 * us[1], us
