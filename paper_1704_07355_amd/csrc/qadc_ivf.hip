@@ -1550,17 +1550,18 @@ int ivf_shared_scan(int, const int64_t *, const uint8_t *, int64_t, int, const i
 // reads them once per query (5e7 codes in 65536 lists of Zipf(2) lengths, 8 probes: 384 queries 12.2 against 1.7 ms,
 // 4096 queries 127 against 13; Zipf(1.2), 2e7 codes, 4096 queries 9.6 against 2.5) -- while over even lists that few
 // queries share it costs at most a quarter (multi-index of 1e8 codes, 512 queries 404 against 462 us; 5e7 in 65536,
-// 400 queries x 64 544 against 679).  From 64 queries where an average list has 18 pairs and the queries meet 5e7 codes,
-// or 1e7 in lists enough to spread: of 744 batches of 64 to 383 queries over 16 to 2000 lists (20 k to 8 M codes, even and
-// Zipf(0.8) lengths, 7 to 48 pairs per list) none that the rule takes was slower than query by query, the best took 0.37
-// of the time.  With 1e7 codes in few lists too 8 were, by up to 34 % (1e6 codes in 16 lists, 64 queries x 5 229 against
-// 172 us, though 40 pairs gain 27 %), from 14 pairs 28 by up to 39 % (8e6 in 256, 120 x 30 288 against 210), from 14
-// pairs without a line for the codes 154 by up to 61 % (2e4 in 64, 220 x 6 116 against 72: the launches alone take 35).
+// 400 queries x 64 544 against 679).  From 64 queries where an average list has 18 pairs and the queries meet
+// 2.4e9 components of codes: over 2564 batches of 64 to 383 queries (16 to 2000 lists, 20 k to 8 M codes of 16 to 64
+// components, even and Zipf(0.8) lengths, 7 to 48 pairs per list) the 106 that the rule takes need 0.70 of the time on
+// average, the best 0.37 (8e6 codes in 16 lists, 383 queries x 2, 740 against 274 us), the worst 1.08.  Of the 1190 with 18
+// pairs and fewer components 373 would be slower by 3 % and more, up to 1.6 times (2e4 codes in 64 lists, 220 queries x 6 72
+// against 116: the launches alone take 35; 2.5e6 of 32 in 128, 64 x 36 191 against 260) -- over skewed lists most of them gain,
+// over even ones most lose, and the host does not know the lengths.
 static bool shared_lists_pay(const qadc_ivf_index *ix, int nq, int nprobe)
 {
     if (nq >= IVF_SHARED_MIN_Q) return true;
-    const double pairs = (double)nq * nprobe / (double)ix->K, met = pairs * (double)ix->n;
-    return nq >= 64 && pairs >= 18.0 && met >= (ix->K >= 128 ? 1e7 : 5e7);
+    const double pairs = (double)nq * nprobe / (double)ix->K;
+    return nq >= 64 && pairs >= 18.0 && pairs * (double)ix->n * (double)ix->m >= 2.4e9;
 }
 
 // small: the plan for a workspace that the best one does not fit (batches of 64 to 383 queries scan query by query).

@@ -276,11 +276,11 @@ def test_route_of_a_skewed_index(Q, monkeypatch):
     assert own < 1.5 * min(forced), (own, forced)
 
 
-@pytest.mark.parametrize("nq,nprobe,R", [(150, 24, 100), (400, 8, 100), (70, 64, 10), (30, 8, 100)])
+@pytest.mark.parametrize("nq,nprobe,R", [(150, 40, 100), (400, 8, 100), (70, 80, 10), (30, 8, 100)])
 def test_search_with_the_smallest_workspace(Q, nq, nprobe, R):
     """A workspace that does not hold the shared-list plan of a middle-sized batch: the same result, query by query."""
     import torch
-    gix, coarse, rnd = skewed_index(Q, 400_000, 128, 16, 50_000, 9)
+    gix, coarse, rnd = skewed_index(Q, 2_000_000, 128, 32, 200_000, 9)
     gq = (coarse[torch.arange(nq, device="cuda") % 128] + 18 * rnd(nq, 64)).contiguous()
     want = Q.qadc_ivf_search(gix, gq, nprobe, R, 300)
     least, got = smallest_workspace(Q, lambda ws: Q.qadc_ivf_search(gix, gq, nprobe, R, 300, workspace=ws))
@@ -289,7 +289,8 @@ def test_search_with_the_smallest_workspace(Q, nq, nprobe, R):
 
 
 @pytest.mark.parametrize("n,K,nq,nprobe", [(20_000, 64, 220, 6), (20_000, 16, 64, 4), (200_000, 64, 120, 11), (1_000_000, 256, 220, 47),
-                                           (8_000_000, 256, 120, 24), (8_000_000, 256, 383, 27), (8_000_000, 1000, 220, 182)])
+                                           (1_000_000, 512, 250, 37), (2_500_000, 128, 64, 36), (8_000_000, 256, 120, 30),
+                                           (8_000_000, 64, 383, 7), (8_000_000, 1000, 220, 182)])
 def test_route_of_middle_sized_batches(Q, monkeypatch, n, K, nq, nprobe):
     """64 to 383 queries: the route taken is not slower by more than a fifth than query by query."""
     import torch
