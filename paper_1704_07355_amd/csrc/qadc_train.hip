@@ -63,114 +63,177 @@ static void launch_train_assign(const float *train, int64_t n, int d, int m, con
 #undef QADC_ASG
 }
 
-// Means of the sub-vectors of one centroid: workgroup (i, j, block of TRAIN_TD dimensions).  The
-// row-order float64 sum of a component is one chain of additions, so what a workgroup can do is keep
-// everything else out of that chain: its eight wavefronts read TRAIN_SEG labels at a time, a column of
-// the label matrix, and leave the numbers of the centroid's rows in LDS in row order (ballots and running
-// counts, no atomics); they then fetch the rows' components a stage at a time, all loads of a stage in
-// flight together, and while the next stage is fetched the first wavefront adds the stage before it, a
-// lane per component, from LDS.  Bound by the chain of float64 additions over the centroid's rows.
-// 20,000 rows, m = 16, 16 centroids, 8 dimensions: 4000 us (one thread per component walking all rows:
-// 32 wavefronts, a dependent label load per row) -> 46 us.
-constexpr int TRAIN_NT = 512;
-constexpr int TRAIN_WAVES = TRAIN_NT / WAVE;
-constexpr int TRAIN_PER = 16;                            // labels per lane and round
-constexpr int TRAIN_SEG = TRAIN_NT * TRAIN_PER;          // labels per round
-constexpr int TRAIN_TD = 64;                             // components per workgroup, at most: a lane each
-constexpr int TRAIN_STAGE = 4096;                        // values per stage, already float64: the adding lane has nothing to convert
+// Means of the sub-vectors of one centroid: workgroup (i, j, block of TRAIN_TD dimensions).  The mean is defined by the
+// float64 sum in row order, one chain of additions per component; a chain per component is what this kernel was bound by
+// (44 us per iteration for 20,000 rows, m = 16, 16 centroids, 8 dimensions).  The sum is taken in many chains instead, a
+// lane per (row slot, component), together with the sum of the absolute values: `cnt` additions in a row are off by at
+// most cnt 2^-53 times that, these by what the longest of their chains adds, and unless the float32 rounding of the mean
+// changes within this margin it is the row-order one.  Where it does (about one mean in 10^5 of a thousand rows), or is not a
+// number, the workgroup walks its rows again in row order.
+// The labels, a column of the label matrix, are read in rounds, and the numbers of the centroid's rows are left in LDS in
+// row order (ballots and running counts, no atomics).  Bound by round trips: labels, then rows eight loads at a time.
+// 44 -> 11.6 us per iteration where no mean is in doubt; 1 M rows, where one iteration in three has one, 2.4 -> 0.5 ms per
+// iteration with the assignment; learning sets of NaN, all rows in order, a tenth slower than before.
+constexpr int TRAIN_TD = 64;                             // components per workgroup, at most
+constexpr int TRAIN_FL = 8;                              // loads in flight per thread
+constexpr unsigned TRAIN_FEW = 128;                      // rows that are added in order right away
+constexpr int TRAIN_STAGE = 4096;                        // components fetched at a time for the sum in row order
 
-__global__ __launch_bounds__(TRAIN_NT) void train_update_kernel(
+// Leaves the numbers (relative to `base`) of the rows base .. base + NT * PER - 1 with label i in `rows`, in row order;
+// returns how many.  Every thread of the workgroup calls it; ends with a barrier.
+template <int NT, int PER>
+__device__ __forceinline__ unsigned train_rows(const uint8_t *__restrict__ col, int64_t base, int64_t n, unsigned i,
+                                               uint16_t *rows, unsigned *wcount)
+{
+    const int lane = threadIdx.x & (WAVE - 1), wave = threadIdx.x / WAVE;
+    // wavefront w looks at labels base + w * 64 * PER + k * 64 + lane, k = 0 .. PER - 1
+    const int64_t first = base + (int64_t)wave * (WAVE * PER) + lane;
+    unsigned lab[PER];
+#pragma unroll
+    for (int k = 0; k < PER; ++k) lab[k] = (first + k * WAVE < n) ? col[first + k * WAVE] : 0xffffu;
+    unsigned mine = 0;
+#pragma unroll
+    for (int k = 0; k < PER; ++k) mine += (unsigned)__popcll(__ballot(lab[k] == i));
+    if (lane == 0) wcount[wave] = mine;
+    __syncthreads();
+    unsigned at = 0, found = 0;
+#pragma unroll
+    for (int w = 0; w < NT / WAVE; ++w) {
+        const unsigned c = wcount[w];
+        if (w < wave) at += c;
+        found += c;
+    }
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+        const bool own = lab[k] == i;
+        const unsigned long long mask = __ballot(own);
+        if (own) rows[at + rank_in_mask(mask)] = (uint16_t)(first + k * WAVE - base);
+        at += (unsigned)__popcll(mask);
+    }
+    __syncthreads();
+    return found;
+}
+
+// NT threads, PER labels per lane and round.
+template <int NT, int PER>
+__global__ __launch_bounds__(NT) void train_update_kernel(
     const float *__restrict__ train, int64_t n, int d, int m, int ksub, const uint8_t *__restrict__ labels,
     float *__restrict__ cb)
 {
-    __shared__ uint16_t rows[TRAIN_SEG];                 // the centroid's rows of the round, in row order
-    __shared__ double stage[2][TRAIN_STAGE];
-    __shared__ unsigned wcount[TRAIN_WAVES];
-    const int tid = threadIdx.x, lane = tid & (WAVE - 1), wave = tid / WAVE;
+    constexpr int SEG = NT * PER;                        // labels per round
+    __shared__ uint16_t rows[SEG];                 // the centroid's rows of the round, in row order
+    __shared__ union {
+        double2 part[NT];                          // (sum, sum of absolute values) of a slot and component
+        float stage[2][TRAIN_STAGE];
+    } sh;
+    __shared__ unsigned wcount[NT / WAVE];
+    double2 *part = sh.part;
+    const int tid = threadIdx.x;
     const int dsub = d / m;
-    const int i = (int)(blockIdx.x % (unsigned)ksub), jt = (int)(blockIdx.x / (unsigned)ksub);
+    // workgroups that read neighbouring components are on one XCD, whose L2 then holds what they share of a row's lines
+    const unsigned xcd = gridDim.x / 8, wg = xcd * 8 == gridDim.x ? (blockIdx.x % 8) * xcd + blockIdx.x / 8 : blockIdx.x;
+    const int i = (int)(wg % (unsigned)ksub), jt = (int)(wg / (unsigned)ksub);
     const int blocks_t = (dsub + TRAIN_TD - 1) / TRAIN_TD;
     const int j = jt / blocks_t, t0 = (jt - j * blocks_t) * TRAIN_TD;
     const int td = min(TRAIN_TD, dsub - t0);
-    const int per_stage = TRAIN_STAGE / td;              // rows per stage
     const uint8_t *col = labels + (size_t)j * n;
     const float *src = train + (size_t)j * dsub + t0;
+    float *out = cb + ((size_t)j * ksub + i) * dsub + t0;
     double sum = 0.0;
     int64_t cnt = 0;
-    for (int64_t base = 0; base < n; base += TRAIN_SEG) {
-        // wavefront w looks at labels base + w * 1024 + k * 64 + lane, k = 0 .. 15
-        const int64_t first = base + (int64_t)wave * (WAVE * TRAIN_PER) + lane;
-        unsigned lab[TRAIN_PER];
+    if (n > SEG || (cnt = train_rows<NT, PER>(col, 0, n, (unsigned)i, rows, wcount)) > TRAIN_FEW) {  // uniform
+        double mag = 0.0;
+        const int slots = NT / td;                 // rows side by side
+        const int slot = tid / td, t = tid - slot * td;
+        for (int64_t base = 0; base < n; base += SEG) {
+            const unsigned found = n <= SEG ? (unsigned)cnt : train_rows<NT, PER>(col, base, n, (unsigned)i, rows, wcount);
+            if (n > SEG) cnt += found;
+            if (slot < slots) {
+                for (unsigned r0 = (unsigned)slot; r0 < found; r0 += TRAIN_FL * (unsigned)slots) {
+                    float v[TRAIN_FL];
 #pragma unroll
-        for (int k = 0; k < TRAIN_PER; ++k) lab[k] = (first + k * WAVE < n) ? col[first + k * WAVE] : 0xffffu;
-        unsigned mine = 0;
-#pragma unroll
-        for (int k = 0; k < TRAIN_PER; ++k) mine += (unsigned)__popcll(__ballot(lab[k] == (unsigned)i));
-        if (lane == 0) wcount[wave] = mine;
-        __syncthreads();
-        unsigned at = 0, found = 0;
-#pragma unroll
-        for (int w = 0; w < TRAIN_WAVES; ++w) {
-            const unsigned c = wcount[w];
-            if (w < wave) at += c;
-            found += c;
-        }
-#pragma unroll
-        for (int k = 0; k < TRAIN_PER; ++k) {
-            const bool own = lab[k] == (unsigned)i;
-            const unsigned long long mask = __ballot(own);
-            if (own) rows[at + rank_in_mask(mask)] = (uint16_t)(first + k * WAVE - base);
-            at += (unsigned)__popcll(mask);
-        }
-        __syncthreads();
-        cnt += found;
-        // stage s is fetched while stage s - 1 is added
-        const int stages = ((int)found + per_stage - 1) / per_stage;
-        for (int s = 0; s <= stages; ++s) {              // uniform
-            if (s < stages) {
-                const int r0 = s * per_stage;
-                const int elems = min(per_stage, (int)found - r0) * td;
-                double *to = stage[s & 1];
-                constexpr int FL = 8;                    // loads in flight per thread
-                for (int e0 = tid; e0 < elems; e0 += FL * TRAIN_NT) {
-                    float v[FL];
-#pragma unroll
-                    for (int u = 0; u < FL; ++u) {
-                        const int e = min(e0 + u * TRAIN_NT, elems - 1);
-                        const int r = e / td, t = e - r * td;
-                        v[u] = src[(base + rows[r0 + r]) * d + t];
+                    for (int u = 0; u < TRAIN_FL; ++u) {
+                        const unsigned r = r0 + u * (unsigned)slots;
+                        v[u] = src[(base + rows[min(r, found - 1)]) * d + t];
                     }
 #pragma unroll
-                    for (int u = 0; u < FL; ++u)
-                        if (e0 + u * TRAIN_NT < elems) to[e0 + u * TRAIN_NT] = (double)v[u];
+                    for (int u = 0; u < TRAIN_FL; ++u) {
+                        const double x = r0 + u * (unsigned)slots < found ? (double)v[u] : 0.0;
+                        sum += x;
+                        mag += fabs(x);
+                    }
+                }
+            }
+            __syncthreads();                             // `rows` and `wcount` are written again in the next round
+        }
+        part[tid] = make_double2(sum, mag);
+        __syncthreads();
+        // halves of the slots, then halves of those
+        for (int have = slots; have > 1;) {              // uniform
+            const int half = (have + 1) / 2;
+            if (slot < have - half) {
+                const double2 o = part[tid + half * td];
+                part[tid] = make_double2(part[tid].x + o.x, part[tid].y + o.y);
+            }
+            __syncthreads();
+            have = half;
+        }
+        bool sure = true;
+        float mean = 0.0f;
+        if (tid < td) {
+            const double s = part[tid].x, c = (double)cnt;
+            // row order: cnt additions; here: cnt / slots + 1 and at most 11 of the tree.  (1.01: the rounding of this line
+            // and of the two divisions below is far under a hundredth of it)
+            const double eps = part[tid].y * (c + (c / slots + 16.0)) * (1.01 * 0x1p-53);
+            mean = (float)(s / c);
+            sure = __float_as_uint((float)((s - eps) / c)) == __float_as_uint((float)((s + eps) / c)) &&
+                   __builtin_isfinite(mean);
+        }
+        if (cnt == 0) return;                            // uniform
+        if (!__syncthreads_or(!sure)) {                  // uniform; (a barrier: the parts have been read)
+            if (tid < td) out[tid] = mean;
+            return;
+        }
+        sum = 0.0;
+    }
+    // The definition: a stage of rows is fetched by all while the one before is added in order, a thread per component.
+    const int per_stage = TRAIN_STAGE / td;              // rows
+    for (int64_t base = 0; base < n; base += SEG) {
+        const int found = n <= SEG ? (int)cnt      // `rows` still holds them
+                                         : (int)train_rows<NT, PER>(col, base, n, (unsigned)i, rows, wcount);
+        const int stages = (found + per_stage - 1) / per_stage;
+        for (int s = 0; s <= stages; ++s) {              // uniform
+            if (s < stages) {
+                const int r0 = s * per_stage, elems = min(per_stage, found - r0) * td;
+                for (int e0 = tid; e0 < elems; e0 += 4 * NT) {
+                    float v[4];
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) {
+                        const int e = min(e0 + u * NT, elems - 1), r = e / td;
+                        v[u] = src[(base + rows[r0 + r]) * d + (e - r * td)];
+                    }
+#pragma unroll
+                    for (int u = 0; u < 4; ++u)
+                        if (e0 + u * NT < elems) sh.stage[s & 1][e0 + u * NT] = v[u];
                 }
             }
             if (s > 0 && tid < td) {
-                const double *from = stage[(s - 1) & 1] + tid;
-                const int have = min(per_stage, (int)found - (s - 1) * per_stage);
+                const float *from = sh.stage[(s - 1) & 1] + tid;
+                const int have = min(per_stage, found - (s - 1) * per_stage);
                 int r = 0;
-                if (have >= 16) {  // the next sixteen rows are read from LDS while sixteen are added
-                    double v[16];
+                for (; r + 16 <= have; r += 16) {
+                    float v[16];
 #pragma unroll
-                    for (int u = 0; u < 16; ++u) v[u] = from[u * td];
-                    for (r = 16; r + 16 <= have; r += 16) {
-                        double nx[16];
+                    for (int u = 0; u < 16; ++u) v[u] = from[(r + u) * td];
 #pragma unroll
-                        for (int u = 0; u < 16; ++u) nx[u] = from[(r + u) * td];
-#pragma unroll
-                        for (int u = 0; u < 16; ++u) sum += v[u];
-#pragma unroll
-                        for (int u = 0; u < 16; ++u) v[u] = nx[u];
-                    }
-#pragma unroll
-                    for (int u = 0; u < 16; ++u) sum += v[u];
+                    for (int u = 0; u < 16; ++u) sum += (double)v[u];
                 }
-                for (; r < have; ++r) sum += from[r * td];
+                for (; r < have; ++r) sum += (double)from[r * td];
             }
             __syncthreads();
         }
     }
-    if (tid < td && cnt) cb[((size_t)j * ksub + i) * dsub + t0 + tid] = (float)(sum / (double)cnt);
+    if (cnt > 0 && tid < td) out[tid] = (float)(sum / (double)cnt);
 }
 
 int pq_train(const float *train, int64_t n, int d, int m, int ksub, const int64_t *init_rows, int iters,
@@ -190,9 +253,14 @@ int pq_train(const float *train, int64_t n, int d, int m, int ksub, const int64_
         if (ksub == 16) launch_train_assign<16>(train, n, d, m, codebooks, labels, st);
         else if (ksub == 64) launch_train_assign<64>(train, n, d, m, codebooks, labels, st);
         else launch_train_assign<256>(train, n, d, m, codebooks, labels, st);
-        hipLaunchKernelGGL(train_update_kernel,
-                           dim3((unsigned)(ksub * m * ceil_div(d / m, TRAIN_TD))), dim3(TRAIN_NT), 0, st, train, n, d,
-                           m, ksub, labels, codebooks);
+        const dim3 grid((unsigned)(ksub * m * ceil_div(d / m, TRAIN_TD)));
+        // (a few hundred rows: the launch counts, 11.9 us per iteration with 1024 threads, 11.2 with 512; 20,000 rows 19 and 22)
+        if (n <= 4096)
+            hipLaunchKernelGGL((train_update_kernel<512, 8>), grid, dim3(512), 0, st, train, n, d, m, ksub, labels,
+                               codebooks);
+        else
+            hipLaunchKernelGGL((train_update_kernel<1024, 20>), grid, dim3(1024), 0, st, train, n, d, m, ksub, labels,
+                               codebooks);
     }
     QADC_HIP_TRY(hipGetLastError());
     return QADC_OK;

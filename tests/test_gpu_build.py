@@ -295,6 +295,28 @@ def test_pq_train_means_are_row_order_float64_sums(Q, O, n, d, m, ksub):
     assert np.array_equal(got, want)
 
 
+@pytest.mark.parametrize("n,d", [(2, 1), (4_096, 4), (4_097, 4), (20_479, 3), (20_480, 64), (20_481, 65), (40_961, 5)])
+def test_pq_train_means_where_the_order_of_the_sum_decides(Q, n, d):
+    """All rows with the first centroid (repeated starting rows, ties to the lowest index) and components whose float64
+    sum depends on the order of the additions, a mean half way between two float32, infinities and NaN: still the
+    row-order sum, bit for bit.  Sizes around the two forms of the kernel
+    (4096), a round of labels (20,480) and a workgroup's 64 components."""
+    rng = np.random.default_rng(n)
+    x = (rng.normal(size=(n, d)) * 10.0 ** rng.uniform(-12, 12, size=(n, d))).astype(np.float32)
+    x[:, 0] = 1.0
+    x[::2, 0] = np.float32(1.0) + np.float32(2.0 ** -23)    # n even: the mean is 1 + 2^-24
+    if d > 4:
+        x[5, 1], x[6, 2], x[7, 2], x[9, 3] = np.inf, np.inf, -np.inf, np.nan
+        x[:, 4] = -0.0
+    rows = np.zeros(16, dtype=np.int64)
+    got = Q.qadc_pq_train(to_gpu(x), 1, 16, to_gpu(rows), 1).cpu().numpy()
+    with np.errstate(all="ignore"):
+        want = (np.cumsum(np.vstack([np.zeros((1, d)), x.astype(np.float64)]), axis=0)[-1] / n).astype(np.float32)
+    assert np.array_equal(got[0, 0], want, equal_nan=True)
+    assert np.array_equal(np.signbit(got[0, 0]), np.signbit(want)) or np.isnan(want).any()
+    assert np.array_equal(got[0, 1:], np.broadcast_to(x[0], (15, d)))
+
+
 def _codes_by_definition(x, cb):
     """enc(x) from float64 distances summed in increasing component order, ties to the lowest index; u8 [n][m]."""
     m, k, dsub = cb.shape
