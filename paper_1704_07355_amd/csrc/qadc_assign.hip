@@ -4,31 +4,34 @@
 //
 // assign_filter_kernel (d <= 256) finds that cell without forming all n x K float64 distances.  With x' and
 // c' the differences to a reference vector, |x - c|^2 = |x'|^2 + |c'|^2 - 2 x'.c', and the part that depends
-// on the cell is a matrix product: both factors are split into two bfloat16 numbers (16 significant bits)
-// and hi.hi + hi.lo + lo.hi is summed in float32 by the matrix units.  A lane keeps, per vector, the three
+// on the cell is a matrix product: both factors are rounded to binary16 (11 significant bits; scaled by a power of two to
+// the middle of its range) and the products summed in float32 by the matrix units.  A lane keeps, per vector, the four
 // smallest of its group minima (a group: the 16 cells of a result tile that lie in one lane).  Whatever the
 // rounding, the closest cell lies in a group whose minimum is within a margin (bound below) of the smallest;
 // those groups -- mostly one -- are measured in float32 and, cells that come within its rounding of each other, in
-// float64 by the definition.  A vector that may have more of them than a lane remembers (more than two equal
-// centroids, values beyond the float32 range, infinities, NaN) is marked, and assign_rest_kernel measures it
-// against all cells.  The result is the definition's, whatever the route.
+// float64 by the definition.  A vector that may have more of them than a lane remembers (many equal or very close
+// centroids), or that is out of binary16's reach, is marked, and assign_rest_kernel takes it through the same filter with
+// factors split into two bfloat16 numbers (16 bits, hi.hi + hi.lo + lo.hi), then measures what is still undecided (more than
+// three equal centroids in a lane, infinities, NaN) against all cells.  The result is the definition's, whatever the route.
 //
-// Bound: 3 x 2 n K d operations on the matrix units.  Measured for 1 M vectors, d = 128, K = 4096: 2.8 ms =
-// 1.1 PFLOP/s of bfloat16 products (the float64 kernel: 37.5 ms); 2.0 ms of it are products and group minima,
-// 0.4 splitting the centroids, which every workgroup does again -- so eight wavefronts share the tiles and hold
-// the operands of 64 vectors each for the whole walk, all but a few of them in registers (256 per lane; 10
-// spilled for d = 128; the form for d = 129 to 255 and other rows spills 46 and takes 2.5 ms for 262 k vectors, d = 200,
-// K = 4096: 17.2 in float64) -- and 0.5 the last step.
+// Bound: 2 n K d operations on the matrix units, the conversion of the centroids (every workgroup does it again, so eight
+// wavefronts share the tiles and hold the operands of 64 vectors each in registers for the whole walk) and the group minima
+// with it on the same issue slots: per 64 cells a wavefront takes 32 products of 32 cycles, 92 vector instructions of four
+// for the minima and 66 for the conversion.  1 M vectors, K = 4096: d = 128 1.49 ms = 0.7 PFLOP/s (2.81 with split factors
+// throughout, whose margins are a tenth; 37.5 in float64), d = 64 0.86 (1.44); 500 k, d = 256 2.2 (3.2); 200 k, d = 96,
+// K = 1000 0.15 (0.21).  Vectors and centroids of one Gaussian, where a few in a hundred vectors have rivals within the margin:
+// 1.73 (2.90).  96 vectors a wavefront instead of 64: 1.51 (18 registers spilled); the rounding of the centroids measured
+// as that of the vectors is, which halves the margin: 1.61.
 // A margin is a matter of the vector and of the closest cells: a far or NaN centroid costs the other cells
-// nothing (2.8 ms; with one margin for all, from the farthest centroid, 122).  Every centroid twice: 1.0 ms for 262 k
-// vectors (4.5 when every cell of a group was measured in float64, a lane per row).  Every centroid four times, all
-// vectors marked: 45 ms per 1 M (69 when the filter's own workgroups walked over the cells, a lane per row).
+// nothing.  Every centroid four times, all vectors marked: 37 ms per 1 M (42 before the tiles of float64 lost the bounds checks
+// of every load and half of the instructions of every comparison).
 //
 // assign_f64_kernel (d > 256: the vectors no longer fit the registers): a workgroup of 256 threads takes 128
 // vectors and walks over all cells 128 at a time; 16 components of both go through LDS as float64 per step,
 // every thread accumulates 8 x 8 distances and keeps, per vector, the best of the cells it has seen; the 16
 // threads of a vector compare their candidates at the end under the order (distance, cell).  Vector-ALU
-// bound: 2 float64 operations per (vector, cell, component), 54 % of the float64 vector peak.
+// bound: 2 float64 operations per (vector, cell, component), three fifths of the float64 vector peak.  (The loads of the next
+// step in registers meanwhile: 15 to 25 % slower, they spill.)
 
 #include "qadc_common.h"
 
@@ -44,9 +47,10 @@ constexpr int ASG_LD = ASG_TM + 2;  // row stride in doubles: keeps 16-byte alig
 struct AssignTile {
     __attribute__((aligned(16))) double xs[ASG_TK][ASG_LD];
     __attribute__((aligned(16))) double cs[ASG_TK][ASG_LD];
-    double cand_d[ASG_TM][16];
+    uint64_t cand_d[ASG_TM][16];
     int cand_c[ASG_TM][16];
 };
+constexpr uint64_t ASG_NONE = 0x7ff0000000000001ull;  // one above the bits of infinity
 
 // The cells of up to ASG_TM vectors, by a workgroup of 256 threads; row(k): the row of x that is vector k of the tile, -1
 // for none.
@@ -59,11 +63,17 @@ __device__ __forceinline__ void assign_tile(AssignTile &s, const float *__restri
 {
     const int tid = threadIdx.x;
     const int tx = tid & 15, ty = tid >> 4;
-    double best_d[8];
+    // the smallest distance so far as its bits, which order like the numbers (none is negative): a NaN is above the start,
+    // infinity below it
+    uint64_t best_d[8];
     int best_c[8];
-    int from[8];  // the rows this thread fetches from
+    const float *xr[8];  // the rows this thread fetches from, at its component (some row where there is no vector)
 #pragma unroll
-    for (int a = 0; a < 8; ++a) { best_d[a] = __builtin_inf(); best_c[a] = 0x7fffffff; from[a] = row(ty + 16 * a); }
+    for (int a = 0; a < 8; ++a) {
+        best_d[a] = ASG_NONE;
+        best_c[a] = 0x7fffffff;
+        xr[a] = x + max(row(ty + 16 * a), 0) * ldx + tx;
+    }
 
     for (int c0 = 0; c0 < K; c0 += ASG_TN) {
         double acc[8][8];
@@ -72,15 +82,21 @@ __device__ __forceinline__ void assign_tile(AssignTile &s, const float *__restri
 #pragma unroll
             for (int b = 0; b < 8; ++b) acc[a][b] = 0.0;
         for (int t0 = 0; t0 < d; t0 += ASG_TK) {
-            // 128 x 16 elements of x and of the centroids, eight of each per thread, zero beyond the edges
+            // 128 x 16 elements of x and of the centroids, eight of each per thread, zero beyond the last component
+            float xl[8], cl[8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) xl[e] = cl[e] = 0.0f;
+            if (t0 + tx < d) {
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {
+                    xl[e] = xr[e][t0];
+                    cl[e] = coarse[(size_t)min(c0 + ty + 16 * e, K - 1) * d + t0 + tx];
+                }
+            }
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
-                const int idx = tid + e * 256;
-                const int r = idx >> 4, col = idx & 15;
-                const int t = t0 + col;
-                const int c = c0 + r;
-                s.xs[col][r] = (from[e] >= 0 && t < d) ? (double)x[from[e] * ldx + t] : 0.0;
-                s.cs[col][r] = (c < K && t < d) ? (double)coarse[(size_t)c * d + t] : 0.0;
+                s.xs[tx][ty + 16 * e] = (double)xl[e];
+                s.cs[tx][ty + 16 * e] = (double)cl[e];
             }
             __syncthreads();
 #pragma unroll 4
@@ -106,17 +122,19 @@ __device__ __forceinline__ void assign_tile(AssignTile &s, const float *__restri
             }
             __syncthreads();
         }
-        // the smaller distance wins, the lower cell among equal distances
+        // the smaller distance wins, the lower cell among equal distances: a thread meets its cells in increasing order
 #pragma unroll
-        for (int a = 0; a < 8; ++a)
+        for (int b = 0; b < 8; ++b) {
+            const int c = c0 + 32 * (b >> 1) + 2 * tx + (b & 1);
+            const uint64_t beyond = c < K ? 0 : ~0ull;
 #pragma unroll
-            for (int b = 0; b < 8; ++b) {
-                const int c = c0 + 32 * (b >> 1) + 2 * tx + (b & 1);
-                if (c < K && (acc[a][b] < best_d[a] || (acc[a][b] == best_d[a] && c < best_c[a]))) {
-                    best_d[a] = acc[a][b];
-                    best_c[a] = c;
-                }
+            for (int a = 0; a < 8; ++a) {
+                const uint64_t dist = __builtin_bit_cast(uint64_t, acc[a][b]) | beyond;
+                const bool closer = dist < best_d[a];
+                best_d[a] = closer ? dist : best_d[a];
+                best_c[a] = closer ? c : best_c[a];
             }
+        }
     }
 #pragma unroll
     for (int a = 0; a < 8; ++a) {
@@ -125,10 +143,10 @@ __device__ __forceinline__ void assign_tile(AssignTile &s, const float *__restri
     }
     __syncthreads();
     if (tid < ASG_TM && row(tid) >= 0) {
-        double bd = s.cand_d[tid][0];
+        uint64_t bd = s.cand_d[tid][0];
         int bc = s.cand_c[tid][0];
         for (int k = 1; k < 16; ++k) {
-            const double dd = s.cand_d[tid][k];
+            const uint64_t dd = s.cand_d[tid][k];
             const int cc = s.cand_c[tid][k];
             if (dd < bd || (dd == bd && cc < bc)) { bd = dd; bc = cc; }
         }
@@ -146,8 +164,6 @@ __global__ __launch_bounds__(256) void assign_f64_kernel(const float *__restrict
                 [&](int k, int bc) { cells[i0 + k] = (accumulate ? cells[i0 + k] : 0) + bc * scale; });
 }
 
-// ------------------------------------------------------------------ what the filter leaves
-
 // A vector that the filter cannot decide is marked in `cells`: what the pass found there (0 without `accumulate`) with
 // bit 30 turned over.  No cell looks like that: cells are below 2^28 where they accumulate and below 2^30 otherwise (the
 // filter takes no more centroids), or, for a vector with a NaN, 0x7fffffff times the scale plus a cell.
@@ -160,29 +176,597 @@ __device__ __forceinline__ bool assign_marked(int cell, int K, int accumulate)
     return accumulate ? (unsigned)was < (1u << 28) || was == (int)(0x7fffffffu * (unsigned)K) : was == 0;
 }
 
-// Every workgroup looks for the marks of `range` vectors (a multiple of ASG_TM, up to ASG_RANGE) and measures those
-// vectors against all cells, by the definition: 128 at a time in tiles, or, of a few, four at a time and a lane per
+// ------------------------------------------------------------------ filter on the matrix units
+
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
+typedef unsigned bits16x8 __attribute__((ext_vector_type(4)));  // eight 16-bit numbers of either kind
+typedef float f32x8 __attribute__((ext_vector_type(8)));
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+
+constexpr int AF_MAX_D = 256;
+
+// hi + lo = v to 2^-18 relative
+__device__ __forceinline__ void split_bf16(const f32x8 v, bits16x8 *hi, bits16x8 *lo)
+{
+    const bf16x8 h = __builtin_convertvector(v, bf16x8);
+    *hi = __builtin_bit_cast(bits16x8, h);
+    *lo = __builtin_bit_cast(bits16x8, __builtin_convertvector(v - __builtin_convertvector(h, f32x8), bf16x8));
+}
+
+// eight consecutive components t .. t+7 of a row, zero at and beyond d
+template <bool VEC>
+__device__ __forceinline__ f32x8 load8(const float *row, int t, int d)
+{
+    f32x8 v;
+    if constexpr (VEC) {  // 16-byte aligned rows of whole steps
+        const float4 a = *reinterpret_cast<const float4 *>(row + t);
+        const float4 b = *reinterpret_cast<const float4 *>(row + t + 4);
+        v[0] = a.x; v[1] = a.y; v[2] = a.z; v[3] = a.w;
+        v[4] = b.x; v[5] = b.y; v[6] = b.z; v[7] = b.w;
+    } else {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) v[e] = t + e < d ? row[t + e] : 0.0f;
+    }
+    return v;
+}
+
+// How the factors of the products are held.
+//   Half: one binary16 number (11 significant bits) of the difference to the reference, scaled by a power of two.
+//   Split: two bfloat16 numbers (16 significant bits, the range of float32), three products per component.
+enum class Factors { Half, Split };
+
+// NT: threads.  KS: steps of 16 components (16 KS >= d).  NB: blocks of 32 vectors per wavefront.  VEC: 16 KS = d, and
+// the rows of x and of the centroids start on 16-byte boundaries.
+template <int NT, int KS, int NB, Factors F>
+struct FilterShape {
+    static constexpr int PS = KS <= 4 ? 4 : 8;     // threads that convert one centroid at a time
+    static constexpr int IT = (KS + PS - 1) / PS;  // steps of 16 components per thread
+    static constexpr int NW = NT / WAVE;
+    static constexpr int TC = NT / PS;             // cells per tile
+    static constexpr int CT = TC / 32;
+    static constexpr int TM = NW * NB * 32;        // vectors per workgroup
+    static constexpr int PARTS = F == Factors::Split ? 2 : 1;
+    static_assert(TC % 32 == 0 && KS <= PS * IT, "");
+};
+
+template <int NT, int KS, int NB, Factors F>
+struct FilterTile {
+    using S = FilterShape<NT, KS, NB, F>;
+    // A tile of centroids as the matrix instructions read them: step s, part (hi, lo), lane, 16 bytes
+    __attribute__((aligned(16))) bits16x8 tile[2][S::CT][KS][S::PARTS][WAVE];
+    __attribute__((aligned(16))) float nrm[2][S::TC];
+    __attribute__((aligned(16))) float ref[16 * KS];  // the reference, scaled
+    float cmax[S::NW];
+    float spread[S::NW];                              // largest distance of a component from the reference
+    int cand[S::TM][6];                               // groups to measure, -1: none; none after the first -1
+};
+
+// Vectors of scores below: Half is sure of scores up to HALF_FAR only, of vectors with |x'|^2 up to HALF_NEAR.
+constexpr float HALF_NEAR = 268435456.0f;   // 2^28
+constexpr float HALF_STRAY = 2147483648.0f; // 2^31: no component of a centroid below it leaves binary16
+constexpr float HALF_FAR = 5e8f;
+constexpr float HALF_CONV = 4400.0f;        // 2^12, and a sixteenth for what HALF_TINY pays for
+constexpr float HALF_TINY = 3e-4f;          // per component: conversions below the normal range of binary16, flushed or not
+
+// The cells of up to TM vectors by a workgroup; row(k): the row of x that is vector k, -1 for none.  store(row, cell) for a
+// vector that is decided, undecided(row) for one that is not.
+template <int NT, int KS, int NB, bool VEC, Factors F, typename Row, typename Store, typename Undecided>
+__device__ __forceinline__ void filter_tile(FilterTile<NT, KS, NB, F> &sh, const float *__restrict__ coarse, int K, int d,
+                                            const float *__restrict__ x, int64_t ldx, Row row_of, Store store,
+                                            Undecided undecided)
+{
+    using S = FilterShape<NT, KS, NB, F>;
+    constexpr int PS = S::PS, IT = S::IT, NW = S::NW, TC = S::TC, CT = S::CT, TM = S::TM;
+    constexpr bool HALF = F == Factors::Half;
+    constexpr int D = 16 * KS;
+    auto &tile = sh.tile;
+    auto &nrm = sh.nrm;
+    auto &ref = sh.ref;
+    auto &cand = sh.cand;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int col = lane & 31, half = lane >> 5;
+
+    // The reference: per component, the middle of eight centroids of the range.  (Any vector would do; one amid the
+    // centroids keeps the norms, and with them the margins, small, and a few stray or non-finite ones do not move this.)
+    float spread = 0.0f;
+    for (int t = tid; t < D; t += NT) {
+        float v[8];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) v[k] = t < d ? coarse[(size_t)((int64_t)k * K >> 3) * d + t] : 0.0f;
+#pragma unroll
+        for (int a = 0; a < 8; ++a)  // odd-even transposition sort (a NaN goes out at the first comparison)
+#pragma unroll
+            for (int b = a & 1; b + 1 < 8; b += 2) {
+                const float lo = fminf(v[b], v[b + 1]), hi = fmaxf(v[b], v[b + 1]);
+                v[b] = lo;
+                v[b + 1] = hi;
+            }
+        ref[t] = 0.5f * v[3] + 0.5f * v[4];
+        const float f = fmaxf(v[6] - ref[t], ref[t] - v[1]);  // how far the centroids are from it, but for one at either end
+        if (f < 3e38f) spread = fmaxf(spread, f);
+    }
+    if constexpr (HALF) {
+#pragma unroll
+        for (int m = 32; m >= 1; m >>= 1) spread = fmaxf(spread, __shfl_xor(spread, m));
+        if (lane == 0) sh.spread[wave] = spread;
+    }
+    __syncthreads();
+    float scale = 1.0f;
+    if constexpr (HALF) {
+        for (int k = 0; k < NW; ++k) spread = fmaxf(spread, sh.spread[k]);
+        if (spread == 0.0f) {  // uniform; those centroids are all the same: the workgroup's first vector then
+            const float *xr = x + (int64_t)row_of(0) * ldx;  // (there is a first one)
+            for (int t = lane; t < d; t += WAVE) {
+                const float f = fabsf(xr[t] - ref[t]);
+                if (f < 3e38f) spread = fmaxf(spread, f);
+            }
+#pragma unroll
+            for (int m = 32; m >= 1; m >>= 1) spread = fmaxf(spread, __shfl_xor(spread, m));
+        }
+        // the power of two that takes it to 16 .. 32: a thousandth of that still has eleven bits, two thousand times as much
+        // is still in range
+        const int e = (int)(__float_as_uint(spread) >> 23) - 127;  // (-127: nothing at all, or less than 2^-126)
+        scale = __uint_as_float((unsigned)(127 + min(100, 4 - e)) << 23);
+        __syncthreads();  // (nobody still reads the reference as it was)
+        for (int t = tid; t < D; t += NT) ref[t] *= scale;
+        __syncthreads();
+    }
+
+    // this wavefront's vectors: operand -2 x'; lane (col, half) holds components 16 s + 8 half ..
+    bits16x8 bh[NB][KS], bl[NB][HALF ? 1 : KS];
+    float xn[NB];   // |x'|^2
+    float xe2[NB];  // |x' - its operand / -2|^2
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb) {
+        const int64_t i = row_of((wave * NB + nb) * 32 + col);
+        const float *row = x + (i < 0 ? 0 : i) * ldx;
+        float s2 = 0.0f, e2 = 0.0f;
+#pragma unroll
+        for (int s = 0; s < KS; ++s) {
+            const int t = 16 * s + 8 * half;
+            f32x8 v = load8<VEC>(row, t, d);
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                if constexpr (HALF) v[e] = __builtin_fmaf(v[e], scale, -ref[t + e]);  // (zero beyond d)
+                else v[e] = v[e] - ref[t + e];
+                s2 = __builtin_fmaf(v[e], v[e], s2);
+            }
+            if constexpr (HALF) {
+                const f16x8 h = __builtin_convertvector(v, f16x8);
+                const f32x8 err = v - __builtin_convertvector(h, f32x8);
+#pragma unroll
+                for (int e = 0; e < 8; ++e) e2 = __builtin_fmaf(err[e], err[e], e2);
+                bh[nb][s] = __builtin_bit_cast(bits16x8, h * (_Float16)-2.0f);
+            } else {
+                split_bf16(v * -2.0f, &bh[nb][s], &bl[nb][s]);
+            }
+        }
+        xn[nb] = s2 + __shfl_xor(s2, 32);
+        xe2[nb] = e2 + __shfl_xor(e2, 32);
+    }
+
+    // Rounding of a score, whatever the unit: |score - (distance^2 - |x'|^2)| <= xerr + cerr, a part of the vector and one
+    // of the centroid.  The part of the centroid comes off its score from the start, so that a far centroid loosens its
+    // own score and no other's.
+    //   Split: both eps |.|^2: the differences 4 2^-24; what the splits and the missing lo.lo leave out 3.1 2^-18; 3 D + 1
+    //   additions of values up to 2 (|x'|^2 + |c'|^2) (3 D + 1) 2^-22 (2^-23 each: no assumption on how the matrix units
+    //   round); the norms (D + 8) 2^-24; 1.28e-5 + 7.8e-7 D in all.
+    //   Half: the conversions leave ex = |x' - x^| and ec = |c' - c^| <= 2^-11 |c'|; 2 |x^.c^ - x'.c'| <= 2 ex |c^| + 2 |x'| ec,
+    //   and with 2 a b <= w a^2 + b^2 / w that is 2^12 ex^2 + 2^-11 |x'|^2 of the vector (ex is measured, mostly 0.4 2^-11 |x'|)
+    //   and (2^-12 + 2^-11) |c'|^2 of the centroid (ec is not: that would be two fifths of the conversion's work).  Should the
+    //   units take what is below the normal range, 2^-14, for zero: (e + 2^-14 sqrt D)^2 <= 17/16 e^2 + 17 D 2^-28, which is
+    //   HALF_CONV and HALF_TINY and a sixteenth on ec^2.  With the differences, D + 1 additions and the norms (1e-6 + 3.0e-7 D
+    //   of the square) 4.9e-4 + 3.0e-7 D of the vector's and 7.7e-4 + 3.0e-7 D of the centroid's.
+    constexpr float eps = HALF ? 5.1e-4f + 3.3e-7f * D : 1.5e-5f + 9e-7f * D;
+    constexpr float eps_c = HALF ? 7.9e-4f + 3.3e-7f * D : eps;
+
+    // thread -> centroid and steps it converts: eight neighbouring lanes hold eight centroids (their
+    // 16-byte LDS writes are contiguous), a centroid's threads lie in one wavefront
+    const int crow = (tid & 7) + 8 * (tid / (8 * PS));
+    const int part = (tid >> 3) % PS;
+    f32x8 raw[IT][2];
+    auto fetch = [&](int c0) {
+        const float *row = coarse + (size_t)min(c0 + crow, K - 1) * d;
+#pragma unroll
+        for (int it = 0; it < IT; ++it)
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+                if (part + PS * it < KS) raw[it][h] = load8<VEC>(row, 16 * (part + PS * it) + 8 * h, d);
+    };
+    float cmax = 0.0f;  // largest |c'|^2
+    auto stash = [&](int c0, int buf) {
+        float s2 = 0.0f;
+        bits16x8 conv[IT][2];
+#pragma unroll
+        for (int it = 0; it < IT; ++it) {
+            const int s = part + PS * it;
+            if (s < KS) {
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    const float4 r0 = *reinterpret_cast<const float4 *>(&ref[16 * s + 8 * h]);
+                    const float4 r1 = *reinterpret_cast<const float4 *>(&ref[16 * s + 8 * h + 4]);
+                    const f32x8 rv = {r0.x, r0.y, r0.z, r0.w, r1.x, r1.y, r1.z, r1.w};
+                    f32x8 v = raw[it][h];
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) {
+                        if constexpr (HALF) v[e] = __builtin_fmaf(v[e], scale, -rv[e]);
+                        else v[e] = v[e] - rv[e];
+                        s2 = __builtin_fmaf(v[e], v[e], s2);
+                    }
+                    if constexpr (HALF) {
+                        const f16x8 c = __builtin_convertvector(v, f16x8);
+                        conv[it][h] = __builtin_bit_cast(bits16x8, c);
+                    } else {
+                        bits16x8 hi, lo;
+                        split_bf16(v, &hi, &lo);
+                        tile[buf][crow >> 5][s][0][h * 32 + (crow & 31)] = hi;
+                        tile[buf][crow >> 5][s][S::PARTS - 1][h * 32 + (crow & 31)] = lo;
+                    }
+                }
+            }
+        }
+#pragma unroll
+        for (int m = 8; m < 8 * PS; m <<= 1) s2 += __shfl_xor(s2, m);
+        const bool in = c0 + crow < K;
+        if (in) cmax = fmaxf(cmax, s2);  // (NaN: left out)
+        if constexpr (HALF) {
+            // A stray centroid, |c'|^2 > 2^31, may not fit binary16: its score is 0.29 |c'|^2, no more than |c'|^2 - 2 x'.c' of
+            // any vector with |x'| <= 2^14.  (One with a NaN: NaN, and no product makes one of the others.)
+            const bool stray = !(s2 <= HALF_STRAY);
+#pragma unroll
+            for (int it = 0; it < IT; ++it)
+                if (part + PS * it < KS)
+#pragma unroll
+                    for (int h = 0; h < 2; ++h)
+                        tile[buf][crow >> 5][part + PS * it][0][h * 32 + (crow & 31)] = stray ? bits16x8{} : conv[it][h];
+            const float own = stray ? 0.29f * s2 : __builtin_fmaf(-eps_c, s2, s2) - HALF_TINY * D;
+            if (part == 0) nrm[buf][crow] = in ? own : __builtin_inff();
+        } else {
+            if (part == 0) nrm[buf][crow] = in ? s2 * (1.0f - eps) : __builtin_inff();
+        }
+    };
+
+    float b1[NB], b2[NB], b3[NB], b4[NB];  // the four smallest group minima, ascending; the groups of the first three
+    int a1[NB], a2[NB], a3[NB];
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb) {
+        b1[nb] = b2[nb] = b3[nb] = b4[nb] = __builtin_inff();
+        a1[nb] = a2[nb] = a3[nb] = 0;
+    }
+    fetch(0);
+    stash(0, 0);
+    __syncthreads();
+    int buf = 0;
+    for (int c0 = 0; c0 < K; c0 += TC, buf ^= 1) {
+        if (c0 + TC < K) fetch(c0 + TC);  // uniform; travels while this tile is multiplied
+#pragma unroll
+        for (int ct = 0; ct < CT; ++ct) {
+            // result (cell 8 (r / 4) + 4 half + r % 4, vector col) starts at |c'|^2
+            f32x16 init;
+#pragma unroll
+            for (int g = 0; g < 4; ++g) {
+                const float4 v = *reinterpret_cast<const float4 *>(&nrm[buf][ct * 32 + 8 * g + 4 * half]);
+                init[4 * g] = v.x; init[4 * g + 1] = v.y; init[4 * g + 2] = v.z; init[4 * g + 3] = v.w;
+            }
+            f32x16 acc[NB];
+#pragma unroll
+            for (int nb = 0; nb < NB; ++nb) acc[nb] = init;
+            // (the operands of a step are requested two steps ahead)
+            bits16x8 a[3][S::PARTS];
+#pragma unroll
+            for (int s = 0; s < 2; ++s)
+#pragma unroll
+                for (int p = 0; p < S::PARTS; ++p) a[s][p] = tile[buf][ct][s][p][lane];
+#pragma unroll
+            for (int s = 0; s < KS; ++s) {
+                if (s + 2 < KS)
+#pragma unroll
+                    for (int p = 0; p < S::PARTS; ++p) a[(s + 2) % 3][p] = tile[buf][ct][s + 2][p][lane];
+                const bits16x8 ah = a[s % 3][0], al = a[s % 3][S::PARTS - 1];
+                __builtin_amdgcn_sched_barrier(0);  // (left to itself the compiler requests them where they are used)
+                if constexpr (HALF) {
+#pragma unroll
+                    for (int nb = 0; nb < NB; ++nb)
+                        acc[nb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, ah), __builtin_bit_cast(f16x8, bh[nb][s]), acc[nb], 0, 0, 0);
+                } else {
+                    auto bf = [](const bits16x8 &v) { return __builtin_bit_cast(bf16x8, v); };
+#pragma unroll
+                    for (int nb = 0; nb < NB; ++nb)
+                        acc[nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bf(ah), bf(bh[nb][s]), acc[nb], 0, 0, 0);
+#pragma unroll
+                    for (int nb = 0; nb < NB; ++nb)
+                        acc[nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bf(al), bf(bh[nb][s]), acc[nb], 0, 0, 0);
+#pragma unroll
+                    for (int nb = 0; nb < NB; ++nb)
+                        acc[nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bf(ah), bf(bl[nb][HALF ? 0 : s]), acc[nb], 0, 0, 0);
+                }
+            }
+            const int g = c0 / 32 + ct;
+#pragma unroll
+            for (int nb = 0; nb < NB; ++nb) {
+                float v = fminf(acc[nb][0], __builtin_inff());  // (not a NaN: the medians would take it for the smallest)
+#pragma unroll
+                for (int r = 1; r < 16; ++r) v = fminf(v, acc[nb][r]);
+                const bool l1 = v < b1[nb], l2 = v < b2[nb], l3 = v < b3[nb];
+                b4[nb] = __builtin_amdgcn_fmed3f(b3[nb], b4[nb], v);
+                b3[nb] = __builtin_amdgcn_fmed3f(b2[nb], b3[nb], v);
+                b2[nb] = __builtin_amdgcn_fmed3f(b1[nb], b2[nb], v);
+                b1[nb] = fminf(b1[nb], v);
+                const int third = l3 ? g : a3[nb], second = l2 ? g : a2[nb];
+                a3[nb] = l2 ? a2[nb] : third;
+                a2[nb] = l1 ? a1[nb] : second;
+                a1[nb] = l1 ? g : a1[nb];
+            }
+        }
+        if (c0 + TC < K) stash(c0 + TC, buf ^ 1);  // uniform; that buffer was read before the last barrier
+        __syncthreads();
+    }
+
+    // over all the centroids
+#pragma unroll
+    for (int m = 32; m >= 1; m >>= 1) cmax = fmaxf(cmax, __shfl_xor(cmax, m));
+    if (lane == 0) sh.cmax[wave] = cmax;
+    __syncthreads();
+    for (int k = 0; k < NW; ++k) cmax = fmaxf(cmax, sh.cmax[k]);
+
+    // With b1 the smallest score, reached by a cell c*: the closest cell's score is at most b1 + 2 xerr + 2 cerr(c*).
+    // |c*'|^2 is at most the largest of all cells, and |c*'| <= |x'| + |x' - c*'| with |x' - c*'|^2 <= b1 + |x'|^2 + what
+    // rounding adds: under a thousandth of |x'|^2 (Split); xerr + 2 cerr(c*) (Half), the latter at most 1.8e-3 |c*'|^2 + a
+    // constant, so that |c*'| is at most 1 / (1 - 0.043) of what it is without.  A centroid whose score overflows or is NaN (it
+    // loses every comparison) is not the closest to a vector that has one within 1e18 (Split) or within HALF_FAR (Half;
+    // nor has a stray one, with 0.29 2^31 at least, reached b1 then).
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb) {
+        const int v = (wave * NB + nb) * 32 + col;
+        const float low = fminf(b1[nb], __shfl_xor(b1[nb], 32));
+        float thr;
+        bool sure;  // (comparisons that a NaN fails)
+        if constexpr (HALF) {
+            const float tiny = HALF_TINY * D;
+            const float xerr = __builtin_fmaf(eps, xn[nb], __builtin_fmaf(HALF_CONV, xe2[nb], tiny));
+            const float far = 1.05f * (__builtin_sqrtf(xn[nb]) + __builtin_sqrtf(fmaxf(low + xn[nb] + xerr + 2.0f * tiny, 0.0f)));
+            const float cn = 1.01f * fminf(far * far, cmax);
+            thr = low + 2.001f * (xerr + __builtin_fmaf(eps_c, cn, tiny));
+            sure = xn[nb] < HALF_NEAR && low < HALF_FAR && b4[nb] > thr;
+        } else {
+            const float far = __builtin_sqrtf(xn[nb]) + __builtin_sqrtf(fmaxf(low + xn[nb], 0.0f) + 1e-3f * xn[nb]);
+            thr = low + __builtin_fmaf(2.0f * eps, xn[nb] + 1.01f * fminf(far * far, cmax), 1e-30f);
+            sure = xn[nb] < 1e36f && thr < 1e36f && b4[nb] > thr;
+        }
+        // this lane's groups in question, then those of the other half; the first entry is never empty
+        // unless the vector is left to the kernel after this one
+        const int g1 = b1[nb] <= thr ? 2 * a1[nb] + half : -1, g2 = b2[nb] <= thr ? 2 * a2[nb] + half : -1,
+                  g3 = b3[nb] <= thr ? 2 * a3[nb] + half : -1;
+        const int o1 = __shfl_xor(g1, 32), o2 = __shfl_xor(g2, 32), o3 = __shfl_xor(g3, 32);
+        const int other = __shfl_xor((int)sure, 32);  // (asked by all lanes: a lane that does not ask gives nothing)
+        const bool all = !(sure && other);
+        if (half == 0) {
+            // own groups first (they fill up in this order), the others' behind them
+            const int k = (g1 >= 0) + (g2 >= 0) + (g3 >= 0);
+            int c[6] = {g1, g2, g3, -1, -1, -1};
+#pragma unroll
+            for (int e = 0; e < 6; ++e) c[e] = e == k ? o1 : e == k + 1 ? o2 : e == k + 2 ? o3 : c[e];
+#pragma unroll
+            for (int e = 0; e < 6; ++e) cand[v][e] = all ? -2 : c[e];
+            if (all && row_of(v) >= 0) undecided(row_of(v));
+        }
+    }
+    __syncthreads();
+
+    // The groups in question, 16 lanes per vector: the 16 distances of a group in float32, the lanes side by side along
+    // the components (a lane per cell would read 64 different lines per load).  A cell that no other comes within the
+    // rounding of is the closest; else the cells that do are measured by the definition, a lane each.
+    const int r = tid & 15, team = (lane >> 4) * 16;
+    auto cell_of = [&](int g, int k) { return (g >> 1) * 32 + 8 * (k >> 2) + 4 * (g & 1) + (k & 3); };
+    for (int v = tid >> 4; v < TM; v += NT / 16) {
+        const int64_t i = row_of(v);
+        if (i < 0 || cand[v][0] < 0) continue;  // uniform over the 16 lanes
+        const float *xr = x + i * ldx;
+        float xv[KS];
+        constexpr int W = VEC && KS % 4 == 0 ? 4 : 1;  // components per load
+#pragma unroll
+        for (int e = 0; e < KS / W; ++e)
+#pragma unroll
+            for (int u = 0; u < W; ++u) {
+                const int t = W * (r + 16 * e) + u;
+                xv[W * e + u] = VEC || t < d ? xr[t] : 0.0f;
+            }
+        // distance to cell r of group g
+        auto measure = [&](int g) {
+            float part[16];
+#pragma unroll
+            for (int k = 0; k < 16; ++k) {
+                const float *cr = coarse + (size_t)min(cell_of(g, k), K - 1) * d;
+                float acc = 0.0f;
+#pragma unroll
+                for (int e = 0; e < KS / W; ++e) {
+                    float cv[W];
+                    if constexpr (W == 4) {
+                        const float4 f = *reinterpret_cast<const float4 *>(cr + 4 * (r + 16 * e));
+                        cv[0] = f.x; cv[1] = f.y; cv[2] = f.z; cv[3] = f.w;
+                    } else {
+                        const int t = r + 16 * e;
+                        cv[0] = VEC || t < d ? cr[t] : 0.0f;
+                    }
+#pragma unroll
+                    for (int u = 0; u < W; ++u) {
+                        const float df = xv[W * e + u] - cv[u];
+                        acc = __builtin_fmaf(df, df, acc);
+                    }
+                }
+                part[k] = acc;
+            }
+            // sums over the 16 lanes, halving the cells a lane is responsible for: lane r ends with cell r
+#pragma unroll
+            for (int w = 8; w >= 1; w >>= 1)
+#pragma unroll
+                for (int k = 0; k < w; ++k) {
+                    const bool up = r & w;
+                    const float keep = up ? part[k + w] : part[k], give = up ? part[k] : part[k + w];
+                    part[k] = keep + __shfl_xor(give, w);
+                }
+            return cell_of(g, r) < K && part[0] == part[0] ? part[0] : __builtin_inff();  // (a NaN is never the closest)
+        };
+        auto lowest = [&](float f) {
+#pragma unroll
+            for (int w = 8; w >= 1; w >>= 1) f = fminf(f, __shfl_xor(f, w));
+            return f;
+        };
+        // rounding of two sums of d squares (d / 16 + 4 additions, the differences, the squares): (d / 8 + 14) 2^-24,
+        // here at least 1.3 times that
+        auto slack = [&](float f) { return f + __builtin_fmaf(f, 2e-6f + 1e-7f * KS, 1e-33f); };
+        auto among = [&](bool near) { return __popcll((__ballot(near) >> team) & 0xffffull); };
+        const int g0 = cand[v][0];
+        float dist[6];
+        dist[0] = measure(g0);
+#pragma unroll
+        for (int q = 1; q < 6; ++q) dist[q] = __builtin_inff();
+        float close = slack(lowest(dist[0]));
+        int rivals = among(dist[0] <= close);
+        int bc = dist[0] <= close ? cell_of(g0, r) : 0x7fffffff;
+        if (cand[v][1] >= 0) {  // uniform over the 16 lanes
+            float least = dist[0];
+#pragma unroll 1
+            for (int q = 1; q < 6; ++q) {
+                const int g = cand[v][q];
+                if (g < 0) break;  // uniform over the 16 lanes
+                const float to = measure(g);
+                least = fminf(least, to);
+#pragma unroll
+                for (int p = 1; p < 6; ++p) dist[p] = p == q ? to : dist[p];
+            }
+            close = slack(lowest(least));
+            bc = 0x7fffffff;
+            rivals = 0;
+#pragma unroll
+            for (int q = 0; q < 6; ++q) {
+                const bool near = dist[q] <= close && cand[v][q] >= 0;
+                rivals += among(near);
+                if (near) bc = cell_of(cand[v][q], r);
+            }
+        }
+        if (rivals > 1) {  // uniform over the 16 lanes
+            double bd = __builtin_inf();
+            bc = 0x7fffffff;
+#pragma unroll 1
+            for (int q = 0; q < 6; ++q) {
+                const int g = cand[v][q];
+                float dq = dist[0];
+#pragma unroll
+                for (int p = 1; p < 6; ++p) dq = p == q ? dist[p] : dq;
+                const int c = cell_of(g, r);
+                if (g < 0 || !(dq <= close) || c >= K) continue;
+                const float *cr = coarse + (size_t)c * d;
+                double dd = 0.0;
+                auto add = [&](float a, float b) {
+                    const double df = (double)a - (double)b;
+                    dd = fma(df, df, dd);
+                };
+                if constexpr (VEC) {
+#pragma unroll 4
+                    for (int t = 0; t < d; t += 4) {
+                        const float4 a = *reinterpret_cast<const float4 *>(xr + t), b = *reinterpret_cast<const float4 *>(cr + t);
+                        add(a.x, b.x); add(a.y, b.y); add(a.z, b.z); add(a.w, b.w);
+                    }
+                } else {
+#pragma unroll 8
+                    for (int t = 0; t < d; ++t) add(xr[t], cr[t]);
+                }
+                if (dd < bd || (dd == bd && c < bc)) { bd = dd; bc = c; }
+            }
+#pragma unroll
+            for (int w = 8; w >= 1; w >>= 1) {
+                const double od = __shfl_xor(bd, w);
+                const int oc = __shfl_xor(bc, w);
+                if (od < bd || (od == bd && oc < bc)) { bd = od; bc = oc; }
+            }
+        } else {
+#pragma unroll
+            for (int w = 8; w >= 1; w >>= 1) bc = min(bc, __shfl_xor(bc, w));
+        }
+        if (r == 0) store(i, bc);
+    }
+}
+
+template <int NT, int KS, int NB, bool VEC>
+__global__ __launch_bounds__(NT, 2) void assign_filter_kernel(const float *__restrict__ coarse, int K, int d,
+                                                              const float *__restrict__ x, int64_t ldx, int64_t n,
+                                                              int32_t *__restrict__ cells, int scale, int accumulate)
+{
+    __shared__ FilterTile<NT, KS, NB, Factors::Half> sh;
+    const int64_t i0 = (int64_t)blockIdx.x * FilterShape<NT, KS, NB, Factors::Half>::TM;
+    filter_tile<NT, KS, NB, VEC, Factors::Half>(
+        sh, coarse, K, d, x + i0 * ldx, ldx, [&](int k) { return i0 + k < n ? k : -1; },
+        [&](int64_t k, int bc) { cells[i0 + k] = (accumulate ? cells[i0 + k] : 0) + bc * scale; },
+        [&](int64_t k) { cells[i0 + k] = (accumulate ? cells[i0 + k] : 0) ^ ASG_MARK; });
+}
+
+// ------------------------------------------------------------------ what the filter leaves
+
+// Every workgroup looks for the marks of `range` vectors (a multiple of ASG_TM, up to ASG_RANGE).  More than ASG_FEW of
+// them go through the filter again, with split factors, whose margins are a tenth -- until that decides less than a quarter of a
+// tile (centroids four times over: 2 ms of 46 wasted on 1 M vectors without this).  Those left it measures
+// against all cells, by the definition: 128 at a time in tiles, or, of a few, four at a time and a lane per
 // cell (a tile takes as long as five such rounds whatever it holds).  The filter's own last steps were slower at it, and
-// cost the filter its registers.  Ranges rather than single tiles, so that few marks fill few tiles; 512 workgroups.
+// cost the filter its registers.  Ranges rather than single tiles, so that few marks fill few tiles; about 1024 workgroups
+// (512 at a time: with as many ranges, 200 k vectors that are all marked left a quarter of the chip idle, 1.48 ms).
+// AGAIN, DEFINITION: which of the two this launch does (both, but for the 16-step form, which would spill 46 registers:
+// 60 against 48 ms for 500 k vectors of 256 components, all marked).
 constexpr int ASG_RANGE = 4096, ASG_FEW = 20;
 
+template <int KS, bool VEC, bool AGAIN, bool DEFINITION>
 __global__ __launch_bounds__(256) void assign_rest_kernel(const float *__restrict__ coarse, int K, int d,
                                                           const float *__restrict__ x, int64_t ldx, int64_t n, int range,
                                                           int32_t *__restrict__ cells, int scale, int accumulate)
 {
-    __shared__ AssignTile s;
+    using Again = FilterTile<256, KS, 1, Factors::Split>;
+    constexpr int TM = FilterShape<256, KS, 1, Factors::Split>::TM;
+    constexpr size_t BYTES = DEFINITION && (!AGAIN || sizeof(AssignTile) > sizeof(Again)) ? sizeof(AssignTile) : sizeof(Again);
+    __shared__ __attribute__((aligned(16))) char room[BYTES];  // for one of them at a time
+    AssignTile &s = *reinterpret_cast<AssignTile *>(room);
     __shared__ uint16_t todo[ASG_RANGE];
-    __shared__ int ntodo;
+    __shared__ int ntodo, nleft;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int64_t i0 = (int64_t)blockIdx.x * range;
-    if (tid == 0) ntodo = 0;
+    if (tid == 0) { ntodo = 0; nleft = 0; }
     __syncthreads();
     for (int k = tid; k < range; k += 256) {
         const bool found = i0 + k < n && assign_marked(cells[i0 + k], K, accumulate);
         if (found) todo[atomicAdd(&ntodo, 1)] = (uint16_t)k;
     }
     __syncthreads();
-    const int count = ntodo;
+    int count = ntodo;
+    if constexpr (AGAIN) {
+        if (count > ASG_FEW) {  // uniform
+            int behind = 0;  // undecided in the tiles so far
+            for (int k0 = 0; k0 < count; k0 += TM) {  // uniform
+                filter_tile<256, KS, 1, VEC, Factors::Split>(
+                    *reinterpret_cast<Again *>(room), coarse, K, d, x + i0 * ldx, ldx,
+                    [&](int k) { return k0 + k < count ? (int)todo[k0 + k] : -1; },
+                    [&](int64_t k, int bc) { cells[i0 + k] = (cells[i0 + k] ^ ASG_MARK) + bc * scale; },
+                    [&](int64_t) { atomicAdd(&nleft, 1); });
+                __syncthreads();
+                const int left = nleft;
+                if (4 * (left - behind) > 3 * min(TM, count - k0)) break;  // uniform
+                behind = left;
+                __syncthreads();
+            }
+            // the vectors still marked (a thread sees the cells it looks at as the workgroup has left them: behind a barrier)
+            __threadfence_block();
+            __syncthreads();
+            if (tid == 0) nleft = 0;
+            __syncthreads();
+            for (int c0 = 0; c0 < count; c0 += 256) {  // uniform; the list shrinks in place
+                const int k = c0 + tid < count ? todo[c0 + tid] : -1;
+                __syncthreads();
+                if (k >= 0 && assign_marked(cells[i0 + k], K, accumulate)) todo[atomicAdd(&nleft, 1)] = (uint16_t)k;
+                __syncthreads();
+            }
+            count = nleft;
+        }
+    }
+    if constexpr (!DEFINITION) return;
     auto store = [&](int k, int bc) { cells[i0 + k] = (cells[i0 + k] ^ ASG_MARK) + bc * scale; };
     const int few = d <= 4 ? ASG_RANGE : ASG_FEW;  // (a tile computes 16 components at least)
     int k0 = 0;
@@ -243,408 +827,37 @@ __global__ __launch_bounds__(256) void assign_rest_kernel(const float *__restric
     }
 }
 
-// ------------------------------------------------------------------ filter on the matrix units
-
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float f32x8 __attribute__((ext_vector_type(8)));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
-
-constexpr int AF_MAX_D = 256;
-
-// hi + lo = v to 2^-18 relative
-__device__ __forceinline__ void split_bf16(const f32x8 v, bf16x8 *hi, bf16x8 *lo)
-{
-    *hi = __builtin_convertvector(v, bf16x8);
-    *lo = __builtin_convertvector(v - __builtin_convertvector(*hi, f32x8), bf16x8);
-}
-
-// eight consecutive components t .. t+7 of a row, zero at and beyond d
-template <bool VEC>
-__device__ __forceinline__ f32x8 load8(const float *row, int t, int d)
-{
-    f32x8 v;
-    if constexpr (VEC) {  // 16-byte aligned rows of whole steps
-        const float4 a = *reinterpret_cast<const float4 *>(row + t);
-        const float4 b = *reinterpret_cast<const float4 *>(row + t + 4);
-        v[0] = a.x; v[1] = a.y; v[2] = a.z; v[3] = a.w;
-        v[4] = b.x; v[5] = b.y; v[6] = b.z; v[7] = b.w;
-    } else {
-#pragma unroll
-        for (int e = 0; e < 8; ++e) v[e] = t + e < d ? row[t + e] : 0.0f;
-    }
-    return v;
-}
-
-// NT: threads.  KS: steps of 16 components (16 KS >= d).  NB: blocks of 32 vectors per wavefront.  VEC: 16 KS = d, and
-// the rows of x and of the centroids start on 16-byte boundaries.
-template <int NT, int KS, int NB, bool VEC>
-__global__ __launch_bounds__(NT, 2) void assign_filter_kernel(const float *__restrict__ coarse, int K, int d,
-                                                                 const float *__restrict__ x, int64_t ldx,
-                                                                 int64_t n, int32_t *__restrict__ cells, int scale,
-                                                                 int accumulate)
-{
-    constexpr int PS = KS <= 4 ? 4 : 8;     // threads that split one centroid at a time
-    constexpr int IT = (KS + PS - 1) / PS;  // steps of 16 components per thread
-    constexpr int NW = NT / WAVE;
-    constexpr int TC = NT / PS;             // cells per tile
-    constexpr int CT = TC / 32;
-    constexpr int TM = NW * NB * 32;        // vectors per workgroup
-    static_assert(TC % 32 == 0 && KS <= PS * IT, "");
-    // A tile of centroids as the matrix instructions read them: step s, part (hi, lo), lane, 16 bytes
-    __shared__ __attribute__((aligned(16))) bf16x8 tile[2][CT][KS][2][WAVE];
-    __shared__ __attribute__((aligned(16))) float nrm[2][TC];
-    __shared__ __attribute__((aligned(16))) float ref[16 * KS];
-    __shared__ float cmax_s[NW];
-    __shared__ int cand[TM][4];     // groups to measure, -1: none
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int col = lane & 31, half = lane >> 5;
-    const int64_t i0 = (int64_t)blockIdx.x * TM;
-
-    // The reference: per component, the middle of eight centroids of the range.  (Any vector would do; one amid the
-    // centroids keeps the norms, and with them the margins, small, and a few stray or non-finite ones do not move this.)
-    for (int t = tid; t < 16 * KS; t += NT) {
-        float v[8];
-#pragma unroll
-        for (int k = 0; k < 8; ++k) v[k] = t < d ? coarse[(size_t)((int64_t)k * K >> 3) * d + t] : 0.0f;
-#pragma unroll
-        for (int a = 0; a < 8; ++a)  // odd-even transposition sort (a NaN goes out at the first comparison)
-#pragma unroll
-            for (int b = a & 1; b + 1 < 8; b += 2) {
-                const float lo = fminf(v[b], v[b + 1]), hi = fmaxf(v[b], v[b + 1]);
-                v[b] = lo;
-                v[b + 1] = hi;
-            }
-        ref[t] = 0.5f * v[3] + 0.5f * v[4];
-    }
-    __syncthreads();
-
-    // this wavefront's vectors: operand -2 x', split; lane (col, half) holds components 16 s + 8 half ..
-    bf16x8 bh[NB][KS], bl[NB][KS];
-    float xn[NB];  // |x'|^2
-#pragma unroll
-    for (int nb = 0; nb < NB; ++nb) {
-        const int64_t i = i0 + (wave * NB + nb) * 32 + col;
-        const float *row = x + (i < n ? i : 0) * ldx;
-        float s2 = 0.0f;
-#pragma unroll
-        for (int s = 0; s < KS; ++s) {
-            const int t = 16 * s + 8 * half;
-            f32x8 v = load8<VEC>(row, t, d);
-#pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                v[e] = v[e] - ref[t + e];  // (zero beyond d)
-                s2 = __builtin_fmaf(v[e], v[e], s2);
-                v[e] = v[e] * -2.0f;
-            }
-            split_bf16(v, &bh[nb][s], &bl[nb][s]);
-        }
-        xn[nb] = s2 + __shfl_xor(s2, 32);
-    }
-
-    // Rounding of a score, whatever the unit: |score - (distance^2 - |x'|^2)| <= eps (|x'|^2 + |c'|^2), with D = 16 KS:
-    // the differences 4 2^-24; what the splits and the missing lo.lo leave out 3.1 2^-18; 3 D + 1 additions of values
-    // up to 2 (|x'|^2 + |c'|^2) (3 D + 1) 2^-22 (2^-23 each: no assumption on how the matrix units round); the norms
-    // (D + 8) 2^-24; 1.28e-5 + 7.8e-7 D in all.  The part of the centroid comes off its score from the start, so that a
-    // far centroid loosens its own score and no other's.
-    constexpr float eps = 1.5e-5f + 9e-7f * (16 * KS);
-
-    // thread -> centroid and steps it splits: eight neighbouring lanes hold eight centroids (their
-    // 16-byte LDS writes are contiguous), a centroid's threads lie in one wavefront
-    const int crow = (tid & 7) + 8 * (tid / (8 * PS));
-    const int part = (tid >> 3) % PS;
-    f32x8 raw[IT][2];
-    auto fetch = [&](int c0) {
-        const float *row = coarse + (size_t)min(c0 + crow, K - 1) * d;
-#pragma unroll
-        for (int it = 0; it < IT; ++it)
-#pragma unroll
-            for (int h = 0; h < 2; ++h)
-                if (part + PS * it < KS) raw[it][h] = load8<VEC>(row, 16 * (part + PS * it) + 8 * h, d);
-    };
-    float cmax = 0.0f;
-    auto stash = [&](int c0, int buf) {
-        float s2 = 0.0f;
-#pragma unroll
-        for (int it = 0; it < IT; ++it) {
-            const int s = part + PS * it;
-            if (s < KS) {
-#pragma unroll
-                for (int h = 0; h < 2; ++h) {
-                    const float4 r0 = *reinterpret_cast<const float4 *>(&ref[16 * s + 8 * h]);
-                    const float4 r1 = *reinterpret_cast<const float4 *>(&ref[16 * s + 8 * h + 4]);
-                    f32x8 v = raw[it][h];
-                    v[0] -= r0.x; v[1] -= r0.y; v[2] -= r0.z; v[3] -= r0.w;
-                    v[4] -= r1.x; v[5] -= r1.y; v[6] -= r1.z; v[7] -= r1.w;
-#pragma unroll
-                    for (int e = 0; e < 8; ++e) s2 = __builtin_fmaf(v[e], v[e], s2);
-                    bf16x8 hi, lo;
-                    split_bf16(v, &hi, &lo);
-                    tile[buf][crow >> 5][s][0][h * 32 + (crow & 31)] = hi;
-                    tile[buf][crow >> 5][s][1][h * 32 + (crow & 31)] = lo;
-                }
-            }
-        }
-#pragma unroll
-        for (int m = 8; m < 8 * PS; m <<= 1) s2 += __shfl_xor(s2, m);
-        const bool in = c0 + crow < K;
-        if (in) cmax = fmaxf(cmax, s2);  // (NaN: left out)
-        if (part == 0) nrm[buf][crow] = in ? s2 * (1.0f - eps) : __builtin_inff();
-    };
-
-    float b1[NB], b2[NB], b3[NB];  // the three smallest group minima, ascending; the groups of the first two
-    int a1[NB], a2[NB];
-#pragma unroll
-    for (int nb = 0; nb < NB; ++nb) {
-        b1[nb] = b2[nb] = b3[nb] = __builtin_inff();
-        a1[nb] = a2[nb] = 0;
-    }
-    fetch(0);
-    stash(0, 0);
-    __syncthreads();
-    int buf = 0;
-    for (int c0 = 0; c0 < K; c0 += TC, buf ^= 1) {
-        if (c0 + TC < K) fetch(c0 + TC);  // uniform; travels while this tile is multiplied
-#pragma unroll
-        for (int ct = 0; ct < CT; ++ct) {
-            // result (cell 8 (r / 4) + 4 half + r % 4, vector col) starts at |c'|^2
-            f32x16 init;
-#pragma unroll
-            for (int g = 0; g < 4; ++g) {
-                const float4 v = *reinterpret_cast<const float4 *>(&nrm[buf][ct * 32 + 8 * g + 4 * half]);
-                init[4 * g] = v.x; init[4 * g + 1] = v.y; init[4 * g + 2] = v.z; init[4 * g + 3] = v.w;
-            }
-            f32x16 acc[NB];
-#pragma unroll
-            for (int nb = 0; nb < NB; ++nb) acc[nb] = init;
-            // (the operands of a step are requested two steps ahead)
-            bf16x8 a[3][2];
-#pragma unroll
-            for (int s = 0; s < 2; ++s) {
-                a[s][0] = tile[buf][ct][s][0][lane];
-                a[s][1] = tile[buf][ct][s][1][lane];
-            }
-#pragma unroll
-            for (int s = 0; s < KS; ++s) {
-                if (s + 2 < KS) {
-                    a[(s + 2) % 3][0] = tile[buf][ct][s + 2][0][lane];
-                    a[(s + 2) % 3][1] = tile[buf][ct][s + 2][1][lane];
-                }
-                const bf16x8 ah = a[s % 3][0], al = a[s % 3][1];
-                __builtin_amdgcn_sched_barrier(0);  // (left to itself the compiler requests them where they are used)
-#pragma unroll
-                for (int nb = 0; nb < NB; ++nb)
-                    acc[nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah, bh[nb][s], acc[nb], 0, 0, 0);
-#pragma unroll
-                for (int nb = 0; nb < NB; ++nb)
-                    acc[nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(al, bh[nb][s], acc[nb], 0, 0, 0);
-#pragma unroll
-                for (int nb = 0; nb < NB; ++nb)
-                    acc[nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah, bl[nb][s], acc[nb], 0, 0, 0);
-            }
-            const int g = c0 / 32 + ct;
-#pragma unroll
-            for (int nb = 0; nb < NB; ++nb) {
-                float v = fminf(acc[nb][0], acc[nb][1]);
-#pragma unroll
-                for (int r = 2; r < 16; ++r) v = fminf(v, acc[nb][r]);
-                const bool l1 = v < b1[nb], l2 = v < b2[nb];
-                b3[nb] = fminf(b3[nb], fmaxf(b2[nb], v));
-                b2[nb] = fminf(b2[nb], fmaxf(b1[nb], v));
-                b1[nb] = fminf(b1[nb], v);
-                const int second = l2 ? g : a2[nb];
-                a2[nb] = l1 ? a1[nb] : second;
-                a1[nb] = l1 ? g : a1[nb];
-            }
-        }
-        if (c0 + TC < K) stash(c0 + TC, buf ^ 1);  // uniform; that buffer was read before the last barrier
-        __syncthreads();
-    }
-
-    // largest |c'|^2
-#pragma unroll
-    for (int m = 32; m >= 1; m >>= 1) cmax = fmaxf(cmax, __shfl_xor(cmax, m));
-    if (lane == 0) cmax_s[wave] = cmax;
-    __syncthreads();
-    cmax = cmax_s[0];
-    for (int k = 1; k < NW; ++k) cmax = fmaxf(cmax, cmax_s[k]);
-
-    // With b1 the smallest score, reached by a cell c*: the closest cell's score is at most b1 + 2 eps (|x'|^2 + |c*'|^2).
-    // |c*'|^2 is at most the largest of all cells, and |c*'| <= |x'| + |x' - c*'| with |x' - c*'|^2 <= b1 + |x'|^2 + what
-    // rounding adds, under a thousandth of |x'|^2.  A centroid whose score overflows or is NaN (it loses every
-    // comparison) is not the closest to a vector that has one within 1e18.
-#pragma unroll
-    for (int nb = 0; nb < NB; ++nb) {
-        const int v = (wave * NB + nb) * 32 + col;
-        const float low = fminf(b1[nb], __shfl_xor(b1[nb], 32));
-        const float far = __builtin_sqrtf(xn[nb]) + __builtin_sqrtf(fmaxf(low + xn[nb], 0.0f) + 1e-3f * xn[nb]);
-        const float thr = low + __builtin_fmaf(2.0f * eps, xn[nb] + 1.01f * fminf(far * far, cmax), 1e-30f);
-        // (comparisons that a NaN fails)
-        const bool sure = xn[nb] < 1e36f && thr < 1e36f && b3[nb] > thr;
-        // this lane's groups in question, then those of the other half; the first entry is never empty
-        // unless the vector is left to the kernel after this one
-        const int g1 = b1[nb] <= thr ? 2 * a1[nb] + half : -1, g2 = b2[nb] <= thr ? 2 * a2[nb] + half : -1;
-        const int o1 = __shfl_xor(g1, 32), o2 = __shfl_xor(g2, 32);
-        const int other = __shfl_xor((int)sure, 32);  // (asked by all lanes: a lane that does not ask gives nothing)
-        const bool all = !(sure && other);
-        if (half == 0) {
-            cand[v][0] = all ? -2 : g1 >= 0 ? g1 : o1;
-            cand[v][1] = g1 >= 0 ? g2 : o2;
-            cand[v][2] = g1 >= 0 ? o1 : -1;
-            cand[v][3] = g1 >= 0 ? o2 : -1;
-            if (all && i0 + v < n) cells[i0 + v] = (accumulate ? cells[i0 + v] : 0) ^ ASG_MARK;
-        }
-    }
-    __syncthreads();
-
-    // The groups in question, 16 lanes per vector: the 16 distances of a group in float32, the lanes side by side along
-    // the components (a lane per cell would read 64 different lines per load).  A cell that no other comes within the
-    // rounding of is the closest; else the cells that do are measured by the definition, a lane each.
-    const int r = tid & 15, team = (lane >> 4) * 16;
-    auto cell_of = [&](int g, int k) { return (g >> 1) * 32 + 8 * (k >> 2) + 4 * (g & 1) + (k & 3); };
-    for (int v = tid >> 4; v < TM; v += NT / 16) {
-        const int64_t i = i0 + v;
-        if (i >= n || cand[v][0] < 0) continue;  // uniform over the 16 lanes
-        const float *xr = x + i * ldx;
-        float xv[KS];
-        constexpr int W = VEC && KS % 4 == 0 ? 4 : 1;  // components per load
-#pragma unroll
-        for (int e = 0; e < KS / W; ++e)
-#pragma unroll
-            for (int u = 0; u < W; ++u) {
-                const int t = W * (r + 16 * e) + u;
-                xv[W * e + u] = VEC || t < d ? xr[t] : 0.0f;
-            }
-        // distance to cell r of group g
-        auto measure = [&](int g) {
-            float part[16];
-#pragma unroll
-            for (int k = 0; k < 16; ++k) {
-                const float *cr = coarse + (size_t)min(cell_of(g, k), K - 1) * d;
-                float acc = 0.0f;
-#pragma unroll
-                for (int e = 0; e < KS / W; ++e) {
-                    float cv[W];
-                    if constexpr (W == 4) {
-                        const float4 f = *reinterpret_cast<const float4 *>(cr + 4 * (r + 16 * e));
-                        cv[0] = f.x; cv[1] = f.y; cv[2] = f.z; cv[3] = f.w;
-                    } else {
-                        const int t = r + 16 * e;
-                        cv[0] = VEC || t < d ? cr[t] : 0.0f;
-                    }
-#pragma unroll
-                    for (int u = 0; u < W; ++u) {
-                        const float df = xv[W * e + u] - cv[u];
-                        acc = __builtin_fmaf(df, df, acc);
-                    }
-                }
-                part[k] = acc;
-            }
-            // sums over the 16 lanes, halving the cells a lane is responsible for: lane r ends with cell r
-#pragma unroll
-            for (int w = 8; w >= 1; w >>= 1)
-#pragma unroll
-                for (int k = 0; k < w; ++k) {
-                    const bool up = r & w;
-                    const float keep = up ? part[k + w] : part[k], give = up ? part[k] : part[k + w];
-                    part[k] = keep + __shfl_xor(give, w);
-                }
-            return cell_of(g, r) < K && part[0] == part[0] ? part[0] : __builtin_inff();  // (a NaN is never the closest)
-        };
-        auto lowest = [&](float f) {
-#pragma unroll
-            for (int w = 8; w >= 1; w >>= 1) f = fminf(f, __shfl_xor(f, w));
-            return f;
-        };
-        // rounding of two sums of d squares (d / 16 + 4 additions, the differences, the squares): (d / 8 + 14) 2^-24,
-        // here at least 1.3 times that
-        auto slack = [&](float f) { return f + __builtin_fmaf(f, 2e-6f + 1e-7f * KS, 1e-33f); };
-        auto among = [&](bool near) { return __popcll((__ballot(near) >> team) & 0xffffull); };
-        const int g0 = cand[v][0];
-        const bool more = cand[v][1] >= 0 || cand[v][2] >= 0 || cand[v][3] >= 0;  // uniform over the 16 lanes
-        float dist[4] = {measure(g0), __builtin_inff(), __builtin_inff(), __builtin_inff()};
-        float close = slack(lowest(dist[0]));
-        int rivals = among(dist[0] <= close);
-        int bc = dist[0] <= close ? cell_of(g0, r) : 0x7fffffff;
-        if (more) {
-#pragma unroll 1
-            for (int q = 1; q < 4; ++q) {
-                const int g = cand[v][q];
-                if (g < 0) continue;  // uniform over the 16 lanes
-                const float to = measure(g);
-#pragma unroll
-                for (int p = 1; p < 4; ++p) dist[p] = p == q ? to : dist[p];
-            }
-            close = slack(lowest(fminf(fminf(dist[0], dist[1]), fminf(dist[2], dist[3]))));
-            bc = 0x7fffffff;
-            rivals = 0;
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const bool near = dist[q] <= close && cand[v][q] >= 0;
-                rivals += among(near);
-                if (near) bc = cell_of(cand[v][q], r);
-            }
-        }
-        if (rivals > 1) {  // uniform over the 16 lanes
-            double bd = __builtin_inf();
-            bc = 0x7fffffff;
-#pragma unroll 1
-            for (int q = 0; q < 4; ++q) {
-                const int g = cand[v][q];
-                const float dq = q == 0 ? dist[0] : q == 1 ? dist[1] : q == 2 ? dist[2] : dist[3];
-                const int c = cell_of(g, r);
-                if (g < 0 || !(dq <= close) || c >= K) continue;
-                const float *cr = coarse + (size_t)c * d;
-                double dd = 0.0;
-                auto add = [&](float a, float b) {
-                    const double df = (double)a - (double)b;
-                    dd = fma(df, df, dd);
-                };
-                if constexpr (VEC) {
-#pragma unroll 4
-                    for (int t = 0; t < d; t += 4) {
-                        const float4 a = *reinterpret_cast<const float4 *>(xr + t), b = *reinterpret_cast<const float4 *>(cr + t);
-                        add(a.x, b.x); add(a.y, b.y); add(a.z, b.z); add(a.w, b.w);
-                    }
-                } else {
-#pragma unroll 8
-                    for (int t = 0; t < d; ++t) add(xr[t], cr[t]);
-                }
-                if (dd < bd || (dd == bd && c < bc)) { bd = dd; bc = c; }
-            }
-#pragma unroll
-            for (int w = 8; w >= 1; w >>= 1) {
-                const double od = __shfl_xor(bd, w);
-                const int oc = __shfl_xor(bc, w);
-                if (od < bd || (od == bd && oc < bc)) { bd = od; bc = oc; }
-            }
-        } else {
-#pragma unroll
-            for (int w = 8; w >= 1; w >>= 1) bc = min(bc, __shfl_xor(bc, w));
-        }
-        if (r == 0) cells[i] = (accumulate ? cells[i] : 0) + bc * scale;
-    }
-}
-
 // ------------------------------------------------------------------ host
 
 template <int KS>
-static void launch_filter(const float *coarse, int K, int d, const float *x, int64_t ldx, int64_t n, int32_t *cells,
-                          int scale, int accumulate, hipStream_t st)
+static void launch_filter(const float *coarse, int K, int d, const float *x, int64_t ldx, int64_t n, int range,
+                          int32_t *cells, int scale, int accumulate, hipStream_t st)
 {
     const bool vec = d == 16 * KS && ldx % 4 == 0 && ((uintptr_t)coarse & 15) == 0 && ((uintptr_t)x & 15) == 0;
+    const dim3 grid((unsigned)ceil_div(n, 128)), ranges((unsigned)ceil_div(n, range));
+    bool wide = false;
     if constexpr (KS <= 8)
         if (vec && n >= 512 * 256) {  // 512 vectors per workgroup once that fills the chip; else 128
             hipLaunchKernelGGL((assign_filter_kernel<512, KS, 2, true>), dim3((unsigned)ceil_div(n, 512)), dim3(512), 0,
                                st, coarse, K, d, x, ldx, n, cells, scale, accumulate);
-            return;
+            wide = true;
         }
-    const dim3 grid((unsigned)ceil_div(n, 128));
-    if (vec)
+    if (!wide && vec)
         hipLaunchKernelGGL((assign_filter_kernel<256, KS, 1, true>), grid, dim3(256), 0, st, coarse, K, d, x, ldx, n,
                            cells, scale, accumulate);
-    else
+    else if (!wide)
         hipLaunchKernelGGL((assign_filter_kernel<256, KS, 1, false>), grid, dim3(256), 0, st, coarse, K, d, x, ldx, n,
                            cells, scale, accumulate);
+    constexpr bool ONE = KS <= 8;
+    if (vec)
+        hipLaunchKernelGGL((assign_rest_kernel<KS, true, true, ONE>), ranges, dim3(256), 0, st, coarse, K, d, x, ldx, n, range,
+                           cells, scale, accumulate);
+    else
+        hipLaunchKernelGGL((assign_rest_kernel<KS, false, true, ONE>), ranges, dim3(256), 0, st, coarse, K, d, x, ldx, n, range,
+                           cells, scale, accumulate);
+    if constexpr (!ONE)
+        hipLaunchKernelGGL((assign_rest_kernel<KS, false, false, true>), ranges, dim3(256), 0, st, coarse, K, d, x, ldx, n,
+                           range, cells, scale, accumulate);
 }
 
 // cells[i] = (accumulate ? cells[i] : 0) + scale * (closest of K centroids to the d components at x + i ldx)
@@ -652,24 +865,20 @@ static int assign_pass(const float *coarse, int K, int d, const float *x, int64_
                        int scale, int accumulate, hipStream_t st)
 {
     const bool filter = d <= AF_MAX_D && K <= ASG_MARK_MAX_K;
+    const int range = (int)std::min<int64_t>(ASG_RANGE, std::max<int64_t>(256, ceil_div(ceil_div(n, 1024), ASG_TM) * ASG_TM));
     if (!filter)
         hipLaunchKernelGGL(assign_f64_kernel, dim3((unsigned)ceil_div(n, ASG_TM)), dim3(256), 0, st, coarse, K, d, x,
                            ldx, n, cells, scale, accumulate);
     else if (d <= 32)
-        launch_filter<2>(coarse, K, d, x, ldx, n, cells, scale, accumulate, st);
+        launch_filter<2>(coarse, K, d, x, ldx, n, range, cells, scale, accumulate, st);
     else if (d <= 64)
-        launch_filter<4>(coarse, K, d, x, ldx, n, cells, scale, accumulate, st);
+        launch_filter<4>(coarse, K, d, x, ldx, n, range, cells, scale, accumulate, st);
     else if (d <= 96)
-        launch_filter<6>(coarse, K, d, x, ldx, n, cells, scale, accumulate, st);
+        launch_filter<6>(coarse, K, d, x, ldx, n, range, cells, scale, accumulate, st);
     else if (d <= 128)
-        launch_filter<8>(coarse, K, d, x, ldx, n, cells, scale, accumulate, st);
+        launch_filter<8>(coarse, K, d, x, ldx, n, range, cells, scale, accumulate, st);
     else
-        launch_filter<16>(coarse, K, d, x, ldx, n, cells, scale, accumulate, st);
-    if (filter) {
-        const int64_t range = std::min<int64_t>(ASG_RANGE, std::max<int64_t>(512, ceil_div(ceil_div(n, 512), ASG_TM) * ASG_TM));
-        hipLaunchKernelGGL(assign_rest_kernel, dim3((unsigned)ceil_div(n, range)), dim3(256), 0, st, coarse, K, d, x, ldx, n,
-                           (int)range, cells, scale, accumulate);
-    }
+        launch_filter<16>(coarse, K, d, x, ldx, n, range, cells, scale, accumulate, st);
     QADC_HIP_TRY(hipGetLastError());
     return QADC_OK;
 }

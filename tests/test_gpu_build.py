@@ -177,6 +177,37 @@ def test_ivf_assign_values_at_the_ends_of_float32(Q):
     assert np.array_equal(Q.qadc_ivf_assign(to_gpu(coarse), to_gpu(x)).cpu().numpy(), want)
 
 
+@pytest.mark.parametrize("d,K,n", [(16, 300, 4_097), (64, 260, 131_073), (100, 90, 700), (128, 257, 131_500), (250, 130, 600)])
+@pytest.mark.parametrize("kind", ["range", "clusters", "crowds", "same samples", "runs of NaN"])
+def test_ivf_assign_where_the_filter_must_give_up(Q, d, K, n, kind):
+    """What 11-bit factors cannot tell or hold is left to the routes behind them: vectors and centroids beyond their range
+    and below it, clusters far apart of cells close together, three to eight cells as close as each other, a scale guessed
+    from centroids that are all the same, 40 centroids of NaN in a row."""
+    rng = np.random.default_rng(d + K)
+    coarse, x = rng.normal(size=(K, d)), rng.normal(size=(n, d))
+    if kind == "range":
+        coarse[::7] *= 10.0 ** rng.uniform(-8, 8, size=(len(coarse[::7]), 1))
+        x[::5] *= 10.0 ** rng.uniform(-8, 8, size=(len(x[::5]), 1))
+    elif kind == "clusters":
+        far = 300.0 * rng.normal(size=(4, d))
+        coarse, x = coarse + far[rng.integers(0, 4, K)], x + far[rng.integers(0, 4, n)]
+    elif kind == "crowds":
+        copies = 3 + np.arange(K) % 6
+        coarse = np.repeat(coarse, copies, axis=0)[rng.permutation(K)]
+        coarse += 1e-6 * rng.integers(0, 2, size=coarse.shape)
+    elif kind == "same samples":
+        coarse[[k * K // 8 for k in range(8)]] = coarse[0]
+        coarse *= 1e-3
+    coarse, x = coarse.astype(np.float32), x.astype(np.float32)
+    keep = np.arange(K)
+    if kind == "runs of NaN":
+        coarse[20:60, d // 2] = np.nan
+        keep = np.flatnonzero(np.isfinite(coarse).all(1))
+    got = Q.qadc_ivf_assign(to_gpu(coarse), to_gpu(x)).cpu().numpy()
+    some = np.arange(n) if n < 5000 else np.concatenate([np.arange(0, n, 29), np.arange(n - 500, n)])   # (the host takes minutes for all)
+    assert np.array_equal(got[some], keep[_closest(x[some], coarse[keep])])
+
+
 def test_ivf_assign_unaligned_rows(Q):
     """Rows and centroids that start 4 bytes off a 16-byte boundary."""
     rng = np.random.default_rng(9)
