@@ -1012,16 +1012,21 @@ __global__ __launch_bounds__(IVF_SEED_NT) void ivf_seed_kernel(
 
 constexpr int IVF_MAP_NT = 1024;
 constexpr int IVF_MAP_MAXQ = 4096;   // queries per batch, at most
-constexpr unsigned IVF_NO_WG = 0xffffffffu;
+constexpr unsigned IVF_NO_WG = 0xffffffffu;  // (no entry of the map: units_per_wg is below 256)
+constexpr int IVF_MAX_UNITS = 255;
+constexpr unsigned long long IVF_FILL_WGS = 4096;
 
 // Workgroups of the scan: query q gets W_q = clamp(ceil(units_q / units_per_wg), 1, Wmax) of them
 // (work in proportion to the lists it probes); the queries with the most work come first in the
-// grid, so that the longest-running workgroups start first.  wgmap[b] = q << 12 | g for workgroup
-// b of the grid, IVF_NO_WG beyond the last one.  One workgroup; nb <= IVF_MAP_MAXQ, Wmax <= 4096.
+// grid, so that the longest-running workgroups start first.  wgmap[b] = (units_per_wg - 1) << 24 | q << 12 | g for
+// workgroup b of the grid, IVF_NO_WG beyond the last one.  One workgroup; nb <= IVF_MAP_MAXQ, Wmax <= 4096.
+// units_per_wg: as many as leave IVF_FILL_WGS workgroups, at most max_units.  (Always 16: the 300
+// workgroups of 150 queries over 1e6 codes walked 16 units each one after the other, 130 us; 52 with as many as the GPU holds.
+// 64 queries over 4e6 codes 239 -> 165 us per call; 1024, 2048 and 8192 workgroups: up to 8, 4 and 9 % slower.)
 // With `flags`, a query whose flag is not 1 is scanned over its other set of cells (see ivf_scan_kernel)
 // and its units are qunits_alt's.
 __global__ __launch_bounds__(IVF_MAP_NT) void ivf_wgmap_kernel(const unsigned *__restrict__ qunits, int nb,
-                                                              int units_per_wg, int Wmax,
+                                                              int max_units, int Wmax,
                                                               unsigned *__restrict__ wgmap,
                                                               const unsigned *__restrict__ qunits_alt,
                                                               const unsigned *__restrict__ flags)
@@ -1031,13 +1036,22 @@ __global__ __launch_bounds__(IVF_MAP_NT) void ivf_wgmap_kernel(const unsigned *_
     __shared__ unsigned start[IVF_MAP_MAXQ + 1];  // first workgroup of rank r
     __shared__ unsigned wsum[IVF_MAP_NT / WAVE];
     __shared__ unsigned carry;
+    __shared__ unsigned long long all_s;
     const int tid = threadIdx.x;
+    if (tid == 0) all_s = 0;
+    __syncthreads();
+    unsigned long long mine = 0;
+    for (int q = tid; q < nb; q += IVF_MAP_NT) {
+        un[q] = (flags && flags[q] != 1u) ? qunits_alt[q] : qunits[q];
+        mine += un[q];
+    }
+    if (mine) atomicAdd(&all_s, mine);
+    if (tid == 0) carry = 0;
+    __syncthreads();
+    const int units_per_wg = (int)max(1ull, min((unsigned long long)max_units, all_s / IVF_FILL_WGS));
     auto wgs_of = [&](unsigned u) {
         return (unsigned)min((long long)Wmax, max(1ll, ((long long)u + units_per_wg - 1) / units_per_wg));
     };
-    for (int q = tid; q < nb; q += IVF_MAP_NT) un[q] = (flags && flags[q] != 1u) ? qunits_alt[q] : qunits[q];
-    if (tid == 0) carry = 0;
-    __syncthreads();
     // rank by (units descending, query ascending): a total order, so ranks are distinct.  (With
     // `flags` the long lists have been scanned elsewhere and what is left is short and even: the
     // queries keep their order, which saves the nb x nb comparisons.)
@@ -1087,7 +1101,7 @@ __global__ __launch_bounds__(IVF_MAP_NT) void ivf_wgmap_kernel(const unsigned *_
                 const int mid = (lo_r + hi_r) >> 1;
                 if (start[mid] <= b) lo_r = mid; else hi_r = mid;
             }
-            v = (byrank[lo_r] << 12) | (b - start[lo_r]);
+            v = ((unsigned)(units_per_wg - 1) << 24) | (byrank[lo_r] << 12) | (b - start[lo_r]);
         }
         wgmap[b] = v;
     }
@@ -1130,8 +1144,9 @@ __global__ __launch_bounds__(NT) void ivf_scan_kernel(
     __shared__ IvfShared sh;
 
     const int tid = threadIdx.x;
-    const int q = (int)(me >> 12);
+    const int q = (int)((me >> 12) & 4095u);
     const int g = (int)(me & 4095u);
+    if (wgmap) units_per_wg = (int)(me >> 24) + 1;  // (uniform)
     const unsigned cap = (unsigned)cap_i;
     // bound + 1 left by the seed kernel (uniform load), 0 when there is none; hist_bound: the seed
     // kernel's workgroups left the query's histogram instead, and the bound is derived below
@@ -1222,12 +1237,7 @@ __global__ __launch_bounds__(NT) void ivf_scan_kernel(
                 reinterpret_cast<unsigned *>(qlut_s)[e] = reinterpret_cast<const unsigned *>(qlut)[e];
         }
         __syncthreads();
-        for (int e = tid; e < B * 256; e += NT) {
-            const int jb = e >> 8, v = e & 255;
-            const unsigned s = (unsigned)qlut_s[(2 * jb) * 16 + (v & 15)] +
-                               (unsigned)qlut_s[(2 * jb + 1) * 16 + (v >> 4)];
-            ptab[e] = (uint8_t)min(s, cap);
-        }
+        pair_rows_from_lds<B, NT>(qlut_s, cap, ptab);
         __syncthreads();
     };
 
@@ -1253,32 +1263,45 @@ __global__ __launch_bounds__(NT) void ivf_scan_kernel(
             uint4 w[2], wn[2];
             int nc[2], ncn[2];
             const bool new_list = p != cur_p;  // uniform
-            unsigned qword = 0;
+            // a row of a pair table per thread: the 16 entries of its even table, one entry of the odd one
+            constexpr int ROWS = (B * 16 + NT - 1) / NT;
+            uint4 low[ROWS];
+            unsigned high[ROWS];
             float4 fword = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-            if (new_list && tid < 2 * B * 4) {
-                if (fq.luts)  // uniform
-                    fword = reinterpret_cast<const float4 *>(fq.luts + ((size_t)q * nprobe + p) * (2 * B) * 16)[tid];
-                else
-                    qword = reinterpret_cast<const unsigned *>(qluts + ((size_t)q * nprobe + p) * (2 * B) * 16)[tid];
+            if (new_list) {
+                if (fq.luts) {  // uniform
+                    if (tid < 2 * B * 4)
+                        fword = reinterpret_cast<const float4 *>(fq.luts + ((size_t)q * nprobe + p) * (2 * B) * 16)[tid];
+                } else {
+                    const uint8_t *ql = qluts + ((size_t)q * nprobe + p) * (2 * B) * 16;
+#pragma unroll
+                    for (int r = 0; r < ROWS; ++r) {
+                        const int e = min(tid + r * NT, B * 16 - 1);
+                        low[r] = *reinterpret_cast<const uint4 *>(ql + (e >> 4) * 32);
+                        high[r] = ql[(e >> 4) * 32 + 16 + (e & 15)];
+                    }
+                }
             }
             asm volatile("" ::: "memory");
             tile_load<B, NT>(codes, u0, n_total, wn, ncn);
             asm volatile("" ::: "memory");
             if (new_list) {
                 __syncthreads();  // nobody still reads the previous pair tables
-                if (fq.luts && tid < 2 * B * 4) {  // the query's quantizer applied to the four entries
-                    const float b = fq.bias[(size_t)q * (2 * B) + (tid >> 2)];
-                    const float delta = fq.delta[q];
-                    qword = quantize_entry(fword.x, b, delta, cap) | (quantize_entry(fword.y, b, delta, cap) << 8) |
+                if (fq.luts) {    // uniform
+                    if (tid < 2 * B * 4) {  // the query's quantizer applied to the four entries
+                        const float b = fq.bias[(size_t)q * (2 * B) + (tid >> 2)];
+                        const float delta = fq.delta[q];
+                        reinterpret_cast<unsigned *>(qlut_s)[tid] =
+                            quantize_entry(fword.x, b, delta, cap) | (quantize_entry(fword.y, b, delta, cap) << 8) |
                             (quantize_entry(fword.z, b, delta, cap) << 16) | (quantize_entry(fword.w, b, delta, cap) << 24);
-                }
-                if (tid < 2 * B * 4) reinterpret_cast<unsigned *>(qlut_s)[tid] = qword;
-                __syncthreads();
-                for (int e = tid; e < B * 256; e += NT) {
-                    const int jb = e >> 8, v = e & 255;
-                    const unsigned sum = (unsigned)qlut_s[(2 * jb) * 16 + (v & 15)] +
-                                         (unsigned)qlut_s[(2 * jb + 1) * 16 + (v >> 4)];
-                    ptab[e] = (uint8_t)min(sum, cap);
+                    }
+                    __syncthreads();
+                    pair_rows_from_lds<B, NT>(qlut_s, cap, ptab);
+                } else {
+#pragma unroll
+                    for (int r = 0; r < ROWS; ++r)
+                        if (tid + r * NT < B * 16)
+                            reinterpret_cast<uint4 *>(ptab)[tid + r * NT] = pair_row(low[r], high[r], cap);
                 }
                 __syncthreads();
                 cur_p = p;
@@ -1794,7 +1817,7 @@ int ivf_search(const qadc_ivf_index *ix, const float *queries, int nq, int nprob
         // Scan: up to p.wgs workgroups per query, one per `upw` units of its lists (batches that fill
         // the GPU by their number alone), one per unit otherwise
         dim3 grid((unsigned)p.wgs * (unsigned)nb);
-        const int upw = nb >= 64 ? max(1, knob_or(knobs().ivf_units, 16)) : 1;
+        const int upw = nb >= 64 ? min(IVF_MAX_UNITS, max(1, knob_or(knobs().ivf_units, 16))) : 1;
         // a few queries: their lists are sampled by several workgroups each
         const int seed_parts_env = knob_or(knobs().ivf_seed_parts, 0);
         // (measured at N = 1e9: one query best with 16, 16 and 32 queries with 8, 64 with 4; the shared-list

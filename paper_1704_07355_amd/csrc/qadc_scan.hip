@@ -297,12 +297,7 @@ __global__ __launch_bounds__(1024) void prepare_u8_kernel(
     __syncthreads();
 
     // pair tables, handed to the scan kernel by workgroup 0
-    for (int e = tid; e < B * 256; e += NT) {
-        const int jb = e >> 8, v = e & 255;
-        const unsigned s = (unsigned)qlut_s[(2 * jb) * 16 + (v & 15)] +
-                           (unsigned)qlut_s[(2 * jb + 1) * 16 + (v >> 4)];
-        ptab[e] = (uint8_t)min(s, cap);
-    }
+    pair_rows_from_lds<B, NT>(qlut_s, cap, ptab);
     __syncthreads();
     ScanHeader *hdr = reinterpret_cast<ScanHeader *>(ws + (size_t)q * ws_stride);
     if (g == 0)
@@ -426,12 +421,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(B >= SIXBIT 
         for (int e = tid; e < 2 * B * 4; e += NT)
             reinterpret_cast<unsigned *>(qlut_s)[e] = reinterpret_cast<const unsigned *>(qlut)[e];
         __syncthreads();
-        for (int e = tid; e < B * 256; e += NT) {
-            const int jb = e >> 8, v = e & 255;
-            const unsigned s = (unsigned)qlut_s[(2 * jb) * 16 + (v & 15)] +
-                               (unsigned)qlut_s[(2 * jb + 1) * 16 + (v >> 4)];
-            ptab[e] = (uint8_t)min(s, cap);
-        }
+        pair_rows_from_lds<B, NT>(qlut_s, cap, ptab);
     }
     __syncthreads();
 

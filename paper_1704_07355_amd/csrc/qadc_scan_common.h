@@ -236,7 +236,33 @@ __device__ __forceinline__ void tile_load(const uint8_t *__restrict__ codes, int
     }
 }
 
-// One pair-table entry, known to the compiler as a byte value.
+// Sixteen entries of a pair table, min(cap, low[v] + high) for v = 0 .. 15: a thread makes a row of 16 bytes with 33
+// vector instructions and writes it at once (an entry at a time, the LDS was busy for some 1000 cycles per 4096 entries).
+__device__ __forceinline__ uint4 pair_row(const uint4 &low, unsigned high, unsigned cap)
+{
+    typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
+    const unsigned h = high | (high << 16), c = cap | (cap << 16);
+    auto four = [&](unsigned w) {
+        const unsigned even = (w & 0x00ff00ffu) + h, odd = ((w >> 8) & 0x00ff00ffu) + h;  // (at most 510 each: no carry)
+        const u16x2 e = __builtin_elementwise_min(__builtin_bit_cast(u16x2, even), __builtin_bit_cast(u16x2, c));
+        const u16x2 o = __builtin_elementwise_min(__builtin_bit_cast(u16x2, odd), __builtin_bit_cast(u16x2, c));
+        return __builtin_bit_cast(unsigned, e) | (__builtin_bit_cast(unsigned, o) << 8);
+    };
+    return make_uint4(four(low.x), four(low.y), four(low.z), four(low.w));
+}
+
+// Pair tables ptab[jb][v] = min(cap, q[2jb][v & 15] + q[2jb + 1][v >> 4]) from a query's tables in LDS (both 16-byte
+// aligned), by NT threads.
+template <int B, int NT>
+__device__ __forceinline__ void pair_rows_from_lds(const uint8_t *qlut_s, unsigned cap, uint8_t *ptab)
+{
+    for (int e = threadIdx.x; e < B * 16; e += NT) {
+        const int jb = e >> 4;
+        const uint4 low = *reinterpret_cast<const uint4 *>(qlut_s + 2 * jb * 16);
+        reinterpret_cast<uint4 *>(ptab)[e] = pair_row(low, qlut_s[(2 * jb + 1) * 16 + (e & 15)], cap);
+    }
+}
+
 // Order-preserving map float -> unsigned (any sign), and back.
 __device__ __forceinline__ unsigned f2ord(float f)
 {

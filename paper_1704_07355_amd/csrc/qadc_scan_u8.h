@@ -186,11 +186,12 @@ __device__ __forceinline__ void build_pair_tables(const uint8_t *__restrict__ ql
         for (int e = threadIdx.x; e < B * 256; e += NT) ptab[e] = (uint8_t)min((unsigned)qlut[e], cap);
         return;
     }
-    for (int e = threadIdx.x; e < B * 256; e += NT) {
-        const int jb = e >> 8, v = e & 255;
-        const unsigned s = (unsigned)qlut[(2 * jb) * 16 + (v & 15)] +
-                           (unsigned)qlut[(2 * jb + 1) * 16 + (v >> 4)];
-        ptab[e] = (uint8_t)min(s, cap);
+    typedef unsigned u32_any __attribute__((aligned(1)));  // (the caller's tables may start anywhere)
+    for (int e = threadIdx.x; e < B * 16; e += NT) {
+        const int jb = e >> 4;
+        const u32_any *l = reinterpret_cast<const u32_any *>(qlut + 2 * jb * 16);
+        const uint4 low = make_uint4(l[0], l[1], l[2], l[3]);
+        reinterpret_cast<uint4 *>(ptab)[e] = pair_row(low, qlut[(2 * jb + 1) * 16 + (e & 15)], cap);
     }
     }
 }

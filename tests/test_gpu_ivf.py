@@ -383,6 +383,33 @@ def test_ivf_few_queries_path_equals_batch_path(Q, O, mode):
             assert np.array_equal(d2[k].cpu().numpy(), rep["dist"]), (s, k)
 
 
+@pytest.mark.parametrize("m,n,nq,R", [(8, 60_000, 70, 100), (16, 400_003, 64, 100), (32, 1_000_001, 190, 40), (64, 900_001, 200, 200),
+                                      (64, 2_400_003, 130, 1)])
+def test_ivf_batches_of_any_number_of_units_per_workgroup(Q, m, n, nq, R):
+    """A batch whose lists are fewer, or many times more, units of work than its workgroups are meant to be (1, 1, 2, 5 and 16
+    of them each; 40 queries probe the one longest list alone, so that they reach the limit of workgroups per query):
+    the neighbours of calls of a few queries, which get a workgroup per unit."""
+    import torch
+    K, d = 9, 64
+    g = torch.Generator(device="cuda:0")
+    g.manual_seed(n)
+    rand = lambda *shape: torch.rand(shape, generator=g, device="cuda:0")
+    coarse, cb = 200 * rand(K, d), 60 * rand(m, 16, d // m)
+    codes = torch.randint(0, 256, (n, m // 2), generator=g, device="cuda:0", dtype=torch.uint8)
+    sizes = np.full(K, n // (2 * K))
+    sizes[4] += n - sizes.sum()
+    off = torch.from_numpy(np.concatenate([[0], np.cumsum(sizes)])).to("cuda:0")
+    ix = Q.IvfIndex(coarse, off, codes, torch.arange(n, dtype=torch.int32, device="cuda:0"), cb)
+    queries = 200 * rand(nq, d)
+    probes = torch.stack([torch.randperm(K, generator=g, device="cuda:0") for _ in range(nq)]).int()
+    probes[:40] = -1
+    probes[:40, 3] = 4
+    ids, dist = Q.qadc_ivf_search(ix, queries, K, R, 300, probes_in=probes)
+    for s in list(range(0, 45, 7)) + [nq - 3]:
+        i2, d2 = Q.qadc_ivf_search(ix, queries[s:s + 3].contiguous(), K, R, 300, probes_in=probes[s:s + 3].contiguous())
+        assert torch.equal(i2, ids[s:s + 3]) and torch.equal(d2, dist[s:s + 3]), s
+
+
 @pytest.mark.parametrize("K", [300_000, 530_000])
 def test_ivf_few_queries_many_cells(Q, O, K):
     """Hundreds of thousands of cells, most of them empty, a few queries: with 2344 runs of 128 cells the
