@@ -11,10 +11,24 @@
 // proportion to its number of units, each taking a contiguous range of them.
 
 #include <algorithm>
+#include <type_traits>
+#include <utility>
 
 #include "qadc_scan_common.h"
 
 namespace qadc {
+
+// f(integral_constant 0), .., f(integral_constant N - 1)
+template <int... I, typename F>
+__device__ __forceinline__ void static_for_each(std::integer_sequence<int, I...>, F f)
+{
+    (f(std::integral_constant<int, I>{}), ...);
+}
+template <int N, typename F>
+__device__ __forceinline__ void static_for(F f)
+{
+    static_for_each(std::make_integer_sequence<int, N>{}, f);
+}
 
 #ifndef QADC_IVF_EARLY_STAGES
 // (a check at a quarter and at half of the bytes measured the same as the one check at half)
@@ -38,6 +52,20 @@ __device__ __forceinline__ unsigned quantize_entry(float D, float bias, float de
 {
     const float off = fmaxf(0.0f, D - bias);
     const float t = floorf(__fdiv_rn(off, delta));
+    return (t < (float)nbins) ? (unsigned)(uint8_t)t : nbins;
+}
+
+// The same from inv = 1 / delta, for delta between QUANT_INV_MIN and its inverse: off * inv is within 3 2^-24 of the rounded
+// quotient, relatively, and so has the same floor unless a whole number is as near; then the division decides.  (A division
+// per entry was half of the work of ivf_tables_kernel.)
+constexpr float QUANT_INV_MIN = 1e-30f;
+__device__ __forceinline__ unsigned quantize_entry_inv(float D, float bias, float delta, float inv, unsigned nbins)
+{
+    const float off = fmaxf(0.0f, D - bias);
+    float t = off * inv;
+    const bool near = fabsf(t - rintf(t)) < 4e-7f * t;
+    if (near) t = __fdiv_rn(off, delta);
+    t = floorf(t);
     return (t < (float)nbins) ? (unsigned)(uint8_t)t : nbins;
 }
 
@@ -533,129 +561,74 @@ void ivf_select_smallest(const float *dist, int rows, int K, int count, int32_t 
 
 // ----------------------------------------------------------------- Tables
 
-// luts[q][p][j][i] = || (y_q - coarse[probes[q][p]])^j - C^j[i] ||^2, float64 inside, one
-// rounding to float32 (same arithmetic as the exhaustive tables kernel).  Unused probe slots
-// (cell id < 0) get +inf tables: nothing of them is ever scanned.
-__global__ __launch_bounds__(256) void ivf_build_luts_kernel(
+// Batches: Tables, the qmax walk and the quantizer by one workgroup per query, a thread per table entry and, where the
+// tables are smaller than the workgroup, per one of several probed cells at a time.  Entry (j, i) of cell p is
+// || (y_q - centroid_p)^j - C^j[i] ||^2, float64 inside, one rounding to float32 (as the exhaustive tables kernel); unused
+// probe slots (cell id < 0) have +inf tables: nothing of them is ever scanned.
+//   1. qmax = min(R, n_walk)-th smallest float ADC distance (Eq. (2), float32, increasing j) of the first n_walk =
+//      min(init, codes in the probed lists) codes met walking the lists in probe order, each code with the tables of its
+//      own cell; 0 when the lists are empty.  The tables of the lists walked pass through LDS.
+//   2. bias_j = smallest entry of table j over all probed cells.
+//   3. the entries again, quantized (the arithmetic of quantize_luts_kernel).
+// Bound by its float64 instructions and, below some 500 queries, by the chain of steps of one workgroup.  The entries stay in
+// registers between steps 2 and 3: as three kernels, the float tables of 4096 queries x 64 cells were 537 MB written by
+// one, gathered from by the second and read by the third, 560 us (m = 32, d = 128) against 335 now; 512 queries 82 against 49,
+// 150 queries x 24 cells (m = 16) 25 against 12.  (Every entry computed twice instead, with no registers held: 64 us for the
+// 512.  Every lane converting its own residuals: 51.)
+constexpr int IVF_WALK = 4;  // lists walked at a time, per table set that the workgroup's threads are
+template <int DSUB>  // d / m; 0: any
+__global__ __launch_bounds__(1024) void ivf_tables_kernel(
     const float *__restrict__ codebooks, int d, int m, const float *__restrict__ queries,
     const float *__restrict__ coarse, const float *__restrict__ halves, const uint32_t *__restrict__ cell_ids,
-    int Kh, const int32_t *__restrict__ probes, int nprobe, float *__restrict__ luts)
-{
-    extern __shared__ double yr[];  // [d]
-    const int p = blockIdx.x, q = blockIdx.y;
-    const int cell = probes[(size_t)q * nprobe + p];
-    const int dsub = d / m;
-    const int entries = m * 16;
-    float *out = luts + ((size_t)q * nprobe + p) * entries;
-    if (cell < 0) {
-        for (int e = threadIdx.x; e < entries; e += blockDim.x) out[e] = __builtin_inff();
-        return;
-    }
-    if (coarse) {
-        for (int t = threadIdx.x; t < d; t += blockDim.x)
-            yr[t] = (double)queries[(size_t)q * d + t] - (double)coarse[(size_t)cell * d + t];
-    } else {  // list `cell` of a multi-index: the centroid is a pair of half-centroids
-        const int dh = d >> 1;
-        const unsigned id = cell_ids[cell];
-        const float *h0 = halves + (size_t)(id / (unsigned)Kh) * dh;
-        const float *h1 = halves + ((size_t)Kh + id % (unsigned)Kh) * dh;
-        for (int t = threadIdx.x; t < d; t += blockDim.x)
-            yr[t] = (double)queries[(size_t)q * d + t] - (double)(t < dh ? h0[t] : h1[t - dh]);
-    }
-    __syncthreads();
-    for (int e = threadIdx.x; e < entries; e += blockDim.x) {
-        const int j = e >> 4;
-        const float *c = codebooks + (size_t)e * dsub;
-        const double *y = yr + j * dsub;
-        double acc = 0.0;
-        for (int t = 0; t < dsub; ++t) {
-            const double df = y[t] - (double)c[t];
-            acc += df * df;
-        }
-        out[e] = (float)acc;
-    }
-}
-
-// The same tables for batches: one workgroup per query, one thread per table entry (m * 16 threads);
-// the thread keeps its centroid's sub-vector in registers and walks the query's probed cells, reading
-// the cell's coarse centroid (or half-centroids) where its sub-vector lies.  Same arithmetic, value by
-// value, as ivf_build_luts_kernel; a workgroup per (query, cell) spends most of its time starting up.
-template <int DSUB>
-__global__ __launch_bounds__(1024) void ivf_build_luts_batch_kernel(
-    const float *__restrict__ codebooks, int d, int m, const float *__restrict__ queries,
-    const float *__restrict__ coarse, const float *__restrict__ halves, const uint32_t *__restrict__ cell_ids,
-    int Kh, const int32_t *__restrict__ probes, int nprobe, float *__restrict__ luts)
-{
-    const int q = blockIdx.x;
-    const int e = threadIdx.x;  // entry: table j = e / 16, centroid e % 16
-    constexpr int dsub = DSUB;  // d / m
-    const int entries = m * 16;
-    if (e >= entries) return;
-    const int j = e >> 4;
-    const int t0 = j * dsub;
-    double c[DSUB], y[DSUB];
-#pragma unroll
-    for (int t = 0; t < dsub; ++t) {
-        c[t] = (double)codebooks[(size_t)e * dsub + t];
-        y[t] = (double)queries[(size_t)q * d + t0 + t];
-    }
-    const int dh = d >> 1;
-    for (int p = 0; p < nprobe; ++p) {
-        const int cell = probes[(size_t)q * nprobe + p];
-        float *out = luts + ((size_t)q * nprobe + p) * entries;
-        if (cell < 0) {
-            out[e] = __builtin_inff();
-            continue;
-        }
-        const float *cen;  // the centroid's components t0 .. t0 + dsub - 1 (inside one half)
-        if (coarse) {
-            cen = coarse + (size_t)cell * d + t0;
-        } else {
-            const unsigned id = cell_ids[cell];
-            cen = t0 < dh ? halves + (size_t)(id / (unsigned)Kh) * dh + t0
-                          : halves + ((size_t)Kh + id % (unsigned)Kh) * dh + (t0 - dh);
-        }
-        double acc = 0.0;
-#pragma unroll
-        for (int t = 0; t < dsub; ++t) {
-            const double df = (y[t] - (double)cen[t]) - c[t];
-            acc += df * df;
-        }
-        out[e] = (float)acc;
-    }
-}
-
-// ------------------------------------------------------------------- qmax
-
-// qmax[q] = min(R, n_walk)-th smallest float ADC distance (Eq. (2), float32, increasing j)
-// of the first n_walk = min(init, codes in the probed lists) codes met walking the lists in
-// probe order, each code with the tables of its own cell; 0 when the lists are empty.
-__global__ __launch_bounds__(1024) void ivf_qmax_kernel(
-    const int64_t *__restrict__ list_off, const uint8_t *__restrict__ codes, int m,
-    const int32_t *__restrict__ probes, int nprobe, const float *__restrict__ luts, int init, int R,
-    float *__restrict__ qmax, long long unit, unsigned *__restrict__ qunits, int64_t n_total,
-    char *__restrict__ ws, size_t ws_stride, size_t counts_off, int W, size_t countsA_off)
+    int Kh, const int32_t *__restrict__ probes, int nprobe, const int64_t *__restrict__ list_off,
+    const uint8_t *__restrict__ codes, int64_t n_total, int init, int R, int nbins, int qmin_mode, long long unit,
+    unsigned *__restrict__ qunits, uint8_t *__restrict__ qluts, char *__restrict__ ws, size_t ws_stride,
+    size_t counts_off, int W, size_t countsA_off)
 {
     ivf_clear_control(ws + (size_t)blockIdx.x * ws_stride, counts_off, W, countsA_off);
     __shared__ unsigned cand[QADC_MAX_INIT];
+    __shared__ float lut_s[IVF_WALK][1024];
     __shared__ unsigned units_s;
     __shared__ long long start[IVF_MAX_NPROBE + 1];  // codes before probe p in the walk
     __shared__ long long lo[IVF_MAX_NPROBE];
+    __shared__ int row0[IVF_MAX_NPROBE], row1[IVF_MAX_NPROBE];  // the centroid, or the two half-centroids, of probe p; -1
+    __shared__ unsigned bias_ord[64];
+    __shared__ float bias[64];
+    __shared__ float delta_s;
     __shared__ SelectScratch sc;
-    const int q = blockIdx.x;
-    const int tid = threadIdx.x;
-    const int B = m / 2;
-    // list lengths one thread per probe, exclusive prefix sum
     __shared__ unsigned long long wsum[1024 / WAVE];
+    const int q = blockIdx.x;
+    const int tid = threadIdx.x, NT = blockDim.x;
+    const int B = m / 2;
+    const int entries = m * 16;              // a power of two that divides NT
+    const int e = tid & (entries - 1);       // entry: table j = e / 16, centroid e % 16
+    const int sub = tid / entries, subs = NT / entries;
+    const int j = e >> 4;
+    const int dsub = DSUB ? DSUB : d / m;
+    const int t0 = j * dsub;
+    // list lengths one thread per probe, exclusive prefix sum
     unsigned long long len = 0;
     if (tid == 0) units_s = 0;
+    if (tid < 64) bias_ord[tid] = 0xffffffffu;
     __syncthreads();
     if (tid < nprobe) {
         const int cell = probes[(size_t)q * nprobe + tid];
         long long l = 0, h = 0;
-        if (cell >= 0) { l = list_off[cell]; h = list_off[cell + 1]; }
+        int r0 = -1, r1 = -1;
+        if (cell >= 0) {
+            l = list_off[cell];
+            h = list_off[cell + 1];
+            r0 = r1 = cell;
+            if (!coarse) {  // list `cell` of a multi-index: the centroid is a pair of half-centroids
+                const unsigned id = cell_ids[cell];
+                r0 = (int)(id / (unsigned)Kh);
+                r1 = (int)(id % (unsigned)Kh);
+            }
+        }
         if (l < 0 || h > n_total || h < l) l = h = 0;  // offsets that are not a list: nothing is read
         lo[tid] = l;
+        row0[tid] = r0;
+        row1[tid] = r1;
         len = (unsigned long long)(h - l);
         // units the scan kernel cuts this list into (the same expression as there)
         if (h > l) atomicAdd(&units_s, (unsigned)((h - l / 16 * 16 + unit - 1) / unit));
@@ -677,45 +650,195 @@ __global__ __launch_bounds__(1024) void ivf_qmax_kernel(
     }
     __syncthreads();
     if (tid == 0) qunits[q] = units_s;
-    const long long total = start[nprobe];
-    const int n_walk = (int)min((long long)init, total);
-    if (n_walk == 0) {  // uniform
-        if (tid == 0) qmax[q] = 0.0f;
-        return;
-    }
-    for (int i = tid; i < n_walk; i += blockDim.x) {
-        int p = 0;
-        while (start[p + 1] <= i) ++p;  // lists are few; the walk is short
-        // the code as 32-bit words (B is a multiple of 4), then its table entries four bytes at a
-        // time: the eight loads of a word are in flight together, the sum keeps the order of j
-        const unsigned *cw = reinterpret_cast<const unsigned *>(codes + (size_t)(lo[p] + (i - start[p])) * B);
-        const float *lut = luts + ((size_t)q * nprobe + p) * m * 16;
-        float acc = 0.0f;
-        for (int k = 0; k < B / 4; ++k) {
-            const unsigned w = cw[k];
-            float e[8];
+
+    // this thread's centroid and sub-vector of the query, and where its sub-vector of a cell's centroid lies
+    constexpr int REGS = DSUB ? DSUB : 1;
+    double c[REGS], y[REGS];
+    if constexpr (DSUB > 0) {
 #pragma unroll
-            for (int b = 0; b < 4; ++b) {
-                const unsigned comps = (w >> (8 * b)) & 0xffu;
-                const int jb = 4 * k + b;
-                e[2 * b] = lut[(2 * jb) * 16 + (comps & 15u)];
-                e[2 * b + 1] = lut[(2 * jb + 1) * 16 + (comps >> 4)];
-            }
-#pragma unroll
-            for (int b = 0; b < 8; ++b) acc = acc + e[b];
+        for (int t = 0; t < DSUB; ++t) {
+            c[t] = (double)codebooks[(size_t)e * DSUB + t];
+            y[t] = (double)queries[(size_t)q * d + t0 + t];
         }
-        cand[i] = f2ord(acc);
+    }
+    const int dh = d >> 1;
+    const bool first = coarse || t0 < dh;  // (a sub-vector lies inside one half)
+    const float *base = coarse ? coarse + t0 : t0 < dh ? halves + t0 : halves + (size_t)Kh * dh + (t0 - dh);
+    const size_t ld = coarse ? (size_t)d : (size_t)dh;
+    auto row_of = [&](int p) { return first ? row0[p] : row1[p]; };
+    auto entry = [&](int p) {
+        if (row_of(p) < 0) return __builtin_inff();
+        const float *r = base + (size_t)row_of(p) * ld;
+        double acc = 0.0;
+        if constexpr (DSUB > 0) {
+#pragma unroll
+            for (int t = 0; t < DSUB; ++t) {
+                const double df = (y[t] - (double)r[t]) - c[t];
+                acc += df * df;
+            }
+        } else {
+            for (int t = 0; t < dsub; ++t) {
+                const double df = ((double)queries[(size_t)q * d + t0 + t] - (double)r[t]) - (double)codebooks[(size_t)e * dsub + t];
+                acc += df * df;
+            }
+        }
+        return (float)acc;
+    };
+    // The same for SIDE probes at a time: the 16 lanes of a table need the same residuals y - centroid, so lane k % 16 takes
+    // component k % DSUB of probe k / DSUB, and the others get it from there.  (Every lane for itself, conversions and
+    // differences were the larger part of the kernel: 16 conversions to float64 per four entries instead of one.)
+    constexpr int SIDE = DSUB > 0 ? 16 / DSUB : 1;
+    constexpr int AHEAD = DSUB == 2 ? 2 : 4;  // groups of SIDE probes whose centroids are requested together
+    const int own = DSUB > 0 ? min((e & 15) / REGS, SIDE - 1) : 0, own_t = DSUB > 0 ? (e & 15) % REGS : 0;
+    const double own_y = DSUB > 0 ? (double)queries[(size_t)q * d + t0 + own_t] : 0.0;
+    auto residuals = [&](int p) {  // of probes p, p + subs, .. (the last probe's beyond it): this lane's
+        const float *r = base + (size_t)max(row_of(min(p + own * subs, nprobe - 1)), 0) * ld;
+        return own_y - (double)r[own_t];
+    };
+    auto entries_of = [&](int p, double res, float (&v)[SIDE]) {
+        const int lo32 = (int)__builtin_bit_cast(unsigned long long, res), hi32 = (int)(__builtin_bit_cast(unsigned long long, res) >> 32);
+        auto from = [&](auto lane) {
+            constexpr int bcast = 0x150 + decltype(lane)::value;  // to the 16 lanes from this one of theirs
+            const unsigned l = (unsigned)__builtin_amdgcn_mov_dpp(lo32, bcast, 0xf, 0xf, true);
+            const unsigned h = (unsigned)__builtin_amdgcn_mov_dpp(hi32, bcast, 0xf, 0xf, true);
+            return __builtin_bit_cast(double, (unsigned long long)l | ((unsigned long long)h << 32));
+        };
+        static_for<SIDE>([&](auto a) {
+            double acc = 0.0;
+            static_for<REGS>([&](auto t) {
+                const double df = from(std::integral_constant<int, decltype(a)::value * REGS + decltype(t)::value>{}) - c[decltype(t)::value];
+                acc += df * df;
+            });
+            v[decltype(a)::value] = row_of(min(p + decltype(a)::value * subs, nprobe - 1)) < 0 ? __builtin_inff() : (float)acc;
+        });
+    };
+    // f(p, entry) for this thread's probes from p0 on
+    auto each_probe = [&](int p0, auto f) {
+        for (int p = p0 + sub; p < nprobe; p += SIDE * subs) {  // uniform in a wavefront
+            float v[SIDE];
+            if constexpr (DSUB > 0) entries_of(p, residuals(p), v);
+            else v[0] = entry(p);
+#pragma unroll
+            for (int a = 0; a < SIDE; ++a)
+                if (p + a * subs < nprobe) f(p + a * subs, v[a]);
+        }
+    };
+
+    const int n_walk = (int)min((long long)init, start[nprobe]);
+    const int walked = __syncthreads_count(tid < nprobe && start[min(tid, nprobe)] < n_walk);  // lists with a code of the walk before their end
+    unsigned least = 0xffffffffu;  // smallest value of this entry, as its order-preserving image
+    for (int p0 = 0; p0 < walked; p0 += IVF_WALK * subs) {  // uniform
+#pragma unroll
+        for (int a = 0; a < IVF_WALK; ++a) {
+            const int p = p0 + sub + a * subs;
+            if (p < walked) {
+                const float v = entry(p);
+                lut_s[a][tid] = v;
+                least = min(least, f2ord(v));
+            }
+        }
+        __syncthreads();
+        const int s1 = (int)min(start[min(p0 + IVF_WALK * subs, walked)], (long long)n_walk);
+        for (int i = (int)start[p0] + tid; i < s1; i += NT) {
+            int p = p0;
+            while (start[p + 1] <= i) ++p;
+            // the code as 32-bit words (B is a multiple of 4, up to 32), all requested at once: the sum keeps the order of j
+            const unsigned *cw = reinterpret_cast<const unsigned *>(codes + (size_t)(lo[p] + (i - start[p])) * B);
+            const float *lut = &lut_s[0][0] + (p - p0) / subs * 1024 + (p - p0) % subs * entries;
+            unsigned w[8];
+#pragma unroll
+            for (int k = 0; k < 8; ++k) w[k] = 4 * k < B ? cw[k] : 0u;  // (uniform)
+            float acc = 0.0f;
+#pragma unroll
+            for (int k = 0; k < 8; ++k) {
+                if (4 * k < B) {  // uniform
+                    float ent[8];
+#pragma unroll
+                    for (int b = 0; b < 4; ++b) {
+                        const unsigned comps = (w[k] >> (8 * b)) & 0xffu;
+                        const int jb = 4 * k + b;
+                        ent[2 * b] = lut[(2 * jb) * 16 + (comps & 15u)];
+                        ent[2 * b + 1] = lut[(2 * jb + 1) * 16 + (comps >> 4)];
+                    }
+#pragma unroll
+                    for (int b = 0; b < 8; ++b) acc = acc + ent[b];
+                }
+            }
+            cand[i] = f2ord(acc);
+        }
+        __syncthreads();
+    }
+    // the entries of the first KEEP probes of the thread stay in registers for step 3, those beyond are computed twice
+    constexpr int KEEP = DSUB == 0 || DSUB > 8 ? 0 : DSUB <= 4 ? 64 : 32, BLOCK = AHEAD * SIDE;
+    static_assert(KEEP % BLOCK == 0, "whole blocks");
+    float kept[KEEP ? KEEP : 1];
+#pragma unroll
+    for (int k = 0; k < KEEP; k += BLOCK) {
+        if (k * subs < nprobe) {  // uniform
+            double res[AHEAD];
+#pragma unroll
+            for (int a = 0; a < AHEAD; ++a) res[a] = residuals(sub + (k + a * SIDE) * subs);
+#pragma unroll
+            for (int a = 0; a < AHEAD; ++a) {
+                float v[SIDE];
+                entries_of(sub + (k + a * SIDE) * subs, res[a], v);
+#pragma unroll
+                for (int i = 0; i < SIDE; ++i) {
+                    kept[k + a * SIDE + i] = v[i];
+                    least = min(least, f2ord(v[i]));  // (the last probe again where there is none)
+                }
+            }
+        }
+    }
+    each_probe(KEEP * subs, [&](int, float v) { least = min(least, f2ord(v)); });
+#pragma unroll
+    for (int w = 8; w >= 1; w >>= 1) least = min(least, (unsigned)__shfl_xor((int)least, w));
+    if ((e & 15) == 0) atomicMin(&bias_ord[j], least);
+    float qmax = 0.0f;
+    if (n_walk > 0)  // uniform
+        qmax = ord2f(block_radix_select<unsigned, 4>(cand, (unsigned)n_walk, (unsigned)min(R, n_walk), &sc));
+    __syncthreads();
+    if (tid < m) bias[tid] = ord2f(bias_ord[tid]);
+    __syncthreads();
+    if (tid == 0) {
+        float qmin;
+        if (qmin_mode == QADC_QMIN_GLOBAL) {
+            unsigned g = 0xffffffffu;
+            for (int k = 0; k < m; ++k) g = min(g, bias_ord[k]);
+            qmin = ord2f(g);
+            for (int k = 0; k < m; ++k) bias[k] = qmin;
+        } else {
+            qmin = 0.0f;
+#pragma unroll 8
+            for (int k = 0; k < m; ++k) qmin = qmin + bias[k];
+        }
+        float delta = __fdiv_rn(qmax - qmin, (float)nbins);
+        if (!(delta > 0.0f)) delta = 1.0f;
+        delta_s = delta;
     }
     __syncthreads();
-    const unsigned need = (unsigned)min(R, n_walk);
-    const unsigned kth = block_radix_select<unsigned, 4>(cand, (unsigned)n_walk, need, &sc);
-    if (tid == 0) qmax[q] = ord2f(kth);
+    const float delta = delta_s, off = bias[j];
+    const float inv = __fdiv_rn(1.0f, delta);
+    const bool usual = delta >= QUANT_INV_MIN && delta <= 1.0f / QUANT_INV_MIN;  // uniform
+    unsigned *out = reinterpret_cast<unsigned *>(qluts + (size_t)q * nprobe * entries);
+    auto emit = [&](int p, float v) {
+        // four neighbouring lanes' entries as one word (the lanes of a wavefront are at the same probe, or all beyond the last)
+        const unsigned byte = usual ? quantize_entry_inv(v, off, delta, inv, (unsigned)nbins)
+                                    : quantize_entry(v, off, delta, (unsigned)nbins);
+        unsigned word = byte << (8 * (e & 3));
+        word |= (unsigned)__builtin_amdgcn_mov_dpp((int)word, 0xB1, 0xf, 0xf, true);  // lanes 1 0 3 2
+        word |= (unsigned)__builtin_amdgcn_mov_dpp((int)word, 0x4E, 0xf, 0xf, true);  // lanes 2 3 0 1
+        if ((e & 3) == 0) out[((size_t)p * entries + e) >> 2] = word;
+    };
+#pragma unroll
+    for (int k = 0; k < KEEP; ++k)
+        if (sub + k * subs < nprobe) emit(sub + k * subs, kept[k]);  // uniform in a wavefront
+    each_probe(KEEP * subs, emit);
 }
 
 // Calls of a few queries: Tables and the sums of the qmax walk in one launch.  Workgroup (p, q)
-// builds the float tables of the query's p-th cell (the arithmetic of ivf_build_luts_kernel), leaves
-// the minimum of each table, and computes the float ADC sums of the init codes that the walk of
-// ivf_qmax_kernel takes from its list, with the tables still in LDS ...
+// builds the float tables of the query's p-th cell (the arithmetic of ivf_tables_kernel), leaves
+// the minimum of each table, and computes the float ADC sums of the init codes that the walk takes from its list, with the tables still in LDS ...
 constexpr int IVF_FRONT_NT = 256;
 
 __global__ __launch_bounds__(IVF_FRONT_NT) void ivf_front_kernel(
@@ -814,7 +937,7 @@ __global__ __launch_bounds__(IVF_FRONT_NT) void ivf_front_kernel(
         for (int i = 0; i < 16; ++i) mn = min(mn, f2ord(lut_s[tid * 16 + i]));
         mins[((size_t)q * nprobe + p) * m + tid] = mn;
     }
-    // the walk's codes that lie in this list: float32 sums in increasing j (as ivf_qmax_kernel)
+    // the walk's codes that lie in this list: float32 sums in increasing j (as ivf_tables_kernel)
     const long long total = total_s;
     const int n_walk = (int)min((long long)init, total);
     {
@@ -1016,92 +1139,89 @@ constexpr unsigned IVF_NO_WG = 0xffffffffu;  // (no entry of the map: units_per_
 constexpr int IVF_MAX_UNITS = 255;
 constexpr unsigned long long IVF_FILL_WGS = 4096;
 
-// Workgroups of the scan: query q gets W_q = clamp(ceil(units_q / units_per_wg), 1, Wmax) of them
-// (work in proportion to the lists it probes); the queries with the most work come first in the
-// grid, so that the longest-running workgroups start first.  wgmap[b] = (units_per_wg - 1) << 24 | q << 12 | g for
-// workgroup b of the grid, IVF_NO_WG beyond the last one.  One workgroup; nb <= IVF_MAP_MAXQ, Wmax <= 4096.
+// Workgroups of the scan: query q gets W_q = clamp(ceil(units_q / units_per_wg), 1, Wmax) of them, work in proportion to
+// the lists it probes.  wgmap[b] = (units_per_wg - 1) << 24 | q << 12 | g for workgroup b of the grid, IVF_NO_WG beyond
+// the last one.  nb <= IVF_MAP_MAXQ, Wmax <= 4096.
 // units_per_wg: as many as leave IVF_FILL_WGS workgroups, at most max_units.  (Always 16: the 300
 // workgroups of 150 queries over 1e6 codes walked 16 units each one after the other, 130 us; 52 with as many as the GPU holds.
 // 64 queries over 4e6 codes 239 -> 165 us per call; 1024, 2048 and 8192 workgroups: up to 8, 4 and 9 % slower.)
 // With `flags`, a query whose flag is not 1 is scanned over its other set of cells (see ivf_scan_kernel)
 // and its units are qunits_alt's.
+// Queries with more than the average number of units come first in the grid.  Every workgroup takes the running sums over all
+// queries and fills its share of the map: 5 us (one workgroup that also ordered the queries by their units 8 to 20; in the
+// order of the queries alone the scan took 3 to 6 % longer).
 __global__ __launch_bounds__(IVF_MAP_NT) void ivf_wgmap_kernel(const unsigned *__restrict__ qunits, int nb,
                                                               int max_units, int Wmax,
                                                               unsigned *__restrict__ wgmap,
                                                               const unsigned *__restrict__ qunits_alt,
                                                               const unsigned *__restrict__ flags)
 {
-    __shared__ unsigned un[IVF_MAP_MAXQ];      // units of query q
-    __shared__ unsigned byrank[IVF_MAP_MAXQ];  // query at rank r
-    __shared__ unsigned start[IVF_MAP_MAXQ + 1];  // first workgroup of rank r
-    __shared__ unsigned wsum[IVF_MAP_NT / WAVE];
-    __shared__ unsigned carry;
-    __shared__ unsigned long long all_s;
-    const int tid = threadIdx.x;
-    if (tid == 0) all_s = 0;
-    __syncthreads();
-    unsigned long long mine = 0;
-    for (int q = tid; q < nb; q += IVF_MAP_NT) {
-        un[q] = (flags && flags[q] != 1u) ? qunits_alt[q] : qunits[q];
-        mine += un[q];
-    }
-    if (mine) atomicAdd(&all_s, mine);
-    if (tid == 0) carry = 0;
-    __syncthreads();
-    const int units_per_wg = (int)max(1ull, min((unsigned long long)max_units, all_s / IVF_FILL_WGS));
-    auto wgs_of = [&](unsigned u) {
-        return (unsigned)min((long long)Wmax, max(1ll, ((long long)u + units_per_wg - 1) / units_per_wg));
-    };
-    // rank by (units descending, query ascending): a total order, so ranks are distinct.  (With
-    // `flags` the long lists have been scanned elsewhere and what is left is short and even: the
-    // queries keep their order, which saves the nb x nb comparisons.)
-    for (int q = tid; q < nb; q += IVF_MAP_NT) {
-        if (flags) {
-            byrank[q] = (unsigned)q;
-            continue;
-        }
-        const unsigned u = un[q];
-        unsigned r = 0;
-        for (int o = 0; o < nb; ++o) {
-            const unsigned v = un[o];
-            r += (v > u || (v == u && o < q)) ? 1u : 0u;
-        }
-        byrank[r] = (unsigned)q;
-    }
-    __syncthreads();
-    // exclusive running sum of the workgroup counts in rank order
-    for (int r0 = 0; r0 < nb; r0 += IVF_MAP_NT) {
-        const int r = r0 + tid;
-        const unsigned w = r < nb ? wgs_of(un[byrank[r]]) : 0u;
-        unsigned inc = w;
-        const int l = lane_id();
+    constexpr int PER = IVF_MAP_MAXQ / IVF_MAP_NT;  // queries per thread, neighbours
+    __shared__ unsigned start[2][IVF_MAP_MAXQ];     // first workgroup of query q, or of those behind it
+    __shared__ unsigned total_s;
+    __shared__ unsigned long long usum[IVF_MAP_NT / WAVE];
+    __shared__ unsigned wsum[2][IVF_MAP_NT / WAVE];
+    const int tid = threadIdx.x, l = lane_id();
+    unsigned un[PER];
+    unsigned long long all = 0;
 #pragma unroll
-        for (int dd = 1; dd < WAVE; dd <<= 1) {
-            const unsigned up = __shfl_up(inc, dd);
-            if (l >= dd) inc += up;
-        }
-        if (l == WAVE - 1) wsum[tid / WAVE] = inc;
-        __syncthreads();
-        unsigned before = carry;
-        for (int wv = 0; wv < tid / WAVE; ++wv) before += wsum[wv];
-        if (r < nb) start[r] = before + inc - w;
-        __syncthreads();
-        if (tid == IVF_MAP_NT - 1) carry = before + inc;
-        __syncthreads();
+    for (int k = 0; k < PER; ++k) {
+        const int q = tid * PER + k;
+        un[k] = q < nb ? ((flags && flags[q] != 1u) ? qunits_alt[q] : qunits[q]) : 0u;
+        all += un[k];
     }
-    if (tid == 0) start[nb] = carry;
+#pragma unroll
+    for (int w = 32; w >= 1; w >>= 1) all += __shfl_xor(all, w);
+    if (l == 0) usum[tid / WAVE] = all;
     __syncthreads();
-    const unsigned total = start[nb];
+    all = 0;
+    for (int w = 0; w < IVF_MAP_NT / WAVE; ++w) all += usum[w];
+    const int units_per_wg = (int)max(1ull, min((unsigned long long)max_units, all / IVF_FILL_WGS));
+    // running sums of the workgroups, those of the queries with more than the average number of units apart: they come first
+    const unsigned average = (unsigned)(all / (unsigned long long)nb);
+    unsigned mine[2] = {0, 0}, cls[PER];
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+        cls[k] = un[k] > average ? 0u : 1u;
+        un[k] = tid * PER + k < nb ? min((unsigned)Wmax, max(1u, (un[k] + (unsigned)units_per_wg - 1u) / (unsigned)units_per_wg)) : 0u;
+        mine[0] += cls[k] == 0u ? un[k] : 0u;
+        mine[1] += cls[k] == 1u ? un[k] : 0u;
+    }
+    unsigned inc[2] = {mine[0], mine[1]};
+#pragma unroll
+    for (int dd = 1; dd < WAVE; dd <<= 1) {
+        const unsigned up0 = __shfl_up(inc[0], dd), up1 = __shfl_up(inc[1], dd);
+        if (l >= dd) { inc[0] += up0; inc[1] += up1; }
+    }
+    if (l == WAVE - 1) { wsum[0][tid / WAVE] = inc[0]; wsum[1][tid / WAVE] = inc[1]; }
+    __syncthreads();
+    unsigned at[2] = {inc[0] - mine[0], inc[1] - mine[1]}, first = 0;
+    for (int w = 0; w < IVF_MAP_NT / WAVE; ++w) {
+        if (w < tid / WAVE) { at[0] += wsum[0][w]; at[1] += wsum[1][w]; }
+        first += wsum[0][w];
+    }
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+        // (a query takes no room among those of the other kind)
+        const int q = tid * PER + k;
+        start[0][q] = at[0];
+        start[1][q] = first + at[1];
+        at[cls[k]] += un[k];
+    }
+    if (tid == IVF_MAP_NT - 1) total_s = first + at[1];
+    __syncthreads();
+    const unsigned total = total_s;
     const unsigned slots = (unsigned)nb * (unsigned)Wmax;
-    for (unsigned b = tid; b < slots; b += IVF_MAP_NT) {
+    for (unsigned b = blockIdx.x * IVF_MAP_NT + tid; b < slots; b += gridDim.x * IVF_MAP_NT) {
         unsigned v = IVF_NO_WG;
         if (b < total) {
-            int lo_r = 0, hi_r = nb;  // last rank whose first workgroup is <= b
-            while (hi_r - lo_r > 1) {
-                const int mid = (lo_r + hi_r) >> 1;
-                if (start[mid] <= b) lo_r = mid; else hi_r = mid;
+            const unsigned *s = start[b < first ? 0 : 1];
+            int lo_q = 0, hi_q = nb;  // last query whose first workgroup is <= b
+            while (hi_q - lo_q > 1) {
+                const int mid = (lo_q + hi_q) >> 1;
+                if (s[mid] <= b) lo_q = mid; else hi_q = mid;
             }
-            v = ((unsigned)(units_per_wg - 1) << 24) | (byrank[lo_r] << 12) | (b - start[lo_r]);
+            v = ((unsigned)(units_per_wg - 1) << 24) | ((unsigned)lo_q << 12) | (b - s[lo_q]);
         }
         wgmap[b] = v;
     }
@@ -1783,35 +1903,23 @@ int ivf_search(const qadc_ivf_index *ix, const float *queries, int nq, int nprob
                 rc = quantize_luts(16, luts, nb, nprobe, m, nullptr, 0, qmax, R, nbins, qmin_mode, qluts, nullptr,
                                    nullptr, nullptr, st);
         } else {
-            // Tables
-            bool batch_tables = nb >= 64;
-            if (batch_tables) {
-#define QADC_LUTS_CASE(D_)                                                                                       \
-    case D_:                                                                                                    \
-        launch(QADC_PROF_IVF_TABLES, ivf_build_luts_batch_kernel<D_>, dim3(nb), dim3(m * 16), 0, st, ix->codebooks, d, \
-               m, yq, ix->coarse, ix->halves, ix->cell_ids, ix->Kh, probes, nprobe, luts);                      \
-        break;
-                switch (d / m) {
-                    QADC_LUTS_CASE(2)
-                    QADC_LUTS_CASE(4)
-                    QADC_LUTS_CASE(6)
-                    QADC_LUTS_CASE(8)
-                    QADC_LUTS_CASE(16)
-                default:
-                    batch_tables = false;
-                }
-#undef QADC_LUTS_CASE
+            if (qmin_mode != QADC_QMIN_PER_TABLE && qmin_mode != QADC_QMIN_GLOBAL)
+                return fail(QADC_EINVAL, "qadc_ivf_search: qmin_mode=%d", qmin_mode);
+            // (a compute unit holds one workgroup of 1024 threads or two of 512: 300 queries x 64 cells 66 against 54 us)
+            const int nt = m == 64 || nb <= 256 ? 1024 : 512;
+#define QADC_TABLES_CASE(D_)                                                                                             \
+    launch(QADC_PROF_IVF_TABLES, ivf_tables_kernel<D_>, dim3(nb), dim3(nt), 0, st, ix->codebooks, d, m, yq, ix->coarse,  \
+           ix->halves, ix->cell_ids, ix->Kh, (const int32_t *)probes, nprobe, ix->list_off, ix->codes, ix->n, init, R,   \
+           nbins, qmin_mode, unit, qunits, qluts, scan_ws, p.stride, p.l.counts_off, p.W, p.countsA_off)
+            switch (d / m) {
+            case 2: QADC_TABLES_CASE(2); break;
+            case 4: QADC_TABLES_CASE(4); break;
+            case 6: QADC_TABLES_CASE(6); break;
+            case 8: QADC_TABLES_CASE(8); break;
+            case 16: QADC_TABLES_CASE(16); break;
+            default: QADC_TABLES_CASE(0);
             }
-            if (!batch_tables)
-                launch(QADC_PROF_IVF_TABLES, ivf_build_luts_kernel, dim3(nprobe, nb), dim3(256),
-                       (size_t)d * sizeof(double), st, ix->codebooks, d, m, yq, ix->coarse, ix->halves, ix->cell_ids,
-                       ix->Kh, probes, nprobe, luts);
-            // (a few queries: a thread per init code, so that the walk is one round of loads)
-            launch(QADC_PROF_IVF_TABLES, ivf_qmax_kernel, dim3(nb), dim3(nb <= 32 ? 1024 : 256), 0, st, ix->list_off, ix->codes,
-                   m, probes, nprobe, luts, init, R, qmax, unit, qunits, ix->n, scan_ws, p.stride, p.l.counts_off,
-                   p.W, p.countsA_off);
-            rc = quantize_luts(16, luts, nb, nprobe, m, nullptr, 0, qmax, R, nbins, qmin_mode, qluts, nullptr,
-                               nullptr, nullptr, st);
+#undef QADC_TABLES_CASE
         }
         if (rc != QADC_OK) return rc;
         // Scan: up to p.wgs workgroups per query, one per `upw` units of its lists (batches that fill
@@ -1862,7 +1970,7 @@ int ivf_search(const qadc_ivf_index *ix, const float *queries, int nq, int nprob
         // 4 queries 0.163 against 0.181, 8 queries 0.208 against 0.220, 12 the same, 16 slower)
         const bool wide_wgs = !mapped && nb <= knob_or(knobs().ivf_wide_q, IVF_WIDE_MAX_Q);
         if (mapped)
-            launch(QADC_PROF_SEED, ivf_wgmap_kernel, dim3(1), dim3(IVF_MAP_NT), 0, st, qunits, nb, upw, p.wgs, wgmap,
+            launch(QADC_PROF_SEED, ivf_wgmap_kernel, dim3(16), dim3(IVF_MAP_NT), 0, st, qunits, nb, upw, p.wgs, wgmap,
                    (const unsigned *)qunits_light, (const unsigned *)flags);
         const int hist_bound = (p.seed_per_list > 0 && seed_parts > 1) ? 1 : 0;
 #define QADC_IVF_CASE(B_)                                                                              \

@@ -428,7 +428,7 @@ __global__ __launch_bounds__(IVFS_REFINE_NT) void ivfs_refine_kernel(char *__res
 }
 
 // One wavefront per query, after the shared lists are scanned: the cells that are left to the
-// per-query kernel (-1 in the slots of the shared cells), their units of work as ivf_qmax_kernel
+// per-query kernel (-1 in the slots of the shared cells), their units of work as ivf_tables_kernel
 // counts them, and the query's tightened bound back into its control block for that kernel.
 __global__ __launch_bounds__(256) void ivfs_light_kernel(const int32_t *__restrict__ probes, int nprobe, int nb, int K,
                                                          const unsigned *__restrict__ pair_off, int min_pairs,

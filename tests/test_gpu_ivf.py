@@ -383,6 +383,34 @@ def test_ivf_few_queries_path_equals_batch_path(Q, O, mode):
             assert np.array_equal(d2[k].cpu().numpy(), rep["dist"]), (s, k)
 
 
+@pytest.mark.parametrize("m,d,nprobe,nq", [(8, 16, 150, 33), (8, 48, 20, 300), (16, 64, 70, 40), (16, 128, 140, 260), (16, 256, 9, 64),
+                                           (32, 64, 256, 34), (32, 96, 65, 257), (32, 256, 3, 33), (64, 128, 70, 40), (64, 64, 33, 520)])
+@pytest.mark.parametrize("mode", [0, 1])
+def test_ivf_tables_of_batches_equal_those_of_few_queries(Q, m, d, nprobe, nq, mode):
+    """Every sub-vector length with and without a form of its own, several cells at a time or one, more probed cells than a
+    thread keeps, unused slots, a walk over many short lists: the 8-bit tables of calls of a few queries (kernels of their
+    own), byte for byte, and the same neighbours; and of a query whose tables have no range (delta = 1)."""
+    import torch
+    g = torch.Generator(device="cuda:0")
+    g.manual_seed(m * d + nprobe)
+    rand = lambda *shape: torch.rand(shape, generator=g, device="cuda:0")
+    K, n, R, init = nprobe + 30, 40 * (nprobe + 30), 60, 700
+    coarse, cb = 100 * rand(K, d), 40 * rand(m, 16, d // m)
+    codes = torch.randint(0, 256, (n, m // 2), generator=g, device="cuda:0", dtype=torch.uint8)
+    off = torch.arange(K + 1, device="cuda:0") * 40
+    off[3] = off[4]
+    ix = Q.IvfIndex(coarse, off, codes, torch.arange(n, dtype=torch.int32, device="cuda:0"), cb)
+    queries = 100 * rand(nq, d)
+    queries[2] = 1e30
+    probes = torch.stack([torch.randperm(K, generator=g, device="cuda:0")[:nprobe] for _ in range(nq)]).int()
+    probes[1::3, nprobe // 2] = -1
+    ids, dist, pr, ql = Q.qadc_ivf_search(ix, queries, nprobe, R, init, qmin_mode=mode, probes_in=probes, debug=True)
+    for s in (0, 17, nq - 3):
+        i2, d2, p2, q2 = Q.qadc_ivf_search(ix, queries[s:s + 3].contiguous(), nprobe, R, init, qmin_mode=mode,
+                                           probes_in=probes[s:s + 3].contiguous(), debug=True)
+        assert torch.equal(q2, ql[s:s + 3]) and torch.equal(i2, ids[s:s + 3]) and torch.equal(d2, dist[s:s + 3]), s
+
+
 @pytest.mark.parametrize("m,n,nq,R", [(8, 60_000, 70, 100), (16, 400_003, 64, 100), (32, 1_000_001, 190, 40), (64, 900_001, 200, 200),
                                       (64, 2_400_003, 130, 1)])
 def test_ivf_batches_of_any_number_of_units_per_workgroup(Q, m, n, nq, R):
