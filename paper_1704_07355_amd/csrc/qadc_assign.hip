@@ -34,6 +34,7 @@
 // step in registers meanwhile: 15 to 25 % slower, they spill.)
 
 #include "qadc_common.h"
+#include "qadc_half.h"
 
 namespace qadc {
 
@@ -178,12 +179,6 @@ __device__ __forceinline__ bool assign_marked(int cell, int K, int accumulate)
 
 // ------------------------------------------------------------------ filter on the matrix units
 
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
-typedef unsigned bits16x8 __attribute__((ext_vector_type(4)));  // eight 16-bit numbers of either kind
-typedef float f32x8 __attribute__((ext_vector_type(8)));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
-
 constexpr int AF_MAX_D = 256;
 
 // hi + lo = v to 2^-18 relative
@@ -192,23 +187,6 @@ __device__ __forceinline__ void split_bf16(const f32x8 v, bits16x8 *hi, bits16x8
     const bf16x8 h = __builtin_convertvector(v, bf16x8);
     *hi = __builtin_bit_cast(bits16x8, h);
     *lo = __builtin_bit_cast(bits16x8, __builtin_convertvector(v - __builtin_convertvector(h, f32x8), bf16x8));
-}
-
-// eight consecutive components t .. t+7 of a row, zero at and beyond d
-template <bool VEC>
-__device__ __forceinline__ f32x8 load8(const float *row, int t, int d)
-{
-    f32x8 v;
-    if constexpr (VEC) {  // 16-byte aligned rows of whole steps
-        const float4 a = *reinterpret_cast<const float4 *>(row + t);
-        const float4 b = *reinterpret_cast<const float4 *>(row + t + 4);
-        v[0] = a.x; v[1] = a.y; v[2] = a.z; v[3] = a.w;
-        v[4] = b.x; v[5] = b.y; v[6] = b.z; v[7] = b.w;
-    } else {
-#pragma unroll
-        for (int e = 0; e < 8; ++e) v[e] = t + e < d ? row[t + e] : 0.0f;
-    }
-    return v;
 }
 
 // How the factors of the products are held.
@@ -242,13 +220,6 @@ struct FilterTile {
     int cand[S::TM][6];                               // groups to measure, -1: none; none after the first -1
 };
 
-// Vectors of scores below: Half is sure of scores up to HALF_FAR only, of vectors with |x'|^2 up to HALF_NEAR.
-constexpr float HALF_NEAR = 268435456.0f;   // 2^28
-constexpr float HALF_STRAY = 2147483648.0f; // 2^31: no component of a centroid below it leaves binary16
-constexpr float HALF_FAR = 5e8f;
-constexpr float HALF_CONV = 4400.0f;        // 2^12, and a sixteenth for what HALF_TINY pays for
-constexpr float HALF_TINY = 3e-4f;          // per component: conversions below the normal range of binary16, flushed or not
-
 // The cells of up to TM vectors by a workgroup; row(k): the row of x that is vector k, -1 for none.  store(row, cell) for a
 // vector that is decided, undecided(row) for one that is not.
 template <int NT, int KS, int NB, bool VEC, Factors F, typename Row, typename Store, typename Undecided>
@@ -267,24 +238,9 @@ __device__ __forceinline__ void filter_tile(FilterTile<NT, KS, NB, F> &sh, const
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int col = lane & 31, half = lane >> 5;
 
-    // The reference: per component, the middle of eight centroids of the range.  (Any vector would do; one amid the
-    // centroids keeps the norms, and with them the margins, small, and a few stray or non-finite ones do not move this.)
     float spread = 0.0f;
     for (int t = tid; t < D; t += NT) {
-        float v[8];
-#pragma unroll
-        for (int k = 0; k < 8; ++k) v[k] = t < d ? coarse[(size_t)((int64_t)k * K >> 3) * d + t] : 0.0f;
-#pragma unroll
-        for (int a = 0; a < 8; ++a)  // odd-even transposition sort (a NaN goes out at the first comparison)
-#pragma unroll
-            for (int b = a & 1; b + 1 < 8; b += 2) {
-                const float lo = fminf(v[b], v[b + 1]), hi = fmaxf(v[b], v[b + 1]);
-                v[b] = lo;
-                v[b + 1] = hi;
-            }
-        ref[t] = 0.5f * v[3] + 0.5f * v[4];
-        const float f = fmaxf(v[6] - ref[t], ref[t] - v[1]);  // how far the centroids are from it, but for one at either end
-        if (f < 3e38f) spread = fmaxf(spread, f);
+        ref[t] = reference_component(coarse, K, d, t, &spread);
     }
     if constexpr (HALF) {
 #pragma unroll
@@ -304,10 +260,7 @@ __device__ __forceinline__ void filter_tile(FilterTile<NT, KS, NB, F> &sh, const
 #pragma unroll
             for (int m = 32; m >= 1; m >>= 1) spread = fmaxf(spread, __shfl_xor(spread, m));
         }
-        // the power of two that takes it to 16 .. 32: a thousandth of that still has eleven bits, two thousand times as much
-        // is still in range
-        const int e = (int)(__float_as_uint(spread) >> 23) - 127;  // (-127: nothing at all, or less than 2^-126)
-        scale = __uint_as_float((unsigned)(127 + min(100, 4 - e)) << 23);
+        scale = half_scale(spread);
         __syncthreads();  // (nobody still reads the reference as it was)
         for (int t = tid; t < D; t += NT) ref[t] *= scale;
         __syncthreads();
@@ -352,14 +305,9 @@ __device__ __forceinline__ void filter_tile(FilterTile<NT, KS, NB, F> &sh, const
     //   Split: both eps |.|^2: the differences 4 2^-24; what the splits and the missing lo.lo leave out 3.1 2^-18; 3 D + 1
     //   additions of values up to 2 (|x'|^2 + |c'|^2) (3 D + 1) 2^-22 (2^-23 each: no assumption on how the matrix units
     //   round); the norms (D + 8) 2^-24; 1.28e-5 + 7.8e-7 D in all.
-    //   Half: the conversions leave ex = |x' - x^| and ec = |c' - c^| <= 2^-11 |c'|; 2 |x^.c^ - x'.c'| <= 2 ex |c^| + 2 |x'| ec,
-    //   and with 2 a b <= w a^2 + b^2 / w that is 2^12 ex^2 + 2^-11 |x'|^2 of the vector (ex is measured, mostly 0.4 2^-11 |x'|)
-    //   and (2^-12 + 2^-11) |c'|^2 of the centroid (ec is not: that would be two fifths of the conversion's work).  Should the
-    //   units take what is below the normal range, 2^-14, for zero: (e + 2^-14 sqrt D)^2 <= 17/16 e^2 + 17 D 2^-28, which is
-    //   HALF_CONV and HALF_TINY and a sixteenth on ec^2.  With the differences, D + 1 additions and the norms (1e-6 + 3.0e-7 D
-    //   of the square) 4.9e-4 + 3.0e-7 D of the vector's and 7.7e-4 + 3.0e-7 D of the centroid's.
-    constexpr float eps = HALF ? 5.1e-4f + 3.3e-7f * D : 1.5e-5f + 9e-7f * D;
-    constexpr float eps_c = HALF ? 7.9e-4f + 3.3e-7f * D : eps;
+    //   Half: see qadc_half.h.
+    constexpr float eps = HALF ? half_eps(D) : 1.5e-5f + 9e-7f * D;
+    constexpr float eps_c = HALF ? half_eps_c(D) : eps;
 
     // thread -> centroid and steps it converts: eight neighbouring lanes hold eight centroids (their
     // 16-byte LDS writes are contiguous), a centroid's threads lie in one wavefront

@@ -14,6 +14,7 @@
 #include <type_traits>
 #include <utility>
 
+#include "qadc_half.h"
 #include "qadc_scan_common.h"
 
 namespace qadc {
@@ -402,6 +403,61 @@ constexpr int IVF_SEL_NT = 1024;
 constexpr int IVF_SEL_CAP = 4096;
 constexpr int IVF_SEL_MAXBLK = 4096;  // runs of cells whose minima fit in LDS
 
+// The end of a selection, by a workgroup of IVF_SEL_NT threads after a barrier: of the cnt candidates (keys order(dist) <<
+// 32 | cell) in LDS -- of the whole row of distances where there are more than fit -- the `need` smallest in order, and
+// unused slots behind them.
+__device__ __forceinline__ void probes_of_candidates(const float *dq, int K, int nprobe, unsigned need, uint64_t *cand,
+                                                     unsigned &cnt, SelectScratch &sc, int32_t *__restrict__ probes)
+{
+    constexpr int NT = IVF_SEL_NT;
+    const int tid = threadIdx.x;
+    const unsigned ncand = cnt;
+    const bool in_lds = ncand <= (unsigned)IVF_SEL_CAP;
+    __syncthreads();
+
+    auto each_row = [&](auto f) {
+        for (int c = tid; c < K; c += NT) f(((uint64_t)f2ord(dq[c]) << 32) | (uint64_t)(unsigned)c);
+    };
+    if (ncand <= (unsigned)NT) {
+        // a thread per candidate: its rank among all of them is its place among the probes
+        if ((unsigned)tid < ncand) {
+            const uint64_t k = cand[tid];
+            unsigned rank = 0;
+            for (unsigned j = 0; j < ncand; ++j) rank += (cand[j] < k) ? 1u : 0u;
+            if (rank < need) probes[rank] = (int32_t)(unsigned)k;
+        }
+        for (unsigned i = need + tid; i < (unsigned)nprobe; i += NT) probes[i] = -1;
+        return;  // uniform
+    }
+    uint64_t kth;
+    if (in_lds) kth = block_radix_select<uint64_t, 8>(cand, ncand, need, &sc);
+    else kth = block_radix_select_each<uint64_t, 8>(each_row, need, &sc);
+    // the winners (exactly `need`: keys are unique), ordered by rank
+    __shared__ uint64_t sel[IVF_MAX_NPROBE];
+    if (tid == 0) cnt = 0;
+    __syncthreads();
+    if (in_lds) {
+        for (unsigned i = tid; i < ncand; i += NT)
+            if (cand[i] <= kth) sel[atomicAdd(&cnt, 1u)] = cand[i];
+    } else {
+        each_row([&](uint64_t k) {
+            if (k <= kth) sel[atomicAdd(&cnt, 1u)] = k;
+        });
+    }
+    __syncthreads();
+    for (unsigned i = tid; i < (unsigned)nprobe; i += NT) {
+        if (i >= need) {
+            probes[i] = -1;
+        } else {
+            const uint64_t k = sel[i];
+            unsigned rank = 0;
+            for (unsigned j = 0; j < need; ++j) rank += (sel[j] < k) ? 1u : 0u;
+            probes[rank] = (int32_t)(unsigned)k;
+        }
+    }
+}
+
+
 __global__ __launch_bounds__(IVF_SEL_NT) void ivf_select_probes_kernel(
     const float *__restrict__ dist, int K, int nprobe, int32_t *__restrict__ probes,
     const unsigned *__restrict__ blockmin, int nblk, IvfClear clr)
@@ -505,50 +561,132 @@ __global__ __launch_bounds__(IVF_SEL_NT) void ivf_select_probes_kernel(
     }
     }
     __syncthreads();
-    const unsigned ncand = cnt;
-    const bool in_lds = ncand <= (unsigned)IVF_SEL_CAP;
-    __syncthreads();
+    probes_of_candidates(dq, K, nprobe, need, cand, cnt, sc, probes + (size_t)q * nprobe);
+}
 
-    auto each_row = [&](auto f) {
-        for (int c = tid; c < K; c += NT) f(((uint64_t)f2ord(dq[c]) << 32) | (uint64_t)(unsigned)c);
-    };
-    if (ncand <= (unsigned)NT) {
-        // a thread per candidate: its rank among all of them is its place among the probes
-        if ((unsigned)tid < ncand) {
-            const uint64_t k = cand[tid];
-            unsigned rank = 0;
-            for (unsigned j = 0; j < ncand; ++j) rank += (cand[j] < k) ? 1u : 0u;
-            if (rank < need) probes[(size_t)q * nprobe + rank] = (int32_t)(unsigned)k;
+// What ivf_filter_row says.
+__device__ __forceinline__ const uint16_t *filter_row(const float *dist, int K, size_t i)
+{
+    return reinterpret_cast<const uint16_t *>((reinterpret_cast<uintptr_t>(dist + i * (size_t)K) + 15) & ~(uintptr_t)15);
+}
+
+// The same from the bounds of qadc_ivf_filter.hip, one per group of four cells, in the query's row of `dist`: any T that `need`
+// groups do not exceed bounds the need-th smallest score (as above, the need-th smallest of the threads' minima), and with
+// the rounding of the scores and of float32 distances (components + 4 roundings of 2^-24) the scores of all cells among the
+// `need` closest.  The cells of those groups -- some 70 groups for 64 probes -- are measured by the definition
+// (ivf_coarse_dist_kernel's operations in its order), a thread per cell.  A query that this cannot serve (beyond the range of
+// the factors, too many groups as close, a NaN anywhere) is measured against all cells.
+constexpr int IVF_SEL_GROUPS = IVF_SEL_CAP / 4;
+
+__global__ __launch_bounds__(IVF_SEL_NT) void ivf_select_filtered_kernel(
+    const float *__restrict__ coarse, int K, int d, const float *__restrict__ queries, float *__restrict__ dist,
+    const float2 *__restrict__ qstat, int components, int nprobe, int32_t *__restrict__ probes, int vec4)
+{
+    constexpr int NT = IVF_SEL_NT;
+    __shared__ SelectScratch sc;
+    __shared__ uint64_t cand[IVF_SEL_CAP];
+    __shared__ unsigned small_s[NT];
+    __shared__ unsigned groups[IVF_SEL_GROUPS];
+    __shared__ __attribute__((aligned(16))) float ys[256];
+    __shared__ unsigned cnt, ngroup;
+    const int tid = threadIdx.x;
+    const int q = blockIdx.x;
+    const unsigned need = (unsigned)min(nprobe, K);
+    const int tiles = (K + 31) / 32;
+    if (tid < d) ys[tid] = queries[(size_t)q * d + tid];
+    const float2 stat = qstat[q];
+    const unsigned *row = reinterpret_cast<const unsigned *>(filter_row(dist, K, (size_t)q));  // two bounds a word
+    auto order = [](unsigned b) { return (b & 0x8000u) ? ~b & 0xffffu : b | 0x8000u; };
+    auto each_pair = [&](auto f) {  // f(first group, its key, the next one's key)
+        for (int i0 = tid; i0 < 4 * tiles; i0 += 8 * NT) {
+            unsigned w[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) w[u] = i0 + u * NT < 4 * tiles ? row[i0 + u * NT] : 0x7f807f80u;
+#pragma unroll
+            for (int u = 0; u < 8; ++u)
+                if (i0 + u * NT < 4 * tiles) f(2 * (i0 + u * NT), order(w[u] & 0xffffu), order(w[u] >> 16));
         }
-        for (unsigned i = need + tid; i < (unsigned)nprobe; i += NT) probes[(size_t)q * nprobe + i] = -1;
-        return;  // uniform
-    }
-    uint64_t kth;
-    if (in_lds) kth = block_radix_select<uint64_t, 8>(cand, ncand, need, &sc);
-    else kth = block_radix_select_each<uint64_t, 8>(each_row, need, &sc);
-    // the winners (exactly `need`: keys are unique), ordered by rank
-    __shared__ uint64_t sel[IVF_MAX_NPROBE];
-    if (tid == 0) cnt = 0;
-    __syncthreads();
-    if (in_lds) {
-        for (unsigned i = tid; i < ncand; i += NT)
-            if (cand[i] <= kth) sel[atomicAdd(&cnt, 1u)] = cand[i];
-    } else {
-        each_row([&](uint64_t k) {
-            if (k <= kth) sel[atomicAdd(&cnt, 1u)] = k;
+    };
+    unsigned mine = 0xffffu;
+    each_pair([&](int, unsigned k0, unsigned k1) { mine = min(mine, min(k0, k1)); });
+    const int nmin = min(NT, 4 * tiles);  // (at least `need`: the host sees to it)
+    small_s[tid] = mine;
+    if (tid == 0) { cnt = 0; ngroup = 0; }
+    const bool nan = __syncthreads_or(mine <= order(0xff80u));  // minus infinity: a centroid with a NaN
+    const unsigned T = block_radix_select_each<unsigned, 2>(
+        [&](auto f) {
+            if (tid < nmin) f(small_s[tid]);
+        },
+        need, &sc);
+    auto value = [](unsigned o) { return __uint_as_float(((o & 0x8000u) ? o & 0x7fffu : ~o & 0xffffu) << 16); };
+    const float up = value(T + 1u);  // no bound that was rounded to T is beyond the next bfloat16
+    const float xn = stat.x, tiny = HALF_TINY * (float)components;
+    const float xerr = __builtin_fmaf(half_eps(components), xn, __builtin_fmaf(HALF_CONV, stat.y, tiny));
+    const float far = 1.05f * (__builtin_sqrtf(xn) + __builtin_sqrtf(fmaxf(up + xerr + 2.0f * tiny, 0.0f)));
+    const float cerr = __builtin_fmaf(1.01f * half_eps_c(components), far * far, tiny);
+    const float reach = up + xerr + 2.002f * cerr;  // squared distance (scaled) of the need-th closest cell, at most
+    const float thr = __builtin_fmaf(reach, 2e-7f * (float)(components + 4), reach) + 1.001f * xerr;
+    // (comparisons that a NaN fails)
+    const bool sure = !nan && T < 0xff7fu && xn < HALF_NEAR && up - xn < HALF_FAR && thr < 4.0f * HALF_FAR;  // uniform
+    if (sure) {
+        const __bf16 rounded = (__bf16)thr;
+        const unsigned last = order(__builtin_bit_cast(uint16_t, rounded));
+        each_pair([&](int g, unsigned k0, unsigned k1) {
+            if (min(k0, k1) <= last) {
+                if (k0 <= last) {
+                    const unsigned slot = atomicAdd(&ngroup, 1u);
+                    if (slot < (unsigned)IVF_SEL_GROUPS) groups[slot] = (unsigned)g;
+                }
+                if (k1 <= last) {
+                    const unsigned slot = atomicAdd(&ngroup, 1u);
+                    if (slot < (unsigned)IVF_SEL_GROUPS) groups[slot] = (unsigned)g + 1u;
+                }
+            }
         });
     }
     __syncthreads();
-    for (unsigned i = tid; i < (unsigned)nprobe; i += NT) {
-        if (i >= need) {
-            probes[(size_t)q * nprobe + i] = -1;
+    const unsigned ng = ngroup;
+    const bool served = sure && ng <= (unsigned)IVF_SEL_GROUPS;  // uniform
+    auto measure = [&](int c) {
+        const float *cr = coarse + (size_t)c * d;
+        float acc = 0.0f;
+        if (vec4) {  // uniform
+#pragma unroll 8
+            for (int t = 0; t < d; t += 4) {
+                const float4 v = *reinterpret_cast<const float4 *>(cr + t);
+                const float4 y = *reinterpret_cast<const float4 *>(&ys[t]);
+                float df = y.x - v.x;
+                acc = fmaf(df, df, acc);
+                df = y.y - v.y;
+                acc = fmaf(df, df, acc);
+                df = y.z - v.z;
+                acc = fmaf(df, df, acc);
+                df = y.w - v.w;
+                acc = fmaf(df, df, acc);
+            }
         } else {
-            const uint64_t k = sel[i];
-            unsigned rank = 0;
-            for (unsigned j = 0; j < need; ++j) rank += (sel[j] < k) ? 1u : 0u;
-            probes[(size_t)q * nprobe + rank] = (int32_t)(unsigned)k;
+#pragma unroll 8
+            for (int t = 0; t < d; ++t) {
+                const float df = ys[t] - cr[t];
+                acc = fmaf(df, df, acc);
+            }
         }
+        return acc;
+    };
+    float *dq = dist + (size_t)q * K;
+    if (served) {
+        for (unsigned i = tid; i < 4u * ng; i += NT) {
+            const unsigned g = groups[i >> 2];  // place 8 tile + 4 half + k: cells 32 tile + 8 k + 4 half + 0 .. 3
+            const int c = (int)((g >> 3) * 32u + (g & 3u) * 8u + ((g >> 2) & 1u) * 4u + (i & 3u));
+            if (c < K) cand[atomicAdd(&cnt, 1u)] = ((uint64_t)f2ord(measure(c)) << 32) | (uint64_t)(unsigned)c;
+        }
+    } else {
+        for (int c = tid; c < K; c += NT) dq[c] = measure(c);  // (the bounds in that row are done with)
+        if (tid == 0) cnt = IVF_SEL_CAP + 1;
+        __threadfence_block();
     }
+    __syncthreads();
+    probes_of_candidates(dq, K, nprobe, need, cand, cnt, sc, probes + (size_t)q * nprobe);
 }
 
 // rows of `dist` [rows][K] -> out[rows][count]: the count smallest of each row, smallest first
@@ -1659,6 +1797,10 @@ __global__ void ivf_take_probes_kernel(const int32_t *__restrict__ in, int nprob
 
 int quantize_luts(int, const float *, int, int, int, const uint8_t *, int64_t, const float *, int, int,
                   int, uint8_t *, float *, float *, float *, hipStream_t);
+size_t ivf_filter_bytes(int K, int d, int nq);
+bool ivf_filter_pays(int K, int d, int nq, int nprobe);
+void ivf_filter_convert(const float *coarse, int K, int d, const float *queries, int nq, void *room, hipStream_t st);
+const float2 *ivf_filter(int K, int d, int nq, int i0, int ni, void *room, float *dist, int *components, hipStream_t st);
 
 struct IvfPlan {
     int qb, W;
@@ -1874,9 +2016,22 @@ int ivf_search(const qadc_ivf_index *ix, const float *queries, int nq, int nprob
                    dim3((unsigned)std::max<int64_t>(ceil_div(np_total, 256), front ? nb : 0)), dim3(256), 0, st,
                    probes_in + (size_t)q0 * nprobe, nprobe, K, np_total, probes, clr, nb);
         } else {
-            for (int i0 = 0; i0 < nb; i0 += p.qd) {
-                const int ni = min(p.qd, nb - i0);
+            // large calls: bounds from the matrix units first (their factors lie where calls of a few queries keep tables)
+            const bool filtered = (p.qd >= 32 || p.qd >= nb) && ivf_filter_pays(K, d, nb, nprobe) &&
+                                  ivf_filter_bytes(K, d, nb) <= (size_t)p.qb * nprobe * m * 16 * 4;
+            if (filtered) ivf_filter_convert(ix->coarse, K, d, yq, nb, luts, st);
+            const int pass = filtered && p.qd < nb ? p.qd / 32 * 32 : p.qd;
+            for (int i0 = 0; i0 < nb; i0 += pass) {
+                const int ni = min(pass, nb - i0);
                 const float *yi = yq + (size_t)i0 * d;
+                if (filtered) {
+                    int components = 0;
+                    const float2 *qstat = ivf_filter(K, d, nb, i0, ni, luts, dist, &components, st);
+                    const int vec4 = d % 4 == 0 && ((uintptr_t)ix->coarse & 15) == 0;
+                    launch(QADC_PROF_IVF_INDEX, ivf_select_filtered_kernel, dim3(ni), dim3(IVF_SEL_NT), 0, st, ix->coarse,
+                           K, d, yi, dist, qstat, components, nprobe, probes + (size_t)i0 * nprobe, vec4);
+                    continue;
+                }
                 // the minima of the runs of IVF_CT cells go with the distances, and the selection reads
                 // only the runs that matter (when there are enough runs)
                 unsigned *bmin = nullptr;

@@ -542,6 +542,48 @@ def test_cells_do_not_depend_on_the_batch(Q, O, K, d, nq):
         assert torch.equal(probes[iq], one[0]), iq
 
 
+@pytest.mark.parametrize("K,d,nq,nprobe", [(4097, 128, 520, 32), (8200, 40, 900, 7), (16_390, 96, 190, 100), (20_000, 250, 64, 64),
+                                           (65_537, 64, 1100, 24), (4096, 17, 4000, 1)])
+@pytest.mark.parametrize("kind", ["mixture", "ties", "one place", "not a number", "far"])
+def test_cells_of_calls_that_take_the_matrix_units(Q, K, d, nq, nprobe, kind):
+    """Bounds from 11-bit factors choose which cells are measured: the cells are those of calls of a few queries, in the same
+    order, whatever the factors can tell: cells equally close (lowest id first), all but some in one place, NaN of both
+    signs and infinities among the centroids, centroids and queries beyond the factors' range; the last run and tile of
+    cells ragged, several passes, sub-vectors of any length."""
+    import torch
+    g = torch.Generator(device="cuda:0")
+    g.manual_seed(K + nq)
+    randn = lambda *shape: torch.randn(shape, generator=g, device="cuda:0")
+    coarse = 30 * randn(40, d)[torch.randint(0, 40, (K,), generator=g, device="cuda:0")] + 20 * randn(K, d)
+    queries = coarse[torch.randint(0, K, (nq,), generator=g, device="cuda:0")] + 15 * randn(nq, d)
+    if kind == "ties":
+        coarse, queries = (coarse / 40).round(), (queries / 40).round()
+    elif kind == "one place":
+        coarse[: K - 50] = coarse[0].clone()
+    elif kind == "not a number":
+        coarse[5, 3], coarse[K // 2, 0], coarse[K - 1, d - 1] = float("nan"), -float("nan"), float("inf")
+        coarse[77] = torch.from_numpy(np.full(d, 0xFFC00000, dtype=np.uint32).view(np.float32)).to("cuda:0")
+    elif kind == "far":
+        coarse[::500] *= 1e7
+        coarse[7] *= 1e30
+        queries[::40] *= 1e6
+        queries[3, 0] = float("inf")
+    m = 16 if d % 16 == 0 and d % 32 else 8 if d % 8 == 0 else None
+    if m is None:  # the factors' components are padded; a product quantizer's are not
+        pad = 8 - d % 8
+        coarse, queries = (torch.nn.functional.pad(v, (0, pad)) for v in (coarse, queries))
+        d, m = d + pad, 8
+    cb = 10 * randn(m, 16, d // m)
+    n = 5000
+    off = torch.minimum(torch.arange(K + 1, device="cuda:0"), torch.tensor(n, device="cuda:0"))
+    codes = torch.randint(0, 256, (n, m // 2), generator=g, device="cuda:0", dtype=torch.uint8)
+    ix = Q.IvfIndex(coarse.contiguous(), off, codes, torch.arange(n, dtype=torch.int32, device="cuda:0"), cb)
+    cells = lambda y: Q.qadc_ivf_search(ix, y.contiguous(), nprobe, 5, 50, debug=True)[2]
+    got = cells(queries)
+    for s in (0, 32, nq // 2, nq - 32):
+        assert torch.equal(cells(queries[s:s + 32]), got[s:s + 32]), s
+
+
 @pytest.mark.parametrize("K,d,nq", [(9001, 32, 500), (32_767, 24, 129)])
 def test_cells_of_an_odd_number_do_not_depend_on_the_batch(Q, O, K, d, nq):
     """The tiled distance kernel over an odd number of cells: rows of distances that start off an 8-byte boundary."""
