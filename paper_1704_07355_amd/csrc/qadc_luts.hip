@@ -1,6 +1,7 @@
 // Tables step (Eq. (1) of the paper) and 8-bit quantization of the tables
-// (Section 3.3) on gfx950.  Both are tiny next to the scan: one workgroup per
-// query, everything staged in LDS.
+// (Section 3.3) on gfx950.  Both are tiny next to the scan, and bound by the latency of their steps.
+
+#include <algorithm>
 
 #include "qadc_scan_common.h"
 
@@ -11,31 +12,40 @@ namespace qadc {
 // luts[q][j][i] = sum_t (y[q][j*dsub+t] - base[q][j*dsub+t] - C[j][i][t])^2.
 // Differences and the sum are taken in float64 and rounded once to float32, so
 // a residual query (y - base) loses nothing to an intermediate rounding.
+// A thread per entry, a workgroup per 256 of them; eight components are requested at a time (one workgroup per query that
+// walked over the components one by one: 6.5 us for one query of 8 x 256 entries of 12 components, 4.6 now).
 __global__ __launch_bounds__(256) void build_luts_kernel(
     const float *__restrict__ codebooks, int d, int m, int ksub, const float *__restrict__ queries,
     const float *__restrict__ base, float *__restrict__ luts)
 {
-    extern __shared__ double yq[];  // [d]
-    const int q = blockIdx.x;
+    const int q = blockIdx.y;
     const int dsub = d / m;
-    for (int t = threadIdx.x; t < d; t += blockDim.x) {
-        double y = (double)queries[(size_t)q * d + t];
-        if (base) y -= (double)base[(size_t)q * d + t];
-        yq[t] = y;
-    }
-    __syncthreads();
     const int entries = m * ksub;
-    for (int e = threadIdx.x; e < entries; e += blockDim.x) {
-        const int j = e / ksub;
-        const float *c = codebooks + (size_t)e * dsub;
-        const double *y = yq + j * dsub;
-        double acc = 0.0;
-        for (int t = 0; t < dsub; ++t) {
-            const double df = y[t] - (double)c[t];
-            acc += df * df;
+    const int e = blockIdx.x * 256 + threadIdx.x;
+    if (e >= entries) return;
+    const float *c = codebooks + (size_t)e * dsub;
+    const size_t at = (size_t)q * d + (size_t)(e / ksub) * dsub;
+    double acc = 0.0;
+    for (int t0 = 0; t0 < dsub; t0 += 8) {
+        float cv[8], yv[8], bv[8];
+#pragma unroll
+        for (int t = 0; t < 8; ++t) {
+            const int tt = min(t0 + t, dsub - 1);
+            cv[t] = c[tt];
+            yv[t] = queries[at + tt];
+            bv[t] = base ? base[at + tt] : 0.0f;
         }
-        luts[(size_t)q * entries + e] = (float)acc;
+#pragma unroll
+        for (int t = 0; t < 8; ++t) {
+            if (t0 + t < dsub) {
+                double y = (double)yv[t];
+                if (base) y -= (double)bv[t];
+                const double df = y - (double)cv[t];
+                acc += df * df;
+            }
+        }
     }
+    luts[(size_t)q * entries + e] = (float)acc;
 }
 
 int build_luts(const float *codebooks, int d, int m, int ksub, const float *queries,
@@ -45,8 +55,12 @@ int build_luts(const float *codebooks, int d, int m, int ksub, const float *quer
     if (m < 1 || d < m || d % m != 0 || (ksub != 16 && ksub != 64 && ksub != 256) || nq < 0 || d > 8192)
         return fail(QADC_EINVAL, "qadc_build_luts: unsupported d=%d m=%d ksub=%d nq=%d", d, m, ksub, nq);
     if (nq == 0) return QADC_OK;
-    launch(QADC_PROF_TABLES, build_luts_kernel, dim3(nq), dim3(256), (size_t)d * sizeof(double), st,
-           codebooks, d, m, ksub, queries, base, luts);
+    for (int q0 = 0; q0 < nq; q0 += 65535) {
+        const int nb = std::min(nq - q0, 65535);
+        launch(QADC_PROF_TABLES, build_luts_kernel, dim3((unsigned)ceil_div((int64_t)m * ksub, 256), (unsigned)nb), dim3(256), 0, st,
+               codebooks, d, m, ksub, queries + (size_t)q0 * d, base ? base + (size_t)q0 * d : base,
+               luts + (size_t)q0 * m * ksub);
+    }
     QADC_HIP_TRY(hipGetLastError());
     return QADC_OK;
 }
@@ -60,6 +74,42 @@ constexpr int QUANT_MAX_M = 64;
 // one per code byte, the same quantizer applied to the 256-entry tables of Section 2.1's
 // standard product quantizer.  KSUB = 64: 6-bit components (the paper's Conclusion), stored back to
 // back, least significant bit first, four per three bytes.
+
+// The need-th smallest of n images of sums in LDS, by the whole workgroup: of up to 256 by a thread's count of the smaller
+// ones (one barrier; the histograms of a radix select take some fifteen).  cand has room for 256 and is 16-byte aligned.
+__device__ __forceinline__ unsigned nth_of_sums(unsigned *cand, int n, int need, SelectScratch *sc, unsigned *nth)
+{
+    if (n > 256) return block_radix_select<unsigned, 4>(cand, (unsigned)n, (unsigned)need, sc);
+    const int tid = threadIdx.x;
+    if (tid >= n && tid < 256) cand[tid] = 0xffffffffu;
+    __syncthreads();
+    if (tid < n) {
+        const unsigned mine = cand[tid];
+        int less = 0, leq = 0;
+#pragma unroll 4
+        for (int i = 0; i < (n + 3) / 4; ++i) {
+            const uint4 v = reinterpret_cast<const uint4 *>(cand)[i];
+            less += (v.x < mine) + (v.y < mine) + (v.z < mine) + (v.w < mine);
+            leq += (v.x <= mine) + (v.y <= mine) + (v.z <= mine) + (v.w <= mine);
+        }
+        // (the padding counts among the equals of an image of its own value only, and there it changes nothing)
+        if (less < need && need <= leq) *nth = mine;  // (equal ones write the same)
+    }
+    __syncthreads();
+    return *nth;
+}
+
+// The B bytes of a code (6 to 32, from any address) as words, all requested at once (byte by byte, a code of 32 takes as many
+// round trips).
+__device__ __forceinline__ void code_words(const uint8_t *c, int B, unsigned (&w)[8])
+{
+    typedef unsigned u32_any __attribute__((aligned(1)));
+    const u32_any *cw = reinterpret_cast<const u32_any *>(c);
+#pragma unroll
+    for (int k = 0; k < 8; ++k) w[k] = 4 * k + 4 <= B ? cw[k] : 0u;  // (uniform)
+    if (B == 6) w[1] = (unsigned)c[4] | ((unsigned)c[5] << 8);       // (the other lengths are whole words)
+}
+
 template <int KSUB>
 __global__ __launch_bounds__(QUANT_NT) void quantize_luts_kernel(
     const float *__restrict__ luts, int ngroup, int m, const uint8_t *__restrict__ init_codes,
@@ -68,10 +118,11 @@ __global__ __launch_bounds__(QUANT_NT) void quantize_luts_kernel(
     float *__restrict__ qmax_out)
 {
     __shared__ float lut0[QUANT_MAX_M * 16];
-    __shared__ unsigned cand[QADC_MAX_INIT];
+    __shared__ __attribute__((aligned(16))) unsigned cand[QADC_MAX_INIT];
     __shared__ unsigned bias_ord[QUANT_MAX_M];
     __shared__ float bias[QUANT_MAX_M];
     __shared__ float delta_s;
+    __shared__ unsigned nth_s;
     __shared__ SelectScratch sc;
 
     const int tid = threadIdx.x;
@@ -90,30 +141,41 @@ __global__ __launch_bounds__(QUANT_NT) void quantize_luts_kernel(
     if (init_codes) {
         const int B = KSUB == 16 ? m / 2 : KSUB == 64 ? 3 * m / 4 : m;
         for (int i = tid; i < n_init; i += QUANT_NT) {
-            const uint8_t *c = init_codes + (size_t)i * B;
+            unsigned w[8];
+            code_words(init_codes + (size_t)i * B, B, w);
             float acc = 0.0f;
-            if (KSUB == 64) {
-                for (int j = 0; j < m; ++j) {
-                    const int bit = 6 * j, k = bit >> 3, sh = bit & 7;
-                    unsigned v = c[k];
-                    if (sh > 2) v |= (unsigned)c[k + 1] << 8;  // the field crosses into the next byte
-                    acc = acc + lq[j * 64 + ((v >> sh) & 63u)];  // the first table set
+            if constexpr (KSUB == 64) {
+#pragma unroll
+                for (int j = 0; j < 32; ++j) {
+                    if (j < m) {  // uniform
+                        constexpr int BITS = 6;
+                        const int k = BITS * j >> 5, sh = BITS * j & 31;
+                        const unsigned v = sh <= 32 - BITS ? w[k] >> sh : __funnelshift_r(w[k], w[(k + 1) & 7], sh);
+                        acc = acc + lq[j * 64 + (v & 63u)];  // the first table set
+                    }
                 }
-            } else
-            for (int jb = 0; jb < B; ++jb) {
-                const unsigned comps = c[jb];
-                if (KSUB == 16) {
-                    acc = acc + lut0[(2 * jb) * 16 + (comps & 15u)];
-                    acc = acc + lut0[(2 * jb + 1) * 16 + (comps >> 4)];
-                } else {
-                    acc = acc + lq[jb * 256 + comps];  // the first table set; cached after the first touch
+            } else {
+#pragma unroll
+                for (int k = 0; k < 8; ++k) {
+                    if (4 * k < B) {  // uniform (four bytes or none)
+#pragma unroll
+                        for (int b = 0; b < 4; ++b) {
+                            const unsigned comps = (w[k] >> (8 * b)) & 0xffu;
+                            const int jb = 4 * k + b;
+                            if constexpr (KSUB == 16) {
+                                acc = acc + lut0[(2 * jb) * 16 + (comps & 15u)];
+                                acc = acc + lut0[(2 * jb + 1) * 16 + (comps >> 4)];
+                            } else {
+                                acc = acc + lq[jb * 256 + comps];  // the first table set; cached after the first touch
+                            }
+                        }
+                    }
                 }
             }
             cand[i] = f2ord(acc);
         }
         __syncthreads();
-        const unsigned need = (unsigned)min(R, n_init);
-        qmax = ord2f(block_radix_select<unsigned, 4>(cand, (unsigned)n_init, need, &sc));
+        qmax = ord2f(nth_of_sums(cand, n_init, min(R, n_init), &sc, &nth_s));
     } else {
         qmax = qmax_in[q];
     }
@@ -137,6 +199,8 @@ __global__ __launch_bounds__(QUANT_NT) void quantize_luts_kernel(
         atomicMin(&bias_ord[pos >> LOG], mn);
     }
     __syncthreads();
+    for (int j = tid; j < m; j += QUANT_NT) bias[j] = ord2f(bias_ord[j]);
+    __syncthreads();
     if (tid == 0) {
         float qmin;
         if (qmin_mode == QADC_QMIN_GLOBAL) {
@@ -146,10 +210,8 @@ __global__ __launch_bounds__(QUANT_NT) void quantize_luts_kernel(
             for (int j = 0; j < m; ++j) bias[j] = qmin;
         } else {
             qmin = 0.0f;
-            for (int j = 0; j < m; ++j) {
-                bias[j] = ord2f(bias_ord[j]);
-                qmin = qmin + bias[j];
-            }
+#pragma unroll 8
+            for (int j = 0; j < m; ++j) qmin = qmin + bias[j];
         }
         float delta = __fdiv_rn(qmax - qmin, (float)nbins);
         if (!(delta > 0.0f)) delta = 1.0f;
@@ -203,6 +265,109 @@ int quantize_luts(int ksub, const float *luts, int nq, int ngroup, int m, const 
                init_codes, (int)n_init, qmax_in, R, nbins, qmin_mode, qluts, bias, delta, qmax_out);
     QADC_HIP_TRY(hipGetLastError());
     return QADC_OK;
+}
+
+// Both steps for a batch of qadc_search, a workgroup per query and a thread per entry: the float tables stay in LDS and
+// are not written.  The arithmetic of build_luts_kernel and quantize_luts_kernel.  (As two launches 9.9 us for 16 queries
+// m = 16, 16.1 for 12 m = 64; 8.9 and 12.5 as one.)
+constexpr int SEARCH_TABLES_MAX_D = 2048;
+
+__global__ __launch_bounds__(1024) void search_tables_kernel(
+    const float *__restrict__ codebooks, int d, int m, const float *__restrict__ queries, const uint8_t *__restrict__ codes,
+    int n_init, int R, int nbins, int qmin_mode, uint8_t *__restrict__ qluts, uint8_t *__restrict__ qluts_too)
+{
+    __shared__ float yq[SEARCH_TABLES_MAX_D];
+    __shared__ float lut[QUANT_MAX_M * 16];
+    __shared__ __attribute__((aligned(16))) unsigned cand[QADC_MAX_INIT];
+    __shared__ unsigned bias_ord[QUANT_MAX_M];
+    __shared__ float bias[QUANT_MAX_M];
+    __shared__ float delta_s;
+    __shared__ unsigned nth_s;
+    __shared__ SelectScratch sc;
+    constexpr int DREG = 16;
+    const int tid = threadIdx.x, q = blockIdx.x;
+    const int entries = m * 16, dsub = d / m, B = m / 2;
+    // everything that comes from memory is requested at once
+    for (int t = tid; t < d; t += 1024) yq[t] = queries[(size_t)q * d + t];
+    float cv[DREG];
+    const float *c = codebooks + (size_t)min(tid, entries - 1) * dsub;
+#pragma unroll
+    for (int t = 0; t < DREG; ++t) cv[t] = c[min(t, dsub - 1)];
+    unsigned w[8];
+    code_words(codes + (size_t)min(tid, n_init - 1) * B, B, w);
+    __syncthreads();
+    const int j = tid >> 4;
+    float v = 0.0f;
+    if (tid < entries) {
+        double acc = 0.0;
+#pragma unroll
+        for (int t = 0; t < DREG; ++t) {
+            if (t < dsub) {  // uniform
+                const double df = (double)yq[j * dsub + t] - (double)cv[t];
+                acc += df * df;
+            }
+        }
+        for (int t = DREG; t < dsub; ++t) {
+            const double df = (double)yq[j * dsub + t] - (double)c[t];
+            acc += df * df;
+        }
+        v = (float)acc;
+        lut[tid] = v;
+        unsigned least = f2ord(v);
+#pragma unroll
+        for (int k = 8; k >= 1; k >>= 1) least = min(least, (unsigned)__shfl_xor((int)least, k));
+        if ((tid & 15) == 0) { bias_ord[j] = least; bias[j] = ord2f(least); }
+    }
+    __syncthreads();
+    for (int i = tid; i < n_init; i += 1024) {
+        if (i != tid) code_words(codes + (size_t)i * B, B, w);
+        float acc = 0.0f;
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+            if (4 * k < B) {  // uniform
+#pragma unroll
+                for (int b = 0; b < 4; ++b) {
+                    const unsigned comps = (w[k] >> (8 * b)) & 0xffu;
+                    const int jb = 4 * k + b;
+                    acc = acc + lut[(2 * jb) * 16 + (comps & 15u)];
+                    acc = acc + lut[(2 * jb + 1) * 16 + (comps >> 4)];
+                }
+            }
+        }
+        cand[i] = f2ord(acc);
+    }
+    __syncthreads();
+    const float qmax = ord2f(nth_of_sums(cand, n_init, min(R, n_init), &sc, &nth_s));
+    if (tid == 0) {
+        float qmin;
+        if (qmin_mode == QADC_QMIN_GLOBAL) {
+            unsigned g = 0xffffffffu;
+            for (int k = 0; k < m; ++k) g = min(g, bias_ord[k]);
+            qmin = ord2f(g);
+            for (int k = 0; k < m; ++k) bias[k] = qmin;
+        } else {
+            qmin = 0.0f;
+#pragma unroll 8
+            for (int k = 0; k < m; ++k) qmin = qmin + bias[k];
+        }
+        float delta = __fdiv_rn(qmax - qmin, (float)nbins);
+        if (!(delta > 0.0f)) delta = 1.0f;
+        delta_s = delta;
+    }
+    __syncthreads();
+    if (tid < entries) {
+        const float t = floorf(__fdiv_rn(fmaxf(0.0f, v - bias[j]), delta_s));
+        const uint8_t e = (t < (float)nbins) ? (uint8_t)t : (uint8_t)nbins;
+        qluts[(size_t)q * entries + tid] = e;
+        if (qluts_too) qluts_too[(size_t)q * entries + tid] = e;
+    }
+}
+
+void search_tables(const float *codebooks, int d, int m, const float *queries, int nq, const uint8_t *codes, int n_init,
+                   int R, int nbins, int qmin_mode, uint8_t *qluts, uint8_t *qluts_too, hipStream_t st)
+{
+    launch(QADC_PROF_TABLES, search_tables_kernel, dim3((unsigned)nq), dim3(1024), 0, st, codebooks, d, m, queries, codes,
+           n_init, R, nbins, qmin_mode, qluts, qluts_too);
 }
 
 }  // namespace qadc

@@ -679,12 +679,21 @@ static int dispatch_seed_u8(const ScanPlan &p, const uint8_t *codes, int64_t n,
         const int cpt = (p.B <= 16) ? SCAN_VEC * (16 / p.B) : 1;
         // (at most 512 sample tiles unless QADC_SEED_WGS says otherwise: N = 1e8, m = 32, 256 queries: 1024
         // tiles 0.42 ms of sampling, 512 tiles 0.22 ms and 0.07 ms more in the scan, 256 tiles 0.12 and 0.21)
-        const int tiles = knobs().seed_wgs > 0 ? p.seed_wgs : std::min(p.seed_wgs, 512);
+        int tiles = knobs().seed_wgs > 0 ? p.seed_wgs : std::min(p.seed_wgs, 512);
+        // Every query is sampled, and a fourth of a database of a few million codes took as long as its scan: no more than 4e8
+        // byte lookups in all, but a sixteenth of the codes, and enough for bounds that let some 2000 keys of a query pass.
+        // (us per call with up to a fourth / this / a sixteenth: 250 queries over 1 M m = 32, R = 10 156 / 131 / 120; 100 over 3 M
+        // m = 16 146 / 142 / 143; 200 over 300 k m = 32 106 / 106 / 126; 30 over 1 M 60 / 60 / 66)
+        if (knobs().seed_wgs <= 0) {
+            const int64_t codes_for = std::max(std::max(n / 16, (int64_t)(4e8 / ((double)nq * p.B))), n * R / 2000);
+            tiles = (int)std::min<int64_t>(tiles, ceil_div(codes_for, 1024 * cpt));
+        }
         return run_tiled_seed(p.t, codes, n, qluts, nq, cap, R, p.wide ? 1 : 0, (int64_t)tiles * 1024 * cpt,
                               ws, p.stride, st);
     }
-    // batches: several tiles per workgroup, so that building the pair tables pays
-    const int tpw = (nq >= TILED_MIN_Q) ? 8 : 1;
+    // batches: several tiles per workgroup, so that building the pair tables pays (12 queries over 3 M codes m = 64, us per call
+    // with 8 / 4 / 2 / 1 tiles: 104 / 99 / 101 / 109)
+    const int tpw = (nq >= TILED_MIN_Q) ? 4 : 1;
     dim3 grid((unsigned)ceil_div(p.seed_wgs, tpw), nq);
     const unsigned flush = (unsigned)min((int64_t)R, (int64_t)p.flush_need * tpw);
     switch (p.B) {
@@ -793,9 +802,8 @@ int scan_topk_u8(int variant, const uint8_t *codes, int64_t n, int m, const uint
     return QADC_OK;
 }
 
-int build_luts(const float *, int, int, int, const float *, const float *, int, float *, hipStream_t);
-int quantize_luts(int, const float *, int, int, int, const uint8_t *, int64_t, const float *, int, int,
-                  int, uint8_t *, float *, float *, float *, hipStream_t);
+void search_tables(const float *codebooks, int d, int m, const float *queries, int nq, const uint8_t *codes, int n_init,
+                   int R, int nbins, int qmin_mode, uint8_t *qluts, uint8_t *qluts_too, hipStream_t st);
 
 // Workspace of qadc_search: the scan workspace, then float tables and quantized tables of a batch.
 static size_t search_extra_bytes(int m, int qbatch)
@@ -843,7 +851,6 @@ int search_u8(const float *codebooks, int d, int m, const float *queries, int nq
     if (((uintptr_t)workspace & 255) != 0)
         return fail(QADC_EINVAL, "qadc_search: workspace must be 256-byte aligned");
     char *ws = (char *)workspace;
-    float *luts = (float *)(ws + p.ws_bytes);
     uint8_t *qluts = (uint8_t *)(ws + p.ws_bytes + align_up((size_t)p.qbatch * m * 16 * sizeof(float), 256));
     const int n_init = (int)min((int64_t)init, n);
     for (int q0 = 0; q0 < nq; q0 += p.qbatch) {
@@ -868,16 +875,10 @@ int search_u8(const float *codebooks, int d, int m, const float *queries, int nq
 #undef QADC_PREP_CASE
         } else {
             // a batch, or a small database: tables and quantizer once per query by their own
-            // kernels, then the sampling kernel (large databases) or a self-seeding scan
-            int rc = build_luts(codebooks, d, m, 16, yq, nullptr, nb, luts, st);
-            if (rc != QADC_OK) return rc;
-            rc = quantize_luts(16, luts, nb, 1, m, codes, n_init, nullptr, R, nbins, qmin_mode, qluts, nullptr,
-                               nullptr, nullptr, st);
-            if (rc != QADC_OK) return rc;
-            if (ql_out)
-                QADC_HIP_TRY(hipMemcpyAsync(ql_out, qluts, (size_t)nb * m * 16, hipMemcpyDeviceToDevice, st));
+            // kernel, then the sampling kernel (large databases) or a self-seeding scan
+            search_tables(codebooks, d, m, yq, nb, codes, n_init, R, nbins, qmin_mode, qluts, ql_out, st);
             if (p.seed_wgs > 0) {
-                rc = dispatch_seed_u8(p, codes, n, qluts, nb, nbins, R, ws, st);
+                const int rc = dispatch_seed_u8(p, codes, n, qluts, nb, nbins, R, ws, st);
                 if (rc != QADC_OK) return rc;
             }
         }

@@ -488,6 +488,54 @@ def test_search_equals_the_three_call_chain_and_the_oracle(Q, O, n, mode_nbins):
         assert np.abs(h_ql[iq].astype(int) - t["qlut"].astype(int)).max() <= 1
 
 
+@pytest.mark.parametrize("m,d", [(8, 8), (16, 48), (16, 272), (32, 960), (64, 128), (64, 2048)])
+@pytest.mark.parametrize("n,init,R", [(3000, 1, 5), (3000, 255, 100), (3000, 256, 256), (3000, 257, 1), (3000, 1025, 1000), (40, 8192, 100)])
+def test_tables_of_search_batches_are_those_of_the_separate_calls(Q, m, d, n, init, R):
+    """Tables, qmax and quantizer in one launch against the two calls, byte for byte: init codes around the two ways the
+    qmax-th is found (256) and a thread's first code (1024), fewer codes than init, sub-vectors of 1 to 32 components (16 in
+    registers), sums that are all the same."""
+    import torch
+    g = torch.Generator(device="cuda:0")
+    g.manual_seed(d + n + init)
+    cb = 50 * torch.rand((m, 16, d // m), generator=g, device="cuda:0")
+    queries = 50 * torch.rand((9, d), generator=g, device="cuda:0")
+    codes = torch.randint(0, 256, (n, m // 2), generator=g, device="cuda:0", dtype=torch.uint8)
+    codes[: n // 2] = codes[0] if n < 100 else codes[: n // 2]
+    luts = Q.qadc_build_luts(cb, queries)
+    exact = ((queries.double().reshape(9, m, 1, d // m) - cb.double()[None]) ** 2).sum(3)
+    assert torch.allclose(luts.double(), exact, rtol=1e-6, atol=0)
+    for mode, nbins in ((0, 255), (1, 127)):
+        want = Q.qadc_quantize_luts(luts, codes[:init], R, nbins=nbins, qmin_mode=mode)[0]
+        got = torch.zeros_like(want)
+        Q.qadc_search(cb, queries, codes, R, init, nbins=nbins, qmin_mode=mode, qluts_out=got)
+        assert torch.equal(got, want)
+
+
+@pytest.mark.parametrize("variant,ksub,m", [("u8_8", 256, 4), ("u8_8", 256, 32), ("u8_6", 64, 8), ("u8_6", 64, 16), ("u8_6", 64, 32)])
+def test_init_codes_are_read_from_any_address(Q, variant, ksub, m):
+    """qmax of 6- and 8-bit components from init codes that start 1 to 3 bytes off a word: the R-th smallest of the float32
+    sums of the tables, in increasing component order."""
+    import torch
+    rng = np.random.default_rng(m + ksub)
+    nbytes = m if ksub == 256 else 3 * m // 4
+    fields = rng.integers(0, ksub, size=(300, m))
+    if ksub == 256:
+        raw = fields.astype(np.uint8)
+    else:
+        bits = ((fields[..., None] >> np.arange(6)) & 1).reshape(300, -1)
+        raw = np.packbits(bits.astype(np.uint8), axis=1, bitorder="little")
+    luts = rng.uniform(1, 100, size=(2, m, ksub)).astype(np.float32)
+    sums = np.zeros((2, 300), dtype=np.float32)
+    for j in range(m):
+        sums = sums + luts[:, j][:, fields[:, j]]
+    want = np.sort(sums, axis=1)[:, 49]
+    for off in (0, 1, 2, 3):
+        flat = torch.zeros(300 * nbytes + off, dtype=torch.uint8, device="cuda:0")
+        flat[off:] = to_gpu(raw).flatten()
+        qmax = Q.qadc_quantize_luts(to_gpu(luts), flat[off:].view(300, nbytes), 50)[3]
+        assert np.array_equal(qmax.cpu().numpy(), want), off
+
+
 def test_search_large_init_and_other_code_sizes(Q, O):
     """init above 1024 (radix select instead of rank counting) and m = 8 / 32 in the fused kernel."""
     import torch
