@@ -721,9 +721,11 @@ __global__ __launch_bounds__(1024) void ivf_tables_kernel(
     int Kh, const int32_t *__restrict__ probes, int nprobe, const int64_t *__restrict__ list_off,
     const uint8_t *__restrict__ codes, int64_t n_total, int init, int R, int nbins, int qmin_mode, long long unit,
     unsigned *__restrict__ qunits, uint8_t *__restrict__ qluts, char *__restrict__ ws, size_t ws_stride,
-    size_t counts_off, int W, size_t countsA_off)
+    size_t counts_off, int W, size_t countsA_off, unsigned *__restrict__ pair_cnt, int K)
 {
     ivf_clear_control(ws + (size_t)blockIdx.x * ws_stride, counts_off, W, countsA_off);
+    if (pair_cnt)  // the shared-list scan's counts of pairs per cell, taken by the kernel after this one
+        for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < K; i += (int64_t)gridDim.x * blockDim.x) pair_cnt[i] = 0;
     __shared__ unsigned cand[QADC_MAX_INIT];
     __shared__ float lut_s[IVF_WALK][1024];
     __shared__ unsigned units_s;
@@ -1163,12 +1165,18 @@ constexpr int IVF_SEED_NT = 1024;
 constexpr int IVF_SEED_PROBES = 16;  // closest cells whose lists are sampled
 constexpr int IVF_SEED_PCH = 32;  // probed cells whose tables are in LDS at a time
 
+// What the shared-list scan starts from (cnt null: there is none): the pairs of every cell, the queries' bounds and flags.
+struct IvfPairs {
+    unsigned *cnt, *taus, *flags;
+    int K;
+};
+
 template <int B>
 __global__ __launch_bounds__(IVF_SEED_NT) void ivf_seed_kernel(
     const int64_t *__restrict__ list_off, const uint8_t *__restrict__ codes,
     const int32_t *__restrict__ probes, int nprobe, const uint8_t *__restrict__ qluts, int cap_i,
     int R, int per_list, char *__restrict__ ws, size_t ws_stride, int64_t n_total, int long_shift, int nseed,
-    IvfQuantizer fq)
+    IvfQuantizer fq, IvfPairs pairs)
 {
     constexpr int NT = IVF_SEED_NT;
     constexpr int TAB = 2 * B * 16;  // bytes of one cell's quantized tables
@@ -1265,7 +1273,17 @@ __global__ __launch_bounds__(IVF_SEED_NT) void ivf_seed_kernel(
 #pragma unroll
         for (int b = 0; b < 4; ++b) h[b] = hist[4 * tid + b];
         const unsigned t = wave_threshold_bin<4>(h, (unsigned)R);
-        if (tid == 0) hdr->ghist[0][0] = (t < 256u) ? t + 1u : 0u;
+        if (tid == 0) {
+            hdr->ghist[0][0] = (t < 256u) ? t + 1u : 0u;
+            if (pairs.cnt) {
+                pairs.taus[q] = (t < 256u) ? t : IVFS_NONE;
+                pairs.flags[q] = (t < 256u) ? 2u : 1u;  // 2: shared lists there, the others by the per-query kernel; 1: all by that one
+            }
+        }
+    }
+    if (pairs.cnt && tid < nprobe) {
+        const int cell = probes[(size_t)q * nprobe + tid];
+        if (cell >= 0 && cell < pairs.K) atomicAdd(&pairs.cnt[cell], 1u);
     }
 }
 
@@ -1779,19 +1797,27 @@ __global__ __launch_bounds__(NT) void ivf_scan_kernel(
 // Cells given by the caller: a cell outside [0, K) and a cell that an earlier slot of the same
 // query already names become unused slots (-1) -- a list is scanned once, so that keys stay
 // unique, and nothing outside list_off is read.
-__global__ void ivf_take_probes_kernel(const int32_t *__restrict__ in, int nprobe, int K, int64_t total,
+__global__ __launch_bounds__(256) void ivf_take_probes_kernel(const int32_t *__restrict__ in, int nprobe, int K, int64_t total,
                                        int32_t *__restrict__ probes, IvfClear clr, int nq)
 {
     if (clr.scan_ws && (int)blockIdx.x < nq) {  // uniform: workgroup b also clears the control words of query b
         ivf_clear_control(clr.scan_ws + (size_t)blockIdx.x * clr.ws_stride, clr.counts_off, clr.W, clr.countsA_off);
     }
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    // (the workgroup's cells and those before them in the first one's row go through LDS: from memory, one after the other,
+    // 64 cells took 7.4 us)
+    __shared__ int32_t near[256 + IVF_MAX_NPROBE];
+    const int64_t b0 = (int64_t)blockIdx.x * 256, i = b0 + threadIdx.x;
+    const int64_t from = b0 / nprobe * nprobe, upto = min(b0 + 256, total);
+    for (int64_t o = from + threadIdx.x; o < upto; o += 256) near[o - from] = in[o];
+    __syncthreads();
     if (i >= total) return;
     const int64_t row = i / nprobe * nprobe;
-    int cell = in[i];
+    int cell = near[i - from];
     if (cell < 0 || cell >= K) cell = -1;
-    for (int64_t o = row; cell >= 0 && o < i; ++o)
-        if (in[o] == cell) cell = -1;
+    bool seen = false;
+#pragma unroll 8
+    for (int o = (int)(row - from); o < (int)(i - from); ++o) seen |= near[o] == cell;
+    if (seen) cell = -1;
     probes[i] = cell;
 }
 
@@ -2067,7 +2093,8 @@ int ivf_search(const qadc_ivf_index *ix, const float *queries, int nq, int nprob
 #define QADC_TABLES_CASE(D_)                                                                                             \
     launch(QADC_PROF_IVF_TABLES, ivf_tables_kernel<D_>, dim3(nb), dim3(nt), 0, st, ix->codebooks, d, m, yq, ix->coarse,  \
            ix->halves, ix->cell_ids, ix->Kh, (const int32_t *)probes, nprobe, ix->list_off, ix->codes, ix->n, init, R,   \
-           nbins, qmin_mode, unit, qunits, qluts, scan_ws, p.stride, p.l.counts_off, p.W, p.countsA_off)
+           nbins, qmin_mode, unit, qunits, qluts, scan_ws, p.stride, p.l.counts_off, p.W, p.countsA_off,                 \
+           p.shared ? (unsigned *)(ws + p.off_paircnt) : (unsigned *)nullptr, K)
             switch (d / m) {
             case 2: QADC_TABLES_CASE(2); break;
             case 4: QADC_TABLES_CASE(4); break;
@@ -2093,11 +2120,13 @@ int ivf_search(const qadc_ivf_index *ix, const float *queries, int nq, int nprob
         // codes, and the sample is most of the seed kernel's cost
         const int nseed = std::min(nprobe, std::max(1, knob_or(knobs().ivf_seed_probes, IVF_SEED_PROBES)));
         unsigned *flags = p.shared ? (unsigned *)(ws + p.off_flags) : nullptr;
+        IvfPairs pairs = {nullptr, nullptr, nullptr, 0};
+        if (p.shared) pairs = IvfPairs{(unsigned *)(ws + p.off_paircnt), (unsigned *)(ws + p.off_taus), flags, K};
 #define QADC_IVF_SEED_CASE(B_)                                                                          \
     case B_:                                                                                           \
         launch(QADC_PROF_SEED, ivf_seed_kernel<B_>, dim3(nb, seed_parts), dim3(IVF_SEED_NT), 0, st,    \
                ix->list_off, ix->codes, probes, nprobe, qluts, nbins, R, p.seed_per_list, scan_ws,     \
-               p.stride, ix->n, p.shared ? 8 : 0, nseed, fq);                                          \
+               p.stride, ix->n, p.shared ? 8 : 0, nseed, fq, pairs);                                   \
         break;
         if (p.seed_per_list > 0) {
             switch (m / 2) {

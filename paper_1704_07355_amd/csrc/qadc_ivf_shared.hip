@@ -29,7 +29,6 @@
 
 namespace qadc {
 
-constexpr unsigned IVFS_NONE = 0xffffffffu;
 constexpr int IVFS_CHUNK_MIN = 128, IVFS_CHUNK_MAX = 2048;  // codes of a list per work item
 constexpr int IVFS_CHUNK_LONG = 4096;                       // ... of one list that alone fills the GPU (below 2^24)
 constexpr long long IVFS_LIST_ITEMS = 8192;
@@ -62,31 +61,6 @@ __host__ __device__ inline long long ivfs_lead(long long n)
 {
     long long s = ((n + 15) / 16 + 31) / 32 * 32;
     return s < n ? s : n;
-}
-
-__global__ __launch_bounds__(256) void ivfs_zero_kernel(unsigned *__restrict__ p, int64_t n)
-{
-    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (i < n) p[i] = 0;
-}
-
-// One thread per (query, probe slot): counts the pairs of every cell; the thread of a query's
-// first slot copies the query's bound and sets its flag (IVFS_NONE and 1 when the seed kernel found none).
-__global__ __launch_bounds__(256) void ivfs_count_kernel(const int32_t *__restrict__ probes, int nprobe,
-                                                         int64_t npairs, int K, const char *__restrict__ ws,
-                                                         size_t ws_stride, unsigned *__restrict__ pair_cnt,
-                                                         unsigned *__restrict__ taus, unsigned *__restrict__ flags)
-{
-    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (i >= npairs) return;
-    const int cell = probes[i];
-    if (cell >= 0 && cell < K) atomicAdd(&pair_cnt[cell], 1u);
-    if (i % nprobe == 0) {
-        const int64_t q = i / nprobe;
-        const unsigned tau1 = reinterpret_cast<const ScanHeader *>(ws + (size_t)q * ws_stride)->ghist[0][0];
-        taus[q] = tau1 ? tau1 - 1u : IVFS_NONE;
-        flags[q] = tau1 ? 2u : 1u;  // 2: shared lists here, the others by the per-query kernel; 1: all by that one
-    }
 }
 
 // Exclusive running sums over the cells of (pairs, work items of the leading parts, work items of the
@@ -160,17 +134,32 @@ __global__ __launch_bounds__(IVFS_OFF_NT) void ivfs_offsets_add_kernel(int K, co
     __shared__ unsigned base_s[3], all_s[3];
     const int tid = threadIdx.x;
     const int nblk = gridDim.x;
-    if (tid < 3) { base_s[tid] = 0; all_s[tid] = 0; }
-    __syncthreads();
-    for (int b = tid; b < nblk; b += IVFS_OFF_NT) {  // at most 256 workgroups: one round
+    if (tid < WAVE) {  // (an LDS atomic per total: 10 us for 190 workgroups, 5 now)
+        unsigned base[3] = {0, 0, 0}, all[3] = {0, 0, 0};
+        for (int b0 = 0; b0 < nblk; b0 += 4 * WAVE) {  // at most 256 workgroups: one round
+            unsigned t[4][3];
 #pragma unroll
-        for (int k = 0; k < 3; ++k) {
-            const unsigned t = blk[k * nblk + b];
-            if (t) {
-                if (b < (int)blockIdx.x) atomicAdd(&base_s[k], t);
-                atomicAdd(&all_s[k], t);
-            }
+            for (int u = 0; u < 4; ++u)
+#pragma unroll
+                for (int k = 0; k < 3; ++k) t[u][k] = b0 + u * WAVE + tid < nblk ? blk[k * nblk + b0 + u * WAVE + tid] : 0u;
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+#pragma unroll
+                for (int k = 0; k < 3; ++k) {
+                    all[k] += t[u][k];
+                    if (b0 + u * WAVE + tid < (int)blockIdx.x) base[k] += t[u][k];
+                }
         }
+#pragma unroll
+        for (int w = 32; w >= 1; w >>= 1)
+#pragma unroll
+            for (int k = 0; k < 3; ++k) {
+                base[k] += __shfl_xor(base[k], w);
+                all[k] += __shfl_xor(all[k], w);
+            }
+        if (tid == 0)
+#pragma unroll
+            for (int k = 0; k < 3; ++k) { base_s[k] = base[k]; all_s[k] = all[k]; }
     }
     __syncthreads();
     const int c = blockIdx.x * IVFS_OFF_NT + tid;
@@ -377,72 +366,27 @@ __global__ __launch_bounds__(64) void ivfs_scan_kernel(
     }
 }
 
-// One workgroup per query, between the two parts of the scan: the R-th smallest sum among the
-// keys reported so far replaces the query's bound when it is tighter, and only the keys within the
-// new bound stay in the region (the others cannot be among the R best).
+// One workgroup per query, between the two parts of the scan.  What is left to the per-query kernel: the query's cells with
+// -1 in the slots of the shared ones, and their units of work as ivf_tables_kernel counts them.  Then the bound: the R-th
+// smallest sum among the keys reported so far replaces it when it is tighter, only the keys within the new bound stay in the
+// region (the others cannot be among the R best), and it goes to the query's control block for the per-query kernel.
 constexpr int IVFS_REFINE_NT = 256;
-__global__ __launch_bounds__(IVFS_REFINE_NT) void ivfs_refine_kernel(char *__restrict__ ws, size_t ws_stride,
-                                                                     size_t countsA_off, size_t listsA_off,
-                                                                     int pitchA, int R, unsigned *__restrict__ taus,
-                                                                     const unsigned *__restrict__ flags)
+__global__ __launch_bounds__(IVFS_REFINE_NT) void ivfs_refine_kernel(
+    char *__restrict__ ws, size_t ws_stride, size_t countsA_off, size_t listsA_off, int pitchA, int R,
+    unsigned *__restrict__ taus, const unsigned *__restrict__ flags, const int32_t *__restrict__ probes, int nprobe, int K,
+    const unsigned *__restrict__ pair_off, int min_pairs, const int64_t *__restrict__ list_off, int64_t n_total,
+    long long unit, int32_t *__restrict__ probes_light, unsigned *__restrict__ qunits_light)
 {
     constexpr int NT = IVFS_REFINE_NT;
     __shared__ uint64_t lkeys[MERGE_CAP];
     __shared__ unsigned hist[256];
-    __shared__ unsigned tnew, kept;
+    __shared__ unsigned tnew, kept, units_s;
     const int q = blockIdx.x, tid = threadIdx.x;
-    if (flags[q] == 1u || pitchA > MERGE_CAP) return;  // uniform
-    char *base = ws + (size_t)q * ws_stride;
-    unsigned *counts = reinterpret_cast<unsigned *>(base + countsA_off);
-    const unsigned c = counts[0];
-    if (c < (unsigned)R || c > (unsigned)pitchA) return;  // uniform
-    uint64_t *keys = reinterpret_cast<uint64_t *>(base + listsA_off);
+    if (tid == 0) { tnew = 256u; kept = 0; units_s = 0; }
     for (int i = tid; i < 256; i += NT) hist[i] = 0;
-    if (tid == 0) { tnew = 256u; kept = 0; }
     __syncthreads();
-    for (unsigned i = tid; i < c; i += NT) {
-        const uint64_t k = keys[i];
-        lkeys[i] = k;
-        atomicAdd(&hist[(unsigned)(k >> 32) & 255u], 1u);
-    }
-    __syncthreads();
-    if (tid < WAVE) {
-        unsigned h[4];
-#pragma unroll
-        for (int b = 0; b < 4; ++b) h[b] = hist[4 * tid + b];
-        const unsigned t = wave_threshold_bin<4>(h, (unsigned)R);
-        if (tid == 0) tnew = t;
-    }
-    __syncthreads();
-    const unsigned t = tnew;
-    if (t >= 256u || t >= taus[q]) return;  // uniform: no tighter bound
-    for (unsigned i = tid; i < c; i += NT) {
-        const uint64_t k = lkeys[i];
-        if (((unsigned)(k >> 32) & 255u) <= t) keys[atomicAdd(&kept, 1u)] = k;
-    }
-    __syncthreads();
-    if (tid == 0) {
-        taus[q] = t;
-        counts[0] = kept;
-    }
-}
-
-// One wavefront per query, after the shared lists are scanned: the cells that are left to the
-// per-query kernel (-1 in the slots of the shared cells), their units of work as ivf_tables_kernel
-// counts them, and the query's tightened bound back into its control block for that kernel.
-__global__ __launch_bounds__(256) void ivfs_light_kernel(const int32_t *__restrict__ probes, int nprobe, int nb, int K,
-                                                         const unsigned *__restrict__ pair_off, int min_pairs,
-                                                         const int64_t *__restrict__ list_off, int64_t n_total,
-                                                         long long unit, const unsigned *__restrict__ flags,
-                                                         const unsigned *__restrict__ taus, char *__restrict__ ws,
-                                                         size_t ws_stride, int32_t *__restrict__ probes_light,
-                                                         unsigned *__restrict__ qunits_light)
-{
-    const int q = blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (q >= nb) return;  // whole wavefront
-    const int lane = threadIdx.x & 63;
     unsigned units = 0;
-    for (int p = lane; p < nprobe; p += 64) {
+    for (int p = tid; p < nprobe; p += NT) {
         int cell = probes[(size_t)q * nprobe + p];
         if (cell >= 0 && cell < K && pair_off[cell + 1] - pair_off[cell] >= (unsigned)min_pairs) cell = -1;
         probes_light[(size_t)q * nprobe + p] = cell;
@@ -453,11 +397,44 @@ __global__ __launch_bounds__(256) void ivfs_light_kernel(const int32_t *__restri
     }
 #pragma unroll
     for (int s = 32; s >= 1; s >>= 1) units += __shfl_xor(units, s);
-    if (lane == 0) {
-        qunits_light[q] = units;
-        if (flags[q] == 2u && taus[q] != IVFS_NONE)
-            reinterpret_cast<ScanHeader *>(ws + (size_t)q * ws_stride)->ghist[0][0] = taus[q] + 1u;
+    if ((tid & 63) == 0 && units) atomicAdd(&units_s, units);
+    char *base = ws + (size_t)q * ws_stride;
+    unsigned *counts = reinterpret_cast<unsigned *>(base + countsA_off);
+    uint64_t *keys = reinterpret_cast<uint64_t *>(base + listsA_off);
+    const unsigned tau = taus[q], c = counts[0];
+    const bool bounded = flags[q] != 1u && tau != IVFS_NONE;                                          // uniform
+    const bool look = flags[q] != 1u && pitchA <= MERGE_CAP && c >= (unsigned)R && c <= (unsigned)pitchA;  // uniform
+    if (look) {
+        for (unsigned i = tid; i < c; i += NT) {
+            const uint64_t k = keys[i];
+            lkeys[i] = k;
+            atomicAdd(&hist[(unsigned)(k >> 32) & 255u], 1u);
+        }
     }
+    __syncthreads();
+    if (tid == 0) qunits_light[q] = units_s;
+    if (look && tid < WAVE) {
+        unsigned h[4];
+#pragma unroll
+        for (int b = 0; b < 4; ++b) h[b] = hist[4 * tid + b];
+        const unsigned t = wave_threshold_bin<4>(h, (unsigned)R);
+        if (tid == 0) tnew = t;
+    }
+    __syncthreads();
+    const unsigned t = tnew;
+    const bool tighter = look && t < 256u && t < tau;  // uniform
+    if (tighter) {
+        for (unsigned i = tid; i < c; i += NT) {
+            const uint64_t k = lkeys[i];
+            if (((unsigned)(k >> 32) & 255u) <= t) keys[atomicAdd(&kept, 1u)] = k;
+        }
+        __syncthreads();
+        if (tid == 0) {
+            taus[q] = t;
+            counts[0] = kept;
+        }
+    }
+    if (tid == 0 && bounded) reinterpret_cast<ScanHeader *>(base)->ghist[0][0] = (tighter ? t : tau) + 1u;
 }
 
 // The shared part of the scan of one batch (after the seed kernel): pairs by cell, the two parts
@@ -473,9 +450,6 @@ int ivf_shared_scan(int B, const int64_t *list_off, const uint8_t *codes, int64_
     const int64_t npairs = (int64_t)nb * nprobe;
     const int chunk = ivfs_chunk((double)npairs * (double)n_total / (double)K);
     const unsigned pgrid = (unsigned)ceil_div(npairs, 256);
-    launch(QADC_PROF_SEED, ivfs_zero_kernel, dim3((unsigned)ceil_div(K, 256)), dim3(256), 0, st, pair_cnt, (int64_t)K);
-    launch(QADC_PROF_SEED, ivfs_count_kernel, dim3(pgrid), dim3(256), 0, st, probes, nprobe, npairs, K,
-           (const char *)scan_ws, ws_stride, pair_cnt, taus, flags);
     const unsigned ogrid = (unsigned)ceil_div(K, IVFS_OFF_NT);
     unsigned *blk = pair_cnt + (size_t)K + 1;  // (the region of pair_cnt has room for 3 x 256 totals behind it)
     launch(QADC_PROF_SEED, ivfs_offsets_kernel, dim3(ogrid), dim3(IVFS_OFF_NT), 0, st, (const unsigned *)pair_cnt,
@@ -491,7 +465,8 @@ int ivf_shared_scan(int B, const int64_t *list_off, const uint8_t *codes, int64_
                nprobe, qluts, (const unsigned *)taus, scan_ws, ws_stride, countsA_off, listsA_off, pitchA,     \
                flags);                                                                                         \
         launch(QADC_PROF_SEED, ivfs_refine_kernel, dim3((unsigned)nb), dim3(IVFS_REFINE_NT), 0, st, scan_ws,    \
-               ws_stride, countsA_off, listsA_off, pitchA, R, taus, (const unsigned *)flags);                  \
+               ws_stride, countsA_off, listsA_off, pitchA, R, taus, (const unsigned *)flags, probes, nprobe, K,        \
+               (const unsigned *)pair_off, min_pairs, list_off, n_total, unit, probes_light, qunits_light);    \
         launch(QADC_PROF_IVF_SHARED, ivfs_scan_kernel<B_>, dim3((unsigned)wgs), dim3(64), 0, st, 1, chunk, list_off, codes,  \
                n_total, K, (const unsigned *)pair_off, (const unsigned *)item_off1, (const unsigned *)pairs,   \
                nprobe, qluts, (const unsigned *)taus, scan_ws, ws_stride, countsA_off, listsA_off, pitchA,     \
@@ -506,9 +481,6 @@ int ivf_shared_scan(int B, const int64_t *list_off, const uint8_t *codes, int64_
         return fail(QADC_EINVAL, "qadc_ivf_search: %d code bytes", B);
     }
 #undef QADC_IVFS_CASE
-    launch(QADC_PROF_SEED, ivfs_light_kernel, dim3((unsigned)ceil_div(nb, 4)), dim3(256), 0, st, probes, nprobe, nb, K,
-           (const unsigned *)pair_off, min_pairs, list_off, n_total, unit, (const unsigned *)flags,
-           (const unsigned *)taus, scan_ws, ws_stride, probes_light, qunits_light);
     QADC_HIP_TRY(hipGetLastError());
     return QADC_OK;
 }

@@ -13,6 +13,7 @@ constexpr int SCAN_VEC = 2;               // 16-byte loads per thread and tile
 constexpr int SCAN_SLACK = QADC_MAX_R;    // candidate slots beyond one tile
 constexpr int GH_REP = 2;                 // replicas of the grid-wide histogram
 constexpr unsigned NO_KEY = 0xffffffffu;
+constexpr unsigned IVFS_NONE = 0xffffffffu;  // a query of the shared-list scan without a bound
 
 // Per-query control block in the workspace, followed by counts[G] (keys reported by each
 // workgroup) and lists[G][R] (the keys).  Block and counts must be all zero when the scan
