@@ -1456,12 +1456,7 @@ __global__ __launch_bounds__(NT) void ivf_scan_kernel(
     }
     {
         const int l = lane_id();
-        unsigned inc = my_units;
-#pragma unroll
-        for (int dd = 1; dd < WAVE; dd <<= 1) {
-            const unsigned up = __shfl_up(inc, dd);
-            if (l >= dd) inc += up;
-        }
+        const unsigned inc = wave_running_sum(my_units);
         if (l == WAVE - 1) sh.wsum[tid / WAVE] = inc;
         __syncthreads();
         unsigned before = 0;

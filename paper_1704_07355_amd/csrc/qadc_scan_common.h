@@ -62,13 +62,8 @@ __device__ __forceinline__ unsigned wave_threshold_bin(const unsigned (&h)[NB], 
     unsigned tot = 0;
 #pragma unroll
     for (int b = 0; b < NB; ++b) tot += h[b];
-    unsigned inc = tot;
-#pragma unroll
-    for (int d = 1; d < WAVE; d <<= 1) {
-        const unsigned up = __shfl_up(inc, d);
-        if (l >= d) inc += up;
-    }
-    if (total) *total = __shfl(inc, WAVE - 1);
+    const unsigned inc = wave_running_sum(tot);
+    if (total) *total = lane_value(inc, WAVE - 1);
     const unsigned long long m = __ballot(inc >= need);
     if (m == 0) return (unsigned)(WAVE * NB);
     const int first = __ffsll((long long)m) - 1;
@@ -79,7 +74,7 @@ __device__ __forceinline__ unsigned wave_threshold_bin(const unsigned (&h)[NB], 
         run += h[b];
         if (!found && run >= need) { bin = (unsigned)(NB * l + b); found = true; }
     }
-    return __shfl(bin, first);
+    return lane_value(bin, first);
 }
 
 // Cuts keys[0..cnt) back to its `keep` smallest keys and returns the largest key kept.  A list
@@ -711,15 +706,10 @@ __global__ __launch_bounds__(MERGE_NT) void merge_gather_kernel(
                 c[u] = min(c[u], (unsigned)pitch);
                 sum += c[u];
             }
-            unsigned inc = sum;
-#pragma unroll
-            for (int dd = 1; dd < WAVE; dd <<= 1) {
-                const unsigned up = __shfl_up(inc, dd);
-                if (lane >= dd) inc += up;
-            }
+            const unsigned inc = wave_running_sum(sum);
             unsigned base = 0;
             if (lane == WAVE - 1 && inc > 0) base = atomicAdd(&lcnt, inc);
-            unsigned at = __shfl(base, WAVE - 1) + inc - sum;
+            unsigned at = lane_value(base, WAVE - 1) + inc - sum;
 #pragma unroll
             for (int u = 0; u < MERGE_GU; ++u) {
                 const unsigned first = (unsigned)(g0 + u * MERGE_NT + tid) * (unsigned)pitch;

@@ -2,6 +2,8 @@
 // paper): pair tables in LDS, sums of a tile of codes, candidate keys.
 #pragma once
 
+#include <type_traits>
+
 #include "qadc_scan_common.h"
 
 namespace qadc {
@@ -197,33 +199,38 @@ __device__ __forceinline__ void build_pair_tables(const uint8_t *__restrict__ ql
 }
 
 // Ascending bitonic sort of 4 * 64 values held four per lane by one wavefront: element
-// e = 4 * lane + r.  Exchanges at distance < 4 stay inside a lane, the others go through
-// __shfl_xor.  Called by a whole wavefront.
+// e = 4 * lane + r.  Exchanges at distance < 4 stay inside a lane.  Called by a whole wavefront.
 __device__ __forceinline__ void wave_bitonic_sort4(unsigned (&v)[4])
 {
     const unsigned lane = (unsigned)lane_id();
+    auto across = [&](auto x, unsigned k) {  // exchanges between lanes l and l ^ X
+        constexpr int X = decltype(x)::value;
+#pragma unroll
+        for (unsigned r = 0; r < 4; ++r) {
+            const unsigned e = 4 * lane + r;
+            const unsigned other = lane_xor<X>(v[r]);
+            const bool up = (e & k) == 0, lower = (lane & X) == 0;
+            v[r] = (lower == up) ? min(v[r], other) : max(v[r], other);
+        }
+    };
 #pragma unroll
     for (unsigned k = 2; k <= 256; k <<= 1) {
+        if (k >= 256) across(std::integral_constant<int, 32>(), k);
+        if (k >= 128) across(std::integral_constant<int, 16>(), k);
+        if (k >= 64) across(std::integral_constant<int, 8>(), k);
+        if (k >= 32) across(std::integral_constant<int, 4>(), k);
+        if (k >= 16) across(std::integral_constant<int, 2>(), k);
+        if (k >= 8) across(std::integral_constant<int, 1>(), k);
 #pragma unroll
-        for (unsigned j = k >> 1; j > 0; j >>= 1) {
-            if (j >= 4) {
+        for (unsigned j = min(k >> 1, 2u); j > 0; j >>= 1) {
 #pragma unroll
-                for (unsigned r = 0; r < 4; ++r) {
+            for (unsigned r = 0; r < 4; ++r) {
+                if ((r & j) == 0) {
                     const unsigned e = 4 * lane + r;
-                    const unsigned other = __shfl_xor(v[r], (int)(j >> 2));
-                    const bool up = (e & k) == 0, lower = (e & j) == 0;
-                    v[r] = (lower == up) ? min(v[r], other) : max(v[r], other);
-                }
-            } else {
-#pragma unroll
-                for (unsigned r = 0; r < 4; ++r) {
-                    if ((r & j) == 0) {
-                        const unsigned e = 4 * lane + r;
-                        const bool up = (e & k) == 0;
-                        const unsigned a = v[r], b = v[r ^ j];
-                        v[r] = up ? min(a, b) : max(a, b);
-                        v[r ^ j] = up ? max(a, b) : min(a, b);
-                    }
+                    const bool up = (e & k) == 0;
+                    const unsigned a = v[r], b = v[r ^ j];
+                    v[r] = up ? min(a, b) : max(a, b);
+                    v[r ^ j] = up ? max(a, b) : min(a, b);
                 }
             }
         }

@@ -30,15 +30,10 @@ __device__ __forceinline__ void select_bin(SelectScratch *sc, unsigned need)
         unsigned h0 = sc->hist[4 * l + 0], h1 = sc->hist[4 * l + 1];
         unsigned h2 = sc->hist[4 * l + 2], h3 = sc->hist[4 * l + 3];
         unsigned tot = h0 + h1 + h2 + h3;
-        unsigned inc = tot;
-#pragma unroll
-        for (int d = 1; d < WAVE; d <<= 1) {
-            unsigned up = __shfl_up(inc, d);
-            if (l >= d) inc += up;
-        }
+        const unsigned inc = wave_running_sum(tot);
         // a request beyond the histogram's total is answered with its last element, an empty
         // histogram with bin 0 and rank 0: the result is defined for every input
-        const unsigned total = __shfl(inc, WAVE - 1);
+        const unsigned total = lane_value(inc, WAVE - 1);
         if (need > total) need = total;
         if (need == 0 && l == 0) { sc->bin = 0; sc->need = 0; }
         unsigned excl = inc - tot;
