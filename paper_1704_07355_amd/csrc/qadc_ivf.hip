@@ -119,11 +119,17 @@ struct IvfDistRows {
     size_t query_ld, dist_ld, coarse_z, query_z, dist_z;
 };
 
-template <int AQ>
+// LISTED: only the queries list[1 .. list[0]], in their own rows.
+template <int AQ, bool LISTED = false>
 __global__ __launch_bounds__(256) void ivf_coarse_dist_kernel(
     const float *__restrict__ coarse, int K, int d, const float *__restrict__ queries, int nq, IvfDistRows rows,
-    float *__restrict__ dist, unsigned *__restrict__ blockmin, int nblk)
+    float *__restrict__ dist, unsigned *__restrict__ blockmin, int nblk, const unsigned *__restrict__ list)
 {
+    if constexpr (LISTED) {
+        nq = (int)list[0];
+        if ((int)blockIdx.y * 16 * AQ >= nq) return;  // uniform
+    }
+    auto number = [&](int q) { return LISTED ? (int)list[1 + q] : q; };
     coarse += blockIdx.z * rows.coarse_z;
     queries += blockIdx.z * rows.query_z;
     dist += blockIdx.z * rows.dist_z;
@@ -152,7 +158,7 @@ __global__ __launch_bounds__(256) void ivf_coarse_dist_kernel(
             yn[e] = 0.0f;
             if (row < QT) {
                 const int q = q0 + row;
-                if (q < nq && t < d) yn[e] = queries[(size_t)q * rows.query_ld + t];
+                if (q < nq && t < d) yn[e] = queries[(size_t)number(q) * rows.query_ld + t];
             }
         }
     };
@@ -198,6 +204,7 @@ __global__ __launch_bounds__(256) void ivf_coarse_dist_kernel(
 #pragma unroll
     for (int a = 0; a < AQ; ++a) {
         const int q = q0 + AQ * ty + a;
+        const size_t at = q < nq ? number(q) : 0;  // its row
         unsigned mn = 0xffffffffu;  // smallest distance of this query over the workgroup's cells, as its image
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
@@ -206,16 +213,16 @@ __global__ __launch_bounds__(256) void ivf_coarse_dist_kernel(
             if (c + 1 < K) mn = min(mn, f2ord(acc[a][2 * k + 1]));
             if (q >= nq) continue;
             if (c + 1 < K && (rows.dist_ld & 1) == 0 && (rows.dist_z & 1) == 0) {  // the pair is 8-byte aligned
-                *reinterpret_cast<float2 *>(&dist[(size_t)q * rows.dist_ld + c]) = make_float2(acc[a][2 * k], acc[a][2 * k + 1]);
+                *reinterpret_cast<float2 *>(&dist[at * rows.dist_ld + c]) = make_float2(acc[a][2 * k], acc[a][2 * k + 1]);
             } else {
-                if (c < K) dist[(size_t)q * rows.dist_ld + c] = acc[a][2 * k];
-                if (c + 1 < K) dist[(size_t)q * rows.dist_ld + c + 1] = acc[a][2 * k + 1];
+                if (c < K) dist[at * rows.dist_ld + c] = acc[a][2 * k];
+                if (c + 1 < K) dist[at * rows.dist_ld + c + 1] = acc[a][2 * k + 1];
             }
         }
         if (blockmin) {  // uniform: the 16 lanes tx of a query are neighbours in the wavefront
 #pragma unroll
             for (int o = 1; o < 16; o <<= 1) mn = min(mn, (unsigned)__shfl_xor((int)mn, o));
-            if (tx == 0 && q < nq) blockmin[(size_t)q * nblk + blockIdx.x] = mn;
+            if (tx == 0 && q < nq) blockmin[at * nblk + blockIdx.x] = mn;
         }
     }
 }
@@ -372,7 +379,7 @@ void ivf_distances(const float *coarse, int K, int d, const float *queries, int 
     if (nq > 32 && tiles >= 256) {
         dim3 grid((unsigned)nblk, (unsigned)ceil_div(nq, 128), (unsigned)parts);
         launch(QADC_PROF_IVF_INDEX, ivf_coarse_dist_kernel<8>, grid, dim3(256), 0, st, coarse, K, d, queries, nq, rows,
-               dist, bmin, nblk);
+               dist, bmin, nblk, (const unsigned *)nullptr);
     } else {
         const int vec4 = (d % 4 == 0 && rows.query_ld % 4 == 0 && rows.query_z % 4 == 0 && rows.coarse_z % 4 == 0 &&
                           ((uintptr_t)coarse & 15) == 0 && ((uintptr_t)queries & 15) == 0) ? 1 : 0;
@@ -458,11 +465,14 @@ __device__ __forceinline__ void probes_of_candidates(const float *dq, int K, int
 }
 
 
+// LISTED: as in ivf_coarse_dist_kernel.
+template <bool LISTED>
 __global__ __launch_bounds__(IVF_SEL_NT) void ivf_select_probes_kernel(
     const float *__restrict__ dist, int K, int nprobe, int32_t *__restrict__ probes,
-    const unsigned *__restrict__ blockmin, int nblk, IvfClear clr)
+    const unsigned *__restrict__ blockmin, int nblk, IvfClear clr, const unsigned *__restrict__ list)
 {
     constexpr int NT = IVF_SEL_NT;
+    if (LISTED && blockIdx.x >= list[0]) return;  // uniform
     if (clr.scan_ws) {  // uniform
         ivf_clear_control(clr.scan_ws + (size_t)blockIdx.x * clr.ws_stride, clr.counts_off, clr.W, clr.countsA_off);
     }
@@ -470,7 +480,7 @@ __global__ __launch_bounds__(IVF_SEL_NT) void ivf_select_probes_kernel(
     __shared__ uint64_t cand[IVF_SEL_CAP];  // thread minima first, then the candidates
     __shared__ unsigned cnt;
     const int tid = threadIdx.x;
-    const int q = blockIdx.x;
+    const int q = LISTED ? (int)list[1 + blockIdx.x] : (int)blockIdx.x;
     const float *dq = dist + (size_t)q * K;
     const unsigned need = (unsigned)min(nprobe, K);
 
@@ -575,12 +585,15 @@ __device__ __forceinline__ const uint16_t *filter_row(const float *dist, int K, 
 // the rounding of the scores and of float32 distances (components + 4 roundings of 2^-24) the scores of all cells among the
 // `need` closest.  The cells of those groups -- some 70 groups for 64 probes -- are measured by the definition
 // (ivf_coarse_dist_kernel's operations in its order), a thread per cell.  A query that this cannot serve (beyond the range of
-// the factors, too many groups as close, a NaN anywhere) is measured against all cells.
+// the factors, too many groups as close, a NaN anywhere) goes to `rest` (their number, then the queries in any order), for the
+// float32 distances to all cells (2000 queries, 16,334 of 16,384 centroids in one place: 1310 us; measured against all
+// cells by its own workgroup instead, 2670: the centroids from the caches once per query).
 constexpr int IVF_SEL_GROUPS = IVF_SEL_CAP / 4;
 
 __global__ __launch_bounds__(IVF_SEL_NT) void ivf_select_filtered_kernel(
     const float *__restrict__ coarse, int K, int d, const float *__restrict__ queries, float *__restrict__ dist,
-    const float2 *__restrict__ qstat, int components, int nprobe, int32_t *__restrict__ probes, int vec4)
+    const float2 *__restrict__ qstat, int components, int nprobe, int32_t *__restrict__ probes, int vec4,
+    unsigned *__restrict__ rest)
 {
     constexpr int NT = IVF_SEL_NT;
     __shared__ SelectScratch sc;
@@ -646,7 +659,10 @@ __global__ __launch_bounds__(IVF_SEL_NT) void ivf_select_filtered_kernel(
     }
     __syncthreads();
     const unsigned ng = ngroup;
-    const bool served = sure && ng <= (unsigned)IVF_SEL_GROUPS;  // uniform
+    if (!sure || ng > (unsigned)IVF_SEL_GROUPS) {  // uniform
+        if (tid == 0) rest[1 + atomicAdd(rest, 1u)] = (unsigned)q;
+        return;
+    }
     auto measure = [&](int c) {
         const float *cr = coarse + (size_t)c * d;
         float acc = 0.0f;
@@ -674,16 +690,10 @@ __global__ __launch_bounds__(IVF_SEL_NT) void ivf_select_filtered_kernel(
         return acc;
     };
     float *dq = dist + (size_t)q * K;
-    if (served) {
-        for (unsigned i = tid; i < 4u * ng; i += NT) {
-            const unsigned g = groups[i >> 2];  // place 8 tile + 4 half + k: cells 32 tile + 8 k + 4 half + 0 .. 3
-            const int c = (int)((g >> 3) * 32u + (g & 3u) * 8u + ((g >> 2) & 1u) * 4u + (i & 3u));
-            if (c < K) cand[atomicAdd(&cnt, 1u)] = ((uint64_t)f2ord(measure(c)) << 32) | (uint64_t)(unsigned)c;
-        }
-    } else {
-        for (int c = tid; c < K; c += NT) dq[c] = measure(c);  // (the bounds in that row are done with)
-        if (tid == 0) cnt = IVF_SEL_CAP + 1;
-        __threadfence_block();
+    for (unsigned i = tid; i < 4u * ng; i += NT) {
+        const unsigned g = groups[i >> 2];  // place 8 tile + 4 half + k: cells 32 tile + 8 k + 4 half + 0 .. 3
+        const int c = (int)((g >> 3) * 32u + (g & 3u) * 8u + ((g >> 2) & 1u) * 4u + (i & 3u));
+        if (c < K) cand[atomicAdd(&cnt, 1u)] = ((uint64_t)f2ord(measure(c)) << 32) | (uint64_t)(unsigned)c;
     }
     __syncthreads();
     probes_of_candidates(dq, K, nprobe, need, cand, cnt, sc, probes + (size_t)q * nprobe);
@@ -693,8 +703,8 @@ __global__ __launch_bounds__(IVF_SEL_NT) void ivf_select_filtered_kernel(
 // (for the multi-index's half distances)
 void ivf_select_smallest(const float *dist, int rows, int K, int count, int32_t *out, hipStream_t st)
 {
-    launch(QADC_PROF_IVF_INDEX, ivf_select_probes_kernel, dim3((unsigned)rows), dim3(IVF_SEL_NT), 0, st, dist, K,
-           count, out, (const unsigned *)nullptr, 0, IvfClear{nullptr, 0, 0, 0, 0});
+    launch(QADC_PROF_IVF_INDEX, ivf_select_probes_kernel<false>, dim3((unsigned)rows), dim3(IVF_SEL_NT), 0, st, dist, K,
+           count, out, (const unsigned *)nullptr, 0, IvfClear{nullptr, 0, 0, 0, 0}, (const unsigned *)nullptr);
 }
 
 // ----------------------------------------------------------------- Tables
@@ -1823,7 +1833,8 @@ int quantize_luts(int, const float *, int, int, int, const uint8_t *, int64_t, c
 size_t ivf_filter_bytes(int K, int d, int nq);
 bool ivf_filter_pays(int K, int d, int nq, int nprobe);
 void ivf_filter_convert(const float *coarse, int K, int d, const float *queries, int nq, void *room, hipStream_t st);
-const float2 *ivf_filter(int K, int d, int nq, int i0, int ni, void *room, float *dist, int *components, hipStream_t st);
+const float2 *ivf_filter(int K, int d, int nq, int i0, int ni, void *room, float *dist, int *components, unsigned **rest,
+                         hipStream_t st);
 
 struct IvfPlan {
     int qb, W;
@@ -2047,23 +2058,29 @@ int ivf_search(const qadc_ivf_index *ix, const float *queries, int nq, int nprob
             for (int i0 = 0; i0 < nb; i0 += pass) {
                 const int ni = min(pass, nb - i0);
                 const float *yi = yq + (size_t)i0 * d;
-                if (filtered) {
-                    int components = 0;
-                    const float2 *qstat = ivf_filter(K, d, nb, i0, ni, luts, dist, &components, st);
-                    const int vec4 = d % 4 == 0 && ((uintptr_t)ix->coarse & 15) == 0;
-                    launch(QADC_PROF_IVF_INDEX, ivf_select_filtered_kernel, dim3(ni), dim3(IVF_SEL_NT), 0, st, ix->coarse,
-                           K, d, yi, dist, qstat, components, nprobe, probes + (size_t)i0 * nprobe, vec4);
-                    continue;
-                }
                 // the minima of the runs of IVF_CT cells go with the distances, and the selection reads
                 // only the runs that matter (when there are enough runs)
                 unsigned *bmin = nullptr;
                 const int nblk = (int)ceil_div(K, IVF_CT);
                 if (nblk >= 2 * nprobe && nblk <= IVF_SEL_MAXBLK) bmin = (unsigned *)(ws + p.off_bmin);
                 const IvfDistRows rows = {(size_t)d, (size_t)K, 0, 0, 0};
+                if (filtered) {
+                    int components = 0;
+                    unsigned *rest = nullptr;
+                    const float2 *qstat = ivf_filter(K, d, nb, i0, ni, luts, dist, &components, &rest, st);
+                    const int vec4 = d % 4 == 0 && ((uintptr_t)ix->coarse & 15) == 0;
+                    launch(QADC_PROF_IVF_INDEX, ivf_select_filtered_kernel, dim3(ni), dim3(IVF_SEL_NT), 0, st, ix->coarse,
+                           K, d, yi, dist, qstat, components, nprobe, probes + (size_t)i0 * nprobe, vec4, rest);
+                    // the queries that the bounds could not serve (mostly none: the workgroups return at once, 5 us for both launches)
+                    launch(QADC_PROF_IVF_INDEX, ivf_coarse_dist_kernel<8, true>, dim3((unsigned)nblk, (unsigned)ceil_div(ni, 128)),
+                           dim3(256), 0, st, ix->coarse, K, d, yi, ni, rows, dist, bmin, nblk, (const unsigned *)rest);
+                    launch(QADC_PROF_IVF_INDEX, ivf_select_probes_kernel<true>, dim3(ni), dim3(IVF_SEL_NT), 0, st, dist, K,
+                           nprobe, probes + (size_t)i0 * nprobe, (const unsigned *)bmin, nblk, clr, (const unsigned *)rest);
+                    continue;
+                }
                 ivf_distances(ix->coarse, K, d, yi, ni, rows, 1, dist, bmin, st);
-                launch(QADC_PROF_IVF_INDEX, ivf_select_probes_kernel, dim3(ni), dim3(IVF_SEL_NT), 0, st, dist, K,
-                       nprobe, probes + (size_t)i0 * nprobe, (const unsigned *)bmin, (int)ceil_div(K, IVF_CT), clr);
+                launch(QADC_PROF_IVF_INDEX, ivf_select_probes_kernel<false>, dim3(ni), dim3(IVF_SEL_NT), 0, st, dist, K,
+                       nprobe, probes + (size_t)i0 * nprobe, (const unsigned *)bmin, nblk, clr, (const unsigned *)nullptr);
             }
         }
         IvfQuantizer fq = {nullptr, nullptr, nullptr};

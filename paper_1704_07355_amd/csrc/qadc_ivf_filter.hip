@@ -1,7 +1,7 @@
 // Index step of large calls (Section 2.2 of the paper) on the matrix units: for every query and every group of four
 // cells, a lower bound of the smallest distance, from binary16 factors (qadc_half.h).  ivf_select_filtered_kernel takes the
 // groups that can hold one of the nprobe closest cells from them and measures those cells by the definition, so the cells
-// chosen are the definition's; a query the bounds cannot serve is measured against all cells there.
+// chosen are the definition's; a query the bounds cannot serve is left to the kernels of the float32 distances.
 //
 // Bound by 2 nq K d operations on the matrix units and, with as many cycles, by the minima, conversions and stores that go
 // with each result.  4096 queries x 65536 cells of 128 components (four launches): 191 us, 14 for the factors and 291 for the
@@ -134,7 +134,8 @@ template <int KS>
 __global__ __launch_bounds__(256, 2) void ivf_filter_kernel(const bits16x8 *__restrict__ cells, const float *__restrict__ nrm,
                                                             int K, const bits16x8 *__restrict__ qs,
                                                             const float2 *__restrict__ qstat, int nq, int wq,
-                                                            int per_block, float *__restrict__ dist)
+                                                            int per_block, float *__restrict__ dist,
+                                                            unsigned *__restrict__ rest)
 {
     using Room = FilterRoom<KS>;
     constexpr int NBQ = Room::NBQ, STAGE = Room::STAGE;
@@ -146,6 +147,7 @@ __global__ __launch_bounds__(256, 2) void ivf_filter_kernel(const bits16x8 *__re
     const int tiles = (K + 31) / 32;
     const int q0 = ((int)blockIdx.y * wq + wave % wq) * 32 * NBQ;
     const int t0 = (int)blockIdx.x * per_block, t1 = min(tiles, t0 + per_block);
+    if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) *rest = 0;  // ivf_select_filtered_kernel counts in it
     if (t0 >= t1) return;  // uniform
     auto stage = [&](int t, int buf) {  // (tiles beyond the last: the last one again)
 #pragma unroll
@@ -217,10 +219,11 @@ size_t ivf_filter_bytes(int K, int d, int nq)
 {
     const int64_t ks = ceil_div(d, 16) <= 2 ? 2 : ceil_div(d, 16) <= 4 ? 4 : ceil_div(d, 16) <= 6 ? 6 : ceil_div(d, 16) <= 8 ? 8 : 16;
     const int64_t ct = ceil_div(K, 32), qt = ceil_div(nq, 32);
-    return (size_t)((ct + qt) * ks * 1024 + ct * 128) + align_up((size_t)nq * 8, 256);
+    return (size_t)((ct + qt) * ks * 1024 + ct * 128) + align_up((size_t)nq * 12 + 4, 256);
 }
 
-// Worth its launch more and a longer selection?  Whole calls against the float32 distances of every pair: 300 queries, 4096 cells
+// Worth its launches and a longer selection?  Whole calls (before the two launches for queries that the bounds cannot serve: 5 us
+// more a pass of queries) against the float32 distances of every pair: 300 queries, 4096 cells
 // of 64 components (8e7 products) 140 against 147 us, 200 x 4096 x 256 (2e8) the same, 1000 x 4096 x 128 (5e8) 305 / 334,
 // 300 x 16384 x 128 441 / 462, x 256 210 / 277, 2000 x 65536 x 64 874 / 1161.  100 probes of 4096 cells: too many groups are
 // as close (500 queries, d = 128: 609 / 597).  Calls of up to 32 queries have kernels of their own.
@@ -233,6 +236,7 @@ struct IvfFilter {
     bits16x8 *cells, *qs;
     float *nrm;
     float2 *qstat;
+    unsigned *rest;
 };
 
 static IvfFilter filter_parts(void *room, int K, int d, int nq, int ks)
@@ -244,6 +248,7 @@ static IvfFilter filter_parts(void *room, int K, int d, int nq, int ks)
     f.qs = (bits16x8 *)(p + ct * ks * 1024);
     f.nrm = (float *)(p + (ct + qt) * ks * 1024);
     f.qstat = (float2 *)(p + (ct + qt) * ks * 1024 + ct * 128);
+    f.rest = (unsigned *)(f.qstat + nq);
     return f;
 }
 
@@ -258,7 +263,7 @@ static void convert(const float *coarse, int K, int d, const float *queries, int
 }
 
 template <int KS>
-static const float2 *filter(int K, int d, int nq, int i0, int ni, void *room, float *dist, hipStream_t st)
+static const float2 *filter(int K, int d, int nq, int i0, int ni, void *room, float *dist, unsigned **rest, hipStream_t st)
 {
     constexpr int NBQ = FilterRoom<KS>::NBQ, STAGE = FilterRoom<KS>::STAGE;
     const IvfFilter f = filter_parts(room, K, d, nq, KS);
@@ -269,7 +274,8 @@ static const float2 *filter(int K, int d, int nq, int i0, int ni, void *room, fl
     const int per_block = (int)ceil_div(std::max<int64_t>(1, ceil_div((int64_t)tiles * rows, 512)), STAGE) * STAGE;
     launch(QADC_PROF_IVF_INDEX, ivf_filter_kernel<KS>, dim3((unsigned)ceil_div(tiles, per_block), (unsigned)rows), dim3(256), 0, st,
            (const bits16x8 *)f.cells, (const float *)f.nrm, K, (const bits16x8 *)(f.qs + (size_t)(i0 / 32) * KS * WAVE),
-           (const float2 *)(f.qstat + i0), ni, wq, per_block, dist);
+           (const float2 *)(f.qstat + i0), ni, wq, per_block, dist, f.rest);
+    *rest = f.rest;
     return f.qstat + i0;
 }
 
@@ -288,12 +294,13 @@ void ivf_filter_convert(const float *coarse, int K, int d, const float *queries,
 #undef QADC_CALL
 }
 
-// The bounds of queries i0 .. i0 + ni - 1 (i0 a multiple of 32) in the rows of `dist`; returns their (|x'|^2, ex^2), and the
-// number of components the rounding is bounded for.
-const float2 *ivf_filter(int K, int d, int nq, int i0, int ni, void *room, float *dist, int *components, hipStream_t st)
+// The bounds of queries i0 .. i0 + ni - 1 (i0 a multiple of 32) in the rows of `dist`; returns their (|x'|^2, ex^2), the
+// number of components the rounding is bounded for, and a counter (zero after the kernel) with room for nq numbers behind it.
+const float2 *ivf_filter(int K, int d, int nq, int i0, int ni, void *room, float *dist, int *components, unsigned **rest,
+                         hipStream_t st)
 {
     const float2 *r = nullptr;
-#define QADC_CALL(KS_) r = filter<KS_>(K, d, nq, i0, ni, room, dist, st), *components = 16 * KS_
+#define QADC_CALL(KS_) r = filter<KS_>(K, d, nq, i0, ni, room, dist, rest, st), *components = 16 * KS_
     QADC_FILTER_CASES(QADC_CALL)
 #undef QADC_CALL
     return r;
