@@ -2071,7 +2071,7 @@ int ivf_search(const qadc_ivf_index *ix, const float *queries, int nq, int nprob
                     const int vec4 = d % 4 == 0 && ((uintptr_t)ix->coarse & 15) == 0;
                     launch(QADC_PROF_IVF_INDEX, ivf_select_filtered_kernel, dim3(ni), dim3(IVF_SEL_NT), 0, st, ix->coarse,
                            K, d, yi, dist, qstat, components, nprobe, probes + (size_t)i0 * nprobe, vec4, rest);
-                    // the queries that the bounds could not serve (mostly none: the workgroups return at once, 5 us for both launches)
+                    // the queries that the bounds could not serve (mostly none: the workgroups return at once, 5 to 9 us a pass for both)
                     launch(QADC_PROF_IVF_INDEX, ivf_coarse_dist_kernel<8, true>, dim3((unsigned)nblk, (unsigned)ceil_div(ni, 128)),
                            dim3(256), 0, st, ix->coarse, K, d, yi, ni, rows, dist, bmin, nblk, (const unsigned *)rest);
                     launch(QADC_PROF_IVF_INDEX, ivf_select_probes_kernel<true>, dim3(ni), dim3(IVF_SEL_NT), 0, st, dist, K,

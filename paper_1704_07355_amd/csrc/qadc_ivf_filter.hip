@@ -222,8 +222,8 @@ size_t ivf_filter_bytes(int K, int d, int nq)
     return (size_t)((ct + qt) * ks * 1024 + ct * 128) + align_up((size_t)nq * 12 + 4, 256);
 }
 
-// Worth its launches and a longer selection?  Whole calls (before the two launches for queries that the bounds cannot serve: 5 us
-// more a pass of queries) against the float32 distances of every pair: 300 queries, 4096 cells
+// Worth its launches and a longer selection?  Whole calls (before the two launches for queries that the bounds cannot serve: 5 to
+// 9 us more a pass of queries) against the float32 distances of every pair: 300 queries, 4096 cells
 // of 64 components (8e7 products) 140 against 147 us, 200 x 4096 x 256 (2e8) the same, 1000 x 4096 x 128 (5e8) 305 / 334,
 // 300 x 16384 x 128 441 / 462, x 256 210 / 277, 2000 x 65536 x 64 874 / 1161.  100 probes of 4096 cells: too many groups are
 // as close (500 queries, d = 128: 609 / 597).  Calls of up to 32 queries have kernels of their own.
