@@ -78,5 +78,4 @@ constexpr float HALF_FAR = 5e8f;
 constexpr float HALF_CONV = 4400.0f;        // 2^12, and a sixteenth for what HALF_TINY pays for
 constexpr float HALF_TINY = 3e-4f;          // per component: conversions below the normal range of binary16, flushed or not
 
-
 }  // namespace qadc

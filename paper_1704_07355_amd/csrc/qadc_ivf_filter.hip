@@ -17,9 +17,17 @@ namespace qadc {
 
 constexpr int IVFF_MAX_D = 256;
 
+// The bounds are of exact distances, the definition is the float32 one: they order cells alike where its squares neither overflow
+// nor lose bits below the normal range, that is for scales (half_scale) within these.  A square that matters is at most
+// 4 HALF_FAR / scale^2 < 2^124; what a sum of D squares loses below 2^-126, at most D 2^-150 scale^2 of the scaled one, is far
+// inside HALF_TINY D.  Outside (centroids less than 3e-11 or more than 2e15 apart) every query is left to the float32 distances,
+// whose ties the bounds would break.
+constexpr float IVFF_MIN_SCALE = 0x1p-46f, IVFF_MAX_SCALE = 0x1p+39f;
+
 // Tiles of 32 rows as the matrix instructions read them: step s of 16 components, lane (row, half), 16 bytes.  Workgroup b <
 // ctiles takes centroids: operand c^ and the lower bound of |c'|^2 for the scores (minus infinity for a centroid with a
-// NaN: no query can then rely on the bounds).  The others take queries: operand -2 x^, and (|x'|^2, ex^2).
+// NaN: no query can then rely on the bounds).  The others take queries: operand -2 x^, and (|x'|^2, ex^2), NaN where the
+// bounds are not to be used.
 template <int KS>
 __global__ __launch_bounds__(256) void ivf_filter_convert_kernel(const float *__restrict__ coarse, int K, int d,
                                                                  const float *__restrict__ queries, int nq, int ctiles,
@@ -96,7 +104,8 @@ __global__ __launch_bounds__(256) void ivf_filter_convert_kernel(const float *__
         if (!(s2 == s2)) own = -__builtin_inff();
         nrm[row] = in ? own : __builtin_inff();  // (rows are padded to whole tiles)
     } else if (in) {
-        qstat[row] = make_float2(s2, e2);
+        const bool usable = scale >= IVFF_MIN_SCALE && scale <= IVFF_MAX_SCALE;
+        qstat[row] = make_float2(usable ? s2 : __builtin_nanf(""), e2);
     }
 }
 

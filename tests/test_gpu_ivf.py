@@ -584,6 +584,28 @@ def test_cells_of_calls_that_take_the_matrix_units(Q, K, d, nq, nprobe, kind):
         assert torch.equal(cells(queries[s:s + 32]), got[s:s + 32]), s
 
 
+@pytest.mark.parametrize("factor", [1e15, 1.5e18, 2.5e18, 1e19, 1e-11, 1e-22, 3e-23, 1e-24, 1e-38])
+@pytest.mark.parametrize("K,d,nq,nprobe", [(4096, 128, 600, 32), (9000, 64, 500, 5)])
+def test_cells_where_squares_leave_float32(Q, K, d, nq, nprobe, factor):
+    """Distances whose squares overflow or fall below the normal range tie where the exact ones do not (lowest id first): the
+    cells of large calls are still those of calls of a few queries, on both sides of the range that bounds are used in."""
+    import torch
+    g = torch.Generator(device="cuda:0")
+    g.manual_seed(K)
+    randn = lambda *shape: torch.randn(shape, generator=g, device="cuda:0")
+    coarse = randn(K, d) * factor
+    queries = coarse[torch.randint(0, K, (nq,), generator=g, device="cuda:0")] + randn(nq, d) * (0.5 * factor)
+    cb = randn(8, 16, d // 8) * factor
+    n = 3000
+    off = torch.minimum(torch.arange(K + 1, device="cuda:0"), torch.tensor(n, device="cuda:0"))
+    codes = torch.randint(0, 256, (n, 4), generator=g, device="cuda:0", dtype=torch.uint8)
+    ix = Q.IvfIndex(coarse, off, codes, torch.arange(n, dtype=torch.int32, device="cuda:0"), cb)
+    cells = lambda y: Q.qadc_ivf_search(ix, y.contiguous(), nprobe, 5, 50, debug=True)[2]
+    got = cells(queries)
+    for s in (0, nq // 2, nq - 32):
+        assert torch.equal(cells(queries[s:s + 32]), got[s:s + 32]), s
+
+
 @pytest.mark.parametrize("K,d,nq", [(9001, 32, 500), (32_767, 24, 129)])
 def test_cells_of_an_odd_number_do_not_depend_on_the_batch(Q, O, K, d, nq):
     """The tiled distance kernel over an odd number of cells: rows of distances that start off an 8-byte boundary."""
