@@ -67,8 +67,9 @@ static void launch_train_assign(const float *train, int64_t n, int d, int m, con
 // float64 sum in row order, one chain of additions per component; a chain per component is what this kernel was bound by
 // (44 us per iteration for 20,000 rows, m = 16, 16 centroids, 8 dimensions).  The sum is taken in many chains instead, a
 // lane per (row slot, component), together with the sum of the absolute values: `cnt` additions in a row are off by at
-// most cnt 2^-53 times that, these by what the longest of their chains adds, and unless the float32 rounding of the mean
-// changes within this margin it is the row-order one.  Where it does (about one mean in 10^5 of a thousand rows), or is not a
+// most cnt 2^-53 times that, these by what the longest of their chains adds (the first slot's, counted round by round: a
+// round of few rows leaves most slots without one), and unless the float32 rounding of the mean changes within this margin
+// it is the row-order one.  Where it does (about one mean in 10^5 of a thousand rows), or is not a
 // number, the workgroup walks its rows again in row order.
 // The labels, a column of the label matrix, are read in rounds, and the numbers of the centroid's rows are left in LDS in
 // row order (ballots and running counts, no atomics).  Bound by round trips: labels, then rows eight loads at a time.
@@ -143,11 +144,13 @@ __global__ __launch_bounds__(NT) void train_update_kernel(
     int64_t cnt = 0;
     if (n > SEG || (cnt = train_rows<NT, PER>(col, 0, n, (unsigned)i, rows, wcount)) > TRAIN_FEW) {  // uniform
         double mag = 0.0;
+        int64_t chain = 0;                         // additions of the first slot, the most that one has
         const int slots = NT / td;                 // rows side by side
         const int slot = tid / td, t = tid - slot * td;
         for (int64_t base = 0; base < n; base += SEG) {
             const unsigned found = n <= SEG ? (unsigned)cnt : train_rows<NT, PER>(col, base, n, (unsigned)i, rows, wcount);
             if (n > SEG) cnt += found;
+            chain += (found + (unsigned)slots - 1u) / (unsigned)slots;
             if (slot < slots) {
                 for (unsigned r0 = (unsigned)slot; r0 < found; r0 += TRAIN_FL * (unsigned)slots) {
                     float v[TRAIN_FL];
@@ -182,9 +185,9 @@ __global__ __launch_bounds__(NT) void train_update_kernel(
         float mean = 0.0f;
         if (tid < td) {
             const double s = part[tid].x, c = (double)cnt;
-            // row order: cnt additions; here: cnt / slots + 1 and at most 11 of the tree.  (1.01: the rounding of this line
-            // and of the two divisions below is far under a hundredth of it)
-            const double eps = part[tid].y * (c + (c / slots + 16.0)) * (1.01 * 0x1p-53);
+            // row order: cnt additions; here: those of the longest chain and at most 10 of the tree.  (1.01: the rounding of
+            // this line and of the two divisions below is far under a hundredth of it)
+            const double eps = part[tid].y * (c + (double)chain + 10.0) * (1.01 * 0x1p-53);
             mean = (float)(s / c);
             sure = __float_as_uint((float)((s - eps) / c)) == __float_as_uint((float)((s + eps) / c)) &&
                    __builtin_isfinite(mean);

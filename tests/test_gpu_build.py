@@ -348,6 +348,23 @@ def test_pq_train_means_where_the_order_of_the_sum_decides(Q, n, d):
     assert np.array_equal(got[0, 1:], np.broadcast_to(x[0], (15, d)))
 
 
+@pytest.mark.parametrize("per_round", [1, 2, 5])
+@pytest.mark.parametrize("tiny", [2.0 ** -54, 3 * 2.0 ** -54, -(2.0 ** -55)])
+def test_pq_train_means_of_rows_far_apart(Q, per_round, tiny):
+    """256 rows of a centroid, a few per round of 20,480 labels, so that the first chains of the parallel sum are as long as there
+    are rounds; in row order all but two of them vanish in the sum and the mean is half way between two float32."""
+    c, rounds = 256, -(-256 // per_round)
+    x = np.full((rounds * 20_480, 1), 1000.0, dtype=np.float32)
+    at = np.concatenate([r * 20_480 + 7 + 11 * np.arange(per_round) for r in range(rounds)])[:c]
+    x[at, 0] = tiny
+    x[at[0], 0], x[at[1], 0] = 1.0, 2.0 ** -24
+    rows = np.full(16, 0, dtype=np.int64)
+    rows[0] = at[0]
+    got = Q.qadc_pq_train(to_gpu(x), 1, 16, to_gpu(rows), 1).cpu().numpy()
+    want = np.float32(np.cumsum(x[at, 0].astype(np.float64))[-1] / c)
+    assert got[0, 0, 0] == want and np.all(got[0, 1:] == 1000.0)
+
+
 def _codes_by_definition(x, cb):
     """enc(x) from float64 distances summed in increasing component order, ties to the lowest index; u8 [n][m]."""
     m, k, dsub = cb.shape
