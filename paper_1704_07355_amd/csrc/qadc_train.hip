@@ -74,7 +74,8 @@ static void launch_train_assign(const float *train, int64_t n, int d, int m, con
 // The labels, a column of the label matrix, are read in rounds, and the numbers of the centroid's rows are left in LDS in
 // row order (ballots and running counts, no atomics).  Bound by round trips: labels, then rows eight loads at a time.
 // 44 -> 11.6 us per iteration where no mean is in doubt; 1 M rows, where one iteration in three has one, 2.4 -> 0.5 ms per
-// iteration with the assignment; learning sets of NaN, all rows in order, a tenth slower than before.
+// iteration with the assignment; learning sets of NaN, all rows in order, a tenth slower than before, and 4 to 9 % where most
+// workgroups have one of their 64 means in doubt (300,000 to 600,000 rows, 16 centroids near zero, 120 components and more).
 constexpr int TRAIN_TD = 64;                             // components per workgroup, at most
 constexpr int TRAIN_FL = 8;                              // loads in flight per thread
 constexpr unsigned TRAIN_FEW = 128;                      // rows that are added in order right away
@@ -257,9 +258,15 @@ int pq_train(const float *train, int64_t n, int d, int m, int ksub, const int64_
         else if (ksub == 64) launch_train_assign<64>(train, n, d, m, codebooks, labels, st);
         else launch_train_assign<256>(train, n, d, m, codebooks, labels, st);
         const dim3 grid((unsigned)(ksub * m * ceil_div(d / m, TRAIN_TD)));
-        // (a few hundred rows: the launch counts, 11.9 us per iteration with 1024 threads, 11.2 with 512; 20,000 rows 19 and 22)
+        // (a few hundred rows: the launch counts, 11.9 us per iteration with 1024 threads, 11.2 with 512; 20,000 rows 19 and 22.
+        // Five iterations with the assignment, 1024 threads / 512: 5000 rows m = 8, 256 centroids of 12 components 592 / 455 us,
+        // m = 16, 16 of 8 69 / 58; 8192 rows m = 8, 16 centroids of 120 588 / 614, 256 of 12 607 / 459: the rows of one round of
+        // 512 x 16 labels, and as many workgroups as fit, where few rows are a centroid's)
         if (n <= 4096)
             hipLaunchKernelGGL((train_update_kernel<512, 8>), grid, dim3(512), 0, st, train, n, d, m, ksub, labels,
+                               codebooks);
+        else if (n <= 8192)
+            hipLaunchKernelGGL((train_update_kernel<512, 16>), grid, dim3(512), 0, st, train, n, d, m, ksub, labels,
                                codebooks);
         else
             hipLaunchKernelGGL((train_update_kernel<1024, 20>), grid, dim3(1024), 0, st, train, n, d, m, ksub, labels,

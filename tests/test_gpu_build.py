@@ -326,12 +326,12 @@ def test_pq_train_means_are_row_order_float64_sums(Q, O, n, d, m, ksub):
     assert np.array_equal(got, want)
 
 
-@pytest.mark.parametrize("n,d", [(2, 1), (4_096, 4), (4_097, 4), (20_479, 3), (20_480, 64), (20_481, 65), (40_961, 5)])
+@pytest.mark.parametrize("n,d", [(2, 1), (4_096, 4), (4_097, 4), (8_192, 64), (8_193, 2), (20_479, 3), (20_480, 64), (20_481, 65), (40_961, 5)])
 def test_pq_train_means_where_the_order_of_the_sum_decides(Q, n, d):
     """All rows with the first centroid (repeated starting rows, ties to the lowest index) and components whose float64
     sum depends on the order of the additions, a mean half way between two float32, infinities and NaN: still the
-    row-order sum, bit for bit.  Sizes around the two forms of the kernel
-    (4096), a round of labels (20,480) and a workgroup's 64 components."""
+    row-order sum, bit for bit.  Sizes around the forms of the kernel
+    (4096, 8192), a round of labels (20,480) and a workgroup's 64 components."""
     rng = np.random.default_rng(n)
     x = (rng.normal(size=(n, d)) * 10.0 ** rng.uniform(-12, 12, size=(n, d))).astype(np.float32)
     x[:, 0] = 1.0
