@@ -12,9 +12,35 @@ namespace qadc {
 // luts[q][j][i] = sum_t (y[q][j*dsub+t] - base[q][j*dsub+t] - C[j][i][t])^2.
 // Differences and the sum are taken in float64 and rounded once to float32, so
 // a residual query (y - base) loses nothing to an intermediate rounding.
-// A thread per entry, a workgroup per 256 of them; eight components are requested at a time (one workgroup per query that
-// walked over the components one by one: 6.5 us for one query of 8 x 256 entries of 12 components, 4.6 now).
+// A workgroup per query, the query's differences in LDS, walks over the entries.
 __global__ __launch_bounds__(256) void build_luts_kernel(
+    const float *__restrict__ codebooks, int d, int m, int ksub, const float *__restrict__ queries,
+    const float *__restrict__ base, float *__restrict__ luts)
+{
+    extern __shared__ double yq[];  // [d]
+    const int q = blockIdx.x;
+    const int dsub = d / m;
+    for (int t = threadIdx.x; t < d; t += 256) {
+        double y = (double)queries[(size_t)q * d + t];
+        if (base) y -= (double)base[(size_t)q * d + t];
+        yq[t] = y;
+    }
+    __syncthreads();
+    const int entries = m * ksub;
+    for (int e = threadIdx.x; e < entries; e += 256) {
+        const float *c = codebooks + (size_t)e * dsub;
+        const double *y = yq + e / ksub * dsub;
+        double acc = 0.0;
+        for (int t = 0; t < dsub; ++t) {
+            const double df = y[t] - (double)c[t];
+            acc += df * df;
+        }
+        luts[(size_t)q * entries + e] = (float)acc;
+    }
+}
+
+// The same entries, a thread for each and a workgroup per 256 of them; eight components are requested at a time.
+__global__ __launch_bounds__(256) void build_luts_wide_kernel(
     const float *__restrict__ codebooks, int d, int m, int ksub, const float *__restrict__ queries,
     const float *__restrict__ base, float *__restrict__ luts)
 {
@@ -48,6 +74,17 @@ __global__ __launch_bounds__(256) void build_luts_kernel(
     luts[(size_t)q * entries + e] = (float)acc;
 }
 
+// A few queries of 2048 entries and more: eight rounds and more of one workgroup, each a round trip, against one (us, a workgroup
+// per query / a thread per entry: 1 query of 8 x 256 entries of 12 components 6.8 / 4.6, of 120 22 / 16, 64 of 32 x 256 of 4
+// 16.9 / 6.4).  More queries: a thread per entry reads the query again for every entry and twice the lines of the codebook
+// (8 x 256 of 12: 128 queries 6.8 / 6.1, 256 7.5 / 10.3, 4096 50 / 135; of 120: 33 23 / 30, 512 44 / 327; 32 x 64 of 8: 64
+// 4.2 / 4.4, 256 5.2 / 9.5).
+static bool luts_wide_pay(int d, int m, int ksub, int nq)
+{
+    const int64_t entries = (int64_t)m * ksub;
+    return entries >= 2048 && ceil_div(entries, 256) * nq * (d / m) <= 8192;
+}
+
 int build_luts(const float *codebooks, int d, int m, int ksub, const float *queries,
                const float *base, int nq, float *luts, hipStream_t st)
 {
@@ -55,12 +92,12 @@ int build_luts(const float *codebooks, int d, int m, int ksub, const float *quer
     if (m < 1 || d < m || d % m != 0 || (ksub != 16 && ksub != 64 && ksub != 256) || nq < 0 || d > 8192)
         return fail(QADC_EINVAL, "qadc_build_luts: unsupported d=%d m=%d ksub=%d nq=%d", d, m, ksub, nq);
     if (nq == 0) return QADC_OK;
-    for (int q0 = 0; q0 < nq; q0 += 65535) {
-        const int nb = std::min(nq - q0, 65535);
-        launch(QADC_PROF_TABLES, build_luts_kernel, dim3((unsigned)ceil_div((int64_t)m * ksub, 256), (unsigned)nb), dim3(256), 0, st,
-               codebooks, d, m, ksub, queries + (size_t)q0 * d, base ? base + (size_t)q0 * d : base,
-               luts + (size_t)q0 * m * ksub);
-    }
+    if (luts_wide_pay(d, m, ksub, nq))  // (at most 1024 queries)
+        launch(QADC_PROF_TABLES, build_luts_wide_kernel, dim3((unsigned)ceil_div((int64_t)m * ksub, 256), (unsigned)nq), dim3(256), 0,
+               st, codebooks, d, m, ksub, queries, base, luts);
+    else
+        launch(QADC_PROF_TABLES, build_luts_kernel, dim3((unsigned)nq), dim3(256), (size_t)d * sizeof(double), st, codebooks, d, m,
+               ksub, queries, base, luts);
     QADC_HIP_TRY(hipGetLastError());
     return QADC_OK;
 }

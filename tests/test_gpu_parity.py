@@ -50,6 +50,25 @@ def test_build_luts_matches_oracle(Q, O, with_base):
     np.testing.assert_allclose(got, want, rtol=1e-4, atol=0)
 
 
+@pytest.mark.parametrize("d,m,ksub,nq", [(96, 8, 256, 90), (8192, 8, 256, 3), (100, 100, 64, 11), (2048, 64, 64, 9), (960, 8, 256, 40), (7, 7, 256, 1030)])
+@pytest.mark.parametrize("with_base", [False, True])
+def test_build_luts_of_many_queries_equal_those_of_one(Q, d, m, ksub, nq, with_base):
+    """Both kernels, on either side of the line between them: the same tables bit for bit, and the float64 sums rounded once."""
+    import torch
+    g = torch.Generator(device="cuda:0")
+    g.manual_seed(d + nq)
+    cb = 50 * torch.rand((m, ksub, d // m), generator=g, device="cuda:0")
+    y = 50 * torch.rand((nq, d), generator=g, device="cuda:0")
+    base = 50 * torch.rand((nq, d), generator=g, device="cuda:0") if with_base else None
+    got = Q.qadc_build_luts(cb, y, base)
+    for q in {0, 1, nq // 2, nq - 1}:
+        one = Q.qadc_build_luts(cb, y[q:q + 1].contiguous(), base[q:q + 1].contiguous() if with_base else None)
+        assert torch.equal(one[0], got[q]), q
+    res = y.double() - (base.double() if with_base else 0.0)
+    exact = ((res[:3].reshape(-1, m, 1, d // m) - cb.double()[None]) ** 2).sum(3)
+    assert torch.allclose(got[:3].double(), exact, rtol=1e-7, atol=0)  # a float32 rounding, 6e-8
+
+
 def test_build_luts_8bit_tables(Q, O):
     rng = np.random.default_rng(0)
     cb = rng.normal(scale=30, size=(8, 256, 12)).astype(np.float32)
