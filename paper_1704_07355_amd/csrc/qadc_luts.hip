@@ -76,13 +76,13 @@ __global__ __launch_bounds__(256) void build_luts_wide_kernel(
 
 // A few queries of 2048 entries and more: eight rounds and more of one workgroup, each a round trip, against one (us, a workgroup
 // per query / a thread per entry: 1 query of 8 x 256 entries of 12 components 6.8 / 4.6, of 120 22 / 16, 64 of 32 x 256 of 4
-// 16.9 / 6.4).  More queries: a thread per entry reads the query again for every entry and twice the lines of the codebook
-// (8 x 256 of 12: 128 queries 6.8 / 6.1, 256 7.5 / 10.3, 4096 50 / 135; of 120: 33 23 / 30, 512 44 / 327; 32 x 64 of 8: 64
-// 4.2 / 4.4, 256 5.2 / 9.5).
+// 16.9 / 6.4, 128 17.8 / 11.2).  More queries: a thread per entry reads the query again for every entry and twice the lines of
+// the codebook (8 x 256 of 12: 64 queries 6.7 / 4.2, 128 6.8 / 6.1, 256 7.5 / 10.3, 4096 50 / 135; of 120: 16 22 / 17, 33 23 / 30,
+// 512 44 / 327; 32 x 64 of 8: 64 4.2 / 4.4, 256 5.2 / 9.5).
 static bool luts_wide_pay(int d, int m, int ksub, int nq)
 {
-    const int64_t entries = (int64_t)m * ksub;
-    return entries >= 2048 && ceil_div(entries, 256) * nq * (d / m) <= 8192;
+    const int64_t entries = (int64_t)m * ksub, dsub = d / m;
+    return entries >= 2048 && ceil_div(entries, 256) * nq * dsub <= (entries >= 8192 || dsub >= 64 ? 16384 : 8192);
 }
 
 int build_luts(const float *codebooks, int d, int m, int ksub, const float *queries,
@@ -92,7 +92,7 @@ int build_luts(const float *codebooks, int d, int m, int ksub, const float *quer
     if (m < 1 || d < m || d % m != 0 || (ksub != 16 && ksub != 64 && ksub != 256) || nq < 0 || d > 8192)
         return fail(QADC_EINVAL, "qadc_build_luts: unsupported d=%d m=%d ksub=%d nq=%d", d, m, ksub, nq);
     if (nq == 0) return QADC_OK;
-    if (luts_wide_pay(d, m, ksub, nq))  // (at most 1024 queries)
+    if (luts_wide_pay(d, m, ksub, nq))  // (at most 2048 queries)
         launch(QADC_PROF_TABLES, build_luts_wide_kernel, dim3((unsigned)ceil_div((int64_t)m * ksub, 256), (unsigned)nq), dim3(256), 0,
                st, codebooks, d, m, ksub, queries, base, luts);
     else

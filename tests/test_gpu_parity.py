@@ -50,7 +50,7 @@ def test_build_luts_matches_oracle(Q, O, with_base):
     np.testing.assert_allclose(got, want, rtol=1e-4, atol=0)
 
 
-@pytest.mark.parametrize("d,m,ksub,nq", [(96, 8, 256, 90), (8192, 8, 256, 3), (100, 100, 64, 11), (2048, 64, 64, 9), (960, 8, 256, 40), (7, 7, 256, 1030)])
+@pytest.mark.parametrize("d,m,ksub,nq", [(96, 8, 256, 90), (8192, 8, 256, 3), (100, 100, 64, 11), (2048, 64, 64, 9), (960, 8, 256, 18), (128, 32, 256, 130), (8, 8, 256, 1030)])
 @pytest.mark.parametrize("with_base", [False, True])
 def test_build_luts_of_many_queries_equal_those_of_one(Q, d, m, ksub, nq, with_base):
     """Both kernels, on either side of the line between them: the same tables bit for bit, and the float64 sums rounded once."""
