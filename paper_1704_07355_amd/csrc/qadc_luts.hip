@@ -105,67 +105,83 @@ int build_luts(const float *codebooks, int d, int m, int ksub, const float *quer
 // -------------------------------------------------------------- Section 3.3
 
 constexpr int QUANT_NT = 1024;
-constexpr int QUANT_MAX_M = 64;
 
 // KSUB = 16: 4-bit components, two per code byte (the paper's case).  KSUB = 256: 8-bit components,
 // one per code byte, the same quantizer applied to the 256-entry tables of Section 2.1's
 // standard product quantizer.  KSUB = 64: 6-bit components (the paper's Conclusion), stored back to
 // back, least significant bit first, four per three bytes.
 
-// The need-th smallest of n images of sums in LDS, by the whole workgroup: of up to 256 by a thread's count of the smaller
-// ones (one barrier; the histograms of a radix select take some fifteen).  cand has room for 256 and is 16-byte aligned.
-__device__ __forceinline__ unsigned nth_of_sums(unsigned *cand, int n, int need, SelectScratch *sc, unsigned *nth)
+// The bytes of a code (from any address) as words, all requested at once.
+template <int B>
+__device__ __forceinline__ void code_words(const uint8_t *c, unsigned (&w)[(B + 3) / 4])
 {
-    if (n > 256) return block_radix_select<unsigned, 4>(cand, (unsigned)n, (unsigned)need, sc);
-    const int tid = threadIdx.x;
-    if (tid >= n && tid < 256) cand[tid] = 0xffffffffu;
-    __syncthreads();
-    if (tid < n) {
-        const unsigned mine = cand[tid];
-        int less = 0, leq = 0;
-#pragma unroll 4
-        for (int i = 0; i < (n + 3) / 4; ++i) {
-            const uint4 v = reinterpret_cast<const uint4 *>(cand)[i];
-            less += (v.x < mine) + (v.y < mine) + (v.z < mine) + (v.w < mine);
-            leq += (v.x <= mine) + (v.y <= mine) + (v.z <= mine) + (v.w <= mine);
-        }
-        // (the padding counts among the equals of an image of its own value only, and there it changes nothing)
-        if (less < need && need <= leq) *nth = mine;  // (equal ones write the same)
-    }
-    __syncthreads();
-    return *nth;
+    if constexpr (B % 4 != 0) w[B / 4] = 0;
+    __builtin_memcpy(w, c, B);
 }
 
-// The B bytes of a code (6 to 32, from any address) as words, all requested at once (byte by byte, a code of 32 takes as many
-// round trips).
-__device__ __forceinline__ void code_words(const uint8_t *c, int B, unsigned (&w)[8])
+// Float ADC sum of a code (Eq. (2), float32, increasing component) over tables of KSUB entries.
+template <int KSUB, int B>
+__device__ __forceinline__ float sum_of_code(const unsigned (&w)[(B + 3) / 4], const float *lut)
 {
-    typedef unsigned u32_any __attribute__((aligned(1)));
-    const u32_any *cw = reinterpret_cast<const u32_any *>(c);
+    float acc = 0.0f;
+    if constexpr (KSUB == 64) {
 #pragma unroll
-    for (int k = 0; k < 8; ++k) w[k] = 4 * k + 4 <= B ? cw[k] : 0u;  // (uniform)
-    if (B == 6) w[1] = (unsigned)c[4] | ((unsigned)c[5] << 8);       // (the other lengths are whole words)
+        for (int j = 0; j < 4 * B / 3; ++j) {
+            const int k = 6 * j >> 5, sh = 6 * j & 31;
+            const unsigned v = sh <= 26 ? w[k] >> sh : __funnelshift_r(w[k], w[min(k + 1, (B - 1) / 4)], sh);
+            acc = acc + lut[j * 64 + (v & 63u)];
+        }
+    } else {
+#pragma unroll
+        for (int jb = 0; jb < B; ++jb) {
+            const unsigned comps = (w[jb >> 2] >> (8 * (jb & 3))) & 0xffu;
+            if constexpr (KSUB == 16) {
+                acc = acc + lut[(2 * jb) * 16 + (comps & 15u)];
+                acc = acc + lut[(2 * jb + 1) * 16 + (comps >> 4)];
+            } else {
+                acc = acc + lut[jb * 256 + comps];
+            }
+        }
+    }
+    return acc;
 }
 
-template <int KSUB>
-__global__ __launch_bounds__(QUANT_NT) void quantize_luts_kernel(
-    const float *__restrict__ luts, int ngroup, int m, const uint8_t *__restrict__ init_codes,
+// The need-th smallest of n images of sums in LDS, by the whole workgroup.  (As a call, which the compiler makes of it
+// by itself, 1 to 3 us more for some thousand sums.)
+__device__ __forceinline__ unsigned nth_of_sums(const unsigned *cand, int n, int need, SelectScratch *sc)
+{
+    unsigned nth;
+    [[clang::always_inline]] nth = block_radix_select_each<unsigned, 4>(
+        [&](auto f) {
+            for (unsigned i = threadIdx.x; i < (unsigned)n; i += blockDim.x) f(cand[i]);
+        },
+        (unsigned)need, sc);
+    return nth;
+}
+
+// A workgroup per query, two per compute unit (64 registers).  Bound by the chain of its steps for a few queries, by the
+// instructions of the sums and the selection for thousands.  One form per length of a code: with the number of words a number at
+// run time, each word behind a branch, a code's sum took twice as long (us; 4096 queries, 200 init codes, m = 16 84 -> 39, 8000
+// of m = 64 637 -> 267, one query 41 -> 28; 1000 queries, 200 codes of 32 six-bit components 44 -> 21).
+template <int KSUB, int B>
+__global__ __launch_bounds__(QUANT_NT, 8) void quantize_luts_kernel(
+    const float *__restrict__ luts, int ngroup, const uint8_t *__restrict__ init_codes,
     int n_init, const float *__restrict__ qmax_in, int R, int nbins, int qmin_mode,
     uint8_t *__restrict__ qluts, float *__restrict__ bias_out, float *__restrict__ delta_out,
     float *__restrict__ qmax_out)
 {
-    __shared__ float lut0[QUANT_MAX_M * 16];
-    __shared__ __attribute__((aligned(16))) unsigned cand[QADC_MAX_INIT];
-    __shared__ unsigned bias_ord[QUANT_MAX_M];
-    __shared__ float bias[QUANT_MAX_M];
+    constexpr int m = KSUB == 16 ? 2 * B : KSUB == 64 ? 4 * B / 3 : B;
+    __shared__ float lut0[KSUB == 16 ? m * 16 : 1];
+    __shared__ unsigned cand[QADC_MAX_INIT];
+    __shared__ unsigned bias_ord[m];
+    __shared__ float bias[m];
     __shared__ float delta_s;
-    __shared__ unsigned nth_s;
     __shared__ SelectScratch sc;
 
     const int tid = threadIdx.x;
     const int q = blockIdx.x;
     constexpr int LOG = KSUB == 16 ? 4 : KSUB == 64 ? 6 : 8;
-    const int entries = m * KSUB;
+    constexpr int entries = m * KSUB;
     const float *lq = luts + (size_t)q * ngroup * entries;
 
     if (KSUB == 16)
@@ -173,46 +189,16 @@ __global__ __launch_bounds__(QUANT_NT) void quantize_luts_kernel(
     for (int j = tid; j < m; j += QUANT_NT) bias_ord[j] = 0xffffffffu;
     __syncthreads();
 
-    // qmax: R-th smallest float ADC distance (Eq. (2), float32, increasing j) of the init codes
+    // qmax: R-th smallest float ADC distance of the init codes, with the first table set (cached after the first touch)
     float qmax;
     if (init_codes) {
-        const int B = KSUB == 16 ? m / 2 : KSUB == 64 ? 3 * m / 4 : m;
         for (int i = tid; i < n_init; i += QUANT_NT) {
-            unsigned w[8];
-            code_words(init_codes + (size_t)i * B, B, w);
-            float acc = 0.0f;
-            if constexpr (KSUB == 64) {
-#pragma unroll
-                for (int j = 0; j < 32; ++j) {
-                    if (j < m) {  // uniform
-                        constexpr int BITS = 6;
-                        const int k = BITS * j >> 5, sh = BITS * j & 31;
-                        const unsigned v = sh <= 32 - BITS ? w[k] >> sh : __funnelshift_r(w[k], w[(k + 1) & 7], sh);
-                        acc = acc + lq[j * 64 + (v & 63u)];  // the first table set
-                    }
-                }
-            } else {
-#pragma unroll
-                for (int k = 0; k < 8; ++k) {
-                    if (4 * k < B) {  // uniform (four bytes or none)
-#pragma unroll
-                        for (int b = 0; b < 4; ++b) {
-                            const unsigned comps = (w[k] >> (8 * b)) & 0xffu;
-                            const int jb = 4 * k + b;
-                            if constexpr (KSUB == 16) {
-                                acc = acc + lut0[(2 * jb) * 16 + (comps & 15u)];
-                                acc = acc + lut0[(2 * jb + 1) * 16 + (comps >> 4)];
-                            } else {
-                                acc = acc + lq[jb * 256 + comps];  // the first table set; cached after the first touch
-                            }
-                        }
-                    }
-                }
-            }
-            cand[i] = f2ord(acc);
+            unsigned w[(B + 3) / 4];
+            code_words<B>(init_codes + (size_t)i * B, w);
+            cand[i] = f2ord(sum_of_code<KSUB, B>(w, KSUB == 16 ? lut0 : lq));
         }
         __syncthreads();
-        qmax = ord2f(nth_of_sums(cand, n_init, min(R, n_init), &sc, &nth_s));
+        qmax = ord2f(nth_of_sums(cand, n_init, min(R, n_init), &sc));
     } else {
         qmax = qmax_in[q];
     }
@@ -291,47 +277,68 @@ int quantize_luts(int ksub, const float *luts, int nq, int ngroup, int m, const 
         return fail(QADC_EINVAL, "qadc_quantize_luts: neither init_codes nor qmax_in given");
     }
     if (nq == 0) return QADC_OK;
-    if (ksub == 16)
-        launch(QADC_PROF_QUANTIZE, quantize_luts_kernel<16>, dim3(nq), dim3(QUANT_NT), 0, st, luts, ngroup, m,
-               init_codes, (int)n_init, qmax_in, R, nbins, qmin_mode, qluts, bias, delta, qmax_out);
-    else if (ksub == 64)
-        launch(QADC_PROF_QUANTIZE, quantize_luts_kernel<64>, dim3(nq), dim3(QUANT_NT), 0, st, luts, ngroup, m,
-               init_codes, (int)n_init, qmax_in, R, nbins, qmin_mode, qluts, bias, delta, qmax_out);
-    else
-        launch(QADC_PROF_QUANTIZE, quantize_luts_kernel<256>, dim3(nq), dim3(QUANT_NT), 0, st, luts, ngroup, m,
-               init_codes, (int)n_init, qmax_in, R, nbins, qmin_mode, qluts, bias, delta, qmax_out);
+#define QADC_QUANT_CASE(KSUB_, B_)                                                                                     \
+    case B_:                                                                                                        \
+        launch(QADC_PROF_QUANTIZE, quantize_luts_kernel<KSUB_, B_>, dim3(nq), dim3(QUANT_NT), 0, st, luts, ngroup,     \
+               init_codes, (int)n_init, qmax_in, R, nbins, qmin_mode, qluts, bias, delta, qmax_out);                \
+        break;
+    if (ksub == 16) {
+        switch (m / 2) {
+            QADC_QUANT_CASE(16, 4)
+            QADC_QUANT_CASE(16, 8)
+            QADC_QUANT_CASE(16, 16)
+            QADC_QUANT_CASE(16, 32)
+        }
+    } else if (ksub == 64) {
+        switch (3 * m / 4) {
+            QADC_QUANT_CASE(64, 6)
+            QADC_QUANT_CASE(64, 12)
+            QADC_QUANT_CASE(64, 24)
+        }
+    } else {
+        switch (m) {
+            QADC_QUANT_CASE(256, 4)
+            QADC_QUANT_CASE(256, 8)
+            QADC_QUANT_CASE(256, 16)
+            QADC_QUANT_CASE(256, 32)
+        }
+    }
+#undef QADC_QUANT_CASE
     QADC_HIP_TRY(hipGetLastError());
     return QADC_OK;
 }
 
 // Both steps for a batch of qadc_search, a workgroup per query and a thread per entry: the float tables stay in LDS and
 // are not written.  The arithmetic of build_luts_kernel and quantize_luts_kernel.  (As two launches 9.9 us for 16 queries
-// m = 16, 16.1 for 12 m = 64; 8.9 and 12.5 as one.)
+// m = 16, 16.1 for 12 m = 64; 8.9 and 12.1 as one; 500 queries, 8000 init codes, m = 64 51.6, 83.7 with the sum's loop over a number
+// of words that the compiler does not know.)
 constexpr int SEARCH_TABLES_MAX_D = 2048;
 
-__global__ __launch_bounds__(1024) void search_tables_kernel(
-    const float *__restrict__ codebooks, int d, int m, const float *__restrict__ queries, const uint8_t *__restrict__ codes,
+template <int B>
+__global__ __launch_bounds__(1024, 8) void search_tables_kernel(
+    const float *__restrict__ codebooks, int d, const float *__restrict__ queries, const uint8_t *__restrict__ codes,
     int n_init, int R, int nbins, int qmin_mode, uint8_t *__restrict__ qluts, uint8_t *__restrict__ qluts_too)
 {
+    constexpr int m = 2 * B;
     __shared__ float yq[SEARCH_TABLES_MAX_D];
-    __shared__ float lut[QUANT_MAX_M * 16];
-    __shared__ __attribute__((aligned(16))) unsigned cand[QADC_MAX_INIT];
-    __shared__ unsigned bias_ord[QUANT_MAX_M];
-    __shared__ float bias[QUANT_MAX_M];
+    __shared__ float lut[m * 16];
+    __shared__ unsigned cand[QADC_MAX_INIT];
+    __shared__ unsigned bias_ord[m];
+    __shared__ float bias[m];
     __shared__ float delta_s;
-    __shared__ unsigned nth_s;
     __shared__ SelectScratch sc;
     constexpr int DREG = 16;
     const int tid = threadIdx.x, q = blockIdx.x;
-    const int entries = m * 16, dsub = d / m, B = m / 2;
+    constexpr int entries = m * 16;
+    const int dsub = d / m;
     // everything that comes from memory is requested at once
     for (int t = tid; t < d; t += 1024) yq[t] = queries[(size_t)q * d + t];
     float cv[DREG];
     const float *c = codebooks + (size_t)min(tid, entries - 1) * dsub;
 #pragma unroll
     for (int t = 0; t < DREG; ++t) cv[t] = c[min(t, dsub - 1)];
-    unsigned w[8];
-    code_words(codes + (size_t)min(tid, n_init - 1) * B, B, w);
+    unsigned w[B / 4];
+    code_words<B>(codes + (size_t)min(tid, n_init - 1) * B, w);
     __syncthreads();
     const int j = tid >> 4;
     float v = 0.0f;
@@ -357,24 +364,11 @@ __global__ __launch_bounds__(1024) void search_tables_kernel(
     }
     __syncthreads();
     for (int i = tid; i < n_init; i += 1024) {
-        if (i != tid) code_words(codes + (size_t)i * B, B, w);
-        float acc = 0.0f;
-#pragma unroll
-        for (int k = 0; k < 8; ++k) {
-            if (4 * k < B) {  // uniform
-#pragma unroll
-                for (int b = 0; b < 4; ++b) {
-                    const unsigned comps = (w[k] >> (8 * b)) & 0xffu;
-                    const int jb = 4 * k + b;
-                    acc = acc + lut[(2 * jb) * 16 + (comps & 15u)];
-                    acc = acc + lut[(2 * jb + 1) * 16 + (comps >> 4)];
-                }
-            }
-        }
-        cand[i] = f2ord(acc);
+        if (i != tid) code_words<B>(codes + (size_t)i * B, w);
+        cand[i] = f2ord(sum_of_code<16, B>(w, lut));
     }
     __syncthreads();
-    const float qmax = ord2f(nth_of_sums(cand, n_init, min(R, n_init), &sc, &nth_s));
+    const float qmax = ord2f(nth_of_sums(cand, n_init, min(R, n_init), &sc));
     if (tid == 0) {
         float qmin;
         if (qmin_mode == QADC_QMIN_GLOBAL) {
@@ -403,8 +397,18 @@ __global__ __launch_bounds__(1024) void search_tables_kernel(
 void search_tables(const float *codebooks, int d, int m, const float *queries, int nq, const uint8_t *codes, int n_init,
                    int R, int nbins, int qmin_mode, uint8_t *qluts, uint8_t *qluts_too, hipStream_t st)
 {
-    launch(QADC_PROF_TABLES, search_tables_kernel, dim3((unsigned)nq), dim3(1024), 0, st, codebooks, d, m, queries, codes,
-           n_init, R, nbins, qmin_mode, qluts, qluts_too);
+#define QADC_CASE(B_)                                                                                               \
+    case B_:                                                                                                        \
+        launch(QADC_PROF_TABLES, search_tables_kernel<B_>, dim3((unsigned)nq), dim3(1024), 0, st, codebooks, d, queries, \
+               codes, n_init, R, nbins, qmin_mode, qluts, qluts_too);                                              \
+        break;
+    switch (m / 2) {
+        QADC_CASE(4)
+        QADC_CASE(8)
+        QADC_CASE(16)
+        QADC_CASE(32)
+    }
+#undef QADC_CASE
 }
 
 }  // namespace qadc
