@@ -709,6 +709,81 @@ void ivf_select_smallest(const float *dist, int rows, int K, int count, int32_t 
 
 // ----------------------------------------------------------------- Tables
 
+// Float tables of the probed cells for ivf_tables_kernel<0>: luts[q][p][j][i] = || (y_q - centroid_p)^j - C^j[i] ||^2, float64
+// inside, one rounding to float32; +inf for unused probe slots (cell id < 0).
+// A workgroup takes CELLS of a query's cells and reads the codebooks once for them, a thread per entry; the cells' residuals
+// are in LDS as float64, tables a component apart from each other against bank conflicts (CELLS = 0: no room for them, d beyond
+// 8000 or so; taken from memory for every entry).  Bound by the reads of the codebooks, rows d / m floats apart.
+// us for the tables of 64 probed cells, as they are here / an entry by the query's one workgroup, from memory, twice: 40 queries
+// d = 960, m = 32 47 / 902, 500 137 / 3413, d = 96, m = 32 32 / 112, 40 queries d = 200, m = 8 21 / 142.
+template <int CELLS>
+__global__ __launch_bounds__(256) void ivf_float_tables_kernel(
+    const float *__restrict__ codebooks, int d, int m, const float *__restrict__ queries,
+    const float *__restrict__ coarse, const float *__restrict__ halves, const uint32_t *__restrict__ cell_ids,
+    int Kh, const int32_t *__restrict__ probes, int nprobe, float *__restrict__ luts)
+{
+    extern __shared__ double res[];  // [CELLS][m][dsub + 1]
+    constexpr int N = CELLS ? CELLS : 1;
+    const int q = blockIdx.y, p0 = blockIdx.x * N;
+    const int dsub = d / m, dh = d >> 1, pitch = dsub + 1;
+    const int entries = m * 16;
+    const float *yq = queries + (size_t)q * d;
+    const float *row[N][2];  // the centroid's components of the first and of the second half (null: no cell)
+#pragma unroll
+    for (int k = 0; k < N; ++k) {
+        const int cell = p0 + k < nprobe ? probes[(size_t)q * nprobe + p0 + k] : -1;
+        row[k][0] = row[k][1] = nullptr;
+        if (cell >= 0) {
+            if (coarse) {
+                row[k][0] = row[k][1] = coarse + (size_t)cell * d;
+            } else {  // list `cell` of a multi-index: the centroid is a pair of half-centroids
+                const unsigned id = cell_ids[cell];
+                row[k][0] = halves + (size_t)(id / (unsigned)Kh) * dh;
+                row[k][1] = halves + ((size_t)Kh + id % (unsigned)Kh) * dh - dh;
+            }
+        }
+    }
+    auto residual = [&](int k, int t) {
+        const float *r = coarse || t < dh ? row[k][0] : row[k][1];
+        return (double)yq[t] - (r ? (double)r[t] : 0.0);
+    };
+    if constexpr (CELLS > 0) {
+        for (int t = threadIdx.x; t < d; t += 256) {
+            const int at = t + t / dsub;
+#pragma unroll
+            for (int k = 0; k < N; ++k) res[k * m * pitch + at] = residual(k, t);
+        }
+        __syncthreads();
+    }
+    for (int e = threadIdx.x; e < entries; e += 256) {
+        const float *c = codebooks + (size_t)e * dsub;
+        const int j = e >> 4;
+        double acc[N];
+#pragma unroll
+        for (int k = 0; k < N; ++k) acc[k] = 0.0;
+        auto add = [&](int t, float cv) {
+#pragma unroll
+            for (int k = 0; k < N; ++k) {
+                const double df = (CELLS > 0 ? res[k * m * pitch + j * pitch + t] : residual(k, j * dsub + t)) - (double)cv;
+                acc[k] += df * df;
+            }
+        };
+        int t0 = 0;
+        for (; t0 + 8 <= dsub; t0 += 8) {
+            float cv[8];
+#pragma unroll
+            for (int t = 0; t < 8; ++t) cv[t] = c[t0 + t];
+#pragma unroll
+            for (int t = 0; t < 8; ++t) add(t0 + t, cv[t]);
+        }
+        for (; t0 < dsub; ++t0) add(t0, c[t0]);
+#pragma unroll
+        for (int k = 0; k < N; ++k)
+            if (p0 + k < nprobe)
+                luts[((size_t)q * nprobe + p0 + k) * entries + e] = row[k][0] ? (float)acc[k] : __builtin_inff();
+    }
+}
+
 // Batches: Tables, the qmax walk and the quantizer by one workgroup per query, a thread per table entry and, where the
 // tables are smaller than the workgroup, per one of several probed cells at a time.  Entry (j, i) of cell p is
 // || (y_q - centroid_p)^j - C^j[i] ||^2, float64 inside, one rounding to float32 (as the exhaustive tables kernel); unused
@@ -718,17 +793,20 @@ void ivf_select_smallest(const float *dist, int rows, int K, int count, int32_t 
 //      own cell; 0 when the lists are empty.  The tables of the lists walked pass through LDS.
 //   2. bias_j = smallest entry of table j over all probed cells.
 //   3. the entries again, quantized (the arithmetic of quantize_luts_kernel).
-// Bound by its float64 instructions and, below some 500 queries, by the chain of steps of one workgroup.  The entries stay in
-// registers between steps 2 and 3: as three kernels, the float tables of 4096 queries x 64 cells were 537 MB written by
+// Bound by its float64 instructions and, below some 500 queries, by the chain of steps of one workgroup.  A thread's first KEEP
+// entries stay in registers between steps 2 and 3, those beyond are computed twice (128 registers; the forms of 4 and 8
+// components spill 6 of them, that of 16 16): as three kernels, the float tables of 4096 queries x 64 cells were 537 MB written by
 // one, gathered from by the second and read by the third, 560 us (m = 32, d = 128) against 335 now; 512 queries 82 against 49,
 // 150 queries x 24 cells (m = 16) 25 against 12.  (Every entry computed twice instead, with no registers held: 64 us for the
 // 512.  Every lane converting its own residuals: 51.)
+// Other lengths (DSUB = 0), and calls for which that chain is too long (ivf_tables_form): the entries come from memory, where
+// ivf_float_tables_kernel has left them, and are read once.
 constexpr int IVF_WALK = 4;  // lists walked at a time, per table set that the workgroup's threads are
-template <int DSUB>  // d / m; 0: any
+template <int DSUB>  // d / m; 0: any, the entries from `luts`
 __global__ __launch_bounds__(1024) void ivf_tables_kernel(
     const float *__restrict__ codebooks, int d, int m, const float *__restrict__ queries,
     const float *__restrict__ coarse, const float *__restrict__ halves, const uint32_t *__restrict__ cell_ids,
-    int Kh, const int32_t *__restrict__ probes, int nprobe, const int64_t *__restrict__ list_off,
+    int Kh, const int32_t *__restrict__ probes, int nprobe, const float *__restrict__ luts, const int64_t *__restrict__ list_off,
     const uint8_t *__restrict__ codes, int64_t n_total, int init, int R, int nbins, int qmin_mode, long long unit,
     unsigned *__restrict__ qunits, uint8_t *__restrict__ qluts, char *__restrict__ ws, size_t ws_stride,
     size_t counts_off, int W, size_t countsA_off, unsigned *__restrict__ pair_cnt, int K)
@@ -803,13 +881,10 @@ __global__ __launch_bounds__(1024) void ivf_tables_kernel(
 
     // this thread's centroid and sub-vector of the query, and where its sub-vector of a cell's centroid lies
     constexpr int REGS = DSUB ? DSUB : 1;
-    double c[REGS], y[REGS];
+    double c[REGS];
     if constexpr (DSUB > 0) {
 #pragma unroll
-        for (int t = 0; t < DSUB; ++t) {
-            c[t] = (double)codebooks[(size_t)e * DSUB + t];
-            y[t] = (double)queries[(size_t)q * d + t0 + t];
-        }
+        for (int t = 0; t < DSUB; ++t) c[t] = (double)codebooks[(size_t)e * DSUB + t];
     }
     const int dh = d >> 1;
     const bool first = coarse || t0 < dh;  // (a sub-vector lies inside one half)
@@ -817,22 +892,8 @@ __global__ __launch_bounds__(1024) void ivf_tables_kernel(
     const size_t ld = coarse ? (size_t)d : (size_t)dh;
     auto row_of = [&](int p) { return first ? row0[p] : row1[p]; };
     auto entry = [&](int p) {
-        if (row_of(p) < 0) return __builtin_inff();
-        const float *r = base + (size_t)row_of(p) * ld;
-        double acc = 0.0;
-        if constexpr (DSUB > 0) {
-#pragma unroll
-            for (int t = 0; t < DSUB; ++t) {
-                const double df = (y[t] - (double)r[t]) - c[t];
-                acc += df * df;
-            }
-        } else {
-            for (int t = 0; t < dsub; ++t) {
-                const double df = ((double)queries[(size_t)q * d + t0 + t] - (double)r[t]) - (double)codebooks[(size_t)e * dsub + t];
-                acc += df * df;
-            }
-        }
-        return (float)acc;
+        if constexpr (DSUB == 0) return luts[((size_t)q * nprobe + p) * entries + e];
+        return 0.0f;
     };
     // The same for SIDE probes at a time: the 16 lanes of a table need the same residuals y - centroid, so lane k % 16 takes
     // component k % DSUB of probe k / DSUB, and the others get it from there.  (Every lane for itself, conversions and
@@ -864,12 +925,17 @@ __global__ __launch_bounds__(1024) void ivf_tables_kernel(
     };
     // f(p, entry) for this thread's probes from p0 on
     auto each_probe = [&](int p0, auto f) {
-        for (int p = p0 + sub; p < nprobe; p += SIDE * subs) {  // uniform in a wavefront
-            float v[SIDE];
-            if constexpr (DSUB > 0) entries_of(p, residuals(p), v);
-            else v[0] = entry(p);
+        constexpr int STEP = DSUB > 0 ? SIDE : 8;
+        for (int p = p0 + sub; p < nprobe; p += STEP * subs) {  // uniform in a wavefront
+            float v[STEP];
+            if constexpr (DSUB > 0) {
+                entries_of(p, residuals(p), v);
+            } else {
 #pragma unroll
-            for (int a = 0; a < SIDE; ++a)
+                for (int a = 0; a < STEP; ++a) v[a] = entry(min(p + a * subs, nprobe - 1));
+            }
+#pragma unroll
+            for (int a = 0; a < STEP; ++a)
                 if (p + a * subs < nprobe) f(p + a * subs, v[a]);
         }
     };
@@ -878,13 +944,18 @@ __global__ __launch_bounds__(1024) void ivf_tables_kernel(
     const int walked = __syncthreads_count(tid < nprobe && start[min(tid, nprobe)] < n_walk);  // lists with a code of the walk before their end
     unsigned least = 0xffffffffu;  // smallest value of this entry, as its order-preserving image
     for (int p0 = 0; p0 < walked; p0 += IVF_WALK * subs) {  // uniform
+        if constexpr (DSUB == 0) {
 #pragma unroll
-        for (int a = 0; a < IVF_WALK; ++a) {
-            const int p = p0 + sub + a * subs;
-            if (p < walked) {
-                const float v = entry(p);
-                lut_s[a][tid] = v;
-                least = min(least, f2ord(v));
+            for (int a = 0; a < IVF_WALK; ++a) lut_s[a][tid] = entry(min(p0 + sub + a * subs, nprobe - 1));
+        } else {
+            constexpr int AT_ONCE = SIDE < IVF_WALK ? SIDE : IVF_WALK;
+#pragma unroll
+            for (int a0 = 0; a0 < IVF_WALK; a0 += AT_ONCE) {
+                if (p0 + a0 * subs >= walked) break;  // uniform
+                float v[SIDE];
+                entries_of(p0 + sub + a0 * subs, residuals(p0 + sub + a0 * subs), v);
+#pragma unroll
+                for (int a = 0; a < AT_ONCE; ++a) lut_s[a0 + a][tid] = v[a];
             }
         }
         __syncthreads();
@@ -919,23 +990,31 @@ __global__ __launch_bounds__(1024) void ivf_tables_kernel(
         __syncthreads();
     }
     // the entries of the first KEEP probes of the thread stay in registers for step 3, those beyond are computed twice
-    constexpr int KEEP = DSUB == 0 || DSUB > 8 ? 0 : DSUB <= 4 ? 64 : 32, BLOCK = AHEAD * SIDE;
+    constexpr int KEEP = DSUB <= 4 ? 64 : 32, BLOCK = DSUB > 0 ? AHEAD * SIDE : 8;
     static_assert(KEEP % BLOCK == 0, "whole blocks");
     float kept[KEEP ? KEEP : 1];
 #pragma unroll
     for (int k = 0; k < KEEP; k += BLOCK) {
         if (k * subs < nprobe) {  // uniform
-            double res[AHEAD];
+            // (the last probe again where there is none)
+            if constexpr (DSUB == 0) {
 #pragma unroll
-            for (int a = 0; a < AHEAD; ++a) res[a] = residuals(sub + (k + a * SIDE) * subs);
+                for (int a = 0; a < BLOCK; ++a) kept[k + a] = entry(min(sub + (k + a) * subs, nprobe - 1));
 #pragma unroll
-            for (int a = 0; a < AHEAD; ++a) {
-                float v[SIDE];
-                entries_of(sub + (k + a * SIDE) * subs, res[a], v);
+                for (int a = 0; a < BLOCK; ++a) least = min(least, f2ord(kept[k + a]));
+            } else {
+                double res[AHEAD];
 #pragma unroll
-                for (int i = 0; i < SIDE; ++i) {
-                    kept[k + a * SIDE + i] = v[i];
-                    least = min(least, f2ord(v[i]));  // (the last probe again where there is none)
+                for (int a = 0; a < AHEAD; ++a) res[a] = residuals(sub + (k + a * SIDE) * subs);
+#pragma unroll
+                for (int a = 0; a < AHEAD; ++a) {
+                    float v[SIDE];
+                    entries_of(sub + (k + a * SIDE) * subs, res[a], v);
+#pragma unroll
+                    for (int i = 0; i < SIDE; ++i) {
+                        kept[k + a * SIDE + i] = v[i];
+                        least = min(least, f2ord(v[i]));
+                    }
                 }
             }
         }
@@ -1836,6 +1915,21 @@ void ivf_filter_convert(const float *coarse, int K, int d, const float *queries,
 const float2 *ivf_filter(int K, int d, int nq, int i0, int ni, void *room, float *dist, int *components, unsigned **rest,
                          hipStream_t st);
 
+// Which form of ivf_tables_kernel: the sub-vector length, or 0 with the float tables by a kernel of their own before it, a
+// workgroup per four (or one) probed cells -- for lengths without a form, and where one workgroup per query is too long a chain.
+// That one is as long as probed cells x components; below, the float tables' way through memory costs more.  us per call,
+// form of the length / 0, over 2e6 codes: 33 queries, 64 probed cells x 256 components, m = 32 104 / 105, 128 x 256 141 / 126,
+// 256 x 512, m = 64 379 / 278, 256 x 1024 572 / 330; 128 queries 256 x 1024 673 / 509, 1000 queries 200 x 1024 2015 / 1869, 200 x 512
+// 1400 / 1380, 200 x 128, m = 32 551 / 703, 64 x 256, m = 16 347 / 353.
+static int ivf_tables_form(int d, int m, int nb, int nprobe)
+{
+    const int dsub = d / m;
+    const int64_t chain = (int64_t)nprobe * d;
+    if (dsub != 2 && dsub != 4 && dsub != 6 && dsub != 8 && dsub != 16) return 0;
+    if (nb <= 128 && chain >= (dsub == 4 ? 65536 : 32768) && dsub > 2) return 0;
+    return dsub == 16 && chain >= 49152 ? 0 : dsub;
+}
+
 struct IvfPlan {
     int qb, W;
     int wgs;  // workgroups a query gets of the per-query scan, at most (W: report regions laid out)
@@ -2104,16 +2198,28 @@ int ivf_search(const qadc_ivf_index *ix, const float *queries, int nq, int nprob
             const int nt = m == 64 || nb <= 256 ? 1024 : 512;
 #define QADC_TABLES_CASE(D_)                                                                                             \
     launch(QADC_PROF_IVF_TABLES, ivf_tables_kernel<D_>, dim3(nb), dim3(nt), 0, st, ix->codebooks, d, m, yq, ix->coarse,  \
-           ix->halves, ix->cell_ids, ix->Kh, (const int32_t *)probes, nprobe, ix->list_off, ix->codes, ix->n, init, R,   \
+           ix->halves, ix->cell_ids, ix->Kh, (const int32_t *)probes, nprobe, (const float *)luts, ix->list_off, ix->codes, ix->n, init, R,   \
            nbins, qmin_mode, unit, qunits, qluts, scan_ws, p.stride, p.l.counts_off, p.W, p.countsA_off,                 \
            p.shared ? (unsigned *)(ws + p.off_paircnt) : (unsigned *)nullptr, K)
-            switch (d / m) {
+            switch (ivf_tables_form(d, m, nb, nprobe)) {
             case 2: QADC_TABLES_CASE(2); break;
             case 4: QADC_TABLES_CASE(4); break;
             case 6: QADC_TABLES_CASE(6); break;
             case 8: QADC_TABLES_CASE(8); break;
             case 16: QADC_TABLES_CASE(16); break;
-            default: QADC_TABLES_CASE(0);
+            default: {
+                const size_t cell_bytes = (size_t)(d + m) * sizeof(double);
+                const int cells = cell_bytes > 65536 ? 0 : 4 * cell_bytes > 65536 || (int64_t)nb * nprobe < 4096 ? 1 : 4;
+#define QADC_FLOAT_CASE(CELLS_)                                                                                           \
+    launch(QADC_PROF_IVF_TABLES, ivf_float_tables_kernel<CELLS_>,                                                        \
+           dim3((unsigned)ceil_div(nprobe, std::max(1, CELLS_)), (unsigned)nb), dim3(256), CELLS_ * cell_bytes, st,       \
+           ix->codebooks, d, m, yq, ix->coarse, ix->halves, ix->cell_ids, ix->Kh, (const int32_t *)probes, nprobe, luts)
+                if (cells == 0) QADC_FLOAT_CASE(0);
+                else if (cells == 1) QADC_FLOAT_CASE(1);
+                else QADC_FLOAT_CASE(4);
+#undef QADC_FLOAT_CASE
+                QADC_TABLES_CASE(0);
+            }
             }
 #undef QADC_TABLES_CASE
         }

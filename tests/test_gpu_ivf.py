@@ -384,11 +384,13 @@ def test_ivf_few_queries_path_equals_batch_path(Q, O, mode):
 
 
 @pytest.mark.parametrize("m,d,nprobe,nq", [(8, 16, 150, 33), (8, 48, 20, 300), (16, 64, 70, 40), (16, 128, 140, 260), (16, 256, 9, 64),
-                                           (32, 64, 256, 34), (32, 96, 65, 257), (32, 256, 3, 33), (64, 128, 70, 40), (64, 64, 33, 520)])
+                                           (32, 64, 256, 34), (32, 96, 65, 257), (32, 256, 3, 33), (64, 128, 70, 40), (64, 64, 33, 520),
+                                           (8, 200, 21, 300), (16, 512, 7, 33), (32, 960, 65, 64), (64, 1024, 33, 34), (64, 256, 256, 33),
+                                           (16, 256, 191, 33), (16, 256, 192, 130), (8, 8192, 3, 33)])
 @pytest.mark.parametrize("mode", [0, 1])
 def test_ivf_tables_of_batches_equal_those_of_few_queries(Q, m, d, nprobe, nq, mode):
-    """Every sub-vector length with and without a form of its own, several cells at a time or one, more probed cells than a
-    thread keeps, unused slots, a walk over many short lists: the 8-bit tables of calls of a few queries (kernels of their
+    """Every sub-vector length with and without a form of its own, either side of the line between the forms, several cells
+    at a time or one, a ragged last set of cells, components that have no room in LDS, more probed cells than a thread keeps, unused slots, a walk over many short lists: the 8-bit tables of calls of a few queries (kernels of their
     own), byte for byte, and the same neighbours; and of a query whose tables have no range (delta = 1)."""
     import torch
     g = torch.Generator(device="cuda:0")

@@ -318,3 +318,30 @@ def test_probes_do_not_depend_on_the_batch(Q, K, dh, nq):
 def test_probes_of_an_odd_number_of_centroids_do_not_depend_on_the_batch(Q, K, dh, nq):
     """The tiled distance kernel over both halves: the second half's distances start off an 8-byte boundary."""
     test_probes_do_not_depend_on_the_batch(Q, K, dh, nq)
+
+
+@pytest.mark.parametrize("d,m,nprobe,nq", [(96, 32, 37, 40), (96, 8, 9, 700), (256, 16, 20, 50), (768, 64, 70, 33), (128, 32, 40, 34), (1024, 64, 40, 35)])
+def test_tables_of_batches_with_halves_equal_those_with_centroids(Q, d, m, nprobe, nq):
+    """Lists whose centroids are pairs of half-centroids and the same lists with the centroids written out: the same 8-bit
+    tables, byte for byte, and neighbours, for sub-vector lengths with and without a form of their own."""
+    import torch
+    Kh = 9
+    g = torch.Generator(device="cuda:0")
+    g.manual_seed(d + m)
+    halves = 100 * torch.rand((2, Kh, d // 2), generator=g, device="cuda:0")
+    cb = 40 * torch.rand((m, 16, d // m), generator=g, device="cuda:0")
+    K, n = Kh * Kh, 81 * 30
+    codes = torch.randint(0, 256, (n, m // 2), generator=g, device="cuda:0", dtype=torch.uint8)
+    off, ids = torch.arange(K + 1, device="cuda:0") * 30, torch.arange(n, dtype=torch.int32, device="cuda:0")
+    pairs = Q.IvfIndex(None, off, codes, ids, cb, halves=halves, cell_ids=torch.arange(K, dtype=torch.int32, device="cuda:0"))
+    whole = Q.IvfIndex(Q.qadc_multi_index_cells(halves), off, codes, ids, cb)
+    queries = 100 * torch.rand((nq, d), generator=g, device="cuda:0")
+    probes = torch.stack([torch.randperm(K, generator=g, device="cuda:0")[:nprobe] for _ in range(nq)]).int()
+    probes[::5, nprobe // 3] = -1
+    a = Q.qadc_ivf_search(pairs, queries, nprobe, 50, 300, probes_in=probes, debug=True)
+    b = Q.qadc_ivf_search(whole, queries, nprobe, 50, 300, probes_in=probes, debug=True)
+    for x, y in zip(a, b):
+        assert torch.equal(x, y)
+    few = Q.qadc_ivf_search(pairs, queries[:5].contiguous(), nprobe, 50, 300, probes_in=probes[:5].contiguous(), debug=True)
+    for x, y in zip(a, few):
+        assert torch.equal(x[:5], y)
