@@ -1245,7 +1245,7 @@ __global__ __launch_bounds__(IVF_FINISH_NT) void ivf_finish_kernel(
 // ------------------------------------------------------------------- Seed
 //
 // A bound for the scan: the quantized sums (Alg. 2) of a sample of the query's codes -- the
-// first `per_list` codes of every probed list -- are histogrammed by one workgroup per query;
+// first `per_list` codes of the closest lists and those of the qmax walk -- are histogrammed by one workgroup per query;
 // the bin where the running count reaches R bounds the query's R-th smallest sum from above.
 // It is left in the first word of the query's control block as bound + 1 (0: no bound).
 // The sample uses the 16-entry tables directly (two lookups per code byte): building pair
@@ -1264,7 +1264,7 @@ template <int B>
 __global__ __launch_bounds__(IVF_SEED_NT) void ivf_seed_kernel(
     const int64_t *__restrict__ list_off, const uint8_t *__restrict__ codes,
     const int32_t *__restrict__ probes, int nprobe, const uint8_t *__restrict__ qluts, int cap_i,
-    int R, int per_list, char *__restrict__ ws, size_t ws_stride, int64_t n_total, int long_shift, int nseed,
+    int R, int per_list, char *__restrict__ ws, size_t ws_stride, int64_t n_total, int long_shift, int nseed, int init,
     IvfQuantizer fq, IvfPairs pairs)
 {
     constexpr int NT = IVF_SEED_NT;
@@ -1283,17 +1283,29 @@ __global__ __launch_bounds__(IVF_SEED_NT) void ivf_seed_kernel(
     const int per_part = (nseed + parts - 1) / parts;
     const int p_begin = blockIdx.y * per_part, p_end = min(nseed, p_begin + per_part);
     const unsigned cap = (unsigned)cap_i;
+    long long whole = 0;
     if (tid < nprobe) {
         const int cell = probes[(size_t)q * nprobe + tid];
         long long l = 0, h = 0;
         if (cell >= 0) { l = list_off[cell]; h = list_off[cell + 1]; }
         if (l < 0 || h > n_total || h < l) l = h = 0;  // offsets that are not a list: nothing is read
         lo[tid] = l;
-        len[tid] = (int)min((long long)per_list, h - l);
-        // with long_shift the sample of a list is at least its 2^-long_shift part: the bound then
-        // reflects the lists in proportion to their lengths
-        more[tid] = long_shift > 0 ? (int)max(0ll, min((h - l) >> long_shift, 1ll << 30) - per_list) : 0;
+        whole = h - l;
+        len[tid] = (int)min((long long)per_list, whole);
     }
+    // The sample holds the codes that qmax was found among: R of them are within the quantizer's range (sums that saturate do
+    // not count: next to always fewer than leave R), so that there is a bound.  Where it did not, lists longer than
+    // per_list and many init codes left fewer than R: no bound, and a scan with barriers in every tile.  (100 queries x 100 lists
+    // of 3900 codes, m = 16, R = 100, 3000 init codes 366 -> 148 us a call; 500 x 64 of 500, m = 8, 1000 init codes 389 -> 173.)
+    // With long_shift the sample of a list is at least its 2^-long_shift part: the bound then reflects the lists in
+    // proportion to their lengths.
+    long long least = 0;
+    if (tid < WAVE) {  // (the closest 64 at most; nseed is 16)
+        const unsigned taken = tid < nseed ? (unsigned)min((long long)init, whole) : 0u;
+        least = max(0, init - (int)(wave_running_sum(taken) - taken));  // what the walk still takes when it comes to this list
+    }
+    if (long_shift > 0) least = max(least, min(whole >> long_shift, 1ll << 30));
+    if (tid < nprobe) more[tid] = (int)max(0ll, min(least, whole) - per_list);
     for (int e = tid; e < 256; e += NT) hist[e] = 0;
     for (int p0 = p_begin; p0 < p_end; p0 += IVF_SEED_PCH) {  // uniform
         const int np = min(IVF_SEED_PCH, p_end - p0);
@@ -2244,7 +2256,7 @@ int ivf_search(const qadc_ivf_index *ix, const float *queries, int nq, int nprob
     case B_:                                                                                           \
         launch(QADC_PROF_SEED, ivf_seed_kernel<B_>, dim3(nb, seed_parts), dim3(IVF_SEED_NT), 0, st,    \
                ix->list_off, ix->codes, probes, nprobe, qluts, nbins, R, p.seed_per_list, scan_ws,     \
-               p.stride, ix->n, p.shared ? 8 : 0, nseed, fq, pairs);                                   \
+               p.stride, ix->n, p.shared ? 8 : 0, nseed, init, fq, pairs);                             \
         break;
         if (p.seed_per_list > 0) {
             switch (m / 2) {

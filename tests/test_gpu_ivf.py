@@ -440,6 +440,38 @@ def test_ivf_batches_of_any_number_of_units_per_workgroup(Q, m, n, nq, R):
         assert torch.equal(i2, ids[s:s + 3]) and torch.equal(d2, dist[s:s + 3]), s
 
 
+@pytest.mark.parametrize("nq", [1, 20, 40, 70, 300, 400])
+@pytest.mark.parametrize("m,R,init", [(8, 100, 3000), (16, 100, 8192), (32, 1, 700), (64, 60, 5000), (16, 1000, 1001)])
+def test_ivf_bounds_from_long_walks(Q, nq, m, R, init):
+    """Many init codes, met in lists several times as long as what is sampled of a list, in a part of one and in many (one of
+    them empty): the R smallest (sum, position) of all probed codes, by the returned tables."""
+    import torch
+    K, d, nprobe = 40, 64, 25
+    g = torch.Generator(device="cuda:0")
+    g.manual_seed(m + R + nq)
+    sizes = np.full(K, 700)
+    sizes[::4], sizes[1::4], sizes[9] = 9000, 40, 0
+    n = int(sizes.sum())
+    rand = lambda *shape: torch.rand(shape, generator=g, device="cuda:0")
+    coarse, cb = 100 * rand(K, d), 60 * rand(m, 16, d // m)
+    codes = torch.randint(0, 256, (n, m // 2), generator=g, device="cuda:0", dtype=torch.uint8)
+    off = torch.from_numpy(np.concatenate([[0], np.cumsum(sizes)])).to("cuda:0")
+    ix = Q.IvfIndex(coarse, off, codes, torch.arange(n, dtype=torch.int32, device="cuda:0"), cb)
+    queries = 100 * rand(nq, d)
+    ids, dist, probes, ql = Q.qadc_ivf_search(ix, queries, nprobe, R, init, debug=True)
+    comps = torch.stack([codes & 15, codes >> 4], 2).reshape(n, m).long()
+    for q in {0, nq // 2, nq - 1}:
+        pos, sums = [], []
+        for p, cell in enumerate(probes[q].tolist()):
+            lo, hi = int(off[cell]), int(off[cell + 1])
+            t = ql[q, p].int()
+            total = sum(t[j][comps[lo:hi, j]] for j in range(m))
+            pos.append(np.arange(lo, hi)), sums.append(np.minimum(total.cpu().numpy(), 255))
+        pos, sums = np.concatenate(pos), np.concatenate(sums)
+        best = np.lexsort((pos, sums))[:R]
+        assert np.array_equal(ids[q].cpu().numpy()[:len(best)], pos[best]) and np.array_equal(dist[q].cpu().numpy()[:len(best)], sums[best]), q
+
+
 @pytest.mark.parametrize("K", [300_000, 530_000])
 def test_ivf_few_queries_many_cells(Q, O, K):
     """Hundreds of thousands of cells, most of them empty, a few queries: with 2344 runs of 128 cells the
