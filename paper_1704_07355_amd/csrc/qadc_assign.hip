@@ -4,15 +4,16 @@
 //
 // assign_filter_kernel (d <= 256) finds that cell without forming all n x K float64 distances.  With x' and
 // c' the differences to a reference vector, |x - c|^2 = |x'|^2 + |c'|^2 - 2 x'.c', and the part that depends
-// on the cell is a matrix product: both factors are rounded to binary16 (11 significant bits; scaled by a power of two to
-// the middle of its range) and the products summed in float32 by the matrix units.  A lane keeps, per vector, the four
+// on the cell is a matrix product, summed in float32 by the matrix units.  Both factors are one binary16 number each (11
+// significant bits; scaled by a power of two to the middle of its range), or, where that does not pay (half_factors_pay),
+// split into two bfloat16 numbers (16 bits, hi.hi + hi.lo + lo.hi).  A lane keeps, per vector, the four
 // smallest of its group minima (a group: the 16 cells of a result tile that lie in one lane).  Whatever the
 // rounding, the closest cell lies in a group whose minimum is within a margin (bound below) of the smallest;
 // those groups -- mostly one -- are measured in float32 and, cells that come within its rounding of each other, in
 // float64 by the definition.  A vector that may have more of them than a lane remembers (many equal or very close
-// centroids), or that is out of binary16's reach, is marked, and assign_rest_kernel takes it through the same filter with
-// factors split into two bfloat16 numbers (16 bits, hi.hi + hi.lo + lo.hi), then measures what is still undecided (more than
-// three equal centroids in a lane, infinities, NaN) against all cells.  The result is the definition's, whatever the route.
+// centroids), or that is out of the factors' reach, is marked, and assign_rest_kernel takes it through the filter with
+// split factors (if it has not been), then measures what is still undecided (more than three equal centroids in a lane,
+// infinities, NaN) against all cells.  The result is the definition's, whatever the route.
 //
 // Bound: 2 n K d operations on the matrix units, the conversion of the centroids (every workgroup does it again, so eight
 // wavefronts share the tiles and hold the operands of 64 vectors each in registers for the whole walk) and the group minima
@@ -21,7 +22,8 @@
 // throughout, whose margins are a tenth; 37.5 in float64), d = 64 0.86 (1.44); 500 k, d = 256 2.2 (3.2); 200 k, d = 96,
 // K = 1000 0.15 (0.21).  Vectors and centroids of one Gaussian, where a few in a hundred vectors have rivals within the margin:
 // 1.73 (2.90).  96 vectors a wavefront instead of 64: 1.51 (18 registers spilled); the rounding of the centroids measured
-// as that of the vectors is, which halves the margin: 1.61.
+// as that of the vectors is, which halves the margin: 1.61.  Rows of 129 to 255 components, or that are not on 16-byte
+// boundaries, take the split form that spills 192 registers: 120 k, K = 4096, d = 200 0.93 ms (d = 256 0.59).
 // A margin is a matter of the vector and of the closest cells: a far or NaN centroid costs the other cells
 // nothing.  Every centroid four times, all vectors marked: 37 ms per 1 M (42 before the tiles of float64 lost the bounds checks
 // of every load and half of the instructions of every comparison).
@@ -231,6 +233,10 @@ __device__ __forceinline__ void filter_tile(FilterTile<NT, KS, NB, F> &sh, const
     constexpr int PS = S::PS, IT = S::IT, NW = S::NW, TC = S::TC, CT = S::CT, TM = S::TM;
     constexpr bool HALF = F == Factors::Half;
     constexpr int D = 16 * KS;
+    // groups remembered: three, or two where the split form's smaller margin seldom needs the third and it costs more than it
+    // saves (few products per group: K = 16384, d = 16 4 %; registers spilled: d = 200 8 %)
+    constexpr bool THIRD = HALF || (KS > 2 && (VEC || KS <= 8));
+    constexpr int NC = THIRD ? 6 : 4;  // both lanes of a vector
     auto &tile = sh.tile;
     auto &nrm = sh.nrm;
     auto &ref = sh.ref;
@@ -278,7 +284,7 @@ __device__ __forceinline__ void filter_tile(FilterTile<NT, KS, NB, F> &sh, const
 #pragma unroll
         for (int s = 0; s < KS; ++s) {
             const int t = 16 * s + 8 * half;
-            f32x8 v = load8<VEC>(row, t, d);
+            f32x8 v = load8<VEC, (KS > 8)>(row, t, d);
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
                 if constexpr (HALF) v[e] = __builtin_fmaf(v[e], scale, -ref[t + e]);  // (zero beyond d)
@@ -320,7 +326,7 @@ __device__ __forceinline__ void filter_tile(FilterTile<NT, KS, NB, F> &sh, const
         for (int it = 0; it < IT; ++it)
 #pragma unroll
             for (int h = 0; h < 2; ++h)
-                if (part + PS * it < KS) raw[it][h] = load8<VEC>(row, 16 * (part + PS * it) + 8 * h, d);
+                if (part + PS * it < KS) raw[it][h] = load8<VEC, (KS > 8)>(row, 16 * (part + PS * it) + 8 * h, d);
     };
     float cmax = 0.0f;  // largest |c'|^2
     auto stash = [&](int c0, int buf) {
@@ -437,12 +443,12 @@ __device__ __forceinline__ void filter_tile(FilterTile<NT, KS, NB, F> &sh, const
 #pragma unroll
                 for (int r = 1; r < 16; ++r) v = fminf(v, acc[nb][r]);
                 const bool l1 = v < b1[nb], l2 = v < b2[nb], l3 = v < b3[nb];
-                b4[nb] = __builtin_amdgcn_fmed3f(b3[nb], b4[nb], v);
+                if constexpr (THIRD) b4[nb] = __builtin_amdgcn_fmed3f(b3[nb], b4[nb], v);
                 b3[nb] = __builtin_amdgcn_fmed3f(b2[nb], b3[nb], v);
                 b2[nb] = __builtin_amdgcn_fmed3f(b1[nb], b2[nb], v);
                 b1[nb] = fminf(b1[nb], v);
                 const int third = l3 ? g : a3[nb], second = l2 ? g : a2[nb];
-                a3[nb] = l2 ? a2[nb] : third;
+                if constexpr (THIRD) a3[nb] = l2 ? a2[nb] : third;
                 a2[nb] = l1 ? a1[nb] : second;
                 a1[nb] = l1 ? g : a1[nb];
             }
@@ -480,23 +486,23 @@ __device__ __forceinline__ void filter_tile(FilterTile<NT, KS, NB, F> &sh, const
         } else {
             const float far = __builtin_sqrtf(xn[nb]) + __builtin_sqrtf(fmaxf(low + xn[nb], 0.0f) + 1e-3f * xn[nb]);
             thr = low + __builtin_fmaf(2.0f * eps, xn[nb] + 1.01f * fminf(far * far, cmax), 1e-30f);
-            sure = xn[nb] < 1e36f && thr < 1e36f && b4[nb] > thr;
+            sure = xn[nb] < 1e36f && thr < 1e36f && (THIRD ? b4[nb] : b3[nb]) > thr;
         }
         // this lane's groups in question, then those of the other half; the first entry is never empty
         // unless the vector is left to the kernel after this one
         const int g1 = b1[nb] <= thr ? 2 * a1[nb] + half : -1, g2 = b2[nb] <= thr ? 2 * a2[nb] + half : -1,
-                  g3 = b3[nb] <= thr ? 2 * a3[nb] + half : -1;
+                  g3 = THIRD && b3[nb] <= thr ? 2 * a3[nb] + half : -1;
         const int o1 = __shfl_xor(g1, 32), o2 = __shfl_xor(g2, 32), o3 = __shfl_xor(g3, 32);
         const int other = __shfl_xor((int)sure, 32);  // (asked by all lanes: a lane that does not ask gives nothing)
         const bool all = !(sure && other);
         if (half == 0) {
             // own groups first (they fill up in this order), the others' behind them
             const int k = (g1 >= 0) + (g2 >= 0) + (g3 >= 0);
-            int c[6] = {g1, g2, g3, -1, -1, -1};
+            int c[6] = {g1, g2, g3, -1, -1, -1};  // (NC of them)
 #pragma unroll
-            for (int e = 0; e < 6; ++e) c[e] = e == k ? o1 : e == k + 1 ? o2 : e == k + 2 ? o3 : c[e];
+            for (int e = 0; e < NC; ++e) c[e] = e == k ? o1 : e == k + 1 ? o2 : e == k + 2 ? o3 : c[e];
 #pragma unroll
-            for (int e = 0; e < 6; ++e) cand[v][e] = all ? -2 : c[e];
+            for (int e = 0; e < NC; ++e) cand[v][e] = all ? -2 : c[e];
             if (all && row_of(v) >= 0) undecided(row_of(v));
         }
     }
@@ -566,29 +572,29 @@ __device__ __forceinline__ void filter_tile(FilterTile<NT, KS, NB, F> &sh, const
         auto slack = [&](float f) { return f + __builtin_fmaf(f, 2e-6f + 1e-7f * KS, 1e-33f); };
         auto among = [&](bool near) { return __popcll((__ballot(near) >> team) & 0xffffull); };
         const int g0 = cand[v][0];
-        float dist[6];
+        float dist[NC];
         dist[0] = measure(g0);
 #pragma unroll
-        for (int q = 1; q < 6; ++q) dist[q] = __builtin_inff();
+        for (int q = 1; q < NC; ++q) dist[q] = __builtin_inff();
         float close = slack(lowest(dist[0]));
         int rivals = among(dist[0] <= close);
         int bc = dist[0] <= close ? cell_of(g0, r) : 0x7fffffff;
         if (cand[v][1] >= 0) {  // uniform over the 16 lanes
             float least = dist[0];
 #pragma unroll 1
-            for (int q = 1; q < 6; ++q) {
+            for (int q = 1; q < NC; ++q) {
                 const int g = cand[v][q];
                 if (g < 0) break;  // uniform over the 16 lanes
                 const float to = measure(g);
                 least = fminf(least, to);
 #pragma unroll
-                for (int p = 1; p < 6; ++p) dist[p] = p == q ? to : dist[p];
+                for (int p = 1; p < NC; ++p) dist[p] = p == q ? to : dist[p];
             }
             close = slack(lowest(least));
             bc = 0x7fffffff;
             rivals = 0;
 #pragma unroll
-            for (int q = 0; q < 6; ++q) {
+            for (int q = 0; q < NC; ++q) {
                 const bool near = dist[q] <= close && cand[v][q] >= 0;
                 rivals += among(near);
                 if (near) bc = cell_of(cand[v][q], r);
@@ -598,11 +604,11 @@ __device__ __forceinline__ void filter_tile(FilterTile<NT, KS, NB, F> &sh, const
             double bd = __builtin_inf();
             bc = 0x7fffffff;
 #pragma unroll 1
-            for (int q = 0; q < 6; ++q) {
+            for (int q = 0; q < NC; ++q) {
                 const int g = cand[v][q];
                 float dq = dist[0];
 #pragma unroll
-                for (int p = 1; p < 6; ++p) dq = p == q ? dist[p] : dq;
+                for (int p = 1; p < NC; ++p) dq = p == q ? dist[p] : dq;
                 const int c = cell_of(g, r);
                 if (g < 0 || !(dq <= close) || c >= K) continue;
                 const float *cr = coarse + (size_t)c * d;
@@ -637,14 +643,14 @@ __device__ __forceinline__ void filter_tile(FilterTile<NT, KS, NB, F> &sh, const
     }
 }
 
-template <int NT, int KS, int NB, bool VEC>
+template <int NT, int KS, int NB, bool VEC, Factors F>
 __global__ __launch_bounds__(NT, 2) void assign_filter_kernel(const float *__restrict__ coarse, int K, int d,
                                                               const float *__restrict__ x, int64_t ldx, int64_t n,
                                                               int32_t *__restrict__ cells, int scale, int accumulate)
 {
-    __shared__ FilterTile<NT, KS, NB, Factors::Half> sh;
-    const int64_t i0 = (int64_t)blockIdx.x * FilterShape<NT, KS, NB, Factors::Half>::TM;
-    filter_tile<NT, KS, NB, VEC, Factors::Half>(
+    __shared__ FilterTile<NT, KS, NB, F> sh;
+    const int64_t i0 = (int64_t)blockIdx.x * FilterShape<NT, KS, NB, F>::TM;
+    filter_tile<NT, KS, NB, VEC, F>(
         sh, coarse, K, d, x + i0 * ldx, ldx, [&](int k) { return i0 + k < n ? k : -1; },
         [&](int64_t k, int bc) { cells[i0 + k] = (accumulate ? cells[i0 + k] : 0) + bc * scale; },
         [&](int64_t k) { cells[i0 + k] = (accumulate ? cells[i0 + k] : 0) ^ ASG_MARK; });
@@ -777,35 +783,58 @@ __global__ __launch_bounds__(256) void assign_rest_kernel(const float *__restric
 
 // ------------------------------------------------------------------ host
 
+// One binary16 product per component, or factors split into two bfloat16 numbers from the start?  The first leaves more
+// vectors undecided, for which the split form and the float64 tiles come after it.  Its time over that of the split form, vectors
+// well inside their cells / vectors and centroids of one Gaussian, where most vectors have rivals: 1 M vectors, d = 128, K = 4096
+// 0.51 / 0.56, d = 32, K = 1024 0.76 / 0.90, 120 k d = 256, K = 16384 0.74 / 0.90, 60 k d = 64, K = 4096 0.67 / 1.18, d = 128,
+// K = 256 0.95 / 1.15; but where a call is less than a round of workgroups (10 k, K = 4096, d = 64 0.87 / 1.56, d = 96 0.87 / 1.43;
+// 30 k, d = 128, K = 256 0.96 / 1.02; 60 k, d = 32, K = 16384 0.72 / 1.12), in few dimensions (1 M, d = 2, K = 4096 1.66, d = 16,
+// K = 64 0.97 / 1.09, d = 24, K = 256 0.93 / 1.08) and for rows that are not whole steps (1 M, d = 100, K = 64 0.98 / 1.08,
+// d = 200, K = 256 0.93 / 1.13) a tenth is won where all is well and more lost where it is not.
+static bool half_factors_pay(int K, int d, int64_t n, bool vec)
+{
+    if (vec && n >= 49152 && (d >= 64 ? K >= 256 : K >= 1024 && K <= 4096)) return true;
+    if (n < 98304 || (d > 128 && !vec)) return false;
+    if (vec || (d > 32 && d <= 64)) return true;
+    return d >= 8 && K >= (d > 64 ? 1024 : 4096);
+}
+
 template <int KS>
 static void launch_filter(const float *coarse, int K, int d, const float *x, int64_t ldx, int64_t n, int range,
                           int32_t *cells, int scale, int accumulate, hipStream_t st)
 {
     const bool vec = d == 16 * KS && ldx % 4 == 0 && ((uintptr_t)coarse & 15) == 0 && ((uintptr_t)x & 15) == 0;
     const dim3 grid((unsigned)ceil_div(n, 128)), ranges((unsigned)ceil_div(n, range));
-    bool wide = false;
-    if constexpr (KS <= 8)
-        if (vec && n >= 512 * 256) {  // 512 vectors per workgroup once that fills the chip; else 128
-            hipLaunchKernelGGL((assign_filter_kernel<512, KS, 2, true>), dim3((unsigned)ceil_div(n, 512)), dim3(512), 0,
-                               st, coarse, K, d, x, ldx, n, cells, scale, accumulate);
-            wide = true;
-        }
-    if (!wide && vec)
-        hipLaunchKernelGGL((assign_filter_kernel<256, KS, 1, true>), grid, dim3(256), 0, st, coarse, K, d, x, ldx, n,
-                           cells, scale, accumulate);
-    else if (!wide)
-        hipLaunchKernelGGL((assign_filter_kernel<256, KS, 1, false>), grid, dim3(256), 0, st, coarse, K, d, x, ldx, n,
-                           cells, scale, accumulate);
+#define QADC_FILTER(NT_, NB_, VEC_, F_, GRID_)                                                                             \
+    hipLaunchKernelGGL((assign_filter_kernel<NT_, KS, NB_, VEC_, Factors::F_>), GRID_, dim3(NT_), 0, st, coarse, K, d, x,  \
+                       ldx, n, cells, scale, accumulate)
+#define QADC_REST(VEC_, AGAIN_, DEFINITION_)                                                                               \
+    hipLaunchKernelGGL((assign_rest_kernel<AGAIN_ ? KS : 2, VEC_, AGAIN_, DEFINITION_>), ranges, dim3(256), 0, st, coarse, K, \
+                       d, x, ldx, n, range, cells, scale, accumulate)
     constexpr bool ONE = KS <= 8;
-    if (vec)
-        hipLaunchKernelGGL((assign_rest_kernel<KS, true, true, ONE>), ranges, dim3(256), 0, st, coarse, K, d, x, ldx, n, range,
-                           cells, scale, accumulate);
-    else
-        hipLaunchKernelGGL((assign_rest_kernel<KS, false, true, ONE>), ranges, dim3(256), 0, st, coarse, K, d, x, ldx, n, range,
-                           cells, scale, accumulate);
-    if constexpr (!ONE)
-        hipLaunchKernelGGL((assign_rest_kernel<KS, false, false, true>), ranges, dim3(256), 0, st, coarse, K, d, x, ldx, n,
-                           range, cells, scale, accumulate);
+    if (!half_factors_pay(K, d, n, vec)) {
+        if (vec) QADC_FILTER(256, 1, true, Split, grid);
+        else QADC_FILTER(256, 1, false, Split, grid);
+        QADC_REST(false, false, true);
+        return;
+    }
+    if (vec) {
+        bool wide = false;
+        if constexpr (KS <= 8) {
+            wide = n >= 512 * 256;  // 512 vectors per workgroup once that fills the chip; else 128
+            if (wide) QADC_FILTER(512, 2, true, Half, dim3((unsigned)ceil_div(n, 512)));
+        }
+        if (!wide) QADC_FILTER(256, 1, true, Half, grid);
+        QADC_REST(true, true, ONE);
+    } else {
+        if constexpr (KS <= 8) {  // (half_factors_pay: no more components)
+            QADC_FILTER(256, 1, false, Half, grid);
+            QADC_REST(false, true, ONE);
+        }
+    }
+    if constexpr (!ONE) QADC_REST(false, false, true);
+#undef QADC_FILTER
+#undef QADC_REST
 }
 
 // cells[i] = (accumulate ? cells[i] : 0) + scale * (closest of K centroids to the d components at x + i ldx)

@@ -13,16 +13,35 @@ typedef unsigned bits16x8 __attribute__((ext_vector_type(4)));  // eight 16-bit 
 typedef float f32x8 __attribute__((ext_vector_type(8)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 
-// eight consecutive components t .. t+7 of a row, zero at and beyond d
-template <bool VEC>
+// Eight consecutive components t .. t+7 of a row, zero at and beyond d.  VEC: 16-byte aligned rows of whole steps.  Other
+// rows: whole eights in wide loads (a test per component otherwise: 1 M vectors, K = 256, d = 100 1.00 -> 0.80, d = 40 0.82 ->
+// 0.65 of the time), the rest one by one.  SKIP: no look at eights beyond d -- worth its branch where a row has many of them or
+// the registers for them are short (d = 136 to 250: 1.05 -> 0.90), not otherwise (d = 8, 1 M vectors 0.97 -> 1.14).
+template <bool VEC, bool SKIP = false>
 __device__ __forceinline__ f32x8 load8(const float *row, int t, int d)
 {
     f32x8 v;
-    if constexpr (VEC) {  // 16-byte aligned rows of whole steps
+    if constexpr (VEC) {
         const float4 a = *reinterpret_cast<const float4 *>(row + t);
         const float4 b = *reinterpret_cast<const float4 *>(row + t + 4);
         v[0] = a.x; v[1] = a.y; v[2] = a.z; v[3] = a.w;
         v[4] = b.x; v[5] = b.y; v[6] = b.z; v[7] = b.w;
+    } else if constexpr (SKIP) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) v[e] = 0.0f;
+        if (t + 8 <= d) {
+#pragma unroll
+            for (int e = 0; e < 8; ++e) v[e] = row[t + e];
+        } else if (t < d) {
+#pragma unroll
+            for (int e = 0; e < 7; ++e) {
+                const float f = row[min(t + e, d - 1)];
+                v[e] = t + e < d ? f : 0.0f;
+            }
+        }
+    } else if (t + 8 <= d) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) v[e] = row[t + e];
     } else {
 #pragma unroll
         for (int e = 0; e < 8; ++e) v[e] = t + e < d ? row[t + e] : 0.0f;

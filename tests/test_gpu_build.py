@@ -177,7 +177,9 @@ def test_ivf_assign_values_at_the_ends_of_float32(Q):
     assert np.array_equal(Q.qadc_ivf_assign(to_gpu(coarse), to_gpu(x)).cpu().numpy(), want)
 
 
-@pytest.mark.parametrize("d,K,n", [(16, 300, 4_097), (64, 260, 131_073), (100, 90, 700), (128, 257, 131_500), (250, 130, 600)])
+@pytest.mark.parametrize("d,K,n", [(16, 300, 4_097), (64, 260, 131_073), (100, 90, 700), (128, 257, 131_500), (250, 130, 600),
+                                   (32, 200, 98_304), (32, 1_030, 49_200), (48, 70, 98_310), (64, 256, 49_152), (96, 90, 98_305),
+                                   (96, 300, 49_151), (100, 1_024, 98_400), (24, 4_100, 98_320), (8, 4_097, 98_304), (256, 260, 49_155)])
 @pytest.mark.parametrize("kind", ["range", "clusters", "crowds", "same samples", "runs of NaN"])
 def test_ivf_assign_where_the_filter_must_give_up(Q, d, K, n, kind):
     """What 11-bit factors cannot tell or hold is left to the routes behind them: vectors and centroids beyond their range
