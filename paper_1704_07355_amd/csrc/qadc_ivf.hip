@@ -2249,6 +2249,12 @@ int ivf_search(const qadc_ivf_index *ix, const float *queries, int nq, int nprob
         // the bound is sampled from the lists of the closest cells only: they hold most of a query's best
         // codes, and the sample is most of the seed kernel's cost
         const int nseed = std::min(nprobe, std::max(1, knob_or(knobs().ivf_seed_probes, IVF_SEED_PROBES)));
+        // The init codes that the sample holds (see the seed kernel).  Not where a workgroup takes longer for them than the scan of
+        // the query's lists saves: fewer than 64 queries with 64-byte components (1 query of 2e7 codes, 8000 init codes 104 without,
+        // 110 us per call with them; m = 32 104 / 90), and lists of a few dozen codes, nearly all sampled anyway, unless R is a small
+        // part of the init codes (1e6 codes in 30000 lists, R = 100, 16 queries, 200 init codes 67 / 77, 3000 93 / 74; 70 queries, m = 8
+        // 99 / 113, 1000 init codes 3 % less with them).
+        const int walked = p.shared || ((nb >= 64 || m <= 32) && (p.seed_per_list > 64 || init >= 8 * R)) ? init : 0;
         unsigned *flags = p.shared ? (unsigned *)(ws + p.off_flags) : nullptr;
         IvfPairs pairs = {nullptr, nullptr, nullptr, 0};
         if (p.shared) pairs = IvfPairs{(unsigned *)(ws + p.off_paircnt), (unsigned *)(ws + p.off_taus), flags, K};
@@ -2256,7 +2262,7 @@ int ivf_search(const qadc_ivf_index *ix, const float *queries, int nq, int nprob
     case B_:                                                                                           \
         launch(QADC_PROF_SEED, ivf_seed_kernel<B_>, dim3(nb, seed_parts), dim3(IVF_SEED_NT), 0, st,    \
                ix->list_off, ix->codes, probes, nprobe, qluts, nbins, R, p.seed_per_list, scan_ws,     \
-               p.stride, ix->n, p.shared ? 8 : 0, nseed, init, fq, pairs);                             \
+               p.stride, ix->n, p.shared ? 8 : 0, nseed, walked, fq, pairs);                           \
         break;
         if (p.seed_per_list > 0) {
             switch (m / 2) {
