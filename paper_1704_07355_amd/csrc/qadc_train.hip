@@ -145,15 +145,15 @@ __global__ __launch_bounds__(NT) void train_update_kernel(
     int64_t cnt = 0;
     if (n > SEG || (cnt = train_rows<NT, PER>(col, 0, n, (unsigned)i, rows, wcount)) > TRAIN_FEW) {  // uniform
         double mag = 0.0;
-        int64_t chain = 0;                         // additions of the first slot, the most that one has
+        int64_t chain = 0;                         // additions of this slot (the first, with the most, decides below)
         const int slots = NT / td;                 // rows side by side
         const int slot = tid / td, t = tid - slot * td;
         for (int64_t base = 0; base < n; base += SEG) {
             const unsigned found = n <= SEG ? (unsigned)cnt : train_rows<NT, PER>(col, base, n, (unsigned)i, rows, wcount);
             if (n > SEG) cnt += found;
-            chain += (found + (unsigned)slots - 1u) / (unsigned)slots;
             if (slot < slots) {
                 for (unsigned r0 = (unsigned)slot; r0 < found; r0 += TRAIN_FL * (unsigned)slots) {
+                    chain += TRAIN_FL;
                     float v[TRAIN_FL];
 #pragma unroll
                     for (int u = 0; u < TRAIN_FL; ++u) {
