@@ -15,6 +15,7 @@
 #include <utility>
 
 #include "qadc_half.h"
+#include "qadc_ivf_filter.h"
 #include "qadc_scan_common.h"
 
 namespace qadc {
@@ -93,8 +94,8 @@ __device__ __forceinline__ void ivf_clear_control(char *base, size_t counts_off,
     if (countsA_off && threadIdx.x == 0) *reinterpret_cast<unsigned *>(base + countsA_off) = 0;
 }
 
-// Where the kernels of the Index step clear a query's control words (calls of a few queries, which
-// have no qmax kernel to do it); scan_ws null: not here.
+// Where the kernels of the Index step clear a query's control words (calls of a few queries;
+// ivf_tables_kernel does it for the others); scan_ws null: not here.
 struct IvfClear {
     char *scan_ws;
     size_t ws_stride, counts_off, countsA_off;
@@ -574,12 +575,6 @@ __global__ __launch_bounds__(IVF_SEL_NT) void ivf_select_probes_kernel(
     probes_of_candidates(dq, K, nprobe, need, cand, cnt, sc, probes + (size_t)q * nprobe);
 }
 
-// What ivf_filter_row says.
-__device__ __forceinline__ const uint16_t *filter_row(const float *dist, int K, size_t i)
-{
-    return reinterpret_cast<const uint16_t *>((reinterpret_cast<uintptr_t>(dist + i * (size_t)K) + 15) & ~(uintptr_t)15);
-}
-
 // The same from the bounds of qadc_ivf_filter.hip, one per group of four cells, in the query's row of `dist`: any T that `need`
 // groups do not exceed bounds the need-th smallest score (as above, the need-th smallest of the threads' minima), and with
 // the rounding of the scores and of float32 distances (components + 4 roundings of 2^-24) the scores of all cells among the
@@ -608,7 +603,7 @@ __global__ __launch_bounds__(IVF_SEL_NT) void ivf_select_filtered_kernel(
     const int tiles = (K + 31) / 32;
     if (tid < d) ys[tid] = queries[(size_t)q * d + tid];
     const float2 stat = qstat[q];
-    const unsigned *row = reinterpret_cast<const unsigned *>(filter_row(dist, K, (size_t)q));  // two bounds a word
+    const unsigned *row = reinterpret_cast<const unsigned *>(ivf_filter_row(dist, K, (size_t)q));  // two bounds a word
     auto order = [](unsigned b) { return (b & 0x8000u) ? ~b & 0xffffu : b | 0x8000u; };
     auto each_pair = [&](auto f) {  // f(first group, its key, the next one's key)
         for (int i0 = tid; i0 < 4 * tiles; i0 += 8 * NT) {
@@ -691,8 +686,7 @@ __global__ __launch_bounds__(IVF_SEL_NT) void ivf_select_filtered_kernel(
     };
     float *dq = dist + (size_t)q * K;
     for (unsigned i = tid; i < 4u * ng; i += NT) {
-        const unsigned g = groups[i >> 2];  // place 8 tile + 4 half + k: cells 32 tile + 8 k + 4 half + 0 .. 3
-        const int c = (int)((g >> 3) * 32u + (g & 3u) * 8u + ((g >> 2) & 1u) * 4u + (i & 3u));
+        const int c = (int)(ivf_filter_first_cell(groups[i >> 2]) + (i & 3u));
         if (c < K) cand[atomicAdd(&cnt, 1u)] = ((uint64_t)f2ord(measure(c)) << 32) | (uint64_t)(unsigned)c;
     }
     __syncthreads();
@@ -1888,8 +1882,6 @@ __global__ __launch_bounds__(NT) void ivf_scan_kernel(
     for (unsigned i = tid; i < have; i += NT) dst[i] = keys[i];
 }
 
-// out_ids[q][r] = ids[position] for the positions the merge kernel wrote (in place).  Anything
-// that is not a storage position becomes the padding value.
 // Cells given by the caller: a cell outside [0, K) and a cell that an earlier slot of the same
 // query already names become unused slots (-1) -- a list is scanned once, so that keys stay
 // unique, and nothing outside list_off is read.
@@ -1921,11 +1913,6 @@ __global__ __launch_bounds__(256) void ivf_take_probes_kernel(const int32_t *__r
 
 int quantize_luts(int, const float *, int, int, int, const uint8_t *, int64_t, const float *, int, int,
                   int, uint8_t *, float *, float *, float *, hipStream_t);
-size_t ivf_filter_bytes(int K, int d, int nq);
-bool ivf_filter_pays(int K, int d, int nq, int nprobe);
-void ivf_filter_convert(const float *coarse, int K, int d, const float *queries, int nq, void *room, hipStream_t st);
-const float2 *ivf_filter(int K, int d, int nq, int i0, int ni, void *room, float *dist, int *components, unsigned **rest,
-                         hipStream_t st);
 
 // Which form of ivf_tables_kernel: the sub-vector length, or 0 with the float tables by a kernel of their own before it, a
 // workgroup per four (or one) probed cells -- for lengths without a form, and where one workgroup per query is too long a chain.
@@ -1969,8 +1956,8 @@ int ivf_shared_scan(int, const int64_t *, const uint8_t *, int64_t, int, const i
                     int, char *, size_t, size_t, size_t, int, unsigned *, unsigned *, unsigned *, unsigned *,
                     unsigned *, unsigned *, unsigned *, int32_t *, unsigned *, long long, int, int, hipStream_t);
 
-// Is a batch large enough that its popular lists are scanned once for all their queries?  That costs ten launches
-// more; it gains where lists are met by many queries.  From 384 queries always: what the queries meet follows from the
+// Is a batch large enough that its popular lists are scanned once for all their queries?  That costs six launches
+// more (ten when the figures here were taken: some 10 to 15 us); it gains where lists are met by many queries.  From 384 queries always: what the queries meet follows from the
 // lengths of the lists, which only the GPU knows, and where a few lists hold most of the codes a query-by-query scan
 // reads them once per query (5e7 codes in 65536 lists of Zipf(2) lengths, 8 probes: 384 queries 12.2 against 1.7 ms,
 // 4096 queries 127 against 13; Zipf(1.2), 2e7 codes, 4096 queries 9.6 against 2.5) -- while over even lists that few

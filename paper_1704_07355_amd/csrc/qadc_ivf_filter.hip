@@ -11,6 +11,7 @@
 
 #include "qadc_common.h"
 #include "qadc_half.h"
+#include "qadc_ivf_filter.h"
 #include "qadc_profile.h"
 
 namespace qadc {
@@ -109,16 +110,10 @@ __global__ __launch_bounds__(256) void ivf_filter_convert_kernel(const float *__
     }
 }
 
-// Where the bounds of query i lie: in its own row of K distances, which the selection may overwrite.
-__host__ __device__ inline uint16_t *ivf_filter_row(float *dist, int K, size_t i)
-{
-    return reinterpret_cast<uint16_t *>((reinterpret_cast<uintptr_t>(dist + i * (size_t)K) + 15) & ~(uintptr_t)15);
-}
-
 // A wavefront holds the operands of 32 NBQ queries in registers; the tiles of cells pass through LDS, STAGE at a time, the
 // next ones on their way there (without a register) while these are multiplied.  wq: wavefronts of a workgroup side by side
 // along the queries; the 4 / wq along the cells share out the tiles of a stage.  Result (cell 8 g + 4 half + k, query) of a tile:
-// the smallest of k = 0 .. 3, plus |x'|^2, as bfloat16 at place 8 tile + 4 half + g of the query's row.
+// the smallest of k = 0 .. 3, plus |x'|^2, as bfloat16 at its place in the query's row (qadc_ivf_filter.h).
 template <int KS>
 struct FilterRoom {
     static constexpr int NBQ = KS <= 8 ? 4 : 2;
@@ -179,7 +174,7 @@ __global__ __launch_bounds__(256, 2) void ivf_filter_kernel(const bits16x8 *__re
 #pragma unroll
         for (int s = 0; s < KS; ++s) b[nb][s] = qs[((size_t)qt * KS + s) * WAVE + lane];
         xn[nb] = qstat[q].x;
-        out[nb] = ivf_filter_row(dist, K, (size_t)q) + 4 * half;
+        out[nb] = ivf_filter_row(dist, K, (size_t)q) + ivf_filter_place(0, half, 0);
     }
     __syncthreads();
     int buf = 0;
@@ -214,7 +209,7 @@ __global__ __launch_bounds__(256, 2) void ivf_filter_kernel(const bits16x8 *__re
                         for (int g = 0; g < 4; ++g)
                             v[g] = fminf(fminf(acc[e][4 * g], acc[e][4 * g + 1]), fminf(acc[e][4 * g + 2], acc[e][4 * g + 3])) + xn[nb];
                         if (q0 + 32 * nb + col < nq)
-                            *reinterpret_cast<bf16x4 *>(out[nb] + 8 * (t + k)) = __builtin_convertvector(v, bf16x4);
+                            *reinterpret_cast<bf16x4 *>(out[nb] + ivf_filter_place(t + k, 0, 0)) = __builtin_convertvector(v, bf16x4);
                     }
                 }
             }
@@ -231,11 +226,11 @@ size_t ivf_filter_bytes(int K, int d, int nq)
     return (size_t)((ct + qt) * ks * 1024 + ct * 128) + align_up((size_t)nq * 12 + 4, 256);
 }
 
-// Worth its launches and a longer selection?  Whole calls (before the two launches for queries that the bounds cannot serve: 5 to
-// 9 us more a pass of queries) against the float32 distances of every pair: 300 queries, 4096 cells
-// of 64 components (8e7 products) 140 against 147 us, 200 x 4096 x 256 (2e8) the same, 1000 x 4096 x 128 (5e8) 305 / 334,
-// 300 x 16384 x 128 441 / 462, x 256 210 / 277, 2000 x 65536 x 64 874 / 1161.  100 probes of 4096 cells: too many groups are
-// as close (500 queries, d = 128: 609 / 597).  Calls of up to 32 queries have kernels of their own.
+// Worth its launches and a longer selection?  Whole calls over 2e5 codes, cells and queries of a mixture, all launches included,
+// against the float32 distances of every pair: at 2.5e8 to 7e8 products (queries x cells x components) 0.80 to 0.98 of the time where
+// the cells are 128 times the probes and more (d = 32, 2500 queries, K = 8192, 64 probes 1.03), from 1e9 on 0.5 to 0.95; at 1e8
+// to 2.5e8 0.87 to 1.01; below, and at 64 cells a probe -- too many groups are as close -- up to 1.12; K = 2048 0.86 to 1.06.
+// Calls of up to 32 queries have kernels of their own.
 bool ivf_filter_pays(int K, int d, int nq, int nprobe)
 {
     return d <= IVFF_MAX_D && nq > 32 && K >= 4096 && K >= 128 * nprobe && (double)nq * K * d >= 2.5e8;
