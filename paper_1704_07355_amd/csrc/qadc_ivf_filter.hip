@@ -3,8 +3,9 @@
 // groups that can hold one of the nprobe closest cells from them and measures those cells by the definition, so the cells
 // chosen are the definition's; a query the bounds cannot serve is left to the kernels of the float32 distances.
 //
-// Bound by 2 nq K d operations on the matrix units and, with as many cycles, by the minima, conversions and stores that go
-// with each result.  4096 queries x 65536 cells of 128 components (four launches): 191 us, 14 for the factors and 291 for the
+// Bound by the stores of the bounds: 8 bytes per lane, tile and query, whose lines are written out in parts (98 MB for 33 of bounds
+// per 1024 queries x 65536 cells; wavefronts wait for two thirds of their cycles, the matrix units are busy a fifth).  4096
+// queries x 65536 cells of 128 components (four launches): 185 us, 15 for the factors and 283 for the
 // selection, where the float32 distances of all pairs took 1590 and 80; 1000 x 16384 10 + 7 + 58.  (Tiles of cells from memory
 // straight into registers, a tile ahead: 348 us, 26 registers spilled.)
 #include <algorithm>
