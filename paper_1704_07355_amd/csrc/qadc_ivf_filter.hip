@@ -3,8 +3,8 @@
 // groups that can hold one of the nprobe closest cells from them and measures those cells by the definition, so the cells
 // chosen are the definition's; a query the bounds cannot serve is left to the kernels of the float32 distances.
 //
-// Bound by the stores of the bounds: 8 bytes per lane, tile and query, whose lines are written out in parts (98 MB for 33 of bounds
-// per 1024 queries x 65536 cells; wavefronts wait for two thirds of their cycles, the matrix units are busy a fifth).  4096
+// Bound by latency: wavefronts (two per SIMD at 1024 queries x 65536 cells) wait for two thirds of their cycles, the matrix units
+// are busy a fifth; the bounds, 8 bytes per lane, tile and query, leave the L2 in parts of lines (98 MB for 33).  4096
 // queries x 65536 cells of 128 components (four launches): 185 us, 15 for the factors and 283 for the
 // selection, where the float32 distances of all pairs took 1590 and 80; 1000 x 16384 10 + 7 + 58.  (Tiles of cells from memory
 // straight into registers, a tile ahead: 348 us, 26 registers spilled.)
