@@ -7,7 +7,8 @@
 // on the cell is a matrix product, summed in float32 by the matrix units.  Both factors are one binary16 number each (11
 // significant bits; scaled by a power of two to the middle of its range), or, where that does not pay (half_factors_pay),
 // split into two bfloat16 numbers (16 bits, hi.hi + hi.lo + lo.hi).  A lane keeps, per vector, the four
-// smallest of its group minima (a group: the 16 cells of a result tile that lie in one lane).  Whatever the
+// smallest of its group minima (a group: four consecutive cells, whose scores lie in one lane), with the number of the group
+// in the lowest bits of its minimum.  Whatever the
 // rounding, the closest cell lies in a group whose minimum is within a margin (bound below) of the smallest;
 // those groups -- mostly one -- are measured in float32 and, cells that come within its rounding of each other, in
 // float64 by the definition.  A vector that may have more of them than a lane remembers (many equal or very close
@@ -16,14 +17,16 @@
 // infinities, NaN) against all cells.  The result is the definition's, whatever the route.
 //
 // Bound: 2 n K d operations on the matrix units, the conversion of the centroids (every workgroup does it again, so eight
-// wavefronts share the tiles and hold the operands of 64 vectors each in registers for the whole walk) and the group minima
-// with it on the same issue slots: per 64 cells a wavefront takes 32 products of 32 cycles, 92 vector instructions of four
-// for the minima and 66 for the conversion.  1 M vectors, K = 4096: d = 128 1.49 ms = 0.7 PFLOP/s (2.81 with split factors
-// throughout, whose margins are a tenth; 37.5 in float64), d = 64 0.86 (1.44); 500 k, d = 256 2.2 (3.2); 200 k, d = 96,
-// K = 1000 0.15 (0.21).  Vectors and centroids of one Gaussian, where a few in a hundred vectors have rivals within the margin:
-// 1.73 (2.90).  96 vectors a wavefront instead of 64: 1.51 (18 registers spilled); the rounding of the centroids measured
-// as that of the vectors is, which halves the margin: 1.61.  Rows of 129 to 255 components, or that are not on 16-byte
-// boundaries, take the split form that spills 192 registers: 120 k, K = 4096, d = 200 0.93 ms (d = 256 0.59).
+// wavefronts share the tiles and hold the operands of 64 vectors each in registers for the whole walk) and the group minima;
+// per 64 cells a wavefront takes 32 products of 32 cycles and 190 vector instructions of four, which run beside the products
+// (a wavefront alone: 4 instructions beside a product cost it nothing, 8 a fifth) where they stand among them: the
+// minima are those of the 32 cells before, the conversion that of the next tile, and all is one block of code.  1.05 M vectors,
+// d = 128: 0.25 ms + 0.22 ms per 1024 centroids = 1.2 PFLOP/s; the first part is the vectors, read twice, and the groups measured
+// at the end: groups of 16 cells, 8 KiB of centroids per vector from L2, made it 0.48 ms (K = 4096: 1.42 ms -> 1.13; d = 64
+// 0.80 -> 0.67; 500 k, d = 256 2.24 -> 1.60; 200 k, d = 96, K = 1000 0.147 -> 0.094; 37.5 ms in float64).  Vectors and centroids
+// of one Gaussian, where a few in a hundred vectors have rivals within the margin: 1.75 -> 1.38.  The minima of the same 32 cells and
+// the conversion behind the products: 0.25 ms per 1024 centroids.  Not faster: the order of instructions given by hand
+// (1.23 ms for 1.13), workgroups of 256 threads, two per compute unit (1.58).
 // A margin is a matter of the vector and of the closest cells: a far or NaN centroid costs the other cells
 // nothing.  Every centroid four times, all vectors marked: 37 ms per 1 M (42 before the tiles of float64 lost the bounds checks
 // of every load and half of the instructions of every comparison).
@@ -182,6 +185,7 @@ __device__ __forceinline__ bool assign_marked(int cell, int K, int accumulate)
 // ------------------------------------------------------------------ filter on the matrix units
 
 constexpr int AF_MAX_D = 256;
+constexpr float AF_NONE = 0x1p127f;  // no score (its low bits may be replaced: it stays a number)
 
 // hi + lo = v to 2^-18 relative
 __device__ __forceinline__ void split_bf16(const f32x8 v, bits16x8 *hi, bits16x8 *lo)
@@ -200,14 +204,17 @@ enum class Factors { Half, Split };
 // the rows of x and of the centroids start on 16-byte boundaries.
 template <int NT, int KS, int NB, Factors F>
 struct FilterShape {
-    static constexpr int PS = KS <= 4 ? 4 : 8;     // threads that convert one centroid at a time
+    static constexpr int PS = KS <= 2 ? 2 : KS <= 4 ? 4 : 8;     // threads that convert one centroid at a time
     static constexpr int IT = (KS + PS - 1) / PS;  // steps of 16 components per thread
     static constexpr int NW = NT / WAVE;
     static constexpr int TC = NT / PS;             // cells per tile
     static constexpr int CT = TC / 32;
     static constexpr int TM = NW * NB * 32;        // vectors per workgroup
     static constexpr int PARTS = F == Factors::Split ? 2 : 1;
-    static_assert(TC % 32 == 0 && KS <= PS * IT, "");
+    // cells after which the groups found are given their numbers and merged with those before (a multiple of the tile)
+    static constexpr int SEG = F == Factors::Split ? 512 : 4096;
+    static constexpr unsigned MASK = SEG / 8 - 1;  // low bits of a group's minimum that hold its number in the segment
+    static_assert(TC % 32 == 0 && SEG % TC == 0 && KS <= PS * IT, "");
 };
 
 template <int NT, int KS, int NB, Factors F>
@@ -220,6 +227,8 @@ struct FilterTile {
     float cmax[S::NW];
     float spread[S::NW];                              // largest distance of a component from the reference
     int cand[S::TM][6];                               // groups to measure, -1: none; none after the first -1
+    float low[4][NB][NT];                             // of the segments before: a thread's smallest minima, ascending,
+    int group[3][NB][NT];                             // and the groups of the first three
 };
 
 // The cells of up to TM vectors by a workgroup; row(k): the row of x that is vector k, -1 for none.  store(row, cell) for a
@@ -233,10 +242,7 @@ __device__ __forceinline__ void filter_tile(FilterTile<NT, KS, NB, F> &sh, const
     constexpr int PS = S::PS, IT = S::IT, NW = S::NW, TC = S::TC, CT = S::CT, TM = S::TM;
     constexpr bool HALF = F == Factors::Half;
     constexpr int D = 16 * KS;
-    // groups remembered: three, or two where the split form's smaller margin seldom needs the third and it costs more than it
-    // saves (few products per group: K = 16384, d = 16 4 %; registers spilled: d = 200 8 %)
-    constexpr bool THIRD = HALF || (KS > 2 && (VEC || KS <= 8));
-    constexpr int NC = THIRD ? 6 : 4;  // both lanes of a vector
+    constexpr int NC = 6;  // groups to measure: three of each lane of a vector
     auto &tile = sh.tile;
     auto &nrm = sh.nrm;
     auto &ref = sh.ref;
@@ -312,8 +318,11 @@ __device__ __forceinline__ void filter_tile(FilterTile<NT, KS, NB, F> &sh, const
     //   additions of values up to 2 (|x'|^2 + |c'|^2) (3 D + 1) 2^-22 (2^-23 each: no assumption on how the matrix units
     //   round); the norms (D + 8) 2^-24; 1.28e-5 + 7.8e-7 D in all.
     //   Half: see qadc_half.h.
-    constexpr float eps = HALF ? half_eps(D) : 1.5e-5f + 9e-7f * D;
-    constexpr float eps_c = HALF ? half_eps_c(D) : eps;
+    // The number of a group in the low bits of its minimum: log2 (SEG / 8) bits, an error of 2 (SEG / 8) 2^-24 of the score,
+    // which is at most |x'|^2 + 2 |c'|^2 (1 + what rounding adds).
+    constexpr float eps_g = 1.01f * (float)(S::SEG / 4) / 16777216.0f;
+    constexpr float eps = (HALF ? half_eps(D) : 1.5e-5f + 9e-7f * D) + eps_g;
+    constexpr float eps_c = (HALF ? half_eps_c(D) : 1.5e-5f + 9e-7f * D) + 2.0f * eps_g;
 
     // thread -> centroid and steps it converts: eight neighbouring lanes hold eight centroids (their
     // 16-byte LDS writes are contiguous), a centroid's threads lie in one wavefront
@@ -375,86 +384,135 @@ __device__ __forceinline__ void filter_tile(FilterTile<NT, KS, NB, F> &sh, const
                     for (int h = 0; h < 2; ++h)
                         tile[buf][crow >> 5][part + PS * it][0][h * 32 + (crow & 31)] = stray ? bits16x8{} : conv[it][h];
             const float own = stray ? 0.29f * s2 : __builtin_fmaf(-eps_c, s2, s2) - HALF_TINY * D;
-            if (part == 0) nrm[buf][crow] = in ? own : __builtin_inff();
+            nrm[buf][crow] = in ? own : AF_NONE;  // (its threads all write the same: a branch would part the block of code)
         } else {
-            if (part == 0) nrm[buf][crow] = in ? s2 * (1.0f - eps) : __builtin_inff();
+            nrm[buf][crow] = in ? s2 * (1.0f - eps_c) : AF_NONE;
         }
     };
 
-    float b1[NB], b2[NB], b3[NB], b4[NB];  // the four smallest group minima, ascending; the groups of the first three
-    int a1[NB], a2[NB], a3[NB];
+    // 32 cells' scores start at their norms: result r is of cell 8 (r / 4) + 4 half + r % 4 and vector col.
+    auto multiply = [&](int buf, int ct, f32x16 (&acc)[NB]) {
+        f32x16 init;
 #pragma unroll
-    for (int nb = 0; nb < NB; ++nb) {
-        b1[nb] = b2[nb] = b3[nb] = b4[nb] = __builtin_inff();
-        a1[nb] = a2[nb] = a3[nb] = 0;
-    }
-    fetch(0);
-    stash(0, 0);
-    __syncthreads();
-    int buf = 0;
-    for (int c0 = 0; c0 < K; c0 += TC, buf ^= 1) {
-        if (c0 + TC < K) fetch(c0 + TC);  // uniform; travels while this tile is multiplied
+        for (int g = 0; g < 4; ++g) {
+            const float4 v = *reinterpret_cast<const float4 *>(&nrm[buf][ct * 32 + 8 * g + 4 * half]);
+            init[4 * g] = v.x; init[4 * g + 1] = v.y; init[4 * g + 2] = v.z; init[4 * g + 3] = v.w;
+        }
 #pragma unroll
-        for (int ct = 0; ct < CT; ++ct) {
-            // result (cell 8 (r / 4) + 4 half + r % 4, vector col) starts at |c'|^2
-            f32x16 init;
+        for (int nb = 0; nb < NB; ++nb) acc[nb] = init;
 #pragma unroll
-            for (int g = 0; g < 4; ++g) {
-                const float4 v = *reinterpret_cast<const float4 *>(&nrm[buf][ct * 32 + 8 * g + 4 * half]);
-                init[4 * g] = v.x; init[4 * g + 1] = v.y; init[4 * g + 2] = v.z; init[4 * g + 3] = v.w;
-            }
-            f32x16 acc[NB];
+        for (int s = 0; s < KS; ++s) {
+            const bits16x8 ah = tile[buf][ct][s][0][lane], al = tile[buf][ct][s][S::PARTS - 1][lane];
+            if constexpr (HALF) {
 #pragma unroll
-            for (int nb = 0; nb < NB; ++nb) acc[nb] = init;
-            // (the operands of a step are requested two steps ahead)
-            bits16x8 a[3][S::PARTS];
+                for (int nb = 0; nb < NB; ++nb)
+                    acc[nb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, ah), __builtin_bit_cast(f16x8, bh[nb][s]), acc[nb], 0, 0, 0);
+            } else {
+                auto bf = [](const bits16x8 &v) { return __builtin_bit_cast(bf16x8, v); };
 #pragma unroll
-            for (int s = 0; s < 2; ++s)
+                for (int nb = 0; nb < NB; ++nb)
+                    acc[nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bf(ah), bf(bh[nb][s]), acc[nb], 0, 0, 0);
 #pragma unroll
-                for (int p = 0; p < S::PARTS; ++p) a[s][p] = tile[buf][ct][s][p][lane];
+                for (int nb = 0; nb < NB; ++nb)
+                    acc[nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bf(al), bf(bh[nb][s]), acc[nb], 0, 0, 0);
 #pragma unroll
-            for (int s = 0; s < KS; ++s) {
-                if (s + 2 < KS)
-#pragma unroll
-                    for (int p = 0; p < S::PARTS; ++p) a[(s + 2) % 3][p] = tile[buf][ct][s + 2][p][lane];
-                const bits16x8 ah = a[s % 3][0], al = a[s % 3][S::PARTS - 1];
-                __builtin_amdgcn_sched_barrier(0);  // (left to itself the compiler requests them where they are used)
-                if constexpr (HALF) {
-#pragma unroll
-                    for (int nb = 0; nb < NB; ++nb)
-                        acc[nb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, ah), __builtin_bit_cast(f16x8, bh[nb][s]), acc[nb], 0, 0, 0);
-                } else {
-                    auto bf = [](const bits16x8 &v) { return __builtin_bit_cast(bf16x8, v); };
-#pragma unroll
-                    for (int nb = 0; nb < NB; ++nb)
-                        acc[nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bf(ah), bf(bh[nb][s]), acc[nb], 0, 0, 0);
-#pragma unroll
-                    for (int nb = 0; nb < NB; ++nb)
-                        acc[nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bf(al), bf(bh[nb][s]), acc[nb], 0, 0, 0);
-#pragma unroll
-                    for (int nb = 0; nb < NB; ++nb)
-                        acc[nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bf(ah), bf(bl[nb][HALF ? 0 : s]), acc[nb], 0, 0, 0);
-                }
-            }
-            const int g = c0 / 32 + ct;
-#pragma unroll
-            for (int nb = 0; nb < NB; ++nb) {
-                float v = fminf(acc[nb][0], __builtin_inff());  // (not a NaN: the medians would take it for the smallest)
-#pragma unroll
-                for (int r = 1; r < 16; ++r) v = fminf(v, acc[nb][r]);
-                const bool l1 = v < b1[nb], l2 = v < b2[nb], l3 = v < b3[nb];
-                if constexpr (THIRD) b4[nb] = __builtin_amdgcn_fmed3f(b3[nb], b4[nb], v);
-                b3[nb] = __builtin_amdgcn_fmed3f(b2[nb], b3[nb], v);
-                b2[nb] = __builtin_amdgcn_fmed3f(b1[nb], b2[nb], v);
-                b1[nb] = fminf(b1[nb], v);
-                const int third = l3 ? g : a3[nb], second = l2 ? g : a2[nb];
-                if constexpr (THIRD) a3[nb] = l2 ? a2[nb] : third;
-                a2[nb] = l1 ? a1[nb] : second;
-                a1[nb] = l1 ? g : a1[nb];
+                for (int nb = 0; nb < NB; ++nb)
+                    acc[nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bf(ah), bf(bl[nb][HALF ? 0 : s]), acc[nb], 0, 0, 0);
             }
         }
-        if (c0 + TC < K) stash(c0 + TC, buf ^ 1);  // uniform; that buffer was read before the last barrier
-        __syncthreads();
+    };
+    // A lane's four smallest group minima of the segment, ascending.  A group is four consecutive cells; its number takes the
+    // place of the lowest bits of its minimum, so that the two are sorted as one.
+    float b1[NB], b2[NB], b3[NB], b4[NB];
+    unsigned mask = S::MASK;
+    asm("" : "+v"(mask));  // (in a register: one instruction for the exchange of bits)
+    auto note = [&](const f32x16 (&acc)[NB], unsigned first) {
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+#pragma unroll
+            for (int nb = 0; nb < NB; ++nb) {
+                float v = fminf(fminf(acc[nb][4 * u], acc[nb][4 * u + 1]), acc[nb][4 * u + 2]);
+                v = fminf(fminf(v, acc[nb][4 * u + 3]), AF_NONE);  // (no NaN: the medians would take it for the smallest)
+                v = __uint_as_float((__float_as_uint(v) & ~mask) | ((first + u) & mask));
+                b4[nb] = __builtin_amdgcn_fmed3f(b3[nb], b4[nb], v);
+                b3[nb] = __builtin_amdgcn_fmed3f(b2[nb], b3[nb], v);
+                b2[nb] = __builtin_amdgcn_fmed3f(b1[nb], b2[nb], v);
+                b1[nb] = __builtin_amdgcn_fmed3f(b1[nb], v, -AF_NONE);  // (the smaller; a minimum would first make v canonical)
+            }
+    };
+    int a1[NB], a2[NB], a3[NB];  // the groups of b1, b2, b3, once the last segment is done
+    fetch(0);
+    stash(0, 0);
+    fetch(min(TC, K - 1));
+    __syncthreads();
+    f32x16 acc[2][NB];  // of this 32 cells and of the 32 before, whose minima are taken beside these products
+    int buf = 0;
+    for (int s0 = 0; s0 < K; s0 += S::SEG) {  // uniform
+        const int s1 = min(K, s0 + S::SEG);
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb) {
+            b1[nb] = b2[nb] = b3[nb] = b4[nb] = AF_NONE;
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[1][nb][r] = AF_NONE;
+        }
+        for (int c0 = s0; c0 < s1; c0 += TC, buf ^= 1) {
+            // one block of code, so that the conversion of the next tile and the minima of the results before are dealt out
+            // among the products
+#pragma unroll
+            for (int ct = 0; ct < CT; ++ct) {
+                multiply(buf, ct, acc[ct & 1]);
+                note(acc[(ct & 1) ^ 1], (unsigned)((c0 - s0) / 8 + 4 * ct - 4) & S::MASK);
+                if (ct == 0) {
+                    stash(c0 + TC, buf ^ 1);  // (nobody reads what is beyond the last; that buffer was read before the last barrier)
+                    fetch(min(c0 + 2 * TC, K - 1));
+                }
+            }
+            if constexpr (CT == 1) {
+#pragma unroll
+                for (int nb = 0; nb < NB; ++nb) acc[1][nb] = acc[0][nb];
+            }
+            __syncthreads();
+        }
+        note(acc[1], (unsigned)((s1 - s0 - 1) / TC * CT + CT - 1) * 4);
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb) {
+            auto group = [&](float b) { return (int)(__float_as_uint(b) & S::MASK) * 2 + s0 / 4 + half; };
+            auto value = [&](float b) { return __uint_as_float(__float_as_uint(b) & ~S::MASK); };
+            float v[4] = {value(b1[nb]), value(b2[nb]), value(b3[nb]), value(b4[nb])};
+            int g[3] = {group(b1[nb]), group(b2[nb]), group(b3[nb])};
+            if (s0 > 0) {  // uniform
+                float n[4];
+                int h[3];
+#pragma unroll
+                for (int k = 0; k < 4; ++k) n[k] = sh.low[k][nb][tid];
+#pragma unroll
+                for (int k = 0; k < 3; ++k) h[k] = sh.group[k][nb][tid];
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    const int gk = g[min(k, 2)];  // (the fourth comes last: all that counts is its value)
+                    const bool l1 = v[k] < n[0], l2 = v[k] < n[1], l3 = v[k] < n[2];
+                    n[3] = __builtin_amdgcn_fmed3f(n[2], n[3], v[k]);
+                    n[2] = __builtin_amdgcn_fmed3f(n[1], n[2], v[k]);
+                    n[1] = __builtin_amdgcn_fmed3f(n[0], n[1], v[k]);
+                    n[0] = fminf(n[0], v[k]);
+                    h[2] = l2 ? h[1] : l3 ? gk : h[2];
+                    h[1] = l1 ? h[0] : l2 ? gk : h[1];
+                    h[0] = l1 ? gk : h[0];
+                }
+#pragma unroll
+                for (int k = 0; k < 4; ++k) v[k] = n[k];
+#pragma unroll
+                for (int k = 0; k < 3; ++k) g[k] = h[k];
+            }
+            if (s1 < K) {  // uniform
+#pragma unroll
+                for (int k = 0; k < 4; ++k) sh.low[k][nb][tid] = v[k];
+#pragma unroll
+                for (int k = 0; k < 3; ++k) sh.group[k][nb][tid] = g[k];
+            }
+            b1[nb] = v[0]; b2[nb] = v[1]; b3[nb] = v[2]; b4[nb] = v[3];
+            a1[nb] = g[0]; a2[nb] = g[1]; a3[nb] = g[2];
+        }
     }
 
     // over all the centroids
@@ -466,8 +524,8 @@ __device__ __forceinline__ void filter_tile(FilterTile<NT, KS, NB, F> &sh, const
 
     // With b1 the smallest score, reached by a cell c*: the closest cell's score is at most b1 + 2 xerr + 2 cerr(c*).
     // |c*'|^2 is at most the largest of all cells, and |c*'| <= |x'| + |x' - c*'| with |x' - c*'|^2 <= b1 + |x'|^2 + what
-    // rounding adds: under a thousandth of |x'|^2 (Split); xerr + 2 cerr(c*) (Half), the latter at most 1.8e-3 |c*'|^2 + a
-    // constant, so that |c*'| is at most 1 / (1 - 0.043) of what it is without.  A centroid whose score overflows or is NaN (it
+    // rounding adds: under 1.1 thousandths of |x'|^2 (Split); xerr + 2 cerr(c*) (Half), the latter at most 2.0e-3 |c*'|^2 + a
+    // constant, so that |c*'| is at most 1 / (1 - 0.045) of what it is without.  A centroid whose score overflows or is NaN (it
     // loses every comparison) is not the closest to a vector that has one within 1e18 (Split) or within HALF_FAR (Half;
     // nor has a stray one, with 0.29 2^31 at least, reached b1 then).
 #pragma unroll
@@ -484,21 +542,21 @@ __device__ __forceinline__ void filter_tile(FilterTile<NT, KS, NB, F> &sh, const
             thr = low + 2.001f * (xerr + __builtin_fmaf(eps_c, cn, tiny));
             sure = xn[nb] < HALF_NEAR && low < HALF_FAR && b4[nb] > thr;
         } else {
-            const float far = __builtin_sqrtf(xn[nb]) + __builtin_sqrtf(fmaxf(low + xn[nb], 0.0f) + 1e-3f * xn[nb]);
-            thr = low + __builtin_fmaf(2.0f * eps, xn[nb] + 1.01f * fminf(far * far, cmax), 1e-30f);
-            sure = xn[nb] < 1e36f && thr < 1e36f && (THIRD ? b4[nb] : b3[nb]) > thr;
+            const float far = __builtin_sqrtf(xn[nb]) + __builtin_sqrtf(fmaxf(low + xn[nb], 0.0f) + 1.1e-3f * xn[nb]);
+            thr = low + 2.0f * __builtin_fmaf(eps, xn[nb], __builtin_fmaf(eps_c, 1.01f * fminf(far * far, cmax), 1e-30f));
+            sure = xn[nb] < 1e36f && thr < 1e36f && b4[nb] > thr;
         }
         // this lane's groups in question, then those of the other half; the first entry is never empty
         // unless the vector is left to the kernel after this one
-        const int g1 = b1[nb] <= thr ? 2 * a1[nb] + half : -1, g2 = b2[nb] <= thr ? 2 * a2[nb] + half : -1,
-                  g3 = THIRD && b3[nb] <= thr ? 2 * a3[nb] + half : -1;
+        const int g1 = b1[nb] <= thr ? a1[nb] : -1, g2 = b2[nb] <= thr ? a2[nb] : -1,
+                  g3 = b3[nb] <= thr ? a3[nb] : -1;
         const int o1 = __shfl_xor(g1, 32), o2 = __shfl_xor(g2, 32), o3 = __shfl_xor(g3, 32);
         const int other = __shfl_xor((int)sure, 32);  // (asked by all lanes: a lane that does not ask gives nothing)
         const bool all = !(sure && other);
         if (half == 0) {
             // own groups first (they fill up in this order), the others' behind them
             const int k = (g1 >= 0) + (g2 >= 0) + (g3 >= 0);
-            int c[6] = {g1, g2, g3, -1, -1, -1};  // (NC of them)
+            int c[NC] = {g1, g2, g3, -1, -1, -1};
 #pragma unroll
             for (int e = 0; e < NC; ++e) c[e] = e == k ? o1 : e == k + 1 ? o2 : e == k + 2 ? o3 : c[e];
 #pragma unroll
@@ -508,40 +566,39 @@ __device__ __forceinline__ void filter_tile(FilterTile<NT, KS, NB, F> &sh, const
     }
     __syncthreads();
 
-    // The groups in question, 16 lanes per vector: the 16 distances of a group in float32, the lanes side by side along
+    // The groups in question, eight lanes per vector: the four distances of a group in float32, the lanes side by side along
     // the components (a lane per cell would read 64 different lines per load).  A cell that no other comes within the
     // rounding of is the closest; else the cells that do are measured by the definition, a lane each.
-    const int r = tid & 15, team = (lane >> 4) * 16;
-    auto cell_of = [&](int g, int k) { return (g >> 1) * 32 + 8 * (k >> 2) + 4 * (g & 1) + (k & 3); };
-    for (int v = tid >> 4; v < TM; v += NT / 16) {
+    const int r = tid & 7, team = lane & ~7, mine = r >> 1;  // (two lanes end with the same cell, 4 g + mine)
+    for (int v = tid >> 3; v < TM; v += NT / 8) {
         const int64_t i = row_of(v);
-        if (i < 0 || cand[v][0] < 0) continue;  // uniform over the 16 lanes
+        if (i < 0 || cand[v][0] < 0) continue;  // uniform over the eight lanes
         const float *xr = x + i * ldx;
-        float xv[KS];
-        constexpr int W = VEC && KS % 4 == 0 ? 4 : 1;  // components per load
+        constexpr int W = VEC ? 4 : 1;  // components per load
+        float xv[2 * KS];
 #pragma unroll
-        for (int e = 0; e < KS / W; ++e)
+        for (int e = 0; e < 2 * KS / W; ++e)
 #pragma unroll
             for (int u = 0; u < W; ++u) {
-                const int t = W * (r + 16 * e) + u;
+                const int t = W * (r + 8 * e) + u;
                 xv[W * e + u] = VEC || t < d ? xr[t] : 0.0f;
             }
-        // distance to cell r of group g
+        // distance to cell 4 g + mine
         auto measure = [&](int g) {
-            float part[16];
+            float part[4];
 #pragma unroll
-            for (int k = 0; k < 16; ++k) {
-                const float *cr = coarse + (size_t)min(cell_of(g, k), K - 1) * d;
+            for (int k = 0; k < 4; ++k) {
+                const float *cr = coarse + (size_t)min(4 * g + k, K - 1) * d;
                 float acc = 0.0f;
 #pragma unroll
-                for (int e = 0; e < KS / W; ++e) {
+                for (int e = 0; e < 2 * KS / W; ++e) {
                     float cv[W];
                     if constexpr (W == 4) {
-                        const float4 f = *reinterpret_cast<const float4 *>(cr + 4 * (r + 16 * e));
+                        const float4 f = *reinterpret_cast<const float4 *>(cr + 4 * (r + 8 * e));
                         cv[0] = f.x; cv[1] = f.y; cv[2] = f.z; cv[3] = f.w;
                     } else {
-                        const int t = r + 16 * e;
-                        cv[0] = VEC || t < d ? cr[t] : 0.0f;
+                        const int t = r + 8 * e;
+                        cv[0] = t < d ? cr[t] : 0.0f;
                     }
 #pragma unroll
                     for (int u = 0; u < W; ++u) {
@@ -551,26 +608,27 @@ __device__ __forceinline__ void filter_tile(FilterTile<NT, KS, NB, F> &sh, const
                 }
                 part[k] = acc;
             }
-            // sums over the 16 lanes, halving the cells a lane is responsible for: lane r ends with cell r
+            // sums over the eight lanes, halving the cells a lane is responsible for
 #pragma unroll
-            for (int w = 8; w >= 1; w >>= 1)
+            for (int w = 4; w >= 2; w >>= 1)
 #pragma unroll
-                for (int k = 0; k < w; ++k) {
+                for (int k = 0; k < w / 2; ++k) {
                     const bool up = r & w;
-                    const float keep = up ? part[k + w] : part[k], give = up ? part[k] : part[k + w];
+                    const float keep = up ? part[k + w / 2] : part[k], give = up ? part[k] : part[k + w / 2];
                     part[k] = keep + __shfl_xor(give, w);
                 }
-            return cell_of(g, r) < K && part[0] == part[0] ? part[0] : __builtin_inff();  // (a NaN is never the closest)
+            const float to = part[0] + __shfl_xor(part[0], 1);
+            return 4 * g + mine < K && to == to ? to : __builtin_inff();  // (a NaN is never the closest)
         };
         auto lowest = [&](float f) {
 #pragma unroll
-            for (int w = 8; w >= 1; w >>= 1) f = fminf(f, __shfl_xor(f, w));
+            for (int w = 4; w >= 2; w >>= 1) f = fminf(f, __shfl_xor(f, w));
             return f;
         };
-        // rounding of two sums of d squares (d / 16 + 4 additions, the differences, the squares): (d / 8 + 14) 2^-24,
+        // rounding of two sums of d squares (d / 8 + 3 additions, the differences, the squares): (d / 4 + 12) 2^-24,
         // here at least 1.3 times that
-        auto slack = [&](float f) { return f + __builtin_fmaf(f, 2e-6f + 1e-7f * KS, 1e-33f); };
-        auto among = [&](bool near) { return __popcll((__ballot(near) >> team) & 0xffffull); };
+        auto slack = [&](float f) { return f + __builtin_fmaf(f, 2e-6f + 3.2e-7f * KS, 1e-33f); };
+        auto among = [&](bool near) { return __popcll((__ballot(near) >> team) & 0x55ull); };
         const int g0 = cand[v][0];
         float dist[NC];
         dist[0] = measure(g0);
@@ -578,13 +636,13 @@ __device__ __forceinline__ void filter_tile(FilterTile<NT, KS, NB, F> &sh, const
         for (int q = 1; q < NC; ++q) dist[q] = __builtin_inff();
         float close = slack(lowest(dist[0]));
         int rivals = among(dist[0] <= close);
-        int bc = dist[0] <= close ? cell_of(g0, r) : 0x7fffffff;
-        if (cand[v][1] >= 0) {  // uniform over the 16 lanes
+        int bc = dist[0] <= close ? 4 * g0 + mine : 0x7fffffff;
+        if (cand[v][1] >= 0) {  // uniform over the eight lanes
             float least = dist[0];
 #pragma unroll 1
             for (int q = 1; q < NC; ++q) {
                 const int g = cand[v][q];
-                if (g < 0) break;  // uniform over the 16 lanes
+                if (g < 0) break;  // uniform over the eight lanes
                 const float to = measure(g);
                 least = fminf(least, to);
 #pragma unroll
@@ -597,10 +655,10 @@ __device__ __forceinline__ void filter_tile(FilterTile<NT, KS, NB, F> &sh, const
             for (int q = 0; q < NC; ++q) {
                 const bool near = dist[q] <= close && cand[v][q] >= 0;
                 rivals += among(near);
-                if (near) bc = cell_of(cand[v][q], r);
+                if (near) bc = 4 * cand[v][q] + mine;
             }
         }
-        if (rivals > 1) {  // uniform over the 16 lanes
+        if (rivals > 1) {  // uniform over the eight lanes
             double bd = __builtin_inf();
             bc = 0x7fffffff;
 #pragma unroll 1
@@ -609,7 +667,7 @@ __device__ __forceinline__ void filter_tile(FilterTile<NT, KS, NB, F> &sh, const
                 float dq = dist[0];
 #pragma unroll
                 for (int p = 1; p < NC; ++p) dq = p == q ? dist[p] : dq;
-                const int c = cell_of(g, r);
+                const int c = 4 * g + mine;
                 if (g < 0 || !(dq <= close) || c >= K) continue;
                 const float *cr = coarse + (size_t)c * d;
                 double dd = 0.0;
@@ -630,14 +688,14 @@ __device__ __forceinline__ void filter_tile(FilterTile<NT, KS, NB, F> &sh, const
                 if (dd < bd || (dd == bd && c < bc)) { bd = dd; bc = c; }
             }
 #pragma unroll
-            for (int w = 8; w >= 1; w >>= 1) {
+            for (int w = 4; w >= 2; w >>= 1) {
                 const double od = __shfl_xor(bd, w);
                 const int oc = __shfl_xor(bc, w);
                 if (od < bd || (od == bd && oc < bc)) { bd = od; bc = oc; }
             }
         } else {
 #pragma unroll
-            for (int w = 8; w >= 1; w >>= 1) bc = min(bc, __shfl_xor(bc, w));
+            for (int w = 4; w >= 2; w >>= 1) bc = min(bc, __shfl_xor(bc, w));
         }
         if (r == 0) store(i, bc);
     }
@@ -669,6 +727,37 @@ __global__ __launch_bounds__(NT, 2) void assign_filter_kernel(const float *__res
 // 60 against 48 ms for 500 k vectors of 256 components, all marked).
 constexpr int ASG_RANGE = 4096, ASG_FEW = 20;
 
+// Centroids up to the last one that differs from its predecessor, by 256 threads (`last`: a word of LDS).  Those behind it are
+// copies of it, and the lowest of equal cells wins: a list of centroids that is padded at its end, or one centroid over and over,
+// is measured without them (1024 equal centroids, d = 64, 200 k vectors: 1.22 -> 0.17 ms).  One round trip where there are none.
+__device__ __forceinline__ int without_copies(const float *__restrict__ coarse, int K, int d, int *last)
+{
+    constexpr int PER = 16;
+    const int tid = threadIdx.x;
+    const unsigned *c = reinterpret_cast<const unsigned *>(coarse);
+    if (tid == 0) *last = 0;
+    __syncthreads();
+    for (int64_t end = (int64_t)K * d; end > d; end -= 256 * PER) {  // uniform
+        unsigned a[PER], b[PER];
+#pragma unroll
+        for (int u = 0; u < PER; ++u) {
+            const int64_t i = max(end - 1 - tid - 256 * u, (int64_t)d);
+            a[u] = c[i];
+            b[u] = c[i - d];
+        }
+        int row = 0;
+#pragma unroll
+        for (int u = 0; u < PER; ++u)
+            if (row == 0 && a[u] != b[u]) row = (int)(max(end - 1 - tid - 256 * u, (int64_t)d) / d);
+        if (row) atomicMax(last, row);
+        __syncthreads();
+        const int found = *last;
+        __syncthreads();  // (read by all before the next round writes it)
+        if (found) return found + 1;  // uniform
+    }
+    return 1;
+}
+
 template <int KS, bool VEC, bool AGAIN, bool DEFINITION>
 __global__ __launch_bounds__(256) void assign_rest_kernel(const float *__restrict__ coarse, int K, int d,
                                                           const float *__restrict__ x, int64_t ldx, int64_t n, int range,
@@ -680,7 +769,7 @@ __global__ __launch_bounds__(256) void assign_rest_kernel(const float *__restric
     __shared__ __attribute__((aligned(16))) char room[BYTES];  // for one of them at a time
     AssignTile &s = *reinterpret_cast<AssignTile *>(room);
     __shared__ uint16_t todo[ASG_RANGE];
-    __shared__ int ntodo, nleft;
+    __shared__ int ntodo, nleft, last;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int64_t i0 = (int64_t)blockIdx.x * range;
     if (tid == 0) { ntodo = 0; nleft = 0; }
@@ -691,6 +780,9 @@ __global__ __launch_bounds__(256) void assign_rest_kernel(const float *__restric
     }
     __syncthreads();
     int count = ntodo;
+    if (count == 0) return;  // uniform
+    const int cells_in_all = K;
+    if (count > ASG_FEW) K = without_copies(coarse, K, d, &last);  // uniform
     if constexpr (AGAIN) {
         if (count > ASG_FEW) {  // uniform
             int behind = 0;  // undecided in the tiles so far
@@ -714,7 +806,7 @@ __global__ __launch_bounds__(256) void assign_rest_kernel(const float *__restric
             for (int c0 = 0; c0 < count; c0 += 256) {  // uniform; the list shrinks in place
                 const int k = c0 + tid < count ? todo[c0 + tid] : -1;
                 __syncthreads();
-                if (k >= 0 && assign_marked(cells[i0 + k], K, accumulate)) todo[atomicAdd(&nleft, 1)] = (uint16_t)k;
+                if (k >= 0 && assign_marked(cells[i0 + k], cells_in_all, accumulate)) todo[atomicAdd(&nleft, 1)] = (uint16_t)k;
                 __syncthreads();
             }
             count = nleft;
@@ -799,6 +891,22 @@ static bool half_factors_pay(int K, int d, int64_t n, bool vec)
     return d >= 8 && K >= (d > 64 ? 1024 : 4096);
 }
 
+// 512 (256 beyond 128 components) vectors per workgroup, or 128?  The wide form converts the centroids a quarter as often and is
+// one workgroup per compute unit; it loses where the chip is not filled and the walk over the centroids is short.  us, narrow /
+// wide: K = 4096, d = 128 50 k 129 / 112, 66 k 190 / 113, 131 k 312 / 149, 262 k 512 / 288; d = 64 50 k 69 / 74, 66 k 102 / 76,
+// 148 k 194 / 157; d = 256 50 k 251 / 179, 262 k 1017 / 751; d = 32 66 k 62 / 61, 115 k 83 / 62, 148 k 103 / 118, 197 k 132 / 118;
+// K = 256, d = 128 66 k 35 / 35, 115 k 49 / 37, 148 k 56 / 65, 197 k 73 / 68, 262 k 83 / 72; d = 64 115 k 26 / 25, 148 k 34 / 44,
+// 262 k 47 / 48; d = 256 66 k 68 / 74, 115 k 83 / 77, 262 k 160 / 152.
+template <int KS>
+static bool wide_pays(int K, int64_t n)
+{
+    if (K >= 1024 && KS > 2) return n >= (KS > 8 ? 32768 : 65536);
+    if (KS > 8) return n >= 98304;
+    const int64_t round = 512 * 256;  // vectors that fill the chip once
+    if (K >= 1024 || KS > 4) return n >= 3 * round / 4 && (n <= round || n >= 3 * round / 2);
+    return n >= 2 * round;
+}
+
 template <int KS>
 static void launch_filter(const float *coarse, int K, int d, const float *x, int64_t ldx, int64_t n, int range,
                           int32_t *cells, int scale, int accumulate, hipStream_t st)
@@ -819,10 +927,10 @@ static void launch_filter(const float *coarse, int K, int d, const float *x, int
         return;
     }
     if (vec) {
-        bool wide = false;
-        if constexpr (KS <= 8) {
-            wide = n >= 512 * 256;  // 512 vectors per workgroup once that fills the chip; else 128
-            if (wide) QADC_FILTER(512, 2, true, Half, dim3((unsigned)ceil_div(n, 512)));
+        const bool wide = wide_pays<KS>(K, n);
+        if (wide) {
+            if constexpr (KS <= 8) QADC_FILTER(512, 2, true, Half, dim3((unsigned)ceil_div(n, 512)));
+            else QADC_FILTER(512, 1, true, Half, dim3((unsigned)ceil_div(n, 256)));
         }
         if (!wide) QADC_FILTER(256, 1, true, Half, grid);
         QADC_REST(true, true, ONE);

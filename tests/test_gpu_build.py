@@ -529,6 +529,30 @@ def test_ivf_assign_of_crowded_cells(Q, d, K, n, kind):
     assert torch.equal(got, want)
 
 
+# split factors (few vectors) are merged every 512 cells, binary16 factors every 4096; the workgroups of 512 threads from 32,768
+# (d = 256), 65,536 and 98,304 vectors (d = 32)
+@pytest.mark.parametrize("d,K,n", [(128, 511, 700), (64, 513, 700), (200, 1540, 500), (32, 1030, 900),
+                                   (64, 4095, 50_001), (128, 4097, 50_001), (128, 4099, 65_601), (64, 8193, 65_536),
+                                   (256, 4100, 32_801), (32, 4096, 98_400), (96, 12_300, 66_000), (24, 4_200, 99_000)])
+def test_ivf_assign_over_many_cells(Q, d, K, n):
+    """The closest cell, and the lowest of equal ones, in any of the stretches of cells whose finds are merged: whole numbers,
+    whose squares and sums float64 holds exactly."""
+    import torch
+    g = torch.Generator(device="cuda:0")
+    g.manual_seed(d + K + n)
+    coarse = torch.randint(0, 60, (K, d), generator=g, device="cuda:0").float()
+    coarse[K - K // 5:] = coarse[:K // 5]                                # the same centroids, far apart
+    coarse[K // 2] = coarse[K - 1]
+    x = coarse[torch.randint(0, K, (n,), generator=g, device="cuda:0")]
+    x = x + torch.randint(-20, 21, (n, d), generator=g, device="cuda:0").float()
+    got = Q.qadc_ivf_assign(coarse, x)
+    c = coarse.double()
+    for s in range(0, n, 8192):
+        dist = (c * c).sum(1)[None] - 2 * (x[s:s + 8192].double() @ c.T)
+        want = (dist == dist.min(1, keepdim=True).values).int().argmax(1).int()
+        assert torch.equal(got[s:s + 8192], want)
+
+
 @pytest.mark.parametrize("K,dh,n", [(2, 4, 1_000), (64, 16, 4_000), (333, 32, 131_500)])
 def test_multi_index_assign_of_crowded_cells(Q, K, dh, n):
     """Both halves leave vectors to the second kernel, which finds them among the cells of the first half."""
