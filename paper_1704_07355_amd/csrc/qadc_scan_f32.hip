@@ -94,6 +94,25 @@ __device__ __forceinline__ void tile_dists(const uint4 (&w)[2], const float *lut
     }
 }
 
+// The same in two steps: the sum over the first half of a code's bytes, and the rest of it.
+template <int KSUB, int ROW, int FROM, int TO>
+__device__ __forceinline__ float add_bytes(const uint4 (&w)[2], int slot, const float *lut, float acc)
+{
+#pragma unroll
+    for (int jb = FROM; jb < TO; ++jb) {
+        unsigned b;
+        if constexpr (ROW <= 16) b = byte_of(w[slot / (16 / ROW)], slot % (16 / ROW) * ROW + jb);
+        else b = byte_of(w[jb >> 4], jb & 15);
+        if constexpr (KSUB == 16) {
+            acc = acc + lut[(2 * jb) * 16 + (b & 15u)];
+            acc = acc + lut[(2 * jb + 1) * 16 + (b >> 4)];
+        } else {
+            acc = acc + lut[jb * 256 + b];
+        }
+    }
+    return acc;
+}
+
 template <int ROW, int NT>
 __device__ __forceinline__ bool slot_valid(const int (&nc)[2], int slot)
 {
@@ -110,6 +129,63 @@ __device__ __forceinline__ unsigned slot_index(int slot)
     } else {
         return threadIdx.x;
     }
+}
+
+// Smallest entry of tables FROM .. TO - 1 (KSUB entries each, in LDS), by the wavefronts of the workgroup in turn.  A table with an
+// entry that is not finite gets a NaN where `finite_only`, else the smallest that is a number.
+template <int KSUB, int FROM, int TO, int NT>
+__device__ __forceinline__ void table_minima(const float *lut, float *tmin, bool finite_only)
+{
+    const int l = lane_id();
+    for (int j = FROM + (int)(threadIdx.x / WAVE); j < TO; j += NT / WAVE) {  // uniform over the wavefront
+        float b = lut[j * KSUB + l % KSUB];
+        bool finite = fabsf(b) < __builtin_inff();
+#pragma unroll
+        for (int k = 1; k < KSUB / WAVE; ++k) {
+            const float e = lut[j * KSUB + k * WAVE + l];
+            finite = finite && fabsf(e) < __builtin_inff();
+            b = fminf(b, e);
+        }
+#pragma unroll
+        for (int x = 32; x >= 1; x >>= 1) b = fminf(b, __shfl_xor(b, x));
+        if (finite_only && __ballot(!finite) != 0ull) b = __builtin_nanf("");
+        if (l == 0) tmin[j] = b;
+    }
+}
+
+// The largest sum over the first half of a code's tables with which the whole sum can still lie in a bin up to tau: the
+// rest is at least the minima of its tables, and float32 additions keep the order.  Whole wavefronts; lane i looks at the
+// i-th of 64 places of what is left of all float32 numbers, in their order, five times, and then at the last four.
+template <int FROM, int TO>
+__device__ __forceinline__ float half_bound(const float *tmin, F32Range r, unsigned tau)
+{
+    float rest[TO - FROM];
+    bool finite = true;
+#pragma unroll
+    for (int j = FROM; j < TO; ++j) {
+        rest[j - FROM] = tmin[j];
+        finite = finite && tmin[j] == tmin[j];
+    }
+    if (!finite) return __builtin_inff();  // (uniform: entries that are no numbers keep no order)
+    unsigned base = 0;
+#pragma unroll 1
+    for (int shift = 26; shift >= -4; shift -= 6) {
+        const unsigned at = base + ((unsigned)lane_id() << max(shift, 0));
+        float x = ord2f(at);
+        bool ok;
+        if (x != x) {
+            ok = at < 0x80000000u;  // (images of no number: below -infinity, above infinity)
+        } else {
+#pragma unroll
+            for (int j = 0; j < TO - FROM; ++j) x = x + rest[j];
+            ok = f32_bin(x, r) <= tau;
+        }
+        if (shift < 0 && lane_id() >= 4) ok = false;
+        const unsigned long long m = __ballot(ok);
+        if (m == 0ull) return -__builtin_inff();  // (tau is a bin that no sum reaches)
+        base += (unsigned)(63 - __clzll((long long)m)) << max(shift, 0);
+    }
+    return ord2f(base);
 }
 
 // Range kernel: one workgroup per query; lo = sum_j min_i D^j[i] (float32, increasing j),
@@ -129,7 +205,9 @@ __global__ __launch_bounds__(F32_NT) void f32_range_kernel(
     const int q = blockIdx.x;
     load_float_tables<KSUB, ROW, NT>(luts + (size_t)q * M * KSUB, lut);
     __syncthreads();
-    if (tid < M) {
+    if constexpr (KSUB == 256) {  // (a thread per table: 2 us more)
+        table_minima<KSUB, 0, M, NT>(lut, tmin, false);
+    } else if (tid < M) {
         float b = lut[tid * KSUB];
         for (int i = 1; i < KSUB; ++i) b = fminf(b, lut[tid * KSUB + i]);
         tmin[tid] = b;
@@ -137,13 +215,16 @@ __global__ __launch_bounds__(F32_NT) void f32_range_kernel(
     for (int i = tid; i < n0; i += NT) {
         const uint8_t *c = codes + (size_t)i * ROW;
         float acc = 0.0f;
-        for (int jb = 0; jb < ROW; ++jb) {
-            const unsigned b = c[jb];
-            if constexpr (KSUB == 16) {
+        if constexpr (KSUB == 256) {
+            unsigned w[ROW / 4];
+            __builtin_memcpy(w, c, ROW);
+#pragma unroll
+            for (int jb = 0; jb < ROW; ++jb) acc = acc + lut[jb * 256 + ((w[jb >> 2] >> (8 * (jb & 3))) & 0xffu)];
+        } else {
+            for (int jb = 0; jb < ROW; ++jb) {
+                const unsigned b = c[jb];
                 acc = acc + lut[(2 * jb) * 16 + (b & 15u)];
                 acc = acc + lut[(2 * jb + 1) * 16 + (b >> 4)];
-            } else {
-                acc = acc + lut[jb * 256 + b];
             }
         }
         cand[i] = f2ord(acc);
@@ -211,6 +292,16 @@ __global__ __launch_bounds__(F32_NT) void seed_f32_kernel(
     }
 }
 
+// 8-bit codes of 8 bytes and more are summed half by half: the scan is bound by the conflicts of its lookups in 256-entry tables
+// (50 M codes of 8 bytes 84 us = 4.8 TB/s), and of most codes half a sum is enough (67.6 us = 5.9 TB/s; 20 M of 16 bytes 88 -> 78
+// a call).  The bound on half a sum costs a workgroup a microsecond, worth it from one and a half tiles each (F32_SEED_HALVES;
+// four queries over 2 M codes of 8 bytes 49 -> 54 us with one).  4-bit codes, whose 16-entry tables have no conflicts, and 4-byte
+// codes lose by it (20 M codes 60 -> 67 us, 41 -> 46); so do tables without structure where half a sum says little (20 M of 32
+// bytes, uniform entries 497 -> 508 for four queries; learned ones 501 -> 483).
+template <int KSUB, int ROW>
+constexpr bool F32_HALVES = KSUB == 256 && ROW >= 8;
+constexpr int F32_SEED_HALVES = 2;
+
 // Scan kernel.  KSUB = 16: ROW = m/2 bytes per code, two components per byte; KSUB = 256:
 // ROW = m bytes.  Workgroup g takes tiles g, g+G, ...  With a grid-wide bound the pass is
 // barrier-free (keys whose bin is at or below the bound are appended to the LDS list); on
@@ -228,6 +319,7 @@ __global__ __launch_bounds__(F32_NT) void scan_f32_kernel(
     __shared__ float lut[M * KSUB];
     __shared__ uint64_t keys[C::CAP];
     __shared__ F32Shared sh;
+    __shared__ float tmin[M];
 
     const int tid = threadIdx.x;
     const int q = blockIdx.y;
@@ -259,30 +351,73 @@ __global__ __launch_bounds__(F32_NT) void scan_f32_kernel(
     __syncthreads();
 
     const bool seeded = sh.tau < 255u;  // uniform (bin 255 is never counted)
+    if constexpr (F32_HALVES<KSUB, ROW>) {
+        if (seeded && has_seed == F32_SEED_HALVES) {  // uniform
+            table_minima<KSUB, M / 2, M, NT>(lut, tmin, true);
+            __syncthreads();
+        }
+    }
     unsigned have = 0;
     bool careful = !seeded;
     if (seeded) {
         const unsigned tau = sh.tau;
         const F32Range r = ranges[q];
         unsigned rel = 0;
-        for (int64_t t0 = (int64_t)g * C::TILE; t0 < n; t0 += G * C::TILE, rel += C::TILE) {
+        if constexpr (F32_HALVES<KSUB, ROW>) {
+            const float upto = has_seed == F32_SEED_HALVES ? half_bound<M / 2, M>(tmin, r, tau) : __builtin_inff();
+            const int64_t step = G * C::TILE;
             uint4 w[2];
             int nc[2];
-            tile_load<ROW, NT>(codes, t0, n, w, nc);
-            float d[C::CPT];
-            tile_dists<KSUB, ROW, NT>(w, lut, d);
-            bool pass[C::CPT], any = false;
-#pragma unroll
-            for (int c = 0; c < C::CPT; ++c) {
-                pass[c] = slot_valid<ROW, NT>(nc, c) && f32_bin(d[c], r) <= tau;
-                any = any || pass[c];
-            }
-            if (__ballot(any) != 0ull) {  // the append code only runs in waves with a hit
+            tile_load<ROW, NT>(codes, (int64_t)g * C::TILE, n, w, nc);
+            for (int64_t t0 = (int64_t)g * C::TILE; t0 < n; t0 += step, rel += C::TILE) {  // uniform
+                uint4 wn[2] = {w[0], w[1]};
+                int ncn[2] = {0, 0};
+                if (t0 + step + C::TILE <= n) tile_load<ROW, NT, true>(codes, t0 + step, n, wn, ncn);
+                else if (t0 + step < n) tile_load<ROW, NT>(codes, t0 + step, n, wn, ncn);
+                // half of every sum first: most codes are beyond the bound by then, mostly all of a wavefront's
+                float d[C::CPT];
+                bool pass[C::CPT], any = false;
 #pragma unroll
                 for (int c = 0; c < C::CPT; ++c) {
-                    const unsigned slot = wave_append_slot(pass[c], &sh.fcnt);
-                    if (pass[c] && slot < (unsigned)C::CAP)
-                        keys[slot] = ((uint64_t)f2ord(d[c]) << 32) | (rel + slot_index<ROW, NT>(c));
+                    d[c] = add_bytes<KSUB, ROW, 0, ROW / 2>(w, c, lut, 0.0f);
+                    pass[c] = slot_valid<ROW, NT>(nc, c) && !(d[c] > upto);
+                    any = any || pass[c];
+                }
+                if (__ballot(any) != 0ull) {
+#pragma unroll
+                    for (int c = 0; c < C::CPT; ++c) {
+                        if (pass[c]) {
+                            d[c] = add_bytes<KSUB, ROW, ROW / 2, ROW>(w, c, lut, d[c]);
+                            pass[c] = f32_bin(d[c], r) <= tau;
+                        }
+                        const unsigned slot = wave_append_slot(pass[c], &sh.fcnt);
+                        if (pass[c] && slot < (unsigned)C::CAP)
+                            keys[slot] = ((uint64_t)f2ord(d[c]) << 32) | (rel + slot_index<ROW, NT>(c));
+                    }
+                }
+                w[0] = wn[0]; w[1] = wn[1];
+                nc[0] = ncn[0]; nc[1] = ncn[1];
+            }
+        } else {
+            for (int64_t t0 = (int64_t)g * C::TILE; t0 < n; t0 += G * C::TILE, rel += C::TILE) {
+                uint4 w[2];
+                int nc[2];
+                tile_load<ROW, NT>(codes, t0, n, w, nc);
+                float d[C::CPT];
+                tile_dists<KSUB, ROW, NT>(w, lut, d);
+                bool pass[C::CPT], any = false;
+#pragma unroll
+                for (int c = 0; c < C::CPT; ++c) {
+                    pass[c] = slot_valid<ROW, NT>(nc, c) && f32_bin(d[c], r) <= tau;
+                    any = any || pass[c];
+                }
+                if (__ballot(any) != 0ull) {  // the append code only runs in waves with a hit
+#pragma unroll
+                    for (int c = 0; c < C::CPT; ++c) {
+                        const unsigned slot = wave_append_slot(pass[c], &sh.fcnt);
+                        if (pass[c] && slot < (unsigned)C::CAP)
+                            keys[slot] = ((uint64_t)f2ord(d[c]) << 32) | (rel + slot_index<ROW, NT>(c));
+                    }
                 }
             }
         }
@@ -533,7 +668,10 @@ static bool make_f32_plan(int variant, int64_t n, int m, int nq, int R, F32Plan 
     const int cpt = (p->ROW <= 16) ? SCAN_VEC * (16 / p->ROW) : 1;
     const int tile = F32_NT * cpt;
     const int64_t tiles = n > 0 ? ceil_div(n, tile) : 1;
-    int64_t G = knob_or(knobs().scan_f32_wgs, 1024);
+    // (8-bit codes of 8 bytes and more: fewer, longer workgroups, whose bounds on half a sum are made once each; us with 1024 / 512:
+    // four queries over 20 M codes of 8 bytes 132 / 127, one query 55 / 62; one over 20 M of 32 bytes 168 / 144)
+    const int64_t g_def = p->KSUB == 256 && (p->ROW == 32 || (p->ROW >= 8 && nq > 1)) ? 512 : 1024;
+    int64_t G = knob_or(knobs().scan_f32_wgs, (int)g_def);
     if (G < 1) G = 1;
     if (G > tiles) G = tiles;
     const int64_t max_tiles_per_wg = 0xffffffffll / tile;
@@ -636,7 +774,7 @@ static int dispatch_f32(const F32Plan &p, const uint8_t *codes, int64_t n, const
             if (rc != QADC_OK) return rc;                                                            \
         }                                                                                            \
         launch(QADC_PROF_SCAN, (scan_f32_kernel<KSUB, ROW_>), grid, block, 0, st, codes, n, luts,     \
-               (const F32Range *)ranges, p.seed_wgs > 0 ? 1 : 0, R, ws, p.stride, p.l.counts_off,     \
+               (const F32Range *)ranges, p.seed_wgs > 0 ? (2 * ceil_div(n, F32_NT * ScanCfg<ROW_, F32_NT>::CPT) >= 3 * p.G ? F32_SEED_HALVES : 1) : 0, R, ws, p.stride, p.l.counts_off,     \
                p.l.lists_off, (const unsigned *)flags);                                              \
         break;
     switch (p.ROW) {

@@ -808,6 +808,37 @@ def test_float_scan_batches_with_ties_and_useless_bounds(Q, O):
     assert np.array_equal(idx_np(idx), wi) and np.array_equal(dist.cpu().numpy(), wd)
 
 
+# (8-bit codes of 8 bytes and more are summed half by half from 768 tiles, of 2048, 1024 and 512 codes; four queries from 384 tiles of
+# 2048 and 1024)
+@pytest.mark.parametrize("m,n,nq", [(8, 3_150_001, 1), (8, 1_600_003, 4), (16, 1_600_007, 1), (16, 800_001, 3), (32, 393_300, 1),
+                                    (32, 393_217, 2), (8, 3_145_727, 1), (4, 3_000_001, 1)])
+@pytest.mark.parametrize("kind", ["squares", "signed", "equal_halves", "huge", "infinite"])
+def test_float_scan_half_by_half(Q, O, m, n, nq, kind):
+    """The bound on half a sum drops no code: tables with negative entries, second halves that are all the same, entries beyond
+    float32's reach; codes planted at both ends whose first half alone is large or small."""
+    from oracle import cref
+    rng = np.random.default_rng(m + n + nq)
+    codes = rng.integers(0, 256, size=(n, m), dtype=np.uint8)
+    luts = rng.gamma(2.0, 50.0, size=(nq, m, 256)).astype(np.float32)
+    if kind == "signed":
+        luts -= np.float32(150.0)
+    if kind == "equal_halves":
+        luts[:, m // 2:] = np.float32(3.0)
+    if kind == "huge":
+        luts[:, :, ::7] = 3e38
+    if kind == "infinite":
+        luts[:, -1, 5] = np.inf
+        luts[:, 0, 9] = np.inf
+    best = luts[0].argmin(1).astype(np.uint8)
+    codes[n - 1] = best
+    codes[0, m // 2:] = best[m // 2:]
+    codes[n // 2, :m // 2] = best[:m // 2]
+    codes[n - 3:n - 1] = codes[n // 2]
+    wi, wd = cref.scan_topk_f32(codes, luts, 100)
+    idx, dist = Q.qadc_scan_topk(Q.QADC_F32_8BIT, to_gpu(codes), to_gpu(luts), 100)
+    assert np.array_equal(idx_np(idx), wi) and np.array_equal(dist.cpu().numpy(), wd)
+
+
 @pytest.mark.parametrize("m,n,nq", [(16, 300_007, 8), (16, 300_007, 19), (8, 700_000, 16), (32, 280_000, 9)])
 def test_float_scan_of_4bit_codes_in_query_batches(Q, O, m, n, nq):
     """Batches of eight queries and more over 4-bit codes take the query-tiled float kernel too (two
