@@ -265,6 +265,8 @@ def run_batched(args):
         Q.qadc_profile_enable(False)
         ach = n * nb * m / (ms_scan * 1e-3) / 1e12
         kernel = batch_scan_kernel(n, m, nb)
+        if kernel == "scan_u8_mfma_kernel" and launches > 2:  # filtered by decoded codes, in parts
+            kernel = "scan_u8_decoded_kernel (+ what it leaves, and the redo launch)"
         if kernel == "scan_u8_mfma_kernel":
             # The method's work is m lookup-adds per (code, query) pair (Alg. 2); the ceiling quoted for
             # it is the vector ALU's byte-lane rate, whatever unit executes it.  This kernel forms the
@@ -287,7 +289,7 @@ def run_batched(args):
             roofline = {"bound": "alu", "achieved": round(ach, 2),
                         "kernel": kernel + (" (+ 16-bit-lane and redo launches)" if "tiled" in kernel else ""),
                         "peak": ALU_PEAK_TLOOKUPS, "unit": "T lookup-adds/s", "frac": round(ach / ALU_PEAK_TLOOKUPS, 4),
-                        "traffic": TILED_TRAFFIC if (n, m, nb) == (100_000_000, 32, 256) else None,
+                        "traffic": TILED_TRAFFIC if "tiled" in kernel and (n, m, nb) == (100_000_000, 32, 256) else None,
                         "traffic_source": "profiles/hbm_traffic_configs_3_4_5.md (rocprofv3 --pmc FETCH_SIZE, bytes read per launch)",
                         "scan_ms": round(ms_scan, 3), "launches_timed": launches}
         kernels = {"scan_ms": round(ms_scan, 3), "tables_quantize_ms": round(ms_prep, 3),

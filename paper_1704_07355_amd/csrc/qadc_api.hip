@@ -47,6 +47,7 @@ void knobs_refresh()
     k.tiled_seed = env_knob("QADC_TILED_SEED");
     k.scan_f32_wgs = env_knob("QADC_SCAN_F32_WGS");
     k.tiled_mfma = env_knob("QADC_TILED_MFMA");
+    k.tiled_decoded = env_knob("QADC_TILED_DECODED");
     k.mfma_min_q = env_knob("QADC_MFMA_MIN_Q");
     k.mfma_min_q2 = env_knob("QADC_MFMA_MIN_Q2");
     k.mfma_min_q4 = env_knob("QADC_MFMA_MIN_Q4");

@@ -317,7 +317,8 @@ constexpr int SEARCH_TABLES_MAX_D = 2048;
 template <int B>
 __global__ __launch_bounds__(1024, 8) void search_tables_kernel(
     const float *__restrict__ codebooks, int d, const float *__restrict__ queries, const uint8_t *__restrict__ codes,
-    int n_init, int R, int nbins, int qmin_mode, uint8_t *__restrict__ qluts, uint8_t *__restrict__ qluts_too)
+    int n_init, int R, int nbins, int qmin_mode, uint8_t *__restrict__ qluts, uint8_t *__restrict__ qluts_too,
+    float *__restrict__ deltas)
 {
     constexpr int m = 2 * B;
     __shared__ float yq[SEARCH_TABLES_MAX_D];
@@ -384,6 +385,7 @@ __global__ __launch_bounds__(1024, 8) void search_tables_kernel(
         float delta = __fdiv_rn(qmax - qmin, (float)nbins);
         if (!(delta > 0.0f)) delta = 1.0f;
         delta_s = delta;
+        if (deltas) deltas[q] = delta;
     }
     __syncthreads();
     if (tid < entries) {
@@ -395,12 +397,12 @@ __global__ __launch_bounds__(1024, 8) void search_tables_kernel(
 }
 
 void search_tables(const float *codebooks, int d, int m, const float *queries, int nq, const uint8_t *codes, int n_init,
-                   int R, int nbins, int qmin_mode, uint8_t *qluts, uint8_t *qluts_too, hipStream_t st)
+                   int R, int nbins, int qmin_mode, uint8_t *qluts, uint8_t *qluts_too, float *deltas, hipStream_t st)
 {
 #define QADC_CASE(B_)                                                                                               \
     case B_:                                                                                                        \
         launch(QADC_PROF_TABLES, search_tables_kernel<B_>, dim3((unsigned)nq), dim3(1024), 0, st, codebooks, d, queries, \
-               codes, n_init, R, nbins, qmin_mode, qluts, qluts_too);                                              \
+               codes, n_init, R, nbins, qmin_mode, qluts, qluts_too, deltas);                                            \
         break;
     switch (m / 2) {
         QADC_CASE(4)

@@ -750,14 +750,14 @@ static void dispatch_scan_u8(const ScanPlan &p, const uint8_t *codes, int64_t n,
 // Scan + merge of one batch whose control blocks are ready (seed/prepare kernel done or not needed).
 static int scan_and_merge_u8(const ScanPlan &p, const uint8_t *codes, int64_t n, const uint8_t *qluts,
                              int nb, int nbins, int R, char *ws, uint32_t *out_idx, uint8_t *out_dist,
-                             hipStream_t st)
+                             const DecodedBatch *decoded, hipStream_t st)
 {
     unsigned *flags = nullptr;
     if (p.tiled && nb >= p.tiled_min) {
         unsigned *taus = reinterpret_cast<unsigned *>(ws + p.taus_off);
         flags = reinterpret_cast<unsigned *>(ws + p.flags_off);
         const int rc = run_tiled_scan(p.t, codes, n, nb, nbins, R, taus, ws, p.stride, p.countsA_off,
-                                      p.listsA_off, flags, p.wide ? nullptr : qluts, st);
+                                      p.listsA_off, flags, p.wide ? nullptr : qluts, decoded, st);
         if (rc != QADC_OK) return rc;
     }
     if (p.NT == 1024) dispatch_scan_u8<1024>(p, codes, n, qluts, nb, nbins, R, ws, flags, st);
@@ -797,7 +797,7 @@ int scan_topk_u8(int variant, const uint8_t *codes, int64_t n, int m, const uint
             if (rs != QADC_OK) return rs;
         }
         const int rc = scan_and_merge_u8(p, codes, n, ql, nb, nbins, R, ws, out_idx + (size_t)q0 * R,
-                                         out_dist + (size_t)q0 * R, st);
+                                         out_dist + (size_t)q0 * R, nullptr, st);
         if (rc != QADC_OK) return rc;
     }
     QADC_HIP_TRY(hipGetLastError());
@@ -805,7 +805,7 @@ int scan_topk_u8(int variant, const uint8_t *codes, int64_t n, int m, const uint
 }
 
 void search_tables(const float *codebooks, int d, int m, const float *queries, int nq, const uint8_t *codes, int n_init,
-                   int R, int nbins, int qmin_mode, uint8_t *qluts, uint8_t *qluts_too, hipStream_t st);
+                   int R, int nbins, int qmin_mode, uint8_t *qluts, uint8_t *qluts_too, float *deltas, hipStream_t st);
 
 // Workspace of qadc_search: the scan workspace, then float tables and quantized tables of a batch.
 static size_t search_extra_bytes(int m, int qbatch)
@@ -859,6 +859,13 @@ int search_u8(const float *codebooks, int d, int m, const float *queries, int nq
         const int nb = min(p.qbatch, nq - q0);
         const float *yq = queries + (size_t)q0 * d;
         uint8_t *ql_out = qluts_out ? qluts_out + (size_t)q0 * m * 16 : nullptr;
+        // (the region of float tables, which no batch writes: the steps of its quantizers, and what the scan of decoded codes
+        // takes; 4 m + 12 bytes a query and 64 m of its 64 m a query, and a batch has two queries)
+        float *deltas = (float *)(ws + p.ws_bytes);
+        const size_t deltas_bytes = align_up((size_t)nb * sizeof(float), 16);
+        const DecodedBatch db = {codebooks, yq, deltas, d, (char *)deltas + deltas_bytes,
+                                 (size_t)p.qbatch * m * 16 * sizeof(float) - deltas_bytes};
+        const bool batch = !(p.seed_wgs > 0 && nb < TILED_MIN_Q && !(p.tiled && nb >= p.tiled_min)) && nb >= 2;
         if (p.seed_wgs > 0 && nb < TILED_MIN_Q && !(p.tiled && nb >= p.tiled_min)) {
             // few queries: one launch; every sampling workgroup recomputes the tables it needs
             dim3 grid(p.seed_wgs, nb);
@@ -878,14 +885,14 @@ int search_u8(const float *codebooks, int d, int m, const float *queries, int nq
         } else {
             // a batch, or a small database: tables and quantizer once per query by their own
             // kernel, then the sampling kernel (large databases) or a self-seeding scan
-            search_tables(codebooks, d, m, yq, nb, codes, n_init, R, nbins, qmin_mode, qluts, ql_out, st);
+            search_tables(codebooks, d, m, yq, nb, codes, n_init, R, nbins, qmin_mode, qluts, ql_out, batch ? deltas : nullptr, st);
             if (p.seed_wgs > 0) {
                 const int rc = dispatch_seed_u8(p, codes, n, qluts, nb, nbins, R, ws, st);
                 if (rc != QADC_OK) return rc;
             }
         }
         const int rc = scan_and_merge_u8(p, codes, n, qluts, nb, nbins, R, ws, out_idx + (size_t)q0 * R,
-                                         out_dist + (size_t)q0 * R, st);
+                                         out_dist + (size_t)q0 * R, batch ? &db : nullptr, st);
         if (rc != QADC_OK) return rc;
     }
     QADC_HIP_TRY(hipGetLastError());

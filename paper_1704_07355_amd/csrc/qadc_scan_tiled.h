@@ -18,12 +18,58 @@ constexpr int TILED_MFMA_MIN_Q_B4 = 32;  // ... of 4-byte codes, in any workspac
 constexpr int TILED_MFMA_MIN_Q2 = 64;  // smallest batch for its 64-queries-per-wavefront form
 constexpr int TILED_MFMA_MIN_Q4 = 128; // ... for 128 queries per wavefront (codes of up to 8 bytes)
 
+// Workgroup id -> (query group, database chunk).  Workgroups are handed to the 8 XCDs in turn,
+// each XCD with an L2 of its own: XCD x = id % 8 takes the chunks congruent to x, and all query
+// groups of a chunk follow each other in its share of the ids, so that the chunk is fetched
+// from HBM once and every XCD gets the same mix of groups, whichever of them are active.
+__device__ __forceinline__ void tiled_group_and_chunk(int ngroups, int &grp, int &chunk)
+{
+    const unsigned id = blockIdx.x;
+    const unsigned slot = id >> 3;
+    grp = (int)(slot % (unsigned)ngroups);
+    chunk = (int)((slot / (unsigned)ngroups) * 8u + (id & 7u));
+}
+
 struct TiledPlan {
     int B, GC;
     int64_t chunk;
     size_t lds_bytes;
     bool mfma;  // the matrix-core kernel scans the batch
 };
+
+// What scan_u8_decoded_kernel needs beside the quantized tables: the codebooks [m][16][d / m] and queries [nq][d] they come from,
+// the quantizers' steps [nq], and room (see search_u8).  Null where a caller has only the tables.
+struct DecodedBatch {
+    const float *codebooks, *queries, *deltas;
+    int d;
+    char *room;
+    size_t room_bytes;
+};
+bool decoded_pays(int B, int64_t n, int nq, int cap, int R, const DecodedBatch &db);
+// A part of its scan: units of unit_codes codes from code `from` up to `to`; `word`: where their bits start.
+constexpr int DECODED_PARTS = 4;
+struct DecodedPart {
+    int64_t from, to;
+    int unit_codes, units, word;
+    unsigned limit;
+};
+// What it has left: for set s (of `queries` queries) and a part's unit u, bit u % 32 of word s * pitch + word + u / 32; and
+// everything behind a part of which more pairs passed (passed[part]) than its limit.  Null: nothing was done.
+struct DecodedLeft {
+    const unsigned *bits, *passed;
+    int pitch, queries, nparts;
+    DecodedPart parts[DECODED_PARTS];
+};
+// Has it stopped behind one of the first k parts?
+__device__ __forceinline__ bool decoded_stopped(const DecodedLeft &all, int k)
+{
+    for (int i = 0; i < k; ++i)
+        if (all.passed[i] > all.parts[i].limit) return true;
+    return false;
+}
+DecodedLeft run_decoded_scan(const TiledPlan &t, const uint8_t *codes, int64_t n, int nq, int cap, int R, const uint8_t *qluts,
+                             unsigned *taus, char *ws, size_t ws_stride, size_t countsA_off, size_t listsA_off,
+                             unsigned *flags, const DecodedBatch &db, hipStream_t st);
 
 // 4-bit codes of B bytes that the byte-lane kernels scan faster than the matrix-core kernel
 bool tiled_bytes_pay(int B, int64_t n, int nq);
@@ -41,7 +87,7 @@ bool make_tiled_plan(int64_t n, int m, int nq, bool codes4, bool small, TiledPla
 // ws + q*ws_stride + countsA_off ([GC] u32), lists at + listsA_off ([GC][TILED_LCAP] u64).
 int run_tiled_scan(const TiledPlan &t, const uint8_t *codes, int64_t n, int nq, int cap, int R,
                    unsigned *taus, char *ws, size_t ws_stride, size_t countsA_off, size_t listsA_off,
-                   unsigned *flags, const uint8_t *qluts16, hipStream_t st);
+                   unsigned *flags, const uint8_t *qluts16, const DecodedBatch *decoded, hipStream_t st);
 
 // Pair tables of the batch + the sampled histograms behind the bounds, in the query-tiled way:
 // what seed_u8_kernel does per query.  `sample_codes`: codes of the sample per query.

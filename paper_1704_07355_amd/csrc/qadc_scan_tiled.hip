@@ -66,18 +66,6 @@ __global__ __launch_bounds__(256) void scan_tau_kernel(const char *__restrict__ 
     if (l == 0) taus[q] = t;
 }
 
-// Workgroup id -> (query group, database chunk).  Workgroups are handed to the 8 XCDs in turn,
-// each XCD with an L2 of its own: XCD x = id % 8 takes the chunks congruent to x, and all query
-// groups of a chunk follow each other in its share of the ids, so that the chunk is fetched
-// from HBM once and every XCD gets the same mix of groups, whichever of them are active.
-__device__ __forceinline__ void tiled_group_and_chunk(int ngroups, int &grp, int &chunk)
-{
-    const unsigned id = blockIdx.x;
-    const unsigned slot = id >> 3;
-    grp = (int)(slot % (unsigned)ngroups);
-    chunk = (int)((slot / (unsigned)ngroups) * 8u + (id & 7u));
-}
-
 constexpr int TILED16_GP = 2;                       // code bytes summed in byte lanes
 constexpr unsigned TILED16_CL = 255 / TILED16_GP;   // entries are clamped to this
 
@@ -471,32 +459,37 @@ constexpr int MFMA_SUB = 2;    // 32-code steps per load
 // G: groups of 32 queries per wavefront.  2 for large batches of up to 32 code bytes (the table
 // operands of 64 queries fill 128 registers when B = 16); 1 for B = 32 and for batches that would
 // leave most of a 64-query wavefront empty.
-template <int B, int G>
-__global__ __launch_bounds__(64) void scan_u8_mfma_kernel(
-    const uint8_t *__restrict__ codes, int64_t n, int64_t chunk, int nq, int cap_i,
-    const uint8_t *__restrict__ qluts, const unsigned *__restrict__ taus, char *__restrict__ ws,
-    size_t ws_stride, size_t countsA_off, size_t listsA_off, unsigned *__restrict__ flags)
-{
-    constexpr int WPC = B / 4;   // 32-bit words per code
-    constexpr int QW = 32 * G;   // queries per wavefront
-    constexpr int LC = (G > 2) ? TILED_LCAP / 2 : TILED_LCAP;  // keys kept per query (LDS: 16 KiB of lists)
-    __shared__ unsigned keys[QW][LC];
-    __shared__ unsigned cnt[QW];
+template <int G>
+struct MfmaShared {
+    static constexpr int QW = 32 * G;   // queries per wavefront
+    static constexpr int LC = (G > 2) ? TILED_LCAP / 2 : TILED_LCAP;  // keys kept per query (16 KiB of lists)
+    unsigned keys[QW][LC];
+    unsigned cnt[QW];
     // of nibble c, at offset 8 c of either table: the 8 value bytes (byte 2 (c / 4) is 1) and the
     // position bits.  (Two tables, so that the two reads of a nibble stay an 8-byte and a 4-byte read
     // that land in the operand's registers, instead of one 12-byte read that has to be moved there.)
-    __shared__ v2i_t nibval[16];
-    __shared__ v2i_t nibpos[16];
+    v2i_t nibval[16];
+    v2i_t nibpos[16];
+};
+
+// The codes c0 .. c1 - 1 (not none) for set `set` of queries, reported in region `region`.  ADD: others may have reported there.
+template <int B, int G, bool ADD>
+__device__ __forceinline__ void mfma_scan_codes(MfmaShared<G> &sh, int64_t c0, int64_t c1, int set, int region,
+                                                const uint8_t *__restrict__ codes, int nq, unsigned cap,
+                                                const uint8_t *__restrict__ qluts, const unsigned *__restrict__ taus,
+                                                char *__restrict__ ws, size_t ws_stride, size_t countsA_off,
+                                                size_t listsA_off, unsigned *__restrict__ flags)
+{
+    constexpr int WPC = B / 4;   // 32-bit words per code
+    constexpr int QW = MfmaShared<G>::QW, LC = MfmaShared<G>::LC;
+    auto &keys = sh.keys;
+    auto &cnt = sh.cnt;
+    auto &nibval = sh.nibval;
+    auto &nibpos = sh.nibpos;
 
     const int l = threadIdx.x;
     const int row = l & 31, half = l >> 5;
-    int set, gc;
-    tiled_group_and_chunk((nq + QW - 1) / QW, set, gc);
     const int q0 = set * QW;
-    const unsigned cap = (unsigned)cap_i;
-    const int64_t c0 = (int64_t)gc * chunk;
-    const int64_t c1 = min(n, c0 + chunk);
-    if (c0 >= c1) return;  // uniform
 
     // this lane's table entries: for code byte jb, the 16 entries of table 2jb + half of query
     // q0 + 32g + row (zeros for a query that does not exist: it never passes)
@@ -637,8 +630,17 @@ __global__ __launch_bounds__(64) void scan_u8_mfma_kernel(
         } else if (c) {
             char *base = ws + (size_t)q * ws_stride;
             unsigned *counts = reinterpret_cast<unsigned *>(base + countsA_off);
-            uint64_t *dst = reinterpret_cast<uint64_t *>(base + listsA_off) + (size_t)gc * TILED_LCAP;
-            counts[gc] = c;
+            uint64_t *dst = reinterpret_cast<uint64_t *>(base + listsA_off) + (size_t)region * TILED_LCAP;
+            if constexpr (ADD) {
+                const unsigned before = atomicAdd(&counts[region], c);
+                if (before + c > (unsigned)TILED_LCAP) {
+                    flags[q] = 1u;
+                    continue;
+                }
+                dst += before;
+            } else {
+                counts[region] = c;
+            }
             for (unsigned i = 0; i < c; ++i) {
                 const unsigned key = keys[k][i];
                 dst[i] = ((uint64_t)(key >> 24) << 32) | (uint64_t)(c0 + (key & 0xffffffu));
@@ -648,12 +650,84 @@ __global__ __launch_bounds__(64) void scan_u8_mfma_kernel(
 }
 
 template <int B, int G>
+__global__ __launch_bounds__(64) void scan_u8_mfma_kernel(
+    const uint8_t *__restrict__ codes, int64_t n, int64_t chunk, int nq, int cap_i,
+    const uint8_t *__restrict__ qluts, const unsigned *__restrict__ taus, char *__restrict__ ws,
+    size_t ws_stride, size_t countsA_off, size_t listsA_off, unsigned *__restrict__ flags)
+{
+    __shared__ MfmaShared<G> sh;
+    int set, gc;
+    tiled_group_and_chunk((nq + MfmaShared<G>::QW - 1) / MfmaShared<G>::QW, set, gc);
+    const int64_t c0 = (int64_t)gc * chunk;
+    const int64_t c1 = min(n, c0 + chunk);
+    if (c0 >= c1) return;  // uniform
+    mfma_scan_codes<B, G, false>(sh, c0, c1, set, gc, codes, nq, (unsigned)cap_i, qluts, taus, ws, ws_stride, countsA_off,
+                                 listsA_off, flags);
+}
+
+// The units that scan_u8_decoded_kernel has given up, those of an eighth of a word of its bits by a wavefront.
+template <int B, int G>
+__global__ __launch_bounds__(64) void scan_u8_left_kernel(
+    const uint8_t *__restrict__ codes, DecodedLeft left, int regions, int nq, int cap_i,
+    const uint8_t *__restrict__ qluts, const unsigned *__restrict__ taus, char *__restrict__ ws,
+    size_t ws_stride, size_t countsA_off, size_t listsA_off, unsigned *__restrict__ flags)
+{
+    __shared__ MfmaShared<G> sh;
+    constexpr int QW = MfmaShared<G>::QW;
+    const int sets = (nq + QW - 1) / QW;
+    const int set = (int)(blockIdx.x % (unsigned)sets), word = (int)(blockIdx.x / (unsigned)sets) >> 3,
+              first = (int)(blockIdx.x / (unsigned)sets & 7u) * 4;
+    DecodedPart of = left.parts[0];
+#pragma unroll
+    for (int k = 1; k < DECODED_PARTS; ++k)
+        if (k < left.nparts && word >= left.parts[k].word) of = left.parts[k];
+    for (unsigned units = left.bits[set * QW / left.queries * left.pitch + word] >> first & 15u; units != 0; units &= units - 1) {  // uniform
+        const int unit = 32 * (word - of.word) + first + __ffs((int)units) - 1;
+        const int64_t c0 = of.from + (int64_t)unit * of.unit_codes;
+        mfma_scan_codes<B, G, true>(sh, c0, min(of.to, c0 + of.unit_codes), set, unit % regions, codes, nq, (unsigned)cap_i, qluts,
+                                    taus, ws, ws_stride, countsA_off, listsA_off, flags);
+        __syncthreads();
+    }
+}
+
+// The codes behind the part at which scan_u8_decoded_kernel stopped.
+template <int B, int G>
+__global__ __launch_bounds__(64) void scan_u8_rest_kernel(
+    const uint8_t *__restrict__ codes, DecodedLeft left, int64_t n, int64_t chunk, int nq, int cap_i,
+    const uint8_t *__restrict__ qluts, const unsigned *__restrict__ taus, char *__restrict__ ws,
+    size_t ws_stride, size_t countsA_off, size_t listsA_off, unsigned *__restrict__ flags)
+{
+    __shared__ MfmaShared<G> sh;
+    constexpr int QW = MfmaShared<G>::QW;
+    int set, gc;
+    tiled_group_and_chunk((nq + QW - 1) / QW, set, gc);
+    if (!decoded_stopped(left, left.nparts)) return;  // uniform
+    int64_t rest = n;
+    for (int k = left.nparts - 1; k >= 0; --k)
+        if (left.passed[k] > left.parts[k].limit) rest = left.parts[k].to;
+    const int64_t c0 = max(rest, (int64_t)gc * chunk);
+    const int64_t c1 = min(n, (int64_t)(gc + 1) * chunk);
+    if (c0 >= c1) return;  // uniform
+    mfma_scan_codes<B, G, true>(sh, c0, c1, set, gc, codes, nq, (unsigned)cap_i, qluts, taus, ws, ws_stride, countsA_off,
+                                listsA_off, flags);
+}
+
+template <int B, int G>
 static int launch_tiled_mfma(const TiledPlan &t, const uint8_t *codes, int64_t n, int nq, int cap,
                              const uint8_t *qluts, const unsigned *taus, char *ws, size_t ws_stride,
-                             size_t countsA_off, size_t listsA_off, unsigned *flags, hipStream_t st)
+                             size_t countsA_off, size_t listsA_off, unsigned *flags, const DecodedLeft &left, hipStream_t st)
 {
     const unsigned gc8 = (unsigned)ceil_div(t.GC, 8) * 8u;
     dim3 grid((unsigned)ceil_div(nq, 32 * G) * gc8);
+    if constexpr (B == 8 || B == 16) {
+        if (left.bits) {
+            launch(QADC_PROF_SCAN, (scan_u8_rest_kernel<B, G>), grid, dim3(64), 0, st, codes, left, n, t.chunk, nq, cap, qluts, taus,
+                   ws, ws_stride, countsA_off, listsA_off, flags);
+            launch(QADC_PROF_SCAN, (scan_u8_left_kernel<B, G>), dim3((unsigned)(ceil_div(nq, 32 * G) * left.pitch * 8)), dim3(64), 0, st,
+                   codes, left, t.GC, nq, cap, qluts, taus, ws, ws_stride, countsA_off, listsA_off, flags);
+            return QADC_OK;
+        }
+    }
     launch(QADC_PROF_SCAN, (scan_u8_mfma_kernel<B, G>), grid, dim3(64), 0, st, codes, n, t.chunk, nq, cap, qluts, taus,
            ws, ws_stride, countsA_off, listsA_off, flags);
     return QADC_OK;
@@ -866,14 +940,18 @@ int run_tiled_seed(const TiledPlan &t, const uint8_t *codes, int64_t n, const ui
 
 int run_tiled_scan(const TiledPlan &t, const uint8_t *codes, int64_t n, int nq, int cap, int R,
                    unsigned *taus, char *ws, size_t ws_stride, size_t countsA_off, size_t listsA_off,
-                   unsigned *flags, const uint8_t *qluts16, hipStream_t st)
+                   unsigned *flags, const uint8_t *qluts16, const DecodedBatch *decoded, hipStream_t st)
 {
     launch(QADC_PROF_SEED, scan_tau_kernel, dim3((unsigned)ceil_div(nq, 4)), dim3(256), 0, st,
            (const char *)ws, ws_stride, nq, R, taus);
     // (a last, short sub-batch of a large batch goes to the other kernels, over the same chunks)
     // (its table operands are 16-byte loads: tables at any other alignment go the other way too)
     if (t.mfma && qluts16 && reinterpret_cast<uintptr_t>(qluts16) % 16 == 0 && nq >= mfma_min_q(t.B)) {
-#define QADC_MFMA_ARGS t, codes, n, nq, cap, qluts16, taus, ws, ws_stride, countsA_off, listsA_off, flags, st
+        DecodedLeft left = {};
+        if (decoded && decoded_pays(t.B, n, nq, cap, R, *decoded))
+            left = run_decoded_scan(t, codes, n, nq, cap, R, qluts16, taus, ws, ws_stride, countsA_off, listsA_off, flags, *decoded,
+                                    st);
+#define QADC_MFMA_ARGS t, codes, n, nq, cap, qluts16, taus, ws, ws_stride, countsA_off, listsA_off, flags, left, st
         const bool two = t.B <= 16 && nq >= mfma_min_q2();  // 64 queries per wavefront
         const bool four = mfma_four(t.B, nq);               // 128
         switch (t.B) {

@@ -1110,3 +1110,46 @@ def test_search_of_a_batch_on_the_query_tiled_path(Q, O):
     for iq in range(16):
         wi, wd = oracle_topk(codes, h_ql[iq], 100)
         assert np.array_equal(idx_np(si)[iq], wi) and np.array_equal(sd[iq].cpu().numpy(), wd)
+
+
+@pytest.mark.parametrize("n,d,m,nq,R,nbins,kind", [
+    (1_000_003, 128, 32, 65, 100, 255, "mixture"),   # one query more than half a set; units of 512 codes, a ragged last one
+    (1_300_064, 96, 32, 129, 10, 255, "mixture"),    # three components a table, a set with one query
+    (1_000_000, 64, 16, 256, 1, 255, "mixture"),     # 8-byte codes
+    (2_000_037, 16, 16, 250, 37, 200, "mixture"),    # one component a table
+    (1_100_001, 128, 32, 200, 100, 127, "mixture"),  # coarse steps: the batch goes back to the one-hot products behind a part
+    (1_000_003, 32, 16, 140, 50, 255, "far"),        # queries beyond the centroids' int8 range: units are given up
+    (1_000_100, 64, 32, 128, 100, 255, "equal"),     # every code the same: ties, lists that overflow
+    (1_000_100, 64, 16, 128, 20, 255, "nan")])       # a query of NaN and one of infinities beside ordinary ones
+def test_batch_scan_by_decoded_codes(Q, monkeypatch, n, d, m, nq, R, nbins, kind):
+    """Large batches filtered by int8 products of decoded codes: the one-hot products' results, whatever passes the filter
+    (which is a lower bound in whole numbers; the sums themselves are exact)."""
+    import torch
+    g = torch.Generator(device="cuda:0")
+    g.manual_seed(n + m)
+    means = 48 + 32 * torch.randn((16, d), generator=g, device="cuda:0")
+
+    def vectors(k):
+        label = torch.randint(0, 16, (k,), generator=g, device="cuda:0")
+        return means[label] + 24 * torch.randn((k, d), generator=g, device="cuda:0")
+    learn = vectors(5000)
+    cb = Q.qadc_pq_train(learn, m, 16, torch.arange(16, device="cuda:0"), 5)
+    codes = Q.qadc_pq_encode(cb, vectors(n))
+    queries = vectors(nq)
+    if kind == "far":
+        queries = queries * 40
+    if kind == "equal":
+        codes[:] = codes[0]
+    if kind == "nan":
+        queries[3] = float("nan")
+        queries[5] = float("inf")
+    found = []
+    for knob in ("0", "1"):
+        monkeypatch.setenv("QADC_TILED_DECODED", knob)
+        Q.qadc_profile_enable(True)
+        found.append(Q.qadc_search(cb, queries, codes, R, 200, nbins))
+        _, launches = Q.qadc_profile_read(Q.QADC_PROF_SCAN)
+        Q.qadc_profile_enable(False)
+        found[-1] += (launches,)
+    assert torch.equal(found[0][0], found[1][0]) and torch.equal(found[0][1], found[1][1])
+    assert found[1][2] >= found[0][2] + 4, (found[0][2], found[1][2])  # its parts, and what is left
