@@ -7,6 +7,8 @@
 // centroid by the mean of its sub-vectors (float64 sum in row order, stored as float32);
 // a centroid that owns nothing keeps its value.  No atomics: the result is deterministic.
 
+#include <type_traits>
+
 #include "qadc_nearest.h"
 
 namespace qadc {
@@ -72,12 +74,14 @@ static void launch_train_assign(const float *train, int64_t n, int d, int m, con
 // it is the row-order one.  Where it does (about one mean in 10^5 of a thousand rows), or is not a
 // number, the workgroup walks its rows again in row order.
 // The labels, a column of the label matrix, are read in rounds, and the numbers of the centroid's rows are left in LDS in
-// row order (ballots and running counts, no atomics).  Bound by round trips: labels, then rows eight loads at a time.
+// row order (bits of the labels that match, ballots of the lanes' counts; no atomics).  Bound by the instructions of that search
+// and by round trips: labels, then rows four to twelve loads at a time, as many as the longest slot has.  (A label a lane
+// and instruction, eight loads in flight and halves of the sums' tree: 20,000 rows, m = 16, 16 centroids of 8 dimensions, 17.1
+// us per iteration with the assignment, now 16.4; 20,000, 256 of 8 104 -> 97; 300,001, 256 of 16 1805 -> 1488; 1 M, 16 of 8 502 -> 469.)
 // 44 -> 11.6 us per iteration where no mean is in doubt; 1 M rows, where one iteration in three has one, 2.4 -> 0.5 ms per
 // iteration with the assignment; learning sets of NaN, all rows in order, a tenth slower than before, and 4 to 9 % where most
 // workgroups have one of their 64 means in doubt (300,000 to 600,000 rows, 16 centroids near zero, 120 components and more).
 constexpr int TRAIN_TD = 64;                             // components per workgroup, at most
-constexpr int TRAIN_FL = 8;                              // loads in flight per thread
 constexpr unsigned TRAIN_FEW = 128;                      // rows that are added in order right away
 constexpr int TRAIN_STAGE = 4096;                        // components fetched at a time for the sum in row order
 
@@ -85,33 +89,58 @@ constexpr int TRAIN_STAGE = 4096;                        // components fetched a
 // returns how many.  Every thread of the workgroup calls it; ends with a barrier.
 template <int NT, int PER>
 __device__ __forceinline__ unsigned train_rows(const uint8_t *__restrict__ col, int64_t base, int64_t n, unsigned i,
-                                               uint16_t *rows, unsigned *wcount)
+                                               uint16_t *rows, unsigned *wcount, unsigned *fetched)
 {
+    static_assert(PER % 4 == 0 && PER < 32, "whole words, and counts of five bits");
     const int lane = threadIdx.x & (WAVE - 1), wave = threadIdx.x / WAVE;
-    // wavefront w looks at labels base + w * 64 * PER + k * 64 + lane, k = 0 .. PER - 1
-    const int64_t first = base + (int64_t)wave * (WAVE * PER) + lane;
-    unsigned lab[PER];
+    // a wavefront fetches 64 PER labels, 256 at a time, and a lane looks at PER in a row: bit k of `own` is set where number k is i
+    constexpr int WORDS = PER / 4;
+    const unsigned at0 = threadIdx.x * PER;
+    const int64_t first = base + wave * (WAVE * PER);
+    unsigned *mine_in = fetched + wave * (WAVE * WORDS);
+    unsigned w[WORDS];
 #pragma unroll
-    for (int k = 0; k < PER; ++k) lab[k] = (first + k * WAVE < n) ? col[first + k * WAVE] : 0xffffu;
-    unsigned mine = 0;
+    for (int k = 0; k < WORDS; ++k) {
+        const int64_t at = first + (k * WAVE + lane) * 4;
+        w[k] = (i ^ 1u) * 0x01010101u;  // (a label that is not there is one that is not i)
+        if (at + 4 <= n) __builtin_memcpy(&w[k], col + at, 4);
+    }
+    if (first + WAVE * PER > n) {  // uniform: the last word may be a part of one
 #pragma unroll
-    for (int k = 0; k < PER; ++k) mine += (unsigned)__popcll(__ballot(lab[k] == i));
-    if (lane == 0) wcount[wave] = mine;
+        for (int k = 0; k < WORDS; ++k)
+            for (int u = 0; u < 3; ++u) {
+                const int64_t at = first + (k * WAVE + lane) * 4;
+                if (at + 4 > n && at + u < n) w[k] = (w[k] & ~(255u << (8 * u))) | (unsigned)col[at + u] << (8 * u);
+            }
+    }
+#pragma unroll
+    for (int k = 0; k < WORDS; ++k) mine_in[k * WAVE + lane] = w[k];
+    __builtin_amdgcn_wave_barrier();  // (a wavefront's LDS accesses are in order; the compiler keeps them so)
+    unsigned own = 0;
+#pragma unroll
+    for (int k = 0; k < WORDS; ++k) {
+        const unsigned x = mine_in[lane * WORDS + k] ^ i * 0x01010101u;
+        const unsigned zero = ~(((x & 0x7f7f7f7fu) + 0x7f7f7f7fu) | x | 0x7f7f7f7fu);  // bit 7 of a byte: it was i
+        own |= ((zero >> 7) * 0x10204080u >> 28) << (4 * k);
+    }
+    const unsigned mine = (unsigned)__popc(own);
+    unsigned before = 0, total = 0;  // rows of the lanes before this one, of the wavefront
+#pragma unroll
+    for (int b = 0; b < 5; ++b) {
+        const unsigned long long mask = __ballot(mine >> b & 1u);
+        before += rank_in_mask(mask) << b;
+        total += (unsigned)__popcll(mask) << b;
+    }
+    if (lane == 0) wcount[wave] = total;
     __syncthreads();
-    unsigned at = 0, found = 0;
+    unsigned at = before, found = 0;
 #pragma unroll
     for (int w = 0; w < NT / WAVE; ++w) {
         const unsigned c = wcount[w];
         if (w < wave) at += c;
         found += c;
     }
-#pragma unroll
-    for (int k = 0; k < PER; ++k) {
-        const bool own = lab[k] == i;
-        const unsigned long long mask = __ballot(own);
-        if (own) rows[at + rank_in_mask(mask)] = (uint16_t)(first + k * WAVE - base);
-        at += (unsigned)__popcll(mask);
-    }
+    for (unsigned left = own; left != 0; left &= left - 1) rows[at++] = (uint16_t)(at0 + (unsigned)__ffs((int)left) - 1);
     __syncthreads();
     return found;
 }
@@ -127,6 +156,7 @@ __global__ __launch_bounds__(NT) void train_update_kernel(
     __shared__ union {
         double2 part[NT];                          // (sum, sum of absolute values) of a slot and component
         float stage[2][TRAIN_STAGE];
+        unsigned labels[SEG / 4];                  // of the round, while its rows are looked for
     } sh;
     __shared__ unsigned wcount[NT / WAVE];
     double2 *part = sh.part;
@@ -143,52 +173,73 @@ __global__ __launch_bounds__(NT) void train_update_kernel(
     float *out = cb + ((size_t)j * ksub + i) * dsub + t0;
     double sum = 0.0;
     int64_t cnt = 0;
-    if (n > SEG || (cnt = train_rows<NT, PER>(col, 0, n, (unsigned)i, rows, wcount)) > TRAIN_FEW) {  // uniform
+    if (n > SEG || (cnt = train_rows<NT, PER>(col, 0, n, (unsigned)i, rows, wcount, sh.labels)) > TRAIN_FEW) {  // uniform
         double mag = 0.0;
         int64_t chain = 0;                         // additions of this slot (the first, with the most, decides below)
         const int slots = NT / td;                 // rows side by side
         const int slot = tid / td, t = tid - slot * td;
         for (int64_t base = 0; base < n; base += SEG) {
-            const unsigned found = n <= SEG ? (unsigned)cnt : train_rows<NT, PER>(col, base, n, (unsigned)i, rows, wcount);
+            const unsigned found = n <= SEG ? (unsigned)cnt : train_rows<NT, PER>(col, base, n, (unsigned)i, rows, wcount, sh.labels);
             if (n > SEG) cnt += found;
             if (slot < slots) {
-                for (unsigned r0 = (unsigned)slot; r0 < found; r0 += TRAIN_FL * (unsigned)slots) {
-                    chain += TRAIN_FL;
-                    float v[TRAIN_FL];
+                const float *from = src + base * d + t;
+                // U of the slot's rows from row r0 on, their loads in flight together
+                auto add = [&](auto many, unsigned r0) {
+                    constexpr int U = decltype(many)::value;
+                    float v[U];
 #pragma unroll
-                    for (int u = 0; u < TRAIN_FL; ++u) {
-                        const unsigned r = r0 + u * (unsigned)slots;
-                        v[u] = src[(base + rows[min(r, found - 1)]) * d + t];
-                    }
+                    for (int u = 0; u < U; ++u) v[u] = from[(int64_t)rows[min(r0 + u * (unsigned)slots, found - 1)] * d];
 #pragma unroll
-                    for (int u = 0; u < TRAIN_FL; ++u) {
-                        const double x = r0 + u * (unsigned)slots < found ? (double)v[u] : 0.0;
+                    for (int u = 0; u < U; ++u) {
+                        const double x = (double)(r0 + u * (unsigned)slots < found ? v[u] : 0.0f);
                         sum += x;
                         mag += fabs(x);
                     }
-                }
+                    chain += U;
+                };
+                const unsigned most = (found + (unsigned)slots - 1) / (unsigned)slots;  // a slot's rows
+                unsigned r = 0;
+                for (; r + 8 < most; r += 12) add(std::integral_constant<int, 12>(), slot + r * slots);
+                if (r + 4 < most) add(std::integral_constant<int, 8>(), slot + r * slots);
+                else if (r < most) add(std::integral_constant<int, 4>(), slot + r * slots);
             }
             __syncthreads();                             // `rows` and `wcount` are written again in the next round
         }
-        part[tid] = make_double2(sum, mag);
+        int parts = slots;
+        if (td < WAVE && (td & (td - 1)) == 0) {         // uniform: the lanes of a wavefront that hold a component, by shuffles
+            for (int k = td; k < WAVE; k *= 2) {
+                sum += __shfl_xor(sum, k);
+                mag += __shfl_xor(mag, k);
+            }
+            parts = NT / WAVE;
+            if ((tid & (WAVE - 1)) < td) part[tid / WAVE * td + t] = make_double2(sum, mag);
+        } else {
+            part[tid] = make_double2(sum, mag);
+        }
         __syncthreads();
-        // halves of the slots, then halves of those
-        for (int have = slots; have > 1;) {              // uniform
-            const int half = (have + 1) / 2;
-            if (slot < have - half) {
-                const double2 o = part[tid + half * td];
-                part[tid] = make_double2(part[tid].x + o.x, part[tid].y + o.y);
+        // an eighth of the slots, then an eighth of those
+        for (int have = parts; have > 1;) {              // uniform
+            const int next = (have + 7) / 8;
+            if (slot < next) {
+                double2 all = part[tid];
+#pragma unroll
+                for (int u = 1; u < 8; ++u) {
+                    const double2 o = part[min(slot + u * next, have - 1) * td + t];
+                    if (slot + u * next < have) all = make_double2(all.x + o.x, all.y + o.y);
+                }
+                part[tid] = all;
             }
             __syncthreads();
-            have = half;
+            have = next;
         }
         bool sure = true;
         float mean = 0.0f;
         if (tid < td) {
             const double s = part[tid].x, c = (double)cnt;
-            // row order: cnt additions; here: those of the longest chain and at most 10 of the tree.  (1.01: the rounding of
+            // row order: cnt additions; here: those of the longest chain and at most 21 of the tree (NT / td slots, or 6 and
+            // 14 of the shuffles' 16).  (1.01: the rounding of
             // this line and of the two divisions below is far under a hundredth of it)
-            const double eps = part[tid].y * (c + (double)chain + 10.0) * (1.01 * 0x1p-53);
+            const double eps = part[tid].y * (c + (double)chain + 28.0) * (1.01 * 0x1p-53);
             mean = (float)(s / c);
             sure = __float_as_uint((float)((s - eps) / c)) == __float_as_uint((float)((s + eps) / c)) &&
                    __builtin_isfinite(mean);
@@ -204,7 +255,7 @@ __global__ __launch_bounds__(NT) void train_update_kernel(
     const int per_stage = TRAIN_STAGE / td;              // rows
     for (int64_t base = 0; base < n; base += SEG) {
         const int found = n <= SEG ? (int)cnt      // `rows` still holds them
-                                         : (int)train_rows<NT, PER>(col, base, n, (unsigned)i, rows, wcount);
+                                         : (int)train_rows<NT, PER>(col, base, n, (unsigned)i, rows, wcount, sh.labels);
         const int stages = (found + per_stage - 1) / per_stage;
         for (int s = 0; s <= stages; ++s) {              // uniform
             if (s < stages) {

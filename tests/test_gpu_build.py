@@ -587,3 +587,37 @@ def test_ivf_assign_is_not_slowed_by_a_few_centroids(Q, d, K):
         change(c)
         us = gpu_us(lambda: Q.qadc_ivf_assign(c, x), reps=5)
         assert us < limit * usual, (us, usual)
+
+
+@pytest.mark.parametrize("n", [1, 3, 129, 131, 255, 2049, 4097, 8191, 8194, 20479, 20482, 21001, 40963])
+@pytest.mark.parametrize("dsub", [1, 3, 8, 64])
+def test_pq_train_finds_every_row_of_a_centroid(Q, n, dsub):
+    """Whole numbers (every sum is exact in float64): the means are those of the rows, at the ends of a word of labels, of a
+    wavefront's share and of a round; columns of labels that do not start on a word; one centroid that owns nearly all rows."""
+    rng = np.random.default_rng(n * 100 + dsub)
+    m = 3
+    own = np.where(rng.random((n, m)) < 0.8, 5, rng.integers(0, 16, (n, m)))
+    own[0] = 5
+    own[-1] = 15
+    # component 0 says which centroid; the others are noise of whole numbers, smaller than the distance of two centroids
+    x = rng.integers(-3, 4, (n, m, dsub)).astype(np.float32)
+    x[:, :, 0] += 1024.0 * own
+    for c in range(min(n, 16)):  # rows that name every centroid, where there are as many
+        own[c] = (5 + c) % 16 if n >= 16 else own[c]
+    if n >= 16:
+        x[:16, :, 0] = 1024.0 * own[:16]
+    rows = np.array([min(c, n - 1) for c in range(16)], dtype=np.int64)
+    cb0 = x[rows]                                            # [16][m][dsub]
+    want = np.empty((m, 16, dsub), dtype=np.float32)
+    for j in range(m):
+        dist = ((x[:, j, None, :].astype(np.float64) - cb0[None, :, j, :]) ** 2).sum(-1) if n <= 4097 else None
+        if dist is None:
+            order = np.argsort(cb0[:, j, 0], kind="stable")  # one centroid per value of component 0 (n >= 16)
+            label = order[np.rint(x[:, j, 0] / 1024).astype(int)]
+        else:
+            label = dist.argmin(1)
+        for i in range(16):
+            r = x[label == i, j].astype(np.float64)
+            want[j, i] = (r.sum(0) / len(r)).astype(np.float32) if len(r) else cb0[i, j]
+    got = Q.qadc_pq_train(to_gpu(x.reshape(n, m * dsub)), m, 16, to_gpu(rows), 1).cpu().numpy()
+    assert np.array_equal(got.reshape(m, 16, dsub), want)
