@@ -670,7 +670,8 @@ static void launch_scan_u8(const ScanPlan &p, const uint8_t *codes, int64_t n, c
 }
 
 static int dispatch_seed_u8(const ScanPlan &p, const uint8_t *codes, int64_t n,
-                            const uint8_t *qluts, int nq, int cap, int R, char *ws, hipStream_t st)
+                            const uint8_t *qluts, int nq, int cap, int R, char *ws, hipStream_t st,
+                            const DecodedBatch *decoded = nullptr)
 {
     // batches that the query-tiled kernels scan are sampled in the query-tiled way too
     // (not 32-byte codes: their tables for eight queries fill the LDS and are interleaved by every workgroup;
@@ -680,6 +681,10 @@ static int dispatch_seed_u8(const ScanPlan &p, const uint8_t *codes, int64_t n,
         // (at most 512 sample tiles unless QADC_SEED_WGS says otherwise: N = 1e8, m = 32, 256 queries: 1024
         // tiles 0.42 ms of sampling, 512 tiles 0.22 ms and 0.07 ms more in the scan, 256 tiles 0.12 and 0.21)
         int tiles = knobs().seed_wgs > 0 ? p.seed_wgs : std::min(p.seed_wgs, 512);
+        // Where the decoded codes are scanned, in parts, the first part finds a better bound than the sample's at a third of
+        // its price (512 / 256 / 192 / 128 tiles, us per call: 100 M x 256, m = 32, d = 128, R = 100 4095 / 4014 / 3977, and
+        // beyond it too many pairs pass; 50 M x 200, R = 10 1881 / 1802 / 1790 / 1761; 73 M x 256, m = 16, d = 64 1890 / 1769 / 1734).
+        if (knobs().seed_wgs <= 0 && scans_decoded(p.t, n, nq, cap, R, p.wide ? nullptr : qluts, decoded)) tiles = std::min(tiles, 192);
         // Every query is sampled, and a fourth of a database of a few million codes took as long as its scan: no more than 4e8
         // byte lookups in all, but a sixteenth of the codes, and enough for bounds that let some 2000 keys of a query pass.
         // (us per call with up to a fourth / this / a sixteenth: 250 queries over 1 M m = 32, R = 10 156 / 131 / 120; 100 over 3 M
@@ -887,7 +892,7 @@ int search_u8(const float *codebooks, int d, int m, const float *queries, int nq
             // kernel, then the sampling kernel (large databases) or a self-seeding scan
             search_tables(codebooks, d, m, yq, nb, codes, n_init, R, nbins, qmin_mode, qluts, ql_out, batch ? deltas : nullptr, st);
             if (p.seed_wgs > 0) {
-                const int rc = dispatch_seed_u8(p, codes, n, qluts, nb, nbins, R, ws, st);
+                const int rc = dispatch_seed_u8(p, codes, n, qluts, nb, nbins, R, ws, st, batch ? &db : nullptr);
                 if (rc != QADC_OK) return rc;
             }
         }

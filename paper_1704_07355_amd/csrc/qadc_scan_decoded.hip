@@ -4,8 +4,8 @@
 //
 // Bound: the matrix units, at the clock that int8 products of arbitrary operands are given, with the lookups of decoded
 // components and the tests of results issued beside them.  100 M codes of 16 bytes x 256 queries, a mixture's vectors: the whole
-// search 5.33 ms with scan_u8_mfma_kernel, 4.00 ms here (4 parts; 2e-3 of the pairs pass the first one, 4e-4 the last);
-// 73 M codes of 8 bytes x 256 queries 2.23 -> 1.87 ms.
+// search 5.33 ms with scan_u8_mfma_kernel, 3.92 ms here (4 parts; 4e-3 of the pairs pass the first one, 4e-4 the last);
+// 73 M codes of 8 bytes x 256 queries 2.26 -> 1.73 ms.
 
 #include <algorithm>
 #include <type_traits>
@@ -401,24 +401,26 @@ constexpr int DECODED_G = 4;  // groups of 32 queries per wavefront
 
 // When it pays: matrix products a pair are half of scan_u8_mfma_kernel's, but every pair that passes costs some 30 cycles, and how
 // many pass depends on how many sums the last bound lets in (R of n) and on what the quantizer's steps lose.  Measured against
-// scan_u8_mfma_kernel (the whole search, us; 255 bins unless said, 200..1000 initial codes, vectors of a mixture of 64):
-//   16-byte codes, 128 dimensions    100 M x 256, R 100: 5334 -> 3992     100 M x 200, R 100: 5154 -> 4526
-//                                     50 M x 200, R 10:  2512 -> 1872      36 M x 250, R 30:  1976 -> 1742
+// scan_u8_mfma_kernel (the whole search, us; 255 bins unless said, 100..1000 initial codes, vectors of a mixture of 64; what is beyond the line
+// with three times the sample):
+//   16-byte codes, 128 dimensions    100 M x 256, R 100: 5338 -> 3939     100 M x 200, R 100: 5221 -> 4426
+//                                     50 M x 200, R 10:  2513 -> 1745      36 M x 250, R 30:  1972 -> 1624
 //     beyond the line                 50 M x 128, R 100: 1406 -> 1384      36 M x 256, R 100: 2015 -> 2073
 //                                     20 M x 256, R 100: 1187 -> 1309      36 M x 256, R 100, 127 bins: 2122 -> 3951
-//   8-byte codes, 64 dimensions       73 M x 256, R 100: 2232 -> 1866      36 M x 100, R 70:   719 -> 628
+//   8-byte codes, 64 dimensions       73 M x 256, R 100: 2262 -> 1729      36 M x 100, R 50:   704 -> 594
 //     beyond the line                100 M x 200, R 200: 3805 -> 3985      73 M x 256, R 100, 127 bins: 2287 -> 2411
 // (Fewer than 64 queries in the last set of 128 are scanned as 128, and the parts' launches cost some 60 us: n.)
 // Sizes don't tell what data and quantizers do, so each part counts the pairs that passed, and behind a part with more than
-// DECODED_PASS / 4096 of all its pairs the batch goes back to the one-hot products: within the line that has cost 1 % at 100 M
-// (5420 -> 5440) and up to 4 % at 36 M.  For the 8-byte codes a product is cheaper beside the check: their share is smaller.
-constexpr int DECODED_PASS[2] = {3, 13};          // 8- and 16-byte codes
+// DECODED_PASS / 4096 of all its pairs the batch goes back to the one-hot products: within the line that has cost 1 % (100 M x 256,
+// 96 dimensions, 100 initial codes: 5349 -> 5411; let on, 2739 -> 2851 for 128 queries).  For the 8-byte codes a product is
+// cheaper beside the check: their share is smaller.
+constexpr int DECODED_PASS[2][2] = {{6, 4}, {21, 15}};  // 8- and 16-byte codes: the first part, whose bound is the sample's, the others
 constexpr int64_t DECODED_MIN_N = 32000000;
 constexpr int64_t DECODED_N_PER_R[2] = {700000, 1000000};
 constexpr int DECODED_MIN_BINS = 224;
 constexpr int DECODED_MIN_LAST = 64;              // queries in the last set of 128
 
-// The scan in parts, the bound tightened behind each but the last (the first one's is a sample's: R of some 1e5 codes, and the
+// The scan in parts, the bound tightened behind each but the last (the first one's is a sample's: R of some 8e5 codes, and the
 // share that passes falls 4 to 6 times with it; 1/16, 1/3 and the rest took as long, and cost 5 % more where the batch goes back).
 // Units: four for every wavefront that the chip holds at once, of 512 to 8192 codes.
 static int decoded_parts(int B, int64_t n, int nq, int sets, DecodedPart (&parts)[DECODED_PARTS])
@@ -432,7 +434,7 @@ static int decoded_parts(int B, int64_t n, int nq, int sets, DecodedPart (&parts
         if (to <= from) continue;
         const int64_t unit = std::min<int64_t>(8192, std::max<int64_t>(512, ceil_div(ceil_div(to - from, want), 64) * 64));
         parts[k] = {from, to, (int)unit, (int)ceil_div(to - from, unit), word,
-                    (unsigned)std::min<int64_t>((to - from) / 64 * nq / 64 * DECODED_PASS[B / 16], UINT32_MAX / 2)};
+                    (unsigned)std::min<int64_t>((to - from) / 64 * nq / 64 * DECODED_PASS[B / 16][k > 0], UINT32_MAX / 2)};
         word += (int)ceil_div(parts[k].units, 32);
         from = to;
         ++k;

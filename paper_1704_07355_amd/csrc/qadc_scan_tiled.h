@@ -46,6 +46,9 @@ struct DecodedBatch {
     size_t room_bytes;
 };
 bool decoded_pays(int B, int64_t n, int nq, int cap, int R, const DecodedBatch &db);
+// Does run_tiled_scan take that route?
+struct TiledPlan;
+bool scans_decoded(const TiledPlan &t, int64_t n, int nq, int cap, int R, const uint8_t *qluts16, const DecodedBatch *decoded);
 // A part of its scan: units of unit_codes codes from code `from` up to `to`; `word`: where their bits start.
 constexpr int DECODED_PARTS = 4;
 struct DecodedPart {

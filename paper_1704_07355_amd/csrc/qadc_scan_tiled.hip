@@ -938,17 +938,27 @@ int run_tiled_seed(const TiledPlan &t, const uint8_t *codes, int64_t n, const ui
     }
 }
 
+// (a last, short sub-batch of a large batch goes to the other kernels, over the same chunks)
+// (its table operands are 16-byte loads: tables at any other alignment go the other way too)
+static bool scans_by_mfma(const TiledPlan &t, int nq, const uint8_t *qluts16)
+{
+    return t.mfma && qluts16 && reinterpret_cast<uintptr_t>(qluts16) % 16 == 0 && nq >= mfma_min_q(t.B);
+}
+
+bool scans_decoded(const TiledPlan &t, int64_t n, int nq, int cap, int R, const uint8_t *qluts16, const DecodedBatch *decoded)
+{
+    return decoded && scans_by_mfma(t, nq, qluts16) && decoded_pays(t.B, n, nq, cap, R, *decoded);
+}
+
 int run_tiled_scan(const TiledPlan &t, const uint8_t *codes, int64_t n, int nq, int cap, int R,
                    unsigned *taus, char *ws, size_t ws_stride, size_t countsA_off, size_t listsA_off,
                    unsigned *flags, const uint8_t *qluts16, const DecodedBatch *decoded, hipStream_t st)
 {
     launch(QADC_PROF_SEED, scan_tau_kernel, dim3((unsigned)ceil_div(nq, 4)), dim3(256), 0, st,
            (const char *)ws, ws_stride, nq, R, taus);
-    // (a last, short sub-batch of a large batch goes to the other kernels, over the same chunks)
-    // (its table operands are 16-byte loads: tables at any other alignment go the other way too)
-    if (t.mfma && qluts16 && reinterpret_cast<uintptr_t>(qluts16) % 16 == 0 && nq >= mfma_min_q(t.B)) {
+    if (scans_by_mfma(t, nq, qluts16)) {
         DecodedLeft left = {};
-        if (decoded && decoded_pays(t.B, n, nq, cap, R, *decoded))
+        if (scans_decoded(t, n, nq, cap, R, qluts16, decoded))
             left = run_decoded_scan(t, codes, n, nq, cap, R, qluts16, taus, ws, ws_stride, countsA_off, listsA_off, flags, *decoded,
                                     st);
 #define QADC_MFMA_ARGS t, codes, n, nq, cap, qluts16, taus, ws, ws_stride, countsA_off, listsA_off, flags, left, st
