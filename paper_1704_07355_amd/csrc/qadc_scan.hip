@@ -684,7 +684,9 @@ static int dispatch_seed_u8(const ScanPlan &p, const uint8_t *codes, int64_t n,
         // Where the decoded codes are scanned, in parts, the first part finds a better bound than the sample's at a third of
         // its price (512 / 256 / 192 / 128 tiles, us per call: 100 M x 256, m = 32, d = 128, R = 100 4095 / 4014 / 3977, and
         // beyond it too many pairs pass; 50 M x 200, R = 10 1881 / 1802 / 1790 / 1761; 73 M x 256, m = 16, d = 64 1890 / 1769 / 1734).
-        if (knobs().seed_wgs <= 0 && scans_decoded(p.t, n, nq, cap, R, p.wide ? nullptr : qluts, decoded)) tiles = std::min(tiles, 192);
+        // (8000 codes per key of R: a part's units have room for 128 pairs within the bound.)
+        if (knobs().seed_wgs <= 0 && scans_decoded(p.t, n, nq, cap, R, p.wide ? nullptr : qluts, decoded))
+            tiles = std::min(tiles, std::max(192, (int)ceil_div(8000ll * R, 1024 * cpt)));
         // Every query is sampled, and a fourth of a database of a few million codes took as long as its scan: no more than 4e8
         // byte lookups in all, but a sixteenth of the codes, and enough for bounds that let some 2000 keys of a query pass.
         // (us per call with up to a fourth / this / a sixteenth: 250 queries over 1 M m = 32, R = 10 156 / 131 / 120; 100 over 3 M

@@ -4,8 +4,9 @@
 //
 // Bound: the matrix units, at the clock that int8 products of arbitrary operands are given, with the lookups of decoded
 // components and the tests of results issued beside them.  100 M codes of 16 bytes x 256 queries, a mixture's vectors: the whole
-// search 5.33 ms with scan_u8_mfma_kernel, 3.92 ms here (4 parts; 4e-3 of the pairs pass the first one, 4e-4 the last);
-// 73 M codes of 8 bytes x 256 queries 2.26 -> 1.73 ms.
+// search 5.31 ms with scan_u8_mfma_kernel, 3.96 ms here (4 parts; 4e-3 of the pairs pass the first one, 4e-4 the last);
+// 73 M codes of 8 bytes x 256 queries 2.20 -> 1.55 ms.  A wavefront has 307 cycles of a SIMD for a block (two a SIMD: 214 registers;
+// three for 8-byte codes: 156), 33 vector, 4 matrix, 8 LDS and 7 scalar instructions: issue, not the products (36 % busy).
 
 #include <algorithm>
 #include <type_traits>
@@ -64,19 +65,19 @@ __global__ __launch_bounds__(32 * B) void decoded_prepare_kernel(const float *__
 // What remains is reported when the unit is done: lists per (query, region) as scan_u8_mfma_kernel's, region = unit modulo the
 // number of regions.  A unit of which more pairs pass than pay, or more at a time than LDS has room for, is given up: a bit in
 // `left`, and scan_u8_left_kernel, launched after this one, does it.
-constexpr int DECODED_NW = 8;      // wavefronts per workgroup
-constexpr int DECODED_LANES = 64;  // lanes' results that wait (and 64 more of one block)
+constexpr int decoded_nw(int B) { return B == 8 ? 12 : 8; }      // wavefronts per workgroup
+constexpr int decoded_lanes(int B) { return B == 8 ? 48 : 64; }  // lanes' results that wait (and 64 more of one block)
 constexpr int DECODED_STAGE = 128; // pairs within the bound that a unit can have (and 64 more)
 constexpr unsigned DECODED_ALLOW = 1024;  // pairs of a unit that may pass, and as many more as the pairs seen
 constexpr int DECODED_SHARE = 8;          // shifted down by this
 
 template <int B, int G>
 struct DecodedShared {
-    static constexpr int QW = 32 * G, NW = DECODED_NW;
+    static constexpr int QW = 32 * G, NW = decoded_nw(B), LANES = decoded_lanes(B);
     __attribute__((aligned(16))) int tab[B * 32];  // (at the front: the lookups' offsets are then part of their instructions)
     __attribute__((aligned(16))) int norm[NW][2][32];
-    __attribute__((aligned(16))) v4i_t results[NW][DECODED_LANES + 64][4];
-    unsigned place[NW][DECODED_LANES + 64];        // their query << 24 | first code, of the unit
+    __attribute__((aligned(16))) v4i_t results[NW][LANES + 64][4];
+    unsigned place[NW][LANES + 64];        // their query << 24 | first code, of the unit
     unsigned pairs[NW][128];                       // that passed: query << 24 | code of the unit
     uint2 found[NW][DECODED_STAGE + 64];           // that are within the bound, with their sum
     int thr[QW];                                   // a result passes when it is below
@@ -85,7 +86,7 @@ struct DecodedShared {
 };
 
 template <int B, int G>
-__global__ __launch_bounds__(64 * DECODED_NW) void scan_u8_decoded_kernel(
+__global__ __launch_bounds__(64 * decoded_nw(B)) void scan_u8_decoded_kernel(
     const uint8_t *__restrict__ codes, DecodedLeft all, int which, int regions, int nq, int cap_i,
     const uint8_t *__restrict__ qluts, const int *__restrict__ tables, const int *__restrict__ operands,
     const int2 *__restrict__ scales, const unsigned *__restrict__ taus, char *__restrict__ ws, size_t ws_stride,
@@ -234,7 +235,7 @@ __global__ __launch_bounds__(64 * DECODED_NW) void scan_u8_decoded_kernel(
                 for (int u = 0; u < 4; ++u) results[at][u] = v4i_t{r[4 * u], r[4 * u + 1], r[4 * u + 2], r[4 * u + 3]};
                 place[at] = own + (rel + ((unsigned)g << 29));
             }
-            waiting = min(waiting + (unsigned)__popcll(all), (unsigned)DECODED_LANES);
+            waiting = min(waiting + (unsigned)__popcll(all), (unsigned)S::LANES);
         };
         auto norms = [&](int buf) {
             v16i_t r;
@@ -305,14 +306,14 @@ __global__ __launch_bounds__(64 * DECODED_NW) void scan_u8_decoded_kernel(
             spread();
             step(std::integral_constant<int, 1>(), w0, rel + 32u);
             if (waiting >= 16u) {
-                give_up = waiting >= (unsigned)DECODED_LANES || seen > DECODED_ALLOW + (rel >> DECODED_SHARE) * (unsigned)QW;
+                give_up = waiting >= (unsigned)S::LANES || seen > DECODED_ALLOW + (rel >> DECODED_SHARE) * (unsigned)QW;
                 if (give_up) break;
                 drain();
             }
         }
         if (!give_up) {
             test(acc[1], G - 1, (len - 1u) / 64u * 64u + 32u);
-            give_up = waiting >= (unsigned)DECODED_LANES;
+            give_up = waiting >= (unsigned)S::LANES;
             if (!give_up) {
                 drain();
                 if (npairs) check(npairs);
@@ -403,11 +404,11 @@ constexpr int DECODED_G = 4;  // groups of 32 queries per wavefront
 // many pass depends on how many sums the last bound lets in (R of n) and on what the quantizer's steps lose.  Measured against
 // scan_u8_mfma_kernel (the whole search, us; 255 bins unless said, 100..1000 initial codes, vectors of a mixture of 64; what is beyond the line
 // with three times the sample):
-//   16-byte codes, 128 dimensions    100 M x 256, R 100: 5338 -> 3939     100 M x 200, R 100: 5221 -> 4426
-//                                     50 M x 200, R 10:  2513 -> 1745      36 M x 250, R 30:  1972 -> 1624
+//   16-byte codes, 128 dimensions    100 M x 256, R 100: 5315 -> 3955      40 M x 384, R 40:  3977 -> 2415
+//                                     50 M x 200, R 10:  2447 -> 1702      36 M x 250, R 30:  1929 -> 1562
 //     beyond the line                 50 M x 128, R 100: 1406 -> 1384      36 M x 256, R 100: 2015 -> 2073
 //                                     20 M x 256, R 100: 1187 -> 1309      36 M x 256, R 100, 127 bins: 2122 -> 3951
-//   8-byte codes, 64 dimensions       73 M x 256, R 100: 2262 -> 1729      36 M x 100, R 50:   704 -> 594
+//   8-byte codes, 64 dimensions       73 M x 256, R 100: 2200 -> 1545      36 M x 100, R 50:   695 -> 504
 //     beyond the line                100 M x 200, R 200: 3805 -> 3985      73 M x 256, R 100, 127 bins: 2287 -> 2411
 // (Fewer than 64 queries in the last set of 128 are scanned as 128, and the parts' launches cost some 60 us: n.)
 // Sizes don't tell what data and quantizers do, so each part counts the pairs that passed, and behind a part with more than
@@ -422,17 +423,23 @@ constexpr int DECODED_MIN_LAST = 64;              // queries in the last set of 
 
 // The scan in parts, the bound tightened behind each but the last (the first one's is a sample's: R of some 8e5 codes, and the
 // share that passes falls 4 to 6 times with it; 1/16, 1/3 and the rest took as long, and cost 5 % more where the batch goes back).
-// Units: four for every wavefront that the chip holds at once, of 512 to 8192 codes.
+// Units: as few for every wavefront that the chip holds at once as leave them at 8192 codes (2048 in the first two parts, whose
+// bounds let more in), and the same number for each: four and what is left over, 73 M x 256, m = 16 1.73 -> 1.55 ms, 40 M x 384,
+// m = 32 3.69 -> 2.42 (there with more workgroups than the chip holds).  At least 512 codes.
+// Workgroups of a set: a CU holds one, an XCD's share is whole.
+static int decoded_wgs(int sets) { return std::max(256 / (8 * sets), 1) * 8; }
+
 static int decoded_parts(int B, int64_t n, int nq, int sets, DecodedPart (&parts)[DECODED_PARTS])
 {
     const int64_t ends[DECODED_PARTS] = {n / 64, n / 12, n / 3, n};
-    const int64_t want = 4 * std::max<int64_t>(ceil_div(2048, sets), 1);
+    const int64_t waves = (int64_t)decoded_wgs(sets) * decoded_nw(B);  // of a set, that the chip holds at once
     int64_t from = 0;
     int k = 0, word = 0;
     for (int64_t e : ends) {
         const int64_t to = e == n ? n : e / 64 * 64;
         if (to <= from) continue;
-        const int64_t unit = std::min<int64_t>(8192, std::max<int64_t>(512, ceil_div(ceil_div(to - from, want), 64) * 64));
+        const int64_t rounds = ceil_div(to - from, waves * (k < 2 ? 2048 : 8192));
+        const int64_t unit = std::max<int64_t>(512, ceil_div(ceil_div(to - from, rounds * waves), 64) * 64);
         parts[k] = {from, to, (int)unit, (int)ceil_div(to - from, unit), word,
                     (unsigned)std::min<int64_t>((to - from) / 64 * nq / 64 * DECODED_PASS[B / 16][k > 0], UINT32_MAX / 2)};
         word += (int)ceil_div(parts[k].units, 32);
@@ -485,9 +492,9 @@ static DecodedLeft run_decoded(const TiledPlan &t, const uint8_t *codes, int64_t
         if (k > 0)
             launch(QADC_PROF_SEED, decoded_refine_kernel, dim3((unsigned)nq), dim3(256), 0, st, ws, ws_stride, countsA_off, listsA_off,
                    t.GC, R, taus, (const unsigned *)flags, all, k - 1);
-        const int64_t wgs = std::min<int64_t>(ceil_div(ceil_div(p.units, DECODED_NW), 8) * 8, ceil_div(256, 8 * sets) * 8);
+        const int64_t wgs = std::min<int64_t>(ceil_div(ceil_div(p.units, decoded_nw(B)), 8) * 8, decoded_wgs(sets));
         const dim3 grid((unsigned)(wgs * sets));
-        launch(QADC_PROF_SCAN, (scan_u8_decoded_kernel<B, G>), grid, dim3(64 * DECODED_NW), 0, st, codes, all, k, t.GC, nq, cap, qluts,
+        launch(QADC_PROF_SCAN, (scan_u8_decoded_kernel<B, G>), grid, dim3(64 * decoded_nw(B)), 0, st, codes, all, k, t.GC, nq, cap, qluts,
                (const int *)tables, (const int *)operands, (const int2 *)scales, (const unsigned *)taus, ws, ws_stride, countsA_off,
                listsA_off, flags, left, passed);
     }

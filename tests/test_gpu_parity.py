@@ -1117,6 +1117,7 @@ def test_search_of_a_batch_on_the_query_tiled_path(Q, O):
     (1_300_064, 96, 32, 129, 10, 255, "mixture"),    # three components a table, a set with one query
     (1_000_000, 64, 16, 256, 1, 255, "mixture"),     # 8-byte codes
     (2_000_037, 16, 16, 250, 37, 200, "mixture"),    # one component a table
+    (1_000_064, 64, 16, 330, 30, 255, "mixture"),    # three sets of queries: fewer workgroups than an XCD holds for each
     (1_100_001, 128, 32, 200, 100, 127, "mixture"),  # coarse steps: the batch goes back to the one-hot products behind a part
     (1_000_003, 32, 16, 140, 50, 255, "far"),        # queries beyond the centroids' int8 range: units are given up
     (1_000_100, 64, 32, 128, 100, 255, "equal"),     # every code the same: ties, lists that overflow
