@@ -372,6 +372,8 @@ __device__ __forceinline__ void filter_tile(FilterTile<NT, KS, NB, F> &sh, const
 #pragma unroll
         for (int m = 8; m < 8 * PS; m <<= 1) s2 += __shfl_xor(s2, m);
         const bool in = c0 + crow < K;
+        // (A cell past the last has the last one's components, and 2 x'.c' may be larger than AF_NONE: infinity stays above.)
+        const float none = __builtin_inff();
         if (in) cmax = fmaxf(cmax, s2);  // (NaN: left out)
         if constexpr (HALF) {
             // A stray centroid, |c'|^2 > 2^31, may not fit binary16: its score is 0.29 |c'|^2, no more than |c'|^2 - 2 x'.c' of
@@ -384,9 +386,9 @@ __device__ __forceinline__ void filter_tile(FilterTile<NT, KS, NB, F> &sh, const
                     for (int h = 0; h < 2; ++h)
                         tile[buf][crow >> 5][part + PS * it][0][h * 32 + (crow & 31)] = stray ? bits16x8{} : conv[it][h];
             const float own = stray ? 0.29f * s2 : __builtin_fmaf(-eps_c, s2, s2) - HALF_TINY * D;
-            nrm[buf][crow] = in ? own : AF_NONE;  // (its threads all write the same: a branch would part the block of code)
+            nrm[buf][crow] = in ? own : none;  // (its threads all write the same: a branch would part the block of code)
         } else {
-            nrm[buf][crow] = in ? s2 * (1.0f - eps_c) : AF_NONE;
+            nrm[buf][crow] = in ? s2 * (1.0f - eps_c) : none;
         }
     };
 

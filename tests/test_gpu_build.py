@@ -570,6 +570,35 @@ def test_multi_index_assign_of_crowded_cells(Q, K, dh, n):
     assert np.array_equal(got, want)
 
 
+# the last tile of the filter has one to 24 places past the last cell, or 31; aligned rows and others; split factors from the start,
+# and behind binary16 ones (50,000 vectors, most of them with more rivals than a lane remembers)
+@pytest.mark.parametrize("d,K,n", [(128, 127, 600), (128, 300, 600), (32, 488, 600), (64, 255, 600), (256, 506, 300),
+                                   (100, 127, 600), (200, 500, 300), (17, 225, 600), (3, 95, 600), (128, 300, 50_000),
+                                   (64, 511, 50_000)])
+@pytest.mark.parametrize("last", [1e34, 1e36, 1e37, -1e38, 3e38])
+def test_ivf_assign_with_a_last_centroid_far_out(Q, d, K, n, last):
+    """Nothing of the last centroid's shows in the places past it, whose scores are no candidates: the ordinary cells win."""
+    rng = np.random.default_rng(K + n)
+    coarse = rng.integers(-9, 10, size=(K, d)).astype(np.float32)
+    if n >= 50_000:
+        coarse[:K // 2] = coarse[K // 2:2 * (K // 2)]
+        coarse[:K // 4] = coarse[K // 4:2 * (K // 4)]
+        coarse[:K // 8] = coarse[K // 8:2 * (K // 8)]
+    coarse[K - 1] = 0
+    coarse[K - 1, d // 3] = last
+    x = (coarse[rng.integers(0, K - 1, size=n)] + rng.integers(-2, 3, size=(n, d))).astype(np.float32)
+    near = coarse[:K - 1].astype(np.float64)
+    want = np.concatenate([((near * near).sum(1)[None] - 2 * xx.astype(np.float64) @ near.T).argmin(1)  # whole numbers: exact
+                           for xx in np.array_split(x, max(1, n // 5000))])
+    assert np.array_equal(Q.qadc_ivf_assign(to_gpu(coarse), to_gpu(x)).cpu().numpy(), want)
+    halves = np.stack([coarse, coarse[::-1]])       # (the far centroid first in the second half)
+    got = Q.qadc_multi_index_assign(to_gpu(halves), to_gpu(np.concatenate([x, x[::-1]], axis=1))).cpu().numpy()
+    # the second half's cells in reverse order: the lowest of equal ones is the last there
+    other = np.concatenate([((near * near).sum(1)[None] - 2 * xx.astype(np.float64) @ near.T)[:, ::-1].argmin(1)
+                            for xx in np.array_split(x[::-1], max(1, n // 5000))]) + 1
+    assert np.array_equal(got, want * K + other)
+
+
 @pytest.mark.parametrize("d,K", [(128, 256), (64, 1024), (200, 300)])
 def test_ivf_assign_is_not_slowed_by_a_few_centroids(Q, d, K):
     """One stray centroid, one that is not finite, all of them twice: not much slower than without."""
