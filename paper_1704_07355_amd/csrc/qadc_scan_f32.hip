@@ -669,8 +669,11 @@ static bool make_f32_plan(int variant, int64_t n, int m, int nq, int R, F32Plan 
     const int tile = F32_NT * cpt;
     const int64_t tiles = n > 0 ? ceil_div(n, tile) : 1;
     // (8-bit codes of 8 bytes and more: fewer, longer workgroups, whose bounds on half a sum are made once each; us with 1024 / 512:
-    // four queries over 20 M codes of 8 bytes 132 / 127, one query 55 / 62; one over 20 M of 32 bytes 168 / 144)
-    const int64_t g_def = p->KSUB == 256 && (p->ROW == 32 || (p->ROW >= 8 && nq > 1)) ? 512 : 1024;
+    // four queries over 20 M codes of 8 bytes 132 / 127, one query 55 / 62; one over 20 M of 32 bytes 168 / 144.  Of 32 bytes the
+    // chip holds 768 at once, and 512 for each of two queries are a round and a third: 20 M 270 / 309, with 768 269; 10 M 152 / 170 /
+    // 153; 4 M 86.1 / 84.9 / 86.2, 1 M 49.2 / 47.5 / 50.8.  More queries with 768 / 512: four over 4 M 142 / 132, over 20 M 500 / 495.)
+    const bool halves = p->KSUB == 256 && p->ROW >= 8;
+    const int64_t g_def = halves && p->ROW == 32 ? (nq == 2 && tiles >= 12288 ? 768 : 512) : halves && nq > 1 ? 512 : 1024;
     int64_t G = knob_or(knobs().scan_f32_wgs, (int)g_def);
     if (G < 1) G = 1;
     if (G > tiles) G = tiles;

@@ -121,3 +121,17 @@ def test_workspaces_sized_for_a_batch_serve_its_smaller_batches():
                         assert less <= Q.qadc_workspace_bytes(call, n, m, nq, R), (call, m, R, n, nq)
     # at least what 2048 report regions per query take
     assert Q.qadc_workspace_bytes(Q.QADC_WS_SCAN_TOPK, 10_000_000, 16, 5, 100) >= 5 * 2048 * 100 * 8
+
+
+@pytest.mark.parametrize("m", [4, 8, 16, 32])
+def test_workspaces_of_float_scans_serve_smaller_calls(m):
+    """The number of workgroups follows the database and the queries; a size given for a call still covers shorter
+    databases and, up to 7, fewer queries."""
+    import paper_1704_07355_amd as Q
+    for R in (1, 100, 1000):
+        before = [0] * 7
+        for n in sorted({*range(100_000, 4_000_000, 157_777), *range(4_000_000, 40_000_000, 977_777), 6_291_456, 6_291_457}):
+            sizes = [Q.qadc_workspace_bytes(Q.QADC_WS_SCAN_F32_8BIT, n, m, nq, R) for nq in range(1, 8)]
+            assert sizes == sorted(sizes) and sizes[0] > 0, (m, R, n, sizes)
+            assert all(a <= b for a, b in zip(before, sizes)), (m, R, n, before, sizes)
+            before = sizes

@@ -839,6 +839,30 @@ def test_float_scan_half_by_half(Q, O, m, n, nq, kind):
     assert np.array_equal(idx_np(idx), wi) and np.array_equal(dist.cpu().numpy(), wd)
 
 
+def test_float_scan_of_two_queries_over_32_byte_codes(Q, O, monkeypatch):
+    """Two queries fill the chip in whole rounds: they take no more than twice what one takes (2.07 times where they do not).
+    The results are the oracle's, and the same whatever the number of workgroups."""
+    import torch
+    from gpu_common import gpu_us
+    from oracle import cref
+    g = torch.Generator(device="cuda:0")
+    g.manual_seed(2)
+    codes = torch.randint(0, 256, (20_000_000, 32), dtype=torch.uint8, generator=g, device="cuda:0")
+    luts = sum(torch.randn((2, 32, 256), generator=g, device="cuda:0") ** 2 for _ in range(3))
+    one, two = (Q.qadc_workspace_init(torch.empty((Q.qadc_workspace_bytes(Q.QADC_WS_SCAN_F32_8BIT, len(codes), 32, k, 100),),
+                                                  dtype=torch.uint8, device="cuda:0")) for k in (1, 2))
+    t1 = gpu_us(lambda: Q.qadc_scan_topk(Q.QADC_F32_8BIT, codes, luts[:1], 100, workspace=one), reps=10)
+    t2 = gpu_us(lambda: Q.qadc_scan_topk(Q.QADC_F32_8BIT, codes, luts, 100, workspace=two), reps=10)
+    assert t2 < 1.95 * t1, (t1, t2)
+    part = codes[:6_300_003].contiguous()  # (12,305 tiles; the rule's line is at 12,288)
+    wi, wd = cref.scan_topk_f32(part.cpu().numpy(), luts.cpu().numpy(), 100)
+    for wgs in (None, "512"):
+        if wgs:
+            monkeypatch.setenv("QADC_SCAN_F32_WGS", wgs)
+        idx, dist = Q.qadc_scan_topk(Q.QADC_F32_8BIT, part, luts, 100)
+        assert np.array_equal(idx_np(idx), wi) and np.array_equal(dist.cpu().numpy(), wd)
+
+
 @pytest.mark.parametrize("m,n,nq", [(16, 300_007, 8), (16, 300_007, 19), (8, 700_000, 16), (32, 280_000, 9)])
 def test_float_scan_of_4bit_codes_in_query_batches(Q, O, m, n, nq):
     """Batches of eight queries and more over 4-bit codes take the query-tiled float kernel too (two
