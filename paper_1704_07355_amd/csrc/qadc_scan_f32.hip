@@ -718,6 +718,11 @@ static bool make_f32_plan(int variant, int64_t n, int m, int nq, int R, F32Plan 
         }
     }
     p->l = scan_layout(p->G, R);
+    // Three queries and more: two or three tiles for every workgroup, where 512 would leave some of them one less (8-byte codes, us
+    // with 1024 / 512 / this: 7 queries over 1.6 M 52.4 / 54.2 / 50.5, 2.4 M 61.9 / 60.9 / 58.9, 3 M 68.5 / 64.3 / 66.1; two over 2.4 M
+    // 32.3 / 30.1 / 31.8).  The layout keeps room for all 512: a size that serves a call serves those with fewer codes.
+    if (halves && !p->tiled && p->ROW <= 16 && nq > 2 && 2 * tiles >= 3 * G && tiles < 3 * G && knobs().scan_f32_wgs < 0)
+        p->G = (int)ceil_div(tiles, ceil_div(tiles, G));
     p->stride = p->l.stride;
     p->countsA_off = p->listsA_off = p->flags_off = 0;
     if (p->tiled) {
