@@ -233,7 +233,7 @@ struct FilterTile {
 
 // The cells of up to TM vectors by a workgroup; row(k): the row of x that is vector k, -1 for none.  store(row, cell) for a
 // vector that is decided, undecided(row) for one that is not.
-template <int NT, int KS, int NB, bool VEC, Factors F, typename Row, typename Store, typename Undecided>
+template <int NT, int KS, int NB, bool VEC, Factors F, bool PHASES, typename Row, typename Store, typename Undecided>
 __device__ __forceinline__ void filter_tile(FilterTile<NT, KS, NB, F> &sh, const float *__restrict__ coarse, int K, int d,
                                             const float *__restrict__ x, int64_t ldx, Row row_of, Store store,
                                             Undecided undecided)
@@ -402,9 +402,24 @@ __device__ __forceinline__ void filter_tile(FilterTile<NT, KS, NB, F> &sh, const
         }
 #pragma unroll
         for (int nb = 0; nb < NB; ++nb) acc[nb] = init;
+        // (in phases the operands of a step are requested two steps ahead: left to itself the compiler requests them where they are used)
+        bits16x8 a[3][S::PARTS];
+        if constexpr (PHASES) {
+#pragma unroll
+            for (int s = 0; s < 2; ++s)
+#pragma unroll
+                for (int p = 0; p < S::PARTS; ++p) a[s][p] = tile[buf][ct][s][p][lane];
+        }
 #pragma unroll
         for (int s = 0; s < KS; ++s) {
-            const bits16x8 ah = tile[buf][ct][s][0][lane], al = tile[buf][ct][s][S::PARTS - 1][lane];
+            if constexpr (PHASES) {
+                if (s + 2 < KS)
+#pragma unroll
+                    for (int p = 0; p < S::PARTS; ++p) a[(s + 2) % 3][p] = tile[buf][ct][s + 2][p][lane];
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            const bits16x8 ah = PHASES ? a[s % 3][0] : tile[buf][ct][s][0][lane],
+                           al = PHASES ? a[s % 3][S::PARTS - 1] : tile[buf][ct][s][S::PARTS - 1][lane];
             if constexpr (HALF) {
 #pragma unroll
                 for (int nb = 0; nb < NB; ++nb)
@@ -435,7 +450,7 @@ __device__ __forceinline__ void filter_tile(FilterTile<NT, KS, NB, F> &sh, const
             for (int nb = 0; nb < NB; ++nb) {
                 float v = fminf(fminf(acc[nb][4 * u], acc[nb][4 * u + 1]), acc[nb][4 * u + 2]);
                 v = fminf(fminf(v, acc[nb][4 * u + 3]), AF_NONE);  // (no NaN: the medians would take it for the smallest)
-                v = __uint_as_float((__float_as_uint(v) & ~mask) | ((first + u) & mask));
+                v = __uint_as_float((__float_as_uint(v) & ~mask) | (PHASES ? first + u : (first + u) & mask));
                 b4[nb] = __builtin_amdgcn_fmed3f(b3[nb], b4[nb], v);
                 b3[nb] = __builtin_amdgcn_fmed3f(b2[nb], b3[nb], v);
                 b2[nb] = __builtin_amdgcn_fmed3f(b1[nb], b2[nb], v);
@@ -445,7 +460,7 @@ __device__ __forceinline__ void filter_tile(FilterTile<NT, KS, NB, F> &sh, const
     int a1[NB], a2[NB], a3[NB];  // the groups of b1, b2, b3, once the last segment is done
     fetch(0);
     stash(0, 0);
-    fetch(min(TC, K - 1));
+    if constexpr (!PHASES) fetch(min(TC, K - 1));
     __syncthreads();
     f32x16 acc[2][NB];  // of this 32 cells and of the 32 before, whose minima are taken beside these products
     int buf = 0;
@@ -458,24 +473,34 @@ __device__ __forceinline__ void filter_tile(FilterTile<NT, KS, NB, F> &sh, const
             for (int r = 0; r < 16; ++r) acc[1][nb][r] = AF_NONE;
         }
         for (int c0 = s0; c0 < s1; c0 += TC, buf ^= 1) {
-            // one block of code, so that the conversion of the next tile and the minima of the results before are dealt out
-            // among the products
+            if constexpr (PHASES) {
+                if (c0 + TC < K) fetch(c0 + TC);  // uniform; travels while this tile is multiplied
 #pragma unroll
-            for (int ct = 0; ct < CT; ++ct) {
-                multiply(buf, ct, acc[ct & 1]);
-                note(acc[(ct & 1) ^ 1], (unsigned)((c0 - s0) / 8 + 4 * ct - 4) & S::MASK);
-                if (ct == 0) {
-                    stash(c0 + TC, buf ^ 1);  // (nobody reads what is beyond the last; that buffer was read before the last barrier)
-                    fetch(min(c0 + 2 * TC, K - 1));
+                for (int ct = 0; ct < CT; ++ct) {
+                    multiply(buf, ct, acc[0]);
+                    note(acc[0], (unsigned)((c0 - s0) / 8 + 4 * ct));
                 }
-            }
-            if constexpr (CT == 1) {
+                if (c0 + TC < K) stash(c0 + TC, buf ^ 1);  // uniform; that buffer was read before the last barrier
+            } else {
+                // one block of code, so that the conversion of the next tile and the minima of the results before are dealt out
+                // among the products
 #pragma unroll
-                for (int nb = 0; nb < NB; ++nb) acc[1][nb] = acc[0][nb];
+                for (int ct = 0; ct < CT; ++ct) {
+                    multiply(buf, ct, acc[ct & 1]);
+                    note(acc[(ct & 1) ^ 1], (unsigned)((c0 - s0) / 8 + 4 * ct - 4) & S::MASK);
+                    if (ct == 0) {
+                        stash(c0 + TC, buf ^ 1);  // (nobody reads what is beyond the last; that buffer was read before the last barrier)
+                        fetch(min(c0 + 2 * TC, K - 1));
+                    }
+                }
+                if constexpr (CT == 1) {
+#pragma unroll
+                    for (int nb = 0; nb < NB; ++nb) acc[1][nb] = acc[0][nb];
+                }
             }
             __syncthreads();
         }
-        note(acc[1], (unsigned)((s1 - s0 - 1) / TC * CT + CT - 1) * 4);
+        if constexpr (!PHASES) note(acc[1], (unsigned)((s1 - s0 - 1) / TC * CT + CT - 1) * 4);
 #pragma unroll
         for (int nb = 0; nb < NB; ++nb) {
             auto group = [&](float b) { return (int)(__float_as_uint(b) & S::MASK) * 2 + s0 / 4 + half; };
@@ -703,14 +728,14 @@ __device__ __forceinline__ void filter_tile(FilterTile<NT, KS, NB, F> &sh, const
     }
 }
 
-template <int NT, int KS, int NB, bool VEC, Factors F>
+template <int NT, int KS, int NB, bool VEC, Factors F, bool PHASES>
 __global__ __launch_bounds__(NT, 2) void assign_filter_kernel(const float *__restrict__ coarse, int K, int d,
                                                               const float *__restrict__ x, int64_t ldx, int64_t n,
                                                               int32_t *__restrict__ cells, int scale, int accumulate)
 {
     __shared__ FilterTile<NT, KS, NB, F> sh;
     const int64_t i0 = (int64_t)blockIdx.x * FilterShape<NT, KS, NB, F>::TM;
-    filter_tile<NT, KS, NB, VEC, F>(
+    filter_tile<NT, KS, NB, VEC, F, PHASES>(
         sh, coarse, K, d, x + i0 * ldx, ldx, [&](int k) { return i0 + k < n ? k : -1; },
         [&](int64_t k, int bc) { cells[i0 + k] = (accumulate ? cells[i0 + k] : 0) + bc * scale; },
         [&](int64_t k) { cells[i0 + k] = (accumulate ? cells[i0 + k] : 0) ^ ASG_MARK; });
@@ -789,7 +814,7 @@ __global__ __launch_bounds__(256) void assign_rest_kernel(const float *__restric
         if (count > ASG_FEW) {  // uniform
             int behind = 0;  // undecided in the tiles so far
             for (int k0 = 0; k0 < count; k0 += TM) {  // uniform
-                filter_tile<256, KS, 1, VEC, Factors::Split>(
+                filter_tile<256, KS, 1, VEC, Factors::Split, true>(
                     *reinterpret_cast<Again *>(room), coarse, K, d, x + i0 * ldx, ldx,
                     [&](int k) { return k0 + k < count ? (int)todo[k0 + k] : -1; },
                     [&](int64_t k, int bc) { cells[i0 + k] = (cells[i0 + k] ^ ASG_MARK) + bc * scale; },
@@ -909,36 +934,57 @@ static bool wide_pays(int K, int64_t n)
     return n >= 2 * round;
 }
 
+// Split factors: the minima and the conversion of the centroids in one block of code with the products, or in phases of their own,
+// the operands of a product requested two steps ahead?  The block is for wavefronts that are alone on a SIMD; two of them have
+// each other's products to run beside, up to 128 components, and 16 steps of products leave no registers for it.  Rows that are not
+// whole steps are converted behind a branch per load, which parts the block: phases from 65 components on.  us, block / phases (before
+// there was a block), K = 16384: d = 128 20 k 536 / 579 (576), 40 k 702 / 632 (625); d = 64 20 k 267 / 302 (291), 40 k 360 / 342
+// (329); d = 256 20 k 955 / 892 (910), 40 k 1247 / 1118 (1139); d = 100 20 k 905 / 816 (821); d = 200 100 k 3024 / 2752 (2900); d = 63
+// 40 k 434 / 472 (466); K = 1000: d = 128 20 k 42.6 / 45.5 (54.0), 40 k 58.9 / 55.5 (66.6); d = 256 20 k 76.6 / 71.7 (86.4).
+template <int KS, bool VEC>
+static bool phases_pay(int64_t n)
+{
+    return VEC ? KS > 8 || n > 128 * 256 : KS > 4;
+}
+
 template <int KS>
 static void launch_filter(const float *coarse, int K, int d, const float *x, int64_t ldx, int64_t n, int range,
                           int32_t *cells, int scale, int accumulate, hipStream_t st)
 {
     const bool vec = d == 16 * KS && ldx % 4 == 0 && ((uintptr_t)coarse & 15) == 0 && ((uintptr_t)x & 15) == 0;
     const dim3 grid((unsigned)ceil_div(n, 128)), ranges((unsigned)ceil_div(n, range));
-#define QADC_FILTER(NT_, NB_, VEC_, F_, GRID_)                                                                             \
-    hipLaunchKernelGGL((assign_filter_kernel<NT_, KS, NB_, VEC_, Factors::F_>), GRID_, dim3(NT_), 0, st, coarse, K, d, x,  \
-                       ldx, n, cells, scale, accumulate)
+#define QADC_FILTER(NT_, NB_, VEC_, F_, PHASES_, GRID_)                                                                    \
+    hipLaunchKernelGGL((assign_filter_kernel<NT_, KS, NB_, VEC_, Factors::F_, PHASES_>), GRID_, dim3(NT_), 0, st, coarse,  \
+                       K, d, x, ldx, n, cells, scale, accumulate)
 #define QADC_REST(VEC_, AGAIN_, DEFINITION_)                                                                               \
     hipLaunchKernelGGL((assign_rest_kernel<AGAIN_ ? KS : 2, VEC_, AGAIN_, DEFINITION_>), ranges, dim3(256), 0, st, coarse, K, \
                        d, x, ldx, n, range, cells, scale, accumulate)
     constexpr bool ONE = KS <= 8;
     if (!half_factors_pay(K, d, n, vec)) {
-        if (vec) QADC_FILTER(256, 1, true, Split, grid);
-        else QADC_FILTER(256, 1, false, Split, grid);
+        if (vec) {
+            if (phases_pay<KS, true>(n)) QADC_FILTER(256, 1, true, Split, true, grid);
+            else if constexpr (KS <= 8) QADC_FILTER(256, 1, true, Split, false, grid);
+        } else {
+            if (phases_pay<KS, false>(n)) {
+                if constexpr (KS > 4) QADC_FILTER(256, 1, false, Split, true, grid);
+            } else if constexpr (KS <= 4) {
+                QADC_FILTER(256, 1, false, Split, false, grid);
+            }
+        }
         QADC_REST(false, false, true);
         return;
     }
     if (vec) {
         const bool wide = wide_pays<KS>(K, n);
         if (wide) {
-            if constexpr (KS <= 8) QADC_FILTER(512, 2, true, Half, dim3((unsigned)ceil_div(n, 512)));
-            else QADC_FILTER(512, 1, true, Half, dim3((unsigned)ceil_div(n, 256)));
+            if constexpr (KS <= 8) QADC_FILTER(512, 2, true, Half, false, dim3((unsigned)ceil_div(n, 512)));
+            else QADC_FILTER(512, 1, true, Half, false, dim3((unsigned)ceil_div(n, 256)));
         }
-        if (!wide) QADC_FILTER(256, 1, true, Half, grid);
+        if (!wide) QADC_FILTER(256, 1, true, Half, false, grid);
         QADC_REST(true, true, ONE);
     } else {
         if constexpr (KS <= 8) {  // (half_factors_pay: no more components)
-            QADC_FILTER(256, 1, false, Half, grid);
+            QADC_FILTER(256, 1, false, Half, false, grid);
             QADC_REST(false, true, ONE);
         }
     }

@@ -553,6 +553,14 @@ def test_ivf_assign_over_many_cells(Q, d, K, n):
         assert torch.equal(got[s:s + 8192], want)
 
 
+# split factors in phases: aligned rows from 32,769 vectors on or beyond 128 components, others from 65 components on; the block on the
+# other side of the line
+@pytest.mark.parametrize("d,K,n", [(128, 513, 32_769), (128, 1031, 32_768), (64, 1540, 33_000), (32, 520, 32_800), (96, 33, 40_001),
+                                   (256, 1057, 700), (65, 515, 900), (100, 1025, 33_001), (255, 40, 130), (63, 1030, 33_000)])
+def test_ivf_assign_of_split_factors_in_phases(Q, d, K, n):
+    test_ivf_assign_over_many_cells(Q, d, K, n)
+
+
 @pytest.mark.parametrize("K,dh,n", [(2, 4, 1_000), (64, 16, 4_000), (333, 32, 131_500)])
 def test_multi_index_assign_of_crowded_cells(Q, K, dh, n):
     """Both halves leave vectors to the second kernel, which finds them among the cells of the first half."""
