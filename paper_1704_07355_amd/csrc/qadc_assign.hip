@@ -984,7 +984,15 @@ static void launch_filter(const float *coarse, int K, int d, const float *x, int
         QADC_REST(true, true, ONE);
     } else {
         if constexpr (KS <= 8) {  // (half_factors_pay: no more components)
-            QADC_FILTER(256, 1, false, Half, false, grid);
+            // (rows that are not whole steps: us, narrow / wide (groups of 16 cells, narrow), 100 k vectors, K = 16384: d = 40 441 / 311
+            // (392), d = 63 615 / 325 (618), d = 80 847 / 530 (1380); K = 4096: d = 40 123 / 90 (127); 148 k 188 / 177 (206), vectors
+            // and centroids of one Gaussian 228 / 232 (266); K = 2048 134 / 150 (172))
+            bool wide = false;
+            if constexpr (KS == 4 || KS == 6) {
+                wide = K >= 4096;
+                if (wide) QADC_FILTER(512, 2, false, Half, false, dim3((unsigned)ceil_div(n, 512)));
+            }
+            if (!wide) QADC_FILTER(256, 1, false, Half, false, grid);
             QADC_REST(false, true, ONE);
         }
     }

@@ -561,6 +561,12 @@ def test_ivf_assign_of_split_factors_in_phases(Q, d, K, n):
     test_ivf_assign_over_many_cells(Q, d, K, n)
 
 
+# 512 vectors per workgroup from 4096 cells on, where a row is not whole steps of 16 components or not aligned
+@pytest.mark.parametrize("d,K,n", [(33, 4096, 98_304), (47, 4109, 98_401), (64, 4095, 98_305), (65, 4097, 99_001), (95, 8193, 98_815)])
+def test_ivf_assign_of_unaligned_rows_by_wide_workgroups(Q, d, K, n):
+    test_ivf_assign_over_many_cells(Q, d, K, n)
+
+
 @pytest.mark.parametrize("K,dh,n", [(2, 4, 1_000), (64, 16, 4_000), (333, 32, 131_500)])
 def test_multi_index_assign_of_crowded_cells(Q, K, dh, n):
     """Both halves leave vectors to the second kernel, which finds them among the cells of the first half."""
