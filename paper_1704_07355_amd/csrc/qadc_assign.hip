@@ -28,8 +28,8 @@
 // the conversion behind the products: 0.25 ms per 1024 centroids.  Not faster: the order of instructions given by hand
 // (1.23 ms for 1.13), workgroups of 256 threads, two per compute unit (1.58).
 // A margin is a matter of the vector and of the closest cells: a far or NaN centroid costs the other cells
-// nothing.  Every centroid four times, all vectors marked: 37 ms per 1 M (42 before the tiles of float64 lost the bounds checks
-// of every load and half of the instructions of every comparison).
+// nothing.  The slow case: 4096 different centroids that are all within the margin of every vector, 200 k of them, d = 128: 9.9 ms; every
+// centroid eight times 2.3 (copies are left out: list_cells).
 //
 // assign_f64_kernel (d > 256: the vectors no longer fit the registers): a workgroup of 256 threads takes 128
 // vectors and walks over all cells 128 at a time; 16 components of both go through LDS as float64 per step,
@@ -59,13 +59,13 @@ struct AssignTile {
 constexpr uint64_t ASG_NONE = 0x7ff0000000000001ull;  // one above the bits of infinity
 
 // The cells of up to ASG_TM vectors, by a workgroup of 256 threads; row(k): the row of x that is vector k of the tile, -1
-// for none.
+// for none; cell(k), increasing with k: the k-th of K cells.
 // Thread (tx, ty), tx = tid & 15, ty = tid >> 4, owns the vectors 8*ty .. 8*ty+7 of the tile and
 // the cells 32*k + 2*tx + e (k < 4, e < 2): a wavefront's 16-byte reads of the cells are
 // contiguous across its lanes, its reads of the vectors are the same for 16 lanes.
-template <typename Row, typename Store>
+template <typename Row, typename Cell, typename Store>
 __device__ __forceinline__ void assign_tile(AssignTile &s, const float *__restrict__ coarse, int K, int d,
-                                            const float *__restrict__ x, int64_t ldx, Row row, Store store)
+                                            const float *__restrict__ x, int64_t ldx, Row row, Cell cell, Store store)
 {
     const int tid = threadIdx.x;
     const int tx = tid & 15, ty = tid >> 4;
@@ -82,6 +82,9 @@ __device__ __forceinline__ void assign_tile(AssignTile &s, const float *__restri
     }
 
     for (int c0 = 0; c0 < K; c0 += ASG_TN) {
+        int from[8];  // cells this thread fetches
+#pragma unroll
+        for (int e = 0; e < 8; ++e) from[e] = cell(min(c0 + ty + 16 * e, K - 1));
         double acc[8][8];
 #pragma unroll
         for (int a = 0; a < 8; ++a)
@@ -96,7 +99,7 @@ __device__ __forceinline__ void assign_tile(AssignTile &s, const float *__restri
 #pragma unroll
                 for (int e = 0; e < 8; ++e) {
                     xl[e] = xr[e][t0];
-                    cl[e] = coarse[(size_t)min(c0 + ty + 16 * e, K - 1) * d + t0 + tx];
+                    cl[e] = coarse[(size_t)from[e] * d + t0 + tx];
                 }
             }
 #pragma unroll
@@ -156,7 +159,7 @@ __device__ __forceinline__ void assign_tile(AssignTile &s, const float *__restri
             const int cc = s.cand_c[tid][k];
             if (dd < bd || (dd == bd && cc < bc)) { bd = dd; bc = cc; }
         }
-        store(row(tid), bc);
+        store(row(tid), bc == 0x7fffffff ? bc : cell(bc));
     }
 }
 
@@ -166,7 +169,7 @@ __global__ __launch_bounds__(256) void assign_f64_kernel(const float *__restrict
 {
     __shared__ AssignTile s;
     const int64_t i0 = (int64_t)blockIdx.x * ASG_TM;
-    assign_tile(s, coarse, K, d, x + i0 * ldx, ldx, [&](int k) { return i0 + k < n ? k : -1; },
+    assign_tile(s, coarse, K, d, x + i0 * ldx, ldx, [&](int k) { return i0 + k < n ? k : -1; }, [](int k) { return k; },
                 [&](int k, int bc) { cells[i0 + k] = (accumulate ? cells[i0 + k] : 0) + bc * scale; });
 }
 
@@ -754,35 +757,152 @@ __global__ __launch_bounds__(NT, 2) void assign_filter_kernel(const float *__res
 // 60 against 48 ms for 500 k vectors of 256 components, all marked).
 constexpr int ASG_RANGE = 4096, ASG_FEW = 20;
 
-// Centroids up to the last one that differs from its predecessor, by 256 threads (`last`: a word of LDS).  Those behind it are
-// copies of it, and the lowest of equal cells wins: a list of centroids that is padded at its end, or one centroid over and over,
-// is measured without them (1024 equal centroids, d = 64, 200 k vectors: 1.22 -> 0.17 ms).  One round trip where there are none.
-__device__ __forceinline__ int without_copies(const float *__restrict__ coarse, int K, int d, int *last)
+// Copies of a centroid (a list padded to its length, clusters that started from equal vectors, one centroid over and over) leave
+// every vector near them to the definition, and add nothing to it: the lowest of equal cells wins.  Before a workgroup measures more
+// than a tile of vectors it looks for them, wherever they stand, and lists the other cells, increasing; where there are no copies, or
+// more than ASG_LIST other cells, or more than ASG_COPIES_K in all, it returns 0 and nothing is listed.
+// Rows are hashed, 16 lanes each; a slot is for the lowest row of a hash, and the others with that hash are compared with it, bit by bit.
+// (A copy may go unnoticed where its original found no slot.)  us, with this / all cells measured, 200 k vectors, d = 64, K = 1024:
+// one centroid over and over 379 / 1254, the last or the first of them another 309 / 711, two in turn 374 / 1242, 20 of them in any order 373 /
+// 1224, 128 eight times each 374 / 1217; K = 4096, d = 128: one 1350 / 9900, 512 eight times 2340 / 9930; K = 16384, d = 32, 30 k
+// 2048 eight times 1266 / 2990; no copies 1232 / 1230, 9993 / 10044, 3014 / 3000.
+constexpr int ASG_LIST = 4096, ASG_SLOTS = 4096, ASG_COPIES_K = 65536;
+
+struct AssignCopies {
+    unsigned long long slots[ASG_SLOTS];  // row << 32 | hash
+    unsigned copy[ASG_COPIES_K / 32];     // a bit per row
+    unsigned count[4];
+    int some;
+};
+
+// The sum over the 16 lanes of a row, in all of them.
+__device__ __forceinline__ unsigned team_sum(unsigned v)
 {
-    constexpr int PER = 16;
-    const int tid = threadIdx.x;
+    v += dpp_or_zero<0x128>(v);  // (rotations by 8, 4, 2, 1)
+    v += dpp_or_zero<0x124>(v);
+    v += dpp_or_zero<0x122>(v);
+    return v + dpp_or_zero<0x121>(v);
+}
+
+__device__ __forceinline__ int list_cells(AssignCopies &s, uint16_t *list, const float *__restrict__ coarse, int K, int d)
+{
+    constexpr int U = 8;  // rows of a team (16 lanes) in flight
+    constexpr unsigned SLOT = 0x100000000ull / ASG_SLOTS;  // hashes that share a slot
+    constexpr int PROBES = 4;
+    const int tid = threadIdx.x, r = tid & 15, team = tid >> 4, lane = tid & 63, wave = tid >> 6;
     const unsigned *c = reinterpret_cast<const unsigned *>(coarse);
-    if (tid == 0) *last = 0;
+    for (int i = tid; i < ASG_SLOTS; i += 256) s.slots[i] = ~0ull;
+    for (int i = tid; i < (K + 31) / 32; i += 256) s.copy[i] = 0;
+    if (tid == 0) s.some = 0;
     __syncthreads();
-    for (int64_t end = (int64_t)K * d; end > d; end -= 256 * PER) {  // uniform
-        unsigned a[PER], b[PER];
+    auto mix = [](unsigned a) {
+        a ^= a >> 16; a *= 0x85ebca6bu;
+        a ^= a >> 13; a *= 0xc2b2ae35u;
+        return a ^ a >> 16;
+    };
+    // of row at(c0 + 16 u + team), u = r (r < U): a hash of up to 32 components
+    auto hash = [&](int c0, auto at) {
+        unsigned h[U];
 #pragma unroll
-        for (int u = 0; u < PER; ++u) {
-            const int64_t i = max(end - 1 - tid - 256 * u, (int64_t)d);
-            a[u] = c[i];
-            b[u] = c[i - d];
+        for (int u = 0; u < U; ++u) {
+            const unsigned *row = c + (size_t)at(min(c0 + 16 * u + team, K - 1)) * d;
+            unsigned a = 0;
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+                const int e = r + 16 * j, t = d > 32 ? e * d >> 5 : e;
+                if (t < d) a = (a + row[t]) * 0x9e3779b1u + (unsigned)e;
+            }
+            h[u] = mix(a);
         }
-        int row = 0;
+        unsigned own = 0;
 #pragma unroll
-        for (int u = 0; u < PER; ++u)
-            if (row == 0 && a[u] != b[u]) row = (int)(max(end - 1 - tid - 256 * u, (int64_t)d) / d);
-        if (row) atomicMax(last, row);
+        for (int u = 0; u < U; ++u) {
+            h[u] = team_sum(h[u]);
+            own = r == u ? h[u] : own;
+        }
+        return mix(own);
+    };
+    auto insert = [&](int c0, int end, auto at) {
+        const unsigned h = hash(c0, at);
+        const int k = c0 + 16 * r + team;
+        if (r < U && k < end) {
+            const int row = at(k);
+            const unsigned long long own = (unsigned long long)row << 32 | h;
+            for (int p = 0; p < PROBES; ++p) {
+                unsigned long long *slot = &s.slots[(h / SLOT + p) % ASG_SLOTS];
+                unsigned long long was = atomicCAS(slot, ~0ull, own);
+                if (was == ~0ull) break;
+                if ((unsigned)was != h) continue;
+                was = atomicMin(slot, own);  // (the same hash: the lowest row)
+                if (was != own) {
+                    const int late = max(row, (int)(was >> 32));
+                    atomicOr(&s.copy[late >> 5], 1u << (late & 31));
+                    s.some = 1;
+                }
+                break;
+            }
+        }
+    };
+    auto itself = [](int k) { return k; };
+    // a sample first: copies that are few are not worth looking for (twice 4096 cells: 8 pairs of the 256 rows)
+    const int sample = max(K / 16, 256);
+    if (sample < K) {  // uniform
+        for (int c0 = 0; c0 < sample; c0 += 16 * U)  // uniform
+            insert(c0, sample, [&](int k) { return (int)((uint64_t)mix((unsigned)k + 1u) * (unsigned)K >> 32); });
         __syncthreads();
-        const int found = *last;
-        __syncthreads();  // (read by all before the next round writes it)
-        if (found) return found + 1;  // uniform
+        if (!s.some) return 0;  // uniform
     }
-    return 1;
+    for (int c0 = 0; c0 < K; c0 += 16 * U) insert(c0, K, itself);  // uniform
+    __syncthreads();
+    if (!s.some) return 0;  // uniform
+    for (int c0 = 0; c0 < K; c0 += 16 * U) {  // uniform
+        const unsigned h = hash(c0, itself);
+        const int mine = c0 + 16 * r + team;
+        const bool suspect = r < U && mine < K && (s.copy[mine >> 5] >> (mine & 31) & 1u);
+        int own = K;
+        if (suspect)
+            for (int p = 0; p < PROBES && own == K; ++p) {
+                const unsigned long long in = s.slots[(h / SLOT + p) % ASG_SLOTS];
+                if ((unsigned)in == h && in != ~0ull) own = (int)(in >> 32);
+            }
+        if (__ballot(suspect) == 0ull) continue;  // uniform over the wavefront
+        const unsigned *a[U], *b[U];
+        unsigned diff[U] = {};
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int row = min(c0 + 16 * u + team, K - 1), with = __shfl(suspect ? own : mine, (lane & 48) + u);
+            a[u] = c + (size_t)row * d;
+            b[u] = c + (size_t)min(with, K - 1) * d;
+        }
+        for (int t = r; t < d; t += 16)
+#pragma unroll
+            for (int u = 0; u < U; ++u) diff[u] |= a[u][t] ^ b[u][t];
+        bool differs = false;  // row r of the team
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const bool any = team_sum(diff[u] ? 1u : 0u) != 0;
+            differs = r == u ? any : differs;
+        }
+        differs = differs || own >= mine;
+        if (suspect && differs) atomicAnd(&s.copy[mine >> 5], ~(1u << (mine & 31)));
+    }
+    __syncthreads();
+    unsigned found = 0;
+    for (int c0 = 0; c0 < K; c0 += 256) {  // uniform
+        const int row = c0 + tid;
+        const bool keep = row < K && !(s.copy[row >> 5] >> (row & 31) & 1u);
+        const unsigned long long mask = __ballot(keep);
+        if (lane == 0) s.count[wave] = (unsigned)__popcll(mask);
+        __syncthreads();
+        unsigned at = found + rank_in_mask(mask);
+        for (int w = 0; w < 4; ++w) {
+            if (w < wave) at += s.count[w];
+            found += s.count[w];
+        }
+        if (keep && at < (unsigned)ASG_LIST) list[at] = (uint16_t)row;
+        __syncthreads();
+    }
+    return found <= (unsigned)ASG_LIST ? (int)found : 0;
 }
 
 template <int KS, bool VEC, bool AGAIN, bool DEFINITION>
@@ -793,10 +913,12 @@ __global__ __launch_bounds__(256) void assign_rest_kernel(const float *__restric
     using Again = FilterTile<256, KS, 1, Factors::Split>;
     constexpr int TM = FilterShape<256, KS, 1, Factors::Split>::TM;
     constexpr size_t BYTES = DEFINITION && (!AGAIN || sizeof(AssignTile) > sizeof(Again)) ? sizeof(AssignTile) : sizeof(Again);
+    static_assert(sizeof(AssignCopies) <= sizeof(AssignTile), "");
     __shared__ __attribute__((aligned(16))) char room[BYTES];  // for one of them at a time
     AssignTile &s = *reinterpret_cast<AssignTile *>(room);
     __shared__ uint16_t todo[ASG_RANGE];
-    __shared__ int ntodo, nleft, last;
+    __shared__ uint16_t list[DEFINITION ? ASG_LIST : 1];
+    __shared__ int ntodo, nleft;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int64_t i0 = (int64_t)blockIdx.x * range;
     if (tid == 0) { ntodo = 0; nleft = 0; }
@@ -808,8 +930,6 @@ __global__ __launch_bounds__(256) void assign_rest_kernel(const float *__restric
     __syncthreads();
     int count = ntodo;
     if (count == 0) return;  // uniform
-    const int cells_in_all = K;
-    if (count > ASG_FEW) K = without_copies(coarse, K, d, &last);  // uniform
     if constexpr (AGAIN) {
         if (count > ASG_FEW) {  // uniform
             int behind = 0;  // undecided in the tiles so far
@@ -833,7 +953,7 @@ __global__ __launch_bounds__(256) void assign_rest_kernel(const float *__restric
             for (int c0 = 0; c0 < count; c0 += 256) {  // uniform; the list shrinks in place
                 const int k = c0 + tid < count ? todo[c0 + tid] : -1;
                 __syncthreads();
-                if (k >= 0 && assign_marked(cells[i0 + k], cells_in_all, accumulate)) todo[atomicAdd(&nleft, 1)] = (uint16_t)k;
+                if (k >= 0 && assign_marked(cells[i0 + k], K, accumulate)) todo[atomicAdd(&nleft, 1)] = (uint16_t)k;
                 __syncthreads();
             }
             count = nleft;
@@ -842,9 +962,15 @@ __global__ __launch_bounds__(256) void assign_rest_kernel(const float *__restric
     if constexpr (!DEFINITION) return;
     auto store = [&](int k, int bc) { cells[i0 + k] = (cells[i0 + k] ^ ASG_MARK) + bc * scale; };
     const int few = d <= 4 ? ASG_RANGE : ASG_FEW;  // (a tile computes 16 components at least)
-    int k0 = 0;
+    int k0 = 0, listed = 0;
+    if (count > min(few, ASG_TM) && K <= ASG_COPIES_K) {  // uniform
+        listed = list_cells(*reinterpret_cast<AssignCopies *>(room), list, coarse, K, d);
+        if (listed) K = listed;
+        __syncthreads();
+    }
+    auto cell = [&](int k) { return listed ? (int)list[k] : k; };
     for (; count - k0 > few; k0 += ASG_TM) {  // uniform
-        assign_tile(s, coarse, K, d, x + i0 * ldx, ldx, [&](int k) { return k0 + k < count ? (int)todo[k0 + k] : -1; }, store);
+        assign_tile(s, coarse, K, d, x + i0 * ldx, ldx, [&](int k) { return k0 + k < count ? (int)todo[k0 + k] : -1; }, cell, store);
         __syncthreads();
     }
     double(&red_d)[16][4] = *reinterpret_cast<double(*)[16][4]>(s.cand_d);
@@ -860,7 +986,7 @@ __global__ __launch_bounds__(256) void assign_rest_kernel(const float *__restric
             bc[k] = 0x7fffffff;
         }
         for (int c = tid; c < K; c += 256) {
-            const float *cr = coarse + (size_t)c * d;
+            const float *cr = coarse + (size_t)cell(c) * d;
             double acc[4] = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll 4
             for (int t = 0; t < d; ++t) {
@@ -894,7 +1020,7 @@ __global__ __launch_bounds__(256) void assign_rest_kernel(const float *__restric
                     d0 = red_d[w][tid];
                     c0 = red_c[w][tid];
                 }
-            store(todo[k0 + tid], c0);
+            store(todo[k0 + tid], c0 == 0x7fffffff ? c0 : cell(c0));
         }
         __syncthreads();
     }

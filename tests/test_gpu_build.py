@@ -613,6 +613,64 @@ def test_ivf_assign_with_a_last_centroid_far_out(Q, d, K, n, last):
     assert np.array_equal(got, want * K + other)
 
 
+def _with_copies(kind, c, rng):
+    """Centroids of which most are copies of others."""
+    K = len(c)
+    i = np.arange(K)
+    if kind == "one":
+        return c[i * 0]
+    if kind == "last_differs":
+        return c[np.where(i == K - 1, 1, 0)]
+    if kind == "first_differs":
+        return c[np.where(i == 0, 1, 0)]
+    if kind == "alternating":
+        return c[i % 2]
+    if kind == "padded_in_front":
+        return c[np.where(i < K // 2, K // 2, i)]
+    if kind == "eight_times":
+        return c[i % max(1, K // 8)]
+    return c[rng.integers(0, min(K, 20), size=K)]  # any_order
+
+
+# (copies are looked for where more than 20 of a workgroup's vectors, or more than 128 of up to four components, are left to the definition; a
+# sample of 256 rows from 257 cells on, at most 65,536 cells, of which 4096 are listed)
+@pytest.mark.parametrize("d,K,n", [(16, 3, 300), (64, 256, 700), (128, 257, 5_000), (100, 700, 3_000), (2, 900, 2_000), (200, 300, 900),
+                                   (256, 290, 600), (64, 1024, 70_000), (8, 40_000, 300), (4, 65_537, 400), (17, 5_000, 600)])
+@pytest.mark.parametrize("kind", ["one", "last_differs", "first_differs", "alternating", "padded_in_front", "eight_times", "any_order"])
+def test_ivf_assign_with_copies_of_centroids(Q, d, K, n, kind):
+    """The lowest of equal cells, wherever the copies stand; two columns with both zeros, and rows of NaN that are copies."""
+    rng = np.random.default_rng(d + K)
+    first = rng.integers(-3, 4, size=(K, d)).astype(np.float32)
+    coarse = _with_copies(kind, first, rng)
+    if kind in ("alternating", "any_order"):
+        coarse[K // 3, 0] = coarse[K // 2, -1] = np.float32(-0.0)
+    if kind == "eight_times" and K > 100:
+        coarse[K // 8:K // 7] = np.nan
+    x = (coarse[rng.integers(0, K, size=n)] + rng.integers(-1, 2, size=(n, d))).astype(np.float32)
+    x = np.where(np.isnan(x), 0, x).astype(np.float32)
+    c = np.where(np.isnan(coarse), np.inf, coarse)
+    wanted = []
+    for xx in np.array_split(x.astype(np.float64), max(1, n * K // 20_000_000)):
+        cc = np.where(np.isinf(c), 0, c).astype(np.float64)
+        dist = (xx * xx).sum(1)[:, None] - 2 * xx @ cc.T + (cc * cc).sum(1)[None]  # whole numbers: exact
+        wanted.append(np.where(np.isinf(c).any(1)[None], np.inf, dist).argmin(1))
+    assert np.array_equal(Q.qadc_ivf_assign(to_gpu(coarse), to_gpu(x)).cpu().numpy(), np.concatenate(wanted))
+
+
+@pytest.mark.parametrize("d,K", [(128, 256), (64, 1024), (200, 300), (128, 4096)])
+@pytest.mark.parametrize("kind", ["one", "last_differs", "first_differs", "alternating", "padded_in_front", "eight_times", "any_order"])
+def test_ivf_assign_is_not_slowed_by_copies_of_centroids(Q, d, K, kind):
+    """Copies cost a search for them and the filter's passes in vain, not an exact pass over all cells (up to 37 times the usual)."""
+    import torch
+    from gpu_common import gpu_us
+    rng = np.random.default_rng(d)
+    coarse = (30 * rng.normal(size=(K, d))).astype(np.float32)
+    x = to_gpu((coarse[rng.integers(0, K, size=200_000)] + 18 * rng.normal(size=(200_000, d))).astype(np.float32))
+    usual = gpu_us(lambda c=to_gpu(coarse): Q.qadc_ivf_assign(c, x), reps=5)
+    us = gpu_us(lambda c=to_gpu(_with_copies(kind, coarse, rng)): Q.qadc_ivf_assign(c, x), reps=5)
+    assert us < 12 * usual, (us, usual)
+
+
 @pytest.mark.parametrize("d,K", [(128, 256), (64, 1024), (200, 300)])
 def test_ivf_assign_is_not_slowed_by_a_few_centroids(Q, d, K):
     """One stray centroid, one that is not finite, all of them twice: not much slower than without."""
