@@ -1178,3 +1178,39 @@ def test_batch_scan_by_decoded_codes(Q, monkeypatch, n, d, m, nq, R, nbins, kind
         found[-1] += (launches,)
     assert torch.equal(found[0][0], found[1][0]) and torch.equal(found[0][1], found[1][1])
     assert found[1][2] >= found[0][2] + 4, (found[0][2], found[1][2])  # its parts, and what is left
+
+
+def _in_runs(Q, means, d, m, n, run, seed):
+    """Codebooks, queries and the codes of n vectors of 64 clusters that arrive in runs of one cluster."""
+    import torch
+    g = torch.Generator(device="cuda:0")
+    g.manual_seed(seed)
+
+    def vectors(label):
+        return means[label] + 24 * torch.randn((len(label), d), generator=g, device="cuda:0")
+    random = lambda k: torch.randint(0, 64, (k,), generator=g, device="cuda:0")
+    cb = Q.qadc_pq_train(vectors(random(20_000)), m, 16, torch.arange(16, device="cuda:0"), 5)
+    label = random((n + run - 1) // run).repeat_interleave(run)[:n]
+    codes = torch.cat([Q.qadc_pq_encode(cb, vectors(label[s:s + 1_000_000])) for s in range(0, n, 1_000_000)])
+    return cb, vectors(random(256)), codes
+
+
+@pytest.mark.parametrize("n,d,m,R", [(36_000_000, 64, 16, 50), (40_000_000, 128, 32, 10)])
+def test_batch_search_of_a_database_in_runs_of_a_cluster(Q, n, d, m, R):
+    """The sample behind a batch's bounds looks at many places of the database: where vectors of a cluster lie side by side it
+    still holds some of every cluster, and the bounds are those of a database in any order."""
+    import torch
+    from gpu_common import gpu_us
+    g = torch.Generator(device="cuda:0")
+    g.manual_seed(m)
+    means = 48 + 32 * torch.randn((64, d), generator=g, device="cuda:0")
+    us = []
+    for run in (1, 20_000):
+        cb, queries, codes = _in_runs(Q, means, d, m, n, run, n)
+        if run > 1:  # the first codes are the same: so are the quantizers
+            codes[:1000] = first
+        first = codes[:1000].clone()
+        ws = Q.qadc_workspace_init(torch.empty((Q.qadc_workspace_bytes(Q.QADC_WS_SEARCH, n, m, 256, R),), dtype=torch.uint8,
+                                               device="cuda:0"))
+        us.append(gpu_us(lambda: Q.qadc_search(cb, queries, codes, R, 1000, workspace=ws), reps=3))
+    assert us[1] < 1.6 * us[0], us
