@@ -142,8 +142,10 @@ __global__ __launch_bounds__(64 * decoded_nw(B)) void scan_u8_decoded_kernel(
     auto order = [] { asm volatile("" ::: "memory"); };  // (a wavefront's LDS accesses are in the order of the program)
 
     for (int unit = part * NW + wave; unit < of.units; unit += parts * NW) {  // uniform over the wavefront
-        const int64_t c0 = of.from + (int64_t)unit * of.unit_codes;
-        const unsigned len = (unsigned)min((int64_t)of.unit_codes, of.to - c0);  // (below 2^24, and 2^29 bytes)
+        int64_t c0, c1;
+        decoded_unit(all, of, unit, c0, c1);
+        if (c0 >= c1) continue;  // (behind the end of the last block)
+        const unsigned len = (unsigned)(c1 - c0);  // (below 2^24, and 2^29 bytes)
         const uint8_t *unit_data = codes + c0 * B;
         // lane l reads code l of 64; v_permlane32_swap hands the words of the first and the last 32 to both halves
         auto fetch = [&](unsigned rel, unsigned (&w)[NK]) {
@@ -248,7 +250,8 @@ __global__ __launch_bounds__(64 * decoded_nw(B)) void scan_u8_decoded_kernel(
             return r;
         };
         // share g of G of the lookups of words w[]; the squares of a share come a block later
-        constexpr int SH = G > 1 ? G - 1 : 1;  // blocks with lookups
+        constexpr int SH = G - 1;  // blocks with lookups
+        static_assert(G > 1, "");
         int sq[2];
         auto lookup = [&](const unsigned (&w)[NK], v4i_t (&op)[NK], int g) {
 #pragma unroll
@@ -281,7 +284,6 @@ __global__ __launch_bounds__(64 * decoded_nw(B)) void scan_u8_decoded_kernel(
                 if (g > 0) square(a[S0 ^ 1], g - 1);
                 test(acc[(S0 * G + g + 1) & 1], g > 0 ? g - 1 : G - 1, g > 0 ? rel : rel - 32u);
             }
-            if (G == 1) square(a[S0 ^ 1], 0);
             leave_norm(S0 ^ 1);
         };
         fetch(0, cn);
@@ -423,30 +425,49 @@ constexpr int DECODED_MIN_LAST = 64;              // queries in the last set of 
 
 // The scan in parts, the bound tightened behind each but the last (the first one's is a sample's: R of some 8e5 codes, and the
 // share that passes falls 4 to 6 times with it; 1/16, 1/3 and the rest took as long, and cost 5 % more where the batch goes back).
-// Units: as few for every wavefront that the chip holds at once as leave them at 8192 codes (2048 in the first two parts, whose
-// bounds let more in), and the same number for each: four and what is left over, 73 M x 256, m = 16 1.73 -> 1.55 ms, 40 M x 384,
-// m = 32 3.69 -> 2.42 (there with more workgroups than the chip holds).  At least 512 codes.
+// A part is a stretch of every block of the database, not of the database: stored cluster by cluster, the first 64th of it bounds
+// the queries of one cluster (73 M codes of 8 bytes in runs of 20,000 of a cluster, 256 queries, R = 100, by the tightened bounds and
+// the one-hot products 35.5 ms, now 2.0; whole clusters one after the other, R = 10 5.2 ms for 100 M of 16 bytes, now 3.8).
+// Blocks and units: as many units for every wavefront that the chip holds at once, of about 8192 codes (2048 in the first two parts, whose
+// bounds let more in): four rounds and what is left over instead, 73 M x 256, m = 16 1.55 -> 1.73 ms, 40 M x 384, m = 32 2.42 -> 3.69 (there
+// with more workgroups than the chip holds); 976 blocks for 1024 wavefronts, 32 M x 256 1.11 -> 1.15.
 // Workgroups of a set: a CU holds one, an XCD's share is whole.
 static int decoded_wgs(int sets) { return std::max(256 / (8 * sets), 1) * 8; }
 
-static int decoded_parts(int B, int64_t n, int nq, int sets, DecodedPart (&parts)[DECODED_PARTS])
+static void decoded_parts(int B, int64_t n, int nq, int sets, DecodedLeft *all)
 {
-    const int64_t ends[DECODED_PARTS] = {n / 64, n / 12, n / 3, n};
     const int64_t waves = (int64_t)decoded_wgs(sets) * decoded_nw(B);  // of a set, that the chip holds at once
+    // a block for every wavefront, or for every second, third ... of them: a block's first part is a unit of 448 codes at least
+    const int64_t blocks = std::max<int64_t>(1, waves / std::max<int64_t>(1, ceil_div(waves, std::max<int64_t>(1, n / (64 * 448)))));
+    const int64_t block = ceil_div(ceil_div(n, blocks), 64) * 64;
+    all->n = n;
+    all->block = (int)block;
+    all->blocks = (int)ceil_div(n, block);
+    const int64_t ends[DECODED_PARTS] = {block / 64, block / 12, block / 3, block};
     int64_t from = 0;
     int k = 0, word = 0;
     for (int64_t e : ends) {
-        const int64_t to = e == n ? n : e / 64 * 64;
+        const int64_t to = e / 64 * 64;
         if (to <= from) continue;
-        const int64_t rounds = ceil_div(to - from, waves * (k < 2 ? 2048 : 8192));
-        const int64_t unit = std::max<int64_t>(512, ceil_div(ceil_div(to - from, rounds * waves), 64) * 64);
-        parts[k] = {from, to, (int)unit, (int)ceil_div(to - from, unit), word,
-                    (unsigned)std::min<int64_t>((to - from) / 64 * nq / 64 * DECODED_PASS[B / 16][k > 0], UINT32_MAX / 2)};
-        word += (int)ceil_div(parts[k].units, 32);
+        const int64_t codes = (to - from) * all->blocks;
+        // units per block: what takes a wavefront the shortest
+        const int64_t len = to - from, most = k < 2 ? 2560 : 10240, few = ceil_div(len, most);
+        const int64_t many = std::max(few, std::min(len / 448, few + 4 + waves / all->blocks));
+        int per = 0, unit = 0;
+        int64_t least = INT64_MAX;
+        for (int64_t p = few; p <= many; ++p) {
+            const int64_t u = ceil_div(ceil_div(len, p), 64) * 64, time = ceil_div(p * all->blocks, waves) * (u + 128);
+            if (time < least) { least = time; per = (int)p; unit = (int)u; }
+        }
+        all->parts[k] = {(int)from, (int)to, unit, per, per * all->blocks, word,
+                         (unsigned)std::min<int64_t>(codes / 64 * nq / 64 * DECODED_PASS[B / 16][k > 0], UINT32_MAX / 2)};
+        word += (int)ceil_div(all->parts[k].units, 32);
         from = to;
         ++k;
     }
-    return k;
+    all->nparts = k;
+    all->pitch = word;
+    all->queries = 32 * DECODED_G;
 }
 
 // Room a batch takes: decoded tables, operands and scales, and the bits of `words` words per set.
@@ -458,12 +479,13 @@ static size_t decoded_room(int m, int nq, int sets, int words)
 bool decoded_pays(int B, int64_t n, int nq, int cap, int R, const DecodedBatch &db)
 {
     if (knobs().tiled_decoded == 0 || (B != 8 && B != 16) || db.d > 8 * B) return false;
+    const int sets = (int)ceil_div(nq, 32 * DECODED_G);
     const bool sizes = n >= DECODED_MIN_N && n >= R * DECODED_N_PER_R[B / 16] && cap >= DECODED_MIN_BINS &&
                        (nq - 1) % (32 * DECODED_G) >= DECODED_MIN_LAST - 1;
     if (!sizes && knobs().tiled_decoded < 0) return false;
-    DecodedPart parts[DECODED_PARTS];
-    const int sets = (int)ceil_div(nq, 32 * DECODED_G), k = decoded_parts(B, n, nq, sets, parts);
-    return decoded_room(2 * B, nq, sets, parts[k - 1].word + (int)ceil_div(parts[k - 1].units, 32)) <= db.room_bytes;
+    DecodedLeft all = {};
+    decoded_parts(B, n, nq, sets, &all);
+    return decoded_room(2 * B, nq, sets, all.pitch) <= db.room_bytes;
 }
 
 template <int B>
@@ -478,10 +500,7 @@ static DecodedLeft run_decoded(const TiledPlan &t, const uint8_t *codes, int64_t
     constexpr int G = DECODED_G;
     const int sets = (int)ceil_div(nq, 32 * G);
     DecodedLeft all = {};
-    all.queries = 32 * G;
-    all.nparts = decoded_parts(B, n, nq, sets, all.parts);
-    const DecodedPart &last = all.parts[all.nparts - 1];
-    all.pitch = last.word + (int)ceil_div(last.units, 32);
+    decoded_parts(B, n, nq, sets, &all);
     left = passed + DECODED_PARTS;
     all.bits = left;
     all.passed = passed;

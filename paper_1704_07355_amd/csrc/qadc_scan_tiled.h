@@ -47,22 +47,29 @@ struct DecodedBatch {
 };
 bool decoded_pays(int B, int64_t n, int nq, int cap, int R, const DecodedBatch &db);
 // Does run_tiled_scan take that route?
-struct TiledPlan;
 bool scans_decoded(const TiledPlan &t, int64_t n, int nq, int cap, int R, const uint8_t *qluts16, const DecodedBatch *decoded);
-// A part of its scan: units of unit_codes codes from code `from` up to `to`; `word`: where their bits start.
+// The database lies in blocks of `block` codes.  A part of the scan takes codes from .. to - 1 of every block (the last one may end before
+// that), in `per_block` units of unit_codes codes; `word`: where their bits start.
 constexpr int DECODED_PARTS = 4;
 struct DecodedPart {
-    int64_t from, to;
-    int unit_codes, units, word;
+    int from, to, unit_codes, per_block, units, word;
     unsigned limit;
 };
 // What it has left: for set s (of `queries` queries) and a part's unit u, bit u % 32 of word s * pitch + word + u / 32; and
 // everything behind a part of which more pairs passed (passed[part]) than its limit.  Null: nothing was done.
 struct DecodedLeft {
     const unsigned *bits, *passed;
-    int pitch, queries, nparts;
+    int64_t n;
+    int pitch, queries, nparts, block, blocks;
     DecodedPart parts[DECODED_PARTS];
 };
+// The codes c0 .. c1 - 1 of a unit (none where c1 <= c0).
+__device__ __forceinline__ void decoded_unit(const DecodedLeft &all, const DecodedPart &of, int unit, int64_t &c0, int64_t &c1)
+{
+    const int z = unit / of.per_block, at = of.from + (unit - z * of.per_block) * of.unit_codes;
+    c0 = (int64_t)z * all.block + at;
+    c1 = min(all.n, c0 + min(of.unit_codes, of.to - at));
+}
 // Has it stopped behind one of the first k parts?
 __device__ __forceinline__ bool decoded_stopped(const DecodedLeft &all, int k)
 {

@@ -683,33 +683,36 @@ __global__ __launch_bounds__(64) void scan_u8_left_kernel(
         if (k < left.nparts && word >= left.parts[k].word) of = left.parts[k];
     for (unsigned units = left.bits[set * QW / left.queries * left.pitch + word] >> first & 15u; units != 0; units &= units - 1) {  // uniform
         const int unit = 32 * (word - of.word) + first + __ffs((int)units) - 1;
-        const int64_t c0 = of.from + (int64_t)unit * of.unit_codes;
-        mfma_scan_codes<B, G, true>(sh, c0, min(of.to, c0 + of.unit_codes), set, unit % regions, codes, nq, (unsigned)cap_i, qluts,
-                                    taus, ws, ws_stride, countsA_off, listsA_off, flags);
+        int64_t c0, c1;
+        decoded_unit(left, of, unit, c0, c1);
+        mfma_scan_codes<B, G, true>(sh, c0, c1, set, unit % regions, codes, nq, (unsigned)cap_i, qluts, taus, ws, ws_stride,
+                                    countsA_off, listsA_off, flags);
         __syncthreads();
     }
 }
 
-// The codes behind the part at which scan_u8_decoded_kernel stopped.
+// The codes behind the part at which scan_u8_decoded_kernel stopped, those of every block in `pieces` pieces.
 template <int B, int G>
 __global__ __launch_bounds__(64) void scan_u8_rest_kernel(
-    const uint8_t *__restrict__ codes, DecodedLeft left, int64_t n, int64_t chunk, int nq, int cap_i,
+    const uint8_t *__restrict__ codes, DecodedLeft left, int pieces, int regions, int nq, int cap_i,
     const uint8_t *__restrict__ qluts, const unsigned *__restrict__ taus, char *__restrict__ ws,
     size_t ws_stride, size_t countsA_off, size_t listsA_off, unsigned *__restrict__ flags)
 {
     __shared__ MfmaShared<G> sh;
     constexpr int QW = MfmaShared<G>::QW;
-    int set, gc;
-    tiled_group_and_chunk((nq + QW - 1) / QW, set, gc);
-    if (!decoded_stopped(left, left.nparts)) return;  // uniform
-    int64_t rest = n;
+    int set, piece;
+    tiled_group_and_chunk((nq + QW - 1) / QW, set, piece);
+    const int z = piece / pieces, j = piece - z * pieces;
+    if (z >= left.blocks || !decoded_stopped(left, left.nparts)) return;  // uniform
+    int rest = left.block;
     for (int k = left.nparts - 1; k >= 0; --k)
         if (left.passed[k] > left.parts[k].limit) rest = left.parts[k].to;
-    const int64_t c0 = max(rest, (int64_t)gc * chunk);
-    const int64_t c1 = min(n, (int64_t)(gc + 1) * chunk);
+    const int len = ((left.block - rest + pieces - 1) / pieces + 63) / 64 * 64;
+    const int64_t c0 = (int64_t)z * left.block + rest + (int64_t)j * len;
+    const int64_t c1 = min(min(left.n, (int64_t)(z + 1) * left.block), c0 + len);
     if (c0 >= c1) return;  // uniform
-    mfma_scan_codes<B, G, true>(sh, c0, c1, set, gc, codes, nq, (unsigned)cap_i, qluts, taus, ws, ws_stride, countsA_off,
-                                listsA_off, flags);
+    mfma_scan_codes<B, G, true>(sh, c0, c1, set, piece % regions, codes, nq, (unsigned)cap_i, qluts, taus, ws, ws_stride,
+                                countsA_off, listsA_off, flags);
 }
 
 template <int B, int G>
@@ -721,8 +724,11 @@ static int launch_tiled_mfma(const TiledPlan &t, const uint8_t *codes, int64_t n
     dim3 grid((unsigned)ceil_div(nq, 32 * G) * gc8);
     if constexpr (B == 8 || B == 16) {
         if (left.bits) {
-            launch(QADC_PROF_SCAN, (scan_u8_rest_kernel<B, G>), grid, dim3(64), 0, st, codes, left, n, t.chunk, nq, cap, qluts, taus,
-                   ws, ws_stride, countsA_off, listsA_off, flags);
+            // (about as many pieces as the scan of the whole database has chunks)
+            const int pieces = (int)ceil_div(t.GC, left.blocks);
+            launch(QADC_PROF_SCAN, (scan_u8_rest_kernel<B, G>),
+                   dim3((unsigned)ceil_div(nq, 32 * G) * ((unsigned)ceil_div((int64_t)left.blocks * pieces, 8) * 8u)), dim3(64), 0, st,
+                   codes, left, pieces, t.GC, nq, cap, qluts, taus, ws, ws_stride, countsA_off, listsA_off, flags);
             launch(QADC_PROF_SCAN, (scan_u8_left_kernel<B, G>), dim3((unsigned)(ceil_div(nq, 32 * G) * left.pitch * 8)), dim3(64), 0, st,
                    codes, left, t.GC, nq, cap, qluts, taus, ws, ws_stride, countsA_off, listsA_off, flags);
             return QADC_OK;

@@ -1180,6 +1180,99 @@ def test_batch_scan_by_decoded_codes(Q, monkeypatch, n, d, m, nq, R, nbins, kind
     assert found[1][2] >= found[0][2] + 4, (found[0][2], found[1][2])  # its parts, and what is left
 
 
+def _by_both_routes(Q, monkeypatch, search, forced):
+    """What `search` returns by the one-hot products alone, the same by decoded codes (forced, or as the sizes have it), and the
+    launches of the scan either way."""
+    found = []
+    for knob in ("0", "1" if forced else None):
+        if knob:
+            monkeypatch.setenv("QADC_TILED_DECODED", knob)
+        else:
+            monkeypatch.delenv("QADC_TILED_DECODED")
+        Q.qadc_profile_enable(True)
+        found.append(search())
+        found[-1] += (Q.qadc_profile_read(Q.QADC_PROF_SCAN)[1],)
+        Q.qadc_profile_enable(False)
+    return found
+
+
+@pytest.mark.parametrize("n,d,m,nq,R,nbins,order", [
+    (40_000_003, 64, 16, 100, 50, 255, "any"),      # 8-byte codes: twelve wavefronts, a last set of 100
+    (36_000_001, 128, 32, 200, 30, 255, "any"),     # 16-byte codes, a last set of 72
+    (33_000_037, 64, 16, 256, 40, 255, "clusters"),  # a database of one cluster after the other
+    (36_000_001, 128, 32, 128, 100, 127, "any")])   # coarse steps: the one-hot products go on behind a later part (forced)
+def test_batch_scan_by_decoded_codes_over_many_units(Q, monkeypatch, n, d, m, nq, R, nbins, order):
+    """Several units for every wavefront, in every part, by the rule on sizes; the oracle's results for a few queries and the one-hot
+    products' for all."""
+    import torch
+    from oracle import cref
+    g = torch.Generator(device="cuda:0")
+    g.manual_seed(n + m)
+    means = 48 + 32 * torch.randn((64, d), generator=g, device="cuda:0")
+
+    def vectors(label):
+        return means[label] + 24 * torch.randn((len(label), d), generator=g, device="cuda:0")
+    cb = Q.qadc_pq_train(vectors(torch.randint(0, 64, (20_000,), generator=g, device="cuda:0")), m, 16,
+                         torch.arange(16, device="cuda:0"), 5)
+    label = torch.randint(0, 64, (n,), generator=g, device="cuda:0")
+    if order == "clusters":
+        label[1000:] = label[1000:].sort().values
+    codes = torch.empty((n, m // 2), dtype=torch.uint8, device="cuda:0")
+    for s in range(0, n, 1_000_000):
+        Q.qadc_pq_encode(cb, vectors(label[s:s + 1_000_000]), out=codes[s:s + 1_000_000])
+    queries = vectors(label[torch.randint(0, n, (nq,), generator=g, device="cuda:0")])
+    qluts = torch.empty((nq, m, 16), dtype=torch.uint8, device="cuda:0")
+    by_onehot, by_codes = _by_both_routes(Q, monkeypatch, lambda: Q.qadc_search(cb, queries, codes, R, 1000, nbins, qluts_out=qluts),
+                                          nbins < 224)
+    assert torch.equal(by_onehot[0], by_codes[0]) and torch.equal(by_onehot[1], by_codes[1])
+    assert by_onehot[2] == 2 and by_codes[2] == 7, (by_onehot[2], by_codes[2])  # four parts, what is left, the rest; queries redone
+    some = [0, nq // 2, nq - 1]
+    wi, wd = cref.scan_topk_u8(codes.cpu().numpy(), qluts[some].cpu().numpy(), R, nbins)
+    assert np.array_equal(idx_np(by_codes[0])[some], wi) and np.array_equal(by_codes[1].cpu().numpy()[some], wd)
+
+
+@pytest.mark.parametrize("m,nq,smallest", [(16, 200, True), (32, 128, True), (32, 1000, False), (16, 1111, False)])
+def test_batch_scan_by_decoded_codes_in_small_workspaces_and_several_launches(Q, monkeypatch, m, nq, smallest):
+    """Longer chunks and fewer queries at a time where the workspace holds no more; more queries than one launch takes."""
+    import torch
+    from gpu_common import smallest_workspace
+    g = torch.Generator(device="cuda:0")
+    g.manual_seed(nq)
+    n, d, R = 1_000_003, 2 * m, 40
+    means = 48 + 32 * torch.randn((16, d), generator=g, device="cuda:0")
+    vectors = lambda k: means[torch.randint(0, 16, (k,), generator=g, device="cuda:0")] + 24 * torch.randn((k, d), generator=g, device="cuda:0")
+    cb = Q.qadc_pq_train(vectors(5000), m, 16, torch.arange(16, device="cuda:0"), 5)
+    codes, queries = Q.qadc_pq_encode(cb, vectors(n)), vectors(nq)
+    nbytes = None
+    if smallest:
+        nbytes, _ = smallest_workspace(Q, lambda ws: Q.qadc_search(cb, queries, codes, R, 200, workspace=ws))
+
+    def search():
+        ws = Q.qadc_workspace_init(torch.empty((nbytes,), dtype=torch.uint8, device="cuda:0")) if smallest else None
+        return Q.qadc_search(cb, queries, codes, R, 200, workspace=ws)
+    by_onehot, by_codes = _by_both_routes(Q, monkeypatch, search, True)
+    assert torch.equal(by_onehot[0], by_codes[0]) and torch.equal(by_onehot[1], by_codes[1])
+    assert by_codes[2] > by_onehot[2] and (smallest or by_onehot[2] > 2), (by_onehot[2], by_codes[2])
+
+
+def test_batch_scan_by_decoded_codes_of_one_cluster_after_the_other(Q, monkeypatch):
+    """Every part of the scan holds some of every cluster: its bounds tighten for all queries, and it is no slower than the one-hot
+    products (it was where a part was a stretch of the database)."""
+    import torch
+    from gpu_common import gpu_us
+    g = torch.Generator(device="cuda:0")
+    g.manual_seed(3)
+    n, d, m, R = 32_000_000, 128, 32, 10
+    means = 48 + 32 * torch.randn((64, d), generator=g, device="cuda:0")
+    cb, queries, codes = _in_runs(Q, means, d, m, n, n // 64, 3)
+    ws = Q.qadc_workspace_init(torch.empty((Q.qadc_workspace_bytes(Q.QADC_WS_SEARCH, n, m, 256, R),), dtype=torch.uint8, device="cuda:0"))
+    us = {}
+    for knob in ("0", "1"):
+        monkeypatch.setenv("QADC_TILED_DECODED", knob)
+        us[knob] = gpu_us(lambda: Q.qadc_search(cb, queries, codes, R, 1000, workspace=ws), reps=3)
+    assert us["1"] < us["0"], us
+
+
 def _in_runs(Q, means, d, m, n, run, seed):
     """Codebooks, queries and the codes of n vectors of 64 clusters that arrive in runs of one cluster."""
     import torch
