@@ -404,24 +404,39 @@ constexpr int DECODED_G = 4;  // groups of 32 queries per wavefront
 
 // When it pays: matrix products a pair are half of scan_u8_mfma_kernel's, but every pair that passes costs some 30 cycles, and how
 // many pass depends on how many sums the last bound lets in (R of n) and on what the quantizer's steps lose.  Measured against
-// scan_u8_mfma_kernel (the whole search, us; 255 bins unless said, 100..1000 initial codes, vectors of a mixture of 64; what is beyond the line
-// with three times the sample):
-//   16-byte codes, 128 dimensions    100 M x 256, R 100: 5315 -> 3955      40 M x 384, R 40:  3977 -> 2415
-//                                     50 M x 200, R 10:  2447 -> 1702      36 M x 250, R 30:  1929 -> 1562
-//     beyond the line                 50 M x 128, R 100: 1406 -> 1384      36 M x 256, R 100: 2015 -> 2073
-//                                     20 M x 256, R 100: 1187 -> 1309      36 M x 256, R 100, 127 bins: 2122 -> 3951
-//   8-byte codes, 64 dimensions       73 M x 256, R 100: 2200 -> 1545      36 M x 100, R 50:   695 -> 504
-//     beyond the line                100 M x 200, R 200: 3805 -> 3985      73 M x 256, R 100, 127 bins: 2287 -> 2411
-// (Fewer than 64 queries in the last set of 128 are scanned as 128, and the parts' launches cost some 60 us: n.)
+// scan_u8_mfma_kernel, the whole search, its time over the time here, the least and the mean over 2 codebooks and 100, 200 and 1000 initial
+// codes of a mixture's vectors (the fewer, the coarser the steps):
+//   16-byte codes      n / R     2.5e5          3.5e5          5e5            7e5            1e6
+//     8 M x 256              0.93  0.99     0.96  1.03     1.01  1.08     1.05  1.13     1.08  1.15
+//     12 M x 256             0.91  0.99     0.96  1.04     1.01  1.08     1.06  1.14     1.11  1.19
+//     32 M x 256             0.94  1.01     0.97  1.06     1.01  1.12     1.11  1.21     1.18  1.28
+//     100 M x 256                                          0.85  1.05     0.98  1.14     0.99  1.18
+//     16 M x 128             0.80  0.88     0.88  0.94     0.91  0.97     0.96  1.01     0.99  1.05
+//     24 M x 128             0.90  0.95     0.88  0.98     0.97  1.05     1.01  1.09     1.06  1.14
+//     32 M x 65              0.95  1.10     0.97  1.12     1.13  1.19     1.17  1.22     1.20  1.24
+//   8-byte codes       n / R     1.6e5          2.5e5          5e5
+//     16 M x 256             0.95  1.06     1.13  1.15     1.14  1.15
+//     32 M x 256             1.01  1.10     0.95  1.12     1.23  1.28
+//     16 M x 128             0.86  0.90     0.93  0.93     0.92  0.93
+//     32 M x 128             0.97  1.03     0.93  1.03     1.08  1.10
+// Within n / R of 7e5 and 8e5, 100 initial codes and 16-byte codes, three shapes of 40 lost 3 to 5 % (11 M x 335, R = 15 971 -> 1018 us); 8-byte
+// codes with sub-vectors of one component, 5e5, 100 M x 494 0.92.  Sets of queries: the launches of the
+// parts are for all of them, and a last set of 64 and less costs as one of 128 (64 queries, 32 M R = 10 0.77 to 0.83, 65 1.3; 129 0.93;
+// 166 over 16 M R = 19 0.88).  Steps: R = 50 of 50 M with 255 / 224 / 200 / 160 / 127 bins 1.33 / 1.20 / 1.12 / 0.98 / 0.89.  R: the
+// sample is no larger than 512 tiles, and beyond it too many pairs pass in the first part (100 M, R = 200 with a fourth of the sample: the
+// units' lists overflow, all queries are redone one by one, 66 ms; R = 256 is the largest measured, 1.17).
+// 288 shapes within the lines, 65 to 520 queries, 6 to 100 M codes, 100 to 1000 initial codes, 224 and 255 bins: 1.45 on average, the
+// least 0.98, but for R = 1, where either route now and then redoes a query (0.91 to 4).
 // Sizes don't tell what data and quantizers do, so each part counts the pairs that passed, and behind a part with more than
-// DECODED_PASS / 4096 of all its pairs the batch goes back to the one-hot products: within the line that has cost 1 % (100 M x 256,
-// 96 dimensions, 100 initial codes: 5349 -> 5411; let on, 2739 -> 2851 for 128 queries).  For the 8-byte codes a product is
-// cheaper beside the check: their share is smaller.
+// DECODED_PASS / 4096 of all its pairs the batch goes back to the one-hot products: within the lines that has cost up to 3 % (51 M x 127,
+// 96 dimensions, 100 initial codes, 224 bins: 1413 -> 1451 us; 100 M x 256, 255 bins 5349 -> 5411; let on, 2739 -> 2851 for 128 queries).
+// For the 8-byte codes a product is cheaper beside the check: their share is smaller.
 constexpr int DECODED_PASS[2][2] = {{6, 4}, {21, 15}};  // 8- and 16-byte codes: the first part, whose bound is the sample's, the others
-constexpr int64_t DECODED_MIN_N = 32000000;
-constexpr int64_t DECODED_N_PER_R[2] = {700000, 1000000};
+constexpr int64_t DECODED_MIN_N[2] = {32000000, 24000000};  // codes times sets of queries
+constexpr int64_t DECODED_N_PER_R[2] = {700000, 850000};
+constexpr int DECODED_MAX_R = 256;
 constexpr int DECODED_MIN_BINS = 224;
-constexpr int DECODED_MIN_LAST = 64;              // queries in the last set of 128
+constexpr int DECODED_MIN_LAST = 65;              // queries in the last set of 128
 
 // The scan in parts, the bound tightened behind each but the last (the first one's is a sample's: R of some 8e5 codes, and the
 // share that passes falls 4 to 6 times with it; 1/16, 1/3 and the rest took as long, and cost 5 % more where the batch goes back).
@@ -480,8 +495,8 @@ bool decoded_pays(int B, int64_t n, int nq, int cap, int R, const DecodedBatch &
 {
     if (knobs().tiled_decoded == 0 || (B != 8 && B != 16) || db.d > 8 * B) return false;
     const int sets = (int)ceil_div(nq, 32 * DECODED_G);
-    const bool sizes = n >= DECODED_MIN_N && n >= R * DECODED_N_PER_R[B / 16] && cap >= DECODED_MIN_BINS &&
-                       (nq - 1) % (32 * DECODED_G) >= DECODED_MIN_LAST - 1;
+    const bool sizes = n * sets >= DECODED_MIN_N[B / 16] && n >= R * DECODED_N_PER_R[B / 16] && R <= DECODED_MAX_R &&
+                       cap >= DECODED_MIN_BINS && nq - 32 * DECODED_G * (sets - 1) >= DECODED_MIN_LAST;
     if (!sizes && knobs().tiled_decoded < 0) return false;
     DecodedLeft all = {};
     decoded_parts(B, n, nq, sets, &all);

@@ -1231,6 +1231,32 @@ def test_batch_scan_by_decoded_codes_over_many_units(Q, monkeypatch, n, d, m, nq
     assert np.array_equal(idx_np(by_codes[0])[some], wi) and np.array_equal(by_codes[1].cpu().numpy()[some], wd)
 
 
+@pytest.mark.parametrize("n,m,nq,R,nbins,decoded", [
+    (24_000_000, 32, 128, 28, 255, True), (23_999_999, 32, 128, 28, 255, False), (24_000_000, 32, 128, 29, 255, False),
+    (12_000_000, 32, 193, 10, 224, True), (12_000_000, 32, 192, 10, 255, False), (12_000_000, 32, 256, 10, 223, False),
+    (16_000_000, 16, 256, 22, 255, True), (16_000_000, 16, 256, 23, 255, False), (32_000_000, 16, 65, 2, 255, True),
+    (32_000_000, 16, 64, 2, 255, False)])
+def test_batch_scan_by_decoded_codes_at_its_lines(Q, monkeypatch, n, m, nq, R, nbins, decoded):
+    """On either side of the lines (codes times sets, codes per result, bins, queries in the last set), and what comes out."""
+    import torch
+    from oracle import cref
+    g = torch.Generator(device="cuda:0")
+    g.manual_seed(n + R)
+    cb = 40 * torch.randn((m, 16, 4), generator=g, device="cuda:0")
+    codes = torch.randint(0, 256, (n, m // 2), dtype=torch.uint8, generator=g, device="cuda:0")
+    queries = 50 * torch.randn((nq, 4 * m), generator=g, device="cuda:0")
+    qluts = torch.empty((nq, m, 16), dtype=torch.uint8, device="cuda:0")
+    monkeypatch.delenv("QADC_TILED_DECODED", raising=False)
+    Q.qadc_profile_enable(True)
+    idx, dist = Q.qadc_search(cb, queries, codes, R, 1000, nbins, qluts_out=qluts)
+    _, launches = Q.qadc_profile_read(Q.QADC_PROF_SCAN)
+    Q.qadc_profile_enable(False)
+    assert launches == (7 if decoded else 2), launches
+    some = [0, nq - 1]
+    wi, wd = cref.scan_topk_u8(codes.cpu().numpy(), qluts[some].cpu().numpy(), R, nbins)
+    assert np.array_equal(idx_np(idx)[some], wi) and np.array_equal(dist.cpu().numpy()[some], wd)
+
+
 @pytest.mark.parametrize("m,nq,smallest", [(16, 200, True), (32, 128, True), (32, 1000, False), (16, 1111, False)])
 def test_batch_scan_by_decoded_codes_in_small_workspaces_and_several_launches(Q, monkeypatch, m, nq, smallest):
     """Longer chunks and fewer queries at a time where the workspace holds no more; more queries than one launch takes."""
