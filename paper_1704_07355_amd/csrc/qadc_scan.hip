@@ -682,9 +682,10 @@ static int dispatch_seed_u8(const ScanPlan &p, const uint8_t *codes, int64_t n,
         // tiles 0.42 ms of sampling, 512 tiles 0.22 ms and 0.07 ms more in the scan, 256 tiles 0.12 and 0.21)
         int tiles = knobs().seed_wgs > 0 ? p.seed_wgs : std::min(p.seed_wgs, 512);
         // Where the decoded codes are scanned, in parts, the first part finds a better bound than the sample's at a third of
-        // its price (512 / 256 / 192 / 128 tiles, us per call: 100 M x 256, m = 32, d = 128, R = 100 4095 / 4014 / 3977, and
-        // beyond it too many pairs pass; 50 M x 200, R = 10 1881 / 1802 / 1790 / 1761; 73 M x 256, m = 16, d = 64 1890 / 1769 / 1734).
-        // (8000 codes per key of R: a part's units have room for 128 pairs within the bound.)
+        // its price: 192 tiles, but 8000 codes for every one of the R.  us per call with 96 / 128 / 192 / 256 / 384 / 512 tiles: 36 M x 256,
+        // m = 32, R = 10 1213 / 1217 / 1239 / 1270 / 1305 / 1347 (fewer find fewer clusters of a database that is not in random order);
+        // 100 M x 256, R = 100 3991 / 3956 / 3955 / 3969 / 4016 / 4055 (391 here: 4012), R = 200 67,771 / 66,534 / 4904 / 4640 / 4599 /
+        // 4608: with 2000 codes for each more than the 128 pairs pass that a unit of the first part has room for, and the lists overflow.
         if (knobs().seed_wgs <= 0 && scans_decoded(p.t, n, nq, cap, R, p.wide ? nullptr : qluts, decoded))
             tiles = std::min(tiles, std::max(192, (int)ceil_div(8000ll * R, 1024 * cpt)));
         // Every query is sampled, and a fourth of a database of a few million codes took as long as its scan: no more than 4e8
