@@ -252,6 +252,21 @@ def run_batched(args):
     ms_per_step = e0.elapsed_time(e1) / args.steps
     pairs = n * nb / (ms_per_step * 1e-3)
 
+    def scan_launches_unfiltered():
+        """Launches of a batch's scan with the filter of decoded codes switched off: fewer where the batch takes it."""
+        before = os.environ.get("QADC_TILED_DECODED")
+        os.environ["QADC_TILED_DECODED"] = "0"
+        Q.qadc_profile_enable(True)
+        step(args.warmup + args.steps - 1)
+        torch.cuda.synchronize()
+        count = Q.qadc_profile_read(Q.QADC_PROF_SCAN)[1]
+        Q.qadc_profile_enable(False)
+        del os.environ["QADC_TILED_DECODED"]
+        if before is not None:
+            os.environ["QADC_TILED_DECODED"] = before
+        step(args.warmup + args.steps - 1)  # (the outputs compared below are the timed route's)
+        return count
+
     roofline = kernels = None
     if not args.no_profile:
         Q.qadc_profile_enable(True)
@@ -265,9 +280,20 @@ def run_batched(args):
         Q.qadc_profile_enable(False)
         ach = n * nb * m / (ms_scan * 1e-3) / 1e12
         kernel = batch_scan_kernel(n, m, nb)
-        if kernel == "scan_u8_mfma_kernel" and launches > 2:  # filtered by decoded codes, in parts
-            kernel = "scan_u8_decoded_kernel (+ what it leaves, and the redo launch)"
-        if kernel == "scan_u8_mfma_kernel":
+        filtered = kernel == "scan_u8_mfma_kernel" and launches > scan_launches_unfiltered()
+        if filtered:
+            # A pair's bound is a product of 4 m int8 numbers (m tables of up to four components), for whole sets of 128 queries; the
+            # sums themselves are formed for the pairs that pass.
+            ops = n * (-(-nb // 128) * 128) * 4 * m * 2 / (ms_scan * 1e-3) / 1e12
+            roofline = {"bound": "mfma", "kernel": "scan_u8_decoded_kernel (four parts; what they leave, and the redo launch)",
+                        "achieved": round(ops, 1), "peak": MFMA_I8_PEAK_TOPS, "unit": "T int8 ops/s",
+                        "frac": round(ops / MFMA_I8_PEAK_TOPS, 4),
+                        "note": "4 m int8 multiply-adds per (code, query) pair give a lower bound of its sum; bound by instruction "
+                                "issue (lookups of the decoded components and tests beside the products), "
+                                "profiles/scan_u8_decoded_config3.md",
+                        "lookup_adds_replaced": round(ach, 2), "lookup_adds_replaced_unit": "T/s", "traffic": None,
+                        "scan_ms": round(ms_scan, 3), "launches_timed": launches}
+        elif kernel == "scan_u8_mfma_kernel":
             # The method's work is m lookup-adds per (code, query) pair (Alg. 2); the ceiling quoted for
             # it is the vector ALU's byte-lane rate, whatever unit executes it.  This kernel forms the
             # sums as one-hot int8 products on the sparse matrix instruction: every lookup-add is a
@@ -316,7 +342,7 @@ def run_batched(args):
         "warmup": args.warmup, "ms_per_step": round(ms_per_step, 4), "higher_is_better": True,
         "scaling": "weak", "vs_baseline": None, "dtype": "u8", "data": "synthetic",
         "config": {"workload": "config 3: d=128 mixture, PQ m=%d x 4-bit, N=%d codes, batches of %d queries "
-                   "through qadc_search (a wavefront scans each code for 64 queries), R=%d, init=%d"
+                   "through qadc_search, R=%d, init=%d"
                    % (m, n, nb, R, init), "n": n, "m": m, "R": R, "init": init, "batch": nb},
         "gcodes_per_s_per_query": round(pairs / nb / 1e9, 2),
         "roofline": roofline, "kernels": kernels, "cpu_baseline": cpu, "database_build_s": round(t_build, 2)})
@@ -951,7 +977,7 @@ def run_build(args):
         cpu = {"value": round(ns / secs, 1), "unit": "vectors/s", "cores": 1, "kind": "oracle",
                "sample": "first %d vectors, NumPy oracle ivf_build against K=%d cells" % (ns, K),
                "seconds": round(secs, 2), "gpu_matches_oracle": same}
-    flops = 3.0 * n * K * d                       # a subtraction and a fused multiply-add per component
+    flops = 2.0 * n * K * d                       # the filter's binary16 products; what they leave open is measured in float32, float64
     out = {"metric": "vectors/s (inverted index built from raw vectors: assign + group + encode)",
            "value": round(n / ((phase["assign"] + phase["group"] + phase["encode"]) * 1e-3), 1),
            "unit": "vectors/s", "n_gpus": 1, "steps": args.steps, "warmup": args.warmup,
@@ -960,8 +986,9 @@ def run_build(args):
            "config": {"workload": "index build: n=%d vectors d=%d, K=%d coarse centroids, m=%d x 4-bit residual codes"
                                   % (n, d, K, m), "n": n, "d": d, "K": K, "m": m},
            "phase_ms": {k: round(v, 3) for k, v in phase.items()},
-           "roofline": {"bound": "alu", "kernel": "ivf_assign_kernel", "achieved": round(flops / (phase["assign"] * 1e-3) / 1e12, 2),
-                        "peak": 78.6, "unit": "TFLOP/s", "frac": round(flops / (phase["assign"] * 1e-3) / 78.6e12, 4),
+           "roofline": {"bound": "mfma", "kernel": "assign_filter_kernel (and what it leaves)",
+                        "achieved": round(flops / (phase["assign"] * 1e-3) / 1e12, 2),
+                        "peak": 2500.0, "unit": "TFLOP/s", "frac": round(flops / (phase["assign"] * 1e-3) / 2500e12, 4),
                         "traffic": None},
            "layout_gb_per_s": {"pack": round(2 * codes.numel() / (phase["pack"] * 1e-3) / 1e9, 1),
                                "unpack": round(2 * codes.numel() / (phase["unpack"] * 1e-3) / 1e9, 1)},
