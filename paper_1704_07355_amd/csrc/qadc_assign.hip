@@ -23,7 +23,7 @@
 // minima are those of the 32 cells before, the conversion that of the next tile, and all is one block of code.  1.05 M vectors,
 // d = 128: 0.25 ms + 0.22 ms per 1024 centroids = 1.2 PFLOP/s; the first part is the vectors, read twice, and the groups measured
 // at the end: groups of 16 cells, 8 KiB of centroids per vector from L2, made it 0.48 ms (K = 4096: 1.42 ms -> 1.13; d = 64
-// 0.80 -> 0.67; 500 k, d = 256 2.24 -> 1.60; 200 k, d = 96, K = 1000 0.147 -> 0.094; 37.5 ms in float64).  Vectors and centroids
+// 0.80 -> 0.67; 500 k, d = 256 2.24 -> 1.49; 200 k, d = 96, K = 1000 0.147 -> 0.094; 37.5 ms in float64).  Vectors and centroids
 // of one Gaussian, where a few in a hundred vectors have rivals within the margin: 1.75 -> 1.38.  The minima of the same 32 cells and
 // the conversion behind the products: 0.25 ms per 1024 centroids.  Not faster: the order of instructions given by hand
 // (1.23 ms for 1.13), workgroups of 256 threads, two per compute unit (1.58).

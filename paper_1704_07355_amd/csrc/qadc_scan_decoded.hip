@@ -2,11 +2,11 @@
 // work with half of its matrix instructions and a quarter of its table operands, for 4-bit codes whose sub-vectors have up to
 // four components, where the codebooks and the queries are at hand (qadc_search).
 //
-// Bound: the matrix units, at the clock that int8 products of arbitrary operands are given, with the lookups of decoded
-// components and the tests of results issued beside them.  100 M codes of 16 bytes x 256 queries, a mixture's vectors: the whole
-// search 5.31 ms with scan_u8_mfma_kernel, 3.96 ms here (4 parts; 4e-3 of the pairs pass the first one, 4e-4 the last);
-// 73 M codes of 8 bytes x 256 queries 2.20 -> 1.55 ms.  A wavefront has 307 cycles of a SIMD for a block (two a SIMD: 214 registers;
-// three for 8-byte codes: 156), 33 vector, 4 matrix, 8 LDS and 7 scalar instructions: issue, not the products (36 % busy).
+// Bound: instruction issue.  A block of 32 codes x 32 queries takes a SIMD 303 cycles (16-byte codes): 128 of them in the matrix unit
+// (42 % busy; 38 % over all four parts), with 32 vector, 7.5 LDS and 5.7 scalar instructions beside its products (lookups of decoded
+// components, tests of results); either of the two wavefronts that 214 registers leave (three for 8-byte codes: 156) issues in 43 % of its cycles
+// and waits to issue in 33 %.  100 M codes of 16 bytes x 256 queries, a mixture's vectors: the whole search 5.31 ms with
+// scan_u8_mfma_kernel, 4.00 here (4e-3 of the pairs pass the first part, 4e-4 the last); 73 M codes of 8 bytes x 256 queries 2.12 -> 1.46.
 
 #include <algorithm>
 #include <type_traits>
